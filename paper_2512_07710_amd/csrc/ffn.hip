@@ -15,15 +15,16 @@
 // The product is taken as (features x tokens): in the 32x32 accumulator layout a lane then
 // owns ONE token column and 16 feature rows, so the activation scale is one scalar per lane
 // and sub-tile, and the 128-wide amax of the epilogue is a lane-local reduction plus one
-// cross-half shuffle and one exchange between the two waves that share a token.
+// cross-half shuffle and one exchange between the four waves that share a token.
 // Activation scales are K-block major ([K/128][rows]): the 32 lanes of a half-wave read 32
 // consecutive floats of one plane.
 //
-// Eight waves per block: wave (wt, wf) owns 64 tokens x 128 staged weight rows (2 x 4
-// sub-tiles): 6 operand sub-tiles feed 8 MFMA pairs.  Waves whose 64 tokens lie beyond the
-// expert's last row skip their MFMAs, so a ragged tail costs a fraction of a tile.
+// Eight waves per block: wave (wt, wf) owns 64 staged weight rows x half of the tile's groups of 32
+// tokens (2 x 4 sub-tiles in a full tile: 6 operand sub-tiles feed 8 MFMA pairs).  The two waves of
+// a SIMD, w and w + 4, take the two halves, so a tile of n groups costs every SIMD n/8 of a full
+// tile's matrix work.  The K loop is instantiated for 1 to 4 groups per wave.
 //
-// GEMM1: staged rows of wave wf are [64 gate rows | 64 up rows] of the same features;
+// GEMM1: staged rows of wave wf are [32 gate rows | 32 up rows] of the same features;
 //        epilogue h = silu(g)*u, re-quantised to e4m3 with one scale per (row, 128 features).
 // GEMM2: staged rows are 256 consecutive output features; epilogue: fp32 rows, turned through LDS so
 //        that every row is stored in contiguous 256-byte pieces.
@@ -34,6 +35,7 @@ namespace {
 
 typedef int v8i __attribute__((ext_vector_type(8)));
 typedef float v16f __attribute__((ext_vector_type(16)));
+typedef int v4i __attribute__((ext_vector_type(4)));
 
 constexpr int KB = QBLOCK;                        // K bytes per stage (= one scale block)
 constexpr int W_ROWS = 256;                       // staged weight rows per block
@@ -82,23 +84,19 @@ __global__ __launch_bounds__(256) void build_work(const int32_t* __restrict__ of
     const int base = (s_tiles[e] - nt) * n_ft;
     for (int idx = tid; idx < nt * n_ft; idx += 256) {
         const int f = idx / nt, i = idx - f * nt;
-        // Down projection: experts with three or more tiles whose remainder is at most 128 rows get full tiles
-        // plus one short tile: a short tile keeps half of the block's waves out of the matrix work and,
-        // measured, costs 0.7 to 0.9 of a full one, less than making every tile of the expert ragged.
-        // Otherwise, and always in the gate/up projection, the expert's G = ceil(cnt/64) groups of 64 rows (the
-        // share of one wave pair) are dealt out evenly: tile i covers groups [i*G/nt, (i+1)*G/nt).  The tiles
-        // that share a weight tile then advance in step and fetch it once, and only the expert's last group is partly
-        // filled: splitting the ROWS evenly instead leaves a partly filled group in every tile, whose wave pair does a
-        // full group's matrix work (3 % of the gate/up projection at 896..1152 rows per expert: the kernel runs at
-        // the power cap, so matrix work that is thrown away costs time even where it hides behind other waves).
-        // A tile that runs faster than the tiles it shares a weight tile with does not pay: it runs ahead and the
-        // weight tile is fetched twice.  Measured for a remainder of at most 64 rows cut off as a NARROW tile (a fifth
-        // of a full tile's time by itself): gate/up projection 8 % slower at 248..264 rows per expert, 3 % slower at
-        // 896..1152.  Narrow tiles therefore arise only where an expert has at most 64 rows altogether.
-        const bool short_tail = blockIdx.y == 1 && nt >= 3 && cnt - (nt - 1) * TOK_TILE <= TOK_TILE / 2;
-        const int G = (cnt + 63) / 64;
-        const int lo = short_tail ? i * TOK_TILE : min(cnt, 64 * (int)((int64_t)i * G / nt));
-        const int hi = short_tail ? min(cnt, lo + TOK_TILE) : min(cnt, 64 * (int)((int64_t)(i + 1) * G / nt));
+        // The expert's G = ceil(cnt/32) groups of 32 rows are dealt out evenly: tile i covers groups [i*G/nt, (i+1)*G/nt).
+        // The tiles that share a weight tile are then within one group of each other: they advance nearly in step and
+        // fetch it once, only the expert's last group is partly filled, and a tile's matrix time follows its height.
+        // With the groups of 64 of a layout whose short tiles left whole waves idle (so that every tile cost the time
+        // of a full one) the gate/up projection took 1.98 ms at 1030 rows per expert and takes 1.82, at 258 rows
+        // 0.81 -> 0.71 ms, at 896..1152 rows 1.94 -> 1.87 ms (d = 7168, F = 2048, 64 experts; 258: d = 5120, F = 1536,
+        // 128 experts); at full tiles nothing changes.  The down projection is 6 % faster at 258 rows, 3 % at 960, and
+        // 3..5 % slower at 1030..1152; cutting its remainder off as one short tile measures the same as dealing evenly.
+        // A remainder of at most 64 rows as a NARROW tile does not pay in the gate/up projection: it runs ahead of the
+        // tiles it shares the weight tile with, and the weight tile is fetched twice (8 % slower at 248..264 rows).
+        const int G = (cnt + 31) / 32;
+        const int lo = min(cnt, 32 * (int)((int64_t)i * G / nt));
+        const int hi = min(cnt, 32 * (int)((int64_t)(i + 1) * G / nt));
         Work w;
         w.expert = e;
         w.row0 = start + lo;
@@ -121,6 +119,10 @@ __device__ inline void dma16(uint32_t lds_addr, uint32_t voff, const void* sbase
 // The matrix instructions are written as volatile asm so that they stay exactly where the
 // source puts them: the schedule below relies on it.  T = A*B (first K half) and T += A*B.
 __device__ inline void mfma_first(v16f& t, const v8i& a, const v8i& b) {
+    // "+v", although t is only written: the product registers then stay where they are through the whole K loop
+    asm volatile("v_mfma_f32_32x32x64_f8f6f4 %0, %1, %2, 0" : "+v"(t) : "v"(a), "v"(b) : "memory");
+}
+__device__ inline void mfma_new(v16f& t, const v8i& a, const v8i& b) {
     asm volatile("v_mfma_f32_32x32x64_f8f6f4 %0, %1, %2, 0" : "=&v"(t) : "v"(a), "v"(b) : "memory");
 }
 __device__ inline void mfma_acc(v16f& t, const v8i& a, const v8i& b) {
@@ -130,14 +132,244 @@ __device__ inline void mfma_acc(v16f& t, const v8i& a, const v8i& b) {
 // values feeding x cannot move below it.
 #define PIN(x) asm volatile("" : "+v"(x))
 
-// the 32 K-bytes a lane feeds to one 32x32x64 MFMA, from a row's two swizzled 16-byte chunks
-__device__ inline v8i lds_operand(const uint8_t* row, uint32_t o0, uint32_t o1) {
-    const uint4 lo = *reinterpret_cast<const uint4*>(row + o0);
-    const uint4 hi = *reinterpret_cast<const uint4*>(row + o1);
-    v8i r;
-    r[0] = lo.x; r[1] = lo.y; r[2] = lo.z; r[3] = lo.w;
-    r[4] = hi.x; r[5] = hi.y; r[6] = hi.z; r[7] = hi.w;
+// the 32 K-bytes a lane feeds to one 32x32x64 MFMA, from its row's two swizzled 16-byte chunks at LDS addresses c0, c1
+typedef __attribute__((address_space(3))) const v4i* lds_v4i;
+__device__ inline v8i lds_operand(uint32_t c0, uint32_t c1, int plus) {
+    const v4i lo = *reinterpret_cast<lds_v4i>(c0 + plus), hi = *reinterpret_cast<lds_v4i>(c1 + plus);
+    return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+}
+
+// ------------------------------------------------------------------ operand copies
+// What one wave brings of every K block: staged weight rows [32w, 32w+32) and staged activation rows [32w, 32w+32).
+struct Feed {
+    uint32_t lds_rows;                                         // LDS address of this wave's rows in ring slot 0
+    uint32_t w_off[2], x_off[4];                               // per lane: byte offset of its 16-byte chunk in copies 0,1 / 0..3
+    const uint8_t* w_base[2];                                  // weight copies 0,1 and copies 2,3 (the same lane offsets again)
+    const uint8_t* x_base;
+    int x_copies;                                              // activation copies that carry rows of the tile
+};
+
+// Copy J of K block kb goes out if J < n.  The condition is a scalar branch inside the asm: the compiler's control flow
+// stays a straight line, which the register allocation of the K loop depends on (with C++ conditions around the copies
+// the loop spills).
+#define COPY_IF(J, N, LDS, VOFF, SBASE)                                                                    \
+    asm volatile("s_cmp_gt_i32 %3, %4\n\ts_cbranch_scc0 .Lskip%=\n\ts_mov_b32 m0, %0\n\ts_nop 0\n\t"     \
+                 "global_load_lds_dwordx4 %1, %2\n.Lskip%=:"                                              \
+                 :: "s"(LDS), "v"(VOFF), "s"(SBASE), "s"(N), "n"(J) : "memory", "scc")
+// a < b ? -1 : 0 for wave-uniform values, in a scalar register whatever the compiler makes of the comparison
+__device__ __forceinline__ int all_ones_if_less(int a, int b) {
+    int r;
+    asm("s_cmp_lt_i32 %1, %2\n\ts_cselect_b32 %0, -1, 0" : "=s"(r) : "s"(a), "s"(b) : "scc");
     return r;
+}
+template <int J>
+__device__ __forceinline__ void copy_w1(const Feed& f, int kb, int wslot, int n) {
+    COPY_IF(J, n, f.lds_rows + wslot * W_TILE + J * 8 * KB, f.w_off[J & 1], f.w_base[J >> 1] + (size_t)kb * KB);
+}
+template <int J>
+__device__ __forceinline__ void copy_x1(const Feed& f, int kb, int xslot, int n) {
+    COPY_IF(J, n, f.lds_rows + X_RING + xslot * X_TILE + J * 8 * KB, f.x_off[J], f.x_base + (size_t)kb * KB);
+}
+#undef COPY_IF
+__device__ __forceinline__ void copy_w(const Feed& f, int kb, int wslot, int n = 4) {
+    copy_w1<0>(f, kb, wslot, n);
+    copy_w1<1>(f, kb, wslot, n);
+    copy_w1<2>(f, kb, wslot, n);
+    copy_w1<3>(f, kb, wslot, n);
+}
+__device__ __forceinline__ void copy_x(const Feed& f, int kb, int xslot) {
+    copy_x1<0>(f, kb, xslot, f.x_copies);
+    copy_x1<1>(f, kb, xslot, f.x_copies);
+    copy_x1<2>(f, kb, xslot, f.x_copies);
+    copy_x1<3>(f, kb, xslot, f.x_copies);
+}
+
+// ------------------------------------------------------------------ K loop of a full tile
+struct Tile {
+    uint32_t lds0;                                             // LDS address of ring slot 0
+    int nkb;
+    uint32_t a_row, b_row;                                     // LDS byte offset of the lane's row in weight / activation slot 0
+    int l32, half;
+    int row, n_rows;                                           // the lane's first token row; rows of a scale plane
+    const uint8_t* act_s;
+    const float *sa, *sb;                                      // weight scales of the wave's gate / up rows (or both the same)
+};
+
+// One wave: 64 staged weight rows (sub-tiles s = 0, 1) x NTS groups of 32 tokens, 2*NTS sub-tile products per K block.
+//
+// Pipeline.  K block kb of the weight tile lives in ring slot kb % 3, of the activation tile in slot kb % 2.  Each wave
+// passes ONE barrier per K block, placed after its last LDS read of block kb (before its last token group's two
+// products).  Behind that barrier block kb+1 is complete in LDS and the slots of block kb are free.  The copies that
+// refill them follow: activation block kb+2, then weight block kb+3 - always in that order, so that "all but the newest
+// four copies have landed" is exactly "everything but the weight block two steps ahead".  They go out one behind each
+// matrix instruction (activations over the last two products, weights over the first two of the next step; NTS = 1 has
+// no products to spare and sends the weights at the end of the step), so that the wave does not sit at the issue of a
+// copy while the queue drains (in two bursts of four the gate/up projection ran 4 % slower).  The last two products
+// already fetch the first operands of block kb+1 into registers: the weight operands a[s] stay for a whole step, the
+// token operands go through two register sets in turn (three for NTS = 3, so that a step always starts with set 0).
+template <int NTS, bool GATED>
+__device__ __forceinline__ void k_loop(const Tile& t, const Feed& f, v16f (&acc)[2][4]) {
+    const int nkb = t.nkb;
+    // LDS byte address of a lane's first operand chunk (ks = 0, j = 0) relative to a ring slot; chunk (ks, j) is that
+    // address with bits 6 and 4 flipped by ks and j (the swizzle is an exclusive or of the chunk number)
+    const uint32_t off00 = (uint32_t)((t.half * 2) ^ (t.l32 & 7) ^ ((t.l32 >> 3) & 1)) << 4;
+    const uint32_t a00 = t.lds0 + t.a_row + off00, b00 = t.lds0 + t.b_row + off00;
+    auto read_ops = [&](v8i (&o)[2], uint32_t at, int plus) {
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) o[ks] = lds_operand((at ^ (ks * 64)), (at ^ (ks * 64 + 16)), plus);
+    };
+    // activation scales of this lane's token columns (K-block major: one plane per K block), by buffer loads whose
+    // range check covers the token columns past the end of the plane (they read 0 and are never stored): one address
+    // register for all groups.  Issued as asm; the data is only touched behind a vmcnt wait.
+    // The lanes of a pair (l, l+32) serve the same token: the lower one fetches the even groups' scales and the upper
+    // one the odd groups', and a half-wave swap hands them round (half the loads, half the registers in flight).
+    constexpr int NXS = (NTS + 1) / 2;
+    const uint32_t xs_at = 4u * (uint32_t)(t.row + t.half * 32);
+    const size_t plane = (size_t)t.n_rows * 4;
+    float xs_n[NXS], xs[NXS * 2];
+#pragma unroll
+    for (int i = 0; i < NXS; ++i) xs_n[i] = 0.f;
+    auto xs_load = [&](int kb, int go) {                       // scalar condition inside the asm, as in COPY_IF
+        const uint64_t base = (uint64_t)(uintptr_t)(t.act_s + (size_t)kb * plane);
+        v4i rsrc;
+        rsrc[0] = (int)(uint32_t)base;
+        rsrc[1] = (int)(uint32_t)((base >> 32) & 0xFFFFu);
+        rsrc[2] = (int)(uint32_t)min(plane, (size_t)0xFFFFFFFFu);
+        rsrc[3] = 0x00020000;                                  // raw 32-bit data
+#pragma unroll
+        for (int i = 0; i < NXS; ++i)
+            asm volatile("s_cmp_lg_u32 %3, 0\n\ts_cbranch_scc0 .Lskip%=\n\tbuffer_load_dword %0, %1, %2, 0 offen offset:%4\n.Lskip%=:"
+                         : "+v"(xs_n[i]) : "v"(xs_at), "s"(rsrc), "s"(go), "n"(i * 256) : "memory", "scc");
+    };
+    auto xs_take = [&]() {
+#pragma unroll
+        for (int i = 0; i < NXS; ++i)
+            asm volatile("v_mov_b32 %0, %2\n\tv_mov_b32 %1, %2\n\ts_nop 1\n\tv_permlane32_swap_b32 %0, %1"
+                         : "=&v"(xs[2 * i]), "=&v"(xs[2 * i + 1]) : "v"(xs_n[i]));
+    };
+    xs_load(0, 1);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    xs_take();
+    if (nkb > 1) {
+        xs_load(1, 1);
+        copy_x(f, 1, 1);
+        copy_w(f, 1, 1);
+    }
+    if (nkb > 2) copy_w(f, 2, 2);
+    constexpr int NB = NTS == 3 ? 3 : 2;                      // register sets of token operands
+    v8i a[2][2], b[NB][2];
+    read_ops(a[0], a00, 0);
+    read_ops(b[0], b00, 0);
+    read_ops(a[1], a00, 32 * KB);
+    float wsc[2];                                              // weight scales of the block being folded, in scalar registers
+    asm volatile("s_load_dword %0, %2, 0x0\n\ts_load_dword %1, %3, 0x0\n\ts_waitcnt lgkmcnt(0)"
+                 : "=&s"(wsc[0]), "=&s"(wsc[1]) : "s"(t.sa), "s"(t.sb) : "memory");
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+        for (int ts = 0; ts < NTS; ++ts)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[s][ts][r] = 0.f;
+    v16f T[2];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) T[1][r] = 0.f;                // folded once, with scale 0, before its first product
+    T[0] = T[1];
+    float sc_cur = 0.f, sc_pend = 0.f;                         // scale being folded with; of the product still held in T[1]
+
+    auto scale = [&](float x, float w) {                       // w * x at this place (see PIN)
+        float r;
+        asm volatile("v_mul_f32 %0, %1, %2" : "=v"(r) : "s"(w), "v"(x));
+        return r;
+    };
+    // fold product (S, TS), held in T[S], into its accumulator
+#define FOLD(S, TS, SCV)                                                                        \
+    do {                                                                                        \
+        const float scv_ = (SCV);                                                               \
+        PIN(T[S]);                                                                              \
+        _Pragma("unroll") for (int r = 0; r < 16; ++r)                                          \
+            acc[S][TS][r] = fmaf(scv_, T[S][r], acc[S][TS][r]);                                 \
+        PIN(acc[S][TS]);                                                                        \
+    } while (0)
+
+    int wslot = 0;                                             // ring slot of weight block kb
+    int kb = 0;
+    do {                                                       // (K >= 128: at least one block)
+        const int wnext = (wslot == NW_BUF - 1) ? 0 : wslot + 1;
+        const int wprev = (wslot == 0) ? NW_BUF - 1 : wslot - 1;             // slot of block kb-1 = of block kb+2
+        const uint32_t sX = b00 + (kb & 1) * X_TILE;                         // block kb
+        const uint32_t sWn = a00 + wnext * W_TILE;                           // block kb+1
+        const uint32_t sXn = b00 + ((kb & 1) ^ 1) * X_TILE;                  // block kb+1
+        const int kn = min(kb + 1, nkb - 1);
+        float wsc_n[2];                                        // weight scales of block kb+1
+        const int more = all_ones_if_less(kb + 2, nkb);        // is there a block kb+2?
+        const int nx = f.x_copies & more;                      // copies of activation block kb+2
+        const int nw = 4 & more & all_ones_if_less(0, kb);     // copies of weight block kb+2 (the prologue sent block 2)
+        // 2*NTS sub-tile products, two MFMAs each.  The 16 scale-FMAs of product i-1 sit behind the
+        // second MFMA of product i: by then its result has left the matrix pipe (two more MFMAs
+        // have been issued since), and the vector ALU works in the shadow of the MFMA just issued.
+#pragma unroll
+        for (int i = 0; i < 2 * NTS; ++i) {
+            const int ts = i >> 1, s = i & 1;
+            const int bi = ts % NB, bnext = ts + 1 < NTS ? (ts + 1) % NB : NTS == 1 ? 1 : 0;
+            const bool last2 = i == 2 * NTS - 2, last = i == 2 * NTS - 1;
+            if (last2) {
+                // all of this wave's reads of block kb have been issued; wait for them and for the
+                // copies that must be complete (all of them in the last two steps), then meet the other waves
+                asm volatile("s_waitcnt vmcnt(4) lgkmcnt(0)\n\ts_cmp_lg_u32 %0, 0\n\ts_cbranch_scc1 .Lmore%=\n\t"
+                             "s_waitcnt vmcnt(0)\n.Lmore%=:" :: "s"(more) : "memory", "scc");
+                __builtin_amdgcn_s_barrier();
+                asm volatile("" ::: "memory");
+            }
+            mfma_first(T[s], a[s][0], b[bi][0]);
+            // one copy behind every matrix instruction: weight block kb+2 over products 0 and 1
+            if (NTS > 1 && i == 0) copy_w1<0>(f, kb + 2, wprev, nw);
+            if (NTS > 1 && i == 1) copy_w1<2>(f, kb + 2, wprev, nw);
+            if (last) copy_x1<2>(f, kb + 2, kb & 1, nx);
+            if (s == 0 && !last2) read_ops(b[bnext], sX, (ts + 1) * 32 * KB);
+            if (last2) {
+                read_ops(b[bnext], sXn, 0);
+                copy_x1<0>(f, kb + 2, kb & 1, nx);
+            }
+            if (i == (NTS > 2 ? 2 : 0)) {
+                // issued by hand, behind operand reads that are not waited for until two products later (a scalar load in
+                // flight turns the next wait for an LDS read into a wait for everything); complete at the barrier
+                asm volatile("s_load_dword %0, %2, 0x0\n\ts_load_dword %1, %3, 0x0"
+                             : "=&s"(wsc_n[0]), "=&s"(wsc_n[1]) : "s"(t.sa + kn), "s"(t.sb + kn) : "memory");
+            }
+            mfma_acc(T[s], a[s][1], b[bi][1]);
+            if (NTS > 1 && i == 0) copy_w1<1>(f, kb + 2, wprev, nw);
+            if (NTS > 1 && i == 1) copy_w1<3>(f, kb + 2, wprev, nw);
+            if (last2) copy_x1<1>(f, kb + 2, kb & 1, nx);
+            if (last) copy_x1<3>(f, kb + 2, kb & 1, nx);
+            if (i == 0) FOLD(1, NTS - 1, sc_pend);
+            else {
+                const int ps = (i - 1) & 1, pts = (i - 1) >> 1;
+                if (GATED || ps == 0) sc_cur = scale(xs[pts], wsc[GATED ? ps : 0]);
+                FOLD(ps, pts, sc_cur);
+            }
+            if (last2) read_ops(a[0], sWn, 0);
+            if (last) {
+                sc_pend = GATED ? scale(xs[NTS - 1], wsc[1]) : sc_cur;
+                xs_take();                                     // block kb+1: landed before the barrier above
+                if (NTS == 1) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // (its barrier came before the load)
+                asm volatile("s_mov_b32 %0, %2\n\ts_mov_b32 %1, %3" : "=&s"(wsc[0]), "=&s"(wsc[1]) : "s"(wsc_n[0]), "s"(wsc_n[1]));
+                read_ops(a[1], sWn, 32 * KB);
+                xs_load(kb + 2, more);
+                if (NTS == 1) {
+                    copy_w(f, kb + 3, wslot, 4 & all_ones_if_less(kb + 3, nkb));
+                    b[0][0] = b[1][0];
+                    b[0][1] = b[1][1];
+                }
+            }
+        }
+        wslot = wnext;
+    } while (++kb < nkb);
+    // the last product: wait out the matrix pipe, then fold it
+    asm volatile("s_nop 15\n\ts_nop 15\n\ts_nop 7" ::: "memory");
+    FOLD(1, NTS - 1, sc_pend);
+#undef FOLD
 }
 
 // ------------------------------------------------------------------ GEMM kernel
@@ -183,7 +415,7 @@ __global__ __launch_bounds__(NTHREADS, 1) void ffn_gemm(const uint8_t* __restric
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l32 = lane & 31, half = lane >> 5;
-    const int wt = wave >> 1, wf = wave & 1;                   // token group (64 rows), weight-row half
+    const int wt = wave >> 2, wf = wave & 3;                   // token half, weight-row quarter (64 rows)
     const int nkb = K / KB;
     const int nblk_out = NOUT / QBLOCK;
 
@@ -191,88 +423,45 @@ __global__ __launch_bounds__(NTHREADS, 1) void ffn_gemm(const uint8_t* __restric
     //      [32w, 32w+32) of every K block, 4 + 4 instructions of 8 rows each; lane i -> row i/8,
     //      LDS chunk slot i%8 which receives global chunk slot ^ (row & 7) ^ ((row >> 3) & 1): with that
     //      swizzle the 32-row x 16-byte operand reads below touch all 64 LDS banks evenly.
-    //      Staged weight row r: GATED: features f0 + (r/128)*64 + r%64, gate (Wa) if (r/64)%2 == 0 else up (Wb).
+    //      Staged weight row r: GATED: features f0 + (r/64)*32 + r%32, gate (Wa) if (r/32)%2 == 0 else up (Wb).
     //      NARROW tiles (at most 64 rows, see below): wave w's 32 staged rows are 32 consecutive features of the tile
     //      (down projection) or, GATED, [16 gate rows | 16 up rows] of features f0 + 16w .. 16w+15.
     const bool narrow = wk.nrows <= NARROW_ROWS;               // block-uniform
-    const uint8_t* w_base[2];                                  // wave-uniform: matrix of copy instructions 0,1 and 2,3
-    uint32_t w_off[4], x_off[4];
+    // A wave whose features all lie beyond NOUT (down projection, NOUT an odd multiple of 128: feature tile half empty)
+    // copies the last 32 features again; they are multiplied and not stored.
+    Feed feed;
     {
         const int sub = lane >> 3, cslot = lane & 7;
-        const size_t we = (size_t)e * NOUT * (size_t)K;
-        if (GATED && narrow) {
-            w_base[0] = Wa + we;
-            w_base[1] = Wb + we;
-        } else {
-            w_base[0] = w_base[1] = ((GATED && ((wave >> 1) & 1)) ? Wb : Wa) + we;
-        }
+        const int f_wave = GATED ? (narrow ? f0 + wave * 16 : f0 + (wave >> 1) * 32) : min(f0 + wave * 32, NOUT - 32);
+        const size_t w0 = ((size_t)e * NOUT + f_wave) * (size_t)K;
+        const bool split = GATED && narrow;                    // copies 0,1 gate rows and 2,3 up rows of the same features
+        feed.w_base[0] = ((GATED && !narrow && (wave & 1)) ? Wb : Wa) + w0;
+        feed.w_base[1] = split ? Wb + w0 : feed.w_base[0] + (size_t)16 * K;
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const int r = wave * 32 + j * 8 + sub;
-            int f = GATED ? (narrow ? f0 + wave * 16 + ((j * 8 + sub) & 15) : f0 + (r >> 7) * 64 + (r & 63)) : f0 + r;
-            f = min(f, NOUT - 1);
-            w_off[j] = (uint32_t)f * (uint32_t)K + ((cslot ^ (r & 7) ^ ((r >> 3) & 1)) << 4);
+            const uint32_t chunk = (cslot ^ (r & 7) ^ ((r >> 3) & 1)) << 4;
+            if (j < 2) feed.w_off[j] = (uint32_t)(j * 8 + sub) * (uint32_t)K + chunk;
             const int p = min(wk.row0 + r, row_end - 1);      // rows past the tile repeat its last row
             const int src = GATHER ? (int)min((uint32_t)perm[p] / (uint32_t)fan, (uint32_t)(n_tok - 1)) : p - wk.row0;
-            x_off[j] = (uint32_t)src * (uint32_t)K + ((cslot ^ (r & 7) ^ ((r >> 3) & 1)) << 4);
+            feed.x_off[j] = (uint32_t)src * (uint32_t)K + chunk;
         }
     }
-    const uint8_t* x_base = GATHER ? act : act + (size_t)wk.row0 * K;
+    feed.x_base = GATHER ? act : act + (size_t)wk.row0 * K;
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t*)smem;
-    const uint32_t lds_rows = lds0 + wave * 32 * KB;           // this wave's rows inside a tile buffer
+    feed.lds_rows = lds0 + wave * 32 * KB;                     // this wave's rows inside a tile buffer
 
-    auto issue_w = [&](int kb, int wslot) {
-        const uint32_t dst = lds_rows + wslot * W_TILE;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) dma16(dst + j * 8 * KB, w_off[j], w_base[j >> 1] + (size_t)kb * KB);
-    };
-    auto issue_w1 = [&](int kb, int wslot, int j) {
-        const uint32_t dst = lds_rows + wslot * W_TILE;
-        dma16(dst + j * 8 * KB, w_off[j], w_base[j >> 1] + (size_t)kb * KB);
-    };
-    // 8-row activation copies that lie wholly beyond the expert's last row are not issued at all
-    // (a ragged last tile then moves only the rows it has); wave-uniform
-    const int x_copies = __builtin_amdgcn_readfirstlane(max(0, min(4, (row_end - wk.row0 - wave * 32 + 7) / 8)));
-    // the skip is a scalar branch inside the asm: the compiler's control flow stays a straight line
-#define X_COPY(KBLK, XSLOT, J)                                                                                  \
-    asm volatile("s_cmp_gt_i32 %3, %4\n\ts_cbranch_scc0 .Lskipx%=\n\ts_mov_b32 m0, %0\n\ts_nop 0\n\t"           \
-                 "global_load_lds_dwordx4 %1, %2\n.Lskipx%=:"                                                   \
-                 :: "s"(lds_rows + X_RING + (XSLOT) * X_TILE + (J) * 8 * KB), "v"(x_off[J]),                    \
-                    "s"(x_base + (size_t)(KBLK) * KB), "s"(x_copies), "n"(J) : "memory", "scc")
-    auto issue_x = [&](int kb, int xslot) {
-        X_COPY(kb, xslot, 0);
-        X_COPY(kb, xslot, 1);
-        X_COPY(kb, xslot, 2);
-        X_COPY(kb, xslot, 3);
-    };
+    // 8-row activation copies that lie wholly beyond the tile's last row are not issued at all
+    // (a ragged tile then moves only the rows it has); wave-uniform
+    feed.x_copies = __builtin_amdgcn_readfirstlane(max(0, min(4, (row_end - wk.row0 - wave * 32 + 7) / 8)));
 
     // ---- weight scales of this wave's rows (wave-uniform -> scalar loads)
-    const int blk_a = GATED ? wk.ft : min(wk.ft * 2 + (narrow ? wave >> 2 : wf), nblk_out - 1);
+    const int blk_a = GATED ? wk.ft : min(wk.ft * 2 + (narrow ? wave >> 2 : wf >> 1), nblk_out - 1);
     const float* sa_e = sa + ((size_t)e * nblk_out + blk_a) * nkb;
     const float* sb_e = GATED ? sb + ((size_t)e * nblk_out + blk_a) * nkb : sa_e;
 
-    const bool wave_active = wk.row0 + wt * 64 < row_end;      // wave-uniform
-
-    v16f acc[4][2];
-#pragma unroll
-    for (int s = 0; s < 4; ++s)
-#pragma unroll
-        for (int ts = 0; ts < 2; ++ts)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[s][ts][r] = 0.f;
-
-    // Pipeline.  K block kb of the weight tile lives in ring slot kb % 3, of the activation tile in
-    // slot kb % 2.  Each wave passes ONE barrier per K block, placed after its last LDS read of block
-    // kb (before sub-tile product 6 of 8).  Behind that barrier block kb+1 is complete in LDS and the
-    // slots of block kb are free.  The copies that refill them follow: activation block kb+2, then
-    // weight block kb+3 - always in that order, so that "all but the newest four copies have landed" is
-    // exactly "everything but the weight block two steps ahead".  They go out one behind each matrix
-    // instruction (activations over products 6 and 7, weights over products 0 and 1 of the next step),
-    // so that the wave does not sit at the issue of a copy while the queue drains (in two bursts of four
-    // the gate/up projection ran 4 % slower).  Products 6 and 7 already fetch the first operands of
-    // block kb+1 into registers.
-    issue_x(0, 0);
-    issue_w(0, 0);
+    copy_x(feed, 0, 0);
+    copy_w(feed, 0, 0);
     if (narrow) {
         // ---- NARROW tile: at most 64 rows.  In the layout above only the two waves of token group 0 would
         //      multiply, alone on their SIMDs, and such a tile costs 0.7 of a full one.  Here all eight waves work:
@@ -280,14 +469,9 @@ __global__ __launch_bounds__(NTHREADS, 1) void ffn_gemm(const uint8_t* __restric
         //      32x32 products, four matrix instructions per K block), so the matrix work is spread over every SIMD
         //      and the tile runs at the speed its weight tile streams in.  Same rings, same copy order, same
         //      barrier per K block as the full tiles; nothing is overlapped by hand - the copies are the bound.
-        uint32_t offk[2][2];
-#pragma unroll
-        for (int ks = 0; ks < 2; ++ks)
-#pragma unroll
-            for (int j = 0; j < 2; ++j)
-                offk[ks][j] = (uint32_t)(((ks * 4 + half * 2 + j) ^ (l32 & 7) ^ ((l32 >> 3) & 1)) << 4);
-        const uint32_t a_row = (uint32_t)(wave * 32 + l32) * KB;
-        const uint32_t b_row = (uint32_t)(X_RING + l32 * KB);
+        const uint32_t off00 = (uint32_t)((half * 2) ^ (l32 & 7) ^ ((l32 >> 3) & 1)) << 4;
+        const uint32_t a00 = lds0 + (uint32_t)(wave * 32 + l32) * KB + off00;
+        const uint32_t b00 = lds0 + (uint32_t)(X_RING + l32 * KB) + off00;
         uint32_t xs_i[2];
 #pragma unroll
         for (int ts = 0; ts < 2; ++ts) xs_i[ts] = 4u * (uint32_t)min(wk.row0 + ts * 32 + l32, n_rows - 1);
@@ -307,10 +491,10 @@ __global__ __launch_bounds__(NTHREADS, 1) void ffn_gemm(const uint8_t* __restric
         if (nkb > 1) {
             xs_load(xs_n[0], 1, 0);
             xs_load(xs_n[1], 1, 1);
-            issue_x(1, 1);
-            issue_w(1, 1);
+            copy_x(feed, 1, 1);
+            copy_w(feed, 1, 1);
         }
-        if (nkb > 2) issue_w(2, 2);
+        if (nkb > 2) copy_w(feed, 2, 2);
         v16f an[2];
 #pragma unroll
         for (int ts = 0; ts < 2; ++ts)
@@ -318,20 +502,21 @@ __global__ __launch_bounds__(NTHREADS, 1) void ffn_gemm(const uint8_t* __restric
             for (int r = 0; r < 16; ++r) an[ts][r] = 0.f;
         int wslot = 0;
         for (int kb = 0; kb < nkb; ++kb) {
-            const uint8_t* sW = smem + wslot * W_TILE + a_row;
-            const uint8_t* sX = smem + b_row + (kb & 1) * X_TILE;
+            const uint32_t sW = a00 + wslot * W_TILE, sX = b00 + (kb & 1) * X_TILE;
             v8i a[2], b[2][2];
 #pragma unroll
             for (int ks = 0; ks < 2; ++ks) {
-                a[ks] = lds_operand(sW, offk[ks][0], offk[ks][1]);
-                b[0][ks] = lds_operand(sX, offk[ks][0], offk[ks][1]);
-                b[1][ks] = lds_operand(sX + 32 * KB, offk[ks][0], offk[ks][1]);
+                a[ks] = lds_operand(sW ^ (ks * 64), sW ^ (ks * 64 + 16), 0);
+                b[0][ks] = lds_operand(sX ^ (ks * 64), sX ^ (ks * 64 + 16), 0);
+                b[1][ks] = lds_operand(sX ^ (ks * 64), sX ^ (ks * 64 + 16), 32 * KB);
             }
-            const float wsa = sa_e[kb], wsb = sb_e[kb];
+            float wsa, wsb;                                    // complete at the barrier below
+            asm volatile("s_load_dword %0, %2, 0x0\n\ts_load_dword %1, %3, 0x0"
+                         : "=&s"(wsa), "=&s"(wsb) : "s"(sa_e + kb), "s"(sb_e + kb) : "memory");
             v16f T0, T1;
-            mfma_first(T0, a[0], b[0][0]);
+            mfma_new(T0, a[0], b[0][0]);
             mfma_acc(T0, a[1], b[0][1]);
-            mfma_first(T1, a[0], b[1][0]);
+            mfma_new(T1, a[0], b[1][0]);
             mfma_acc(T1, a[1], b[1][1]);
             // this wave's reads of block kb are done (the operands are in registers): wait for the copies that must be
             // complete (all but the weight block two steps ahead), meet the other waves, refill the freed slots
@@ -339,15 +524,16 @@ __global__ __launch_bounds__(NTHREADS, 1) void ffn_gemm(const uint8_t* __restric
             else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
             __builtin_amdgcn_s_barrier();
             asm volatile("" ::: "memory");
+            asm volatile("" : "+s"(wsa), "+s"(wsb));           // not used above this point
             const float x0 = xs_cur[0], x1 = xs_cur[1];
 #pragma unroll
             for (int ts = 0; ts < 2; ++ts) asm volatile("v_mov_b32 %0, %1" : "=v"(xs_cur[ts]) : "v"(xs_n[ts]));
             if (kb + 2 < nkb) {
                 xs_load(xs_n[0], kb + 2, 0);
                 xs_load(xs_n[1], kb + 2, 1);
-                issue_x(kb + 2, kb & 1);
+                copy_x(feed, kb + 2, kb & 1);
             }
-            if (kb + 3 < nkb) issue_w(kb + 3, wslot);
+            if (kb + 3 < nkb) copy_w(feed, kb + 3, wslot);
             // the four matrix instructions have left the pipe by now; a few wait states more cost nothing here
             asm volatile("s_nop 15\n\ts_nop 15\n\ts_nop 7" ::: "memory");
             PIN(T0);
@@ -430,270 +616,118 @@ __global__ __launch_bounds__(NTHREADS, 1) void ffn_gemm(const uint8_t* __restric
         }
         return;
     }
-    if (!wave_active) {
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        __builtin_amdgcn_s_barrier();
-        asm volatile("" ::: "memory");
-        if (nkb > 1) { issue_x(1, 1); issue_w(1, 1); }
-        if (nkb > 2) issue_w(2, 2);
-        int wslot = 0;
-        for (int kb = 0; kb < nkb; ++kb) {
-            if (kb + 2 < nkb) asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
-            else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            __builtin_amdgcn_s_barrier();
-            asm volatile("" ::: "memory");
-            if (kb + 2 < nkb) issue_x(kb + 2, kb & 1);
-            if (kb + 3 < nkb) issue_w(kb + 3, wslot);
-            wslot = (wslot == NW_BUF - 1) ? 0 : wslot + 1;
-        }
-    } else {
-        // per-lane constants of the operand reads
-        uint32_t offk[2][2];
-#pragma unroll
-        for (int ks = 0; ks < 2; ++ks)
-#pragma unroll
-            for (int j = 0; j < 2; ++j)
-                offk[ks][j] = (uint32_t)(((ks * 4 + half * 2 + j) ^ (l32 & 7) ^ ((l32 >> 3) & 1)) << 4);
-        const uint32_t a_row = (uint32_t)(wf * 128 + l32) * KB;
-        const uint32_t b_row = (uint32_t)(X_RING + (wt * 64 + l32) * KB);
-        // activation scales of this lane's two token columns (K-block major: one plane per K block)
-        uint32_t xs_i[2];                                      // byte offset of the lane's row inside a plane
-#pragma unroll
-        for (int ts = 0; ts < 2; ++ts) xs_i[ts] = 4u * (uint32_t)min(wk.row0 + wt * 64 + ts * 32 + l32, n_rows - 1);
-        const size_t plane = (size_t)n_rows * 4;
-        // issued as asm (saddr + 32-bit lane offset); the data is only touched behind a vmcnt wait
-        auto xs_load = [&](float& dst, int kb, int ts) {
-            asm volatile("global_load_dword %0, %1, %2" : "=v"(dst) : "v"(xs_i[ts]),
-                         "s"(reinterpret_cast<const uint8_t*>(act_s) + (size_t)kb * plane) : "memory");
-        };
-        float xs_n[2];
-        xs_load(xs_n[0], 0, 0);
-        xs_load(xs_n[1], 0, 1);
-        float xs_cur[2];
-
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        __builtin_amdgcn_s_barrier();
-        asm volatile("" ::: "memory");
-#pragma unroll
-        for (int ts = 0; ts < 2; ++ts) asm volatile("v_mov_b32 %0, %1" : "=v"(xs_cur[ts]) : "v"(xs_n[ts]));
-        if (nkb > 1) {
-            xs_load(xs_n[0], 1, 0);
-            xs_load(xs_n[1], 1, 1);
-            issue_x(1, 1);
-            issue_w(1, 1);
-        }
-        if (nkb > 2) issue_w(2, 2);
-        v8i b[2][2], a[2][2];
-#pragma unroll
-        for (int ks = 0; ks < 2; ++ks) a[0][ks] = lds_operand(smem + a_row, offk[ks][0], offk[ks][1]);
-#pragma unroll
-        for (int ts = 0; ts < 2; ++ts)
-#pragma unroll
-            for (int ks = 0; ks < 2; ++ks)
-                b[ts][ks] = lds_operand(smem + b_row + ts * 32 * KB, offk[ks][0], offk[ks][1]);
-        float sc[2][2];
-        {
-            const float wsa = sa_e[0], wsb = sb_e[0];
-#pragma unroll
-            for (int ts = 0; ts < 2; ++ts) {
-                sc[ts][0] = xs_cur[ts] * wsa;
-                sc[ts][1] = xs_cur[ts] * wsb;
-            }
-        }
-        v16f T0, T1;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) { T0[r] = 0.f; T1[r] = 0.f; }
-        float sc_pend = 0.f;                                   // scale of the sub-tile product still held in T1
-
-        // fold product `PS, PTS` (held in T0 for PTS == 0, T1 for PTS == 1) into its accumulator
-#define FOLD(PS, PTS, SCV)                                                                      \
-        do {                                                                                    \
-            if ((PTS) == 0) {                                                                   \
-                PIN(T0);                                                                        \
-                _Pragma("unroll") for (int r = 0; r < 16; ++r)                                  \
-                    acc[PS][0][r] = fmaf((SCV), T0[r], acc[PS][0][r]);                          \
-            } else {                                                                            \
-                PIN(T1);                                                                        \
-                _Pragma("unroll") for (int r = 0; r < 16; ++r)                                  \
-                    acc[PS][1][r] = fmaf((SCV), T1[r], acc[PS][1][r]);                          \
-            }                                                                                   \
-            PIN(acc[PS][PTS]);                                                                  \
-        } while (0)
-
-        int wslot = 0;                                         // ring slot of weight block kb
-        for (int kb = 0; kb < nkb; ++kb) {
-            const int wnext = (wslot == NW_BUF - 1) ? 0 : wslot + 1;
-            const int wprev = (wslot == 0) ? NW_BUF - 1 : wslot - 1;             // slot of block kb-1 = of block kb+2
-            const uint8_t* sW = smem + wslot * W_TILE + a_row;                   // block kb
-            const uint8_t* sWn = smem + wnext * W_TILE + a_row;                  // block kb+1
-            const uint8_t* sXn = smem + b_row + ((kb & 1) ^ 1) * X_TILE;         // block kb+1
-            const int kn = min(kb + 1, nkb - 1);
-            const float wsa_n = sa_e[kn], wsb_n = sb_e[kn];            // consumed at the end of this step
-            // Eight sub-tile products, two MFMAs each.  The 16 scale-FMAs of product i-1 sit behind the
-            // second MFMA of product i: by then its result has left the matrix pipe (two more MFMAs
-            // have been issued since), and the vector ALU works in the shadow of the MFMA just issued.
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const int s = i >> 1, ts = i & 1;
-                if (i == 6) {
-                    // all of this wave's reads of block kb have been issued; wait for them and for the
-                    // copies that must be complete, then meet the other waves
-                    if (kb + 2 < nkb) asm volatile("s_waitcnt vmcnt(4) lgkmcnt(0)" ::: "memory");
-                    else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
-                    __builtin_amdgcn_s_barrier();
-                    asm volatile("" ::: "memory");
-#pragma unroll
-                    for (int t2 = 0; t2 < 2; ++t2) asm volatile("v_mov_b32 %0, %1" : "=v"(xs_cur[t2]) : "v"(xs_n[t2]));
-                }
-                if (ts == 0) mfma_first(T0, a[s & 1][0], b[0][0]); else mfma_first(T1, a[s & 1][0], b[1][0]);
-                // one copy behind every matrix instruction: weight block kb+2 over products 0 and 1
-                if (i < 2 && kb >= 1 && kb + 2 < nkb) issue_w1(kb + 2, wprev, i * 2);
-                if (i == 7 && kb + 2 < nkb) X_COPY(kb + 2, kb & 1, 2);
-                if (ts == 0 && s < 3) {
-#pragma unroll
-                    for (int ks = 0; ks < 2; ++ks)
-                        a[(s + 1) & 1][ks] = lds_operand(sW + (s + 1) * 32 * KB, offk[ks][0], offk[ks][1]);
-                }
-                if (i == 6) {
-#pragma unroll
-                    for (int ks = 0; ks < 2; ++ks) a[0][ks] = lds_operand(sWn, offk[ks][0], offk[ks][1]);
-                    if (kb + 2 < nkb) {
-                        xs_load(xs_n[0], kb + 2, 0);
-                        xs_load(xs_n[1], kb + 2, 1);
-                        X_COPY(kb + 2, kb & 1, 0);
-                    }
-                }
-                if (ts == 0) mfma_acc(T0, a[s & 1][1], b[0][1]); else mfma_acc(T1, a[s & 1][1], b[1][1]);
-                if (i < 2 && kb >= 1 && kb + 2 < nkb) issue_w1(kb + 2, wprev, i * 2 + 1);
-                if (i == 6 && kb + 2 < nkb) X_COPY(kb + 2, kb & 1, 1);
-                if (i == 7 && kb + 2 < nkb) X_COPY(kb + 2, kb & 1, 3);
-                if (i == 0) {
-                    FOLD(3, 1, sc_pend);
-                } else {
-                    const int ps = (i - 1) >> 1, pts = (i - 1) & 1;
-                    FOLD(ps, pts, sc[pts][(GATED && ps >= 2) ? 1 : 0]);
-                }
-                if (i == 6) {
-#pragma unroll
-                    for (int ks = 0; ks < 2; ++ks) b[0][ks] = lds_operand(sXn, offk[ks][0], offk[ks][1]);
-                }
-                if (i == 7) {
-                    sc_pend = sc[1][GATED ? 1 : 0];
-#pragma unroll
-                    for (int t2 = 0; t2 < 2; ++t2) {
-                        sc[t2][0] = xs_cur[t2] * wsa_n;
-                        sc[t2][1] = xs_cur[t2] * wsb_n;
-                    }
-#pragma unroll
-                    for (int ks = 0; ks < 2; ++ks) b[1][ks] = lds_operand(sXn + 32 * KB, offk[ks][0], offk[ks][1]);
-                }
-            }
-            wslot = wnext;
-        }
-        // the last product: wait out the matrix pipe, then fold it
-        asm volatile("s_nop 15\n\ts_nop 15\n\ts_nop 7" ::: "memory");
-        FOLD(3, 1, sc_pend);
-#undef FOLD
-#undef X_COPY
+    // ---- full tile: 32-row token groups n = ceil(rows / 32) of 3..8; waves 0..3 (token half 0) take the first ceil(n/2)
+    //      of them, waves 4..7 the others.  Wave w and wave w + 4 share a SIMD, so every SIMD multiplies n groups: the
+    //      matrix time of a tile follows its height in steps of 32 rows.
+    const int n_grp = (wk.nrows + 31) >> 5;
+    const int grp0 = wt == 0 ? 0 : (n_grp + 1) >> 1;           // this wave's first token group
+    const int nts = wt == 0 ? (n_grp + 1) >> 1 : n_grp >> 1;   // and how many it has (1..4), wave-uniform
+    v16f acc[2][4];                                            // k_loop<nts> defines the first nts of each
+    Tile tile;
+    tile.lds0 = lds0;
+    tile.nkb = nkb;
+    tile.a_row = (uint32_t)(wf * 64 + l32) * KB;
+    tile.b_row = (uint32_t)(X_RING + (grp0 * 32 + l32) * KB);
+    tile.l32 = l32;
+    tile.half = half;
+    tile.row = wk.row0 + grp0 * 32 + l32;
+    tile.n_rows = n_rows;
+    tile.act_s = reinterpret_cast<const uint8_t*>(act_s);
+    tile.sa = sa_e;
+    tile.sb = sb_e;
+    switch (nts) {
+        case 4: k_loop<4, GATED>(tile, feed, acc); break;
+        case 3: k_loop<3, GATED>(tile, feed, acc); break;
+        case 2: k_loop<2, GATED>(tile, feed, acc); break;
+        default: k_loop<1, GATED>(tile, feed, acc); break;
     }
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
     __builtin_amdgcn_s_barrier();                              // every wave is done with the operand rings
     asm volatile("" ::: "memory");
 
     // ---- epilogue.  Accumulator (s, ts, r) of this lane belongs to token
-    //      row0 + wt*64 + ts*32 + l32 and staged weight row wf*128 + s*32 + (r/4)*8 + half*4 + r%4.
+    //      row0 + (grp0 + ts)*32 + l32 and staged weight row wf*64 + s*32 + (r/4)*8 + half*4 + r%4.
     if (GATED) {
-        // gate rows s = 0,1 and up rows s = 2,3 of features f0 + wf*64 + (s&1)*32 + ...
-        float h[2][2][16];
-        float amax[2] = {0.f, 0.f};
-        if (wave_active) {
+        // s = 0 gate, s = 1 up of features f0 + wf*32 + (r/4)*8 + half*4 + r%4
+        float h[4][16];
 #pragma unroll
-            for (int ts = 0; ts < 2; ++ts)
+        for (int ts = 0; ts < 4; ++ts) {
+            if (ts >= nts) break;
+            float am = 0.f;
 #pragma unroll
-                for (int s = 0; s < 2; ++s)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) {
-                        const float g = acc[s][ts][r], u = acc[s + 2][ts][r];
-                        // silu(g)*u with the hardware reciprocal (1 ulp): far below the matrix cores' own error
-                        const float v = g * __builtin_amdgcn_rcpf(1.0f + __expf(-g)) * u;
-                        h[ts][s][r] = v;
-                        amax[ts] = fmaxf(amax[ts], fabsf(v));
-                    }
-#pragma unroll
-            for (int ts = 0; ts < 2; ++ts) {
-                amax[ts] = fmaxf(amax[ts], __shfl_xor(amax[ts], 32));   // the lane pair covers 64 features
-                if (half == 0) s_amax[wf * X_ROWS + wt * 64 + ts * 32 + l32] = amax[ts];
+            for (int r = 0; r < 16; ++r) {
+                const float g = acc[0][ts][r], u = acc[1][ts][r];
+                // silu(g)*u with the hardware reciprocal (1 ulp): far below the matrix cores' own error
+                const float v = g * __builtin_amdgcn_rcpf(1.0f + __expf(-g)) * u;
+                h[ts][r] = v;
+                am = fmaxf(am, fabsf(v));
             }
+            am = fmaxf(am, __shfl_xor(am, 32));                // the lane pair covers 32 features
+            if (half == 0) s_amax[wf * X_ROWS + (grp0 + ts) * 32 + l32] = am;
         }
-        __syncthreads();                                       // the other 64 features live in wave (wt, wf^1)
-        if (wave_active) {
+        __syncthreads();                                       // the other 96 features live in the other three waves of wt
 #pragma unroll
-            for (int ts = 0; ts < 2; ++ts) {
-                const int trow = wt * 64 + ts * 32 + l32;
-                const int p = wk.row0 + trow;
-                const float am = fmaxf(amax[ts], s_amax[(wf ^ 1) * X_ROWS + trow]);
-                const float sc = (am == 0.f) ? 1.0f : am / 448.0f;
-                // h / sc, correctly rounded, for 32 values per token: a reciprocal refined once, then the
-                // quotient estimate corrected by its exact remainder (three instructions instead of a full
-                // division each; equal to the division wherever sc is far from the ends of the fp32 range,
-                // and the plain division elsewhere).  |h / sc| <= 448 up to one rounding, so no clamp.
-                float inv = __builtin_amdgcn_rcpf(sc);
-                inv = fmaf(fmaf(-sc, inv, 1.0f), inv, inv);
-                const bool mid_range = sc > 1e-30f && sc < 1e30f;
-                auto quot = [&](float hv) {
-                    const float q0 = hv * inv;
-                    return mid_range ? fmaf(fmaf(-q0, sc, hv), inv, q0) : hv / sc;
-                };
-                if (p < row_end) {
-                    uint8_t* dst = hq + (size_t)p * NOUT + f0 + wf * 64 + half * 4;
+        for (int ts = 0; ts < 4; ++ts) {
+            if (ts >= nts) break;
+            const int trow = (grp0 + ts) * 32 + l32;
+            const int p = wk.row0 + trow;
+            const float am = fmaxf(fmaxf(s_amax[trow], s_amax[X_ROWS + trow]),
+                                   fmaxf(s_amax[2 * X_ROWS + trow], s_amax[3 * X_ROWS + trow]));
+            const float sc = (am == 0.f) ? 1.0f : am / 448.0f;
+            // h / sc, correctly rounded, for 16 values per token: a reciprocal refined once, then the
+            // quotient estimate corrected by its exact remainder (three instructions instead of a full
+            // division each; equal to the division wherever sc is far from the ends of the fp32 range,
+            // and the plain division elsewhere).  |h / sc| <= 448 up to one rounding, so no clamp.
+            float inv = __builtin_amdgcn_rcpf(sc);
+            inv = fmaf(fmaf(-sc, inv, 1.0f), inv, inv);
+            const bool mid_range = sc > 1e-30f && sc < 1e30f;
+            auto quot = [&](float hv) {
+                const float q0 = hv * inv;
+                return mid_range ? fmaf(fmaf(-q0, sc, hv), inv, q0) : hv / sc;
+            };
+            if (p < row_end) {
+                uint8_t* dst = hq + (size_t)p * NOUT + f0 + wf * 32 + half * 4;
 #pragma unroll
-                    for (int s = 0; s < 2; ++s)
-#pragma unroll
-                        for (int r4 = 0; r4 < 4; ++r4) {
-                            int code = 0;
-                            code = __builtin_amdgcn_cvt_pk_fp8_f32(quot(h[ts][s][r4 * 4]), quot(h[ts][s][r4 * 4 + 1]), code, false);
-                            code = __builtin_amdgcn_cvt_pk_fp8_f32(quot(h[ts][s][r4 * 4 + 2]), quot(h[ts][s][r4 * 4 + 3]), code, true);
-                            *reinterpret_cast<uint32_t*>(dst + s * 32 + r4 * 8) = (uint32_t)code;
-                        }
-                    if (half == 0 && wf == 0) hs[(size_t)wk.ft * n_rows + p] = sc;
+                for (int r4 = 0; r4 < 4; ++r4) {
+                    int code = 0;
+                    code = __builtin_amdgcn_cvt_pk_fp8_f32(quot(h[ts][r4 * 4]), quot(h[ts][r4 * 4 + 1]), code, false);
+                    code = __builtin_amdgcn_cvt_pk_fp8_f32(quot(h[ts][r4 * 4 + 2]), quot(h[ts][r4 * 4 + 3]), code, true);
+                    *reinterpret_cast<uint32_t*>(dst + r4 * 8) = (uint32_t)code;
                 }
+                if (half == 0 && wf == 0) hs[(size_t)wk.ft * n_rows + p] = sc;
             }
         }
     } else {
         // The accumulators hold 16-byte pieces of 64 different rows per store instruction, which the memory
-        // pipeline would take as 64 separate requests.  Each wave therefore turns its 128 x 64 block through a
-        // private LDS region (the operand rings are free now), 64 features at a time, and writes 256 contiguous
+        // pipeline would take as 64 separate requests.  Each wave therefore turns its 64 x 32-token blocks through a
+        // private LDS region (the operand rings are free now), two regions in turn, and writes 256 contiguous
         // bytes of a row with every 16 lanes.
-        if (wave_active) {
-            constexpr int TS_STRIDE = 68;                      // floats per staged token row: 64 + 4 of padding
-            float* const stage = reinterpret_cast<float*>(smem) + wave * (64 * TS_STRIDE);
+        constexpr int TS_STRIDE = 68;                          // floats per staged token row: 64 + 4 of padding
+        const int fcol = f0 + wf * 64;
+        if (fcol < NOUT) {
 #pragma unroll
-            for (int hh = 0; hh < 2; ++hh) {
+            for (int ts = 0; ts < 4; ++ts) {
+                if (ts >= nts) break;
+                float* const stage = reinterpret_cast<float*>(smem) + (wave * 2 + (ts & 1)) * (32 * TS_STRIDE);
 #pragma unroll
-                for (int ts = 0; ts < 2; ++ts)
+                for (int s = 0; s < 2; ++s)
 #pragma unroll
-                    for (int sl = 0; sl < 2; ++sl)
-#pragma unroll
-                        for (int r4 = 0; r4 < 4; ++r4) {
-                            const int s = hh * 2 + sl;
-                            const float4 v = make_float4(acc[s][ts][r4 * 4], acc[s][ts][r4 * 4 + 1],
-                                                         acc[s][ts][r4 * 4 + 2], acc[s][ts][r4 * 4 + 3]);
-                            *reinterpret_cast<float4*>(stage + (ts * 32 + l32) * TS_STRIDE + sl * 32 + r4 * 8 + half * 4) = v;
-                        }
-                // the lanes of a wave run in step: once its own LDS writes have completed, every lane's have
+                    for (int r4 = 0; r4 < 4; ++r4)
+                        *reinterpret_cast<float4*>(stage + l32 * TS_STRIDE + s * 32 + r4 * 8 + half * 4) =
+                            make_float4(acc[s][ts][r4 * 4], acc[s][ts][r4 * 4 + 1], acc[s][ts][r4 * 4 + 2],
+                                        acc[s][ts][r4 * 4 + 3]);
+                // the lanes of a wave run in step: once its own LDS writes have completed, every lane's have (and the
+                // reads of the region used two groups ago have been consumed by their stores)
                 asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-                const int fcol = f0 + wf * 128 + hh * 64;
-                if (fcol < NOUT) {
-#pragma unroll 4
-                    for (int it = 0; it < 16; ++it) {
-                        const int trow = it * 4 + (lane >> 4);
-                        const float4 v = *reinterpret_cast<const float4*>(stage + trow * TS_STRIDE + (lane & 15) * 4);
-                        const int p = wk.row0 + wt * 64 + trow;
-                        if (p < row_end)
-                            *reinterpret_cast<float4*>(y_perm + (size_t)p * NOUT + fcol + (lane & 15) * 4) = v;
-                    }
-                }
-                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // all reads done before the region is rewritten
+                float4 v[8];
+#pragma unroll
+                for (int it = 0; it < 8; ++it)
+                    v[it] = *reinterpret_cast<const float4*>(stage + (it * 4 + (lane >> 4)) * TS_STRIDE + (lane & 15) * 4);
+                const int p = wk.row0 + (grp0 + ts) * 32 + (lane >> 4);
+                float* const dst = y_perm + (size_t)p * NOUT + fcol + (lane & 15) * 4;
+#pragma unroll
+                for (int it = 0; it < 8; ++it)
+                    if (p + it * 4 < row_end) *reinterpret_cast<float4*>(dst + (size_t)(it * 4) * NOUT) = v[it];
             }
         }
     }

@@ -180,3 +180,15 @@ def test_layer_under_hip_graph_capture(gpu_lib, mode):
                 assert not torch.equal(got.view(torch.int16), want.view(torch.int16))
         finally:
             layer.close()
+
+
+@pytest.mark.parametrize("d,F", [(128, 128), (384, 256), (256, 640)])
+def test_tile_heights(gpu_lib, d, F):
+    """Replay logs (k = 1) that give the experts row counts around every tile height the grouped GEMMs distinguish: the
+    narrow tile's limit, each number of 32-row groups a wave can have (odd and even), one row over a full tile, and splits
+    of two and three tiles; one, two, three and five K blocks; output feature tiles that are half empty."""
+    counts = [0, 1, 31, 32, 33, 64, 65, 95, 97, 128, 129, 160, 161, 192, 193, 223, 225, 255, 256, 257, 289, 320, 511, 513, 600]
+    cfg = MoEConfig("heights", T=sum(counts), d=d, E=len(counts), k=1, F=F, modes=("replay",), seed=d + F)
+    rng = np.random.default_rng(cfg.seed)
+    ids = rng.permutation(np.repeat(np.arange(cfg.E, dtype=np.int32), counts)).reshape(cfg.T, 1)
+    _run_and_check_layer(gpu_lib, cfg, "replay", log=(np.ascontiguousarray(ids), np.ones((cfg.T, 1), dtype=np.float32)))
