@@ -192,3 +192,41 @@ def test_tile_heights(gpu_lib, d, F):
     rng = np.random.default_rng(cfg.seed)
     ids = rng.permutation(np.repeat(np.arange(cfg.E, dtype=np.int32), counts)).reshape(cfg.T, 1)
     _run_and_check_layer(gpu_lib, cfg, "replay", log=(np.ascontiguousarray(ids), np.ones((cfg.T, 1), dtype=np.float32)))
+
+
+@pytest.mark.parametrize("rows", [1, 15, 16, 17, 31, 32, 33, 48, 65])
+def test_activation_codes_at_block_edges(gpu_lib, rows):
+    """Row counts around the quantisation kernel's 32-row blocks, plain and fanned out, with the values its short quotient has
+    to get right: groups at both ends of the scale range, where the division itself is taken, negative zeros, and quotients
+    that land on rounding boundaries (every bf16 significand under one scale).  Codes and scales are exact."""
+    from oracle import fp_formats as ff, moe_layer as om
+    d, fan = 384, 2
+    g = torch.Generator().manual_seed(rows)
+    x = torch.randn((rows, d), generator=g)
+    bits = torch.arange(128, dtype=torch.int32) + (126 << 7)                # 0.5 .. 1: every significand
+    x[0, :128] = (bits << 16).view(torch.float32)
+    x[0, 128:256] *= 1e-36
+    x[0, 256:] *= 1e36
+    x[rows - 1, ::3] = -0.0
+    xb = x.to(torch.bfloat16)
+    xb_bits = xb.view(torch.int16).numpy().view(np.uint16)
+    q_o, s_o = om.quantize_rows(ff.bf16_bits_to_f64(xb_bits))
+    neg_zero = (xb_bits & 0x8000) != 0                                      # zeros keep their sign (the oracle's coder may not)
+    dst = torch.randperm(rows * fan, generator=g).to(torch.int32)
+    ctx = gpu_lib.moe_create(0, 128, 1, 1, 128)
+    try:
+        for dst_rows, f in ((None, 1), (dst.cuda(), fan)):
+            q = torch.full((rows * f, d), 0x55, dtype=torch.uint8, device="cuda")
+            s = torch.full((d // 128, rows * f), -1.0, device="cuda")
+            gpu_lib.moe_quantize_fp8(ctx, xb.cuda(), rows, d, 128, dst_rows, f, q, s)
+            torch.cuda.synchronize()
+            src = np.arange(rows)
+            if dst_rows is not None:
+                src = np.empty(rows * fan, dtype=np.int64)
+                src[dst.numpy()] = np.arange(rows * fan) // fan
+            got = q.cpu().numpy()
+            assert np.array_equal(s.cpu().numpy().T, s_o[src])
+            assert np.array_equal(got & 0x7F, (q_o & 0x7F)[src])
+            assert np.array_equal((got & 0x80) != 0, neg_zero[src])
+    finally:
+        gpu_lib.moe_destroy(ctx)
