@@ -230,3 +230,30 @@ def test_activation_codes_at_block_edges(gpu_lib, rows):
             assert np.array_equal((got & 0x80) != 0, neg_zero[src])
     finally:
         gpu_lib.moe_destroy(ctx)
+
+
+@pytest.mark.parametrize("k", [1, 2, 3, 5, 7, 8, 9, 16])
+@pytest.mark.parametrize("d", [128, 1024, 1152])
+def test_combine_at_every_fan_out(gpu_lib, k, d):
+    """One, exactly one and two blocks of columns per token; compiled and run-time fan-outs; slots without a row.  The fp32
+    sums are the slot-order multiply-add chain: k roundings of at most half an ulp of a partial sum each."""
+    T = 5
+    g = torch.Generator().manual_seed(k * 31 + d)
+    y_perm, w = torch.randn((T * k, d), generator=g), torch.rand((T, k), generator=g)
+    inv = torch.randperm(T * k, generator=g).to(torch.int32).view(T, k)
+    inv[2, k // 2] = -1
+    layer = gpu_lib.MoELayer(T, d, 16, k, 128)
+    try:
+        layer.y_perm.copy_(y_perm)
+        layer.inv_perm.copy_(inv.view(-1))
+        layer.topk_w.copy_(w)
+        sums = torch.empty((T, d), device="cuda")
+        layer.combine(sums)
+        torch.cuda.synchronize()
+        rows = torch.where(inv[..., None] >= 0, y_perm[inv.clamp(min=0).long()], torch.zeros(()))
+        terms = w[..., None].double() * rows.double()
+        err = (sums.cpu().double() - terms.sum(1)).abs()
+        assert torch.all(err <= k * 2.0 ** -24 * terms.abs().sum(1) + 1e-30)
+        assert torch.equal(layer.y.cpu(), sums.cpu().to(torch.bfloat16))
+    finally:
+        layer.close()
