@@ -28,16 +28,13 @@
 //        epilogue h = silu(g)*u, re-quantised to e4m3 with one scale per (row, 128 features).
 // GEMM2: staged rows are 256 consecutive output features; epilogue: fp32 rows, turned through LDS so
 //        that every row is stored in contiguous 256-byte pieces.
-#include "moe_internal.hpp"
+#include "ffn_common.hpp"
+
+#include <cmath>
 
 namespace moe355 {
 namespace {
 
-typedef int v8i __attribute__((ext_vector_type(8)));
-typedef float v16f __attribute__((ext_vector_type(16)));
-typedef int v4i __attribute__((ext_vector_type(4)));
-
-constexpr int KB = QBLOCK;                        // K bytes per stage (= one scale block)
 constexpr int W_ROWS = 256;                       // staged weight rows per block
 constexpr int X_ROWS = TOK_TILE;                  // staged activation rows per block (256)
 constexpr int W_TILE = W_ROWS * KB;                // 32 KiB: one K block of the weight tile
@@ -45,29 +42,27 @@ constexpr int X_TILE = X_ROWS * KB;                // 32 KiB: one K block of the
 constexpr int NW_BUF = 3, NX_BUF = 2;              // LDS ring depths
 constexpr int X_RING = NW_BUF * W_TILE;            // byte offset of the activation ring
 constexpr int NTHREADS = 512;
-constexpr int NXCD = 8;
 constexpr int NARROW_ROWS = 64;                     // tiles of at most this many rows take the narrow path of ffn_gemm
 
-struct Work { int32_t expert; int32_t row0; int32_t ft; int32_t nrows; };
-
 // ------------------------------------------------------------------ work list
-// An expert with c rows gets ceil(c/256) row tiles, ordered (expert, feature tile, row tile).  Units
+// An expert with c rows gets ceil(c/tile_rows) row tiles (tile_rows is 256, or 64 for the streaming kernels), ordered (expert, feature tile, row tile).  Units
 // that share a weight tile are thus neighbours and, when they do the same amount of work, the blocks
 // that run them side by side on one XCD advance in step and hit each other's lines in that XCD's L2
 // (a few K steps of skew already exceed what the L2 retains, and the shared tile is then fetched
 // again from HBM).
 // Block (e, l) writes the units of expert e into list l (0: gate/up, n_ft0 feature tiles; 1: down,
 // n_ft1 feature tiles); every block recomputes the tile counts of all experts for its base index.
-__global__ __launch_bounds__(256) void build_work(const int32_t* __restrict__ offsets, int E, int n_ft0, int n_ft1,
-                                                  Work* __restrict__ work0, Work* __restrict__ work1,
-                                                  int32_t* __restrict__ n_work) {
+// tickets (or nullptr): one per unit of list 0, set to zero for the kernel that counts them up.
+__global__ __launch_bounds__(256) void build_work(const int32_t* __restrict__ offsets, int E, int tile_rows0,
+                                                  int tile_rows1, int n_ft0, int n_ft1, Work* __restrict__ work0, Work* __restrict__ work1,
+                                                  int32_t* __restrict__ n_work, int32_t* __restrict__ tickets) {
     __shared__ int32_t s_tiles[MAX_E];
     const int tid = threadIdx.x;
     const int e = blockIdx.x;
-    const int n_ft = blockIdx.y == 0 ? n_ft0 : n_ft1;
+    const int n_ft = blockIdx.y == 0 ? n_ft0 : n_ft1, tile_rows = blockIdx.y == 0 ? tile_rows0 : tile_rows1;
     Work* const work = blockIdx.y == 0 ? work0 : work1;
     int nt_t = 0;
-    if (tid < E) nt_t = (offsets[tid + 1] - offsets[tid] + TOK_TILE - 1) / TOK_TILE;
+    if (tid < E) nt_t = (offsets[tid + 1] - offsets[tid] + tile_rows - 1) / tile_rows;
     s_tiles[tid] = nt_t;
     __syncthreads();
     for (int off = 1; off < MAX_E; off <<= 1) {            // inclusive scan
@@ -79,7 +74,7 @@ __global__ __launch_bounds__(256) void build_work(const int32_t* __restrict__ of
     if (e == 0 && tid == 0) n_work[blockIdx.y] = s_tiles[MAX_E - 1] * n_ft;
     if (e >= E) return;
     const int start = offsets[e], cnt = offsets[e + 1] - start;
-    const int nt = (cnt + TOK_TILE - 1) / TOK_TILE;
+    const int nt = (cnt + tile_rows - 1) / tile_rows;
     if (nt == 0) return;
     const int base = (s_tiles[e] - nt) * n_ft;
     for (int idx = tid; idx < nt * n_ft; idx += 256) {
@@ -103,19 +98,11 @@ __global__ __launch_bounds__(256) void build_work(const int32_t* __restrict__ of
         w.ft = f;
         w.nrows = hi - lo;
         work[base + idx] = w;
+        if (tickets && blockIdx.y == 0) tickets[base + idx] = 0;
     }
 }
 
 // ------------------------------------------------------------------ helpers
-// Direct global -> LDS copies.  Lane i of the wave deposits its bytes at lds_addr + i*size;
-// the global address is sbase + voff (per lane).  Completion is tracked by vmcnt; the
-// compiler does not see these as memory operations of its own, so every wait on them is
-// written out explicitly below.
-__device__ inline void dma16(uint32_t lds_addr, uint32_t voff, const void* sbase) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-                 :: "s"(lds_addr), "v"(voff), "s"(sbase) : "memory");
-}
-
 // The matrix instructions are written as volatile asm so that they stay exactly where the
 // source puts them: the schedule below relies on it.  T = A*B (first K half) and T += A*B.
 __device__ inline void mfma_first(v16f& t, const v8i& a, const v8i& b) {
@@ -131,13 +118,6 @@ __device__ inline void mfma_acc(v16f& t, const v8i& a, const v8i& b) {
 // An empty volatile asm that "rewrites" x: uses of x after it cannot move above it, and
 // values feeding x cannot move below it.
 #define PIN(x) asm volatile("" : "+v"(x))
-
-// the 32 K-bytes a lane feeds to one 32x32x64 MFMA, from its row's two swizzled 16-byte chunks at LDS addresses c0, c1
-typedef __attribute__((address_space(3))) const v4i* lds_v4i;
-__device__ inline v8i lds_operand(uint32_t c0, uint32_t c1, int plus) {
-    const v4i lo = *reinterpret_cast<lds_v4i>(c0 + plus), hi = *reinterpret_cast<lds_v4i>(c1 + plus);
-    return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-}
 
 // ------------------------------------------------------------------ operand copies
 // What one wave brings of every K block: staged weight rows [32w, 32w+32) and staged activation rows [32w, 32w+32).
@@ -176,6 +156,14 @@ __device__ __forceinline__ void copy_w(const Feed& f, int kb, int wslot, int n =
     copy_w1<1>(f, kb, wslot, n);
     copy_w1<2>(f, kb, wslot, n);
     copy_w1<3>(f, kb, wslot, n);
+}
+// The weights of a narrow tile: the tile is all of its expert's rows, so nothing else reads them (non-temporal: a block stream
+// of 128-byte row pieces into LDS reaches 6.0..6.6 TB/s that way and 5.3..5.9 through the caches).
+__device__ __forceinline__ void copy_w_once(const Feed& f, int kb, int wslot) {
+    const uint32_t at = f.lds_rows + wslot * W_TILE;
+    const size_t k0 = (size_t)kb * KB;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) dma16_once(at + j * 8 * KB, f.w_off[j & 1], f.w_base[j >> 1] + k0);
 }
 __device__ __forceinline__ void copy_x(const Feed& f, int kb, int xslot) {
     copy_x1<0>(f, kb, xslot, f.x_copies);
@@ -461,8 +449,8 @@ __global__ __launch_bounds__(NTHREADS, 1) void ffn_gemm(const uint8_t* __restric
     const float* sb_e = GATED ? sb + ((size_t)e * nblk_out + blk_a) * nkb : sa_e;
 
     copy_x(feed, 0, 0);
-    copy_w(feed, 0, 0);
     if (narrow) {
+        copy_w_once(feed, 0, 0);
         // ---- NARROW tile: at most 64 rows.  In the layout above only the two waves of token group 0 would
         //      multiply, alone on their SIMDs, and such a tile costs 0.7 of a full one.  Here all eight waves work:
         //      wave w multiplies the 32 staged weight rows it copies itself by the tile's 64 token columns (two
@@ -492,9 +480,9 @@ __global__ __launch_bounds__(NTHREADS, 1) void ffn_gemm(const uint8_t* __restric
             xs_load(xs_n[0], 1, 0);
             xs_load(xs_n[1], 1, 1);
             copy_x(feed, 1, 1);
-            copy_w(feed, 1, 1);
+            copy_w_once(feed, 1, 1);
         }
-        if (nkb > 2) copy_w(feed, 2, 2);
+        if (nkb > 2) copy_w_once(feed, 2, 2);
         v16f an[2];
 #pragma unroll
         for (int ts = 0; ts < 2; ++ts)
@@ -533,7 +521,7 @@ __global__ __launch_bounds__(NTHREADS, 1) void ffn_gemm(const uint8_t* __restric
                 xs_load(xs_n[1], kb + 2, 1);
                 copy_x(feed, kb + 2, kb & 1);
             }
-            if (kb + 3 < nkb) copy_w(feed, kb + 3, wslot);
+            if (kb + 3 < nkb) copy_w_once(feed, kb + 3, wslot);
             // the four matrix instructions have left the pipe by now; a few wait states more cost nothing here
             asm volatile("s_nop 15\n\ts_nop 15\n\ts_nop 7" ::: "memory");
             PIN(T0);
@@ -616,6 +604,7 @@ __global__ __launch_bounds__(NTHREADS, 1) void ffn_gemm(const uint8_t* __restric
         }
         return;
     }
+    copy_w(feed, 0, 0);
     // ---- full tile: 32-row token groups n = ceil(rows / 32) of 3..8; waves 0..3 (token half 0) take the first ceil(n/2)
     //      of them, waves 4..7 the others.  Wave w and wave w + 4 share a SIMD, so every SIMD multiplies n groups: the
     //      matrix time of a tile follows its height in steps of 32 rows.
@@ -737,9 +726,46 @@ constexpr size_t SMEM_BYTES = NW_BUF * W_TILE + NX_BUF * X_TILE;   // 160 KiB
 
 }  // namespace
 
-size_t ffn_work_bytes(int max_tiles, int F, int d) {
-    return sizeof(Work) * (size_t)max_tiles * (size_t)(F / 128 + (d + 255) / 256);
+// ------------------------------------------------------------------ which kernel takes which GEMM
+// The streaming kernels (ffn_stream.hip) where the weights are the bound, the big tiles where matrix work or the L2 reuse of
+// weights between row tiles counts.  The lines were measured with both sides on the same buffers (us, big tiles / streaming;
+// the big-tile side already reads the weights of narrow tiles past the caches):
+//   gate/up  rows per expert 2: 1026 / 1006 (256 experts), 3: 163 / 142, 6: 136 / 133, 12: 129.5 / 133, 16: 251..287 / 274..287
+//            and, where the tiles leave compute units idle: 96 units, 4 rows 35 / 23, 32 rows 33 / 28; 384 units, 8 rows 79 / 68
+//   down     rows per expert 6: 75 / 68, 16: 75 / 70, 24: 78 / 74, 32: 81 / 78, 48: 85 / 82, 64: 188 / 202
+//   linear   16 rows x 1024 32 / 15, 256 x 8192 52 / 22, 128 x 32768 40 / 31, 512 x 16384 57 / 54, 1024 x 8192 58 / 56;
+//            256 big tiles and more than 64 rows (128 x 65536): 73 / 80
+constexpr int64_t GATE_UP_STREAM_ROWS = 8, GATE_UP_STREAM_ROWS_IDLE = 32, DOWN_STREAM_ROWS = 48;
+constexpr int CUS = 256, LINEAR_STREAM_TILES = 128;
+
+static bool gate_up_streams(const moe_dims* D) {
+    const int64_t N = (int64_t)D->T * D->k;
+    if (N == 0 || D->F > D->d) return false;                   // the rows of y_perm hold h meanwhile
+    if (N <= GATE_UP_STREAM_ROWS * D->E) return true;
+    // experts that meet at least one row when the router favours none
+    const double met = D->E * (1.0 - pow(1.0 - (double)D->k / D->E, (double)D->T));
+    return N <= GATE_UP_STREAM_ROWS_IDLE * D->E && met * (D->F / 128) < CUS;
 }
+static bool down_streams(const moe_dims* D) { return (int64_t)D->T * D->k <= DOWN_STREAM_ROWS * D->E; }
+static bool linear_streams(int32_t rows, int32_t NOUT) {
+    return rows <= STREAM_ROWS || (int64_t)((rows + TOK_TILE - 1) / TOK_TILE) * ((NOUT + 255) / 256) <= LINEAR_STREAM_TILES;
+}
+
+// upper bound on row tiles: every full tile, and one more for each expert that has rows
+static int64_t max_row_tiles(const moe_dims* D, bool streams) {
+    const int64_t N = (int64_t)D->T * D->k;
+    return N / (streams ? STREAM_ROWS : TOK_TILE) + (N < D->E ? N : D->E);
+}
+static int64_t gate_up_units(const moe_dims* D) { return max_row_tiles(D, gate_up_streams(D)) * (D->F / 128); }
+static int64_t down_units(const moe_dims* D) { return max_row_tiles(D, down_streams(D)) * ((D->d + 255) / 256); }
+
+// both work lists; never smaller than what a context of these dims offers to moe_linear_fp8
+size_t ffn_work_bytes(const moe_dims* D) {
+    const int64_t linear = ((int64_t)D->T * D->k / TOK_TILE + D->E) * (D->F / 128 + (D->d + 255) / 256);
+    const int64_t need = gate_up_units(D) + down_units(D);
+    return sizeof(Work) * (size_t)(need > linear ? need : linear);
+}
+size_t ffn_ticket_bytes(const moe_dims* D) { return gate_up_streams(D) ? sizeof(int32_t) * (size_t)gate_up_units(D) : 0; }
 
 static hipError_t set_lds_limits() {
     static bool attr_set = false;
@@ -781,16 +807,22 @@ hipError_t launch_expert_ffn(moe_ctx* c, const uint8_t* xq, const float* xs, con
     const int N = (int)((int64_t)D.T * D.k);
     const int nft1 = D.F / 128;
     const int nft2 = (D.d + 255) / 256;
-    Work* work2 = work + (size_t)c->max_tiles * nft1;          // the down projection's list
+    const bool stream1 = gate_up_streams(&D), stream2 = down_streams(&D);
+    const int units1 = (int)gate_up_units(&D), units2 = (int)down_units(&D);
+    Work* work2 = work + units1;                               // the down projection's list
     int32_t* n_work2 = c->n_tiles + 1;
-    hipLaunchKernelGGL(build_work, dim3(D.E, 2), dim3(256), 0, c->stream, offsets, D.E, nft1, nft2, work, work2,
-                       c->n_tiles);
-    const int grid1 = ((c->max_tiles * nft1 + NXCD - 1) / NXCD) * NXCD;
-    if (perm)
+    hipLaunchKernelGGL(build_work, dim3(D.E, 2), dim3(256), 0, c->stream, offsets, D.E, stream1 ? STREAM_ROWS : TOK_TILE,
+                       stream2 ? STREAM_ROWS : TOK_TILE, nft1, nft2, work, work2, c->n_tiles, stream1 ? c->tickets : nullptr);
+    if (perm && !stream1)                                      // (the streaming kernel gathers the scales itself)
         hipLaunchKernelGGL(gather_scales, dim3((N + 255) / 256, D.d / QBLOCK), dim3(256), 0, c->stream, xs, D.T,
                            perm, D.k, N, c->xs_sorted);
     if (ev) (void)hipEventRecord(ev[0], c->stream);          // the timed interval is the GEMM kernel alone
-    if (perm) {
+    const int grid1 = (units1 + NXCD - 1) / NXCD * NXCD;
+    if (stream1) {
+        // h passes through y_perm: its rows are written by the down projection, after the gate/up projection is done with them
+        hipError_t e = launch_stream_gate_up(c, xq, xs, perm, offsets, work, units1, W1, W3, s1, s3, y_perm);
+        if (e != hipSuccess) return e;
+    } else if (perm) {
         hipLaunchKernelGGL((ffn_gemm<true, true>), dim3(grid1), dim3(NTHREADS), SMEM_BYTES, c->stream, xq, c->xs_sorted, N,
                            perm, D.k, D.T, offsets, work, c->n_tiles, W1, W3, s1, s3, D.d, D.F, c->hq, c->hs,
                            (float*)nullptr);
@@ -800,10 +832,15 @@ hipError_t launch_expert_ffn(moe_ctx* c, const uint8_t* xq, const float* xs, con
                            c->hs, (float*)nullptr);
     }
     if (ev) (void)hipEventRecord(ev[1], c->stream);
-    const int grid2 = ((c->max_tiles * nft2 + NXCD - 1) / NXCD) * NXCD;
-    hipLaunchKernelGGL((ffn_gemm<false, false>), dim3(grid2), dim3(NTHREADS), SMEM_BYTES, c->stream, c->hq, c->hs,
-                       N, (const int32_t*)nullptr, 1, 1, offsets, work2, n_work2, W2, (const uint8_t*)nullptr, s2,
-                       (const float*)nullptr, D.F, D.d, (uint8_t*)nullptr, (float*)nullptr, y_perm);
+    if (stream2) {
+        hipError_t e = launch_stream_down(c, offsets, work2, units2, W2, s2, y_perm);
+        if (e != hipSuccess) return e;
+    } else {
+        const int grid2 = (units2 + NXCD - 1) / NXCD * NXCD;
+        hipLaunchKernelGGL((ffn_gemm<false, false>), dim3(grid2), dim3(NTHREADS), SMEM_BYTES, c->stream, c->hq, c->hs,
+                           N, (const int32_t*)nullptr, 1, 1, offsets, work2, n_work2, W2, (const uint8_t*)nullptr, s2,
+                           (const float*)nullptr, D.F, D.d, (uint8_t*)nullptr, (float*)nullptr, y_perm);
+    }
     if (ev) (void)hipEventRecord(ev[2], c->stream);
     return hipGetLastError();
 }
@@ -818,12 +855,14 @@ hipError_t launch_linear(moe_ctx* c, const uint8_t* xq, const float* xs, int32_t
                          const float* ws, int32_t NOUT, float* y) {
     hipError_t ea = set_lds_limits();
     if (ea != hipSuccess) return ea;
+    if (linear_streams(rows, NOUT)) return launch_stream_linear(c, xq, xs, rows, K, Wq, ws, NOUT, y);
     Work* work = reinterpret_cast<Work*>(c->tiles);
     int32_t* range = c->flags + 2;                             // {0, rows}
     int32_t* n_work = c->n_tiles + 2;
     const int nft = (NOUT + 255) / 256;
     hipLaunchKernelGGL(set_row_range, dim3(1), dim3(1), 0, c->stream, range, rows);
-    hipLaunchKernelGGL(build_work, dim3(1, 1), dim3(256), 0, c->stream, range, 1, nft, nft, work, work, n_work);
+    hipLaunchKernelGGL(build_work, dim3(1, 1), dim3(256), 0, c->stream, range, 1, TOK_TILE, TOK_TILE, nft, nft, work, work, n_work,
+                       (int32_t*)nullptr);
     const int tiles = (rows + TOK_TILE - 1) / TOK_TILE;
     const int grid = ((tiles * nft + NXCD - 1) / NXCD) * NXCD;
     hipLaunchKernelGGL((ffn_gemm<false, false>), dim3(grid), dim3(NTHREADS), SMEM_BYTES, c->stream, xq, xs, rows,

@@ -257,3 +257,42 @@ def test_combine_at_every_fan_out(gpu_lib, k, d):
         assert torch.equal(layer.y.cpu(), sums.cpu().to(torch.bfloat16))
     finally:
         layer.close()
+
+
+@pytest.mark.parametrize("d,F", [(384, 384), (8320, 256), (128, 1152), (640, 384)])
+def test_weight_streaming_tiles(gpu_lib, d, F):
+    """Few rows per expert (a replay log with k = 1): experts of one to three streaming tiles, row counts around one and two
+    groups of 32 columns and around a tile; one to 65 K blocks (fewer than the ring's stages; one more than a wave keeps
+    weight scales for); odd output feature tiles; hidden sizes above d, which leave the gate/up projection on the big tiles."""
+    E = 70 if d <= 640 else 20
+    counts = [1, 2, 31, 32, 33, 63, 64, 65, 96, 129] + [0] * (E - 10)
+    cfg = MoEConfig("stream", T=sum(counts), d=d, E=E, k=1, F=F, modes=("replay",), seed=d + F)
+    rng = np.random.default_rng(cfg.seed)
+    ids = rng.permutation(np.repeat(rng.permutation(cfg.E).astype(np.int32), counts)).reshape(cfg.T, 1)
+    _run_and_check_layer(gpu_lib, cfg, "replay", log=(np.ascontiguousarray(ids), np.ones((cfg.T, 1), dtype=np.float32)))
+
+
+@pytest.mark.parametrize("rows,K,NOUT", [(1, 128, 128), (33, 256, 384), (64, 8320, 640), (65, 384, 256), (300, 1280, 1152)])
+def test_small_linears_equal_the_big_tile_kernel(gpu_lib, rows, K, NOUT):
+    """Dense products small enough for the streaming kernel against the same rows inside a product that takes the big
+    tiles: the same instructions in the same order, so the same bits."""
+    big = 256 * 200                                                     # rows of the large product: over 128 big tiles
+    g = torch.Generator(device="cuda").manual_seed(rows + K)
+    codes = lambda *s: (torch.randn(s, generator=g, device="cuda") * 60).to(torch.float8_e4m3fn).view(torch.uint8)
+    xq, wq = codes(big, K), codes(NOUT, K)
+    xs = torch.rand((K // 128, big), generator=g, device="cuda") + 0.5
+    ws = torch.rand((NOUT // 128, K // 128), generator=g, device="cuda") + 0.5
+    ctx = gpu_lib.moe_create(big, K, 1, 1, 128 * 8)
+    try:
+        y_big = torch.empty((big, NOUT), device="cuda")
+        gpu_lib.moe_linear_fp8(ctx, xq, xs, big, K, wq, ws, NOUT, y_big)
+        y = torch.full((rows, NOUT), float("nan"), device="cuda")
+        gpu_lib.moe_linear_fp8(ctx, xq[:rows].contiguous(), xs[:, :rows].contiguous(), rows, K, wq, ws, NOUT, y)
+        torch.cuda.synchronize()
+        assert torch.equal(y, y_big[:rows])
+        exact = xq[:4].view(torch.float8_e4m3fn).double().view(-1, K // 128, 128) * xs.T[:4, :, None].double()
+        w = wq.view(torch.float8_e4m3fn).double().view(NOUT // 128, 128, K // 128, 128) * ws[:, None, :, None].double()
+        exact = exact.reshape(-1, K) @ w.reshape(NOUT, K).T
+        assert float((y[:4].double() - exact[:rows]).norm() / exact[:rows].norm()) < 1e-4
+    finally:
+        gpu_lib.moe_destroy(ctx)
