@@ -44,25 +44,27 @@ constexpr int X_RING = NW_BUF * W_TILE;            // byte offset of the activat
 constexpr int NTHREADS = 512;
 constexpr int NARROW_ROWS = 64;                     // tiles of at most this many rows take the narrow path of ffn_gemm
 
+// one work unit: rows [row0, row0 + nrows) of an expert x feature tile ft (128 features gate/up, 256 down)
+struct Work { int32_t expert; int32_t row0; int32_t ft; int32_t nrows; };
+
 // ------------------------------------------------------------------ work list
-// An expert with c rows gets ceil(c/tile_rows) row tiles (tile_rows is 256, or 64 for the streaming kernels), ordered (expert, feature tile, row tile).  Units
+// An expert with c rows gets ceil(c/256) row tiles, ordered (expert, feature tile, row tile).  Units
 // that share a weight tile are thus neighbours and, when they do the same amount of work, the blocks
 // that run them side by side on one XCD advance in step and hit each other's lines in that XCD's L2
 // (a few K steps of skew already exceed what the L2 retains, and the shared tile is then fetched
 // again from HBM).
 // Block (e, l) writes the units of expert e into list l (0: gate/up, n_ft0 feature tiles; 1: down,
 // n_ft1 feature tiles); every block recomputes the tile counts of all experts for its base index.
-// tickets (or nullptr): one per unit of list 0, set to zero for the kernel that counts them up.
-__global__ __launch_bounds__(256) void build_work(const int32_t* __restrict__ offsets, int E, int tile_rows0,
-                                                  int tile_rows1, int n_ft0, int n_ft1, Work* __restrict__ work0, Work* __restrict__ work1,
-                                                  int32_t* __restrict__ n_work, int32_t* __restrict__ tickets) {
+__global__ __launch_bounds__(256) void build_work(const int32_t* __restrict__ offsets, int E, int n_ft0,
+                                                  int n_ft1, Work* __restrict__ work0, Work* __restrict__ work1,
+                                                  int32_t* __restrict__ n_work) {
     __shared__ int32_t s_tiles[MAX_E];
     const int tid = threadIdx.x;
     const int e = blockIdx.x;
-    const int n_ft = blockIdx.y == 0 ? n_ft0 : n_ft1, tile_rows = blockIdx.y == 0 ? tile_rows0 : tile_rows1;
+    const int n_ft = blockIdx.y == 0 ? n_ft0 : n_ft1;
     Work* const work = blockIdx.y == 0 ? work0 : work1;
     int nt_t = 0;
-    if (tid < E) nt_t = (offsets[tid + 1] - offsets[tid] + tile_rows - 1) / tile_rows;
+    if (tid < E) nt_t = (offsets[tid + 1] - offsets[tid] + TOK_TILE - 1) / TOK_TILE;
     s_tiles[tid] = nt_t;
     __syncthreads();
     for (int off = 1; off < MAX_E; off <<= 1) {            // inclusive scan
@@ -74,7 +76,7 @@ __global__ __launch_bounds__(256) void build_work(const int32_t* __restrict__ of
     if (e == 0 && tid == 0) n_work[blockIdx.y] = s_tiles[MAX_E - 1] * n_ft;
     if (e >= E) return;
     const int start = offsets[e], cnt = offsets[e + 1] - start;
-    const int nt = (cnt + tile_rows - 1) / tile_rows;
+    const int nt = (cnt + TOK_TILE - 1) / TOK_TILE;
     if (nt == 0) return;
     const int base = (s_tiles[e] - nt) * n_ft;
     for (int idx = tid; idx < nt * n_ft; idx += 256) {
@@ -98,7 +100,6 @@ __global__ __launch_bounds__(256) void build_work(const int32_t* __restrict__ of
         w.ft = f;
         w.nrows = hi - lo;
         work[base + idx] = w;
-        if (tickets && blockIdx.y == 0) tickets[base + idx] = 0;
     }
 }
 
@@ -736,6 +737,7 @@ constexpr size_t SMEM_BYTES = NW_BUF * W_TILE + NX_BUF * X_TILE;   // 160 KiB
 //   linear   16 rows x 1024 32 / 15, 256 x 8192 52 / 22, 128 x 32768 40 / 31, 512 x 16384 57 / 54, 1024 x 8192 58 / 56;
 //            256 big tiles and more than 64 rows (128 x 65536): 73 / 80
 constexpr int64_t GATE_UP_STREAM_ROWS = 8, GATE_UP_STREAM_ROWS_IDLE = 32, DOWN_STREAM_ROWS = 48;
+static_assert(DOWN_STREAM_ROWS >= GATE_UP_STREAM_ROWS_IDLE, "where the gate/up projection streams, the down projection does");
 constexpr int CUS = 256, LINEAR_STREAM_TILES = 128;
 
 static bool gate_up_streams(const moe_dims* D) {
@@ -811,8 +813,10 @@ hipError_t launch_expert_ffn(moe_ctx* c, const uint8_t* xq, const float* xs, con
     const int units1 = (int)gate_up_units(&D), units2 = (int)down_units(&D);
     Work* work2 = work + units1;                               // the down projection's list
     int32_t* n_work2 = c->n_tiles + 1;
-    hipLaunchKernelGGL(build_work, dim3(D.E, 2), dim3(256), 0, c->stream, offsets, D.E, stream1 ? STREAM_ROWS : TOK_TILE,
-                       stream2 ? STREAM_ROWS : TOK_TILE, nft1, nft2, work, work2, c->n_tiles, stream1 ? c->tickets : nullptr);
+    // work lists for what takes the big tiles (the down projection streams wherever the gate/up projection does)
+    if (!stream1)
+        hipLaunchKernelGGL(build_work, dim3(D.E, stream2 ? 1 : 2), dim3(256), 0, c->stream, offsets, D.E, nft1, nft2, work,
+                           work2, c->n_tiles);
     if (perm && !stream1)                                      // (the streaming kernel gathers the scales itself)
         hipLaunchKernelGGL(gather_scales, dim3((N + 255) / 256, D.d / QBLOCK), dim3(256), 0, c->stream, xs, D.T,
                            perm, D.k, N, c->xs_sorted);
@@ -820,7 +824,7 @@ hipError_t launch_expert_ffn(moe_ctx* c, const uint8_t* xq, const float* xs, con
     const int grid1 = (units1 + NXCD - 1) / NXCD * NXCD;
     if (stream1) {
         // h passes through y_perm: its rows are written by the down projection, after the gate/up projection is done with them
-        hipError_t e = launch_stream_gate_up(c, xq, xs, perm, offsets, work, units1, W1, W3, s1, s3, y_perm);
+        hipError_t e = launch_stream_gate_up(c, xq, xs, perm, offsets, units1, W1, W3, s1, s3, y_perm);
         if (e != hipSuccess) return e;
     } else if (perm) {
         hipLaunchKernelGGL((ffn_gemm<true, true>), dim3(grid1), dim3(NTHREADS), SMEM_BYTES, c->stream, xq, c->xs_sorted, N,
@@ -833,7 +837,7 @@ hipError_t launch_expert_ffn(moe_ctx* c, const uint8_t* xq, const float* xs, con
     }
     if (ev) (void)hipEventRecord(ev[1], c->stream);
     if (stream2) {
-        hipError_t e = launch_stream_down(c, offsets, work2, units2, W2, s2, y_perm);
+        hipError_t e = launch_stream_down(c, offsets, units2, W2, s2, y_perm);
         if (e != hipSuccess) return e;
     } else {
         const int grid2 = (units2 + NXCD - 1) / NXCD * NXCD;
@@ -861,8 +865,7 @@ hipError_t launch_linear(moe_ctx* c, const uint8_t* xq, const float* xs, int32_t
     int32_t* n_work = c->n_tiles + 2;
     const int nft = (NOUT + 255) / 256;
     hipLaunchKernelGGL(set_row_range, dim3(1), dim3(1), 0, c->stream, range, rows);
-    hipLaunchKernelGGL(build_work, dim3(1, 1), dim3(256), 0, c->stream, range, 1, TOK_TILE, TOK_TILE, nft, nft, work, work, n_work,
-                       (int32_t*)nullptr);
+    hipLaunchKernelGGL(build_work, dim3(1, 1), dim3(256), 0, c->stream, range, 1, nft, nft, work, work, n_work);
     const int tiles = (rows + TOK_TILE - 1) / TOK_TILE;
     const int grid = ((tiles * nft + NXCD - 1) / NXCD) * NXCD;
     hipLaunchKernelGGL((ffn_gemm<false, false>), dim3(grid), dim3(NTHREADS), SMEM_BYTES, c->stream, xq, xs, rows,

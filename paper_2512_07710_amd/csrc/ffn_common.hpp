@@ -11,9 +11,6 @@ typedef int v4i __attribute__((ext_vector_type(4)));
 constexpr int KB = QBLOCK;                        // K bytes per stage (= one scale block)
 constexpr int NXCD = 8;
 
-// one work unit: rows [row0, row0 + nrows) of an expert x feature tile ft (128 features gate/up, 256 down)
-struct Work { int32_t expert; int32_t row0; int32_t ft; int32_t nrows; };
-
 // Direct global -> LDS copies.  Lane i of the wave deposits its bytes at lds_addr + i*size;
 // the global address is sbase + voff (per lane).  Completion is tracked by vmcnt; the
 // compiler does not see these as memory operations of its own, so every wait on them is

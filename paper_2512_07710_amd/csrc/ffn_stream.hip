@@ -11,7 +11,8 @@
 //   * weights, activations and activation scales all come by direct-to-LDS copies into a ring of D stages (K blocks), D - 2 of
 //     them in flight behind the one being multiplied, one barrier per K block;
 //   * a product is folded into its accumulators while the next K block's operands are read, so that a K step is not a chain
-//     of barrier, operand reads, matrix instructions and multiply-adds;
+//     of barrier, operand reads, matrix instructions and multiply-adds (a second set of operand registers, read a K block
+//     ahead, was slower: the register copies cost more than the overlap);
 //   * activation scales are gathered straight from the token-order planes (a few dozen rows: no sorted copy needed).
 // Gate/up: the scale of a token's 128 hidden features spans the unit's S blocks.  Each block puts its h (fp32) into scratch
 // memory; the last of the S to arrive (an atomic ticket per unit) takes the maximum and writes the codes.  Nobody waits.
@@ -44,10 +45,9 @@ struct StreamArgs {
     int n_rows;
     const int32_t* perm;           // GATHER: sorted row p is token perm[p] / fan
     int fan, n_tok;
-    const Work* work;              // nullptr: one "expert" owns all n_rows rows
-    const int32_t* n_work;
-    const int32_t* offsets;        // of the experts' rows (with work)
-    int32_t* tickets;              // GATED: one per unit, zero before the launch
+    const int32_t* offsets;        // GROUPED: [E+1], of the experts' rows
+    int E;
+    int32_t* tickets;              // GATED: one per unit, zero before and after the launch
     const uint8_t *Wa, *Wb;
     const float *sa, *sb;
     int K, NOUT;
@@ -59,34 +59,97 @@ struct StreamArgs {
     float* y;
 };
 
-template <int NW, int D, bool GATED, bool GATHER>
+// The row tiles of all experts and the units made of them, ordered (expert, feature tile, row tile) as in the big-tile kernel's
+// work list.  Every wave works them out from the offsets in registers: lane l keeps experts 4l .. 4l+3.  (A list written by a
+// kernel of its own costs a launch, 4..5 us of a decode step, and two dependent loads here instead of one.)
+struct Tile { int expert, ft, row0, nrows, tiles; };            // tiles: row tiles of the expert
+template <bool GROUPED>                                        // false: one "expert" owns all n_rows rows
+struct RowTiles {
+    int off[5];                                                // offsets of the lane's experts
+    int before, total;                                         // tiles of the experts before the lane's; of all
+    __device__ RowTiles(const StreamArgs& g, int lane) {
+        if (!GROUPED) {
+            total = (g.n_rows + STREAM_ROWS - 1) / STREAM_ROWS;
+            return;
+        }
+#pragma unroll
+        for (int i = 0; i < 5; ++i) off[i] = g.offsets[min(lane * 4 + i, g.E)];
+        int mine = 0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) mine += count(i);
+        int incl = mine;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const int v = __shfl_up(incl, d);
+            incl += lane >= d ? v : 0;
+        }
+        before = incl - mine;
+        total = __builtin_amdgcn_readlane(incl, 63);
+    }
+    __device__ int count(int i) const { return (off[i + 1] - off[i] + STREAM_ROWS - 1) / STREAM_ROWS; }
+    __device__ Tile find(const StreamArgs& g, int unit, int nft) const {
+        Tile t;
+        if (!GROUPED) {
+            t.expert = 0;
+            t.tiles = total;
+            t.ft = unit / total;
+            t.row0 = (unit - t.ft * total) * STREAM_ROWS;
+            t.nrows = min(STREAM_ROWS, g.n_rows - t.row0);
+            return t;
+        }
+        const int at = unit / nft;                             // a tile of the unit's expert (an expert has tiles * nft units)
+        int end = before + count(0) + count(1) + count(2) + count(3);
+        const int l = __builtin_ctzll(__ballot(end > at));     // at < total: some lane has it
+        int base = __builtin_amdgcn_readlane(before, l), start = 0, cnt = 0;
+        t.expert = 4 * l;
+        t.tiles = 0;
+        bool found = false;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int o = __builtin_amdgcn_readlane(off[i], l), n = __builtin_amdgcn_readlane(off[i + 1], l) - o;
+            const int nt = (n + STREAM_ROWS - 1) / STREAM_ROWS;
+            if (!found && at < base + nt) {
+                found = true;
+                t.expert = 4 * l + i;
+                t.tiles = nt;
+                start = o;
+                cnt = n;
+            }
+            if (!found) base += nt;
+        }
+        const int r = unit - base * nft;
+        t.ft = r / t.tiles;
+        const int i = r - t.ft * t.tiles;
+        // groups of 32 rows dealt out evenly over the expert's tiles
+        const int G = (cnt + 31) / 32;
+        const int lo = min(cnt, 32 * (i * G / t.tiles)), hi = min(cnt, 32 * ((i + 1) * G / t.tiles));
+        t.row0 = start + lo;
+        t.nrows = hi - lo;
+        return t;
+    }
+};
+
+template <int NW, int D, bool GATED, bool GATHER, bool GROUPED>
 __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2))) void ffn_stream(StreamArgs g) {
     constexpr int S = 8 / NW;                                  // blocks per unit
     constexpr int FT = GATED ? 128 : 256;                      // output features per unit
     constexpr int STAGE = stage_bytes(NW);
     extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
 
-    // ---- which block of which unit: XCD x (= blockIdx % 8) walks a contiguous eighth of the list, a unit's blocks side by side
-    const int nft = (g.NOUT + FT - 1) / FT, tiles1 = (g.n_rows + STREAM_ROWS - 1) / STREAM_ROWS;
-    const int total = (g.work ? *g.n_work : tiles1 * nft) * S;
+    // ---- which block of which unit: XCD x (= blockIdx % 8) walks a contiguous eighth of the units, a unit's blocks side by side
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int nft = (g.NOUT + FT - 1) / FT;
+    const RowTiles<GROUPED> tiles(g, lane);
+    const int total = tiles.total * nft * S;
     const int chunk = (total + NXCD - 1) / NXCD;
     const int slot = blockIdx.x / NXCD;
     const int u = (int)(blockIdx.x % NXCD) * chunk + slot;
     if (slot >= chunk || u >= total) return;
     const int unit = u / S;
-    Work wk;
-    if (g.work) wk = g.work[unit];
-    else {
-        const int i = unit % tiles1;
-        wk.expert = 0;
-        wk.ft = unit / tiles1;
-        wk.row0 = i * STREAM_ROWS;
-        wk.nrows = min(STREAM_ROWS, g.n_rows - wk.row0);
-    }
+    const Tile wk = tiles.find(g, unit, nft);
     const int row_end = wk.row0 + wk.nrows;
     const int f0 = wk.ft * FT;
 
-    const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int gw = (u % S) * NW + wave;                        // wave of the unit
     const int l32 = lane & 31, half = lane >> 5;
@@ -230,7 +293,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
     };
     const int n_grp = wk.nrows > 32 ? 2 : 1;
     // non-temporal weight copies where no other row tile of the expert reads them
-    const bool once = g.once && (!g.work || g.offsets[wk.expert + 1] - g.offsets[wk.expert] == wk.nrows);
+    const bool once = g.once && wk.tiles == 1;
     constexpr std::integral_constant<int, 1> one{};
     constexpr std::integral_constant<int, 2> two{};
     if (once) {
@@ -286,6 +349,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
         if (tid == 0) *s_ticket = __hip_atomic_fetch_add(g.tickets + unit, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __syncthreads();
         if (*s_ticket != S - 1) return;
+        if (tid == 0) __hip_atomic_store(g.tickets + unit, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // for the next launch
     }
     // the unit's last block: 16 lanes per row, 8 features each
     for (int r = tid >> 4; r < wk.nrows; r += NW * 4) {        // (the 16 lanes of a row share r)
@@ -329,43 +393,44 @@ constexpr int WAVES = 4, STAGES = 3;
 // 17.0 when it is still there), beyond it cannot.
 constexpr int64_t LINEAR_ONCE_BYTES = 256ll << 20;
 
-template <bool GATED, bool GATHER>
+template <bool GATED, bool GATHER, bool GROUPED>
 hipError_t launch(hipStream_t stream, const StreamArgs& a, int max_units) {
     static bool attr_set = false;
     if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&ffn_stream<WAVES, STAGES, GATED, GATHER>),
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&ffn_stream<WAVES, STAGES, GATED, GATHER, GROUPED>),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, STAGES * stage_bytes(WAVES));
         if (e != hipSuccess) return e;
         attr_set = true;
     }
     const int grid = (max_units * (8 / WAVES) + NXCD - 1) / NXCD * NXCD;
-    hipLaunchKernelGGL((ffn_stream<WAVES, STAGES, GATED, GATHER>), dim3(grid), dim3(WAVES * 64), STAGES * stage_bytes(WAVES), stream, a);
+    hipLaunchKernelGGL((ffn_stream<WAVES, STAGES, GATED, GATHER, GROUPED>), dim3(grid), dim3(WAVES * 64), STAGES * stage_bytes(WAVES), stream, a);
     return hipGetLastError();
 }
 
 }  // namespace
 
-hipError_t launch_stream_gate_up(moe_ctx* c, const uint8_t* xq, const float* xs, const int32_t* perm, const int32_t* offsets, const Work* work,
+hipError_t launch_stream_gate_up(moe_ctx* c, const uint8_t* xq, const float* xs, const int32_t* perm, const int32_t* offsets,
                                  int max_units, const uint8_t* W1, const uint8_t* W3, const float* s1, const float* s3,
                                  float* scratch) {
     const moe_dims& D = c->dims;
-    const StreamArgs a{xq, xs, D.T * D.k, perm, D.k, D.T, work, c->n_tiles, offsets, c->tickets, W1, W3, s1, s3, D.d, D.F,
+    const StreamArgs a{xq, xs, D.T * D.k, perm, D.k, D.T, offsets, D.E, c->tickets, W1, W3, s1, s3, D.d, D.F,
                        true, scratch, D.d, c->hq, c->hs, nullptr};
-    return perm ? launch<true, true>(c->stream, a, max_units) : launch<true, false>(c->stream, a, max_units);
+    return perm ? launch<true, true, true>(c->stream, a, max_units) : launch<true, false, true>(c->stream, a, max_units);
 }
 
-hipError_t launch_stream_down(moe_ctx* c, const int32_t* offsets, const Work* work, int max_units, const uint8_t* W2, const float* s2, float* y_perm) {
+hipError_t launch_stream_down(moe_ctx* c, const int32_t* offsets, int max_units, const uint8_t* W2, const float* s2,
+                              float* y_perm) {
     const moe_dims& D = c->dims;
-    const StreamArgs a{c->hq, c->hs, D.T * D.k, nullptr, 1, 1, work, c->n_tiles + 1, offsets, nullptr, W2, nullptr, s2, nullptr, D.F, D.d,
+    const StreamArgs a{c->hq, c->hs, D.T * D.k, nullptr, 1, 1, offsets, D.E, nullptr, W2, nullptr, s2, nullptr, D.F, D.d,
                        true, nullptr, 0, nullptr, nullptr, y_perm};
-    return launch<false, false>(c->stream, a, max_units);
+    return launch<false, false, true>(c->stream, a, max_units);
 }
 
 hipError_t launch_stream_linear(moe_ctx* c, const uint8_t* xq, const float* xs, int32_t rows, int32_t K, const uint8_t* Wq,
                                 const float* ws, int32_t NOUT, float* y) {
-    const StreamArgs a{xq, xs, rows, nullptr, 1, 1, nullptr, nullptr, nullptr, nullptr, Wq, nullptr, ws, nullptr, K, NOUT,
+    const StreamArgs a{xq, xs, rows, nullptr, 1, 1, nullptr, 1, nullptr, Wq, nullptr, ws, nullptr, K, NOUT,
                        rows <= STREAM_ROWS && (int64_t)K * NOUT > LINEAR_ONCE_BYTES, nullptr, 0, nullptr, nullptr, y};
-    return launch<false, false>(c->stream, a, (rows + STREAM_ROWS - 1) / STREAM_ROWS * ((NOUT + 255) / 256));
+    return launch<false, false, false>(c->stream, a, (rows + STREAM_ROWS - 1) / STREAM_ROWS * ((NOUT + 255) / 256));
 }
 
 }  // namespace moe355

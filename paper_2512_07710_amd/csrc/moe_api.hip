@@ -78,6 +78,8 @@ int moe_create(moe_ctx** out, const moe_dims* dims, void* hip_stream) {
     ok = ok && hipMalloc((void**)&c->hs, nrow * (size_t)(dims->F / QBLOCK) * sizeof(float)) == hipSuccess;
     ok = ok && launch_fill_i32(c->stream, c->flags, 4, 0) == hipSuccess;
     ok = ok && launch_fill_i32(c->stream, c->n_tiles, 4, 0) == hipSuccess;
+    if (c->tickets)
+        ok = ok && launch_fill_i32(c->stream, c->tickets, (int)(ffn_ticket_bytes(dims) / sizeof(int32_t)), 0) == hipSuccess;
     if (!ok) {
         (void)hipGetLastError();
         moe_destroy(c);

@@ -26,7 +26,7 @@ struct moe_ctx {
     int32_t* chunk_counts;   // [n_chunks][E] per-chunk histograms, then their exclusive scans
     void* tiles;             // GEMM work lists (gate/up list, then down list)
     int32_t* n_tiles;        // [2] their lengths
-    int32_t* tickets;        // streaming gate/up projection only: one per work unit
+    int32_t* tickets;        // streaming gate/up projection only: one per unit, zero between launches
     int32_t* flags;          // [4] flags[0] != 0: an expert id outside [0,E) was met; flags[1] != 0: a logged id repeated
                              //     inside a token; [2..3]: row range of a dense linear
     float* xs_sorted;        // [d/128][N] activation scales in sorted order (gathered FFN only)
@@ -72,15 +72,14 @@ hipError_t launch_linear(moe_ctx* c, const uint8_t* xq, const float* xs, int32_t
                          const uint8_t* Wq, const float* ws, int32_t NOUT, float* y);
 hipError_t launch_quantize_weights(hipStream_t s, const uint16_t* w, int64_t rows, int32_t cols, uint8_t* q,
                                    float* scales);
-struct Work;
 size_t ffn_work_bytes(const moe_dims* D);
 size_t ffn_ticket_bytes(const moe_dims* D);
 // The weight-streaming GEMMs (ffn_stream.hip).  perm as in launch_expert_ffn; scratch: [N][d] f32, overwritten
-hipError_t launch_stream_gate_up(moe_ctx* c, const uint8_t* xq, const float* xs, const int32_t* perm, const int32_t* offsets, const Work* work,
+hipError_t launch_stream_gate_up(moe_ctx* c, const uint8_t* xq, const float* xs, const int32_t* perm, const int32_t* offsets,
                                  int max_units, const uint8_t* W1, const uint8_t* W3, const float* s1, const float* s3,
                                  float* scratch);
-hipError_t launch_stream_down(moe_ctx* c, const int32_t* offsets, const Work* work, int max_units, const uint8_t* W2,
-                              const float* s2, float* y_perm);
+hipError_t launch_stream_down(moe_ctx* c, const int32_t* offsets, int max_units, const uint8_t* W2, const float* s2,
+                              float* y_perm);
 hipError_t launch_stream_linear(moe_ctx* c, const uint8_t* xq, const float* xs, int32_t rows, int32_t K, const uint8_t* Wq,
                                 const float* ws, int32_t NOUT, float* y);
 size_t route_workspace_bytes(int E, int d);
