@@ -458,18 +458,48 @@ __global__ __launch_bounds__(256, 1) void route_mfma_kernel(const uint16_t* __re
     }
 }
 
+// wave-wide reductions on the vector ALU's lane shifts; the result is in lane 63 (broadcast by the callers)
+template <int CTRL, int ROWS>
+__device__ inline float lanes_of(float otherwise, float v) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(otherwise), __float_as_int(v), CTRL, ROWS, 0xf, false));
+}
+__device__ inline float lane_value(float v, int lane) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane)); }
+__device__ inline float wave_max(float v) {
+    v = fmaxf(v, lanes_of<0x111, 0xf>(v, v));                  // row_shr 1, 2, 4, 8: rows of 16 lanes
+    v = fmaxf(v, lanes_of<0x112, 0xf>(v, v));
+    v = fmaxf(v, lanes_of<0x114, 0xf>(v, v));
+    v = fmaxf(v, lanes_of<0x118, 0xf>(v, v));
+    v = fmaxf(v, lanes_of<0x142, 0xa>(v, v));                  // row_bcast 15, 31: over the rows
+    v = fmaxf(v, lanes_of<0x143, 0xc>(v, v));
+    return lane_value(v, 63);
+}
+__device__ inline float wave_sum_63(float v) {                 // (left in lane 63)
+    v += lanes_of<0x111, 0xf>(0.f, v);
+    v += lanes_of<0x112, 0xf>(0.f, v);
+    v += lanes_of<0x114, 0xf>(0.f, v);
+    v += lanes_of<0x118, 0xf>(0.f, v);
+    v += lanes_of<0x142, 0xa>(0.f, v);
+    v += lanes_of<0x143, 0xc>(0.f, v);
+    return v;
+}
+
 // Second half of the split router: one wave per token adds the partial logits up in split order, then
 // selects as the single-pass kernel does (larger score, then lower expert index; softmax over the k selected
 // unbiased logits, exponentials summed in slot order) or, with logged ids, picks their logits.  Lane l holds
 // experts l, l+64, l+128, l+192.
+// A round is the wave's largest score, by lane shifts, and the lowest expert that has it, by ballots: both stay on the
+// vector and scalar units.  (Twelve LDS-routed shuffles a round, and two more per slot in the softmax, made this chain 9.3 us
+// for one token of k = 6 and 12.7 for sixteen of k = 8 over 256 experts; it takes 5.6 and 8.8.)
 template <bool IDS>
 __global__ __launch_bounds__(256) void route_finish_kernel(const float* __restrict__ partial, int splits, int T_pad,
                                                            int E_pad, const float* __restrict__ bias,
                                                            const int32_t* __restrict__ logged_idx, int T, int E, int k,
                                                            int32_t* __restrict__ topk_idx, float* __restrict__ topk_w) {
     const int lane = threadIdx.x & 63;
-    const int t = blockIdx.x * 4 + (threadIdx.x >> 6);
+    const int t = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     if (t >= T) return;                                        // wave-uniform
+    int id = NO_CAND;                                          // lane j < k: the j-th selected expert
+    if (IDS && lane < k) id = logged_idx[(size_t)t * k + lane];
     float lg[4], sc[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -487,40 +517,43 @@ __global__ __launch_bounds__(256) void route_finish_kernel(const float* __restri
         sc[i] = e < E ? v + (bias ? bias[e] : 0.f) : -INFINITY;
     }
     float sel = 0.f;                                           // lane j < k: the j-th selected logit
+    float m = -INFINITY;
     for (int j = 0; j < k; ++j) {
-        int be;
+        int be = NO_CAND;
         if (IDS) {
-            be = logged_idx[(size_t)t * k + j];
+            be = __builtin_amdgcn_readlane(id, j);
         } else {
-            float bs = -INFINITY;
-            be = NO_CAND;
+            const float bs = wave_max(fmaxf(fmaxf(sc[0], sc[1]), fmaxf(sc[2], sc[3])));
+            if (bs > -INFINITY) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
-                if (sc[i] > bs) { bs = sc[i]; be = lane + 64 * i; }       // ascending index: ties keep the lower one
-#pragma unroll
-            for (int off = 1; off < 64; off <<= 1) {
-                const float os = __shfl_xor(bs, off);
-                const int oe = __shfl_xor(be, off);
-                if (os > bs || (os == bs && oe < be)) { bs = os; be = oe; }
+                for (int i = 3; i >= 0; --i) {                 // the lowest expert with that score is kept
+                    const uint64_t has = __ballot(sc[i] == bs);
+                    if (has) be = 64 * i + __builtin_ctzll(has);
+                }
             }
         }
         const bool valid = be >= 0 && be < E;                  // wave-uniform (ids outside [0,E) keep logit 0)
         const int slot = valid ? be >> 6 : 0;
         const float mine = slot == 0 ? lg[0] : slot == 1 ? lg[1] : slot == 2 ? lg[2] : lg[3];
-        const float chosen = valid ? __shfl(mine, be & 63) : 0.f;
+        const float chosen = valid ? lane_value(mine, be & 63) : 0.f;
         if (!IDS && valid && lane == (be & 63)) {
 #pragma unroll
             for (int i = 0; i < 4; ++i)
                 if (i == slot) sc[i] = -INFINITY;
         }
-        if (lane == j) sel = chosen;
-        if (lane == 0) topk_idx[(size_t)t * k + j] = be;
+        if (lane == j) {
+            sel = chosen;
+            id = be;
+        }
+        m = fmaxf(m, chosen);
     }
-    float m = -INFINITY;
-    for (int j = 0; j < k; ++j) m = fmaxf(m, __shfl(sel, j));
+    const float ex = expf(sel - m);
     float sum = 0.f;
-    for (int j = 0; j < k; ++j) sum += expf(__shfl(sel, j) - m);
-    if (lane < k) topk_w[(size_t)t * k + lane] = expf(sel - m) / sum;
+    for (int j = 0; j < k; ++j) sum += lane_value(ex, j);
+    if (lane < k) {
+        topk_idx[(size_t)t * k + lane] = id;
+        topk_w[(size_t)t * k + lane] = ex / sum;
+    }
 }
 
 }  // namespace
