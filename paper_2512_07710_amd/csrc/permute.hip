@@ -10,8 +10,8 @@
 //      from a log are also checked here: an id outside [0,E) raises flags[0], an id that repeats an
 //      earlier slot of the same token raises flags[1] (the permutation is still the stable sort of
 //      what was given).
-// The result is unique (stable), so it can be compared bit for bit.  Batches of at most PERM_CHUNK
-// assignments take one fused launch instead (permute_one_chunk).
+// The result is unique (stable), so it can be compared bit for bit.  Batches of at most ONE_BLOCK_MAX_N
+// assignments take one fused launch instead (permute_one_block).
 #include "moe_internal.hpp"
 
 #include <mutex>
@@ -174,34 +174,43 @@ __global__ __launch_bounds__(256) void scatter(const int32_t* __restrict__ ids, 
     perm[pos] = i;
 }
 
-// N <= PERM_CHUNK: the three steps in one block and one launch (decode-sized batches, where the launches
-// themselves are most of the time).  Same ranking as chunk_hist_rank, then the scan over experts and the
-// scatter from registers.
-__global__ __launch_bounds__(256) void permute_one_chunk(const int32_t* __restrict__ ids, int N, int E,
-                                                         int32_t* __restrict__ ids_copy,
-                                                         const float* __restrict__ w_in, float* __restrict__ w_copy,
-                                                         int32_t* __restrict__ offsets, int32_t* __restrict__ perm,
-                                                         int32_t* __restrict__ inv_perm, int k, bool check_dups,
-                                                         int32_t* __restrict__ flags) {
-    constexpr int PER_WAVE = PERM_CHUNK / 4;
-    __shared__ int32_t s_cnt[4][MAX_E];
-    __shared__ int32_t s_off[MAX_E];                  // inclusive scan of the expert totals
+// N <= ONE_BLOCK_MAX_N: the three steps in one block and one launch, where the launches themselves are most of the time.  Sixteen
+// waves rank STEPS times 64 entries each in the manner of chunk_hist_rank, then scan over the experts and scatter from
+// registers; bound by its chain of barriers and memory round trips.  3885 assignments take 9.1 us
+// (the three kernels 16.1), 1536 take 4.8 and 6 take 2.7 (one block of four waves: 6.8 and 4.6).
+constexpr int ONE_BLOCK_WAVES = 16;
+constexpr int ONE_BLOCK_MAX_STEPS = 8;
+constexpr int ONE_BLOCK_MAX_N = ONE_BLOCK_WAVES * ONE_BLOCK_MAX_STEPS * 64;
+
+template <int STEPS>
+__global__ __launch_bounds__(ONE_BLOCK_WAVES * 64) void permute_one_block(
+    const int32_t* __restrict__ ids, int N, int E, int32_t* __restrict__ ids_copy, const float* __restrict__ w_in,
+    float* __restrict__ w_copy, int32_t* __restrict__ offsets, int32_t* __restrict__ perm, int32_t* __restrict__ inv_perm,
+    int k, bool check_dups, int32_t* __restrict__ flags) {
+    constexpr int PER_WAVE = STEPS * 64;
+    __shared__ int32_t s_cnt[ONE_BLOCK_WAVES][MAX_E];
+    __shared__ int32_t s_off[MAX_E];                  // exclusive scan of the expert totals
+    __shared__ int32_t s_part[MAX_E / 64];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    for (int i = tid; i < 4 * MAX_E; i += 256) (&s_cnt[0][0])[i] = 0;
-    __syncthreads();
-    int32_t my_id[PER_WAVE / 64], my_rank[PER_WAVE / 64];
-    const uint64_t lower = (1ull << lane) - 1ull;
+    int32_t my_id[STEPS], my_rank[STEPS];
 #pragma unroll
-    for (int st = 0; st < PER_WAVE / 64; ++st) {
+    for (int st = 0; st < STEPS; ++st) {
         const int i = wave * PER_WAVE + st * 64 + lane;
-        int32_t v = -1;
+        my_id[st] = -1;
         if (i < N) {
-            v = ids[i];
-            if (ids_copy) ids_copy[i] = v;
+            my_id[st] = ids[i];
             if (w_copy) w_copy[i] = w_in[i];
         }
+    }
+    for (int i = tid; i < ONE_BLOCK_WAVES * MAX_E; i += ONE_BLOCK_WAVES * 64) (&s_cnt[0][0])[i] = 0;
+    __syncthreads();
+    const uint64_t lower = (1ull << lane) - 1ull;
+#pragma unroll
+    for (int st = 0; st < STEPS; ++st) {
+        const int i = wave * PER_WAVE + st * 64 + lane;
+        const int32_t v = my_id[st];
+        if (ids_copy && i < N) ids_copy[i] = v;
         const bool valid = v >= 0 && v < E;
-        my_id[st] = v;
         const int key = v & (MAX_E - 1);
         uint64_t same = __ballot(valid);
         if (!valid) same = ~same;
@@ -215,27 +224,33 @@ __global__ __launch_bounds__(256) void permute_one_chunk(const int32_t* __restri
         if (valid && (same & lower) == 0ull) s_cnt[wave][key] = before + __popcll(same);
     }
     __syncthreads();
-    {
-        int run = 0;                                  // thread e: per-wave bases and the total of expert e
+    int total = 0, incl = 0;
+    if (tid < MAX_E) {                                // thread e: per-wave bases and the total of expert e
 #pragma unroll
-        for (int w = 0; w < 4; ++w) {
+        for (int w = 0; w < ONE_BLOCK_WAVES; ++w) {
             const int c = s_cnt[w][tid];
-            s_cnt[w][tid] = run;
-            run += c;
+            s_cnt[w][tid] = total;
+            total += c;
         }
-        s_off[tid] = (tid < E) ? run : 0;
+        if (tid >= E) total = 0;
+        incl = total;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const int v = __shfl_up(incl, off);
+            incl += lane >= off ? v : 0;
+        }
+        if (lane == 63) s_part[wave] = incl;
     }
     __syncthreads();
-    for (int off = 1; off < MAX_E; off <<= 1) {       // inclusive scan over experts
-        const int add = (tid >= off) ? s_off[tid - off] : 0;
-        __syncthreads();
-        s_off[tid] += add;
-        __syncthreads();
+    if (tid < MAX_E) {
+        for (int w = 0; w < wave; ++w) incl += s_part[w];
+        s_off[tid] = incl - total;
+        if (tid < E) offsets[tid + 1] = incl;
+        if (tid == 0) offsets[0] = 0;
     }
-    if (tid < E) offsets[tid + 1] = s_off[tid];
-    if (tid == 0) offsets[0] = 0;
+    __syncthreads();
 #pragma unroll
-    for (int st = 0; st < PER_WAVE / 64; ++st) {
+    for (int st = 0; st < STEPS; ++st) {
         const int i = wave * PER_WAVE + st * 64 + lane;
         if (i >= N) continue;
         const int e = my_id[st];
@@ -250,7 +265,7 @@ __global__ __launch_bounds__(256) void permute_one_chunk(const int32_t* __restri
             for (int q = first; q < i; ++q) dup |= ids[q] == e;
             if (dup) flags[1] = 1;
         }
-        const int pos = (e ? s_off[e - 1] : 0) + s_cnt[wave][e] + my_rank[st];
+        const int pos = s_off[e] + s_cnt[wave][e] + my_rank[st];
         inv_perm[i] = pos;
         perm[pos] = i;
     }
@@ -273,9 +288,16 @@ hipError_t launch_permute(const permute_args& a, const int32_t* ids_in, int32_t*
                           float* w_copy, int32_t* offsets, int32_t* perm, int32_t* inv_perm) {
     const int N = a.T * a.k;
     const int n_chunks = (N + PERM_CHUNK - 1) / PERM_CHUNK;
-    if (n_chunks == 1) {
-        hipLaunchKernelGGL(permute_one_chunk, dim3(1), dim3(256), 0, a.stream, ids_in, N, a.E, ids_copy, w_in, w_copy,
-                           offsets, perm, inv_perm, a.k, a.check_dups, a.flags);
+    if (N > 0 && N <= ONE_BLOCK_MAX_N) {
+#define MOE_ONE_BLOCK(STEPS_)                                                                                              \
+    hipLaunchKernelGGL(permute_one_block<STEPS_>, dim3(1), dim3(ONE_BLOCK_WAVES * 64), 0, a.stream, ids_in, N, a.E, ids_copy, \
+                       w_in, w_copy, offsets, perm, inv_perm, a.k, a.check_dups, a.flags)
+        const int steps = (N + ONE_BLOCK_WAVES * 64 - 1) / (ONE_BLOCK_WAVES * 64);
+        if (steps == 1) MOE_ONE_BLOCK(1);
+        else if (steps == 2) MOE_ONE_BLOCK(2);
+        else if (steps <= 4) MOE_ONE_BLOCK(4);
+        else MOE_ONE_BLOCK(ONE_BLOCK_MAX_STEPS);
+#undef MOE_ONE_BLOCK
         return hipGetLastError();
     }
     if (n_chunks > 0)
