@@ -386,14 +386,17 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
 // Four waves and three stages: two blocks of 75 KB share a CU.  On the same buffers (gate/up, 64 experts x 4096 x 1408 and more):
 // two waves and three or four stages measure the same with few units and 5 % more time in a full grid, one wave 10 % more,
 // five stages (one block per CU) the same or worse.
-constexpr int WAVES = 4, STAGES = 3;
+constexpr int NW = 4, D = 3;
+// A dense product of at most 64 units leaves half of the CUs idle in blocks of four waves: two waves and four stages
+// (40 rows x 4096 x 6144: 18.6 -> 17.4 us, 256 rows x 4096: 20.6 -> 18.9; 128 units: 22.3 -> 24.0).
+constexpr int NW_FEW = 2, D_FEW = 4, FEW_UNITS = 64;
 // Weights that are read once go past the caches: a whole layer's experts never stay in the 256 MB last-level cache until the
 // next step of a model (one sequence, 104 MB of weights, after other data: 76 us for the layer through the caches, 67 past
 // them).  A dense matrix of up to this size may well stay (40 rows x 4096 x 6144: 25.4 and 24.4 us after other data, 16.6 and
 // 17.0 when it is still there), beyond it cannot.
 constexpr int64_t LINEAR_ONCE_BYTES = 256ll << 20;
 
-template <bool GATED, bool GATHER, bool GROUPED>
+template <int WAVES, int STAGES, bool GATED, bool GATHER, bool GROUPED>
 hipError_t launch(hipStream_t stream, const StreamArgs& a, int max_units) {
     static bool attr_set = false;
     if (!attr_set) {
@@ -412,25 +415,27 @@ hipError_t launch(hipStream_t stream, const StreamArgs& a, int max_units) {
 hipError_t launch_stream_gate_up(moe_ctx* c, const uint8_t* xq, const float* xs, const int32_t* perm, const int32_t* offsets,
                                  int max_units, const uint8_t* W1, const uint8_t* W3, const float* s1, const float* s3,
                                  float* scratch) {
-    const moe_dims& D = c->dims;
-    const StreamArgs a{xq, xs, D.T * D.k, perm, D.k, D.T, offsets, D.E, c->tickets, W1, W3, s1, s3, D.d, D.F,
-                       true, scratch, D.d, c->hq, c->hs, nullptr};
-    return perm ? launch<true, true, true>(c->stream, a, max_units) : launch<true, false, true>(c->stream, a, max_units);
+    const moe_dims& m = c->dims;
+    const StreamArgs a{xq, xs, m.T * m.k, perm, m.k, m.T, offsets, m.E, c->tickets, W1, W3, s1, s3, m.d, m.F,
+                       true, scratch, m.d, c->hq, c->hs, nullptr};
+    return perm ? launch<NW, D, true, true, true>(c->stream, a, max_units) : launch<NW, D, true, false, true>(c->stream, a, max_units);
 }
 
 hipError_t launch_stream_down(moe_ctx* c, const int32_t* offsets, int max_units, const uint8_t* W2, const float* s2,
                               float* y_perm) {
-    const moe_dims& D = c->dims;
-    const StreamArgs a{c->hq, c->hs, D.T * D.k, nullptr, 1, 1, offsets, D.E, nullptr, W2, nullptr, s2, nullptr, D.F, D.d,
+    const moe_dims& m = c->dims;
+    const StreamArgs a{c->hq, c->hs, m.T * m.k, nullptr, 1, 1, offsets, m.E, nullptr, W2, nullptr, s2, nullptr, m.F, m.d,
                        true, nullptr, 0, nullptr, nullptr, y_perm};
-    return launch<false, false, true>(c->stream, a, max_units);
+    return launch<NW, D, false, false, true>(c->stream, a, max_units);
 }
 
 hipError_t launch_stream_linear(moe_ctx* c, const uint8_t* xq, const float* xs, int32_t rows, int32_t K, const uint8_t* Wq,
                                 const float* ws, int32_t NOUT, float* y) {
     const StreamArgs a{xq, xs, rows, nullptr, 1, 1, nullptr, 1, nullptr, Wq, nullptr, ws, nullptr, K, NOUT,
                        rows <= STREAM_ROWS && (int64_t)K * NOUT > LINEAR_ONCE_BYTES, nullptr, 0, nullptr, nullptr, y};
-    return launch<false, false, false>(c->stream, a, (rows + STREAM_ROWS - 1) / STREAM_ROWS * ((NOUT + 255) / 256));
+    const int units = (rows + STREAM_ROWS - 1) / STREAM_ROWS * ((NOUT + 255) / 256);
+    return units <= FEW_UNITS ? launch<NW_FEW, D_FEW, false, false, false>(c->stream, a, units)
+                              : launch<NW, D, false, false, false>(c->stream, a, units);
 }
 
 }  // namespace moe355
