@@ -47,6 +47,24 @@ constexpr int NARROW_ROWS = 64;                     // tiles of at most this man
 // one work unit: rows [row0, row0 + nrows) of an expert x feature tile ft (128 features gate/up, 256 down)
 struct Work { int32_t expert; int32_t row0; int32_t ft; int32_t nrows; };
 
+// Rows [row0, row0 + nrows) of tile i when `rows` rows make nt tiles.
+// The expert's G = ceil(cnt/32) groups of 32 rows are dealt out evenly: tile i covers groups [i*G/nt, (i+1)*G/nt).
+// The tiles that share a weight tile are then within one group of each other: they advance nearly in step and
+// fetch it once, only the expert's last group is partly filled, and a tile's matrix time follows its height.
+// With the groups of 64 of a layout whose short tiles left whole waves idle (so that every tile cost the time
+// of a full one) the gate/up projection took 1.98 ms at 1030 rows per expert and takes 1.82, at 258 rows
+// 0.81 -> 0.71 ms, at 896..1152 rows 1.94 -> 1.87 ms (d = 7168, F = 2048, 64 experts; 258: d = 5120, F = 1536,
+// 128 experts); at full tiles nothing changes.  The down projection is 6 % faster at 258 rows, 3 % at 960, and
+// 3..5 % slower at 1030..1152; cutting its remainder off as one short tile measures the same as dealing evenly.
+// A remainder of at most 64 rows as a NARROW tile does not pay in the gate/up projection: it runs ahead of the
+// tiles it shares the weight tile with, and the weight tile is fetched twice (8 % slower at 248..264 rows).
+__device__ inline void split_rows(int rows, int nt, int i, Work& w) {
+    const int64_t G = (rows + 31) / 32;
+    const int lo = min(rows, 32 * (int)(i * G / nt)), hi = min(rows, 32 * (int)((i + 1) * G / nt));
+    w.row0 = lo;
+    w.nrows = hi - lo;
+}
+
 // ------------------------------------------------------------------ work list
 // An expert with c rows gets ceil(c/256) row tiles, ordered (expert, feature tile, row tile).  Units
 // that share a weight tile are thus neighbours and, when they do the same amount of work, the blocks
@@ -81,24 +99,11 @@ __global__ __launch_bounds__(256) void build_work(const int32_t* __restrict__ of
     const int base = (s_tiles[e] - nt) * n_ft;
     for (int idx = tid; idx < nt * n_ft; idx += 256) {
         const int f = idx / nt, i = idx - f * nt;
-        // The expert's G = ceil(cnt/32) groups of 32 rows are dealt out evenly: tile i covers groups [i*G/nt, (i+1)*G/nt).
-        // The tiles that share a weight tile are then within one group of each other: they advance nearly in step and
-        // fetch it once, only the expert's last group is partly filled, and a tile's matrix time follows its height.
-        // With the groups of 64 of a layout whose short tiles left whole waves idle (so that every tile cost the time
-        // of a full one) the gate/up projection took 1.98 ms at 1030 rows per expert and takes 1.82, at 258 rows
-        // 0.81 -> 0.71 ms, at 896..1152 rows 1.94 -> 1.87 ms (d = 7168, F = 2048, 64 experts; 258: d = 5120, F = 1536,
-        // 128 experts); at full tiles nothing changes.  The down projection is 6 % faster at 258 rows, 3 % at 960, and
-        // 3..5 % slower at 1030..1152; cutting its remainder off as one short tile measures the same as dealing evenly.
-        // A remainder of at most 64 rows as a NARROW tile does not pay in the gate/up projection: it runs ahead of the
-        // tiles it shares the weight tile with, and the weight tile is fetched twice (8 % slower at 248..264 rows).
-        const int G = (cnt + 31) / 32;
-        const int lo = min(cnt, 32 * (int)((int64_t)i * G / nt));
-        const int hi = min(cnt, 32 * (int)((int64_t)(i + 1) * G / nt));
         Work w;
+        split_rows(cnt, nt, i, w);
         w.expert = e;
-        w.row0 = start + lo;
+        w.row0 += start;
         w.ft = f;
-        w.nrows = hi - lo;
         work[base + idx] = w;
     }
 }
@@ -370,7 +375,7 @@ __device__ __forceinline__ void k_loop(const Tile& t, const Feed& f, v16f (&acc)
 // expert-ordered copy of the codes is never materialised.  The scales act_s
 // [K/128][n_rows] are in sorted order in both cases (they are 1/128 of the data; a lane-scattered
 // scale read per K step would cost more than it saves).
-template <bool GATED, bool GATHER>
+template <bool GATED, bool GATHER, bool LINEAR>
 __global__ __launch_bounds__(NTHREADS, 1) void ffn_gemm(const uint8_t* __restrict__ act,
                                                         const float* __restrict__ act_s, int n_rows,
                                                         const int32_t* __restrict__ perm, int fan, int n_tok,
@@ -390,12 +395,21 @@ __global__ __launch_bounds__(NTHREADS, 1) void ffn_gemm(const uint8_t* __restric
     float* const s_amax = reinterpret_cast<float*>(smem);
 
     // ---- which work unit: XCD x (= blockIdx % 8) walks the contiguous range [x*chunk, (x+1)*chunk)
-    const int total = *n_work;
+    // (LINEAR: one "expert" owns all n_rows rows, and the unit is worked out here instead of read from a list)
+    const int tiles = (n_rows + TOK_TILE - 1) / TOK_TILE;
+    const int total = LINEAR ? tiles * ((NOUT + FT - 1) / FT) : *n_work;
     const int chunk = (total + NXCD - 1) / NXCD;
     const int slot = blockIdx.x / NXCD;
     const int wi = (blockIdx.x % NXCD) * chunk + slot;
     if (slot >= chunk || wi >= total) return;
-    const Work wk = work[wi];
+    Work wk;
+    if (LINEAR) {
+        wk.expert = 0;
+        wk.ft = wi / tiles;
+        split_rows(n_rows, tiles, wi - wk.ft * tiles, wk);
+    } else {
+        wk = work[wi];
+    }
     const int e = wk.expert;
     const int row_end = wk.row0 + wk.nrows;                    // this tile's rows only
     const int f0 = wk.ft * FT;
@@ -734,8 +748,8 @@ constexpr size_t SMEM_BYTES = NW_BUF * W_TILE + NX_BUF * X_TILE;   // 160 KiB
 //   gate/up  rows per expert 2: 1026 / 1006 (256 experts), 3: 163 / 142, 6: 136 / 133, 12: 129.5 / 133, 16: 251..287 / 274..287
 //            and, where the tiles leave compute units idle: 96 units, 4 rows 35 / 23, 32 rows 33 / 28; 384 units, 8 rows 79 / 68
 //   down     rows per expert 6: 75 / 68, 16: 75 / 70, 24: 78 / 74, 32: 81 / 78, 48: 85 / 82, 64: 188 / 202
-//   linear   16 rows x 1024 32 / 15, 256 x 8192 52 / 22, 128 x 32768 40 / 31, 512 x 16384 57 / 54, 1024 x 8192 58 / 56;
-//            256 big tiles and more than 64 rows (128 x 65536): 73 / 80
+//   linear   (K = 4096) 16 rows x 1024 features 28 / 13, 256 x 8192 48 / 22, 256 x 24576 50 / 45, 128 x 32768 36 / 31; at 128
+//            big tiles level (512 x 16384 53.6 / 53.8, 1024 x 8192 55.7 / 56.0); 256 of more than 64 rows (128 x 65536): 69 / 80
 constexpr int64_t GATE_UP_STREAM_ROWS = 8, GATE_UP_STREAM_ROWS_IDLE = 32, DOWN_STREAM_ROWS = 48;
 static_assert(DOWN_STREAM_ROWS >= GATE_UP_STREAM_ROWS_IDLE, "where the gate/up projection streams, the down projection does");
 constexpr int CUS = 256, LINEAR_STREAM_TILES = 128;
@@ -761,20 +775,17 @@ static int64_t max_row_tiles(const moe_dims* D, bool streams) {
 static int64_t gate_up_units(const moe_dims* D) { return max_row_tiles(D, gate_up_streams(D)) * (D->F / 128); }
 static int64_t down_units(const moe_dims* D) { return max_row_tiles(D, down_streams(D)) * ((D->d + 255) / 256); }
 
-// both work lists; never smaller than what a context of these dims offers to moe_linear_fp8
-size_t ffn_work_bytes(const moe_dims* D) {
-    const int64_t linear = ((int64_t)D->T * D->k / TOK_TILE + D->E) * (D->F / 128 + (D->d + 255) / 256);
-    const int64_t need = gate_up_units(D) + down_units(D);
-    return sizeof(Work) * (size_t)(need > linear ? need : linear);
-}
+// both work lists
+size_t ffn_work_bytes(const moe_dims* D) { return sizeof(Work) * (size_t)(gate_up_units(D) + down_units(D) + 1); }
 size_t ffn_ticket_bytes(const moe_dims* D) { return gate_up_streams(D) ? sizeof(int32_t) * (size_t)gate_up_units(D) : 0; }
 
 static hipError_t set_lds_limits() {
     static bool attr_set = false;
     if (attr_set) return hipSuccess;
-    const void* kernels[3] = {reinterpret_cast<const void*>(&ffn_gemm<true, false>),
-                              reinterpret_cast<const void*>(&ffn_gemm<true, true>),
-                              reinterpret_cast<const void*>(&ffn_gemm<false, false>)};
+    const void* kernels[4] = {reinterpret_cast<const void*>(&ffn_gemm<true, false, false>),
+                              reinterpret_cast<const void*>(&ffn_gemm<true, true, false>),
+                              reinterpret_cast<const void*>(&ffn_gemm<false, false, false>),
+                              reinterpret_cast<const void*>(&ffn_gemm<false, false, true>)};
     for (const void* k : kernels) {
         hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)SMEM_BYTES);
         if (e != hipSuccess) return e;
@@ -827,11 +838,11 @@ hipError_t launch_expert_ffn(moe_ctx* c, const uint8_t* xq, const float* xs, con
         hipError_t e = launch_stream_gate_up(c, xq, xs, perm, offsets, units1, W1, W3, s1, s3, y_perm);
         if (e != hipSuccess) return e;
     } else if (perm) {
-        hipLaunchKernelGGL((ffn_gemm<true, true>), dim3(grid1), dim3(NTHREADS), SMEM_BYTES, c->stream, xq, c->xs_sorted, N,
+        hipLaunchKernelGGL((ffn_gemm<true, true, false>), dim3(grid1), dim3(NTHREADS), SMEM_BYTES, c->stream, xq, c->xs_sorted, N,
                            perm, D.k, D.T, offsets, work, c->n_tiles, W1, W3, s1, s3, D.d, D.F, c->hq, c->hs,
                            (float*)nullptr);
     } else {
-        hipLaunchKernelGGL((ffn_gemm<true, false>), dim3(grid1), dim3(NTHREADS), SMEM_BYTES, c->stream, xq, xs, N,
+        hipLaunchKernelGGL((ffn_gemm<true, false, false>), dim3(grid1), dim3(NTHREADS), SMEM_BYTES, c->stream, xq, xs, N,
                            (const int32_t*)nullptr, 1, 1, offsets, work, c->n_tiles, W1, W3, s1, s3, D.d, D.F, c->hq,
                            c->hs, (float*)nullptr);
     }
@@ -841,7 +852,7 @@ hipError_t launch_expert_ffn(moe_ctx* c, const uint8_t* xq, const float* xs, con
         if (e != hipSuccess) return e;
     } else {
         const int grid2 = (units2 + NXCD - 1) / NXCD * NXCD;
-        hipLaunchKernelGGL((ffn_gemm<false, false>), dim3(grid2), dim3(NTHREADS), SMEM_BYTES, c->stream, c->hq, c->hs,
+        hipLaunchKernelGGL((ffn_gemm<false, false, false>), dim3(grid2), dim3(NTHREADS), SMEM_BYTES, c->stream, c->hq, c->hs,
                            N, (const int32_t*)nullptr, 1, 1, offsets, work2, n_work2, W2, (const uint8_t*)nullptr, s2,
                            (const float*)nullptr, D.F, D.d, (uint8_t*)nullptr, (float*)nullptr, y_perm);
     }
@@ -849,28 +860,18 @@ hipError_t launch_expert_ffn(moe_ctx* c, const uint8_t* xq, const float* xs, con
     return hipGetLastError();
 }
 
-__global__ void set_row_range(int32_t* __restrict__ offsets2, int32_t rows) {
-    offsets2[0] = 0;
-    offsets2[1] = rows;
-}
-
-// Dense block-scaled FP8 linear layer: the down-projection kernel with a single "expert" that owns all rows.
+// Dense block-scaled FP8 linear layer: the down-projection kernel with a single "expert" that owns all rows.  It needs no work list:
+// the two launches that made one took 10 us of the 490 of 8192 rows x 7168 x 8192.
 hipError_t launch_linear(moe_ctx* c, const uint8_t* xq, const float* xs, int32_t rows, int32_t K, const uint8_t* Wq,
                          const float* ws, int32_t NOUT, float* y) {
     hipError_t ea = set_lds_limits();
     if (ea != hipSuccess) return ea;
     if (linear_streams(rows, NOUT)) return launch_stream_linear(c, xq, xs, rows, K, Wq, ws, NOUT, y);
-    Work* work = reinterpret_cast<Work*>(c->tiles);
-    int32_t* range = c->flags + 2;                             // {0, rows}
-    int32_t* n_work = c->n_tiles + 2;
-    const int nft = (NOUT + 255) / 256;
-    hipLaunchKernelGGL(set_row_range, dim3(1), dim3(1), 0, c->stream, range, rows);
-    hipLaunchKernelGGL(build_work, dim3(1, 1), dim3(256), 0, c->stream, range, 1, nft, nft, work, work, n_work);
-    const int tiles = (rows + TOK_TILE - 1) / TOK_TILE;
-    const int grid = ((tiles * nft + NXCD - 1) / NXCD) * NXCD;
-    hipLaunchKernelGGL((ffn_gemm<false, false>), dim3(grid), dim3(NTHREADS), SMEM_BYTES, c->stream, xq, xs, rows,
-                       (const int32_t*)nullptr, 1, 1, range, work, n_work, Wq, (const uint8_t*)nullptr, ws, (const float*)nullptr, K, NOUT, (uint8_t*)nullptr,
-                       (float*)nullptr, y);
+    const int units = (rows + TOK_TILE - 1) / TOK_TILE * ((NOUT + 255) / 256);
+    hipLaunchKernelGGL((ffn_gemm<false, false, true>), dim3((units + NXCD - 1) / NXCD * NXCD), dim3(NTHREADS), SMEM_BYTES,
+                       c->stream, xq, xs, rows, (const int32_t*)nullptr, 1, 1, (const int32_t*)nullptr, (const Work*)nullptr,
+                       (const int32_t*)nullptr, Wq, (const uint8_t*)nullptr, ws, (const float*)nullptr, K, NOUT,
+                       (uint8_t*)nullptr, (float*)nullptr, y);
     return hipGetLastError();
 }
 
