@@ -15,9 +15,9 @@
 // candidates, applies the softmax over the k selected unbiased logits and writes out.
 //
 // Batches of at most 4096 tokens would give that kernel fewer blocks than half the compute units.
-// They take 32-token tiles whose K loop is split over up to 16 blocks; each block writes its
+// Those of more than 32 tokens take 32-token tiles whose K loop is split over up to 16 blocks; each block writes its
 // partial logits, and a second kernel (one wave per token) adds them up in split order and does
-// the same selection with wave-wide reductions.
+// the same selection with wave-wide reductions.  Up to 32 tokens the partial logits come from the vector ALU (route_rows_kernel).
 #include "moe_internal.hpp"
 
 #include <type_traits>
@@ -34,6 +34,9 @@ constexpr int NO_CAND = 0x7FFFFFFF;
 // split over up to ROUTE_MAX_SPLITS blocks per token tile: as many as bring the grid to about 256 blocks.
 constexpr int ROUTE_SPLIT_MAX_T = 4096;
 constexpr int ROUTE_MAX_SPLITS = 16;
+// Batches of at most ROUTE_ROWS_MAX_T tokens score on the vector ALU instead (us for the whole layer, that / matrix cores: one
+// token 44 / 52, 8 x 256 experts 138 / 157, 16 717 / 738 on the widest layer, 32 level, 64 120 / 114, 128 141 / 119).
+constexpr int ROUTE_ROWS_MAX_T = 32;
 
 __device__ inline uint32_t f32_to_bf16_rne_bits(float v) {
     const uint32_t b = __float_as_uint(v);
@@ -483,6 +486,55 @@ __device__ inline float wave_sum_63(float v) {                 // (left in lane 
     return v;
 }
 
+// First half of the router for a handful of tokens (decode steps): partial logits straight from the fp32 weights on the vector ALU,
+// one wave per (expert, slice of ROWS_COLS columns).  The wave keeps its 1024 weights in registers, sixteen per lane, and takes the
+// tokens ROWS_GROUP at a time: an fp32 multiply-add per product, lane sums added up by lane shifts.  partial[slice][token][expert]
+// goes to route_finish_kernel.  Bound by one read of the weights spread over the chip.
+// The matrix-core form reads them once to split them into bf16 planes, writes the planes and reads them again, on as many
+// blocks as there are K splits of one token tile: 10.6 us for one token x 64 experts x 4096, 22.1 for 16 x 256 x 7168, and 8
+// and 20 us more than this form in the layer.  The largest relative error of a gate weight against 64 bits falls as well
+// (3.1e-7 -> 2.3e-7 and 1.0e-6 -> 3.9e-7 at those sizes): sixteen products per chain instead of all of them in one.
+constexpr int ROWS_COLS = 1024, ROWS_GROUP = 8;
+
+__global__ __launch_bounds__(256) void route_rows_kernel(const uint16_t* __restrict__ x, const float* __restrict__ W, int T,
+                                                         int T_pad, int d, int E, int E_pad, float* __restrict__ partial) {
+    const int lane = threadIdx.x & 63;
+    const int e = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    if (e >= E) return;                                        // wave-uniform
+    const int c0 = blockIdx.y * ROWS_COLS + lane * 4;          // columns c0 + 256*j + 0..3 (d is a multiple of 128)
+    float4 w[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        w[j] = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (c0 + 256 * j < d) w[j] = *reinterpret_cast<const float4*>(W + (size_t)e * d + c0 + 256 * j);
+    }
+    for (int t0 = 0; t0 < T; t0 += ROWS_GROUP) {
+        uint2 v[ROWS_GROUP][4];
+#pragma unroll
+        for (int t = 0; t < ROWS_GROUP; ++t)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                v[t][j] = make_uint2(0u, 0u);
+                if (t0 + t < T && c0 + 256 * j < d)
+                    v[t][j] = *reinterpret_cast<const uint2*>(x + (size_t)(t0 + t) * d + c0 + 256 * j);
+            }
+#pragma unroll
+        for (int t = 0; t < ROWS_GROUP; ++t) {
+            if (t0 + t >= T) break;                            // wave-uniform
+            float s = 0.f;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                s = fmaf(__uint_as_float(v[t][j].x << 16), w[j].x, s);
+                s = fmaf(__uint_as_float(v[t][j].x & 0xFFFF0000u), w[j].y, s);
+                s = fmaf(__uint_as_float(v[t][j].y << 16), w[j].z, s);
+                s = fmaf(__uint_as_float(v[t][j].y & 0xFFFF0000u), w[j].w, s);
+            }
+            s = wave_sum_63(s);
+            if (lane == 63) partial[((size_t)blockIdx.y * T_pad + t0 + t) * E_pad + e] = s;
+        }
+    }
+}
+
 // Second half of the split router: one wave per token adds the partial logits up in split order, then
 // selects as the single-pass kernel does (larger score, then lower expert index; softmax over the k selected
 // unbiased logits, exponentials summed in slot order) or, with logged ids, picks their logits.  Lane l holds
@@ -582,6 +634,24 @@ hipError_t launch_route(moe_ctx* c, const uint16_t* x, const float* W_r, const f
     const moe_dims& D = c->dims;
     if (D.T == 0) return hipSuccess;
     const int E_pad = D.E <= 128 ? 128 : 256;
+    // route_finish over `splits` partial logits per token and expert
+    auto finish = [&](int splits, int T_pad) {
+        const dim3 fgrid((D.T + 3) / 4);
+        if (logged_idx)
+            hipLaunchKernelGGL(route_finish_kernel<true>, fgrid, dim3(256), 0, c->stream, c->route_partial, splits, T_pad, E_pad,
+                               (const float*)nullptr, logged_idx, D.T, D.E, D.k, topk_idx, topk_w);
+        else
+            hipLaunchKernelGGL(route_finish_kernel<false>, fgrid, dim3(256), 0, c->stream, c->route_partial, splits, T_pad, E_pad,
+                               bias, logged_idx, D.T, D.E, D.k, topk_idx, topk_w);
+        return hipGetLastError();
+    };
+    const int slices = (D.d + ROWS_COLS - 1) / ROWS_COLS;
+    if (D.T <= ROUTE_ROWS_MAX_T && c->route_partial && slices <= ROUTE_MAX_SPLITS) {
+        const int T_pad = (D.T + 31) / 32 * 32;
+        hipLaunchKernelGGL(route_rows_kernel, dim3((D.E + 3) / 4, slices), dim3(256), 0, c->stream, x, W_r, D.T, T_pad, D.d, D.E,
+                           E_pad, c->route_partial);
+        return finish(slices, T_pad);
+    }
     const int64_t nthreads = (int64_t)E_pad * (D.d / 8);
     hipLaunchKernelGGL(split_router_weights, dim3((unsigned)((nthreads + 255) / 256)), dim3(256), 0, c->stream,
                        W_r, D.E, E_pad, D.d, c->router_planes);
@@ -599,14 +669,7 @@ hipError_t launch_route(moe_ctx* c, const uint16_t* x, const float* W_r, const f
                        bias, logged_idx, D.T, D.d, D.E, D.k, topk_idx, topk_w, c->route_partial, cps)
             if (E_pad == 128) MOE_ROUTE_SPLIT(1); else MOE_ROUTE_SPLIT(2);
 #undef MOE_ROUTE_SPLIT
-            const dim3 fgrid((D.T + 3) / 4);
-            if (logged_idx)
-                hipLaunchKernelGGL(route_finish_kernel<true>, fgrid, dim3(256), 0, c->stream, c->route_partial, splits,
-                                   tiles * 32, E_pad, (const float*)nullptr, logged_idx, D.T, D.E, D.k, topk_idx, topk_w);
-            else
-                hipLaunchKernelGGL(route_finish_kernel<false>, fgrid, dim3(256), 0, c->stream, c->route_partial, splits,
-                                   tiles * 32, E_pad, bias, logged_idx, D.T, D.E, D.k, topk_idx, topk_w);
-            return hipGetLastError();
+            return finish(splits, tiles * 32);
         }
     }
     // token tile: the largest of 128 / 64 / 32 rows that still gives every compute unit a block

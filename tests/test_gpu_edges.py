@@ -296,3 +296,59 @@ def test_small_linears_equal_the_big_tile_kernel(gpu_lib, rows, K, NOUT):
         assert float((y[:4].double() - exact[:rows]).norm() / exact[:rows].norm()) < 1e-4
     finally:
         gpu_lib.moe_destroy(ctx)
+
+
+@pytest.mark.parametrize("T,d,E,k", [(1, 128, 1, 1), (7, 1024, 5, 3), (8, 1152, 100, 8), (9, 2176, 256, 16), (32, 640, 128, 4),
+                                     (33, 640, 129, 4), (2, 16384, 60, 6), (3, 16512, 60, 6)])
+def test_router_of_small_batches(gpu_lib, T, d, E, k):
+    """Routing at the edges of the small-batch router: one token, token groups of eight and the last size it takes; one column
+    slice, a ragged last slice, as many slices as it takes and one more (the matrix-core form); with a selection bias;
+    ids-only replay of the router's own ids gives its weights bit for bit."""
+    from workloads import make_inputs
+    from test_gpu_parity import _compare_routing, _check_permutation, _host
+    cfg = MoEConfig("rows", T=T, d=d, E=E, k=k, F=128, modes=("routed",), seed=T + E)
+    inp = make_inputs(cfg, with_experts=False)
+    h = _host(inp)
+    layer = gpu_lib.MoELayer(cfg.T, cfg.d, cfg.E, cfg.k, cfg.F)
+    try:
+        for bias in (None, np.linspace(-1.0, 1.0, E).astype(np.float32)):
+            layer.route(inp["x"].cuda(), inp["W_r"].cuda(), None if bias is None else torch.from_numpy(bias).cuda())
+            torch.cuda.synchronize()
+            _compare_routing(h, layer, bias)
+            _check_permutation(layer.topk_idx.cpu().numpy(), cfg.E, layer)
+            idx, w = layer.topk_idx.clone(), layer.topk_w.clone()
+            layer.route_replay_ids(inp["x"].cuda(), inp["W_r"].cuda(), idx)
+            torch.cuda.synchronize()
+            assert torch.equal(layer.topk_idx, idx) and torch.equal(layer.topk_w.view(torch.int32), w.view(torch.int32))
+    finally:
+        layer.close()
+
+
+@pytest.mark.parametrize("T,k", [(1, 1), (63, 16), (1024, 1), (1025, 1), (683, 3), (4096, 1), (4097, 1), (1024, 8), (8193, 1)])
+def test_permutation_at_block_edges(gpu_lib, T, k):
+    """Assignment counts around every size the one-block permutation is compiled for, and one beyond it; a few ids are
+    outside [0, E), which leaves their slots without a row."""
+    E = 37
+    rng = np.random.default_rng(T * k)
+    ids = np.argsort(rng.random((T, E)), axis=1)[:, :k].astype(np.int32)
+    w = rng.random((T, k), dtype=np.float32)
+    layer = gpu_lib.MoELayer(T, 128, E, k, 128)
+    try:
+        for bad in (False, True):
+            if bad:
+                ids[rng.integers(0, T, 3), rng.integers(0, k, 3)] = [E, -1, 1 << 20]
+            layer.route_replay(torch.empty((T, 128), dtype=torch.bfloat16, device="cuda"), torch.from_numpy(ids).cuda(),
+                               torch.from_numpy(w).cuda())
+            torch.cuda.synchronize()
+            flat = ids.reshape(-1)
+            ok = (flat >= 0) & (flat < E)
+            order = np.flatnonzero(ok)[np.argsort(flat[ok], kind="stable")]
+            inv = np.full(T * k, -1, dtype=np.int32)
+            inv[order] = np.arange(order.size)
+            assert np.array_equal(layer.perm.cpu().numpy()[:order.size], order)
+            assert np.array_equal(layer.inv_perm.cpu().numpy(), inv)
+            assert np.array_equal(layer.offsets.cpu().numpy(), np.concatenate([[0], np.cumsum(np.bincount(flat[ok], minlength=E))]))
+            assert np.array_equal(layer.topk_idx.cpu().numpy(), ids) and np.array_equal(layer.topk_w.cpu().numpy(), w)
+            assert (gpu_lib.moe_check_ids(layer.ctx) != 0) == bool((~ok).any())
+    finally:
+        layer.close()
