@@ -753,7 +753,7 @@ constexpr int CUS = 256, LINEAR_STREAM_TILES = 128;
 
 static bool gate_up_streams(const moe_dims* D) {
     const int64_t N = (int64_t)D->T * D->k;
-    if (N == 0 || D->F > D->d) return false;                   // the rows of y_perm hold h meanwhile
+    if (N == 0) return false;
     if (N <= GATE_UP_STREAM_ROWS * D->E) return true;
     // experts that meet at least one row when the router favours none
     const double met = D->E * (1.0 - pow(1.0 - (double)D->k / D->E, (double)D->T));
@@ -775,6 +775,9 @@ static int64_t down_units(const moe_dims* D) { return max_row_tiles(D, down_stre
 // both work lists
 size_t ffn_work_bytes(const moe_dims* D) { return sizeof(Work) * (size_t)(gate_up_units(D) + down_units(D) + 1); }
 size_t ffn_ticket_bytes(const moe_dims* D) { return gate_up_streams(D) ? sizeof(int32_t) * (size_t)gate_up_units(D) : 0; }
+size_t ffn_h_rows_bytes(const moe_dims* D) {
+    return gate_up_streams(D) ? sizeof(float) * (size_t)((int64_t)D->T * D->k) * (size_t)D->F : 0;
+}
 
 static hipError_t set_lds_limits() {
     static bool attr_set = false;
@@ -787,6 +790,8 @@ static hipError_t set_lds_limits() {
         hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)SMEM_BYTES);
         if (e != hipSuccess) return e;
     }
+    hipError_t e = set_stream_lds_limits();
+    if (e != hipSuccess) return e;
     attr_set = true;
     return hipSuccess;
 }
@@ -840,8 +845,7 @@ hipError_t launch_expert_ffn(moe_ctx* c, const uint8_t* xq, const float* xs, con
     if (ev) (void)hipEventRecord(ev[0], c->stream);          // the timed interval is the GEMM kernel alone
     const int grid1 = (units1 + NXCD - 1) / NXCD * NXCD;
     if (stream1) {
-        // h passes through y_perm: its rows are written by the down projection, after the gate/up projection is done with them
-        hipError_t e = launch_stream_gate_up(c, xq, xs, perm, offsets, units1, W1, W3, s1, s3, y_perm);
+        hipError_t e = launch_stream_gate_up(c, xq, xs, perm, offsets, units1, W1, W3, s1, s3);
         if (e != hipSuccess) return e;
     } else if (perm) {
         hipLaunchKernelGGL((ffn_gemm<true, true, false>), dim3(grid1), dim3(NTHREADS), SMEM_BYTES, c->stream, xq, c->xs_sorted, N,

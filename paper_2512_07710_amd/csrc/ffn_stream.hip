@@ -14,8 +14,8 @@
 //     of barrier, operand reads, matrix instructions and multiply-adds (a second set of operand registers, read a K block
 //     ahead, was slower: the register copies cost more than the overlap);
 //   * activation scales are gathered straight from the token-order planes (a few dozen rows: no sorted copy needed).
-// Gate/up: the scale of a token's 128 hidden features spans the unit's S blocks.  Each block puts its h (fp32) into scratch
-// memory; the last of the S to arrive (an atomic ticket per unit) takes the maximum and writes the codes.  Nobody waits.
+// Gate/up: the scale of a token's 128 hidden features spans the unit's S blocks.  Each block puts its h (fp32) into the
+// context's workspace; the last of the S to arrive (an atomic ticket per unit) takes the maximum and writes the codes.  Nobody waits.
 #include "ffn_common.hpp"
 
 #include <type_traits>
@@ -52,8 +52,7 @@ struct StreamArgs {
     const float *sa, *sb;
     int K, NOUT;
     bool once;                     // may the weights go past the caches?
-    float* scratch;                // GATED: h rows, scratch_ld floats apart
-    int scratch_ld;
+    float* h_rows;                 // GATED: [n_rows][NOUT] h before its codes
     uint8_t* hq;
     float* hs;
     float* y;
@@ -337,11 +336,11 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
                 make_float4(swiglu(acc[ts][r4 * 4], acc[ts][r4 * 4 + 8]), swiglu(acc[ts][r4 * 4 + 1], acc[ts][r4 * 4 + 9]),
                             swiglu(acc[ts][r4 * 4 + 2], acc[ts][r4 * 4 + 10]), swiglu(acc[ts][r4 * 4 + 3], acc[ts][r4 * 4 + 11]));
     __syncthreads();
-    float* const scratch = g.scratch + (size_t)wk.row0 * g.scratch_ld + f0;
+    float* const rows = g.h_rows + (size_t)wk.row0 * g.NOUT + f0;
     if (S > 1) {
         for (int i = tid; i < wk.nrows * (HW / 2); i += NW * 64) {
             const int r = i / (HW / 2), c = i % (HW / 2) * 2;
-            put2(scratch + (size_t)r * g.scratch_ld + sub_f + c, s_h[r * HP + c], s_h[r * HP + c + 1]);
+            put2(rows + (size_t)r * g.NOUT + sub_f + c, s_h[r * HP + c], s_h[r * HP + c + 1]);
         }
         // every wave's stores have reached the common point before the block takes its ticket
         asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
@@ -362,7 +361,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
         } else {
 #pragma unroll
             for (int i = 0; i < 8; i += 2) {
-                const float2 v = get2(scratch + (size_t)r * g.scratch_ld + c + i);
+                const float2 v = get2(rows + (size_t)r * g.NOUT + c + i);
                 h[i] = v.x;
                 h[i + 1] = v.y;
             }
@@ -398,26 +397,34 @@ constexpr int64_t LINEAR_ONCE_BYTES = 256ll << 20;
 
 template <int WAVES, int STAGES, bool GATED, bool GATHER, bool GROUPED>
 hipError_t launch(hipStream_t stream, const StreamArgs& a, int max_units) {
-    static bool attr_set = false;
-    if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&ffn_stream<WAVES, STAGES, GATED, GATHER, GROUPED>),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, STAGES * stage_bytes(WAVES));
-        if (e != hipSuccess) return e;
-        attr_set = true;
-    }
     const int grid = (max_units * (8 / WAVES) + NXCD - 1) / NXCD * NXCD;
     hipLaunchKernelGGL((ffn_stream<WAVES, STAGES, GATED, GATHER, GROUPED>), dim3(grid), dim3(WAVES * 64), STAGES * stage_bytes(WAVES), stream, a);
     return hipGetLastError();
 }
 
+template <int WAVES, int STAGES, bool GATED, bool GATHER, bool GROUPED>
+hipError_t allow_lds() {
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(&ffn_stream<WAVES, STAGES, GATED, GATHER, GROUPED>),
+                               hipFuncAttributeMaxDynamicSharedMemorySize, STAGES * stage_bytes(WAVES));
+}
+
 }  // namespace
 
+// all instances at once, so that any first call (before a capture, say) covers every later one
+hipError_t set_stream_lds_limits() {
+    hipError_t e = allow_lds<NW, D, true, true, true>();
+    if (e == hipSuccess) e = allow_lds<NW, D, true, false, true>();
+    if (e == hipSuccess) e = allow_lds<NW, D, false, false, true>();
+    if (e == hipSuccess) e = allow_lds<NW, D, false, false, false>();
+    if (e == hipSuccess) e = allow_lds<NW_FEW, D_FEW, false, false, false>();
+    return e;
+}
+
 hipError_t launch_stream_gate_up(moe_ctx* c, const uint8_t* xq, const float* xs, const int32_t* perm, const int32_t* offsets,
-                                 int max_units, const uint8_t* W1, const uint8_t* W3, const float* s1, const float* s3,
-                                 float* scratch) {
+                                 int max_units, const uint8_t* W1, const uint8_t* W3, const float* s1, const float* s3) {
     const moe_dims& m = c->dims;
     const StreamArgs a{xq, xs, m.T * m.k, perm, m.k, m.T, offsets, m.E, c->tickets, W1, W3, s1, s3, m.d, m.F,
-                       true, scratch, m.d, c->hq, c->hs, nullptr};
+                       true, c->h_rows, c->hq, c->hs, nullptr};
     return perm ? launch<NW, D, true, true, true>(c->stream, a, max_units) : launch<NW, D, true, false, true>(c->stream, a, max_units);
 }
 
@@ -425,14 +432,14 @@ hipError_t launch_stream_down(moe_ctx* c, const int32_t* offsets, int max_units,
                               float* y_perm) {
     const moe_dims& m = c->dims;
     const StreamArgs a{c->hq, c->hs, m.T * m.k, nullptr, 1, 1, offsets, m.E, nullptr, W2, nullptr, s2, nullptr, m.F, m.d,
-                       true, nullptr, 0, nullptr, nullptr, y_perm};
+                       true, nullptr, nullptr, nullptr, y_perm};
     return launch<NW, D, false, false, true>(c->stream, a, max_units);
 }
 
 hipError_t launch_stream_linear(moe_ctx* c, const uint8_t* xq, const float* xs, int32_t rows, int32_t K, const uint8_t* Wq,
                                 const float* ws, int32_t NOUT, float* y) {
     const StreamArgs a{xq, xs, rows, nullptr, 1, 1, nullptr, 1, nullptr, Wq, nullptr, ws, nullptr, K, NOUT,
-                       rows <= STREAM_ROWS && (int64_t)K * NOUT > LINEAR_ONCE_BYTES, nullptr, 0, nullptr, nullptr, y};
+                       rows <= STREAM_ROWS && (int64_t)K * NOUT > LINEAR_ONCE_BYTES, nullptr, nullptr, nullptr, y};
     const int units = (rows + STREAM_ROWS - 1) / STREAM_ROWS * ((NOUT + 255) / 256);
     return units <= FEW_UNITS ? launch<NW_FEW, D_FEW, false, false, false>(c->stream, a, units)
                               : launch<NW, D, false, false, false>(c->stream, a, units);

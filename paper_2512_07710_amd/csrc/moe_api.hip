@@ -68,6 +68,7 @@ int moe_create(moe_ctx** out, const moe_dims* dims, void* hip_stream) {
     ok = ok && hipMalloc((void**)&c->chunk_counts, sizeof(int32_t) * (size_t)c->n_chunks * dims->E) == hipSuccess;
     ok = ok && hipMalloc((void**)&c->tiles, ffn_work_bytes(dims)) == hipSuccess;
     if (ffn_ticket_bytes(dims)) ok = ok && hipMalloc((void**)&c->tickets, ffn_ticket_bytes(dims)) == hipSuccess;
+    if (ffn_h_rows_bytes(dims)) ok = ok && hipMalloc((void**)&c->h_rows, ffn_h_rows_bytes(dims)) == hipSuccess;
     ok = ok && hipMalloc((void**)&c->n_tiles, 4 * sizeof(int32_t)) == hipSuccess;
     ok = ok && hipMalloc((void**)&c->flags, 4 * sizeof(int32_t)) == hipSuccess;
     ok = ok && hipMalloc((void**)&c->router_planes, route_workspace_bytes(dims->E, dims->d)) == hipSuccess;
@@ -96,6 +97,7 @@ int moe_destroy(moe_ctx* c) {
     if (c->tiles) (void)hipFree(c->tiles);
     if (c->n_tiles) (void)hipFree(c->n_tiles);
     if (c->tickets) (void)hipFree(c->tickets);
+    if (c->h_rows) (void)hipFree(c->h_rows);
     if (c->flags) (void)hipFree(c->flags);
     if (c->xs_sorted) (void)hipFree(c->xs_sorted);
     if (c->router_planes) (void)hipFree(c->router_planes);

@@ -29,6 +29,7 @@ struct moe_ctx {
     int32_t* tickets;        // streaming gate/up projection only: one per unit, zero between launches
     int32_t* flags;          // [4] flags[0] != 0: an expert id outside [0,E) was met; flags[1] != 0: a logged id repeated
                              //     inside a token; [2..3]: row range of a dense linear
+    float* h_rows;           // streaming gate/up projection only: [N][F] hidden activations before their codes
     float* xs_sorted;        // [d/128][N] activation scales in sorted order (gathered FFN only)
     uint16_t* router_planes; // router weights split into three bf16 planes, matrix-core order
     float* route_partial;    // [splits][T padded to 32][E padded] partial logits of the split router (small batches only)
@@ -74,10 +75,11 @@ hipError_t launch_quantize_weights(hipStream_t s, const uint16_t* w, int64_t row
                                    float* scales);
 size_t ffn_work_bytes(const moe_dims* D);
 size_t ffn_ticket_bytes(const moe_dims* D);
-// The weight-streaming GEMMs (ffn_stream.hip).  perm as in launch_expert_ffn; scratch: [N][d] f32, overwritten
+size_t ffn_h_rows_bytes(const moe_dims* D);
+// The weight-streaming GEMMs (ffn_stream.hip).  perm as in launch_expert_ffn
+hipError_t set_stream_lds_limits();
 hipError_t launch_stream_gate_up(moe_ctx* c, const uint8_t* xq, const float* xs, const int32_t* perm, const int32_t* offsets,
-                                 int max_units, const uint8_t* W1, const uint8_t* W3, const float* s1, const float* s3,
-                                 float* scratch);
+                                 int max_units, const uint8_t* W1, const uint8_t* W3, const float* s1, const float* s3);
 hipError_t launch_stream_down(moe_ctx* c, const int32_t* offsets, int max_units, const uint8_t* W2, const float* s2,
                               float* y_perm);
 hipError_t launch_stream_linear(moe_ctx* c, const uint8_t* xq, const float* xs, int32_t rows, int32_t K, const uint8_t* Wq,

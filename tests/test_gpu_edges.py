@@ -263,7 +263,7 @@ def test_combine_at_every_fan_out(gpu_lib, k, d):
 def test_weight_streaming_tiles(gpu_lib, d, F):
     """Few rows per expert (a replay log with k = 1): experts of one to three streaming tiles, row counts around one and two
     groups of 32 columns and around a tile; one to 65 K blocks (fewer than the ring's stages; one more than a wave keeps
-    weight scales for); odd output feature tiles; hidden sizes above d, which leave the gate/up projection on the big tiles."""
+    weight scales for); odd output feature tiles; a hidden size above d."""
     E = 70 if d <= 640 else 20
     counts = [1, 2, 31, 32, 33, 63, 64, 65, 96, 129] + [0] * (E - 10)
     cfg = MoEConfig("stream", T=sum(counts), d=d, E=E, k=1, F=F, modes=("replay",), seed=d + F)
