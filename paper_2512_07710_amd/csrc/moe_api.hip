@@ -69,16 +69,16 @@ int moe_create(moe_ctx** out, const moe_dims* dims, void* hip_stream) {
     ok = ok && hipMalloc((void**)&c->tiles, ffn_work_bytes(dims)) == hipSuccess;
     if (ffn_ticket_bytes(dims)) ok = ok && hipMalloc((void**)&c->tickets, ffn_ticket_bytes(dims)) == hipSuccess;
     if (ffn_h_rows_bytes(dims)) ok = ok && hipMalloc((void**)&c->h_rows, ffn_h_rows_bytes(dims)) == hipSuccess;
-    ok = ok && hipMalloc((void**)&c->n_tiles, 4 * sizeof(int32_t)) == hipSuccess;
-    ok = ok && hipMalloc((void**)&c->flags, 4 * sizeof(int32_t)) == hipSuccess;
+    ok = ok && hipMalloc((void**)&c->n_tiles, 2 * sizeof(int32_t)) == hipSuccess;
+    ok = ok && hipMalloc((void**)&c->flags, 2 * sizeof(int32_t)) == hipSuccess;
     ok = ok && hipMalloc((void**)&c->router_planes, route_workspace_bytes(dims->E, dims->d)) == hipSuccess;
     if (route_partial_bytes(dims->T, dims->E))
         ok = ok && hipMalloc((void**)&c->route_partial, route_partial_bytes(dims->T, dims->E)) == hipSuccess;
     ok = ok && hipMalloc((void**)&c->xs_sorted, nrow * (size_t)(dims->d / QBLOCK) * sizeof(float)) == hipSuccess;
     ok = ok && hipMalloc((void**)&c->hq, nrow * (size_t)dims->F) == hipSuccess;
     ok = ok && hipMalloc((void**)&c->hs, nrow * (size_t)(dims->F / QBLOCK) * sizeof(float)) == hipSuccess;
-    ok = ok && launch_fill_i32(c->stream, c->flags, 4, 0) == hipSuccess;
-    ok = ok && launch_fill_i32(c->stream, c->n_tiles, 4, 0) == hipSuccess;
+    ok = ok && launch_fill_i32(c->stream, c->flags, 2, 0) == hipSuccess;
+    ok = ok && launch_fill_i32(c->stream, c->n_tiles, 2, 0) == hipSuccess;
     if (c->tickets)
         ok = ok && launch_fill_i32(c->stream, c->tickets, (int)(ffn_ticket_bytes(dims) / sizeof(int32_t)), 0) == hipSuccess;
     if (!ok) {
@@ -153,7 +153,7 @@ int moe_route_replay_ids(moe_ctx* c, const uint16_t* x, const float* W_r, const 
 
 int moe_check_ids(moe_ctx* c) {
     if (!c) return MOE_EINVAL;
-    int32_t h[4] = {0, 0, 0, 0};
+    int32_t h[2] = {0, 0};
     if (hipMemcpyAsync(h, c->flags, sizeof(h), hipMemcpyDeviceToHost, c->stream) != hipSuccess) return MOE_EHIP;
     if (hipStreamSynchronize(c->stream) != hipSuccess) return MOE_EHIP;
     if (h[0] != 0 || h[1] != 0) {
@@ -188,7 +188,7 @@ int moe_linear_fp8(moe_ctx* c, const uint8_t* xq, const float* xs, int32_t rows,
     if ((int64_t)NOUT * K >= (int64_t)1 << 32) return MOE_EINVAL;     // 32-bit byte offsets inside the weight matrix
     const int64_t units = ((int64_t)rows + TOK_TILE - 1) / TOK_TILE * ((NOUT + 255) / 256);
     const int64_t room = (int64_t)c->max_tiles * (c->dims.F / 128 + (c->dims.d + 255) / 256);
-    if (units > room) return MOE_EINVAL;              // the context's work-list storage bounds the problem size
+    if (units > room) return MOE_EINVAL;              // the context's shape bounds the problem size
     if (rows == 0) return MOE_OK;
     return hip_rc(launch_linear(c, xq, xs, rows, K, Wq, ws, NOUT, y));
 }

@@ -27,8 +27,8 @@ struct moe_ctx {
     void* tiles;             // GEMM work lists (gate/up list, then down list)
     int32_t* n_tiles;        // [2] their lengths
     int32_t* tickets;        // streaming gate/up projection only: one per unit, zero between launches
-    int32_t* flags;          // [4] flags[0] != 0: an expert id outside [0,E) was met; flags[1] != 0: a logged id repeated
-                             //     inside a token; [2..3]: row range of a dense linear
+    int32_t* flags;          // [2] flags[0] != 0: an expert id outside [0,E) was met; flags[1] != 0: a logged id repeated
+                             //     inside a token
     float* h_rows;           // streaming gate/up projection only: [N][F] hidden activations before their codes
     float* xs_sorted;        // [d/128][N] activation scales in sorted order (gathered FFN only)
     uint16_t* router_planes; // router weights split into three bf16 planes, matrix-core order
