@@ -10,7 +10,7 @@
 //      from a log are also checked here: an id outside [0,E) raises flags[0], an id that repeats an
 //      earlier slot of the same token raises flags[1] (the permutation is still the stable sort of
 //      what was given).
-// The result is unique (stable), so it can be compared bit for bit.  Batches of at most ONE_BLOCK_MAX_N
+// The result is unique (stable), so it can be compared bit for bit.  Batches of at most one_block_max_n
 // assignments take one fused launch instead (permute_one_block).
 #include "moe_internal.hpp"
 
@@ -174,13 +174,22 @@ __global__ __launch_bounds__(256) void scatter(const int32_t* __restrict__ ids, 
     perm[pos] = i;
 }
 
-// N <= ONE_BLOCK_MAX_N: the three steps in one block and one launch, where the launches themselves are most of the time.  Sixteen
-// waves rank STEPS times 64 entries each in the manner of chunk_hist_rank, then scan over the experts and scatter from
-// registers; bound by its chain of barriers and memory round trips.  3885 assignments take 9.1 us
-// (the three kernels 16.1), 1536 take 4.8 and 6 take 2.7 (one block of four waves: 6.8 and 4.6).
+// Up to one_block_max_n assignments: the three steps in one block and one launch, where the launches themselves are most of the
+// time.  Sixteen waves rank STEPS times 64 entries each in the manner of chunk_hist_rank, then scan over the experts and scatter
+// from registers; bound by its chain of barriers and memory round trips.
+// Whole calls in a row, us, this form / the three launches: replay of 2100 assignments k = 6 7.6 / 10.6, 4000 k = 2 6.9 / 10.3,
+// k = 6 8.7 / 10.7, k = 8 9.5 / 10.9, k = 16 12.0 / 11.5 (3000: 11.1 / 11.5).  Beyond that the search for repeated ids, up to
+// k - 1 reads of earlier slots one after another in each of a thread's STEPS entries, weighs more in one block than launches
+// that overlap: 4500 k = 6 13.3 / 10.6, 8100 15.4 / 11.4, 8096 k = 16 22.3 / 11.9.  Without that search (ids from the router
+// itself) the one block stays ahead: with the router 23.4 / 25.7 at 4500, 25.5 / 27.0 at 8100 and level at 8096 with k = 8.
 constexpr int ONE_BLOCK_WAVES = 16;
 constexpr int ONE_BLOCK_MAX_STEPS = 8;
 constexpr int ONE_BLOCK_MAX_N = ONE_BLOCK_WAVES * ONE_BLOCK_MAX_STEPS * 64;
+constexpr int ONE_BLOCK_CHECKED_MAX_N = 4096, ONE_BLOCK_CHECKED_WIDE_MAX_N = 3072;
+static_assert(ONE_BLOCK_CHECKED_MAX_N <= ONE_BLOCK_MAX_N, "the block holds that many");
+inline int one_block_max_n(bool check_dups, int k) {
+    return !check_dups ? ONE_BLOCK_MAX_N : k <= 8 ? ONE_BLOCK_CHECKED_MAX_N : ONE_BLOCK_CHECKED_WIDE_MAX_N;
+}
 
 template <int STEPS>
 __global__ __launch_bounds__(ONE_BLOCK_WAVES * 64) void permute_one_block(
@@ -288,7 +297,7 @@ hipError_t launch_permute(const permute_args& a, const int32_t* ids_in, int32_t*
                           float* w_copy, int32_t* offsets, int32_t* perm, int32_t* inv_perm) {
     const int N = a.T * a.k;
     const int n_chunks = (N + PERM_CHUNK - 1) / PERM_CHUNK;
-    if (N > 0 && N <= ONE_BLOCK_MAX_N) {
+    if (N > 0 && N <= one_block_max_n(a.check_dups, a.k)) {
 #define MOE_ONE_BLOCK(STEPS_)                                                                                              \
     hipLaunchKernelGGL(permute_one_block<STEPS_>, dim3(1), dim3(ONE_BLOCK_WAVES * 64), 0, a.stream, ids_in, N, a.E, ids_copy, \
                        w_in, w_copy, offsets, perm, inv_perm, a.k, a.check_dups, a.flags)

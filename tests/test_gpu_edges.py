@@ -352,3 +352,34 @@ def test_permutation_at_block_edges(gpu_lib, T, k):
             assert (gpu_lib.moe_check_ids(layer.ctx) != 0) == bool((~ok).any())
     finally:
         layer.close()
+
+
+@pytest.mark.parametrize("T,k", [(1366, 3), (4097, 1), (1024, 8), (8193, 1), (384, 8), (512, 8), (513, 8), (192, 16), (193, 16)])
+def test_permutation_either_side_of_the_one_block_form(gpu_lib, T, k):
+    """Assignment counts around the sizes up to which one block permutes a batch: the router's own ids (no search for repeats:
+    up to 8192) and logged ids (up to 4096, above eight slots a token up to 3072), the latter also with an id repeated in the
+    last token."""
+    from workloads import make_inputs
+    from test_gpu_parity import _check_permutation
+    E = 37
+    cfg = MoEConfig("perm", T=T, d=128, E=E, k=k, F=128, modes=("routed",), seed=T + k)
+    inp = make_inputs(cfg, with_experts=False)
+    layer = gpu_lib.MoELayer(T, 128, E, k, 128)
+    try:
+        layer.route(inp["x"].cuda(), inp["W_r"].cuda(), None)
+        torch.cuda.synchronize()
+        _check_permutation(layer.topk_idx.cpu().numpy(), E, layer)
+        assert gpu_lib.moe_check_ids(layer.ctx) == 0
+        ids, w = layer.topk_idx.clone(), layer.topk_w.clone()
+        for repeated in (False, True):
+            if repeated:
+                if k == 1:
+                    break
+                ids[T - 1, k - 1] = ids[T - 1, 0]
+            layer.route_replay(inp["x"].cuda(), ids, w)
+            torch.cuda.synchronize()
+            _check_permutation(ids.cpu().numpy(), E, layer)
+            assert torch.equal(layer.topk_idx, ids) and torch.equal(layer.topk_w, w)
+            assert (gpu_lib.moe_check_ids(layer.ctx) != 0) == repeated
+    finally:
+        layer.close()
