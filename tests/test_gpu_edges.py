@@ -383,3 +383,32 @@ def test_permutation_either_side_of_the_one_block_form(gpu_lib, T, k):
             assert (gpu_lib.moe_check_ids(layer.ctx) != 0) == repeated
     finally:
         layer.close()
+
+
+@pytest.mark.parametrize("rows,cols,fan", [(1, 128, 16), (15, 256, 5), (33, 384, 17), (100, 1152, 8), (47, 128, 33), (8192 * 32 + 5, 128, 1),
+                                           (4097, 8192, 2)])
+def test_fanned_out_quantisation(gpu_lib, rows, cols, fan):
+    """Fan-outs below, at and above the sixteen indices a row's lanes hold, in groups of four and not; row counts around the
+    blocks of 16; the sizes from which blocks of 32 rows are taken; slots without an output row.  Every output row has the
+    bits of the plain form's row, and skipped rows stay untouched."""
+    g = torch.Generator(device="cuda").manual_seed(rows + fan)
+    x = torch.randn((rows, cols), generator=g, device="cuda").to(torch.bfloat16)
+    dst = torch.randperm(rows * fan, generator=g, device="cuda").to(torch.int32)
+    skipped = torch.zeros(rows * fan, dtype=torch.bool, device="cuda")
+    skipped[torch.randperm(rows * fan, generator=g, device="cuda")[:rows * fan // 7]] = True       # by slot
+    ctx = gpu_lib.moe_create(0, 128, 1, 1, 128)
+    try:
+        q1, s1 = torch.empty((rows, cols), dtype=torch.uint8, device="cuda"), torch.empty((cols // 128, rows), device="cuda")
+        gpu_lib.moe_quantize_fp8(ctx, x, rows, cols, 128, None, 1, q1, s1)
+        q = torch.full((rows * fan, cols), 0x55, dtype=torch.uint8, device="cuda")
+        s = torch.full((cols // 128, rows * fan), -1.0, device="cuda")
+        gpu_lib.moe_quantize_fp8(ctx, x, rows, cols, 128, torch.where(skipped, -1, dst), fan, q, s)
+        torch.cuda.synchronize()
+        src = torch.empty(rows * fan, dtype=torch.int64, device="cuda")
+        src[dst.long()] = torch.arange(rows * fan, device="cuda") // fan
+        written = torch.ones(rows * fan, dtype=torch.bool, device="cuda")
+        written[dst.long()[skipped]] = False
+        assert torch.equal(q, torch.where(written[:, None], q1[src], torch.full_like(q, 0x55)))
+        assert torch.equal(s, torch.where(written, s1[:, src], torch.full_like(s, -1.0)))
+    finally:
+        gpu_lib.moe_destroy(ctx)
