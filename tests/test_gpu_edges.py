@@ -412,3 +412,27 @@ def test_fanned_out_quantisation(gpu_lib, rows, cols, fan):
         assert torch.equal(s, torch.where(written, s1[:, src], torch.full_like(s, -1.0)))
     finally:
         gpu_lib.moe_destroy(ctx)
+
+
+@pytest.mark.parametrize("T,d,k", [(3, 1280, 3), (2, 2176, 8), (5, 4992, 1), (4, 3200, 11)])
+def test_combine_of_widths_that_split_unevenly(gpu_lib, T, d, k):
+    """Two, three, four and five blocks of columns per token whose common width is not a multiple of the columns left: the
+    slot-order multiply-add chain as in the test of the fan-outs, k roundings of at most half an ulp of a partial sum."""
+    g = torch.Generator().manual_seed(d + k)
+    y_perm, w = torch.randn((T * k, d), generator=g), torch.rand((T, k), generator=g)
+    inv = torch.randperm(T * k, generator=g).to(torch.int32).view(T, k)
+    layer = gpu_lib.MoELayer(T, d, 16, k, 128)
+    try:
+        layer.y_perm.copy_(y_perm)
+        layer.inv_perm.copy_(inv.view(-1))
+        layer.topk_w.copy_(w)
+        layer.y.fill_(float("nan"))
+        sums = torch.full((T, d), float("nan"), device="cuda")
+        layer.combine(sums)
+        torch.cuda.synchronize()
+        terms = w[..., None].double() * y_perm[inv.long()].double()
+        err = (sums.cpu().double() - terms.sum(1)).abs()
+        assert torch.all(err <= k * 2.0 ** -24 * terms.abs().sum(1) + 1e-30)
+        assert torch.equal(layer.y.cpu(), sums.cpu().to(torch.bfloat16))
+    finally:
+        layer.close()
