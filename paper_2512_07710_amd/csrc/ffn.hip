@@ -73,15 +73,19 @@ __device__ inline void split_rows(int rows, int nt, int i, Work& w) {
 // again from HBM).
 // Block (e, l) writes the units of expert e into list l (0: gate/up, n_ft0 feature tiles; 1: down,
 // n_ft1 feature tiles); every block recomputes the tile counts of all experts for its base index.
-__device__ inline void build_work(const int32_t* __restrict__ offsets, int E, int e, int list, int n_ft0, int n_ft1,
+// choose: list 1 is left empty (n_work[1] = 0) unless the batch is concentrated, see DOWN_SKEW_UNITS.
+__device__ inline void build_work(const int32_t* __restrict__ offsets, int E, int e, int list, int n_ft0, int n_ft1, bool choose,
                                   Work* __restrict__ work0, Work* __restrict__ work1, int32_t* __restrict__ n_work) {
-    __shared__ int32_t s_tiles[MAX_E];
+    __shared__ int32_t s_tiles[MAX_E], s_small[MAX_E / 64];
     const int tid = threadIdx.x;
     const int n_ft = list == 0 ? n_ft0 : n_ft1;
     Work* const work = list == 0 ? work0 : work1;
-    int nt_t = 0;
-    if (tid < E) nt_t = (offsets[tid + 1] - offsets[tid] + TOK_TILE - 1) / TOK_TILE;
-    s_tiles[tid] = nt_t;
+    const int rows_t = tid < E ? offsets[tid + 1] - offsets[tid] : 0;
+    s_tiles[tid] = (rows_t + TOK_TILE - 1) / TOK_TILE;
+    int small = (rows_t + STREAM_ROWS - 1) / STREAM_ROWS;
+#pragma unroll
+    for (int m = 32; m >= 1; m >>= 1) small += __shfl_xor(small, m);
+    if ((tid & 63) == 0) s_small[tid >> 6] = small;
     __syncthreads();
     for (int off = 1; off < MAX_E; off <<= 1) {            // inclusive scan
         const int a = (tid >= off) ? s_tiles[tid - off] : 0;
@@ -89,7 +93,9 @@ __device__ inline void build_work(const int32_t* __restrict__ offsets, int E, in
         s_tiles[tid] += a;
         __syncthreads();
     }
-    if (e == 0 && tid == 0) n_work[list] = s_tiles[MAX_E - 1] * n_ft;
+    const bool empty = choose && list == 1 && s_small[0] + s_small[1] + s_small[2] + s_small[3] <= 2 * s_tiles[MAX_E - 1];
+    if (e == 0 && tid == 0) n_work[list] = empty ? 0 : s_tiles[MAX_E - 1] * n_ft;
+    if (empty) return;
     const int start = offsets[e], cnt = offsets[e + 1] - start;
     const int nt = (cnt + TOK_TILE - 1) / TOK_TILE;
     if (nt == 0) return;
@@ -748,32 +754,55 @@ constexpr size_t SMEM_BYTES = NW_BUF * W_TILE + NX_BUF * X_TILE;   // 160 KiB
 //   linear   (K = 4096) 16 rows x 1024 features 28 / 13, 256 x 8192 48 / 22, 256 x 24576 50 / 45, 128 x 32768 36 / 31; at 128
 //            big tiles level (512 x 16384 53.6 / 53.8, 1024 x 8192 55.7 / 56.0); 256 of more than 64 rows (128 x 65536): 69 / 80
 constexpr int64_t GATE_UP_STREAM_ROWS = 8, GATE_UP_STREAM_ROWS_IDLE = 32, DOWN_STREAM_ROWS = 48;
-static_assert(DOWN_STREAM_ROWS >= GATE_UP_STREAM_ROWS_IDLE, "where the gate/up projection streams, the down projection does");
+// Rows per expert are a mean.  A skewed load is no reason against streaming (down projection, Zipf loads at a mean of 6..48: 0.73..0.99
+// of the big tiles' time; nine tokens in ten on the same k experts: 0.70..0.97), but a concentrated one is: with every token on the same
+// k experts nothing but their weights is read, once for each tile of 64 rows, matrix work counts, and streaming takes 1.1..1.8 times as
+// long.  The host cannot see the load.  Where the streaming units of such a batch, k experts of T rows, are at most the figures
+// below it still costs a layer nothing to speak of (448 units: 145 us before there was a streaming kernel, 145 with it; 384: 98 and 86; 512: 74.3
+// and 74.0; above: 672 units 160 and 178, 3584 units 424 and 553).  Beyond them the gate/up projection takes the big tiles, which
+// are level there, and for the down projection the kernel that makes the lists counts: more than twice as many 64-row tiles as big ones
+// (an ordinary load has 1.0..1.55 times as many, a concentrated one of that size 2.5..4) fill the big tiles' list, otherwise it
+// stays empty; both kernels are launched and the one that has nothing to do returns.
+constexpr int64_t GATE_UP_SKEW_UNITS = 256, DOWN_SKEW_UNITS = 512;
 constexpr int CUS = 256, LINEAR_STREAM_TILES = 128;
 
+static bool skew_is_harmless(const moe_dims* D, int feature_tiles, int64_t most_units) {
+    const int64_t tiles = (D->T + STREAM_ROWS - 1) / STREAM_ROWS;
+    return tiles <= 1 || D->k * tiles * feature_tiles <= most_units;    // one tile: no weight passes twice
+}
+enum class Down { BIG, STREAM, EITHER };
+static Down down_form(const moe_dims* D) {
+    if ((int64_t)D->T * D->k > DOWN_STREAM_ROWS * D->E) return Down::BIG;
+    return skew_is_harmless(D, (D->d + 255) / 256, DOWN_SKEW_UNITS) ? Down::STREAM : Down::EITHER;
+}
+// (only where the down projection streams for certain: then no lists are needed)
 static bool gate_up_streams(const moe_dims* D) {
     const int64_t N = (int64_t)D->T * D->k;
-    if (N == 0) return false;
+    if (N == 0 || down_form(D) != Down::STREAM || !skew_is_harmless(D, D->F / 128, GATE_UP_SKEW_UNITS)) return false;
     if (N <= GATE_UP_STREAM_ROWS * D->E) return true;
     // experts that meet at least one row when the router favours none
     const double met = D->E * (1.0 - pow(1.0 - (double)D->k / D->E, (double)D->T));
     return N <= GATE_UP_STREAM_ROWS_IDLE * D->E && met * (D->F / 128) < CUS;
 }
-static bool down_streams(const moe_dims* D) { return (int64_t)D->T * D->k <= DOWN_STREAM_ROWS * D->E; }
 static bool linear_streams(int32_t rows, int32_t NOUT) {
     return rows <= STREAM_ROWS || (int64_t)((rows + TOK_TILE - 1) / TOK_TILE) * ((NOUT + 255) / 256) <= LINEAR_STREAM_TILES;
 }
 
 // upper bound on row tiles: every full tile, and one more for each expert that has rows
-static int64_t max_row_tiles(const moe_dims* D, bool streams) {
+static int64_t max_row_tiles(const moe_dims* D, int rows) {
     const int64_t N = (int64_t)D->T * D->k;
-    return N / (streams ? STREAM_ROWS : TOK_TILE) + (N < D->E ? N : D->E);
+    return N / rows + (N < D->E ? N : D->E);
 }
-static int64_t gate_up_units(const moe_dims* D) { return max_row_tiles(D, gate_up_streams(D)) * (D->F / 128); }
-static int64_t down_units(const moe_dims* D) { return max_row_tiles(D, down_streams(D)) * ((D->d + 255) / 256); }
+static int64_t gate_up_units(const moe_dims* D) { return max_row_tiles(D, gate_up_streams(D) ? STREAM_ROWS : TOK_TILE) * (D->F / 128); }
+static int64_t down_stream_units(const moe_dims* D) { return max_row_tiles(D, STREAM_ROWS) * ((D->d + 255) / 256); }
+// EITHER: S > 2B tiles of 64 / of 256 rows over m experts with rows (B >= m, S <= (N + 63m)/64) leave m <= N/65
+static int64_t down_big_units(const moe_dims* D) {
+    const int64_t N = (int64_t)D->T * D->k;
+    return (down_form(D) == Down::EITHER ? N / TOK_TILE + N / 65 : max_row_tiles(D, TOK_TILE)) * ((D->d + 255) / 256);
+}
 
 // both work lists
-size_t ffn_work_bytes(const moe_dims* D) { return sizeof(Work) * (size_t)(gate_up_units(D) + down_units(D) + 1); }
+size_t ffn_work_bytes(const moe_dims* D) { return sizeof(Work) * (size_t)(gate_up_units(D) + down_big_units(D) + 1); }
 size_t ffn_ticket_bytes(const moe_dims* D) { return gate_up_streams(D) ? sizeof(int32_t) * (size_t)gate_up_units(D) : 0; }
 size_t ffn_h_rows_bytes(const moe_dims* D) {
     return gate_up_streams(D) ? sizeof(float) * (size_t)((int64_t)D->T * D->k) * (size_t)D->F : 0;
@@ -800,12 +829,12 @@ static hipError_t set_lds_limits() {
 // 0 .. E*lists-1) and, with perm, the scales of the expert-sorted rows from the per-token scales:
 // out[g][p] = in[g][perm[p] / fan].
 __global__ __launch_bounds__(256) void prepare_big_tiles(const int32_t* __restrict__ offsets, int E, int lists, int n_ft0,
-                                                         int n_ft1, Work* __restrict__ work0, Work* __restrict__ work1,
+                                                         int n_ft1, bool choose, Work* __restrict__ work0, Work* __restrict__ work1,
                                                          int32_t* __restrict__ n_work, const float* __restrict__ in, int T,
                                                          const int32_t* __restrict__ perm, int fan, int N,
                                                          float* __restrict__ out) {
     if ((int)blockIdx.x < E * lists) {
-        build_work(offsets, E, blockIdx.x % E, blockIdx.x / E, n_ft0, n_ft1, work0, work1, n_work);
+        build_work(offsets, E, blockIdx.x % E, blockIdx.x / E, n_ft0, n_ft1, choose, work0, work1, n_work);
         return;
     }
     const uint32_t b = blockIdx.x - E * lists, row_blocks = (uint32_t)((N + 255) / 256);
@@ -832,15 +861,16 @@ hipError_t launch_expert_ffn(moe_ctx* c, const uint8_t* xq, const float* xs, con
     const int N = (int)((int64_t)D.T * D.k);
     const int nft1 = D.F / 128;
     const int nft2 = (D.d + 255) / 256;
-    const bool stream1 = gate_up_streams(&D), stream2 = down_streams(&D);
-    const int units1 = (int)gate_up_units(&D), units2 = (int)down_units(&D);
+    const bool stream1 = gate_up_streams(&D);
+    const Down down = down_form(&D);
+    const int units1 = (int)gate_up_units(&D);
     Work* work2 = work + units1;                               // the down projection's list
     int32_t* n_work2 = c->n_tiles + 1;
-    if (!stream1) {                                            // (the down projection streams wherever the gate/up projection does,
-        const int lists = stream2 ? 1 : 2;                     // and the streaming kernels need neither list nor sorted scales)
+    if (!stream1) {                                            // (the streaming kernels need neither list nor sorted scales)
+        const int lists = down == Down::STREAM ? 1 : 2;
         const int64_t gather = perm ? (int64_t)((N + 255) / 256) * (D.d / QBLOCK) : 0;
         hipLaunchKernelGGL(prepare_big_tiles, dim3((unsigned)(D.E * lists + gather)), dim3(256), 0, c->stream, offsets, D.E, lists,
-                           nft1, nft2, work, work2, c->n_tiles, xs, D.T, perm, D.k, N, c->xs_sorted);
+                           nft1, nft2, down == Down::EITHER, work, work2, c->n_tiles, xs, D.T, perm, D.k, N, c->xs_sorted);
     }
     if (ev) (void)hipEventRecord(ev[0], c->stream);          // the timed interval is the GEMM kernel alone
     const int grid1 = (units1 + NXCD - 1) / NXCD * NXCD;
@@ -857,11 +887,12 @@ hipError_t launch_expert_ffn(moe_ctx* c, const uint8_t* xq, const float* xs, con
                            c->hs, (float*)nullptr);
     }
     if (ev) (void)hipEventRecord(ev[1], c->stream);
-    if (stream2) {
-        hipError_t e = launch_stream_down(c, offsets, units2, W2, s2, y_perm);
+    if (down != Down::BIG) {
+        hipError_t e = launch_stream_down(c, offsets, (int)down_stream_units(&D), down == Down::EITHER ? n_work2 : nullptr, W2, s2, y_perm);
         if (e != hipSuccess) return e;
-    } else {
-        const int grid2 = (units2 + NXCD - 1) / NXCD * NXCD;
+    }
+    if (down != Down::STREAM) {
+        const int grid2 = ((int)down_big_units(&D) + NXCD - 1) / NXCD * NXCD;
         hipLaunchKernelGGL((ffn_gemm<false, false, false>), dim3(grid2), dim3(NTHREADS), SMEM_BYTES, c->stream, c->hq, c->hs,
                            N, (const int32_t*)nullptr, 1, 1, offsets, work2, n_work2, W2, (const uint8_t*)nullptr, s2,
                            (const float*)nullptr, D.F, D.d, (uint8_t*)nullptr, (float*)nullptr, y_perm);

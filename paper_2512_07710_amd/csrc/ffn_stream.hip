@@ -47,6 +47,7 @@ struct StreamArgs {
     int fan, n_tok;
     const int32_t* offsets;        // GROUPED: [E+1], of the experts' rows
     int E;
+    const int32_t* big_units;      // not null: nothing to do where it is not zero
     int32_t* tickets;              // GATED: one per unit, zero before and after the launch
     const uint8_t *Wa, *Wb;
     const float *sa, *sb;
@@ -135,6 +136,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
     constexpr int STAGE = stage_bytes(NW);
     extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
 
+    if (g.big_units && *g.big_units != 0) return;
     // ---- which block of which unit: XCD x (= blockIdx % 8) walks a contiguous eighth of the units, a unit's blocks side by side
     const int tid = threadIdx.x, lane = tid & 63;
     const int nft = (g.NOUT + FT - 1) / FT;
@@ -423,22 +425,22 @@ hipError_t set_stream_lds_limits() {
 hipError_t launch_stream_gate_up(moe_ctx* c, const uint8_t* xq, const float* xs, const int32_t* perm, const int32_t* offsets,
                                  int max_units, const uint8_t* W1, const uint8_t* W3, const float* s1, const float* s3) {
     const moe_dims& m = c->dims;
-    const StreamArgs a{xq, xs, m.T * m.k, perm, m.k, m.T, offsets, m.E, c->tickets, W1, W3, s1, s3, m.d, m.F,
+    const StreamArgs a{xq, xs, m.T * m.k, perm, m.k, m.T, offsets, m.E, nullptr, c->tickets, W1, W3, s1, s3, m.d, m.F,
                        true, c->h_rows, c->hq, c->hs, nullptr};
     return perm ? launch<NW, D, true, true, true>(c->stream, a, max_units) : launch<NW, D, true, false, true>(c->stream, a, max_units);
 }
 
-hipError_t launch_stream_down(moe_ctx* c, const int32_t* offsets, int max_units, const uint8_t* W2, const float* s2,
-                              float* y_perm) {
+hipError_t launch_stream_down(moe_ctx* c, const int32_t* offsets, int max_units, const int32_t* big_units, const uint8_t* W2,
+                              const float* s2, float* y_perm) {
     const moe_dims& m = c->dims;
-    const StreamArgs a{c->hq, c->hs, m.T * m.k, nullptr, 1, 1, offsets, m.E, nullptr, W2, nullptr, s2, nullptr, m.F, m.d,
+    const StreamArgs a{c->hq, c->hs, m.T * m.k, nullptr, 1, 1, offsets, m.E, big_units, nullptr, W2, nullptr, s2, nullptr, m.F, m.d,
                        true, nullptr, nullptr, nullptr, y_perm};
     return launch<NW, D, false, false, true>(c->stream, a, max_units);
 }
 
 hipError_t launch_stream_linear(moe_ctx* c, const uint8_t* xq, const float* xs, int32_t rows, int32_t K, const uint8_t* Wq,
                                 const float* ws, int32_t NOUT, float* y) {
-    const StreamArgs a{xq, xs, rows, nullptr, 1, 1, nullptr, 1, nullptr, Wq, nullptr, ws, nullptr, K, NOUT,
+    const StreamArgs a{xq, xs, rows, nullptr, 1, 1, nullptr, 1, nullptr, nullptr, Wq, nullptr, ws, nullptr, K, NOUT,
                        rows <= STREAM_ROWS && (int64_t)K * NOUT > LINEAR_ONCE_BYTES, nullptr, nullptr, nullptr, y};
     const int units = (rows + STREAM_ROWS - 1) / STREAM_ROWS * ((NOUT + 255) / 256);
     return units <= FEW_UNITS ? launch<NW_FEW, D_FEW, false, false, false>(c->stream, a, units)

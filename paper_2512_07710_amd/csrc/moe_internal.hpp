@@ -80,8 +80,9 @@ size_t ffn_h_rows_bytes(const moe_dims* D);
 hipError_t set_stream_lds_limits();
 hipError_t launch_stream_gate_up(moe_ctx* c, const uint8_t* xq, const float* xs, const int32_t* perm, const int32_t* offsets,
                                  int max_units, const uint8_t* W1, const uint8_t* W3, const float* s1, const float* s3);
-hipError_t launch_stream_down(moe_ctx* c, const int32_t* offsets, int max_units, const uint8_t* W2, const float* s2,
-                              float* y_perm);
+// big_units, if given: nothing to do where it is not zero (the big tiles take the batch)
+hipError_t launch_stream_down(moe_ctx* c, const int32_t* offsets, int max_units, const int32_t* big_units, const uint8_t* W2,
+                              const float* s2, float* y_perm);
 hipError_t launch_stream_linear(moe_ctx* c, const uint8_t* xq, const float* xs, int32_t rows, int32_t K, const uint8_t* Wq,
                                 const float* ws, int32_t NOUT, float* y);
 size_t route_workspace_bytes(int E, int d);

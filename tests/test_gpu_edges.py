@@ -436,3 +436,50 @@ def test_combine_of_widths_that_split_unevenly(gpu_lib, T, d, k):
         assert torch.equal(layer.y.cpu(), sums.cpu().to(torch.bfloat16))
     finally:
         layer.close()
+
+
+def _concentrated_log(T, E, k, cold):
+    """Every token goes to experts 0..k-1, but for `cold` slots of the last tokens that name one other expert each; None: an
+    even load."""
+    ids = np.tile(np.arange(k, dtype=np.int32), (T, 1))
+    if cold is None:
+        ids = (np.arange(T * k).reshape(T, k) % E).astype(np.int32)
+    else:
+        ids.reshape(-1)[T * k - cold:] = np.arange(k, k + cold, dtype=np.int32)
+    return ids, np.full((T, k), 1.0 / k, dtype=np.float32)
+
+
+@pytest.mark.parametrize("cold", [0, 23, 24, None])
+def test_concentrated_loads_either_side_of_the_choice(gpu_lib, cold):
+    """A batch with few rows per expert on average, large enough that the down projection's kernel is chosen from the loads on
+    the device: big tiles where there are more than twice as many 64-row tiles as 256-row ones (72 + cold against 24 + cold
+    here), otherwise the streaming kernel."""
+    cfg = MoEConfig("conc", T=520, d=2048, E=90, k=8, F=128, modes=("replay",), seed=900 + (cold or 0))
+    ids, w = _concentrated_log(cfg.T, cfg.E, cfg.k, cold)
+    n = np.bincount(ids.reshape(-1), minlength=cfg.E)
+    assert (((n + 63) // 64).sum() > 2 * ((n + 255) // 256).sum()) == (cold in (0, 23))
+    _run_and_check_layer(gpu_lib, cfg, "replay", log=(ids, w))
+
+
+def test_one_context_takes_concentrated_and_even_loads_in_turn(gpu_lib):
+    """The same context with loads on both sides of that choice, other activations each time: every call equals a fresh
+    context's (lists, counts and workspaces of the call before must not show)."""
+    from workloads import make_inputs
+    cfg = MoEConfig("turns", T=520, d=2048, E=90, k=8, F=256, modes=("replay",), seed=55)
+    dv = {n: (v.cuda() if isinstance(v, torch.Tensor) else v) for n, v in make_inputs(cfg).items()}
+    kept = gpu_lib.MoELayer(cfg.T, cfg.d, cfg.E, cfg.k, cfg.F)
+    try:
+        for step, cold in enumerate((0, None, 23, 24, 0)):
+            x = torch.roll(dv["x"], step, dims=0)
+            ids, w = (torch.from_numpy(a).cuda() for a in _concentrated_log(cfg.T, cfg.E, cfg.k, cold))
+            got = kept.forward_replay(x, ids, w, dv).clone()
+            fresh = gpu_lib.MoELayer(cfg.T, cfg.d, cfg.E, cfg.k, cfg.F)
+            try:
+                want = fresh.forward_replay(x, ids, w, dv, fused=False)
+                torch.cuda.synchronize()
+                assert torch.isfinite(want.float()).all() and float(want.float().abs().max()) > 0
+                assert torch.equal(got.view(torch.int16), want.view(torch.int16)), step
+            finally:
+                fresh.close()
+    finally:
+        kept.close()
