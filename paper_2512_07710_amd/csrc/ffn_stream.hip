@@ -47,7 +47,7 @@ struct StreamArgs {
     int fan, n_tok;
     const int32_t* offsets;        // GROUPED: [E+1], of the experts' rows
     int E;
-    const int32_t* big_units;      // not null: nothing to do where it is not zero
+    const int32_t* big_units;      // GROUPED, not GATED: if given, nothing to do where it is not zero
     int32_t* tickets;              // GATED: one per unit, zero before and after the launch
     const uint8_t *Wa, *Wb;
     const float *sa, *sb;
@@ -136,7 +136,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
     constexpr int STAGE = stage_bytes(NW);
     extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
 
-    if (g.big_units && *g.big_units != 0) return;
+    if (!GATED && GROUPED && g.big_units && *g.big_units != 0) return;
     // ---- which block of which unit: XCD x (= blockIdx % 8) walks a contiguous eighth of the units, a unit's blocks side by side
     const int tid = threadIdx.x, lane = tid & 63;
     const int nft = (g.NOUT + FT - 1) / FT;
