@@ -18,6 +18,7 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
 constexpr int COMBINE_THREADS = 256;
+constexpr int64_t Y_CACHED_BYTES = 32ll << 20;
 
 // One thread owns four columns of one token, so a block covers up to 1024 columns and a token takes ceil(d/1024) blocks of equal
 // width: each wave issues its k row reads once and is replaced by a fresh one.  KT > 0: k known at compile time, so that the k reads are
@@ -26,11 +27,13 @@ constexpr int COMBINE_THREADS = 256;
 // Bound by the bytes of the expert rows, each read exactly once: they go past the caches (non-temporal).  One block per
 // token that walked the row (4096 x 5120, k = 8): 144 us = 5.0 TB/s, with non-temporal reads 131; in this form 139 without
 // and 119 (6.0 TB/s) with them; 32768 x 7168: 1.58 -> 1.38 ms.
-// y goes through the caches: whatever reads it is the caller's next kernel.  Rows copied in, combined and y read back, us, y past the
-// caches / through them / one block per token: 7168 columns x k = 1 and 50 MB of rows 39.7 / 37.4 / 36.4, 1920 x 2 34.6 / 32.0 / 32.3.
+// Up to Y_CACHED_BYTES y goes through the caches: whatever reads it is the caller's next kernel.  Rows copied in, combined and y read
+// back, us, y past the caches / through them / one block per token: 7168 columns x k = 1 and 50 MB of rows 39.7 / 37.4 / 36.4, 1920 x 2
+// 34.6 / 32.0 / 32.3.  Larger ones gain nothing in that sequence (45 MB of y level, 200 MB 319 / 323), and the layer alone is
+// faster past them: 8192 x 4096, k = 1 (67 MB) 243 / 251, 32768 x 7168, k = 8 13.70 / 13.87 ms.
 // Equal widths: 1152 columns as blocks of 1024 and 128 left seven eighths of every second block idle (10850 rows, k = 1, in the same
 // sequence 43.3, now 39.2; one block per token 36.9.  The layers around such rows: 75.3 us with one block per token, now 73.8).
-template <int KT>
+template <int KT, bool Y_PAST>
 __global__ __launch_bounds__(COMBINE_THREADS) void combine_kernel(const float* __restrict__ y_perm,
                                                                   const int32_t* __restrict__ inv_perm,
                                                                   const float* __restrict__ topk_w, int d, int k_rt,
@@ -71,7 +74,9 @@ __global__ __launch_bounds__(COMBINE_THREADS) void combine_kernel(const float* _
     u32x2 o;
     o[0] = f32_to_bf16_rne(acc[0]) | (f32_to_bf16_rne(acc[1]) << 16);
     o[1] = f32_to_bf16_rne(acc[2]) | (f32_to_bf16_rne(acc[3]) << 16);
-    *reinterpret_cast<u32x2*>(y + (size_t)t * d + (size_t)c4 * 4) = o;
+    u32x2* const to = reinterpret_cast<u32x2*>(y + (size_t)t * d + (size_t)c4 * 4);
+    if (Y_PAST) __builtin_nontemporal_store(o, to);
+    else *to = o;
     if (y_f32) *reinterpret_cast<f32x4*>(y_f32 + (size_t)t * d + (size_t)c4 * 4) = acc;   // the sums before rounding
 }
 
@@ -82,9 +87,15 @@ hipError_t launch_combine(moe_ctx* c, const float* y_perm, const int32_t* inv_pe
     const moe_dims& D = c->dims;
     const int parts = (D.d / 4 + COMBINE_THREADS - 1) / COMBINE_THREADS;
     const int threads = ((D.d / 4 + parts - 1) / parts + 63) / 64 * 64;
-#define MOE_COMBINE(KT_)                                                                                             \
-    hipLaunchKernelGGL(combine_kernel<KT_>, dim3((unsigned)(D.T * parts)), dim3(threads), 0, c->stream, y_perm, \
+    const bool past = (int64_t)D.T * D.d * (int64_t)sizeof(uint16_t) > Y_CACHED_BYTES;
+#define MOE_COMBINE_AS(KT_, PAST_)                                                                                         \
+    hipLaunchKernelGGL((combine_kernel<KT_, PAST_>), dim3((unsigned)(D.T * parts)), dim3(threads), 0, c->stream, y_perm, \
                        inv_perm, topk_w, D.d, D.k, parts, y, y_f32)
+#define MOE_COMBINE(KT_)                     \
+    do {                                     \
+        if (past) MOE_COMBINE_AS(KT_, true); \
+        else MOE_COMBINE_AS(KT_, false);     \
+    } while (0)
     switch (D.k) {
         case 1: MOE_COMBINE(1); break;
         case 2: MOE_COMBINE(2); break;
@@ -97,6 +108,7 @@ hipError_t launch_combine(moe_ctx* c, const float* y_perm, const int32_t* inv_pe
         default: MOE_COMBINE(0); break;
     }
 #undef MOE_COMBINE
+#undef MOE_COMBINE_AS
     return hipGetLastError();
 }
 
