@@ -52,8 +52,9 @@ typedef struct {
 } moe_dims;
 
 /* Create a context for one layer shape.  Allocates the internal device workspace
- * (chunk histograms, the tile work list, and the quantised hidden activations
- * hq [N,F] u8 + hs [F/128][N] f32).  hip_stream is a hipStream_t (NULL = default
+ * (chunk histograms, router weight planes, tile work lists, sorted activation scales, the
+ * quantised hidden activations hq [N,F] u8 + hs [F/128][N] f32 and, where few rows fall on an
+ * expert, their fp32 values [N,F]).  hip_stream is a hipStream_t (NULL = default
  * stream).  The device current at creation must be current at every later call. */
 int moe_create(moe_ctx** out, const moe_dims* dims, void* hip_stream);
 int moe_destroy(moe_ctx* ctx);
@@ -148,12 +149,12 @@ int moe_quantize_weights_fp8(moe_ctx* ctx, const uint16_t* w_bf16, int64_t rows,
 
 /* Dense block-scaled FP8 linear layer (section 3.1.2 applies FP8 to the dense linear layers as well as to the MoE layers):
  *   y[p,n] = sum_kb xs[kb,p]*ws[n/128,kb] * sum_{c in block kb} xq[p,c]*Wq[n,c],  fp32 out.
- * The grouped down-projection kernel with one group that owns every row.
+ * The grouped down-projection kernels with one group that owns every row.
  *   xq [rows,K] u8 and xs [K/128][rows] f32 as written by moe_quantize_fp8 (dst_rows = NULL);
  *   Wq [NOUT,K] u8; ws [NOUT/128, K/128] f32; y [rows,NOUT] f32.  K and NOUT multiples of 128.
- * Uses the context's work-list storage: ceil(rows/256)*ceil(NOUT/256) must not exceed
- * (T*k/256 + E) * (F/128 + ceil(d/256)) of the context's dims, else MOE_EINVAL; NOUT*K must be
- * below 2^32 (MOE_EINVAL otherwise). */
+ * Uses nothing of the context but its stream and, as the measure of the largest problem it admits, its
+ * dims: ceil(rows/256)*ceil(NOUT/256) must not exceed (T*k/256 + E) * (F/128 + ceil(d/256)), else MOE_EINVAL;
+ * NOUT*K must be below 2^32 (MOE_EINVAL otherwise). */
 int moe_linear_fp8(moe_ctx* ctx, const uint8_t* xq, const float* xs, int32_t rows, int32_t K,
                    const uint8_t* Wq, const float* ws, int32_t NOUT, float* y);
 

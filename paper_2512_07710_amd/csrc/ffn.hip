@@ -382,7 +382,6 @@ template <bool GATED, bool GATHER, bool LINEAR>
 __global__ __launch_bounds__(NTHREADS, 1) void ffn_gemm(const uint8_t* __restrict__ act,
                                                         const float* __restrict__ act_s, int n_rows,
                                                         const int32_t* __restrict__ perm, int fan, int n_tok,
-                                                        const int32_t* __restrict__ offsets,
                                                         const Work* __restrict__ work,
                                                         const int32_t* __restrict__ n_work,
                                                         const uint8_t* __restrict__ Wa,
@@ -432,7 +431,8 @@ __global__ __launch_bounds__(NTHREADS, 1) void ffn_gemm(const uint8_t* __restric
     //      Staged weight row r: GATED: features f0 + (r/64)*32 + r%32, gate (Wa) if (r/32)%2 == 0 else up (Wb).
     //      NARROW tiles (at most 64 rows, see below): wave w's 32 staged rows are 32 consecutive features of the tile
     //      (down projection) or, GATED, [16 gate rows | 16 up rows] of features f0 + 16w .. 16w+15.
-    const bool narrow = wk.nrows <= NARROW_ROWS;               // block-uniform
+    // (LINEAR: products of at most 64 rows stream, and a larger one has no tile as short)
+    const bool narrow = !LINEAR && wk.nrows <= NARROW_ROWS;    // block-uniform
     // A wave whose features all lie beyond NOUT (down projection, NOUT an odd multiple of 128: feature tile half empty)
     // copies the last 32 features again; they are multiplied and not stored.
     Feed feed;
@@ -469,12 +469,14 @@ __global__ __launch_bounds__(NTHREADS, 1) void ffn_gemm(const uint8_t* __restric
     copy_x(feed, 0, 0);
     if (narrow) {
         copy_w_once(feed, 0, 0);
-        // ---- NARROW tile: at most 64 rows.  In the layout above only the two waves of token group 0 would
-        //      multiply, alone on their SIMDs, and such a tile costs 0.7 of a full one.  Here all eight waves work:
+        // ---- NARROW tile: at most 64 rows.  In the layout above a wave has at most two products per K block, with one token group
+        //      half of the waves none, behind a schedule made for eight.  Here
         //      wave w multiplies the 32 staged weight rows it copies itself by the tile's 64 token columns (two
-        //      32x32 products, four matrix instructions per K block), so the matrix work is spread over every SIMD
+        //      32x32 products, four matrix instructions per K block), so the matrix work is spread over every wave
         //      and the tile runs at the speed its weight tile streams in.  Same rings, same copy order, same
         //      barrier per K block as the full tiles; nothing is overlapped by hand - the copies are the bound.
+        //      Against k_loop<1> and weights through the caches, us: gate/up of 64 experts x 4096 x 1408 at 24 rows 117 / 137, at 58
+        //      125 / 145, 256 x 7168 x 2048 at 12 rows 1101 / 1260; down at 50 rows 83 / 88 and 754 / 799.
         const uint32_t off00 = (uint32_t)((half * 2) ^ (l32 & 7) ^ ((l32 >> 3) & 1)) << 4;
         const uint32_t a00 = lds0 + (uint32_t)(wave * 32 + l32) * KB + off00;
         const uint32_t b00 = lds0 + (uint32_t)(X_RING + l32 * KB) + off00;
@@ -801,8 +803,11 @@ static int64_t down_big_units(const moe_dims* D) {
     return (down_form(D) == Down::EITHER ? N / TOK_TILE + N / 65 : max_row_tiles(D, TOK_TILE)) * ((D->d + 255) / 256);
 }
 
-// both work lists
-size_t ffn_work_bytes(const moe_dims* D) { return sizeof(Work) * (size_t)(gate_up_units(D) + down_big_units(D) + 1); }
+// length of the gate/up projection's work list, behind which the down projection's lies; and room for both
+static int64_t gate_up_list(const moe_dims* D) { return gate_up_streams(D) ? 0 : gate_up_units(D); }
+size_t ffn_work_bytes(const moe_dims* D) {
+    return sizeof(Work) * (size_t)(gate_up_list(D) + (down_form(D) == Down::STREAM ? 0 : down_big_units(D)) + 1);
+}
 size_t ffn_ticket_bytes(const moe_dims* D) { return gate_up_streams(D) ? sizeof(int32_t) * (size_t)gate_up_units(D) : 0; }
 size_t ffn_h_rows_bytes(const moe_dims* D) {
     return gate_up_streams(D) ? sizeof(float) * (size_t)((int64_t)D->T * D->k) * (size_t)D->F : 0;
@@ -864,7 +869,7 @@ hipError_t launch_expert_ffn(moe_ctx* c, const uint8_t* xq, const float* xs, con
     const bool stream1 = gate_up_streams(&D);
     const Down down = down_form(&D);
     const int units1 = (int)gate_up_units(&D);
-    Work* work2 = work + units1;                               // the down projection's list
+    Work* work2 = work + gate_up_list(&D);                     // the down projection's list
     int32_t* n_work2 = c->n_tiles + 1;
     if (!stream1) {                                            // (the streaming kernels need neither list nor sorted scales)
         const int lists = down == Down::STREAM ? 1 : 2;
@@ -879,11 +884,11 @@ hipError_t launch_expert_ffn(moe_ctx* c, const uint8_t* xq, const float* xs, con
         if (e != hipSuccess) return e;
     } else if (perm) {
         hipLaunchKernelGGL((ffn_gemm<true, true, false>), dim3(grid1), dim3(NTHREADS), SMEM_BYTES, c->stream, xq, c->xs_sorted, N,
-                           perm, D.k, D.T, offsets, work, c->n_tiles, W1, W3, s1, s3, D.d, D.F, c->hq, c->hs,
+                           perm, D.k, D.T, work, c->n_tiles, W1, W3, s1, s3, D.d, D.F, c->hq, c->hs,
                            (float*)nullptr);
     } else {
         hipLaunchKernelGGL((ffn_gemm<true, false, false>), dim3(grid1), dim3(NTHREADS), SMEM_BYTES, c->stream, xq, xs, N,
-                           (const int32_t*)nullptr, 1, 1, offsets, work, c->n_tiles, W1, W3, s1, s3, D.d, D.F, c->hq,
+                           (const int32_t*)nullptr, 1, 1, work, c->n_tiles, W1, W3, s1, s3, D.d, D.F, c->hq,
                            c->hs, (float*)nullptr);
     }
     if (ev) (void)hipEventRecord(ev[1], c->stream);
@@ -894,7 +899,7 @@ hipError_t launch_expert_ffn(moe_ctx* c, const uint8_t* xq, const float* xs, con
     if (down != Down::STREAM) {
         const int grid2 = ((int)down_big_units(&D) + NXCD - 1) / NXCD * NXCD;
         hipLaunchKernelGGL((ffn_gemm<false, false, false>), dim3(grid2), dim3(NTHREADS), SMEM_BYTES, c->stream, c->hq, c->hs,
-                           N, (const int32_t*)nullptr, 1, 1, offsets, work2, n_work2, W2, (const uint8_t*)nullptr, s2,
+                           N, (const int32_t*)nullptr, 1, 1, work2, n_work2, W2, (const uint8_t*)nullptr, s2,
                            (const float*)nullptr, D.F, D.d, (uint8_t*)nullptr, (float*)nullptr, y_perm);
     }
     if (ev) (void)hipEventRecord(ev[2], c->stream);
@@ -910,7 +915,7 @@ hipError_t launch_linear(moe_ctx* c, const uint8_t* xq, const float* xs, int32_t
     if (linear_streams(rows, NOUT)) return launch_stream_linear(c, xq, xs, rows, K, Wq, ws, NOUT, y);
     const int units = (rows + TOK_TILE - 1) / TOK_TILE * ((NOUT + 255) / 256);
     hipLaunchKernelGGL((ffn_gemm<false, false, true>), dim3((units + NXCD - 1) / NXCD * NXCD), dim3(NTHREADS), SMEM_BYTES,
-                       c->stream, xq, xs, rows, (const int32_t*)nullptr, 1, 1, (const int32_t*)nullptr, (const Work*)nullptr,
+                       c->stream, xq, xs, rows, (const int32_t*)nullptr, 1, 1, (const Work*)nullptr,
                        (const int32_t*)nullptr, Wq, (const uint8_t*)nullptr, ws, (const float*)nullptr, K, NOUT,
                        (uint8_t*)nullptr, (float*)nullptr, y);
     return hipGetLastError();

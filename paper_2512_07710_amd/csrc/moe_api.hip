@@ -62,7 +62,6 @@ int moe_create(moe_ctx** out, const moe_dims* dims, void* hip_stream) {
     const int64_t N = (int64_t)dims->T * dims->k;
     c->n_chunks = (int)((N + PERM_CHUNK - 1) / PERM_CHUNK);
     if (c->n_chunks < 1) c->n_chunks = 1;
-    c->max_tiles = (int)(N / TOK_TILE) + dims->E;
     const size_t nrow = (size_t)(N > 0 ? N : 1);
     bool ok = true;
     ok = ok && hipMalloc((void**)&c->chunk_counts, sizeof(int32_t) * (size_t)c->n_chunks * dims->E) == hipSuccess;
@@ -186,9 +185,11 @@ int moe_linear_fp8(moe_ctx* c, const uint8_t* xq, const float* xs, int32_t rows,
     if (!c || !xq || !xs || !Wq || !ws || !y) return MOE_EINVAL;
     if (rows < 0 || K <= 0 || NOUT <= 0 || K % QBLOCK || NOUT % QBLOCK) return MOE_EINVAL;
     if ((int64_t)NOUT * K >= (int64_t)1 << 32) return MOE_EINVAL;     // 32-bit byte offsets inside the weight matrix
-    const int64_t units = ((int64_t)rows + TOK_TILE - 1) / TOK_TILE * ((NOUT + 255) / 256);
-    const int64_t room = (int64_t)c->max_tiles * (c->dims.F / 128 + (c->dims.d + 255) / 256);
-    if (units > room) return MOE_EINVAL;              // the context's shape bounds the problem size
+    // the size a context admits is a promise of the interface: no storage depends on it, and every unit and grid count of what
+    // passes fits the kernels' 32-bit integers
+    const moe_dims& D = c->dims;
+    const int64_t tiles = ((int64_t)rows + TOK_TILE - 1) / TOK_TILE * ((NOUT + 255) / 256);
+    if (tiles > ((int64_t)D.T * D.k / TOK_TILE + D.E) * (D.F / 128 + (D.d + 255) / 256)) return MOE_EINVAL;
     if (rows == 0) return MOE_OK;
     return hip_rc(launch_linear(c, xq, xs, rows, K, Wq, ws, NOUT, y));
 }

@@ -22,7 +22,6 @@ struct moe_ctx {
     hipStream_t stream;
     int device;
     int n_chunks;            // ceil(N / PERM_CHUNK)
-    int max_tiles;           // upper bound on GEMM row tiles: N/TOK_TILE + E
     int32_t* chunk_counts;   // [n_chunks][E] per-chunk histograms, then their exclusive scans
     void* tiles;             // GEMM work lists (gate/up list, then down list)
     int32_t* n_tiles;        // [2] their lengths
