@@ -570,8 +570,7 @@ __global__ __launch_bounds__(NTHREADS, 1) void ffn_gemm(const uint8_t* __restric
             for (int ts = 0; ts < 2; ++ts) {
 #pragma unroll
                 for (int r = 0; r < 8; ++r) {
-                    const float g = an[ts][r], u = an[ts][r + 8];
-                    const float v = g * __builtin_amdgcn_rcpf(1.0f + __expf(-g)) * u;
+                    const float v = swiglu(an[ts][r], an[ts][r + 8]);
                     h[ts][r] = v;
                     amax[ts] = fmaxf(amax[ts], fabsf(v));
                 }
@@ -587,23 +586,13 @@ __global__ __launch_bounds__(NTHREADS, 1) void ffn_gemm(const uint8_t* __restric
 #pragma unroll
                 for (int w = 0; w < 8; ++w) am = fmaxf(am, s_amax[w * 64 + trow]);
                 const float sc = (am == 0.f) ? 1.0f : am / 448.0f;
-                // the same correctly rounded quotient as in the full tiles' epilogue
-                float inv = __builtin_amdgcn_rcpf(sc);
-                inv = fmaf(fmaf(-sc, inv, 1.0f), inv, inv);
-                const bool mid_range = sc > 1e-30f && sc < 1e30f;
-                auto quot = [&](float hv) {
-                    const float q0 = hv * inv;
-                    return mid_range ? fmaf(fmaf(-q0, sc, hv), inv, q0) : hv / sc;
-                };
+                const Quotient q(sc);
                 if (p < row_end) {
                     uint8_t* dst = hq + (size_t)p * NOUT + f0 + wave * 16 + half * 4;
 #pragma unroll
-                    for (int r4 = 0; r4 < 2; ++r4) {
-                        int code = 0;
-                        code = __builtin_amdgcn_cvt_pk_fp8_f32(quot(h[ts][r4 * 4]), quot(h[ts][r4 * 4 + 1]), code, false);
-                        code = __builtin_amdgcn_cvt_pk_fp8_f32(quot(h[ts][r4 * 4 + 2]), quot(h[ts][r4 * 4 + 3]), code, true);
-                        *reinterpret_cast<uint32_t*>(dst + r4 * 8) = (uint32_t)code;
-                    }
+                    for (int r4 = 0; r4 < 2; ++r4)
+                        *reinterpret_cast<uint32_t*>(dst + r4 * 8) =
+                            e4m3_codes4(q, h[ts][r4 * 4], h[ts][r4 * 4 + 1], h[ts][r4 * 4 + 2], h[ts][r4 * 4 + 3]);
                     if (half == 0 && wave == 0) hs[(size_t)wk.ft * n_rows + p] = sc;
                 }
             }
@@ -665,9 +654,7 @@ __global__ __launch_bounds__(NTHREADS, 1) void ffn_gemm(const uint8_t* __restric
             float am = 0.f;
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
-                const float g = acc[0][ts][r], u = acc[1][ts][r];
-                // silu(g)*u with the hardware reciprocal (1 ulp): far below the matrix cores' own error
-                const float v = g * __builtin_amdgcn_rcpf(1.0f + __expf(-g)) * u;
+                const float v = swiglu(acc[0][ts][r], acc[1][ts][r]);
                 h[ts][r] = v;
                 am = fmaxf(am, fabsf(v));
             }
@@ -683,26 +670,13 @@ __global__ __launch_bounds__(NTHREADS, 1) void ffn_gemm(const uint8_t* __restric
             const float am = fmaxf(fmaxf(s_amax[trow], s_amax[X_ROWS + trow]),
                                    fmaxf(s_amax[2 * X_ROWS + trow], s_amax[3 * X_ROWS + trow]));
             const float sc = (am == 0.f) ? 1.0f : am / 448.0f;
-            // h / sc, correctly rounded, for 16 values per token: a reciprocal refined once, then the
-            // quotient estimate corrected by its exact remainder (three instructions instead of a full
-            // division each; equal to the division wherever sc is far from the ends of the fp32 range,
-            // and the plain division elsewhere).  |h / sc| <= 448 up to one rounding, so no clamp.
-            float inv = __builtin_amdgcn_rcpf(sc);
-            inv = fmaf(fmaf(-sc, inv, 1.0f), inv, inv);
-            const bool mid_range = sc > 1e-30f && sc < 1e30f;
-            auto quot = [&](float hv) {
-                const float q0 = hv * inv;
-                return mid_range ? fmaf(fmaf(-q0, sc, hv), inv, q0) : hv / sc;
-            };
+            const Quotient q(sc);
             if (p < row_end) {
                 uint8_t* dst = hq + (size_t)p * NOUT + f0 + wf * 32 + half * 4;
 #pragma unroll
-                for (int r4 = 0; r4 < 4; ++r4) {
-                    int code = 0;
-                    code = __builtin_amdgcn_cvt_pk_fp8_f32(quot(h[ts][r4 * 4]), quot(h[ts][r4 * 4 + 1]), code, false);
-                    code = __builtin_amdgcn_cvt_pk_fp8_f32(quot(h[ts][r4 * 4 + 2]), quot(h[ts][r4 * 4 + 3]), code, true);
-                    *reinterpret_cast<uint32_t*>(dst + r4 * 8) = (uint32_t)code;
-                }
+                for (int r4 = 0; r4 < 4; ++r4)
+                    *reinterpret_cast<uint32_t*>(dst + r4 * 8) =
+                        e4m3_codes4(q, h[ts][r4 * 4], h[ts][r4 * 4 + 1], h[ts][r4 * 4 + 2], h[ts][r4 * 4 + 3]);
                 if (half == 0 && wf == 0) hs[(size_t)wk.ft * n_rows + p] = sc;
             }
         }
