@@ -47,7 +47,7 @@ struct StreamArgs {
     int fan, n_tok;
     const int32_t* offsets;        // GROUPED: [E+1], of the experts' rows
     int E;
-    const int32_t* big_units;      // GROUPED, not GATED: if given, nothing to do where it is not zero
+    const int32_t* big_units;      // CHOSEN: nothing to do where it is not zero
     int32_t* tickets;              // GATED: one per unit, zero before and after the launch
     const uint8_t *Wa, *Wb;
     const float *sa, *sb;
@@ -129,14 +129,15 @@ struct RowTiles {
     }
 };
 
-template <int NW, int D, bool GATED, bool GATHER, bool GROUPED>
+// CHOSEN: the kernel that made the work lists has counted the tiles and may have given the batch to the big tiles
+template <int NW, int D, bool GATED, bool GATHER, bool GROUPED, bool CHOSEN>
 __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2))) void ffn_stream(StreamArgs g) {
     constexpr int S = 8 / NW;                                  // blocks per unit
     constexpr int FT = GATED ? 128 : 256;                      // output features per unit
     constexpr int STAGE = stage_bytes(NW);
     extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
 
-    if (!GATED && GROUPED && g.big_units && *g.big_units != 0) return;
+    if (CHOSEN && *g.big_units != 0) return;
     // ---- which block of which unit: XCD x (= blockIdx % 8) walks a contiguous eighth of the units, a unit's blocks side by side
     const int tid = threadIdx.x, lane = tid & 63;
     const int nft = (g.NOUT + FT - 1) / FT;
@@ -397,16 +398,16 @@ constexpr int NW_FEW = 2, D_FEW = 4, FEW_UNITS = 64;
 // 17.0 when it is still there), beyond it cannot.
 constexpr int64_t LINEAR_ONCE_BYTES = 256ll << 20;
 
-template <int WAVES, int STAGES, bool GATED, bool GATHER, bool GROUPED>
+template <int WAVES, int STAGES, bool GATED, bool GATHER, bool GROUPED, bool CHOSEN = false>
 hipError_t launch(hipStream_t stream, const StreamArgs& a, int max_units) {
     const int grid = (max_units * (8 / WAVES) + NXCD - 1) / NXCD * NXCD;
-    hipLaunchKernelGGL((ffn_stream<WAVES, STAGES, GATED, GATHER, GROUPED>), dim3(grid), dim3(WAVES * 64), STAGES * stage_bytes(WAVES), stream, a);
+    hipLaunchKernelGGL((ffn_stream<WAVES, STAGES, GATED, GATHER, GROUPED, CHOSEN>), dim3(grid), dim3(WAVES * 64), STAGES * stage_bytes(WAVES), stream, a);
     return hipGetLastError();
 }
 
-template <int WAVES, int STAGES, bool GATED, bool GATHER, bool GROUPED>
+template <int WAVES, int STAGES, bool GATED, bool GATHER, bool GROUPED, bool CHOSEN = false>
 hipError_t allow_lds() {
-    return hipFuncSetAttribute(reinterpret_cast<const void*>(&ffn_stream<WAVES, STAGES, GATED, GATHER, GROUPED>),
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(&ffn_stream<WAVES, STAGES, GATED, GATHER, GROUPED, CHOSEN>),
                                hipFuncAttributeMaxDynamicSharedMemorySize, STAGES * stage_bytes(WAVES));
 }
 
@@ -417,6 +418,7 @@ hipError_t set_stream_lds_limits() {
     hipError_t e = allow_lds<NW, D, true, true, true>();
     if (e == hipSuccess) e = allow_lds<NW, D, true, false, true>();
     if (e == hipSuccess) e = allow_lds<NW, D, false, false, true>();
+    if (e == hipSuccess) e = allow_lds<NW, D, false, false, true, true>();
     if (e == hipSuccess) e = allow_lds<NW, D, false, false, false>();
     if (e == hipSuccess) e = allow_lds<NW_FEW, D_FEW, false, false, false>();
     return e;
@@ -435,7 +437,7 @@ hipError_t launch_stream_down(moe_ctx* c, const int32_t* offsets, int max_units,
     const moe_dims& m = c->dims;
     const StreamArgs a{c->hq, c->hs, m.T * m.k, nullptr, 1, 1, offsets, m.E, big_units, nullptr, W2, nullptr, s2, nullptr, m.F, m.d,
                        true, nullptr, nullptr, nullptr, y_perm};
-    return launch<NW, D, false, false, true>(c->stream, a, max_units);
+    return big_units ? launch<NW, D, false, false, true, true>(c->stream, a, max_units) : launch<NW, D, false, false, true>(c->stream, a, max_units);
 }
 
 hipError_t launch_stream_linear(moe_ctx* c, const uint8_t* xq, const float* xs, int32_t rows, int32_t K, const uint8_t* Wq,
