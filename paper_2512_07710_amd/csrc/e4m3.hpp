@@ -20,25 +20,28 @@ __device__ inline float bf16x8_amax(const u32x4& u) {
     return amax;
 }
 
+// v / s from an estimate of 1/s: the reciprocal refined once, then the quotient estimate corrected by its exact remainder
+// (Markstein's correction); signs are arranged so that -0 stays -0.  For every bf16 significand over every scale amax/448 with a
+// bf16 amax, and an estimate up to 2 ulp off, it equals the division (tests/test_quotient_host.py compiles these two functions).
+__host__ __device__ inline float refined_reciprocal(float s, float estimate) { return fmaf(fmaf(-s, estimate, 1.0f), estimate, estimate); }
+__host__ __device__ inline float corrected_quotient(float v, float s, float inv) {
+    const float q0 = v * inv;
+    return fmaf(-fmaf(q0, s, -v), inv, q0);
+}
+
 // Codes of 8 bf16 values over the group's scale s = amax/448 (1 for an all-zero group).
 // A true division is some ten instructions and made the quantisation kernels bound by the vector ALU (weights: 4.4 TB/s,
-// against 5.8 with this form).  The quotient is instead estimated with a reciprocal refined once and corrected by its
-// exact remainder (Markstein's correction); signs are arranged so that -0 stays -0.  For every bf16 significand over every
-// scale amax/448 with a bf16 amax, and a reciprocal estimate up to 2 ulp off, it equals the division (checked exhaustively
-// on the CPU).  In the stated range of s no remainder of a quotient that can reach a non-zero code underflows; outside it
-// (and for an infinite s) the division itself is taken.
+// against 5.8 with this form).  In the stated range of s no remainder of a quotient that can reach a non-zero code underflows;
+// outside it (and for an infinite s) the division itself is taken.
+constexpr float SCALE_MID_MIN = 1e-25f, SCALE_MID_MAX = 1e25f;
 struct E4m3Coder {
     float s, inv;
     bool mid_range;
     __device__ explicit E4m3Coder(float scale) : s(scale) {
-        inv = __builtin_amdgcn_rcpf(s);
-        inv = fmaf(fmaf(-s, inv, 1.0f), inv, inv);
-        mid_range = s > 1e-25f && s < 1e25f;
+        inv = refined_reciprocal(s, __builtin_amdgcn_rcpf(s));
+        mid_range = s > SCALE_MID_MIN && s < SCALE_MID_MAX;
     }
-    __device__ float quotient(float v) const {
-        const float q0 = v * inv;
-        return fmaf(-fmaf(q0, s, -v), inv, q0);
-    }
+    __device__ float quotient(float v) const { return corrected_quotient(v, s, inv); }
     // four codes, a in the low byte.  |v| <= amax, so the quotient is at most 448 up to one rounding, which the conversion
     // rounds back; the lower bound stays because it is what makes a NaN -448.
     __device__ uint32_t pack4(float a, float b, float c, float d) const {

@@ -1,0 +1,207 @@
+"""GPU: the instances and the rules between them that the layers of the other files do not reach: the dense product on the big
+tiles at ragged sizes, the gathering form of the streaming kernel, sizes either side of every rule that chooses between
+streaming and big tiles, graph replay of such layers, values that are not finite in the quantisers."""
+import numpy as np
+import pytest
+import torch
+
+from workloads import MoEConfig, make_inputs
+from test_gpu_parity import _run_and_check_layer
+
+pytestmark = pytest.mark.gpu
+
+
+# --------------------------------------------------------------------------- dense products on the big tiles
+def _codes(g, *shape):
+    return (torch.randn(shape, generator=g, device="cuda") * 60).to(torch.float8_e4m3fn).view(torch.uint8)
+
+
+# all above 128 big tiles, so that none streams: one ragged row tile, two and four, many with a last one of five rows, and 3 to
+# 8 groups of 32 rows in a tile, odd and even
+@pytest.mark.parametrize("rows,K,NOUT", [(70, 384, 259 * 128), (129, 128, 257 * 128), (193, 256, 258 * 128), (257, 256, 131 * 128),
+                                         (300, 1280, 131 * 128), (777, 128, 67 * 128), (130 * 256 + 5, 256, 128), (9000, 640, 9 * 128)])
+def test_big_tile_linear_at_ragged_sizes(gpu_lib, rows, K, NOUT):
+    """Every row of the product: against the same rows in calls of 64, which stream (the same instructions in the same order, so
+    the same bits), and against a 64-bit evaluation (bar 1e-4: the matrix pipe's own rounding is 1.3e-5)."""
+    assert (rows + 255) // 256 * ((NOUT + 255) // 256) > 128
+    g = torch.Generator(device="cuda").manual_seed(rows + K)
+    xq, wq = _codes(g, rows, K), _codes(g, NOUT, K)
+    xs = torch.rand((K // 128, rows), generator=g, device="cuda") + 0.5
+    ws = torch.rand((NOUT // 128, K // 128), generator=g, device="cuda") + 0.5
+    ctx = gpu_lib.moe_create(rows, K, 1, 1, NOUT)
+    try:
+        y = torch.full((rows, NOUT), float("nan"), device="cuda")
+        gpu_lib.moe_linear_fp8(ctx, xq, xs, rows, K, wq, ws, NOUT, y)
+        part = torch.empty((64, NOUT), device="cuda")
+        wd = wq.view(torch.float8_e4m3fn).double().view(NOUT // 128, 128, K // 128, 128) * ws[:, None, :, None].double()
+        wd = wd.view(NOUT, K).T.contiguous()
+        err = ref = 0.0
+        for r in range(0, rows, 64):
+            n = min(64, rows - r)
+            part.fill_(float("nan"))
+            xs_r = xs[:, r:r + n].contiguous()
+            gpu_lib.moe_linear_fp8(ctx, xq[r:r + n], xs_r, n, K, wq, ws, NOUT, part)
+            assert torch.equal(y[r:r + n], part[:n]), r
+            xd = xq[r:r + n].view(torch.float8_e4m3fn).double().view(n, K // 128, 128) * xs_r.T[:, :, None].double()
+            exact = xd.view(n, K) @ wd
+            err += float((part[:n].double() - exact).square().sum())
+            ref += float(exact.square().sum())
+        assert (err / ref) ** 0.5 < 1e-4
+    finally:
+        gpu_lib.moe_destroy(ctx)
+
+
+@pytest.mark.parametrize("K", [128, 1024])
+def test_big_tile_linear_of_small_integers_is_exact(gpu_lib, K):
+    """Unit scales and codes that decode to multiples of 0.5 up to 4: every partial sum is a multiple of 0.25 below 2^22, so fp32
+    accumulation loses nothing and the product must be exact."""
+    rows, NOUT = 333, 131 * 128
+    g = torch.Generator(device="cuda").manual_seed(K)
+    small = lambda *s: (torch.randint(-8, 9, s, generator=g, device="cuda") * 0.5).to(torch.float8_e4m3fn).view(torch.uint8)
+    xq, wq = small(rows, K), small(NOUT, K)
+    ctx = gpu_lib.moe_create(rows, K, 1, 1, NOUT)
+    try:
+        y = torch.full((rows, NOUT), float("nan"), device="cuda")
+        gpu_lib.moe_linear_fp8(ctx, xq, torch.ones((K // 128, rows), device="cuda"), rows, K, wq,
+                               torch.ones((NOUT // 128, K // 128), device="cuda"), NOUT, y)
+        exact = xq.view(torch.float8_e4m3fn).double() @ wq.view(torch.float8_e4m3fn).double().T.contiguous()
+        assert torch.equal(y.double(), exact)
+    finally:
+        gpu_lib.moe_destroy(ctx)
+
+
+# --------------------------------------------------------------------------- the gathering form of the streaming kernel
+def _skewed_log(T, E, hot0, hot1, step):
+    """k = 2 distinct ids a token: expert 0 gets the first `hot0` tokens, expert 1 the last `hot1`, the other slots go round."""
+    t = np.arange(T)
+    ids = np.stack([2 + (t + step) % (E - 2), 2 + (t + step + 1) % (E - 2)], axis=1).astype(np.int32)
+    ids[:hot0, 0] = 0
+    ids[T - hot1:, 1] = 1
+    return np.roll(ids, step, axis=0).copy(), np.random.default_rng(T + step).dirichlet(np.ones(2), T).astype(np.float32)
+
+
+@pytest.mark.parametrize("T,d,E,F,hot0,hot1", [(150, 256, 16, 384, 130, 40), (100, 384, 16, 128, 65, 64), (150, 640, 16, 640, 129, 33),
+                                               (90, 8320, 12, 256, 70, 33), (1, 384, 16, 384, 0, 0), (33, 1152, 24, 256, 33, 32)])
+def test_gathering_streaming_form(gpu_lib, T, d, E, F, hot0, hot1):
+    """Two experts a token, so that gathered rows, token planes and sorted rows differ: two to 65 K blocks, experts of one to three
+    streaming tiles, odd feature tiles.  Three calls on one context with other activations and routing each time, the
+    gathered form against a fresh context's expert-ordered one bit for bit; that one against the oracle."""
+    cfg = MoEConfig("gather", T=T, d=d, E=E, k=2, F=F, modes=("replay",), seed=T + d)
+    assert T * 2 <= 32 * E and E * (F // 128) < 256                      # streams
+    dv = {n: (v.cuda() if isinstance(v, torch.Tensor) else v) for n, v in make_inputs(cfg).items()}
+    _run_and_check_layer(gpu_lib, cfg, "replay", log=_skewed_log(T, E, hot0, hot1, 0))
+    kept = gpu_lib.MoELayer(T, d, E, 2, F)
+    try:
+        for step in (0, 1, 2):
+            x = (torch.roll(dv["x"].float(), step, dims=1) * (1.0 + step)).to(torch.bfloat16)
+            ids, w = (torch.from_numpy(a).cuda() for a in _skewed_log(T, E, hot0, hot1, step))
+            kept.y_perm.fill_(float("nan"))
+            got = kept.forward_replay(x, ids, w, dv, fused=True).clone()
+            hq, hs = kept.hidden()
+            fresh = gpu_lib.MoELayer(T, d, E, 2, F)
+            try:
+                want = fresh.forward_replay(x, ids, w, dv, fused=False)
+                hq_w, hs_w = fresh.hidden()
+                torch.cuda.synchronize()
+                assert torch.equal(hq, hq_w) and torch.equal(hs.view(torch.int32), hs_w.view(torch.int32)), step
+                assert torch.equal(kept.y_perm.view(torch.int32), fresh.y_perm.view(torch.int32)), step
+                assert torch.equal(got.view(torch.int16), want.view(torch.int16)), step
+            finally:
+                fresh.close()
+    finally:
+        kept.close()
+
+
+# --------------------------------------------------------------------------- either side of every rule
+@pytest.mark.parametrize("T,d,E,k,F", [
+    (800, 128, 100, 1, 384), (801, 128, 100, 1, 384),       # gate/up: 8 rows per expert, no idle units
+    (1280, 128, 40, 1, 768), (1281, 128, 40, 1, 768),       #   32 rows, units expected just below 256
+    (1280, 128, 40, 1, 896),                                #   and above
+    (480, 256, 10, 1, 256), (481, 256, 10, 1, 256),         # down: 48 rows per expert
+    (128, 128, 130, 8, 1408), (129, 128, 130, 8, 1408),     # gate/up units of the most concentrated log: 176 and 264
+    (512, 2048, 90, 8, 128), (513, 2048, 90, 8, 128),       # down units of it: 512 and 576
+    (64, 8448, 22, 16, 256), (65, 8448, 22, 16, 256),       #   528 in one row tile, where no weight passes twice; 1056
+], ids=str)
+def test_layers_either_side_of_the_streaming_rules(gpu_lib, T, d, E, k, F):
+    """The last size of one kernel and the first of the other, stage by stage against the oracle.  Equal gate weights: the k rows
+    of a token and their errors are independent, so the layer's relative error is then that of its rows (y_perm, held to the
+    same bar).  With drawn weights few rows carry a token, and with F = 128, one scale block a row, a single hidden code
+    that is steps off moved one of 513 tokens by 3e-2 of its norm, which is 1.3e-3 of the whole tensor's (3e-2 / sqrt(513))."""
+    cfg = MoEConfig("rule", T=T, d=d, E=E, k=k, F=F, modes=("replay",), seed=T + F)
+    rng = np.random.default_rng(T + d)
+    ids = np.argsort(rng.random((T, E)), axis=1)[:, :k].astype(np.int32)
+    _run_and_check_layer(gpu_lib, cfg, "replay", log=(np.ascontiguousarray(ids), np.full((T, k), 1.0 / k, dtype=np.float32)))
+
+
+# --------------------------------------------------------------------------- graph replay
+@pytest.mark.parametrize("T,d,E,k,F", [(24, 640, 16, 2, 384), (520, 2048, 90, 8, 128)], ids=["streaming", "chosen-on-device"])
+def test_graph_replay_with_other_logs_and_activations(gpu_lib, T, d, E, k, F):
+    """A replayed layer recorded into a graph; between replays its inputs change in place, from an even log to one that sends
+    every token to the same experts and back, with eager work in between.  Every replay equals the eager result."""
+    cfg = MoEConfig("graph", T=T, d=d, E=E, k=k, F=F, modes=("replay",), seed=T)
+    dv = {n: (v.cuda() if isinstance(v, torch.Tensor) else v) for n, v in make_inputs(cfg).items()}
+    even = (torch.arange(T * k, device="cuda").view(T, k) % E).to(torch.int32).contiguous()
+    same = torch.arange(k, device="cuda", dtype=torch.int32).repeat(T, 1)
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        layer, eager = (gpu_lib.MoELayer(T, d, E, k, F, stream=stream) for _ in range(2))
+        try:
+            x, ids, w = dv["x"].clone(), even.clone(), torch.full((T, k), 1.0 / k, device="cuda")
+            layer.forward_replay(x, ids, w, dv)
+            stream.synchronize()
+            graph = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(graph, stream=stream):
+                layer.forward_replay(x, ids, w, dv)
+            seen = []
+            for rep, log in enumerate((even, same, even, same, same)):
+                ids.copy_(log)
+                x.copy_(torch.roll(dv["x"], rep, dims=0))
+                layer.y.zero_()
+                layer.y_perm.zero_()
+                graph.replay()
+                want = eager.forward_replay(x, ids, w, dv)
+                stream.synchronize()
+                assert torch.equal(layer.y.view(torch.int16), want.view(torch.int16)), rep
+                seen.append(layer.y.clone())
+                _ = (dv["W_r"] * 2).sum().item()
+            assert not torch.equal(seen[0], seen[1]) and not torch.equal(seen[3], seen[4])
+        finally:
+            layer.close()
+            eager.close()
+
+
+# --------------------------------------------------------------------------- values that are not finite
+def test_quantisers_of_values_that_are_not_finite(gpu_lib):
+    """A NaN does not count towards the scale and becomes -448; an infinity makes the scale infinite, all finite values of its
+    group zeros and infinities -448 (infinity over infinity); a group of NaNs has scale 1.  The other groups are untouched."""
+    rows, cols = 256, 512
+    g = torch.Generator().manual_seed(7)
+    x = torch.randn((rows, cols), generator=g)
+    x[3, 5] = x[3, 130] = x[200, 511] = float("nan")
+    x[9, 128:256] = float("nan")
+    x[17, 260] = float("inf")
+    x[18, 261] = -float("inf")
+    x[19, 262], x[19, 263] = float("inf"), float("nan")
+    xb = x.to(torch.bfloat16)
+    ctx = gpu_lib.moe_create(0, 128, 1, 1, 128)
+
+    def expected(groups):                                              # [..., 128 or 128 x 128 values of a group as the last axis]
+        v = groups.float()
+        amax = torch.where(v.isnan(), torch.zeros(()), v.abs()).amax(-1, keepdim=True)
+        s = torch.where(amax == 0, torch.ones(()), amax / 448.0)
+        q = v / s
+        q = torch.where(q.isnan(), torch.full((), -448.0), q.clamp(-448.0, 448.0))
+        return q.to(torch.float8_e4m3fn).view(torch.uint8), s.squeeze(-1)
+
+    try:
+        q, s = torch.empty((rows, cols), dtype=torch.uint8, device="cuda"), torch.empty((cols // 128, rows), device="cuda")
+        gpu_lib.moe_quantize_fp8(ctx, xb.cuda(), rows, cols, 128, None, 1, q, s)
+        q_e, s_e = expected(xb.view(rows, cols // 128, 128))
+        assert torch.equal(q.cpu().view(rows, cols // 128, 128), q_e) and torch.equal(s.cpu().T, s_e)
+        qw, sw = torch.empty((rows, cols), dtype=torch.uint8, device="cuda"), torch.empty((rows // 128, cols // 128), device="cuda")
+        gpu_lib.moe_quantize_weights_fp8(ctx, xb.cuda(), rows, cols, qw, sw)
+        blocks = lambda t: t.view(rows // 128, 128, cols // 128, 128).transpose(1, 2).reshape(rows // 128, cols // 128, -1)
+        q_e, s_e = expected(blocks(xb))
+        assert torch.equal(blocks(qw.cpu()), q_e) and torch.equal(sw.cpu(), s_e)
+    finally:
+        gpu_lib.moe_destroy(ctx)
