@@ -18,25 +18,23 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
 constexpr int COMBINE_THREADS = 256;
-constexpr int64_t ROWS_CACHED_BYTES = 96ll << 20, Y_CACHED_BYTES = 32ll << 20;
+constexpr int64_t LAYER_CACHED_BYTES = 192ll << 20, ROWS_CACHED_BYTES = 96ll << 20;
 
 // One thread owns four columns of one token, so a block covers up to 1024 columns and a token takes ceil(d/1024) blocks of equal
 // width: each wave issues its k row reads once and is replaced by a fresh one.  KT > 0: k known at compile time, so that the k reads are
 // all in flight before the first multiply-add; KT == 0: any k up to MAX_K.
 //
-// Bound by the bytes of the expert rows, each read exactly once.  Beyond ROWS_CACHED_BYTES they go past the caches (non-temporal).  One
-// block per token that walked the row (4096 x 5120, k = 8): 144 us = 5.0 TB/s, with non-temporal reads 131; in this form 139
-// without and 119 (6.0 TB/s) with them; 32768 x 7168: 1.58 -> 1.38 ms.  Fewer rows are still in the last-level cache, where the
-// down projection left them, and non-temporal reads of them are at the mercy of where they lie: 88 MB of rows (1901 x 1920, k = 6)
-// copied in, combined and y read back 44 or 51 us, 44 through the caches.  Layers, us, rows past the caches / through them: 65..100 MB
-// level, 123 MB 151 / 159, 164 MB 199 / 209, 295 MB 254 / 270.
-// y is read by the caller's next kernel and goes through the caches up to Y_CACHED_BYTES.  The same sequence, us, y past the
-// caches / through them / one block per token: 7168 columns x k = 1 and 50 MB of rows 39.7 / 37.4 / 36.4, 1920 x 2
-// 34.6 / 32.0 / 32.3.  Larger ones gain nothing in it (45 MB of y level, 200 MB 319 / 323), and the layer alone is
-// faster past them: 8192 x 4096, k = 1 (67 MB) 243 / 251, 32768 x 7168, k = 8 13.70 / 13.87 ms.
+// Bound by the bytes of the expert rows, each read exactly once.  PAST: they go past the caches (non-temporal), and so does y.  One block
+// per token that walked the row (4096 x 5120, k = 8): 144 us = 5.0 TB/s, with non-temporal reads 131; in this form 139
+// without and 119 (6.0 TB/s) with them; 32768 x 7168: 1.58 -> 1.38 ms.
+// Not PAST: a layer whose weights and rows stay in the last-level cache together.  Non-temporal reads are then at the mercy of where the
+// rows lie: 88 MB of them (1901 x 1920, k = 6) copied in, combined and y read back 44 or 51 us, through the caches 44; layers of 1233 x
+// 1792, k = 7 (62 MB) 80.6 / 76.5, of 1901 x 2048, k = 6 (93 MB) 100.9 / 95.2.  y stays near for its reader: 7168 columns x k = 1 and
+// 50 MB of rows in the same sequence 39.7 / 37.4.  Other layers are faster PAST: 777 x 2176, k = 5 with 351 MB of weights 117 us,
+// y through the caches 119.5, the rows as well 125; 123 MB of rows 151 / 159, 295 MB 254 / 270.
 // Equal widths: 1152 columns as blocks of 1024 and 128 left seven eighths of every second block idle (10850 rows, k = 1, in the same
 // sequence 43.3, now 39.2; one block per token 36.9.  The layers around such rows: 75.3 us with one block per token, now 73.8).
-template <int KT, bool ROWS_PAST, bool Y_PAST>
+template <int KT, bool PAST>
 __global__ __launch_bounds__(COMBINE_THREADS) void combine_kernel(const float* __restrict__ y_perm,
                                                                   const int32_t* __restrict__ inv_perm,
                                                                   const float* __restrict__ topk_w, int d, int k_rt,
@@ -51,7 +49,7 @@ __global__ __launch_bounds__(COMBINE_THREADS) void combine_kernel(const float* _
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
     auto load = [&](int row) {
         const f32x4* const from = reinterpret_cast<const f32x4*>(y_perm + (size_t)row * d + (size_t)c4 * 4);
-        return ROWS_PAST ? __builtin_nontemporal_load(from) : *from;
+        return PAST ? __builtin_nontemporal_load(from) : *from;
     };
     auto add = [&](float wj, const f32x4& v) {
 #pragma unroll
@@ -79,7 +77,7 @@ __global__ __launch_bounds__(COMBINE_THREADS) void combine_kernel(const float* _
     o[0] = f32_to_bf16_rne(acc[0]) | (f32_to_bf16_rne(acc[1]) << 16);
     o[1] = f32_to_bf16_rne(acc[2]) | (f32_to_bf16_rne(acc[3]) << 16);
     u32x2* const to = reinterpret_cast<u32x2*>(y + (size_t)t * d + (size_t)c4 * 4);
-    if (Y_PAST) __builtin_nontemporal_store(o, to);
+    if (PAST) __builtin_nontemporal_store(o, to);
     else *to = o;
     if (y_f32) *reinterpret_cast<f32x4*>(y_f32 + (size_t)t * d + (size_t)c4 * 4) = acc;   // the sums before rounding
 }
@@ -91,16 +89,15 @@ hipError_t launch_combine(moe_ctx* c, const float* y_perm, const int32_t* inv_pe
     const moe_dims& D = c->dims;
     const int parts = (D.d / 4 + COMBINE_THREADS - 1) / COMBINE_THREADS;
     const int threads = ((D.d / 4 + parts - 1) / parts + 63) / 64 * 64;
-    const int64_t y_bytes = (int64_t)D.T * D.d * (int64_t)sizeof(uint16_t);
-    const bool rows_past = 2 * y_bytes * D.k > ROWS_CACHED_BYTES, y_past = rows_past && y_bytes > Y_CACHED_BYTES;
-#define MOE_COMBINE_AS(KT_, ROWS_, Y_)                                                                                       \
-    hipLaunchKernelGGL((combine_kernel<KT_, ROWS_, Y_>), dim3((unsigned)(D.T * parts)), dim3(threads), 0, c->stream, y_perm, \
+    const int64_t row_bytes = (int64_t)D.T * D.k * D.d * (int64_t)sizeof(float), weight_bytes = 3ll * D.E * D.d * D.F;
+    const bool past = row_bytes > ROWS_CACHED_BYTES || row_bytes + weight_bytes > LAYER_CACHED_BYTES;
+#define MOE_COMBINE_AS(KT_, PAST_)                                                                                         \
+    hipLaunchKernelGGL((combine_kernel<KT_, PAST_>), dim3((unsigned)(D.T * parts)), dim3(threads), 0, c->stream, y_perm, \
                        inv_perm, topk_w, D.d, D.k, parts, y, y_f32)
-#define MOE_COMBINE(KT_)                                     \
-    do {                                                     \
-        if (y_past) MOE_COMBINE_AS(KT_, true, true);         \
-        else if (rows_past) MOE_COMBINE_AS(KT_, true, false); \
-        else MOE_COMBINE_AS(KT_, false, false);              \
+#define MOE_COMBINE(KT_)                     \
+    do {                                     \
+        if (past) MOE_COMBINE_AS(KT_, true); \
+        else MOE_COMBINE_AS(KT_, false);     \
     } while (0)
     switch (D.k) {
         case 1: MOE_COMBINE(1); break;
