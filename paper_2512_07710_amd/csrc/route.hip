@@ -37,6 +37,10 @@ constexpr int ROUTE_MAX_SPLITS = 16;
 // Batches of at most ROUTE_ROWS_MAX_T tokens score on the vector ALU instead (us for the whole layer, that / matrix cores: one
 // token 44 / 52, 8 x 256 experts 138 / 157, 16 717 / 738 on the widest layer, 32 level, 64 120 / 114, 128 141 / 119).
 constexpr int ROUTE_ROWS_MAX_T = 32;
+// A width of one K chunk has no split form: up to 128 experts its single kernel is the faster one beyond this many tokens (route call,
+// us, vector ALU / matrix cores, 8 experts: 16 tokens 11.9 / 12.3, 24 13.7 / 12.3, 32 15.8 / 12.3; 64 experts, 32 17.5 / 16.9; 256
+// experts 19.0 / 23.9).
+constexpr int ROUTE_ROWS_ONE_CHUNK_MAX_T = 16;
 
 __device__ inline uint32_t f32_to_bf16_rne_bits(float v) {
     const uint32_t b = __float_as_uint(v);
@@ -646,7 +650,8 @@ hipError_t launch_route(moe_ctx* c, const uint16_t* x, const float* W_r, const f
         return hipGetLastError();
     };
     const int slices = (D.d + ROWS_COLS - 1) / ROWS_COLS;
-    if (D.T <= ROUTE_ROWS_MAX_T && c->route_partial && slices <= ROUTE_MAX_SPLITS) {
+    const int rows_max = D.d == 128 && E_pad == 128 ? ROUTE_ROWS_ONE_CHUNK_MAX_T : ROUTE_ROWS_MAX_T;
+    if (D.T <= rows_max && c->route_partial && slices <= ROUTE_MAX_SPLITS) {
         const int T_pad = (D.T + 31) / 32 * 32;
         hipLaunchKernelGGL(route_rows_kernel, dim3((D.E + 3) / 4, slices), dim3(256), 0, c->stream, x, W_r, D.T, T_pad, D.d, D.E,
                            E_pad, c->route_partial);

@@ -6,7 +6,7 @@ import pytest
 import torch
 
 from workloads import MoEConfig, make_inputs
-from test_gpu_parity import _run_and_check_layer
+from test_gpu_parity import _check_permutation, _compare_routing, _host, _run_and_check_layer
 
 pytestmark = pytest.mark.gpu
 
@@ -131,6 +131,26 @@ def test_layers_either_side_of_the_streaming_rules(gpu_lib, T, d, E, k, F):
     rng = np.random.default_rng(T + d)
     ids = np.argsort(rng.random((T, E)), axis=1)[:, :k].astype(np.int32)
     _run_and_check_layer(gpu_lib, cfg, "replay", log=(np.ascontiguousarray(ids), np.full((T, k), 1.0 / k, dtype=np.float32)))
+
+
+@pytest.mark.parametrize("T,E,k", [(16, 8, 2), (17, 8, 2), (32, 128, 8), (17, 129, 8), (32, 256, 8)])
+def test_router_of_one_chunk_either_side_of_its_rule(gpu_lib, T, E, k):
+    """d = 128: the vector-ALU router up to 16 tokens (up to 32 above 128 experts), the matrix-core one beyond; ids-only replay
+    of the router's own ids gives its weights bit for bit."""
+    cfg = MoEConfig("chunk", T=T, d=128, E=E, k=k, F=128, modes=("routed",), seed=T + E)
+    inp = make_inputs(cfg, with_experts=False)
+    layer = gpu_lib.MoELayer(T, 128, E, k, 128)
+    try:
+        layer.route(inp["x"].cuda(), inp["W_r"].cuda(), None)
+        torch.cuda.synchronize()
+        _compare_routing(_host(inp), layer)
+        _check_permutation(layer.topk_idx.cpu().numpy(), E, layer)
+        idx, w = layer.topk_idx.clone(), layer.topk_w.clone()
+        layer.route_replay_ids(inp["x"].cuda(), inp["W_r"].cuda(), idx)
+        torch.cuda.synchronize()
+        assert torch.equal(layer.topk_idx, idx) and torch.equal(layer.topk_w.view(torch.int32), w.view(torch.int32))
+    finally:
+        layer.close()
 
 
 # --------------------------------------------------------------------------- graph replay
