@@ -726,7 +726,10 @@ constexpr size_t SMEM_BYTES = NW_BUF * W_TILE + NX_BUF * X_TILE;   // 160 KiB
 // the big-tile side already reads the weights of narrow tiles past the caches):
 //   gate/up  rows per expert 2: 1026 / 1006 (256 experts), 3: 163 / 142, 6: 136 / 133, 12: 129.5 / 133, 16: 251..287 / 274..287
 //            and, where the tiles leave compute units idle: 96 units, 4 rows 35 / 23, 32 rows 33 / 28; 384 units, 8 rows 79 / 68
-//   down     rows per expert 6: 75 / 68, 16: 75 / 70, 24: 78 / 74, 32: 81 / 78, 48: 85 / 82, 64: 188 / 202
+//   down     even loads, rows per expert: 64 experts x 4096 x 1408 12: 72 / 67, 24: 77 / 72, 40: 82 / 80; 128 x 5120 x 1536 24: 199 /
+//            193, 40: 211 / 209, 64 level to 7 % slower; 128 x 2048 x 768 24: 51 / 48, 40: 55 / 52; 16 x 3072 x 2048 40: 24.8 / 25.4;
+//            256 x 7168 x 2048 12: 668 / 639, 24: 709 / 697, 30: 705 / 715, 40: 736 / 762.  The widest layers cross at 27 rows, but
+//            only with even loads: Zipf loads at a mean of 12..48 rows 638 / 624 to 931 / 887 there
 //   linear   (K = 4096) 16 rows x 1024 features 28 / 13, 256 x 8192 48 / 22, 256 x 24576 50 / 45, 128 x 32768 36 / 31; at 128
 //            big tiles level (512 x 16384 53.6 / 53.8, 1024 x 8192 55.7 / 56.0); 256 of more than 64 rows (128 x 65536): 69 / 80
 constexpr int64_t GATE_UP_STREAM_ROWS = 8, GATE_UP_STREAM_ROWS_IDLE = 32, DOWN_STREAM_ROWS = 48;
