@@ -140,7 +140,7 @@ def test_dense_linear_matches_block_scaled_matmul(gpu_lib, rows, K, NOUT):
     g = torch.Generator().manual_seed(rows + K + NOUT)
     x = torch.randn((rows, K), generator=g).to(torch.bfloat16)
     w = (torch.randn((NOUT, K), generator=g) / K ** 0.5).to(torch.bfloat16)
-    layer = gpu_lib.MoELayer(2048, 1280, 4, 2, 1280)          # its work-list storage bounds the linear's size
+    layer = gpu_lib.MoELayer(2048, 1280, 4, 2, 1280)          # its dims bound the linear's size
     try:
         xq = torch.empty((rows, K), dtype=torch.uint8, device="cuda")
         xs = torch.empty((K // 128, rows), dtype=torch.float32, device="cuda")
