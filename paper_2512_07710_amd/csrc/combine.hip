@@ -33,7 +33,7 @@ constexpr int64_t LAYER_CACHED_BYTES = 192ll << 20, ROWS_CACHED_BYTES = 96ll << 
 // 50 MB of rows in the same sequence 39.7 / 37.4.  Other layers are faster PAST: 777 x 2176, k = 5 with 351 MB of weights 117 us,
 // y through the caches 119.5, the rows as well 125; 123 MB of rows 151 / 159, 295 MB 254 / 270.
 // Equal widths: 1152 columns as blocks of 1024 and 128 left seven eighths of every second block idle (10850 rows, k = 1, in the same
-// sequence 43.3, now 39.2; one block per token 36.9.  The layers around such rows: 75.3 us with one block per token, now 73.8).
+// sequence 43.3, now 38.6; one block per token 36.9.  The layers around such rows: 75.3 us with one block per token, now 72.9).
 template <int KT, bool PAST>
 __global__ __launch_bounds__(COMBINE_THREADS) void combine_kernel(const float* __restrict__ y_perm,
                                                                   const int32_t* __restrict__ inv_perm,

@@ -14,7 +14,7 @@ constexpr int NXCD = 8;
 // Direct global -> LDS copies.  Lane i of the wave deposits its bytes at lds_addr + i*size;
 // the global address is sbase + voff (per lane).  Completion is tracked by vmcnt; the
 // compiler does not see these as memory operations of its own, so every wait on them is
-// written out explicitly by the kernels.
+// written out explicitly by the kernels.  (The big tiles issue most of theirs under scalar conditions, in ffn.hip.)
 __device__ inline void dma16(uint32_t lds_addr, uint32_t voff, const void* sbase) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
                  :: "s"(lds_addr), "v"(voff), "s"(sbase) : "memory");
