@@ -18,23 +18,20 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
 constexpr int COMBINE_THREADS = 256;
-constexpr int64_t LAYER_CACHED_BYTES = 192ll << 20, ROWS_CACHED_BYTES = 96ll << 20;
 
 // One thread owns four columns of one token, so a block covers up to 1024 columns and a token takes ceil(d/1024) blocks of equal
 // width: each wave issues its k row reads once and is replaced by a fresh one.  KT > 0: k known at compile time, so that the k reads are
 // all in flight before the first multiply-add; KT == 0: any k up to MAX_K.
 //
-// Bound by the bytes of the expert rows, each read exactly once.  PAST: they go past the caches (non-temporal), and so does y.  One block
-// per token that walked the row (4096 x 5120, k = 8): 144 us = 5.0 TB/s, with non-temporal reads 131; in this form 139
-// without and 119 (6.0 TB/s) with them; 32768 x 7168: 1.58 -> 1.38 ms.
-// Not PAST: a layer whose weights and rows stay in the last-level cache together.  Non-temporal reads are then at the mercy of where the
-// rows lie: 88 MB of them (1901 x 1920, k = 6) copied in, combined and y read back 44 or 51 us, through the caches 44; layers of 1233 x
-// 1792, k = 7 (62 MB) 80.6 / 76.5, of 1901 x 2048, k = 6 (93 MB) 100.9 / 95.2.  y stays near for its reader: 7168 columns x k = 1 and
-// 50 MB of rows in the same sequence 39.7 / 37.4.  Other layers are faster PAST: 777 x 2176, k = 5 with 351 MB of weights 117 us,
-// y through the caches 119.5, the rows as well 125; 123 MB of rows 151 / 159, 295 MB 254 / 270.
-// Equal widths: 1152 columns as blocks of 1024 and 128 left seven eighths of every second block idle (10850 rows, k = 1, in the same
-// sequence 43.3, now 38.6; one block per token 36.9.  The layers around such rows: 75.3 us with one block per token, now 72.9).
-template <int KT, bool PAST>
+// Bound by the bytes of the expert rows, each read exactly once: they go past the caches (non-temporal), and so does y.  One block per
+// token that walked the row (4096 x 5120, k = 8): 144 us = 5.0 TB/s, with non-temporal reads 131; in this form 139 without
+// and 119 (6.0 TB/s) with them; 32768 x 7168: 1.58 -> 1.38 ms.  The same for rows that the last-level cache could hold: layers on buffers
+// of their own taken in turns, us, one block per token / through the caches / past them: 1901 x 1920, k = 6 (88 MB of rows) 104.6 / 102.4 /
+// 93.6, 2000 x 2048, k = 4 109 / 106 / 100, 1233 x 1792, k = 7 84 / 83 / 78.  A single layer repeated on the same buffers with nothing
+// between is the exception (92.9 / 91.1 / 95.8, 92.5 / 89.8 / 93.0, 77.8 / 76.5 / 80.6).
+// Equal widths: 1152 columns as blocks of 1024 and 128 left seven eighths of every second block idle (layers of 6000 x 1152, k = 4
+// 122.2, with equal ones 120.3, of 8600 x 1152, k = 1 74.6 / 71.4).
+template <int KT>
 __global__ __launch_bounds__(COMBINE_THREADS) void combine_kernel(const float* __restrict__ y_perm,
                                                                   const int32_t* __restrict__ inv_perm,
                                                                   const float* __restrict__ topk_w, int d, int k_rt,
@@ -48,8 +45,7 @@ __global__ __launch_bounds__(COMBINE_THREADS) void combine_kernel(const float* _
     const float* const w = topk_w + (size_t)t * k;
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
     auto load = [&](int row) {
-        const f32x4* const from = reinterpret_cast<const f32x4*>(y_perm + (size_t)row * d + (size_t)c4 * 4);
-        return PAST ? __builtin_nontemporal_load(from) : *from;
+        return __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(y_perm + (size_t)row * d + (size_t)c4 * 4));
     };
     auto add = [&](float wj, const f32x4& v) {
 #pragma unroll
@@ -76,9 +72,7 @@ __global__ __launch_bounds__(COMBINE_THREADS) void combine_kernel(const float* _
     u32x2 o;
     o[0] = f32_to_bf16_rne(acc[0]) | (f32_to_bf16_rne(acc[1]) << 16);
     o[1] = f32_to_bf16_rne(acc[2]) | (f32_to_bf16_rne(acc[3]) << 16);
-    u32x2* const to = reinterpret_cast<u32x2*>(y + (size_t)t * d + (size_t)c4 * 4);
-    if (PAST) __builtin_nontemporal_store(o, to);
-    else *to = o;
+    __builtin_nontemporal_store(o, reinterpret_cast<u32x2*>(y + (size_t)t * d + (size_t)c4 * 4));
     if (y_f32) *reinterpret_cast<f32x4*>(y_f32 + (size_t)t * d + (size_t)c4 * 4) = acc;   // the sums before rounding
 }
 
@@ -89,16 +83,9 @@ hipError_t launch_combine(moe_ctx* c, const float* y_perm, const int32_t* inv_pe
     const moe_dims& D = c->dims;
     const int parts = (D.d / 4 + COMBINE_THREADS - 1) / COMBINE_THREADS;
     const int threads = ((D.d / 4 + parts - 1) / parts + 63) / 64 * 64;
-    const int64_t row_bytes = (int64_t)D.T * D.k * D.d * (int64_t)sizeof(float), weight_bytes = 3ll * D.E * D.d * D.F;
-    const bool past = row_bytes > ROWS_CACHED_BYTES || row_bytes + weight_bytes > LAYER_CACHED_BYTES;
-#define MOE_COMBINE_AS(KT_, PAST_)                                                                                         \
-    hipLaunchKernelGGL((combine_kernel<KT_, PAST_>), dim3((unsigned)(D.T * parts)), dim3(threads), 0, c->stream, y_perm, \
+#define MOE_COMBINE(KT_)                                                                                             \
+    hipLaunchKernelGGL(combine_kernel<KT_>, dim3((unsigned)(D.T * parts)), dim3(threads), 0, c->stream, y_perm, \
                        inv_perm, topk_w, D.d, D.k, parts, y, y_f32)
-#define MOE_COMBINE(KT_)                     \
-    do {                                     \
-        if (past) MOE_COMBINE_AS(KT_, true); \
-        else MOE_COMBINE_AS(KT_, false);     \
-    } while (0)
     switch (D.k) {
         case 1: MOE_COMBINE(1); break;
         case 2: MOE_COMBINE(2); break;
@@ -111,7 +98,6 @@ hipError_t launch_combine(moe_ctx* c, const float* y_perm, const int32_t* inv_pe
         default: MOE_COMBINE(0); break;
     }
 #undef MOE_COMBINE
-#undef MOE_COMBINE_AS
     return hipGetLastError();
 }
 
