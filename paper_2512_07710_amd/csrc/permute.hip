@@ -178,18 +178,18 @@ __global__ __launch_bounds__(256) void scatter(const int32_t* __restrict__ ids, 
 // time.  Sixteen waves rank STEPS times 64 entries each in the manner of chunk_hist_rank, then scan over the experts and scatter
 // from registers; bound by its chain of barriers and memory round trips.
 // Whole calls in a row, us, this form / the three launches: replay of 2100 assignments k = 6 7.6 / 10.6, 4000 k = 2 6.9 / 10.3,
-// k = 6 8.7 / 10.7, k = 8 9.5 / 10.9, k = 16 12.0 / 11.5 (3000: 11.1 / 11.5).  Beyond that the search for repeated ids, up to
+// k = 6 8.7 / 10.7, k = 8 9.5 / 10.9, k = 16 12.0 / 11.5 (on cleared caches 16.3 / 18.0).  Beyond that the search for repeated ids, up to
 // k - 1 reads of earlier slots one after another in each of a thread's STEPS entries, weighs more in one block than launches
-// that overlap: 4500 k = 6 13.3 / 10.6, 8100 15.4 / 11.4, 8096 k = 16 22.3 / 11.9.  Without that search (ids from the router
-// itself) the one block stays ahead: with the router 23.4 / 25.7 at 4500, 25.5 / 27.0 at 8100 and level at 8096 with k = 8.
+// that overlap: 4500 k = 6 13.3 / 10.6, 8100 15.4 / 11.4, 8096 k = 16 22.3 / 11.9; layers of 4500 k = 6 57.7 / 55.0, 4800 k = 16
+// 94.2 / 86.8, 8000 k = 8 177 / 173, but 3360 k = 16 54.4 / 55.4.  Without that search (ids from the router
+// itself, one slot a token) the one block stays ahead: with the router 23.4 / 25.7 at 4500, 25.5 / 27.0 at 8100 and level at 8096 with
+// k = 8; replay of 8100 k = 1 11.6 / 11.2, a replayed layer of 4500 k = 1 55.2 / 56.3.
 constexpr int ONE_BLOCK_WAVES = 16;
 constexpr int ONE_BLOCK_MAX_STEPS = 8;
 constexpr int ONE_BLOCK_MAX_N = ONE_BLOCK_WAVES * ONE_BLOCK_MAX_STEPS * 64;
-constexpr int ONE_BLOCK_CHECKED_MAX_N = 4096, ONE_BLOCK_CHECKED_WIDE_MAX_N = 3072;
+constexpr int ONE_BLOCK_CHECKED_MAX_N = 4096;
 static_assert(ONE_BLOCK_CHECKED_MAX_N <= ONE_BLOCK_MAX_N, "the block holds that many");
-inline int one_block_max_n(bool check_dups, int k) {
-    return !check_dups ? ONE_BLOCK_MAX_N : k <= 8 ? ONE_BLOCK_CHECKED_MAX_N : ONE_BLOCK_CHECKED_WIDE_MAX_N;
-}
+inline int one_block_max_n(bool check_dups, int k) { return check_dups && k > 1 ? ONE_BLOCK_CHECKED_MAX_N : ONE_BLOCK_MAX_N; }
 
 template <int STEPS>
 __global__ __launch_bounds__(ONE_BLOCK_WAVES * 64) void permute_one_block(
