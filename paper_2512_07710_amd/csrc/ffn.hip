@@ -754,14 +754,28 @@ static Down down_form(const moe_dims* D) {
     if ((int64_t)D->T * D->k > DOWN_STREAM_ROWS * D->E) return Down::BIG;
     return skew_is_harmless(D, (D->d + 255) / 256, DOWN_SKEW_UNITS) ? Down::STREAM : Down::EITHER;
 }
+static double experts_met(const moe_dims* D) {                 // with at least one row when the router favours none
+    return D->E * (1.0 - pow(1.0 - (double)D->k / D->E, (double)D->T));
+}
 // (only where the down projection streams for certain: then no lists are needed)
 static bool gate_up_streams(const moe_dims* D) {
     const int64_t N = (int64_t)D->T * D->k;
     if (N == 0 || down_form(D) != Down::STREAM || !skew_is_harmless(D, D->F / 128, GATE_UP_SKEW_UNITS)) return false;
     if (N <= GATE_UP_STREAM_ROWS * D->E) return true;
-    // experts that meet at least one row when the router favours none
-    const double met = D->E * (1.0 - pow(1.0 - (double)D->k / D->E, (double)D->T));
-    return N <= GATE_UP_STREAM_ROWS_IDLE * D->E && met * (D->F / 128) < CUS;
+    return N <= GATE_UP_STREAM_ROWS_IDLE * D->E && experts_met(D) * (D->F / 128) < CUS;
+}
+// One token to a few: the kernels of ffn_few.hip while a tile of 16 rows holds every expert's rows and the streaming blocks leave the
+// chip half empty or in an uneven second round (streaming = 1).  Gate/up by units of 128 features, d = 4096: 66 units 0.81, 132 0.79,
+// 198 0.98, 308 0.91; d = 5120: 96 0.88, 192 0.90, 264 0.89, 336 level; shorter rows pay for the ends of a block (d = 2048: 48 units
+// 0.82, 132 0.94, 168 level, 234 1.17), longer ones keep a streaming block busy (d = 7168: 20 0.46, 64 0.73, 128 1.10, 256 1.10).
+// Down: F = 1408 0.91..1.00, 1536 0.84..0.95, 2048 0.95..1.04; F = 768: 1408 blocks 0.94, 1792 1.14.
+static bool gate_up_few(const moe_dims* D) {
+    if (D->T > FEW_ROWS || !gate_up_streams(D)) return false;
+    const double units = experts_met(D) * (D->F / 128);
+    return units < (D->d >= 6144 ? 112 : D->d >= 3072 ? 320 : 200);
+}
+static bool down_few(const moe_dims* D) {
+    return D->T <= FEW_ROWS && down_form(D) == Down::STREAM && (D->F >= 1280 || experts_met(D) * (D->d / 32) <= 1400);
 }
 static bool linear_streams(int32_t rows, int32_t NOUT) {
     return rows <= STREAM_ROWS || (int64_t)((rows + TOK_TILE - 1) / TOK_TILE) * ((NOUT + 255) / 256) <= LINEAR_STREAM_TILES;
@@ -772,7 +786,9 @@ static int64_t max_row_tiles(const moe_dims* D, int rows) {
     const int64_t N = (int64_t)D->T * D->k;
     return N / rows + (N < D->E ? N : D->E);
 }
-static int64_t gate_up_units(const moe_dims* D) { return max_row_tiles(D, gate_up_streams(D) ? STREAM_ROWS : TOK_TILE) * (D->F / 128); }
+static int64_t gate_up_units(const moe_dims* D) {
+    return max_row_tiles(D, gate_up_few(D) ? FEW_ROWS : gate_up_streams(D) ? STREAM_ROWS : TOK_TILE) * (D->F / 128);
+}
 static int64_t down_stream_units(const moe_dims* D) { return max_row_tiles(D, STREAM_ROWS) * ((D->d + 255) / 256); }
 // EITHER: S > 2B tiles of 64 / of 256 rows over m experts with rows (B >= m, S <= (N + 63m)/64) leave m <= N/65
 static int64_t down_big_units(const moe_dims* D) {
@@ -802,6 +818,7 @@ static hipError_t set_lds_limits() {
         if (e != hipSuccess) return e;
     }
     hipError_t e = set_stream_lds_limits();
+    if (e == hipSuccess) e = set_few_lds_limits();
     if (e != hipSuccess) return e;
     attr_set = true;
     return hipSuccess;
@@ -856,7 +873,10 @@ hipError_t launch_expert_ffn(moe_ctx* c, const uint8_t* xq, const float* xs, con
     }
     if (ev) (void)hipEventRecord(ev[0], c->stream);          // the timed interval is the GEMM kernel alone
     const int grid1 = (units1 + NXCD - 1) / NXCD * NXCD;
-    if (stream1) {
+    if (gate_up_few(&D)) {
+        hipError_t e = launch_few_gate_up(c, xq, xs, perm, offsets, (int)max_row_tiles(&D, FEW_ROWS), W1, W3, s1, s3);
+        if (e != hipSuccess) return e;
+    } else if (stream1) {
         hipError_t e = launch_stream_gate_up(c, xq, xs, perm, offsets, units1, W1, W3, s1, s3);
         if (e != hipSuccess) return e;
     } else if (perm) {
@@ -869,7 +889,10 @@ hipError_t launch_expert_ffn(moe_ctx* c, const uint8_t* xq, const float* xs, con
                            c->hs, (float*)nullptr);
     }
     if (ev) (void)hipEventRecord(ev[1], c->stream);
-    if (down != Down::BIG) {
+    if (down_few(&D)) {
+        hipError_t e = launch_few_down(c, offsets, (int)max_row_tiles(&D, FEW_ROWS), W2, s2, y_perm);
+        if (e != hipSuccess) return e;
+    } else if (down != Down::BIG) {
         hipError_t e = launch_stream_down(c, offsets, (int)down_stream_units(&D), down == Down::EITHER ? n_work2 : nullptr, W2, s2, y_perm);
         if (e != hipSuccess) return e;
     }
@@ -889,6 +912,7 @@ hipError_t launch_linear(moe_ctx* c, const uint8_t* xq, const float* xs, int32_t
                          const float* ws, int32_t NOUT, float* y) {
     hipError_t ea = set_lds_limits();
     if (ea != hipSuccess) return ea;
+    if (few_linear_groups(rows, NOUT)) return launch_few_linear(c, xq, xs, rows, K, Wq, ws, NOUT, y);
     if (linear_streams(rows, NOUT)) return launch_stream_linear(c, xq, xs, rows, K, Wq, ws, NOUT, y);
     const int units = (rows + TOK_TILE - 1) / TOK_TILE * ((NOUT + 255) / 256);
     hipLaunchKernelGGL((ffn_gemm<false, false, true>), dim3((units + NXCD - 1) / NXCD * NXCD), dim3(NTHREADS), SMEM_BYTES,

@@ -1,0 +1,326 @@
+// Block-scaled FP8 GEMMs that do not fill the chip: a few rows, and few weights to stream.
+//
+// What bounds such a product is the chain of K steps of its blocks: a block of the streaming kernel (ffn_stream.hip) brings
+// 16 KB of weights in 0.45 us (36 GB/s), however deep its ring, and a dense product of 6144 features makes 48 to 96 of them for
+// 256 CUs.  Here the chip is filled by smaller blocks with more of K in flight: a block owns 32 staged weight rows (gate/up: 16
+// gate rows and the 16 up rows of the same features), and a round takes WK K blocks at once.
+//   * Each of the WK waves brings one K block of the round, weights, activations and scales, by direct-to-LDS copies into a ring
+//     of D rounds; a round costs one barrier (EARLY: a second one behind the operand reads, so that the round's slots are refilled
+//     a round sooner: worth it where D is 2).  Straight into registers the weights came slower than through the streaming
+//     kernel, 3.3..5 TB/s: a load of sixteen rows takes 64 bytes of each, and the rest of the lines is gone when it is asked for.
+//   * 16x16x128 products, one K block each: a tile is up to 16*NT_MAX rows, so a single decoded sequence moves 2 KB of activations
+//     for 4 KB of weights and not 4.  Each gives the bits of two 32x32x64, and a wave folds its products over all of K in order:
+//     the results are those of the other kernels, bit for bit.  (Waves that fold the K blocks they bring, with the sums added at
+//     the end, need no barrier: 1 x 4096 x 4096 5.6 against 6.3 us, 40 x 4096 x 6144 9.0 against 10.6, but a sum then depends
+//     on the number of rows it is computed with, and a log replayed in a larger batch would not reproduce the rollout's bits.)
+//   * Gate/up: the scale of 128 hidden features spans eight blocks, which agree on it as in the streaming kernel.
+// us, streaming kernel / here: linear 1 x 4096 x 2048 10.8 / 5.9, 16 x 7168 x 2048 17.9 / 9.4, 32 x 4096 x 4096 11.5 / 8.0, 40 x 7168 x
+// 8192 21.4 / 17.3, 256 x 7168 x 1024 20.4 / 12.5; gate/up of one token x 6 of 4096 x 1408 21.7 / 17.5, x 2 of 3072 x 2048 15.6 /
+// 9.9; down 8.9 / 8.5 and 9.7 / 6.4.
+#include "ffn_rows.hpp"
+
+#include <type_traits>
+
+namespace moe355 {
+namespace {
+
+typedef float v4f __attribute__((ext_vector_type(4)));
+
+constexpr int PART_LD = 36;                           // floats per row of the LDS tile of partial sums: 32 + 4 of padding
+constexpr int few_stage(int nt) { return 32 * KB + nt * 16 * KB + 256; }
+constexpr int few_part(int nt) { return nt * 16 * PART_LD * 4; }
+constexpr int few_lds(int nt, int wk, int d) {                 // the partial sums and the ticket replace the rings
+    const int ring = wk * d * few_stage(nt), part = few_part(nt) + 16;
+    return ring > part ? ring : part;
+}
+
+// NT_MAX: groups of 16 rows per tile at most; WK: waves, K blocks per round; D: rounds in the ring
+template <int NT_MAX, int WK, int D, bool EARLY, bool GATED, bool GATHER, bool GROUPED>
+__global__ __launch_bounds__(WK * 64) __attribute__((amdgpu_waves_per_eu(2))) void ffn_few(StreamArgs g) {
+    constexpr int ROWS = NT_MAX * 16;
+    constexpr int NTHR = WK * 64;
+    constexpr int HW = GATED ? 16 : 32;                        // output features per block
+    constexpr int FT = GATED ? 128 : HW;                       // and per unit
+    constexpr int S = FT / HW;                                 // blocks per unit
+    constexpr int STAGE = few_stage(NT_MAX);
+    extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
+    float* const s_part = reinterpret_cast<float*>(smem);
+    int32_t& s_ticket = *reinterpret_cast<int32_t*>(smem + few_part(NT_MAX));
+
+    // ---- which block of which unit: as in ffn_stream
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int nft = g.NOUT / FT;
+    const RowTiles<GROUPED, ROWS, 16> tiles(g, lane);
+    const int total = tiles.total * nft * S;
+    const int chunk = (total + NXCD - 1) / NXCD;
+    const int slot = blockIdx.x / NXCD;
+    const int u = (int)(blockIdx.x % NXCD) * chunk + slot;
+    if (slot >= chunk || u >= total) return;
+    const int unit = u / S;
+    const Tile wk = tiles.find(g, unit, nft);
+    const int f0 = wk.ft * FT + (u % S) * HW;                  // the block's first feature
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l16 = lane & 15, grp = lane >> 4;
+    const int nkb = g.K / KB;
+
+    // ---- copy plan: as in ffn_stream, each wave bringing all of its K block
+    const int sub = lane >> 3, cslot = lane & 7;
+    const uint32_t sw[2] = {(uint32_t)(cslot ^ sub) << 4, (uint32_t)(cslot ^ sub ^ 1) << 4};   // even / odd groups of 8 rows
+    const size_t w0 = ((size_t)wk.expert * g.NOUT + f0) * (size_t)g.K;
+    const uint8_t* const w_base[2] = {g.Wa + w0, GATED ? g.Wb + w0 : g.Wa + w0 + (size_t)16 * g.K};
+    const uint32_t w_off[2] = {(uint32_t)sub * (uint32_t)g.K + sw[0], (uint32_t)(8 + sub) * (uint32_t)g.K + sw[1]};
+    auto token = [&](int r) {                                  // the activation row of tile row r (past the end: the last one)
+        const int p = min(wk.row0 + r, wk.row0 + wk.nrows - 1);
+        return GATHER ? (int)min((uint32_t)g.perm[p] / (uint32_t)g.fan, (uint32_t)(g.n_tok - 1)) : p;
+    };
+    const uint8_t* const x_base = GATHER ? g.act : g.act + (size_t)wk.row0 * g.K;
+    const size_t plane = (size_t)(GATHER ? g.n_tok : g.n_rows) * 4;
+    const uint32_t xs_off = 4u * (uint32_t)token(lane);
+    const int nblk_out = g.NOUT / QBLOCK;
+    const int blk = f0 / QBLOCK;
+    const float* const sa_e = g.sa + ((size_t)wk.expert * nblk_out + blk) * nkb;
+    const float* const sb_e = GATED ? g.sb + ((size_t)wk.expert * nblk_out + blk) * nkb : sa_e;
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t*)smem;
+
+    auto run = [&](auto groups, auto once) {
+        constexpr int NT = decltype(groups)::value;
+        constexpr bool ONCE = decltype(once)::value;
+        constexpr int C = 4 + 2 * NT + 1;                      // copies per stage and wave
+        constexpr int NTW = (2 * NT + WK - 1) / WK;            // products of a wave per K block
+        static_assert(WK % 2 == 0 && D <= 3 && (D - 1) * C <= 63, "both weight halves have a wave; wait counts fit the 6-bit field");
+        uint32_t x_off[2 * NT];
+#pragma unroll
+        for (int j = 0; j < 2 * NT; ++j) {
+            const int t = token(j * 8 + sub);
+            x_off[j] = (uint32_t)(GATHER ? t : t - wk.row0) * (uint32_t)g.K + sw[j & 1];
+        }
+        const int own = wave < nkb ? (nkb - wave + WK - 1) / WK : 0;        // the wave brings K blocks wave, wave + WK, ...
+        auto issue = [&](int i, int slot_) {
+            const uint32_t st = lds0 + (slot_ * WK + wave) * STAGE;
+            const int kb = i * WK + wave;
+            const size_t k0 = (size_t)kb * KB;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                if (ONCE) dma16_once(st + j * 1024, w_off[j & 1], w_base[j >> 1] + k0);
+                else dma16(st + j * 1024, w_off[j & 1], w_base[j >> 1] + k0);
+            }
+#pragma unroll
+            for (int j = 0; j < 2 * NT; ++j) dma16(st + 32 * KB + j * 1024, x_off[j], x_base + k0);
+            dma4(st + 32 * KB + NT_MAX * 16 * KB, xs_off, reinterpret_cast<const uint8_t*>(g.act_s) + (size_t)kb * plane);
+        };
+        const int m = wave & 1, nt0 = wave >> 1;               // the wave's products: weight rows 16*m, token groups nt0, nt0 + WK/2, ...
+        const bool busy = nt0 < NT;                            // (one row group: half of the waves only bring K blocks)
+        const float* const s_e = m ? sb_e : sa_e;
+        float ws_l = 0.f;
+        auto load_ws = [&](int kb) {                           // lane l: the scale of K block kb + l
+            ws_l = s_e[min(kb + lane, nkb - 1)];
+            // waited for here, as in ffn_stream
+            asm volatile("s_waitcnt vmcnt(0)" : "+v"(ws_l) :: "memory");
+        };
+        load_ws(0);
+        constexpr int AHEAD = EARLY ? D : D - 1;
+#pragma unroll
+        for (int j = 0; j < AHEAD; ++j)
+            if (j < own) issue(j, j);
+        const uint32_t off0 = (uint32_t)(grp ^ (l16 & 7) ^ ((l16 >> 3) & 1)) << 4;
+        const uint32_t a0 = lds0 + (m * 16 + l16) * KB + off0, b0 = lds0 + 32 * KB + (nt0 * 16 + l16) * KB + off0;
+        const uint32_t x0 = lds0 + 32 * KB + NT_MAX * 16 * KB + (nt0 * 16 + l16) * 4;
+        v4f acc[NTW];
+#pragma unroll
+        for (int t = 0; t < NTW; ++t)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) acc[t][r] = 0.f;
+        const int n = (nkb + WK - 1) / WK;
+        int rslot = 0;
+        for (int i = 0; i < n; ++i) {
+            const int kb0 = i * WK;
+            if (kb0 != 0 && (kb0 & 63) == 0) load_ws(kb0);
+            const int left = own - 1 - i;                      // the wave's stages behind this one, AHEAD - 1 of them issued
+            if (left >= AHEAD - 1) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"((AHEAD - 1) * C) : "memory");
+            else if (AHEAD > 2 && left == AHEAD - 2) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"((AHEAD > 2 ? AHEAD - 2 : 0) * C) : "memory");
+            else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
+            if (!EARLY && i + D - 1 < own) issue(i + D - 1, rslot == 0 ? D - 1 : rslot - 1);
+            const uint32_t st = (uint32_t)(rslot * WK * STAGE);
+            v8i a[WK], b[WK][NTW];
+            float x[WK][NTW];
+            if (busy)
+#pragma unroll
+            for (int j = 0; j < WK; ++j) {                     // (K blocks past the end: old bytes, multiplied and not folded)
+                const uint32_t sA = a0 + st + j * STAGE, sB = b0 + st + j * STAGE;
+                a[j] = lds_operand(sA, sA ^ 64, 0);
+#pragma unroll
+                for (int t = 0; t < NTW; ++t) {
+                    b[j][t] = lds_operand(sB, sB ^ 64, t * (WK / 2) * 16 * KB);
+                    x[j][t] = *reinterpret_cast<__attribute__((address_space(3))) const float*>(x0 + st + j * STAGE + t * (WK / 2) * 64);
+                }
+            }
+            if (EARLY) {
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+                __builtin_amdgcn_s_barrier();                  // the stage is in everybody's registers: its slots are free
+                asm volatile("" ::: "memory");
+                if (i + D < own) issue(i + D, rslot);
+            }
+            rslot = rslot == D - 1 ? 0 : rslot + 1;
+            if (!busy) continue;
+            v4f T[WK][NTW];
+#pragma unroll
+            for (int j = 0; j < WK; ++j)
+#pragma unroll
+                for (int t = 0; t < NTW; ++t) {
+                    const v4f z = {0.f, 0.f, 0.f, 0.f};
+                    T[j][t] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(a[j], b[j][t], z, 0, 0, 0, 0, 0, 0);
+                }
+#pragma unroll
+            for (int j = 0; j < WK; ++j) {
+                if (kb0 + j >= nkb) break;
+                const float ws = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(ws_l), (kb0 + j) & 63));
+#pragma unroll
+                for (int t = 0; t < NTW; ++t) {
+                    const float sc = x[j][t] * ws;
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) acc[t][r] = fmaf(sc, T[j][t][r], acc[t][r]);
+                }
+            }
+        }
+        __syncthreads();                                       // every wave is done with the ring
+#pragma unroll
+        for (int t = 0; t < NTW; ++t)
+            if (nt0 + t * (WK / 2) < NT)
+                *reinterpret_cast<v4f*>(s_part + ((nt0 + t * (WK / 2)) * 16 + l16) * PART_LD + m * 16 + grp * 4) = acc[t];
+    };
+    // the tile's groups, and non-temporal weight copies where no other row tile of the expert reads them
+    const int n_grp = (wk.nrows + 15) >> 4;
+    auto run_grp = [&](auto once) {
+        if (NT_MAX == 1 || n_grp == 1) run(std::integral_constant<int, 1>{}, once);
+        else if (NT_MAX == 2 || n_grp == 2) run(std::integral_constant<int, NT_MAX < 2 ? NT_MAX : 2>{}, once);
+        else if (n_grp == 3) run(std::integral_constant<int, NT_MAX < 3 ? NT_MAX : 3>{}, once);
+        else run(std::integral_constant<int, NT_MAX>{}, once);
+    };
+    if (g.once && wk.tiles == 1) run_grp(std::true_type{});
+    else run_grp(std::false_type{});
+    __syncthreads();
+
+    auto sum4 = [&](int r, int c) { return *reinterpret_cast<const v4f*>(s_part + r * PART_LD + c); };
+    if (!GATED) {
+        for (int i = tid; i < wk.nrows * (HW / 4); i += NTHR) {
+            const int r = i / (HW / 4), c = i % (HW / 4) * 4;
+            *reinterpret_cast<v4f*>(g.y + (size_t)(wk.row0 + r) * g.NOUT + f0 + c) = sum4(r, c);
+        }
+        return;
+    }
+    float* const rows = g.h_rows + (size_t)wk.row0 * g.NOUT;
+    for (int i = tid; i < wk.nrows * (HW / 4); i += NTHR) {
+        const int r = i / (HW / 4), c = i % (HW / 4) * 4;
+        const v4f gt = sum4(r, c), up = sum4(r, 16 + c);
+        float* const dst = rows + (size_t)r * g.NOUT + f0 + c;
+        put2(dst, swiglu(gt[0], up[0]), swiglu(gt[1], up[1]));
+        put2(dst + 2, swiglu(gt[2], up[2]), swiglu(gt[3], up[3]));
+    }
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (tid == 0) s_ticket = __hip_atomic_fetch_add(g.tickets + unit, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    if (s_ticket != S - 1) return;
+    if (tid == 0) __hip_atomic_store(g.tickets + unit, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // for the next launch
+    const int fu = wk.ft * FT;
+    for (int r = tid >> 4; r < wk.nrows; r += NTHR / 16) {
+        const int p = wk.row0 + r, c = (tid & 15) * 8;
+        float h[8];
+        float am = 0.f;
+#pragma unroll
+        for (int i = 0; i < 8; i += 2) {
+            const float2 v = get2(rows + (size_t)r * g.NOUT + fu + c + i);
+            h[i] = v.x;
+            h[i + 1] = v.y;
+        }
+#pragma unroll
+        for (int i = 0; i < 8; ++i) am = fmaxf(am, fabsf(h[i]));
+        am = fmaxf(am, __shfl_xor(am, 1));
+        am = fmaxf(am, __shfl_xor(am, 2));
+        am = fmaxf(am, __shfl_xor(am, 4));
+        am = fmaxf(am, __shfl_xor(am, 8));
+        const float sc = (am == 0.f) ? 1.0f : am / 448.0f;
+        const Quotient q(sc);
+        uint2 codes;
+        codes.x = e4m3_codes4(q, h[0], h[1], h[2], h[3]);
+        codes.y = e4m3_codes4(q, h[4], h[5], h[6], h[7]);
+        *reinterpret_cast<uint2*>(g.hq + (size_t)p * g.NOUT + fu + c) = codes;
+        if ((tid & 15) == 0) g.hs[(size_t)wk.ft * g.n_rows + p] = sc;
+    }
+}
+
+template <int NT_MAX, int WK, int D, bool EARLY, bool GATED, bool GATHER, bool GROUPED>
+hipError_t launch(hipStream_t stream, const StreamArgs& a, int max_tiles) {
+    const int blocks = max_tiles * (a.NOUT / (GATED ? 16 : 32));
+    hipLaunchKernelGGL((ffn_few<NT_MAX, WK, D, EARLY, GATED, GATHER, GROUPED>), dim3((blocks + NXCD - 1) / NXCD * NXCD),
+                       dim3(WK * 64), few_lds(NT_MAX, WK, D), stream, a);
+    return hipGetLastError();
+}
+
+template <int NT_MAX, int WK, int D, bool EARLY, bool GATED, bool GATHER, bool GROUPED>
+hipError_t allow_lds() {
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(&ffn_few<NT_MAX, WK, D, EARLY, GATED, GATHER, GROUPED>),
+                               hipFuncAttributeMaxDynamicSharedMemorySize, few_lds(NT_MAX, WK, D));
+}
+
+// Waves and rounds, measured (us): gate/up four waves and two rounds (50 KB, three blocks to a CU; two tokens x 6 of 4096 x 1408
+// 27.9, two waves 29.3, four and three 29.7), the shorter K of the down projection two and two (one token x 8 of 5120 x 1536
+// 12.7; four and two 14.9, two and three 14.3), linear, where a CU has one block, four and three with the one barrier (16 x
+// 7168 x 2048 9.4; two rounds 10.0).
+constexpr int UP_WK = 4, UP_D = 2, DOWN_WK = 2, DOWN_D = 2, LIN_WK = 4, LIN_D = 3;
+constexpr bool UP_EARLY = true, DOWN_EARLY = true, LIN_EARLY = false;
+
+}  // namespace
+
+hipError_t set_few_lds_limits() {
+    hipError_t e = allow_lds<1, UP_WK, UP_D, UP_EARLY, true, true, true>();
+    if (e == hipSuccess) e = allow_lds<1, UP_WK, UP_D, UP_EARLY, true, false, true>();
+    if (e == hipSuccess) e = allow_lds<1, DOWN_WK, DOWN_D, DOWN_EARLY, false, false, true>();
+    if (e == hipSuccess) e = allow_lds<1, LIN_WK, LIN_D, LIN_EARLY, false, false, false>();
+    if (e == hipSuccess) e = allow_lds<2, LIN_WK, LIN_D, LIN_EARLY, false, false, false>();
+    if (e == hipSuccess) e = allow_lds<4, LIN_WK, LIN_D, LIN_EARLY, false, false, false>();
+    return e;
+}
+
+hipError_t launch_few_gate_up(moe_ctx* c, const uint8_t* xq, const float* xs, const int32_t* perm, const int32_t* offsets,
+                              int max_tiles, const uint8_t* W1, const uint8_t* W3, const float* s1, const float* s3) {
+    const moe_dims& m = c->dims;
+    const StreamArgs a{xq, xs, m.T * m.k, perm, m.k, m.T, offsets, m.E, nullptr, c->tickets, W1, W3, s1, s3, m.d, m.F,
+                       true, c->h_rows, c->hq, c->hs, nullptr};
+    return perm ? launch<1, UP_WK, UP_D, UP_EARLY, true, true, true>(c->stream, a, max_tiles)
+                : launch<1, UP_WK, UP_D, UP_EARLY, true, false, true>(c->stream, a, max_tiles);
+}
+
+hipError_t launch_few_down(moe_ctx* c, const int32_t* offsets, int max_tiles, const uint8_t* W2, const float* s2, float* y_perm) {
+    const moe_dims& m = c->dims;
+    const StreamArgs a{c->hq, c->hs, m.T * m.k, nullptr, 1, 1, offsets, m.E, nullptr, nullptr, W2, nullptr, s2, nullptr, m.F, m.d,
+                       true, nullptr, nullptr, nullptr, y_perm};
+    return launch<1, DOWN_WK, DOWN_D, DOWN_EARLY, false, false, true>(c->stream, a, max_tiles);
+}
+
+// Up to how many blocks this is the better kernel, one to a CU (streaming kernel = 1): 256 blocks, 16-row tiles 16 x 4096 x 8192
+// 0.71, 32-row 32 x 4096 x 8192 0.76, 64-row 40 x 4096 x 8192 0.85, 64 x 4096 x 8192 0.97, 128 x 7168 x 4096 0.94, 256 x 4096 x 2048
+// 0.83; 384 blocks of 16-row tiles (75 KB, two to a CU) 0.91..1.02, of 32-row tiles 1.2, 512 of 64-row tiles 1.5.  Tiles of 32 rows
+// while they fit too (128 x 4096 x 2048 0.62 against 0.83 in tiles of 64).
+constexpr int FEW_BLOCKS = 256, FEW_BLOCKS_16 = 320;
+int few_linear_groups(int32_t rows, int32_t NOUT) {
+    const int64_t cols = NOUT / 32;
+    if (rows <= 16) return cols <= FEW_BLOCKS_16 ? 1 : 0;
+    if ((rows + 31) / 32 * cols <= FEW_BLOCKS) return 2;
+    return (rows + 63) / 64 * cols <= FEW_BLOCKS ? 4 : 0;
+}
+
+hipError_t launch_few_linear(moe_ctx* c, const uint8_t* xq, const float* xs, int32_t rows, int32_t K, const uint8_t* Wq,
+                             const float* ws, int32_t NOUT, float* y) {
+    const StreamArgs a{xq, xs, rows, nullptr, 1, 1, nullptr, 1, nullptr, nullptr, Wq, nullptr, ws, nullptr, K, NOUT,
+                       false, nullptr, nullptr, nullptr, y};   // (so few weights may well stay in the last-level cache)
+    switch (few_linear_groups(rows, NOUT)) {
+        case 1: return launch<1, LIN_WK, LIN_D, LIN_EARLY, false, false, false>(c->stream, a, 1);
+        case 2: return launch<2, LIN_WK, LIN_D, LIN_EARLY, false, false, false>(c->stream, a, (rows + 31) / 32);
+        default: return launch<4, LIN_WK, LIN_D, LIN_EARLY, false, false, false>(c->stream, a, (rows + 63) / 64);
+    }
+}
+
+}  // namespace moe355

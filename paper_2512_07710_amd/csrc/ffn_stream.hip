@@ -16,7 +16,7 @@
 //   * activation scales are gathered straight from the token-order planes (a few dozen rows: no sorted copy needed).
 // Gate/up: the scale of a token's 128 hidden features spans the unit's S blocks.  Each block puts its h (fp32) into the
 // context's workspace; the last of the S to arrive (an atomic ticket per unit) takes the maximum and writes the codes.  Nobody waits.
-#include "ffn_common.hpp"
+#include "ffn_rows.hpp"
 
 #include <type_traits>
 
@@ -28,106 +28,6 @@ constexpr int X_STAGE = STREAM_ROWS * KB;             // one K block of the tile
 constexpr int XS_STAGE = STREAM_ROWS * 4;             // and of their scales
 
 constexpr int stage_bytes(int nw) { return nw * W_WAVE + X_STAGE + XS_STAGE; }
-
-// relaxed device-scope accesses: they go to the point where all XCDs' L2 caches agree
-__device__ inline void put2(float* p, float a, float b) {
-    const uint64_t v = (uint64_t)__float_as_uint(a) | ((uint64_t)__float_as_uint(b) << 32);
-    __hip_atomic_store(reinterpret_cast<uint64_t*>(p), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ inline float2 get2(const float* p) {
-    const uint64_t v = __hip_atomic_load(reinterpret_cast<const uint64_t*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    return make_float2(__uint_as_float((uint32_t)v), __uint_as_float((uint32_t)(v >> 32)));
-}
-
-struct StreamArgs {
-    const uint8_t* act;            // GATHER: [n_tok, K] codes in token order; else [n_rows, K] in sorted order
-    const float* act_s;            // their scales, [K/128][n_tok] or [K/128][n_rows]
-    int n_rows;
-    const int32_t* perm;           // GATHER: sorted row p is token perm[p] / fan
-    int fan, n_tok;
-    const int32_t* offsets;        // GROUPED: [E+1], of the experts' rows
-    int E;
-    const int32_t* big_units;      // CHOSEN: nothing to do where it is not zero
-    int32_t* tickets;              // GATED: one per unit, zero before and after the launch
-    const uint8_t *Wa, *Wb;
-    const float *sa, *sb;
-    int K, NOUT;
-    bool once;                     // may the weights go past the caches?
-    float* h_rows;                 // GATED: [n_rows][NOUT] h before its codes
-    uint8_t* hq;
-    float* hs;
-    float* y;
-};
-
-// The row tiles of all experts and the units made of them, ordered (expert, feature tile, row tile) as in the big-tile kernel's
-// work list.  Every wave works them out from the offsets in registers: lane l keeps experts 4l .. 4l+3.  (A list written by a
-// kernel of its own costs a launch, 4..5 us of a decode step, and two dependent loads here instead of one.)
-struct Tile { int expert, ft, row0, nrows, tiles; };            // tiles: row tiles of the expert
-template <bool GROUPED>                                        // false: one "expert" owns all n_rows rows
-struct RowTiles {
-    int off[5];                                                // offsets of the lane's experts
-    int before, total;                                         // tiles of the experts before the lane's; of all
-    __device__ RowTiles(const StreamArgs& g, int lane) {
-        if (!GROUPED) {
-            total = (g.n_rows + STREAM_ROWS - 1) / STREAM_ROWS;
-            return;
-        }
-#pragma unroll
-        for (int i = 0; i < 5; ++i) off[i] = g.offsets[min(lane * 4 + i, g.E)];
-        int mine = 0;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) mine += count(i);
-        int incl = mine;
-#pragma unroll
-        for (int d = 1; d < 64; d <<= 1) {
-            const int v = __shfl_up(incl, d);
-            incl += lane >= d ? v : 0;
-        }
-        before = incl - mine;
-        total = __builtin_amdgcn_readlane(incl, 63);
-    }
-    __device__ int count(int i) const { return (off[i + 1] - off[i] + STREAM_ROWS - 1) / STREAM_ROWS; }
-    __device__ Tile find(const StreamArgs& g, int unit, int nft) const {
-        Tile t;
-        if (!GROUPED) {
-            t.expert = 0;
-            t.tiles = total;
-            t.ft = unit / total;
-            t.row0 = (unit - t.ft * total) * STREAM_ROWS;
-            t.nrows = min(STREAM_ROWS, g.n_rows - t.row0);
-            return t;
-        }
-        const int at = unit / nft;                             // a tile of the unit's expert (an expert has tiles * nft units)
-        int end = before + count(0) + count(1) + count(2) + count(3);
-        const int l = __builtin_ctzll(__ballot(end > at));     // at < total: some lane has it
-        int base = __builtin_amdgcn_readlane(before, l), start = 0, cnt = 0;
-        t.expert = 4 * l;
-        t.tiles = 0;
-        bool found = false;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int o = __builtin_amdgcn_readlane(off[i], l), n = __builtin_amdgcn_readlane(off[i + 1], l) - o;
-            const int nt = (n + STREAM_ROWS - 1) / STREAM_ROWS;
-            if (!found && at < base + nt) {
-                found = true;
-                t.expert = 4 * l + i;
-                t.tiles = nt;
-                start = o;
-                cnt = n;
-            }
-            if (!found) base += nt;
-        }
-        const int r = unit - base * nft;
-        t.ft = r / t.tiles;
-        const int i = r - t.ft * t.tiles;
-        // groups of 32 rows dealt out evenly over the expert's tiles
-        const int G = (cnt + 31) / 32;
-        const int lo = min(cnt, 32 * (i * G / t.tiles)), hi = min(cnt, 32 * ((i + 1) * G / t.tiles));
-        t.row0 = start + lo;
-        t.nrows = hi - lo;
-        return t;
-    }
-};
 
 // CHOSEN: the kernel that made the work lists has counted the tiles and may have given the batch to the big tiles
 template <int NW, int D, bool GATED, bool GATHER, bool GROUPED, bool CHOSEN>
@@ -141,7 +41,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
     // ---- which block of which unit: XCD x (= blockIdx % 8) walks a contiguous eighth of the units, a unit's blocks side by side
     const int tid = threadIdx.x, lane = tid & 63;
     const int nft = (g.NOUT + FT - 1) / FT;
-    const RowTiles<GROUPED> tiles(g, lane);
+    const RowTiles<GROUPED, STREAM_ROWS, 32> tiles(g, lane);
     const int total = tiles.total * nft * S;
     const int chunk = (total + NXCD - 1) / NXCD;
     const int slot = blockIdx.x / NXCD;

@@ -225,3 +225,58 @@ def test_quantisers_of_values_that_are_not_finite(gpu_lib):
         assert torch.equal(blocks(qw.cpu()), q_e) and torch.equal(sw.cpu(), s_e)
     finally:
         gpu_lib.moe_destroy(ctx)
+
+
+# --------------------------------------------------------------------------- products that do not fill the chip
+# either side of every tile height (16, 32, 64 rows) and of a round's four K blocks; one, two and three row tiles
+@pytest.mark.parametrize("rows", [1, 15, 16, 17, 32, 33, 48, 49, 64, 65, 130])
+@pytest.mark.parametrize("K,NOUT", [(128, 256), (384, 128), (512, 1024), (640, 2688), (1152, 128), (66 * 128, 384)])
+def test_linear_of_few_blocks(gpu_lib, rows, K, NOUT):
+    """At most 256 blocks of 32 features: the same bits as the first NOUT features of a product that is wide enough for the streaming
+    kernel or the big tiles (every kernel folds the K blocks in order), whose own tests hold it to a 64-bit evaluation."""
+    WIDE = 131 * 128
+    assert (rows + 63) // 64 * NOUT // 32 <= 256 < (rows + 63) // 64 * WIDE // 32
+    g = torch.Generator(device="cuda").manual_seed(rows + K + NOUT)
+    xq, wq = _codes(g, rows, K), _codes(g, WIDE, K)
+    xs = torch.rand((K // 128, rows), generator=g, device="cuda") + 0.5
+    ws = torch.rand((WIDE // 128, K // 128), generator=g, device="cuda") + 0.5
+    ctx = gpu_lib.moe_create(rows, K, 1, 1, WIDE)
+    try:
+        wide = torch.full((rows, WIDE), float("nan"), device="cuda")
+        gpu_lib.moe_linear_fp8(ctx, xq, xs, rows, K, wq, ws, WIDE, wide)
+        y = torch.full((rows + 1, NOUT), float("nan"), device="cuda")
+        gpu_lib.moe_linear_fp8(ctx, xq, xs, rows, K, wq[:NOUT], ws[:NOUT // 128].contiguous(), NOUT, y)
+        assert torch.equal(y[:rows], wide[:, :NOUT])
+        assert torch.isnan(y[rows]).all()                    # nothing past the last row
+    finally:
+        gpu_lib.moe_destroy(ctx)
+
+
+@pytest.mark.parametrize("T", [1, 2, 5, 16])
+@pytest.mark.parametrize("d,E,k,F", [(640, 16, 2, 384), (128, 8, 3, 128), (1152, 5, 1, 1280)])
+@pytest.mark.parametrize("hot", [False, True], ids=["spread", "one-set"])
+def test_layer_of_a_few_tokens_has_the_bits_of_a_large_batch(gpu_lib, T, d, E, k, F, hot):
+    """The same tokens and log as the first T of 1500, which take the big tiles: the replayed layer's outputs, hidden codes and scales."""
+    assert 1500 * k > 48 * E
+    g = torch.Generator(device="cuda").manual_seed(T + d + E)
+    big = 1500
+    x = torch.randn((big, d), generator=g, device="cuda").to(torch.bfloat16)
+    ids = torch.rand((big, E), generator=g, device="cuda").topk(k, dim=1).indices.to(torch.int32)
+    if hot:
+        ids[:T] = ids[0].clone()                               # a tile of T rows for each of k experts
+    gates = torch.rand((big, k), generator=g, device="cuda")
+    w = {}
+    for q, s, r, c in (("W1q", "s1", F, d), ("W3q", "s3", F, d), ("W2q", "s2", d, F)):
+        w[q] = _codes(g, E, r, c)
+        w[s] = (torch.rand((E, r // 128, c // 128), generator=g, device="cuda") + 0.5) * 1e-3
+    out = []
+    for n in (big, T):
+        layer = gpu_lib.MoELayer(n, d, E, k, F)
+        for _ in range(2):                                   # (twice: the tickets of the first call are back at zero)
+            layer.forward_replay(x[:n].contiguous(), ids[:n].contiguous(), gates[:n].contiguous(), w)
+        hq, hs = layer.hidden()
+        at = layer.inv_perm.view(n, k)[:T].long().flatten()
+        out.append((layer.y[:T].clone().view(torch.int16), layer.y_perm[at].clone(), hq[at], hs[:, at]))
+        layer.close()
+    for a, b in zip(*out):
+        assert torch.equal(a, b)
