@@ -42,10 +42,18 @@ constexpr int X_TILE = X_ROWS * KB;                // 32 KiB: one K block of the
 constexpr int NW_BUF = 3, NX_BUF = 2;              // LDS ring depths
 constexpr int X_RING = NW_BUF * W_TILE;            // byte offset of the activation ring
 constexpr int NTHREADS = 512;
+constexpr int CODES_LD = 128 + 16;                  // bytes from row to row of the LDS tile of hidden codes
+// Row tiles of an expert up to which its weights are read past the caches (us, through / past them; gate/up | down): 64 experts x 4096
+// x 1408 at 80 rows 141.6 / 133.8 | 102 / 89, 112 148 / 141 | 112 / 98, 224 200 / 197 | 153 / 140, 258 (two tiles) 234 / 236 | 164 /
+// 157, 420 337 / 340 | 232 / 235; 128 x 2048 x 768 at 112 88 / 83 | 76 / 69, 258 142 / 143 | 126 / 119; 16 x 3072 x 2048 at 80 42.1 /
+// 38.3 | 26.3 / 25.7.  With four tiles (1030 rows) the gate/up projection is 2 % slower past them, 4 % at 7168 x 2048.
+constexpr int GATE_UP_ONCE_TILES = 1, DOWN_ONCE_TILES = 2;
 constexpr int NARROW_ROWS = 64;                     // tiles of at most this many rows take the narrow path of ffn_gemm
 
-// one work unit: rows [row0, row0 + nrows) of an expert x feature tile ft (128 features gate/up, 256 down)
-struct Work { int32_t expert; int32_t row0; int32_t ft; int32_t nrows; };
+// one work unit: rows [row0, row0 + nrows) of an expert x feature tile ft (128 features gate/up, 256 down); tiles: row tiles of the
+// expert, as far as MANY_TILES
+struct Work { int32_t expert; int32_t row0; int32_t ft; int16_t nrows, tiles; };
+constexpr int MANY_TILES = 3;
 
 // Rows [row0, row0 + nrows) of tile i when `rows` rows make nt tiles.
 // The expert's G = ceil(cnt/32) groups of 32 rows are dealt out evenly: tile i covers groups [i*G/nt, (i+1)*G/nt).
@@ -62,7 +70,8 @@ __device__ inline void split_rows(int rows, int nt, int i, Work& w) {
     const int64_t G = (rows + 31) / 32;
     const int lo = min(rows, 32 * (int)(i * G / nt)), hi = min(rows, 32 * (int)((i + 1) * G / nt));
     w.row0 = lo;
-    w.nrows = hi - lo;
+    w.nrows = (int16_t)(hi - lo);
+    w.tiles = (int16_t)min(nt, MANY_TILES);
 }
 
 // ------------------------------------------------------------------ work list
@@ -128,6 +137,15 @@ __device__ inline void mfma_acc(v16f& t, const v8i& a, const v8i& b) {
 // values feeding x cannot move below it.
 #define PIN(x) asm volatile("" : "+v"(x))
 
+// A tile's hidden codes go out through LDS, 128 contiguous bytes of a row from 8 lanes: straight from the accumulator layout a
+// store instruction carries 8 bytes for each of 32 rows (gate/up, us: 64 experts x 5120 x 1536 at 1030 rows 964 / 951, 128 x 2048 x 768
+// at 420 198 / 190, 16 x 3072 x 2048 at 224 58.9 / 55.8, of which 0.5..1.5 % is the earlier start of the first weights).
+__device__ inline void store_codes(uint8_t* __restrict__ hq, const uint8_t* s_codes, const Work& wk, int f0, int NOUT, int tid) {
+    for (int i = tid; i < wk.nrows * 8; i += NTHREADS)
+        *reinterpret_cast<uint4*>(hq + (size_t)(wk.row0 + (i >> 3)) * NOUT + f0 + (i & 7) * 16) =
+            *reinterpret_cast<const uint4*>(s_codes + (i >> 3) * CODES_LD + (i & 7) * 16);
+}
+
 // ------------------------------------------------------------------ operand copies
 // What one wave brings of every K block: staged weight rows [32w, 32w+32) and staged activation rows [32w, 32w+32).
 struct Feed {
@@ -141,9 +159,9 @@ struct Feed {
 // Copy J of K block kb goes out if J < n.  The condition is a scalar branch inside the asm: the compiler's control flow
 // stays a straight line, which the register allocation of the K loop depends on (with C++ conditions around the copies
 // the loop spills).
-#define COPY_IF(J, N, LDS, VOFF, SBASE)                                                                    \
+#define COPY_IF(J, N, LDS, VOFF, SBASE, CACHE)                                                             \
     asm volatile("s_cmp_gt_i32 %3, %4\n\ts_cbranch_scc0 .Lskip%=\n\ts_mov_b32 m0, %0\n\ts_nop 0\n\t"     \
-                 "global_load_lds_dwordx4 %1, %2\n.Lskip%=:"                                              \
+                 "global_load_lds_dwordx4 %1, %2" CACHE "\n.Lskip%=:"                                              \
                  :: "s"(LDS), "v"(VOFF), "s"(SBASE), "s"(N), "n"(J) : "memory", "scc")
 // a < b ? -1 : 0 for wave-uniform values, in a scalar register whatever the compiler makes of the comparison
 __device__ __forceinline__ int all_ones_if_less(int a, int b) {
@@ -151,28 +169,24 @@ __device__ __forceinline__ int all_ones_if_less(int a, int b) {
     asm("s_cmp_lt_i32 %1, %2\n\ts_cselect_b32 %0, -1, 0" : "=s"(r) : "s"(a), "s"(b) : "scc");
     return r;
 }
-template <int J>
+// ONCE: weights that few other tiles read go past the caches (non-temporal: a block stream of 128-byte row pieces into LDS reaches
+// 6.0..6.6 TB/s that way and 5.3..5.9 through them)
+template <bool ONCE, int J>
 __device__ __forceinline__ void copy_w1(const Feed& f, int kb, int wslot, int n) {
-    COPY_IF(J, n, f.lds_rows + wslot * W_TILE + J * 8 * KB, f.w_off[J & 1], f.w_base[J >> 1] + (size_t)kb * KB);
+    if (ONCE) COPY_IF(J, n, f.lds_rows + wslot * W_TILE + J * 8 * KB, f.w_off[J & 1], f.w_base[J >> 1] + (size_t)kb * KB, " nt");
+    else COPY_IF(J, n, f.lds_rows + wslot * W_TILE + J * 8 * KB, f.w_off[J & 1], f.w_base[J >> 1] + (size_t)kb * KB, "");
 }
 template <int J>
 __device__ __forceinline__ void copy_x1(const Feed& f, int kb, int xslot, int n) {
-    COPY_IF(J, n, f.lds_rows + X_RING + xslot * X_TILE + J * 8 * KB, f.x_off[J], f.x_base + (size_t)kb * KB);
+    COPY_IF(J, n, f.lds_rows + X_RING + xslot * X_TILE + J * 8 * KB, f.x_off[J], f.x_base + (size_t)kb * KB, "");
 }
 #undef COPY_IF
+template <bool ONCE>
 __device__ __forceinline__ void copy_w(const Feed& f, int kb, int wslot, int n = 4) {
-    copy_w1<0>(f, kb, wslot, n);
-    copy_w1<1>(f, kb, wslot, n);
-    copy_w1<2>(f, kb, wslot, n);
-    copy_w1<3>(f, kb, wslot, n);
-}
-// The weights of a narrow tile: the tile is all of its expert's rows, so nothing else reads them (non-temporal: a block stream
-// of 128-byte row pieces into LDS reaches 6.0..6.6 TB/s that way and 5.3..5.9 through the caches).
-__device__ __forceinline__ void copy_w_once(const Feed& f, int kb, int wslot) {
-    const uint32_t at = f.lds_rows + wslot * W_TILE;
-    const size_t k0 = (size_t)kb * KB;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) dma16_once(at + j * 8 * KB, f.w_off[j & 1], f.w_base[j >> 1] + k0);
+    copy_w1<ONCE, 0>(f, kb, wslot, n);
+    copy_w1<ONCE, 1>(f, kb, wslot, n);
+    copy_w1<ONCE, 2>(f, kb, wslot, n);
+    copy_w1<ONCE, 3>(f, kb, wslot, n);
 }
 __device__ __forceinline__ void copy_x(const Feed& f, int kb, int xslot) {
     copy_x1<0>(f, kb, xslot, f.x_copies);
@@ -204,7 +218,7 @@ struct Tile {
 // copy while the queue drains (in two bursts of four the gate/up projection ran 4 % slower).  The last two products
 // already fetch the first operands of block kb+1 into registers: the weight operands a[s] stay for a whole step, the
 // token operands go through two register sets in turn (three for NTS = 3, so that a step always starts with set 0).
-template <int NTS, bool GATED>
+template <int NTS, bool GATED, bool ONCE>
 __device__ __forceinline__ void k_loop(const Tile& t, const Feed& f, v16f (&acc)[2][4]) {
     const int nkb = t.nkb;
     // LDS byte address of a lane's first operand chunk (ks = 0, j = 0) relative to a ring slot; chunk (ks, j) is that
@@ -245,16 +259,20 @@ __device__ __forceinline__ void k_loop(const Tile& t, const Feed& f, v16f (&acc)
                          : "=&v"(xs[2 * i]), "=&v"(xs[2 * i + 1]) : "v"(xs_n[i]));
     };
     xs_load(0, 1);
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    if (nkb > 1) {                                             // weight block 1 is not waited for
+        copy_w<ONCE>(f, 1, 1);
+        asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
+    } else {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    }
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
     xs_take();
     if (nkb > 1) {
         xs_load(1, 1);
         copy_x(f, 1, 1);
-        copy_w(f, 1, 1);
     }
-    if (nkb > 2) copy_w(f, 2, 2);
+    if (nkb > 2) copy_w<ONCE>(f, 2, 2);
     constexpr int NB = NTS == 3 ? 3 : 2;                      // register sets of token operands
     v8i a[2][2], b[NB][2];
     read_ops(a[0], a00, 0);
@@ -321,8 +339,8 @@ __device__ __forceinline__ void k_loop(const Tile& t, const Feed& f, v16f (&acc)
             }
             mfma_first(T[s], a[s][0], b[bi][0]);
             // one copy behind every matrix instruction: weight block kb+2 over products 0 and 1
-            if (NTS > 1 && i == 0) copy_w1<0>(f, kb + 2, wprev, nw);
-            if (NTS > 1 && i == 1) copy_w1<2>(f, kb + 2, wprev, nw);
+            if (NTS > 1 && i == 0) copy_w1<ONCE, 0>(f, kb + 2, wprev, nw);
+            if (NTS > 1 && i == 1) copy_w1<ONCE, 2>(f, kb + 2, wprev, nw);
             if (last) copy_x1<2>(f, kb + 2, kb & 1, nx);
             if (s == 0 && !last2) read_ops(b[bnext], sX, (ts + 1) * 32 * KB);
             if (last2) {
@@ -336,8 +354,8 @@ __device__ __forceinline__ void k_loop(const Tile& t, const Feed& f, v16f (&acc)
                              : "=&s"(wsc_n[0]), "=&s"(wsc_n[1]) : "s"(t.sa + kn), "s"(t.sb + kn) : "memory");
             }
             mfma_acc(T[s], a[s][1], b[bi][1]);
-            if (NTS > 1 && i == 0) copy_w1<1>(f, kb + 2, wprev, nw);
-            if (NTS > 1 && i == 1) copy_w1<3>(f, kb + 2, wprev, nw);
+            if (NTS > 1 && i == 0) copy_w1<ONCE, 1>(f, kb + 2, wprev, nw);
+            if (NTS > 1 && i == 1) copy_w1<ONCE, 3>(f, kb + 2, wprev, nw);
             if (last2) copy_x1<1>(f, kb + 2, kb & 1, nx);
             if (last) copy_x1<3>(f, kb + 2, kb & 1, nx);
             if (i == 0) FOLD(1, NTS - 1, sc_pend);
@@ -355,7 +373,7 @@ __device__ __forceinline__ void k_loop(const Tile& t, const Feed& f, v16f (&acc)
                 read_ops(a[1], sWn, 32 * KB);
                 xs_load(kb + 2, more);
                 if (NTS == 1) {
-                    copy_w(f, kb + 3, wslot, 4 & all_ones_if_less(kb + 3, nkb));
+                    copy_w<ONCE>(f, kb + 3, wslot, 4 & all_ones_if_less(kb + 3, nkb));
                     b[0][0] = b[1][0];
                     b[0][1] = b[1][1];
                 }
@@ -433,9 +451,12 @@ __global__ __launch_bounds__(NTHREADS, 1) void ffn_gemm(const uint8_t* __restric
     //      (down projection) or, GATED, [16 gate rows | 16 up rows] of features f0 + 16w .. 16w+15.
     // (LINEAR: products of at most 64 rows stream, and a larger one has no tile as short)
     const bool narrow = !LINEAR && wk.nrows <= NARROW_ROWS;    // block-uniform
+    const bool once = !LINEAR && wk.tiles <= (GATED ? GATE_UP_ONCE_TILES : DOWN_ONCE_TILES);   // as is this
     // A wave whose features all lie beyond NOUT (down projection, NOUT an odd multiple of 128: feature tile half empty)
     // copies the last 32 features again; they are multiplied and not stored.
     Feed feed;
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t*)smem;
+    feed.lds_rows = lds0 + wave * 32 * KB;                     // this wave's rows inside a tile buffer
     {
         const int sub = lane >> 3, cslot = lane & 7;
         const int f_wave = GATED ? (narrow ? f0 + wave * 16 : f0 + (wave >> 1) * 32) : min(f0 + wave * 32, NOUT - 32);
@@ -443,19 +464,24 @@ __global__ __launch_bounds__(NTHREADS, 1) void ffn_gemm(const uint8_t* __restric
         const bool split = GATED && narrow;                    // copies 0,1 gate rows and 2,3 up rows of the same features
         feed.w_base[0] = ((GATED && !narrow && (wave & 1)) ? Wb : Wa) + w0;
         feed.w_base[1] = split ? Wb + w0 : feed.w_base[0] + (size_t)16 * K;
+        uint32_t chunk[4];
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const int r = wave * 32 + j * 8 + sub;
-            const uint32_t chunk = (cslot ^ (r & 7) ^ ((r >> 3) & 1)) << 4;
-            if (j < 2) feed.w_off[j] = (uint32_t)(j * 8 + sub) * (uint32_t)K + chunk;
-            const int p = min(wk.row0 + r, row_end - 1);      // rows past the tile repeat its last row
+            chunk[j] = (cslot ^ (r & 7) ^ ((r >> 3) & 1)) << 4;
+            if (j < 2) feed.w_off[j] = (uint32_t)(j * 8 + sub) * (uint32_t)K + chunk[j];
+        }
+        // the weights of K block 0 are on their way before the rows' tokens have been looked up
+        if (narrow || once) copy_w<true>(feed, 0, 0);
+        else copy_w<false>(feed, 0, 0);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int p = min(wk.row0 + wave * 32 + j * 8 + sub, row_end - 1);   // rows past the tile repeat its last row
             const int src = GATHER ? (int)min((uint32_t)perm[p] / (uint32_t)fan, (uint32_t)(n_tok - 1)) : p - wk.row0;
-            feed.x_off[j] = (uint32_t)src * (uint32_t)K + chunk;
+            feed.x_off[j] = (uint32_t)src * (uint32_t)K + chunk[j];
         }
     }
     feed.x_base = GATHER ? act : act + (size_t)wk.row0 * K;
-    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t*)smem;
-    feed.lds_rows = lds0 + wave * 32 * KB;                     // this wave's rows inside a tile buffer
 
     // 8-row activation copies that lie wholly beyond the tile's last row are not issued at all
     // (a ragged tile then moves only the rows it has); wave-uniform
@@ -468,7 +494,6 @@ __global__ __launch_bounds__(NTHREADS, 1) void ffn_gemm(const uint8_t* __restric
 
     copy_x(feed, 0, 0);
     if (narrow) {
-        copy_w_once(feed, 0, 0);
         // ---- NARROW tile: at most 64 rows.  In the layout above a wave has at most two products per K block, with one token group
         //      half of the waves none, behind a schedule made for eight.  Here
         //      wave w multiplies the 32 staged weight rows it copies itself by the tile's 64 token columns (two
@@ -491,7 +516,12 @@ __global__ __launch_bounds__(NTHREADS, 1) void ffn_gemm(const uint8_t* __restric
         float xs_n[2], xs_cur[2];
         xs_load(xs_n[0], 0, 0);
         xs_load(xs_n[1], 0, 1);
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        if (nkb > 1) {
+            copy_w<true>(feed, 1, 1);
+            asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
+        } else {
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        }
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
 #pragma unroll
@@ -500,9 +530,8 @@ __global__ __launch_bounds__(NTHREADS, 1) void ffn_gemm(const uint8_t* __restric
             xs_load(xs_n[0], 1, 0);
             xs_load(xs_n[1], 1, 1);
             copy_x(feed, 1, 1);
-            copy_w_once(feed, 1, 1);
         }
-        if (nkb > 2) copy_w_once(feed, 2, 2);
+        if (nkb > 2) copy_w<true>(feed, 2, 2);
         v16f an[2];
 #pragma unroll
         for (int ts = 0; ts < 2; ++ts)
@@ -541,7 +570,7 @@ __global__ __launch_bounds__(NTHREADS, 1) void ffn_gemm(const uint8_t* __restric
                 xs_load(xs_n[1], kb + 2, 1);
                 copy_x(feed, kb + 2, kb & 1);
             }
-            if (kb + 3 < nkb) copy_w_once(feed, kb + 3, wslot);
+            if (kb + 3 < nkb) copy_w<true>(feed, kb + 3, wslot);
             // the four matrix instructions have left the pipe by now; a few wait states more cost nothing here
             asm volatile("s_nop 15\n\ts_nop 15\n\ts_nop 7" ::: "memory");
             PIN(T0);
@@ -578,6 +607,7 @@ __global__ __launch_bounds__(NTHREADS, 1) void ffn_gemm(const uint8_t* __restric
                 if (half == 0) s_amax[wave * 64 + ts * 32 + l32] = amax[ts];
             }
             __syncthreads();                                   // the 128 features of a token's group live in all 8 waves
+            uint8_t* const s_codes = smem + 8 * NARROW_ROWS * 4;       // out through LDS, as from a full tile
 #pragma unroll
             for (int ts = 0; ts < 2; ++ts) {
                 const int trow = ts * 32 + l32;
@@ -587,15 +617,15 @@ __global__ __launch_bounds__(NTHREADS, 1) void ffn_gemm(const uint8_t* __restric
                 for (int w = 0; w < 8; ++w) am = fmaxf(am, s_amax[w * 64 + trow]);
                 const float sc = (am == 0.f) ? 1.0f : am / 448.0f;
                 const Quotient q(sc);
-                if (p < row_end) {
-                    uint8_t* dst = hq + (size_t)p * NOUT + f0 + wave * 16 + half * 4;
+                uint8_t* const dst = s_codes + trow * CODES_LD + wave * 16 + half * 4;
 #pragma unroll
-                    for (int r4 = 0; r4 < 2; ++r4)
-                        *reinterpret_cast<uint32_t*>(dst + r4 * 8) =
-                            e4m3_codes4(q, h[ts][r4 * 4], h[ts][r4 * 4 + 1], h[ts][r4 * 4 + 2], h[ts][r4 * 4 + 3]);
-                    if (half == 0 && wave == 0) hs[(size_t)wk.ft * n_rows + p] = sc;
-                }
+                for (int r4 = 0; r4 < 2; ++r4)
+                    *reinterpret_cast<uint32_t*>(dst + r4 * 8) =
+                        e4m3_codes4(q, h[ts][r4 * 4], h[ts][r4 * 4 + 1], h[ts][r4 * 4 + 2], h[ts][r4 * 4 + 3]);
+                if (half == 0 && wave == 0 && p < row_end) hs[(size_t)wk.ft * n_rows + p] = sc;
             }
+            __syncthreads();
+            store_codes(hq, s_codes, wk, f0, NOUT, tid);
         } else {
             // 64 rows x 256 features: 16-byte pieces straight from the accumulator layout (a narrow tile's output is small)
 #pragma unroll
@@ -613,7 +643,6 @@ __global__ __launch_bounds__(NTHREADS, 1) void ffn_gemm(const uint8_t* __restric
         }
         return;
     }
-    copy_w(feed, 0, 0);
     // ---- full tile: 32-row token groups n = ceil(rows / 32) of 3..8; waves 0..3 (token half 0) take the first ceil(n/2)
     //      of them, waves 4..7 the others.  Wave w and wave w + 4 share a SIMD, so every SIMD multiplies n groups: the
     //      matrix time of a tile follows its height in steps of 32 rows.
@@ -633,12 +662,18 @@ __global__ __launch_bounds__(NTHREADS, 1) void ffn_gemm(const uint8_t* __restric
     tile.act_s = reinterpret_cast<const uint8_t*>(act_s);
     tile.sa = sa_e;
     tile.sb = sb_e;
+#define LOOP(NTS)                                              \
+    do {                                                       \
+        if (once) k_loop<NTS, GATED, true>(tile, feed, acc);   \
+        else k_loop<NTS, GATED, false>(tile, feed, acc);       \
+    } while (0)
     switch (nts) {
-        case 4: k_loop<4, GATED>(tile, feed, acc); break;
-        case 3: k_loop<3, GATED>(tile, feed, acc); break;
-        case 2: k_loop<2, GATED>(tile, feed, acc); break;
-        default: k_loop<1, GATED>(tile, feed, acc); break;
+        case 4: LOOP(4); break;
+        case 3: LOOP(3); break;
+        case 2: LOOP(2); break;
+        default: LOOP(1); break;
     }
+#undef LOOP
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
     __builtin_amdgcn_s_barrier();                              // every wave is done with the operand rings
     asm volatile("" ::: "memory");
@@ -662,6 +697,7 @@ __global__ __launch_bounds__(NTHREADS, 1) void ffn_gemm(const uint8_t* __restric
             if (half == 0) s_amax[wf * X_ROWS + (grp0 + ts) * 32 + l32] = am;
         }
         __syncthreads();                                       // the other 96 features live in the other three waves of wt
+        uint8_t* const s_codes = smem + 4 * X_ROWS * 4;        // [X_ROWS][CODES_LD], behind s_amax
 #pragma unroll
         for (int ts = 0; ts < 4; ++ts) {
             if (ts >= nts) break;
@@ -671,15 +707,15 @@ __global__ __launch_bounds__(NTHREADS, 1) void ffn_gemm(const uint8_t* __restric
                                    fmaxf(s_amax[2 * X_ROWS + trow], s_amax[3 * X_ROWS + trow]));
             const float sc = (am == 0.f) ? 1.0f : am / 448.0f;
             const Quotient q(sc);
-            if (p < row_end) {
-                uint8_t* dst = hq + (size_t)p * NOUT + f0 + wf * 32 + half * 4;
+            uint8_t* const dst = s_codes + trow * CODES_LD + wf * 32 + half * 4;
 #pragma unroll
-                for (int r4 = 0; r4 < 4; ++r4)
-                    *reinterpret_cast<uint32_t*>(dst + r4 * 8) =
-                        e4m3_codes4(q, h[ts][r4 * 4], h[ts][r4 * 4 + 1], h[ts][r4 * 4 + 2], h[ts][r4 * 4 + 3]);
-                if (half == 0 && wf == 0) hs[(size_t)wk.ft * n_rows + p] = sc;
-            }
+            for (int r4 = 0; r4 < 4; ++r4)
+                *reinterpret_cast<uint32_t*>(dst + r4 * 8) =
+                    e4m3_codes4(q, h[ts][r4 * 4], h[ts][r4 * 4 + 1], h[ts][r4 * 4 + 2], h[ts][r4 * 4 + 3]);
+            if (half == 0 && wf == 0 && p < row_end) hs[(size_t)wk.ft * n_rows + p] = sc;
         }
+        __syncthreads();
+        store_codes(hq, s_codes, wk, f0, NOUT, tid);
     } else {
         // The accumulators hold 16-byte pieces of 64 different rows per store instruction, which the memory
         // pipeline would take as 64 separate requests.  Each wave therefore turns its 64 x 32-token blocks through a
@@ -879,14 +915,13 @@ hipError_t launch_expert_ffn(moe_ctx* c, const uint8_t* xq, const float* xs, con
     } else if (stream1) {
         hipError_t e = launch_stream_gate_up(c, xq, xs, perm, offsets, units1, W1, W3, s1, s3);
         if (e != hipSuccess) return e;
-    } else if (perm) {
-        hipLaunchKernelGGL((ffn_gemm<true, true, false>), dim3(grid1), dim3(NTHREADS), SMEM_BYTES, c->stream, xq, c->xs_sorted, N,
-                           perm, D.k, D.T, work, c->n_tiles, W1, W3, s1, s3, D.d, D.F, c->hq, c->hs,
-                           (float*)nullptr);
     } else {
-        hipLaunchKernelGGL((ffn_gemm<true, false, false>), dim3(grid1), dim3(NTHREADS), SMEM_BYTES, c->stream, xq, xs, N,
-                           (const int32_t*)nullptr, 1, 1, work, c->n_tiles, W1, W3, s1, s3, D.d, D.F, c->hq,
-                           c->hs, (float*)nullptr);
+        auto launch = [&](auto kernel, const float* scales, int fan, int n_tok) {
+            hipLaunchKernelGGL(kernel, dim3(grid1), dim3(NTHREADS), SMEM_BYTES, c->stream, xq, scales, N, perm, fan, n_tok, work,
+                               c->n_tiles, W1, W3, s1, s3, D.d, D.F, c->hq, c->hs, (float*)nullptr);
+        };
+        if (perm) launch(ffn_gemm<true, true, false>, c->xs_sorted, D.k, D.T);
+        else launch(ffn_gemm<true, false, false>, xs, 1, 1);
     }
     if (ev) (void)hipEventRecord(ev[1], c->stream);
     if (down_few(&D)) {
@@ -898,9 +933,9 @@ hipError_t launch_expert_ffn(moe_ctx* c, const uint8_t* xq, const float* xs, con
     }
     if (down != Down::STREAM) {
         const int grid2 = ((int)down_big_units(&D) + NXCD - 1) / NXCD * NXCD;
-        hipLaunchKernelGGL((ffn_gemm<false, false, false>), dim3(grid2), dim3(NTHREADS), SMEM_BYTES, c->stream, c->hq, c->hs,
-                           N, (const int32_t*)nullptr, 1, 1, work2, n_work2, W2, (const uint8_t*)nullptr, s2,
-                           (const float*)nullptr, D.F, D.d, (uint8_t*)nullptr, (float*)nullptr, y_perm);
+        hipLaunchKernelGGL((ffn_gemm<false, false, false>), dim3(grid2), dim3(NTHREADS), SMEM_BYTES, c->stream, c->hq, c->hs, N, (const int32_t*)nullptr, 1, 1,
+                           work2, n_work2, W2, (const uint8_t*)nullptr, s2, (const float*)nullptr, D.F, D.d, (uint8_t*)nullptr,
+                           (float*)nullptr, y_perm);
     }
     if (ev) (void)hipEventRecord(ev[2], c->stream);
     return hipGetLastError();

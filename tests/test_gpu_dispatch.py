@@ -252,10 +252,11 @@ def test_linear_of_few_blocks(gpu_lib, rows, K, NOUT):
         gpu_lib.moe_destroy(ctx)
 
 
-@pytest.mark.parametrize("T", [1, 2, 5, 16])
+# 200 and 400 tokens on one set of experts: one and two full tiles an expert, whose weights go past the caches
+@pytest.mark.parametrize("T", [1, 2, 5, 16, 200, 400])
 @pytest.mark.parametrize("d,E,k,F", [(640, 16, 2, 384), (128, 8, 3, 128), (1152, 5, 1, 1280)])
 @pytest.mark.parametrize("hot", [False, True], ids=["spread", "one-set"])
-def test_layer_of_a_few_tokens_has_the_bits_of_a_large_batch(gpu_lib, T, d, E, k, F, hot):
+def test_layer_of_a_small_batch_has_the_bits_of_a_large_one(gpu_lib, T, d, E, k, F, hot):
     """The same tokens and log as the first T of 1500, which take the big tiles: the replayed layer's outputs, hidden codes and scales."""
     assert 1500 * k > 48 * E
     g = torch.Generator(device="cuda").manual_seed(T + d + E)
