@@ -88,6 +88,16 @@ int moe_route_replay(moe_ctx* ctx, const uint16_t* x_bf16, const int32_t* logged
                      const float* logged_w, int32_t* topk_idx, float* topk_w,
                      int32_t* offsets, int32_t* perm, int32_t* inv_perm);
 
+/* The two calls above with the batch's token-order quantisation, moe_quantize_fp8(ctx, x, T, d, 128, NULL, 1, xq_tok, xs_tok),
+ * taken along in the launches of the permutation, which leave most of the chip idle.  Same outputs, bit for bit, as the two
+ * separate calls.  xq_tok [T,d] u8, xs_tok [d/128][T] f32 and x_bf16 must not be NULL (T == 0: not read). */
+int moe_route_quantize(moe_ctx* ctx, const uint16_t* x_bf16, const float* W_router, const float* sel_bias,
+                       int32_t k, int32_t* topk_idx, float* topk_w, int32_t* offsets, int32_t* perm,
+                       int32_t* inv_perm, uint8_t* xq_tok, float* xs_tok);
+int moe_route_replay_quantize(moe_ctx* ctx, const uint16_t* x_bf16, const int32_t* logged_idx,
+                              const float* logged_w, int32_t* topk_idx, float* topk_w, int32_t* offsets,
+                              int32_t* perm, int32_t* inv_perm, uint8_t* xq_tok, float* xs_tok);
+
 /* moe_route_replay for callers that cannot allocate device memory: code under HIP graph capture, tight
  * serving loops, harnesses that forbid hipMalloc.  It needs no context: the permutation's workspace (per-chunk
  * histograms) lives in a static 512 KiB device array inside the library, which bounds the batch at

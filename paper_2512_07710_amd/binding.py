@@ -18,7 +18,7 @@ LIB_PATH = os.path.join(_HERE, "libmoe355.so")
 _lib: Optional[ctypes.CDLL] = None
 
 EXPORTS = ("moe_create", "moe_destroy", "moe_strerror", "moe_route", "moe_route_replay", "moe_route_replay_noalloc",
-           "moe_route_replay_ids",
+           "moe_route_replay_ids", "moe_route_quantize", "moe_route_replay_quantize",
            "moe_check_ids", "moe_quantize_fp8", "moe_quantize_weights_fp8", "moe_linear_fp8", "moe_expert_ffn_fp8",
            "moe_expert_ffn_fp8_gather", "moe_combine", "moe_balance_lengths", "moe_debug_copy_hidden",
            "moe_probe_copy", "moe_probe_fp8_mfma", "moe_profile_enable", "moe_profile_read", "moe_version")
@@ -51,6 +51,8 @@ def load_library(path: Optional[str] = None) -> ctypes.CDLL:
     lib.moe_version.restype = ctypes.c_char_p
     lib.moe_route.argtypes = [vp, vp, vp, vp, i32, vp, vp, vp, vp, vp]
     lib.moe_route_replay.argtypes = [vp, vp, vp, vp, vp, vp, vp, vp, vp]
+    lib.moe_route_quantize.argtypes = [vp, vp, vp, vp, i32] + [vp] * 7
+    lib.moe_route_replay_quantize.argtypes = [vp] * 11
     lib.moe_route_replay_ids.argtypes = [vp] * 9
     lib.moe_route_replay_noalloc.argtypes = [vp, i32, i32, i32, vp, vp, vp, vp, vp, vp, vp, vp]
     lib.moe_check_ids.argtypes = [vp]
@@ -120,6 +122,22 @@ def moe_route_replay(ctx, x, logged_idx, logged_w, topk_idx, topk_w, offsets, pe
                                            _ptr(topk_w, torch.float32), _ptr(offsets, torch.int32),
                                            _ptr(perm, torch.int32), _ptr(inv_perm, torch.int32)),
            "moe_route_replay")
+
+
+def moe_route_quantize(ctx, x, W_router, sel_bias, k, topk_idx, topk_w, offsets, perm, inv_perm, xq_tok, xs_tok) -> None:
+    i32, f32 = torch.int32, torch.float32
+    _check(load_library().moe_route_quantize(ctx, _ptr(x, torch.bfloat16), _ptr(W_router, f32), _ptr(sel_bias, f32), k,
+                                             _ptr(topk_idx, i32), _ptr(topk_w, f32), _ptr(offsets, i32), _ptr(perm, i32),
+                                             _ptr(inv_perm, i32), _ptr(xq_tok, torch.uint8), _ptr(xs_tok, f32)),
+           "moe_route_quantize")
+
+
+def moe_route_replay_quantize(ctx, x, logged_idx, logged_w, topk_idx, topk_w, offsets, perm, inv_perm, xq_tok, xs_tok) -> None:
+    i32, f32 = torch.int32, torch.float32
+    _check(load_library().moe_route_replay_quantize(ctx, _ptr(x, torch.bfloat16), _ptr(logged_idx, i32), _ptr(logged_w, f32),
+                                                    _ptr(topk_idx, i32), _ptr(topk_w, f32), _ptr(offsets, i32),
+                                                    _ptr(perm, i32), _ptr(inv_perm, i32), _ptr(xq_tok, torch.uint8),
+                                                    _ptr(xs_tok, f32)), "moe_route_replay_quantize")
 
 
 def moe_route_replay_noalloc(stream, T, E, k, logged_idx, logged_w, topk_idx, topk_w, offsets, perm, inv_perm,

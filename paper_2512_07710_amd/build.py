@@ -20,7 +20,8 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Xclang", "-tar
 def _compile(src: str, force: bool) -> str:
     obj = os.path.join(CSRC, src.replace(".hip", ".o"))
     deps = [os.path.join(CSRC, src), os.path.join(CSRC, "moe_internal.hpp"), os.path.join(CSRC, "e4m3.hpp"),
-            os.path.join(CSRC, "ffn_common.hpp"), os.path.join(CSRC, "ffn_rows.hpp"),
+            os.path.join(CSRC, "ffn_common.hpp"), os.path.join(CSRC, "ffn_rows.hpp"), os.path.join(CSRC, "permute_block.hpp"),
+            os.path.join(CSRC, "quantize_rows.hpp"),
             os.path.join(ROOT, "include", "moe355.h")]
     if not force and os.path.exists(obj) and all(os.path.getmtime(obj) >= os.path.getmtime(p) for p in deps):
         return obj

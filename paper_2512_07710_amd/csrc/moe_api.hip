@@ -29,8 +29,30 @@ bool dims_ok(const moe_dims* d) {
     return true;
 }
 
-permute_args perm_args(moe_ctx* c, bool check_dups) {
-    return permute_args{c->stream, c->dims.T, c->dims.E, c->dims.k, c->chunk_counts, c->flags, check_dups};
+// the token-order quantisation that goes with a routing call; both pointers or none
+token_quant tokens_of(const moe_ctx* c, const uint16_t* x, uint8_t* q, float* scales) {
+    token_quant t;
+    if (q) t = token_quant{x, c->dims.T, c->dims.d, q, scales};
+    return t;
+}
+
+int route(moe_ctx* c, const uint16_t* x, const float* W_r, const float* bias, int32_t k, int32_t* topk_idx, float* topk_w,
+          int32_t* offsets, int32_t* perm, int32_t* inv_perm, uint8_t* xq, float* xs) {
+    if (!c || k != c->dims.k) return MOE_EINVAL;
+    if (c->dims.T == 0) return route_empty(c, offsets);
+    if (!x || !W_r || !topk_idx || !topk_w || !offsets || !perm || !inv_perm) return MOE_EINVAL;
+    return hip_rc(launch_route(c, x, W_r, bias, nullptr, topk_idx, topk_w, offsets, perm, inv_perm, tokens_of(c, x, xq, xs)));
+}
+
+int route_replay(moe_ctx* c, const uint16_t* x, const int32_t* logged_idx, const float* logged_w, int32_t* topk_idx, float* topk_w,
+                 int32_t* offsets, int32_t* perm, int32_t* inv_perm, uint8_t* xq, float* xs) {
+    if (!c) return MOE_EINVAL;
+    if (c->dims.T == 0) return route_empty(c, offsets);
+    if (!logged_idx || !logged_w || !topk_idx || !topk_w || !offsets || !perm || !inv_perm) return MOE_EINVAL;
+    int32_t* idx_copy = (topk_idx == logged_idx) ? nullptr : topk_idx;
+    float* w_copy = (topk_w == logged_w) ? nullptr : topk_w;
+    return hip_rc(launch_permute(permute_args_of(c, true), logged_idx, idx_copy, logged_w, w_copy, offsets, perm, inv_perm,
+                                 tokens_of(c, x, xq, xs)));
 }
 
 }  // namespace
@@ -113,24 +135,25 @@ int moe_destroy(moe_ctx* c) {
 
 int moe_route(moe_ctx* c, const uint16_t* x, const float* W_r, const float* bias, int32_t k,
               int32_t* topk_idx, float* topk_w, int32_t* offsets, int32_t* perm, int32_t* inv_perm) {
-    if (!c || k != c->dims.k) return MOE_EINVAL;
-    if (c->dims.T == 0) return route_empty(c, offsets);
-    if (!x || !W_r || !topk_idx || !topk_w || !offsets || !perm || !inv_perm) return MOE_EINVAL;
-    hipError_t e = launch_route(c, x, W_r, bias, nullptr, topk_idx, topk_w);
-    if (e != hipSuccess) return MOE_EHIP;
-    return hip_rc(launch_permute(perm_args(c, false), topk_idx, nullptr, nullptr, nullptr, offsets, perm, inv_perm));
+    return route(c, x, W_r, bias, k, topk_idx, topk_w, offsets, perm, inv_perm, nullptr, nullptr);
+}
+
+int moe_route_quantize(moe_ctx* c, const uint16_t* x, const float* W_r, const float* bias, int32_t k, int32_t* topk_idx,
+                       float* topk_w, int32_t* offsets, int32_t* perm, int32_t* inv_perm, uint8_t* xq_tok, float* xs_tok) {
+    if (c && c->dims.T != 0 && (!xq_tok || !xs_tok)) return MOE_EINVAL;
+    return route(c, x, W_r, bias, k, topk_idx, topk_w, offsets, perm, inv_perm, xq_tok, xs_tok);
 }
 
 int moe_route_replay(moe_ctx* c, const uint16_t* x, const int32_t* logged_idx, const float* logged_w,
                      int32_t* topk_idx, float* topk_w, int32_t* offsets, int32_t* perm,
                      int32_t* inv_perm) {
-    (void)x;
-    if (!c) return MOE_EINVAL;
-    if (c->dims.T == 0) return route_empty(c, offsets);
-    if (!logged_idx || !logged_w || !topk_idx || !topk_w || !offsets || !perm || !inv_perm) return MOE_EINVAL;
-    int32_t* idx_copy = (topk_idx == logged_idx) ? nullptr : topk_idx;
-    float* w_copy = (topk_w == logged_w) ? nullptr : topk_w;
-    return hip_rc(launch_permute(perm_args(c, true), logged_idx, idx_copy, logged_w, w_copy, offsets, perm, inv_perm));
+    return route_replay(c, x, logged_idx, logged_w, topk_idx, topk_w, offsets, perm, inv_perm, nullptr, nullptr);
+}
+
+int moe_route_replay_quantize(moe_ctx* c, const uint16_t* x, const int32_t* logged_idx, const float* logged_w, int32_t* topk_idx,
+                              float* topk_w, int32_t* offsets, int32_t* perm, int32_t* inv_perm, uint8_t* xq_tok, float* xs_tok) {
+    if (c && c->dims.T != 0 && (!x || !xq_tok || !xs_tok)) return MOE_EINVAL;
+    return route_replay(c, x, logged_idx, logged_w, topk_idx, topk_w, offsets, perm, inv_perm, xq_tok, xs_tok);
 }
 
 int moe_route_replay_noalloc(void* hip_stream, int32_t T, int32_t E, int32_t k, const int32_t* logged_idx,
@@ -145,9 +168,7 @@ int moe_route_replay_ids(moe_ctx* c, const uint16_t* x, const float* W_r, const 
     if (!c) return MOE_EINVAL;
     if (c->dims.T == 0) return route_empty(c, offsets);
     if (!x || !W_r || !logged_idx || !topk_idx || !topk_w || !offsets || !perm || !inv_perm) return MOE_EINVAL;
-    hipError_t e = launch_route(c, x, W_r, nullptr, logged_idx, topk_idx, topk_w);
-    if (e != hipSuccess) return MOE_EHIP;
-    return hip_rc(launch_permute(perm_args(c, true), topk_idx, nullptr, nullptr, nullptr, offsets, perm, inv_perm));
+    return hip_rc(launch_route(c, x, W_r, nullptr, logged_idx, topk_idx, topk_w, offsets, perm, inv_perm, token_quant{}));
 }
 
 int moe_check_ids(moe_ctx* c) {

@@ -43,9 +43,20 @@ struct moe_ctx {
 
 namespace moe355 {
 
-// logged_idx == nullptr: top-k selection; otherwise the ids are given and only the gate weights are computed
-hipError_t launch_route(moe_ctx* c, const uint16_t* x, const float* W_r, const float* bias,
-                        const int32_t* logged_idx, int32_t* topk_idx, float* topk_w);
+// Token-order quantisation that a permutation's launch takes along: rows of `cols` bf16 -> codes and [cols/128][rows] scales.
+// x == nullptr: none.
+struct token_quant {
+    const uint16_t* x = nullptr;
+    int64_t rows = 0;
+    int32_t cols = 0;
+    uint8_t* q = nullptr;
+    float* scales = nullptr;
+};
+// logged_idx == nullptr: top-k selection; otherwise the ids are given (and searched for repeats) and only the gate weights are
+// computed.  Router, then the permutation, with `tokens` quantised along the way.
+hipError_t launch_route(moe_ctx* c, const uint16_t* x, const float* W_r, const float* bias, const int32_t* logged_idx,
+                        int32_t* topk_idx, float* topk_w, int32_t* offsets, int32_t* perm, int32_t* inv_perm,
+                        const token_quant& tokens);
 // Permutation of T*k assignments over E experts on `stream`.  chunk_counts: ceil(T*k / PERM_CHUNK) * E ints of
 // scratch; flags: two ints, [0] raised by an id outside [0,E), [1] (check_dups only) by a repeat inside a token.
 struct permute_args {
@@ -56,7 +67,10 @@ struct permute_args {
     bool check_dups;
 };
 hipError_t launch_permute(const permute_args& a, const int32_t* ids_in, int32_t* ids_copy, const float* w_in,
-                          float* w_copy, int32_t* offsets, int32_t* perm, int32_t* inv_perm);
+                          float* w_copy, int32_t* offsets, int32_t* perm, int32_t* inv_perm, const token_quant& tokens);
+inline permute_args permute_args_of(moe_ctx* c, bool check_dups) {
+    return permute_args{c->stream, c->dims.T, c->dims.E, c->dims.k, c->chunk_counts, c->flags, check_dups};
+}
 // Router Replay with every byte of workspace in a static device array (permute.hip)
 int route_replay_noalloc(hipStream_t stream, int32_t T, int32_t E, int32_t k, const int32_t* logged_idx,
                          const float* logged_w, int32_t* topk_idx, float* topk_w, int32_t* offsets, int32_t* perm,

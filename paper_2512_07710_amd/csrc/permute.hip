@@ -12,7 +12,8 @@
 //      what was given).
 // The result is unique (stable), so it can be compared bit for bit.  Batches of at most one_block_max_n
 // assignments take one fused launch instead (permute_one_block).
-#include "moe_internal.hpp"
+#include "permute_block.hpp"
+#include "quantize_rows.hpp"
 
 #include <mutex>
 
@@ -59,7 +60,11 @@ hipError_t scratch_on_current_device(int32_t** out) {
 __global__ __launch_bounds__(256) void chunk_hist_rank(const int32_t* __restrict__ ids, int N, int E,
                                                        int32_t* __restrict__ chunk_counts,
                                                        int32_t* __restrict__ rank_out,
-                                                       int32_t* __restrict__ ids_copy) {
+                                                       int32_t* __restrict__ ids_copy, int n_chunks, token_quant tokens) {
+    if ((int)blockIdx.x >= n_chunks) {                // (as in permute_one_block)
+        quantize_block<256, 2>(tokens, blockIdx.x - n_chunks);
+        return;
+    }
     constexpr int PER_WAVE = PERM_CHUNK / 4;          // 512 entries, 8 steps of 64
     __shared__ int32_t s_cnt[4][MAX_E];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -174,110 +179,23 @@ __global__ __launch_bounds__(256) void scatter(const int32_t* __restrict__ ids, 
     perm[pos] = i;
 }
 
-// Up to one_block_max_n assignments: the three steps in one block and one launch, where the launches themselves are most of the
-// time.  Sixteen waves rank STEPS times 64 entries each in the manner of chunk_hist_rank, then scan over the experts and scatter
-// from registers; bound by its chain of barriers and memory round trips.
-// Whole calls in a row, us, this form / the three launches: replay of 2100 assignments k = 6 7.6 / 10.6, 4000 k = 2 6.9 / 10.3,
-// k = 6 8.7 / 10.7, k = 8 9.5 / 10.9, k = 16 12.0 / 11.5 (on cleared caches 16.3 / 18.0).  Beyond that the search for repeated ids, up to
-// k - 1 reads of earlier slots one after another in each of a thread's STEPS entries, weighs more in one block than launches
-// that overlap: 4500 k = 6 13.3 / 10.6, 8100 15.4 / 11.4, 8096 k = 16 22.3 / 11.9; layers of 4500 k = 6 57.7 / 55.0, 4800 k = 16
-// 94.2 / 86.8, 8000 k = 8 177 / 173, but 3360 k = 16 54.4 / 55.4.  Without that search (ids from the router
-// itself, one slot a token) the one block stays ahead: with the router 23.4 / 25.7 at 4500, 25.5 / 27.0 at 8100 and level at 8096 with
-// k = 8; replay of 8100 k = 1 11.6 / 11.2, a replayed layer of 4500 k = 1 55.2 / 56.3.
-constexpr int ONE_BLOCK_WAVES = 16;
-constexpr int ONE_BLOCK_MAX_STEPS = 8;
 constexpr int ONE_BLOCK_MAX_N = ONE_BLOCK_WAVES * ONE_BLOCK_MAX_STEPS * 64;
 constexpr int ONE_BLOCK_CHECKED_MAX_N = 4096;
 static_assert(ONE_BLOCK_CHECKED_MAX_N <= ONE_BLOCK_MAX_N, "the block holds that many");
 inline int one_block_max_n(bool check_dups, int k) { return check_dups && k > 1 ? ONE_BLOCK_CHECKED_MAX_N : ONE_BLOCK_MAX_N; }
 
+// The quantisation of the same batch's tokens, which waits for nobody, may come along in blocks of its own (block 0 permutes): beside
+// one busy block the rest of the chip is idle, and a launch less (777 tokens x 2176: 9.2 + 4.9 us one after the other).
 template <int STEPS>
 __global__ __launch_bounds__(ONE_BLOCK_WAVES * 64) void permute_one_block(
     const int32_t* __restrict__ ids, int N, int E, int32_t* __restrict__ ids_copy, const float* __restrict__ w_in,
     float* __restrict__ w_copy, int32_t* __restrict__ offsets, int32_t* __restrict__ perm, int32_t* __restrict__ inv_perm,
-    int k, bool check_dups, int32_t* __restrict__ flags) {
-    constexpr int PER_WAVE = STEPS * 64;
-    __shared__ int32_t s_cnt[ONE_BLOCK_WAVES][MAX_E];
-    __shared__ int32_t s_off[MAX_E];                  // exclusive scan of the expert totals
-    __shared__ int32_t s_part[MAX_E / 64];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    int32_t my_id[STEPS], my_rank[STEPS];
-#pragma unroll
-    for (int st = 0; st < STEPS; ++st) {
-        const int i = wave * PER_WAVE + st * 64 + lane;
-        my_id[st] = -1;
-        if (i < N) {
-            my_id[st] = ids[i];
-            if (w_copy) w_copy[i] = w_in[i];
-        }
+    int k, bool check_dups, int32_t* __restrict__ flags, token_quant tokens) {
+    if (blockIdx.x > 0) {
+        quantize_block<ONE_BLOCK_WAVES * 64, 1>(tokens, blockIdx.x - 1);
+        return;
     }
-    for (int i = tid; i < ONE_BLOCK_WAVES * MAX_E; i += ONE_BLOCK_WAVES * 64) (&s_cnt[0][0])[i] = 0;
-    __syncthreads();
-    const uint64_t lower = (1ull << lane) - 1ull;
-#pragma unroll
-    for (int st = 0; st < STEPS; ++st) {
-        const int i = wave * PER_WAVE + st * 64 + lane;
-        const int32_t v = my_id[st];
-        if (ids_copy && i < N) ids_copy[i] = v;
-        const bool valid = v >= 0 && v < E;
-        const int key = v & (MAX_E - 1);
-        uint64_t same = __ballot(valid);
-        if (!valid) same = ~same;
-#pragma unroll
-        for (int bit = 0; bit < 8; ++bit) {
-            const uint64_t bal = __ballot((key >> bit) & 1);
-            same &= ((key >> bit) & 1) ? bal : ~bal;
-        }
-        const int before = s_cnt[wave][key];
-        my_rank[st] = before + __popcll(same & lower);
-        if (valid && (same & lower) == 0ull) s_cnt[wave][key] = before + __popcll(same);
-    }
-    __syncthreads();
-    int total = 0, incl = 0;
-    if (tid < MAX_E) {                                // thread e: per-wave bases and the total of expert e
-#pragma unroll
-        for (int w = 0; w < ONE_BLOCK_WAVES; ++w) {
-            const int c = s_cnt[w][tid];
-            s_cnt[w][tid] = total;
-            total += c;
-        }
-        if (tid >= E) total = 0;
-        incl = total;
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const int v = __shfl_up(incl, off);
-            incl += lane >= off ? v : 0;
-        }
-        if (lane == 63) s_part[wave] = incl;
-    }
-    __syncthreads();
-    if (tid < MAX_E) {
-        for (int w = 0; w < wave; ++w) incl += s_part[w];
-        s_off[tid] = incl - total;
-        if (tid < E) offsets[tid + 1] = incl;
-        if (tid == 0) offsets[0] = 0;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int st = 0; st < STEPS; ++st) {
-        const int i = wave * PER_WAVE + st * 64 + lane;
-        if (i >= N) continue;
-        const int e = my_id[st];
-        if (e < 0 || e >= E) {
-            flags[0] = 1;
-            inv_perm[i] = -1;
-            continue;
-        }
-        if (check_dups) {
-            const int first = i - i % k;
-            bool dup = false;
-            for (int q = first; q < i; ++q) dup |= ids[q] == e;
-            if (dup) flags[1] = 1;
-        }
-        const int pos = s_off[e] + s_cnt[wave][e] + my_rank[st];
-        inv_perm[i] = pos;
-        perm[pos] = i;
-    }
+    permute_block<STEPS>([&](int i) { return ids[i]; }, N, E, ids_copy, w_in, w_copy, offsets, perm, inv_perm, k, check_dups, flags);
 }
 
 __global__ void fill_i32(int32_t* __restrict__ p, int n, int32_t v) {
@@ -294,13 +212,14 @@ hipError_t launch_fill_i32(hipStream_t stream, int32_t* p, int n, int32_t v) {
 }
 
 hipError_t launch_permute(const permute_args& a, const int32_t* ids_in, int32_t* ids_copy, const float* w_in,
-                          float* w_copy, int32_t* offsets, int32_t* perm, int32_t* inv_perm) {
+                          float* w_copy, int32_t* offsets, int32_t* perm, int32_t* inv_perm, const token_quant& tokens) {
     const int N = a.T * a.k;
     const int n_chunks = (N + PERM_CHUNK - 1) / PERM_CHUNK;
     if (N > 0 && N <= one_block_max_n(a.check_dups, a.k)) {
 #define MOE_ONE_BLOCK(STEPS_)                                                                                              \
-    hipLaunchKernelGGL(permute_one_block<STEPS_>, dim3(1), dim3(ONE_BLOCK_WAVES * 64), 0, a.stream, ids_in, N, a.E, ids_copy, \
-                       w_in, w_copy, offsets, perm, inv_perm, a.k, a.check_dups, a.flags)
+    hipLaunchKernelGGL(permute_one_block<STEPS_>, dim3(grid), dim3(ONE_BLOCK_WAVES * 64), 0, a.stream, ids_in, N, a.E, ids_copy, \
+                       w_in, w_copy, offsets, perm, inv_perm, a.k, a.check_dups, a.flags, tokens)
+        const unsigned grid = (unsigned)(1 + quantize_blocks<ONE_BLOCK_WAVES * 64, 1>(tokens));
         const int steps = (N + ONE_BLOCK_WAVES * 64 - 1) / (ONE_BLOCK_WAVES * 64);
         if (steps == 1) MOE_ONE_BLOCK(1);
         else if (steps == 2) MOE_ONE_BLOCK(2);
@@ -310,8 +229,8 @@ hipError_t launch_permute(const permute_args& a, const int32_t* ids_in, int32_t*
         return hipGetLastError();
     }
     if (n_chunks > 0)
-        hipLaunchKernelGGL(chunk_hist_rank, dim3(n_chunks), dim3(256), 0, a.stream, ids_in, N, a.E,
-                           a.chunk_counts, inv_perm, ids_copy);
+        hipLaunchKernelGGL(chunk_hist_rank, dim3((unsigned)(n_chunks + quantize_blocks<256, 2>(tokens))), dim3(256), 0, a.stream, ids_in,
+                           N, a.E, a.chunk_counts, inv_perm, ids_copy, n_chunks, tokens);
     hipLaunchKernelGGL(scan_chunks, dim3(1), dim3(256), 0, a.stream, a.chunk_counts, n_chunks, a.E, N,
                        offsets);
     if (N > 0)
@@ -338,8 +257,8 @@ int route_replay_noalloc(hipStream_t stream, int32_t T, int32_t E, int32_t k, co
     const permute_args a{stream, T, E, k, base, flags, true};
     int32_t* idx_copy = (topk_idx == logged_idx) ? nullptr : topk_idx;
     float* w_copy = (topk_w == logged_w) ? nullptr : topk_w;
-    return launch_permute(a, logged_idx, idx_copy, logged_w, w_copy, offsets, perm, inv_perm) == hipSuccess ? MOE_OK
-                                                                                                           : MOE_EHIP;
+    return launch_permute(a, logged_idx, idx_copy, logged_w, w_copy, offsets, perm, inv_perm, token_quant{}) == hipSuccess ? MOE_OK
+                                                                                                                          : MOE_EHIP;
 }
 
 }  // namespace moe355

@@ -1,0 +1,109 @@
+// The whole permutation of a small batch in one block: shared by the permutation's own launch and the router's last one.
+#pragma once
+#include "moe_internal.hpp"
+
+namespace moe355 {
+
+// Up to one_block_max_n assignments: the three steps of permute.hip in one block and one launch, where the launches themselves are most of the
+// time.  Sixteen waves rank STEPS times 64 entries each in the manner of chunk_hist_rank, then scan over the experts and scatter
+// from registers; bound by its chain of barriers and memory round trips.
+// Whole calls in a row, us, this form / the three launches: replay of 2100 assignments k = 6 7.6 / 10.6, 4000 k = 2 6.9 / 10.3,
+// k = 6 8.7 / 10.7, k = 8 9.5 / 10.9, k = 16 12.0 / 11.5 (on cleared caches 16.3 / 18.0).  Beyond that the search for repeated ids, up to
+// k - 1 reads of earlier slots one after another in each of a thread's STEPS entries, weighs more in one block than launches
+// that overlap: 4500 k = 6 13.3 / 10.6, 8100 15.4 / 11.4, 8096 k = 16 22.3 / 11.9; layers of 4500 k = 6 57.7 / 55.0, 4800 k = 16
+// 94.2 / 86.8, 8000 k = 8 177 / 173, but 3360 k = 16 54.4 / 55.4.  Without that search (ids from the router
+// itself, one slot a token) the one block stays ahead: with the router 23.4 / 25.7 at 4500, 25.5 / 27.0 at 8100 and level at 8096 with
+// k = 8; replay of 8100 k = 1 11.6 / 11.2, a replayed layer of 4500 k = 1 55.2 / 56.3.
+constexpr int ONE_BLOCK_WAVES = 16;
+constexpr int ONE_BLOCK_MAX_STEPS = 8;
+
+// id_at(i): the expert of assignment i < N; every thread of the block calls it
+template <int STEPS, class IdAt>
+__device__ inline void permute_block(IdAt id_at, int N, int E, int32_t* __restrict__ ids_copy, const float* __restrict__ w_in,
+                                     float* __restrict__ w_copy, int32_t* __restrict__ offsets, int32_t* __restrict__ perm,
+                                     int32_t* __restrict__ inv_perm, int k, bool check_dups, int32_t* __restrict__ flags) {
+    constexpr int PER_WAVE = STEPS * 64;
+    __shared__ int32_t s_cnt[ONE_BLOCK_WAVES][MAX_E];
+    __shared__ int32_t s_off[MAX_E];                  // exclusive scan of the expert totals
+    __shared__ int32_t s_part[MAX_E / 64];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    int32_t my_id[STEPS], my_rank[STEPS];
+#pragma unroll
+    for (int st = 0; st < STEPS; ++st) {
+        const int i = wave * PER_WAVE + st * 64 + lane;
+        my_id[st] = -1;
+        if (i < N) {
+            my_id[st] = id_at(i);
+            if (w_copy) w_copy[i] = w_in[i];
+        }
+    }
+    for (int i = tid; i < ONE_BLOCK_WAVES * MAX_E; i += ONE_BLOCK_WAVES * 64) (&s_cnt[0][0])[i] = 0;
+    __syncthreads();
+    const uint64_t lower = (1ull << lane) - 1ull;
+#pragma unroll
+    for (int st = 0; st < STEPS; ++st) {
+        const int i = wave * PER_WAVE + st * 64 + lane;
+        const int32_t v = my_id[st];
+        if (ids_copy && i < N) ids_copy[i] = v;
+        const bool valid = v >= 0 && v < E;
+        const int key = v & (MAX_E - 1);
+        uint64_t same = __ballot(valid);
+        if (!valid) same = ~same;
+#pragma unroll
+        for (int bit = 0; bit < 8; ++bit) {
+            const uint64_t bal = __ballot((key >> bit) & 1);
+            same &= ((key >> bit) & 1) ? bal : ~bal;
+        }
+        const int before = s_cnt[wave][key];
+        my_rank[st] = before + __popcll(same & lower);
+        if (valid && (same & lower) == 0ull) s_cnt[wave][key] = before + __popcll(same);
+    }
+    __syncthreads();
+    int total = 0, incl = 0;
+    if (tid < MAX_E) {                                // thread e: per-wave bases and the total of expert e
+#pragma unroll
+        for (int w = 0; w < ONE_BLOCK_WAVES; ++w) {
+            const int c = s_cnt[w][tid];
+            s_cnt[w][tid] = total;
+            total += c;
+        }
+        if (tid >= E) total = 0;
+        incl = total;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const int v = __shfl_up(incl, off);
+            incl += lane >= off ? v : 0;
+        }
+        if (lane == 63) s_part[wave] = incl;
+    }
+    __syncthreads();
+    if (tid < MAX_E) {
+        for (int w = 0; w < wave; ++w) incl += s_part[w];
+        s_off[tid] = incl - total;
+        if (tid < E) offsets[tid + 1] = incl;
+        if (tid == 0) offsets[0] = 0;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int st = 0; st < STEPS; ++st) {
+        const int i = wave * PER_WAVE + st * 64 + lane;
+        if (i >= N) continue;
+        const int e = my_id[st];
+        if (e < 0 || e >= E) {
+            flags[0] = 1;
+            inv_perm[i] = -1;
+            continue;
+        }
+        if (check_dups) {
+            const int first = i - i % k;
+            bool dup = false;
+            for (int q = first; q < i; ++q) dup |= id_at(q) == e;
+            if (dup) flags[1] = 1;
+        }
+        const int pos = s_off[e] + s_cnt[wave][e] + my_rank[st];
+        inv_perm[i] = pos;
+        perm[pos] = i;
+    }
+}
+
+}  // namespace moe355

@@ -1,0 +1,43 @@
+// One row's share of the token-order quantisation, for kernels that carry it along in blocks of their own.
+#pragma once
+#include "e4m3.hpp"
+#include "moe_internal.hpp"
+
+namespace moe355 {
+
+// Sixteen lanes own one 128-column group g of row r: each loads 8 bf16 (16 bytes), the group maximum is reduced with four
+// xor-shuffles, the code is quantize.hip's.  All sixteen lanes of a live row call it.
+__device__ inline void quantize_row_group(const token_quant& t, int64_t r, int g, int sub) {
+    const size_t at = (size_t)r * t.cols + (size_t)g * QBLOCK + sub * 8;
+    const u32x4 raw = *reinterpret_cast<const u32x4*>(t.x + at);
+    float amax = bf16x8_amax(raw);
+    amax = fmaxf(amax, __shfl_xor(amax, 1));
+    amax = fmaxf(amax, __shfl_xor(amax, 2));
+    amax = fmaxf(amax, __shfl_xor(amax, 4));
+    amax = fmaxf(amax, __shfl_xor(amax, 8));
+    const E4m3Coder coder((amax == 0.f) ? 1.0f : amax / 448.0f);
+    *reinterpret_cast<u32x2*>(t.q + at) = coder.pack8(raw);
+    if (sub == 0) t.scales[(size_t)g * t.rows + r] = coder.s;
+}
+
+// block `unit` of THREADS threads: TOKEN_QUANT_ROWS rows of THREADS/(16*TOKEN_QUANT_ROWS) groups at a time (scales leave in runs of
+// 32 words)
+constexpr int TOKEN_QUANT_ROWS = 32;
+template <int THREADS, int PASSES>
+__device__ inline void quantize_block(const token_quant& t, uint32_t unit) {
+    constexpr int RPP = TOKEN_QUANT_ROWS / PASSES;             // rows per pass
+    constexpr int GPB = THREADS / 16 / RPP;                    // groups per block
+    const int groups = t.cols / QBLOCK, per_row = (groups + GPB - 1) / GPB;
+    const int g = (int)(unit % per_row) * GPB + (int)(threadIdx.x >> 4) / RPP;
+    const int64_t r0 = (int64_t)(unit / per_row) * TOKEN_QUANT_ROWS + (threadIdx.x >> 4) % RPP;
+#pragma unroll
+    for (int i = 0; i < PASSES; ++i)
+        if (g < groups && r0 + i * RPP < t.rows) quantize_row_group(t, r0 + i * RPP, g, threadIdx.x & 15);
+}
+template <int THREADS, int PASSES>
+inline int64_t quantize_blocks(const token_quant& t) {
+    constexpr int GPB = THREADS / 16 / (TOKEN_QUANT_ROWS / PASSES);
+    return t.x ? (t.rows + TOKEN_QUANT_ROWS - 1) / TOKEN_QUANT_ROWS * ((t.cols / QBLOCK + GPB - 1) / GPB) : 0;
+}
+
+}  // namespace moe355

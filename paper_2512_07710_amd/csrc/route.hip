@@ -18,7 +18,8 @@
 // Those of more than 32 tokens take 32-token tiles whose K loop is split over up to 16 blocks; each block writes its
 // partial logits, and a second kernel (one wave per token) adds them up in split order and does
 // the same selection with wave-wide reductions.  Up to 32 tokens the partial logits come from the vector ALU (route_rows_kernel).
-#include "moe_internal.hpp"
+#include "permute_block.hpp"
+#include "quantize_rows.hpp"
 
 #include <type_traits>
 
@@ -546,14 +547,11 @@ __global__ __launch_bounds__(256) void route_rows_kernel(const uint16_t* __restr
 // A round is the wave's largest score, by lane shifts, and the lowest expert that has it, by ballots: both stay on the
 // vector and scalar units.  (Twelve LDS-routed shuffles a round, and two more per slot in the softmax, made this chain 9.3 us
 // for one token of k = 6 and 12.7 for sixteen of k = 8 over 256 experts; it takes 5.6 and 8.8.)
+struct Choice { int id; float w; };                            // lane j < k: slot j of the token
 template <bool IDS>
-__global__ __launch_bounds__(256) void route_finish_kernel(const float* __restrict__ partial, int splits, int T_pad,
-                                                           int E_pad, const float* __restrict__ bias,
-                                                           const int32_t* __restrict__ logged_idx, int T, int E, int k,
-                                                           int32_t* __restrict__ topk_idx, float* __restrict__ topk_w) {
-    const int lane = threadIdx.x & 63;
-    const int t = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    if (t >= T) return;                                        // wave-uniform
+__device__ inline Choice finish_token(const float* __restrict__ partial, int splits, int T_pad, int E_pad,
+                                      const float* __restrict__ bias, const int32_t* __restrict__ logged_idx, int t, int lane, int E,
+                                      int k) {
     int id = NO_CAND;                                          // lane j < k: the j-th selected expert
     if (IDS && lane < k) id = logged_idx[(size_t)t * k + lane];
     float lg[4], sc[4];
@@ -606,10 +604,49 @@ __global__ __launch_bounds__(256) void route_finish_kernel(const float* __restri
     const float ex = expf(sel - m);
     float sum = 0.f;
     for (int j = 0; j < k; ++j) sum += lane_value(ex, j);
+    return Choice{id, ex / sum};
+}
+
+template <bool IDS>
+__global__ __launch_bounds__(256) void route_finish_kernel(const float* __restrict__ partial, int splits, int T_pad,
+                                                           int E_pad, const float* __restrict__ bias,
+                                                           const int32_t* __restrict__ logged_idx, int T, int E, int k,
+                                                           int32_t* __restrict__ topk_idx, float* __restrict__ topk_w) {
+    const int lane = threadIdx.x & 63;
+    const int t = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    if (t >= T) return;                                        // wave-uniform
+    const Choice c = finish_token<IDS>(partial, splits, T_pad, E_pad, bias, logged_idx, t, lane, E, k);
     if (lane < k) {
-        topk_idx[(size_t)t * k + lane] = id;
-        topk_w[(size_t)t * k + lane] = ex / sum;
+        topk_idx[(size_t)t * k + lane] = c.id;
+        topk_w[(size_t)t * k + lane] = c.w;
     }
+}
+
+// The same for at most one token a wave of one block, which then permutes the assignments it has just made; the tokens'
+// quantisation may come along in further blocks.  One token x 64 experts: 4.9 us and a launch of 2.7 for the permutation alone.
+template <bool IDS>
+__global__ __launch_bounds__(ONE_BLOCK_WAVES * 64) void route_finish_permute(
+    const float* __restrict__ partial, int splits, int T_pad, int E_pad, const float* __restrict__ bias,
+    const int32_t* __restrict__ logged_idx, int T, int E, int k, int32_t* __restrict__ topk_idx, float* __restrict__ topk_w,
+    int32_t* __restrict__ offsets, int32_t* __restrict__ perm, int32_t* __restrict__ inv_perm, int32_t* __restrict__ flags,
+    token_quant tokens) {
+    if (blockIdx.x > 0) {
+        quantize_block<ONE_BLOCK_WAVES * 64, 1>(tokens, blockIdx.x - 1);
+        return;
+    }
+    __shared__ int32_t s_ids[ONE_BLOCK_WAVES * MAX_K];
+    const int lane = threadIdx.x & 63;
+    const int t = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    if (t < T) {
+        const Choice c = finish_token<IDS>(partial, splits, T_pad, E_pad, bias, logged_idx, t, lane, E, k);
+        if (lane < k) {
+            s_ids[t * k + lane] = c.id;
+            topk_idx[(size_t)t * k + lane] = c.id;
+            topk_w[(size_t)t * k + lane] = c.w;
+        }
+    }
+    __syncthreads();
+    permute_block<1>([&](int i) { return s_ids[i]; }, T * k, E, nullptr, nullptr, nullptr, offsets, perm, inv_perm, k, IDS, flags);
 }
 
 }  // namespace
@@ -633,13 +670,28 @@ size_t route_partial_bytes(int T, int E) {
     return (size_t)route_splits_for(T) * T_pad * E_pad * sizeof(float);
 }
 
-hipError_t launch_route(moe_ctx* c, const uint16_t* x, const float* W_r, const float* bias,
-                        const int32_t* logged_idx, int32_t* topk_idx, float* topk_w) {
+hipError_t launch_route(moe_ctx* c, const uint16_t* x, const float* W_r, const float* bias, const int32_t* logged_idx,
+                        int32_t* topk_idx, float* topk_w, int32_t* offsets, int32_t* perm, int32_t* inv_perm,
+                        const token_quant& tokens) {
     const moe_dims& D = c->dims;
     if (D.T == 0) return hipSuccess;
+    auto permute = [&]() {
+        return launch_permute(permute_args_of(c, logged_idx != nullptr), topk_idx, nullptr, nullptr, nullptr, offsets, perm, inv_perm,
+                              tokens);
+    };
     const int E_pad = D.E <= 128 ? 128 : 256;
-    // route_finish over `splits` partial logits per token and expert
+    // route_finish over `splits` partial logits per token and expert, and the permutation
     auto finish = [&](int splits, int T_pad) {
+        if (D.T <= ONE_BLOCK_WAVES) {
+            const dim3 grid((unsigned)(1 + quantize_blocks<ONE_BLOCK_WAVES * 64, 1>(tokens)));
+            auto launch = [&](auto kernel) {
+                hipLaunchKernelGGL(kernel, grid, dim3(ONE_BLOCK_WAVES * 64), 0, c->stream, c->route_partial, splits, T_pad, E_pad,
+                                   logged_idx ? nullptr : bias, logged_idx, D.T, D.E, D.k, topk_idx, topk_w, offsets, perm, inv_perm,
+                                   c->flags, tokens);
+                return hipGetLastError();
+            };
+            return logged_idx ? launch(route_finish_permute<true>) : launch(route_finish_permute<false>);
+        }
         const dim3 fgrid((D.T + 3) / 4);
         if (logged_idx)
             hipLaunchKernelGGL(route_finish_kernel<true>, fgrid, dim3(256), 0, c->stream, c->route_partial, splits, T_pad, E_pad,
@@ -647,7 +699,8 @@ hipError_t launch_route(moe_ctx* c, const uint16_t* x, const float* W_r, const f
         else
             hipLaunchKernelGGL(route_finish_kernel<false>, fgrid, dim3(256), 0, c->stream, c->route_partial, splits, T_pad, E_pad,
                                bias, logged_idx, D.T, D.E, D.k, topk_idx, topk_w);
-        return hipGetLastError();
+        const hipError_t e = hipGetLastError();
+        return e == hipSuccess ? permute() : e;
     };
     const int slices = (D.d + ROWS_COLS - 1) / ROWS_COLS;
     const int rows_max = D.d == 128 && E_pad == 128 ? ROUTE_ROWS_ONE_CHUNK_MAX_T : ROUTE_ROWS_MAX_T;
@@ -696,7 +749,8 @@ hipError_t launch_route(moe_ctx* c, const uint16_t* x, const float* W_r, const f
     }
 #undef MOE_ROUTE_TS
 #undef MOE_ROUTE_LAUNCH
-    return hipGetLastError();
+    const hipError_t e = hipGetLastError();
+    return e == hipSuccess ? permute() : e;
 }
 
 }  // namespace moe355

@@ -90,13 +90,18 @@ class MoELayer:
     # ---- whole layer ----------------------------------------------------------------
     # `fused` = True: activations quantised once per token, gathered inside the gate/up GEMM;
     # False: the expert-ordered copy xq/xs is materialised first (same results bit for bit)
+    def _ffn_gather(self, w):
+        self.expert_ffn_gather(w)
+        self.combine()
+        return self.y
+
     def _ffn(self, x, w, fused):
+        """What follows a routing call of its own."""
         if fused:
             self.quantize_tokens(x)
-            self.expert_ffn_gather(w)
-        else:
-            self.quantize(x)
-            self.expert_ffn(w)
+            return self._ffn_gather(w)
+        self.quantize(x)
+        self.expert_ffn(w)
         self.combine()
         return self.y
 
@@ -107,15 +112,17 @@ class MoELayer:
 
     def _ffn_after_side(self, w):
         self.stream.wait_stream(self.side_stream)
-        self.expert_ffn_gather(w)
-        self.combine()
-        return self.y
+        return self._ffn_gather(w)
 
     def forward_routed(self, x, W_r, sel_bias, w, fused=True):
         if fused is True and self.overlap_quantize:
             self._quantize_tokens_beside(x)
             self.route(x, W_r, sel_bias)
             return self._ffn_after_side(w)
+        if fused:
+            B.moe_route_quantize(self.ctx, x, W_r, sel_bias, self.k, self.topk_idx, self.topk_w, self.offsets, self.perm,
+                                 self.inv_perm, self.xq_tok, self.xs_tok)
+            return self._ffn_gather(w)
         self.route(x, W_r, sel_bias)
         return self._ffn(x, w, fused)
 
@@ -124,6 +131,10 @@ class MoELayer:
             self._quantize_tokens_beside(x)
             self.route_replay(x, logged_idx, logged_w)
             return self._ffn_after_side(w)
+        if fused:
+            B.moe_route_replay_quantize(self.ctx, x, logged_idx, logged_w, self.topk_idx, self.topk_w, self.offsets,
+                                        self.perm, self.inv_perm, self.xq_tok, self.xs_tok)
+            return self._ffn_gather(w)
         self.route_replay(x, logged_idx, logged_w)
         return self._ffn(x, w, fused)
 

@@ -281,3 +281,73 @@ def test_layer_of_a_small_batch_has_the_bits_of_a_large_one(gpu_lib, T, d, E, k,
         layer.close()
     for a, b in zip(*out):
         assert torch.equal(a, b)
+
+
+# --------------------------------------------------------------------------- quantisation in the permutation's launches
+# one block beside the router's last step (T <= 16), one block of its own, three launches; a row more and less than 32
+@pytest.mark.parametrize("T,d,E,k", [(1, 128, 8, 2), (16, 1152, 200, 16), (16, 128, 130, 3), (17, 640, 16, 4), (31, 2176, 60, 5),
+                                     (33, 128, 5, 1), (700, 384, 256, 6), (2100, 896, 64, 8)])
+def test_routing_with_quantisation_is_the_two_calls(gpu_lib, T, d, E, k):
+    """Routed and replayed: ids, weights, permutation, codes and scales of the joint call against the separate ones, bit for bit; the
+    quantised arrays are written to their ends and not beyond."""
+    g = torch.Generator(device="cuda").manual_seed(T + d)
+    x = torch.randn((T, d), generator=g, device="cuda").to(torch.bfloat16)
+    W_r = torch.randn((E, d), generator=g, device="cuda") * d ** -0.5
+    bias = torch.randn((E,), generator=g, device="cuda")
+    log = torch.rand((T, E), generator=g, device="cuda").topk(k, dim=1).indices.to(torch.int32).contiguous()
+    log_w = torch.rand((T, k), generator=g, device="cuda")
+    log[T // 2, 0] = E + 3                                    # reported by both, skipped by both
+    ctx = gpu_lib.moe_create(T, d, E, k, 128)
+
+    def outputs():
+        i32 = dict(dtype=torch.int32, device="cuda")
+        return [torch.full((T, k), -7, **i32), torch.full((T, k), -7.0, device="cuda"), torch.full((E + 1,), -7, **i32),
+                torch.full((T * k,), -7, **i32), torch.full((T * k,), -7, **i32)]
+
+    def codes():
+        return torch.full((T * d + 64,), 0x55, dtype=torch.uint8, device="cuda"), torch.full((T * d // 128 + 16,), -7.0, device="cuda")
+    try:
+        for routed in (True, False):
+            a, b, (qa, sa), (qb, sb) = outputs(), outputs(), codes(), codes()
+            if routed:
+                gpu_lib.moe_route(ctx, x, W_r, bias, k, *a)
+                gpu_lib.moe_quantize_fp8(ctx, x, T, d, 128, None, 1, qa, sa)
+                gpu_lib.moe_route_quantize(ctx, x, W_r, bias, k, *b, qb, sb)
+                assert gpu_lib.moe_check_ids(ctx) == 0
+            else:
+                gpu_lib.moe_route_replay(ctx, x, log, log_w, *a)
+                assert gpu_lib.moe_check_ids(ctx) != 0
+                gpu_lib.moe_quantize_fp8(ctx, x, T, d, 128, None, 1, qa, sa)
+                gpu_lib.moe_route_replay_quantize(ctx, x, log, log_w, *b, qb, sb)
+                assert gpu_lib.moe_check_ids(ctx) != 0
+            for u, v in zip(a + [qa, sa], b + [qb, sb]):
+                assert torch.equal(u, v)
+            assert (qb[T * d:] == 0x55).all() and (sb[T * d // 128:] == -7.0).all()
+    finally:
+        gpu_lib.moe_destroy(ctx)
+
+
+@pytest.mark.parametrize("T,d,E,k", [(1, 256, 8, 2), (16, 640, 256, 16), (13, 1152, 60, 5)])
+def test_one_block_router_permutes_as_the_log_does(gpu_lib, T, d, E, k):
+    """Up to 16 tokens the router's last block permutes: against the replay of its own log, which permutes in a launch of its own; ids-only
+    replay of that log gives the same weights, and a repeated id is reported."""
+    g = torch.Generator(device="cuda").manual_seed(T + d)
+    x = torch.randn((T, d), generator=g, device="cuda").to(torch.bfloat16)
+    W_r = torch.randn((E, d), generator=g, device="cuda") * d ** -0.5
+    ctx = gpu_lib.moe_create(T, d, E, k, 128)
+    new = lambda: [torch.empty((T, k), dtype=torch.int32, device="cuda"), torch.empty((T, k), device="cuda"),
+                   *(torch.full((n,), -7, dtype=torch.int32, device="cuda") for n in (E + 1, T * k, T * k))]
+    try:
+        a, b, c = new(), new(), new()
+        gpu_lib.moe_route(ctx, x, W_r, None, k, *a)
+        gpu_lib.moe_route_replay(ctx, x, a[0], a[1], *b)
+        gpu_lib.moe_route_replay_ids(ctx, x, W_r, a[0], *c)
+        assert gpu_lib.moe_check_ids(ctx) == 0
+        for u, v, w in zip(a, b, c):
+            assert torch.equal(u, v) and torch.equal(u, w)
+        twice = a[0].clone()
+        twice[T - 1, k - 1] = twice[T - 1, 0]
+        gpu_lib.moe_route_replay_ids(ctx, x, W_r, twice, *c)
+        assert gpu_lib.moe_check_ids(ctx) != 0
+    finally:
+        gpu_lib.moe_destroy(ctx)
