@@ -74,41 +74,99 @@ __device__ inline void split_rows(int rows, int nt, int i, Work& w) {
     w.tiles = (int16_t)min(nt, MANY_TILES);
 }
 
+// ------------------------------------------------------------------ tile heights
+// 256 rows are the most a tile can have, but not always the best: units come in rounds of one a CU, and a round that is a
+// quarter full takes nearly as long as a full one.  16 experts of 750 rows x 3072 x 2048 make 3.25 rounds of tiles of up to 256 rows,
+// 178 us, and 4 full ones of shorter tiles, 160.  The cost of `units` units in K steps of a 10-row-group tile (a step costs 0.2 + 0.1 n at
+// n groups of 32 rows, what lies between two tiles 4 steps, a started round 0.7 of a full one) was fitted to 27 layers of 130 to 1100
+// rows per expert, both projections, heights 96 to 256: the height it picks is 0.2 % above the best of them on average, always
+// taking 256 5.7 %.
+constexpr int HEIGHTS = 5;                          // 256, 224, 192, 160, 128
+__host__ __device__ constexpr int tile_height(int j) { return TOK_TILE - 32 * j; }
+__host__ __device__ inline float tiles_cost(int64_t units, float groups_per_tile, int nkb) {
+    const int64_t full = units / 256, rest = units % 256;
+    const float rounds = (float)full + (rest ? 0.7f + 0.3f / 256.0f * (float)rest : 0.0f);
+    return rounds * (4.0f + (float)nkb * (0.2f + 0.1f * groups_per_tile));
+}
+// the best of the heights that need at most `capacity` units (256 needs no asking)
+__host__ __device__ inline int pick_height(const int (&tiles)[HEIGHTS], int groups, int n_ft, int nkb, int64_t capacity) {
+    int best = 0;
+    float least = 0.0f;
+    for (int j = 0; j < HEIGHTS && tiles[0] > 0; ++j) {
+        const int64_t units = (int64_t)tiles[j] * n_ft;
+        if (j > 0 && units > capacity) break;
+        const float c = tiles_cost(units, (float)groups / (float)tiles[j], nkb);
+        if (j == 0 || c < least) {
+            least = c;
+            best = j;
+        }
+    }
+    return tile_height(best);
+}
+
 // ------------------------------------------------------------------ work list
-// An expert with c rows gets ceil(c/256) row tiles, ordered (expert, feature tile, row tile).  Units
+// An expert with c rows gets ceil(c/h) row tiles, h the launch's tile height, ordered (expert, feature tile, row tile).  Units
 // that share a weight tile are thus neighbours and, when they do the same amount of work, the blocks
 // that run them side by side on one XCD advance in step and hit each other's lines in that XCD's L2
 // (a few K steps of skew already exceed what the L2 retains, and the shared tile is then fetched
 // again from HBM).
-// Block (e, l) writes the units of expert e into list l (0: gate/up, n_ft0 feature tiles; 1: down,
-// n_ft1 feature tiles); every block recomputes the tile counts of all experts for its base index.
+// inclusive prefix sum over the wave, by lane shifts
+template <int CTRL, int ROWS>
+__device__ inline int from_lanes(int v) { return __builtin_amdgcn_update_dpp(0, v, CTRL, ROWS, 0xf, false); }
+__device__ inline int wave_scan(int v) {
+    v += from_lanes<0x111, 0xf>(v);                            // row_shr 1, 2, 4, 8: rows of 16 lanes
+    v += from_lanes<0x112, 0xf>(v);
+    v += from_lanes<0x114, 0xf>(v);
+    v += from_lanes<0x118, 0xf>(v);
+    v += from_lanes<0x142, 0xa>(v);                            // row_bcast 15, 31: over the rows
+    v += from_lanes<0x143, 0xc>(v);
+    return v;
+}
+// One list for each projection: its feature tiles, K blocks and room.
+struct ListShape { int n_ft, nkb, capacity; bool one_height; };
+// Block (e, l) writes the units of expert e into list l (0: gate/up, 1: down); every block recomputes the tile counts of all
+// experts for its base index and the height.
 // choose: list 1 is left empty (n_work[1] = 0) unless the batch is concentrated, see DOWN_SKEW_UNITS.
-__device__ inline void build_work(const int32_t* __restrict__ offsets, int E, int e, int list, int n_ft0, int n_ft1, bool choose,
-                                  Work* __restrict__ work0, Work* __restrict__ work1, int32_t* __restrict__ n_work) {
-    __shared__ int32_t s_tiles[MAX_E], s_small[MAX_E / 64];
-    const int tid = threadIdx.x;
-    const int n_ft = list == 0 ? n_ft0 : n_ft1;
-    Work* const work = list == 0 ? work0 : work1;
+__device__ inline void build_work(const int32_t* __restrict__ offsets, int E, int e, int list, const ListShape& shape, bool choose,
+                                  Work* __restrict__ work, int32_t* __restrict__ n_work) {
+    constexpr int SUMS = HEIGHTS + 2, WAVES = MAX_E / 64;      // tiles at each height, groups of 32 rows, tiles of 64
+    __shared__ int32_t s_sums[WAVES][SUMS], s_scan[WAVES], s_base;
+    const int tid = threadIdx.x, wave = tid >> 6;
+    const int n_ft = shape.n_ft;
     const int rows_t = tid < E ? offsets[tid + 1] - offsets[tid] : 0;
-    s_tiles[tid] = (rows_t + TOK_TILE - 1) / TOK_TILE;
-    int small = (rows_t + STREAM_ROWS - 1) / STREAM_ROWS;
 #pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) small += __shfl_xor(small, m);
-    if ((tid & 63) == 0) s_small[tid >> 6] = small;
-    __syncthreads();
-    for (int off = 1; off < MAX_E; off <<= 1) {            // inclusive scan
-        const int a = (tid >= off) ? s_tiles[tid - off] : 0;
-        __syncthreads();
-        s_tiles[tid] += a;
-        __syncthreads();
+    for (int j = 0; j < SUMS; ++j) {
+        if (shape.one_height && j > 0 && j <= HEIGHTS) continue;
+        const int h = j < HEIGHTS ? tile_height(j) : j == HEIGHTS ? 32 : STREAM_ROWS;
+        const int sum = wave_scan((rows_t + h - 1) / h);
+        if ((tid & 63) == 63) s_sums[wave][j] = sum;
     }
-    const bool empty = choose && list == 1 && s_small[0] + s_small[1] + s_small[2] + s_small[3] <= 2 * s_tiles[MAX_E - 1];
-    if (e == 0 && tid == 0) n_work[list] = empty ? 0 : s_tiles[MAX_E - 1] * n_ft;
+    __syncthreads();
+    int sums[SUMS], tiles[HEIGHTS];
+#pragma unroll
+    for (int j = 0; j < SUMS; ++j) sums[j] = s_sums[0][j] + s_sums[1][j] + s_sums[2][j] + s_sums[3][j];
+#pragma unroll
+    for (int j = 0; j < HEIGHTS; ++j) tiles[j] = sums[j];
+    const int h = shape.one_height ? TOK_TILE : pick_height(tiles, sums[HEIGHTS], n_ft, shape.nkb, shape.capacity);
+    int total = tiles[0];                                      // at the chosen height
+#pragma unroll
+    for (int j = 1; j < HEIGHTS; ++j) total = h == tile_height(j) ? tiles[j] : total;
+    const bool empty = choose && list == 1 && sums[HEIGHTS + 1] <= 2 * tiles[0];
+    if (e == 0 && tid == 0) n_work[list] = empty ? 0 : total * n_ft;
     if (empty) return;
+    const int before = wave_scan((rows_t + h - 1) / h);        // tiles up to expert tid, in its wave
+    if ((tid & 63) == 63) s_scan[wave] = before;
+    __syncthreads();
+    if (tid == e) {
+        int base = before - (rows_t + h - 1) / h;
+        for (int w = 0; w < wave; ++w) base += s_scan[w];
+        s_base = base;
+    }
+    __syncthreads();
     const int start = offsets[e], cnt = offsets[e + 1] - start;
-    const int nt = (cnt + TOK_TILE - 1) / TOK_TILE;
+    const int nt = (cnt + h - 1) / h;
     if (nt == 0) return;
-    const int base = (s_tiles[e] - nt) * n_ft;
+    const int base = s_base * n_ft;
     for (int idx = tid; idx < nt * n_ft; idx += 256) {
         const int f = idx / nt, i = idx - f * nt;
         Work w;
@@ -415,8 +473,8 @@ __global__ __launch_bounds__(NTHREADS, 1) void ffn_gemm(const uint8_t* __restric
     float* const s_amax = reinterpret_cast<float*>(smem);
 
     // ---- which work unit: XCD x (= blockIdx % 8) walks the contiguous range [x*chunk, (x+1)*chunk)
-    // (LINEAR: one "expert" owns all n_rows rows, and the unit is worked out here instead of read from a list)
-    const int tiles = (n_rows + TOK_TILE - 1) / TOK_TILE;
+    // (LINEAR: one "expert" owns all n_rows rows in `fan` row tiles, and the unit is worked out here instead of read from a list)
+    const int tiles = fan;
     const int total = LINEAR ? tiles * ((NOUT + FT - 1) / FT) : *n_work;
     const int chunk = (total + NXCD - 1) / NXCD;
     const int slot = blockIdx.x / NXCD;
@@ -817,19 +875,40 @@ static bool linear_streams(int32_t rows, int32_t NOUT) {
     return rows <= STREAM_ROWS || (int64_t)((rows + TOK_TILE - 1) / TOK_TILE) * ((NOUT + 255) / 256) <= LINEAR_STREAM_TILES;
 }
 
+static int linear_tiles(int32_t rows, int nft, int nkb) {
+    int tiles[HEIGHTS];
+    for (int j = 0; j < HEIGHTS; ++j) tiles[j] = (int)(((int64_t)rows + tile_height(j) - 1) / tile_height(j));
+    const int h = pick_height(tiles, (int)(((int64_t)rows + 31) / 32), nft, nkb, (int64_t)1 << 30);
+    return (int)(((int64_t)rows + h - 1) / h);
+}
+
 // upper bound on row tiles: every full tile, and one more for each expert that has rows
 static int64_t max_row_tiles(const moe_dims* D, int rows) {
     const int64_t N = (int64_t)D->T * D->k;
     return N / rows + (N < D->E ? N : D->E);
 }
+// Room of a big-tile list, and blocks of its launch: the least height that can be the better one has to fit.  A first round that is
+// not full may gain from half the height; the more rounds, the less there is to gain, and blocks without a unit are not free either
+// (nor is the choice: 777 tokens x 5 of 60 experts 1.3 us, 256 x 6 of 64 0.8): experts with a mean of up to 96 rows are one tile each
+// whatever the height, but for a few of a skewed load.
+constexpr int64_t ONE_HEIGHT_ROWS = 96;
+static bool one_height(const moe_dims* D) { return (int64_t)D->T * D->k <= ONE_HEIGHT_ROWS * D->E; }
+static int64_t big_units(const moe_dims* D, int nft) {
+    const int64_t units = max_row_tiles(D, TOK_TILE) * nft, half = max_row_tiles(D, TOK_TILE / 2) * nft;
+    if (one_height(D)) return units;
+    if (half <= 2 * CUS) return half;
+    return units <= 8 * CUS ? max_row_tiles(D, 192) * nft : units <= 16 * CUS ? max_row_tiles(D, 224) * nft : units;
+}
 static int64_t gate_up_units(const moe_dims* D) {
-    return max_row_tiles(D, gate_up_few(D) ? FEW_ROWS : gate_up_streams(D) ? STREAM_ROWS : TOK_TILE) * (D->F / 128);
+    if (!gate_up_streams(D)) return big_units(D, D->F / 128);
+    return max_row_tiles(D, gate_up_few(D) ? FEW_ROWS : STREAM_ROWS) * (D->F / 128);
 }
 static int64_t down_stream_units(const moe_dims* D) { return max_row_tiles(D, STREAM_ROWS) * ((D->d + 255) / 256); }
 // EITHER: S > 2B tiles of 64 / of 256 rows over m experts with rows (B >= m, S <= (N + 63m)/64) leave m <= N/65
 static int64_t down_big_units(const moe_dims* D) {
     const int64_t N = (int64_t)D->T * D->k;
-    return (down_form(D) == Down::EITHER ? N / TOK_TILE + N / 65 : max_row_tiles(D, TOK_TILE)) * ((D->d + 255) / 256);
+    const int nft = (D->d + 255) / 256;
+    return down_form(D) == Down::EITHER ? (N / TOK_TILE + N / 65) * nft : big_units(D, nft);
 }
 
 // length of the gate/up projection's work list, behind which the down projection's lies; and room for both
@@ -863,13 +942,14 @@ static hipError_t set_lds_limits() {
 // What the big tiles need before they start, in one launch (two took 2..3 us more of every layer): the work lists (blocks
 // 0 .. E*lists-1) and, with perm, the scales of the expert-sorted rows from the per-token scales:
 // out[g][p] = in[g][perm[p] / fan].
-__global__ __launch_bounds__(256) void prepare_big_tiles(const int32_t* __restrict__ offsets, int E, int lists, int n_ft0,
-                                                         int n_ft1, bool choose, Work* __restrict__ work0, Work* __restrict__ work1,
-                                                         int32_t* __restrict__ n_work, const float* __restrict__ in, int T,
-                                                         const int32_t* __restrict__ perm, int fan, int N,
-                                                         float* __restrict__ out) {
+__global__ __launch_bounds__(256) void prepare_big_tiles(const int32_t* __restrict__ offsets, int E, int lists, ListShape shape0,
+                                                         ListShape shape1, bool choose, Work* __restrict__ work0,
+                                                         Work* __restrict__ work1, int32_t* __restrict__ n_work,
+                                                         const float* __restrict__ in, int T, const int32_t* __restrict__ perm,
+                                                         int fan, int N, float* __restrict__ out) {
     if ((int)blockIdx.x < E * lists) {
-        build_work(offsets, E, blockIdx.x % E, blockIdx.x / E, n_ft0, n_ft1, choose, work0, work1, n_work);
+        const int list = blockIdx.x / E;
+        build_work(offsets, E, blockIdx.x % E, list, list == 0 ? shape0 : shape1, choose, list == 0 ? work0 : work1, n_work);
         return;
     }
     const uint32_t b = blockIdx.x - E * lists, row_blocks = (uint32_t)((N + 255) / 256);
@@ -905,7 +985,9 @@ hipError_t launch_expert_ffn(moe_ctx* c, const uint8_t* xq, const float* xs, con
         const int lists = down == Down::STREAM ? 1 : 2;
         const int64_t gather = perm ? (int64_t)((N + 255) / 256) * (D.d / QBLOCK) : 0;
         hipLaunchKernelGGL(prepare_big_tiles, dim3((unsigned)(D.E * lists + gather)), dim3(256), 0, c->stream, offsets, D.E, lists,
-                           nft1, nft2, down == Down::EITHER, work, work2, c->n_tiles, xs, D.T, perm, D.k, N, c->xs_sorted);
+                           ListShape{nft1, D.d / KB, units1, one_height(&D)},
+                           ListShape{nft2, D.F / KB, (int)down_big_units(&D), one_height(&D)}, down == Down::EITHER,
+                           work, work2, c->n_tiles, xs, D.T, perm, D.k, N, c->xs_sorted);
     }
     if (ev) (void)hipEventRecord(ev[0], c->stream);          // the timed interval is the GEMM kernel alone
     const int grid1 = (units1 + NXCD - 1) / NXCD * NXCD;
@@ -949,9 +1031,9 @@ hipError_t launch_linear(moe_ctx* c, const uint8_t* xq, const float* xs, int32_t
     if (ea != hipSuccess) return ea;
     if (few_linear_groups(rows, NOUT)) return launch_few_linear(c, xq, xs, rows, K, Wq, ws, NOUT, y);
     if (linear_streams(rows, NOUT)) return launch_stream_linear(c, xq, xs, rows, K, Wq, ws, NOUT, y);
-    const int units = (rows + TOK_TILE - 1) / TOK_TILE * ((NOUT + 255) / 256);
-    hipLaunchKernelGGL((ffn_gemm<false, false, true>), dim3((units + NXCD - 1) / NXCD * NXCD), dim3(NTHREADS), SMEM_BYTES,
-                       c->stream, xq, xs, rows, (const int32_t*)nullptr, 1, 1, (const Work*)nullptr,
+    const int nft = (NOUT + 255) / 256, tiles = linear_tiles(rows, nft, K / KB);
+    hipLaunchKernelGGL((ffn_gemm<false, false, true>), dim3((tiles * nft + NXCD - 1) / NXCD * NXCD), dim3(NTHREADS), SMEM_BYTES,
+                       c->stream, xq, xs, rows, (const int32_t*)nullptr, tiles, 1, (const Work*)nullptr,
                        (const int32_t*)nullptr, Wq, (const uint8_t*)nullptr, ws, (const float*)nullptr, K, NOUT,
                        (uint8_t*)nullptr, (float*)nullptr, y);
     return hipGetLastError();
