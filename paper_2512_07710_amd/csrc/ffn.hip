@@ -824,8 +824,9 @@ constexpr size_t SMEM_BYTES = NW_BUF * W_TILE + NX_BUF * X_TILE;   // 160 KiB
 //            193, 40: 211 / 209, 64 level to 7 % slower; 128 x 2048 x 768 24: 51 / 48, 40: 55 / 52; 16 x 3072 x 2048 40: 24.8 / 25.4;
 //            256 x 7168 x 2048 12: 668 / 639, 24: 709 / 697, 30: 705 / 715, 40: 736 / 762.  The widest layers cross at 27 rows, but
 //            only with even loads: Zipf loads at a mean of 12..48 rows 638 / 624 to 931 / 887 there
-//   linear   (K = 4096) 16 rows x 1024 features 28 / 13, 256 x 8192 48 / 22, 256 x 24576 50 / 45, 128 x 32768 36 / 31; at 128
-//            big tiles level (512 x 16384 53.6 / 53.8, 1024 x 8192 55.7 / 56.0); 256 of more than 64 rows (128 x 65536): 69 / 80
+//   linear   by streaming units, big tiles of the chosen height / streaming (more than 64 rows; K = 1024 and 7168 cross at the same
+//            place): 128 units 512 x 4096 x 4096 27.4 / 17.4, 256 512 x 8192 35.0 / 31.5, 1000 x 4096 29.2 / 24.3, 2000 x 2048 29.2 / 24.7;
+//            320 320 x 16384 35.9 / 44.8, 352 1400 x 4096 30.7 / 36.2, 512 1000 x 8192 39.6 / 57.1, 704 700 x 16384 47.9 / 78.6
 constexpr int64_t GATE_UP_STREAM_ROWS = 8, GATE_UP_STREAM_ROWS_IDLE = 32, DOWN_STREAM_ROWS = 48;
 // Rows per expert are a mean.  A skewed load is no reason against streaming (down projection, Zipf loads at a mean of 6..48: 0.73..0.99
 // of the big tiles' time; nine tokens in ten on the same k experts: 0.70..0.97), but a concentrated one is: with every token on the same
@@ -837,7 +838,7 @@ constexpr int64_t GATE_UP_STREAM_ROWS = 8, GATE_UP_STREAM_ROWS_IDLE = 32, DOWN_S
 // (an ordinary load has 1.0..1.55 times as many, a concentrated one of that size 2.5..4) fill the big tiles' list, otherwise it
 // stays empty; both kernels are launched and the one that has nothing to do returns.
 constexpr int64_t GATE_UP_SKEW_UNITS = 256, DOWN_SKEW_UNITS = 512;
-constexpr int CUS = 256, LINEAR_STREAM_TILES = 128;
+constexpr int CUS = 256, LINEAR_STREAM_UNITS = 256;
 
 static bool skew_is_harmless(const moe_dims* D, int feature_tiles, int64_t most_units) {
     const int64_t tiles = (D->T + STREAM_ROWS - 1) / STREAM_ROWS;
@@ -872,7 +873,7 @@ static bool down_few(const moe_dims* D) {
     return D->T <= FEW_ROWS && down_form(D) == Down::STREAM && (D->F >= 1280 || experts_met(D) * (D->d / 32) <= 1400);
 }
 static bool linear_streams(int32_t rows, int32_t NOUT) {
-    return rows <= STREAM_ROWS || (int64_t)((rows + TOK_TILE - 1) / TOK_TILE) * ((NOUT + 255) / 256) <= LINEAR_STREAM_TILES;
+    return rows <= STREAM_ROWS || ((int64_t)rows + STREAM_ROWS - 1) / STREAM_ROWS * ((NOUT + 255) / 256) <= LINEAR_STREAM_UNITS;
 }
 
 static int linear_tiles(int32_t rows, int nft, int nkb) {

@@ -351,3 +351,25 @@ def test_one_block_router_permutes_as_the_log_does(gpu_lib, T, d, E, k):
         assert gpu_lib.moe_check_ids(ctx) != 0
     finally:
         gpu_lib.moe_destroy(ctx)
+
+
+# 255 and 260 units of 64 rows x 256 features: the streaming kernel, and big tiles of the height that fills a round; one short row tile
+@pytest.mark.parametrize("rows,K,NOUT", [(300, 384, 51 * 256), (300, 384, 52 * 256), (300, 640, 52 * 256 - 128), (65, 256, 131 * 256)])
+def test_linear_either_side_of_the_streaming_line(gpu_lib, rows, K, NOUT):
+    """The same bits as in calls of 64 rows, which stream."""
+    g = torch.Generator(device="cuda").manual_seed(rows + NOUT)
+    xq, wq = _codes(g, rows, K), _codes(g, NOUT, K)
+    xs = torch.rand((K // 128, rows), generator=g, device="cuda") + 0.5
+    ws = torch.rand((NOUT // 128, K // 128), generator=g, device="cuda") + 0.5
+    ctx = gpu_lib.moe_create(rows, K, 1, 1, NOUT)
+    try:
+        y = torch.full((rows + 1, NOUT), float("nan"), device="cuda")
+        gpu_lib.moe_linear_fp8(ctx, xq, xs, rows, K, wq, ws, NOUT, y)
+        part = torch.empty((64, NOUT), device="cuda")
+        for r in range(0, rows, 64):
+            n = min(64, rows - r)
+            gpu_lib.moe_linear_fp8(ctx, xq[r:r + n], xs[:, r:r + n].contiguous(), n, K, wq, ws, NOUT, part)
+            assert torch.equal(y[r:r + n], part[:n]), r
+        assert torch.isnan(y[rows]).all()
+    finally:
+        gpu_lib.moe_destroy(ctx)
