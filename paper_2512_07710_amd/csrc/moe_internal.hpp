@@ -10,7 +10,7 @@ constexpr int QBLOCK = 128;        // quantisation group (activations 1x128, wei
 constexpr int PERM_CHUNK = 2048;   // assignments handled by one block of the permutation kernels
 constexpr int TOK_TILE = 256;      // expert-sorted rows per GEMM tile
 constexpr int STREAM_ROWS = 64;    // expert-sorted rows per tile of the weight-streaming GEMMs
-constexpr int FEW_ROWS = 16;       // expert-sorted rows per tile of the split-K GEMMs
+constexpr int FEW_ROWS = 16;       // expert-sorted rows per tile of the small-block GEMMs
 constexpr int MAX_E = 256;
 constexpr int MAX_K = 16;
 constexpr int PROF_MAX_CALLS = 512;
@@ -99,7 +99,7 @@ hipError_t launch_stream_down(moe_ctx* c, const int32_t* offsets, int max_units,
                               const float* s2, float* y_perm);
 hipError_t launch_stream_linear(moe_ctx* c, const uint8_t* xq, const float* xs, int32_t rows, int32_t K, const uint8_t* Wq,
                                 const float* ws, int32_t NOUT, float* y);
-// The split-K GEMMs for products that do not fill the chip (ffn_few.hip), tiles of FEW_ROWS rows in the grouped ones
+// The GEMMs in small blocks for products that do not fill the chip (ffn_few.hip), tiles of FEW_ROWS rows in the grouped ones
 hipError_t set_few_lds_limits();
 hipError_t launch_few_gate_up(moe_ctx* c, const uint8_t* xq, const float* xs, const int32_t* perm, const int32_t* offsets,
                               int max_tiles, const uint8_t* W1, const uint8_t* W3, const float* s1, const float* s3);
