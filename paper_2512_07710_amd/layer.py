@@ -88,6 +88,11 @@ class MoELayer:
         B.moe_combine(self.ctx, self.y_perm, self.inv_perm, self.topk_w, self.y, y_f32)
 
     # ---- whole layer ----------------------------------------------------------------
+    def _as_written(self, *stages):
+        """Are these stages the methods above?  One that a subclass or a wrapper has replaced is called, not passed over by a call
+        that does the work of two (looked at in every pass: either may come and go)."""
+        return all(getattr(getattr(self, n), "__func__", None) is _STAGES[n] for n in stages)
+
     # `fused` = True: activations quantised once per token, gathered inside the gate/up GEMM;
     # False: the expert-ordered copy xq/xs is materialised first (same results bit for bit)
     def _ffn_gather(self, w):
@@ -115,11 +120,11 @@ class MoELayer:
         return self._ffn_gather(w)
 
     def forward_routed(self, x, W_r, sel_bias, w, fused=True):
-        if fused is True and self.overlap_quantize:
+        if fused is True and self.overlap_quantize and self._as_written("quantize_tokens"):
             self._quantize_tokens_beside(x)
             self.route(x, W_r, sel_bias)
             return self._ffn_after_side(w)
-        if fused:
+        if fused and self._as_written("route", "quantize_tokens"):
             B.moe_route_quantize(self.ctx, x, W_r, sel_bias, self.k, self.topk_idx, self.topk_w, self.offsets, self.perm,
                                  self.inv_perm, self.xq_tok, self.xs_tok)
             return self._ffn_gather(w)
@@ -127,11 +132,11 @@ class MoELayer:
         return self._ffn(x, w, fused)
 
     def forward_replay(self, x, logged_idx, logged_w, w, fused=True):
-        if fused is True and self.overlap_quantize:
+        if fused is True and self.overlap_quantize and self._as_written("quantize_tokens"):
             self._quantize_tokens_beside(x)
             self.route_replay(x, logged_idx, logged_w)
             return self._ffn_after_side(w)
-        if fused:
+        if fused and self._as_written("route_replay", "quantize_tokens"):
             B.moe_route_replay_quantize(self.ctx, x, logged_idx, logged_w, self.topk_idx, self.topk_w, self.offsets,
                                         self.perm, self.inv_perm, self.xq_tok, self.xs_tok)
             return self._ffn_gather(w)
@@ -146,3 +151,6 @@ class MoELayer:
         B.moe_debug_copy_hidden(self.ctx, hq, hs)
         torch.cuda.synchronize(self.device)
         return hq, hs
+
+
+_STAGES = {name: getattr(MoELayer, name) for name in ("route", "route_replay", "quantize_tokens")}
