@@ -373,3 +373,93 @@ def test_linear_either_side_of_the_streaming_line(gpu_lib, rows, K, NOUT):
         assert torch.isnan(y[rows]).all()
     finally:
         gpu_lib.moe_destroy(ctx)
+
+
+# --------------------------------------------------------------------------- the order of a sum
+def _cancelling_rows(g, n, K):
+    """Codes [n, K] for activations of 256 in even and 2^-9 in odd columns: in every K block a product of 2^16, one of -2^16 and one of
+    2^-18, each in a 16-column piece of its own.  The matrix instructions add such pieces one after another and keep some 24 bits, so
+    whether the small one is in the result depends on their order, and only the order that all kernels promise gives the same bits."""
+    w = torch.zeros((n, K // 128, 8, 16), dtype=torch.uint8, device="cuda")
+    piece = torch.rand((n, K // 128, 8), generator=g, device="cuda").argsort(dim=2)
+    at = torch.randint(0, 8, (n, K // 128, 3), generator=g, device="cuda") * 2
+    for j, code in enumerate((0x78, 0xF8, 0x01)):
+        p, col = piece[..., j], at[..., j] + (j == 2)
+        w.view(n, K // 128, 128).scatter_(2, (p * 16 + col)[..., None], code)
+    return w.view(n, K)
+
+
+def _alternating(*shape):
+    x = torch.full(shape, 0x78, dtype=torch.uint8, device="cuda")
+    x[..., 1::2] = 0x01
+    return x
+
+
+@pytest.mark.parametrize("rows", [1, 17, 40, 64, 300])
+@pytest.mark.parametrize("K", [128, 640])
+def test_linear_sums_in_one_order(gpu_lib, rows, K):
+    """Tiles of 16, 32 and 64 rows in small blocks, the streaming kernel and the big tiles: one order of a row's products."""
+    WIDE = 131 * 256
+    g = torch.Generator(device="cuda").manual_seed(rows + K)
+    wq, xq = _cancelling_rows(g, WIDE, K), _alternating(rows, K)
+    xs, ws = torch.ones((K // 128, rows), device="cuda"), torch.ones((WIDE // 128, K // 128), device="cuda")
+    ctx = gpu_lib.moe_create(rows, K, 1, 1, WIDE)
+    try:
+        out = []
+        for n in (WIDE, 4096, 1024):                          # big tiles or streaming, then smaller forms
+            y = torch.full((rows, n), float("nan"), device="cuda")
+            gpu_lib.moe_linear_fp8(ctx, xq, xs, rows, K, wq[:n], ws[:n // 128].contiguous(), n, y)
+            out.append(y[:, :1024].clone())
+        kept = out[0][0] * 2.0 ** 18                          # K blocks whose small product is in the sum
+        assert (kept == 0).any() and (kept == K // 128).any()
+        for y in out[1:]:
+            assert torch.equal(y, out[0])
+        assert (out[0] == out[0][0]).all()                    # nor does a row's place in its tile matter
+    finally:
+        gpu_lib.moe_destroy(ctx)
+
+
+@pytest.mark.parametrize("T", [1, 5, 16, 200, 400])
+@pytest.mark.parametrize("which", ["gate_up", "down"])
+def test_layer_sums_in_one_order(gpu_lib, T, which):
+    """The first T of 1500 tokens, which take the big tiles, in small blocks, the streaming kernel and narrow tiles."""
+    d, E, k, F, big = 640, 16, 2, 384, 1500
+    g = torch.Generator(device="cuda").manual_seed(T)
+    ids = torch.rand((big, E), generator=g, device="cuda").topk(k, dim=1).indices.to(torch.int32)
+    gates = torch.rand((big, k), generator=g, device="cuda")
+    one = lambda r, c: torch.ones((E, r // 128, c // 128), device="cuda")
+    w = {"s1": one(F, d), "s3": one(F, d), "s2": one(d, F)}
+    if which == "gate_up":                                    # codes of scale 1: 256 and 2^-9, a maximum of 448 in every group
+        x = _alternating(big, d).view(torch.float8_e4m3fn).to(torch.bfloat16)
+        x.view(big, d // 128, 128)[:, :, 126] = 448.0
+        for n in ("W1q", "W3q"):
+            w[n] = _cancelling_rows(g, E * F, d).view(E, F, d)
+            w[n].view(E, F, d // 128, 128)[..., 126] = 0
+        w["s1"] *= 2.0 ** 18
+        w["s3"] *= 2.0 ** 18
+        w["W2q"] = _codes(g, E, d, F)
+    else:                                                     # one column of x decides: h is 448^3 and 448^2 * 2^-9 in turn
+        x = torch.zeros((big, d), device="cuda", dtype=torch.bfloat16)
+        x[:, 0] = 448.0
+        w["W1q"] = torch.zeros((E, F, d), dtype=torch.uint8, device="cuda")
+        w["W3q"] = w["W1q"].clone()
+        w["W1q"][:, :, 0] = 0x38
+        w["W3q"][:, :, 0] = 0x7E
+        w["W3q"][:, 1::2, 0] = 0x01
+        w["W2q"] = _cancelling_rows(g, E * d, F).view(E, d, F)
+    out = []
+    for n in (big, T):
+        layer = gpu_lib.MoELayer(n, d, E, k, F)
+        layer.forward_replay(x[:n].contiguous(), ids[:n].contiguous(), gates[:n].contiguous(), w)
+        hq, hs = layer.hidden()
+        at = layer.inv_perm.view(n, k)[:T].long().flatten()
+        out.append((hq[at], hs[:, at], layer.y_perm[at].clone(), layer.y[:T].clone().view(torch.int16)))
+        layer.close()
+    if which == "gate_up":
+        h = out[0][0][0]
+        assert (h == 0).any() and (h != 0).any()
+    else:
+        small = out[0][2][0].abs()
+        assert out[0][0][0].unique().numel() == 2 and small.unique().numel() > 1
+    for a, b in zip(*out):
+        assert torch.equal(a, b)
