@@ -64,8 +64,13 @@ constexpr int MANY_TILES = 3;
 // 0.81 -> 0.71 ms, at 896..1152 rows 1.94 -> 1.87 ms (d = 7168, F = 2048, 64 experts; 258: d = 5120, F = 1536,
 // 128 experts); at full tiles nothing changes.  The down projection is 6 % faster at 258 rows, 3 % at 960, and
 // 3..5 % slower at 1030..1152; cutting its remainder off as one short tile measures the same as dealing evenly.
-// A remainder of at most 64 rows as a NARROW tile does not pay in the gate/up projection: it runs ahead of the
-// tiles it shares the weight tile with, and the weight tile is fetched twice (8 % slower at 248..264 rows).
+// A remainder of at most 64 rows as a narrow tile that reads past the caches does not pay in the gate/up projection: it runs ahead
+// of the tiles it shares the weight tile with, and the weight tile is fetched twice (8 % slower at 248..264 rows).
+// An expert of 129..160 rows in tiles of at most 128 has 64 rows in a narrow tile and the others in a full one.  Both read the
+// weights the same way (GATE_UP_ONCE_TILES): with the narrow one past the caches each of the two fetched them, and the gate/up
+// projection of such experts took (us, that / this / both on the full tile's loop / one tile of 160): 32 x 7168 x 512 113 / 80 / 85 /
+// 78, 16 x 7168 x 1024 91 / 69 / 76 / 77, 8 x 7168 x 2048 79 / 64 / 72 / 73, 8 x 5120 x 1536 53 / 48 / 51 / 57, 16 x 2048 x 768 24.3 /
+// 22.9 / 25.1 / 27.7.
 __device__ inline void split_rows(int rows, int nt, int i, Work& w) {
     const int64_t G = (rows + 31) / 32;
     const int lo = min(rows, 32 * (int)(i * G / nt)), hi = min(rows, 32 * (int)((i + 1) * G / nt));
@@ -513,6 +518,10 @@ __global__ __launch_bounds__(NTHREADS, 1) void ffn_gemm(const uint8_t* __restric
     // A wave whose features all lie beyond NOUT (down projection, NOUT an odd multiple of 128: feature tile half empty)
     // copies the last 32 features again; they are multiplied and not stored.
     Feed feed;
+    auto weights = [&](int kb, int slot) {
+        if (once) copy_w<true>(feed, kb, slot);
+        else copy_w<false>(feed, kb, slot);
+    };
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t*)smem;
     feed.lds_rows = lds0 + wave * 32 * KB;                     // this wave's rows inside a tile buffer
     {
@@ -530,8 +539,7 @@ __global__ __launch_bounds__(NTHREADS, 1) void ffn_gemm(const uint8_t* __restric
             if (j < 2) feed.w_off[j] = (uint32_t)(j * 8 + sub) * (uint32_t)K + chunk[j];
         }
         // the weights of K block 0 are on their way before the rows' tokens have been looked up
-        if (narrow || once) copy_w<true>(feed, 0, 0);
-        else copy_w<false>(feed, 0, 0);
+        weights(0, 0);
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const int p = min(wk.row0 + wave * 32 + j * 8 + sub, row_end - 1);   // rows past the tile repeat its last row
@@ -575,7 +583,7 @@ __global__ __launch_bounds__(NTHREADS, 1) void ffn_gemm(const uint8_t* __restric
         xs_load(xs_n[0], 0, 0);
         xs_load(xs_n[1], 0, 1);
         if (nkb > 1) {
-            copy_w<true>(feed, 1, 1);
+            weights(1, 1);
             asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
         } else {
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -589,7 +597,7 @@ __global__ __launch_bounds__(NTHREADS, 1) void ffn_gemm(const uint8_t* __restric
             xs_load(xs_n[1], 1, 1);
             copy_x(feed, 1, 1);
         }
-        if (nkb > 2) copy_w<true>(feed, 2, 2);
+        if (nkb > 2) weights(2, 2);
         v16f an[2];
 #pragma unroll
         for (int ts = 0; ts < 2; ++ts)
@@ -628,7 +636,7 @@ __global__ __launch_bounds__(NTHREADS, 1) void ffn_gemm(const uint8_t* __restric
                 xs_load(xs_n[1], kb + 2, 1);
                 copy_x(feed, kb + 2, kb & 1);
             }
-            if (kb + 3 < nkb) copy_w<true>(feed, kb + 3, wslot);
+            if (kb + 3 < nkb) weights(kb + 3, wslot);
             // the four matrix instructions have left the pipe by now; a few wait states more cost nothing here
             asm volatile("s_nop 15\n\ts_nop 15\n\ts_nop 7" ::: "memory");
             PIN(T0);
