@@ -34,6 +34,37 @@ struct StreamArgs {
     float* y;
 };
 
+// ---- hidden rows of a unit whose 128 features are spread over S blocks
+// Every wave's part of h has been put; is this the last of the unit's blocks to arrive?  (Then all of h can be read with get2.)
+template <int S>
+__device__ inline bool last_of_unit(int32_t* tickets, int unit, int32_t& s_ticket, int tid) {
+    // every wave's stores have reached the common point before the block takes its ticket
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (tid == 0) s_ticket = __hip_atomic_fetch_add(tickets + unit, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    if (s_ticket != S - 1) return false;
+    if (tid == 0) __hip_atomic_store(tickets + unit, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // for the next launch
+    return true;
+}
+// Sixteen lanes own row p of feature tile ft, lane `sub` features 8*sub .. 8*sub+7 in h: their scale and codes.
+__device__ inline void put_hidden_row(const StreamArgs& g, int p, int ft, int sub, const float (&h)[8]) {
+    float am = 0.f;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) am = fmaxf(am, fabsf(h[i]));
+    am = fmaxf(am, __shfl_xor(am, 1));
+    am = fmaxf(am, __shfl_xor(am, 2));
+    am = fmaxf(am, __shfl_xor(am, 4));
+    am = fmaxf(am, __shfl_xor(am, 8));
+    const float sc = (am == 0.f) ? 1.0f : am / 448.0f;
+    const Quotient q(sc);
+    uint2 codes;
+    codes.x = e4m3_codes4(q, h[0], h[1], h[2], h[3]);
+    codes.y = e4m3_codes4(q, h[4], h[5], h[6], h[7]);
+    *reinterpret_cast<uint2*>(g.hq + (size_t)p * g.NOUT + ft * 128 + sub * 8) = codes;
+    if (sub == 0) g.hs[(size_t)ft * g.n_rows + p] = sc;
+}
+
 // The row tiles of all experts and the units made of them, ordered (expert, feature tile, row tile) as in the big-tile kernel's
 // work list.  Every wave works them out from the offsets in registers: lane l keeps experts 4l .. 4l+3.  (A list written by a
 // kernel of its own costs a launch, 4..5 us of a decode step, and two dependent loads here instead of one.)

@@ -245,19 +245,12 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
             const int r = i / (HW / 2), c = i % (HW / 2) * 2;
             put2(rows + (size_t)r * g.NOUT + sub_f + c, s_h[r * HP + c], s_h[r * HP + c + 1]);
         }
-        // every wave's stores have reached the common point before the block takes its ticket
-        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
-        __syncthreads();
-        if (tid == 0) *s_ticket = __hip_atomic_fetch_add(g.tickets + unit, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __syncthreads();
-        if (*s_ticket != S - 1) return;
-        if (tid == 0) __hip_atomic_store(g.tickets + unit, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // for the next launch
+        if (!last_of_unit<S>(g.tickets, unit, *s_ticket, tid)) return;
     }
     // the unit's last block: 16 lanes per row, 8 features each
     for (int r = tid >> 4; r < wk.nrows; r += NW * 4) {        // (the 16 lanes of a row share r)
-        const int p = wk.row0 + r, c = (tid & 15) * 8;
+        const int c = (tid & 15) * 8;
         float h[8];
-        float am = 0.f;
         if (S == 1 || c / HW == u % S) {
 #pragma unroll
             for (int i = 0; i < 8; ++i) h[i] = s_h[r * HP + c - sub_f + i];
@@ -269,19 +262,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
                 h[i + 1] = v.y;
             }
         }
-#pragma unroll
-        for (int i = 0; i < 8; ++i) am = fmaxf(am, fabsf(h[i]));
-        am = fmaxf(am, __shfl_xor(am, 1));
-        am = fmaxf(am, __shfl_xor(am, 2));
-        am = fmaxf(am, __shfl_xor(am, 4));
-        am = fmaxf(am, __shfl_xor(am, 8));
-        const float sc = (am == 0.f) ? 1.0f : am / 448.0f;
-        const Quotient q(sc);
-        uint2 codes;
-        codes.x = e4m3_codes4(q, h[0], h[1], h[2], h[3]);
-        codes.y = e4m3_codes4(q, h[4], h[5], h[6], h[7]);
-        *reinterpret_cast<uint2*>(g.hq + (size_t)p * g.NOUT + f0 + c) = codes;
-        if ((tid & 15) == 0) g.hs[(size_t)wk.ft * g.n_rows + p] = sc;
+        put_hidden_row(g, wk.row0 + r, wk.ft, tid & 15, h);
     }
 }
 

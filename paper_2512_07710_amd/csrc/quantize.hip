@@ -11,8 +11,7 @@
 // of its own, and every element paid a true division: 15.6 us for 4096 x 5120 and 36.1 for 8192 x 7168 called in a row, against
 // 12.4 and 28.2 (6.2 TB/s) with 32 rows per block.  Non-temporal loads
 // would be 11 % faster at 32768 x 7168 but slower at 8192 and below, where x is still in the last-level cache.
-#include "e4m3.hpp"
-#include "moe_internal.hpp"
+#include "quantize_rows.hpp"
 
 namespace moe355 {
 namespace {
@@ -55,13 +54,8 @@ __global__ __launch_bounds__(256) void quantize_rows_kernel(const uint16_t* __re
 #pragma unroll
         for (int i = 0; i < PASSES; ++i) {
             const int64_t r = r0 + i * 16;             // the 16 lanes of a group share it
-            float amax = bf16x8_amax(raw[i]);
-            amax = fmaxf(amax, __shfl_xor(amax, 1));
-            amax = fmaxf(amax, __shfl_xor(amax, 2));
-            amax = fmaxf(amax, __shfl_xor(amax, 4));
-            amax = fmaxf(amax, __shfl_xor(amax, 8));
+            const E4m3Coder coder = group_coder(raw[i]);
             if (r >= rows_in) continue;
-            const E4m3Coder coder((amax == 0.f) ? 1.0f : amax / 448.0f);
             const u32x2 codes = coder.pack8(raw[i]);
             auto put = [&](int64_t orow) {
                 if (orow < 0) return;                  // assignment skipped by the permutation

@@ -1,21 +1,27 @@
-// One row's share of the token-order quantisation, for kernels that carry it along in blocks of their own.
+// The quantisation of a group of 128 columns, shared by the quantisation's own kernel (quantize.hip) and those that carry the
+// token-order quantisation along in blocks of their own.
 #pragma once
 #include "e4m3.hpp"
 #include "moe_internal.hpp"
 
 namespace moe355 {
 
-// Sixteen lanes own one 128-column group g of row r: each loads 8 bf16 (16 bytes), the group maximum is reduced with four
-// xor-shuffles, the code is quantize.hip's.  All sixteen lanes of a live row call it.
-__device__ inline void quantize_row_group(const token_quant& t, int64_t r, int g, int sub) {
-    const size_t at = (size_t)r * t.cols + (size_t)g * QBLOCK + sub * 8;
-    const u32x4 raw = *reinterpret_cast<const u32x4*>(t.x + at);
+// Sixteen lanes own one 128-column group, 8 bf16 each: its maximum, reduced with four xor-shuffles, makes the scale.  All sixteen
+// call it.
+__device__ inline E4m3Coder group_coder(const u32x4& raw) {
     float amax = bf16x8_amax(raw);
     amax = fmaxf(amax, __shfl_xor(amax, 1));
     amax = fmaxf(amax, __shfl_xor(amax, 2));
     amax = fmaxf(amax, __shfl_xor(amax, 4));
     amax = fmaxf(amax, __shfl_xor(amax, 8));
-    const E4m3Coder coder((amax == 0.f) ? 1.0f : amax / 448.0f);
+    return E4m3Coder((amax == 0.f) ? 1.0f : amax / 448.0f);
+}
+
+// Group g of row r in token order.  All sixteen lanes of a live row call it.
+__device__ inline void quantize_row_group(const token_quant& t, int64_t r, int g, int sub) {
+    const size_t at = (size_t)r * t.cols + (size_t)g * QBLOCK + sub * 8;
+    const u32x4 raw = *reinterpret_cast<const u32x4*>(t.x + at);
+    const E4m3Coder coder = group_coder(raw);
     *reinterpret_cast<u32x2*>(t.q + at) = coder.pack8(raw);
     if (sub == 0) t.scales[(size_t)g * t.rows + r] = coder.s;
 }
