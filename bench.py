@@ -233,7 +233,7 @@ def main() -> int:
         "route_replay": _stage_ms(torch, lambda: layer.route_replay(x, log_idx, log_w)),
     }
     (priv["step_routed"] if head_mode == "routed" else priv["step_replay"])()
-    stages["quantize"] = _stage_ms(torch, lambda: layer.quantize_tokens(x))          # once per token (the timed path)
+    stages["quantize"] = _stage_ms(torch, lambda: layer.quantize_tokens(x))          # once per token; the timed step has it beside the routing
     stages["expert_ffn"] = _stage_ms(torch, lambda: layer.expert_ffn_gather(inp))     # gathers inside the gate/up GEMM
     stages["combine"] = _stage_ms(torch, layer.combine)
     # the unfused alternative: expert-ordered copy of the activations, then the plain grouped FFN

@@ -202,12 +202,18 @@ def _combine_alone_sampled(r, toks):
 
 
 def _fused_is_bit_identical(r):
-    """The gather-fused path (activations quantised once per token, gathered inside the gate/up GEMM) must
-    reproduce the materialised path bit for bit at full size."""
-    L = r.layer
-    L.y.zero_()
-    L._ffn(r.inp["x"], r.inp, fused=True)
+    """The whole-layer call as a user makes it (routing and token quantisation in one call or side by side, activations quantised once
+    per token and gathered inside the gate/up GEMM) must reproduce the materialised path bit for bit at full size."""
+    L, inp = r.layer, r.inp
+    for t in (L.y, L.topk_idx, L.topk_w, L.offsets, L.perm, L.inv_perm, L.xq_tok, L.xs_tok):
+        t.zero_()
+    if r.mode == "routed":
+        L.forward_routed(inp["x"], inp["W_r"], inp.get("sel_bias"), inp)
+    else:
+        L.forward_replay(inp["x"], r.log[0], r.log[1], inp)
     torch.cuda.synchronize()
+    for got, want in ((L.topk_idx, r.idx), (L.topk_w, r.w), (L.offsets, r.offsets), (L.perm, r.perm), (L.inv_perm, r.inv_perm)):
+        assert np.array_equal(got.cpu().numpy(), want)
     hq_f, hs_f = L.hidden()
     assert torch.equal(r.hq, hq_f) and torch.equal(r.hs.view(torch.int32), hs_f.view(torch.int32))
     assert torch.equal(r.y.view(torch.int16), L.y.view(torch.int16))
