@@ -11,6 +11,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB_PATH = os.path.join(HERE, "libmoe355.so")
 SOURCES = ("moe_api.hip", "route.hip", "permute.hip", "quantize.hip", "wquant.hip", "ffn.hip", "ffn_stream.hip", "ffn_few.hip", "combine.hip", "balance.hip", "probe.hip")
+HEADERS = ("moe_internal.hpp", "e4m3.hpp", "ffn_common.hpp", "ffn_rows.hpp", "ffn_rules.hpp", "permute_block.hpp", "quantize_rows.hpp")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 # packed-fp32 code generation is switched off for every device compile
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Xclang", "-target-feature", "-Xclang",
@@ -19,10 +20,7 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Xclang", "-tar
 
 def _compile(src: str, force: bool) -> str:
     obj = os.path.join(CSRC, src.replace(".hip", ".o"))
-    deps = [os.path.join(CSRC, src), os.path.join(CSRC, "moe_internal.hpp"), os.path.join(CSRC, "e4m3.hpp"),
-            os.path.join(CSRC, "ffn_common.hpp"), os.path.join(CSRC, "ffn_rows.hpp"), os.path.join(CSRC, "permute_block.hpp"),
-            os.path.join(CSRC, "quantize_rows.hpp"),
-            os.path.join(ROOT, "include", "moe355.h")]
+    deps = [os.path.join(CSRC, src), os.path.join(ROOT, "include", "moe355.h"), *(os.path.join(CSRC, h) for h in HEADERS)]
     if not force and os.path.exists(obj) and all(os.path.getmtime(obj) >= os.path.getmtime(p) for p in deps):
         return obj
     cmd = [HIPCC, *FLAGS, "-c", os.path.join(CSRC, src), "-o", obj]

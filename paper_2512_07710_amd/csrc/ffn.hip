@@ -29,8 +29,7 @@
 // GEMM2: staged rows are 256 consecutive output features; epilogue: fp32 rows, turned through LDS so
 //        that every row is stored in contiguous 256-byte pieces.
 #include "ffn_common.hpp"
-
-#include <cmath>
+#include "ffn_rules.hpp"
 
 namespace moe355 {
 namespace {
@@ -43,72 +42,6 @@ constexpr int NW_BUF = 3, NX_BUF = 2;              // LDS ring depths
 constexpr int X_RING = NW_BUF * W_TILE;            // byte offset of the activation ring
 constexpr int NTHREADS = 512;
 constexpr int CODES_LD = 128 + 16;                  // bytes from row to row of the LDS tile of hidden codes
-// Row tiles of an expert up to which its weights are read past the caches (us, through / past them; gate/up | down): 64 experts x 4096
-// x 1408 at 80 rows 141.6 / 133.8 | 102 / 89, 112 148 / 141 | 112 / 98, 224 200 / 197 | 153 / 140, 258 (two tiles) 234 / 236 | 164 /
-// 157, 420 337 / 340 | 232 / 235; 128 x 2048 x 768 at 112 88 / 83 | 76 / 69, 258 142 / 143 | 126 / 119; 16 x 3072 x 2048 at 80 42.1 /
-// 38.3 | 26.3 / 25.7.  With four tiles (1030 rows) the gate/up projection is 2 % slower past them, 4 % at 7168 x 2048.
-constexpr int GATE_UP_ONCE_TILES = 1, DOWN_ONCE_TILES = 2;
-constexpr int NARROW_ROWS = 64;                     // tiles of at most this many rows take the narrow path of ffn_gemm
-
-// one work unit: rows [row0, row0 + nrows) of an expert x feature tile ft (128 features gate/up, 256 down); tiles: row tiles of the
-// expert, as far as MANY_TILES
-struct Work { int32_t expert; int32_t row0; int32_t ft; int16_t nrows, tiles; };
-constexpr int MANY_TILES = 3;
-
-// Rows [row0, row0 + nrows) of tile i when `rows` rows make nt tiles.
-// The expert's G = ceil(cnt/32) groups of 32 rows are dealt out evenly: tile i covers groups [i*G/nt, (i+1)*G/nt).
-// The tiles that share a weight tile are then within one group of each other: they advance nearly in step and
-// fetch it once, only the expert's last group is partly filled, and a tile's matrix time follows its height.
-// With the groups of 64 of a layout whose short tiles left whole waves idle (so that every tile cost the time
-// of a full one) the gate/up projection took 1.98 ms at 1030 rows per expert and takes 1.82, at 258 rows
-// 0.81 -> 0.71 ms, at 896..1152 rows 1.94 -> 1.87 ms (d = 7168, F = 2048, 64 experts; 258: d = 5120, F = 1536,
-// 128 experts); at full tiles nothing changes.  The down projection is 6 % faster at 258 rows, 3 % at 960, and
-// 3..5 % slower at 1030..1152; cutting its remainder off as one short tile measures the same as dealing evenly.
-// A remainder of at most 64 rows as a narrow tile that reads past the caches does not pay in the gate/up projection: it runs ahead
-// of the tiles it shares the weight tile with, and the weight tile is fetched twice (8 % slower at 248..264 rows).
-// An expert of 129..160 rows in tiles of at most 128 has 64 rows in a narrow tile and the others in a full one.  Both read the
-// weights the same way (GATE_UP_ONCE_TILES): with the narrow one past the caches each of the two fetched them, and the gate/up
-// projection of such experts took (us, that / this / both on the full tile's loop / one tile of 160): 32 x 7168 x 512 113 / 80 / 85 /
-// 78, 16 x 7168 x 1024 91 / 69 / 76 / 77, 8 x 7168 x 2048 79 / 64 / 72 / 73, 8 x 5120 x 1536 53 / 48 / 51 / 57, 16 x 2048 x 768 24.3 /
-// 22.9 / 25.1 / 27.7.
-__device__ inline void split_rows(int rows, int nt, int i, Work& w) {
-    const int64_t G = (rows + 31) / 32;
-    const int lo = min(rows, 32 * (int)(i * G / nt)), hi = min(rows, 32 * (int)((i + 1) * G / nt));
-    w.row0 = lo;
-    w.nrows = (int16_t)(hi - lo);
-    w.tiles = (int16_t)min(nt, MANY_TILES);
-}
-
-// ------------------------------------------------------------------ tile heights
-// 256 rows are the most a tile can have, but not always the best: units come in rounds of one a CU, and a round that is a
-// quarter full takes nearly as long as a full one.  16 experts of 750 rows x 3072 x 2048 make 3.25 rounds of tiles of up to 256 rows,
-// 178 us, and 4 full ones of shorter tiles, 160.  The cost of `units` units in K steps of a 10-row-group tile (a step costs 0.2 + 0.1 n at
-// n groups of 32 rows, what lies between two tiles 4 steps, a started round 0.7 of a full one) was fitted to 27 layers of 130 to 1100
-// rows per expert, both projections, heights 96 to 256: the height it picks is 0.2 % above the best of them on average, always
-// taking 256 5.7 %.
-constexpr int HEIGHTS = 5;                          // 256, 224, 192, 160, 128
-__host__ __device__ constexpr int tile_height(int j) { return TOK_TILE - 32 * j; }
-__host__ __device__ inline float tiles_cost(int64_t units, float groups_per_tile, int nkb) {
-    const int64_t full = units / 256, rest = units % 256;
-    const float rounds = (float)full + (rest ? 0.7f + 0.3f / 256.0f * (float)rest : 0.0f);
-    return rounds * (4.0f + (float)nkb * (0.2f + 0.1f * groups_per_tile));
-}
-// the best of the heights that need at most `capacity` units (256 needs no asking)
-__host__ __device__ inline int pick_height(const int (&tiles)[HEIGHTS], int groups, int n_ft, int nkb, int64_t capacity) {
-    int best = 0;
-    float least = 0.0f;
-    for (int j = 0; j < HEIGHTS && tiles[0] > 0; ++j) {
-        const int64_t units = (int64_t)tiles[j] * n_ft;
-        if (j > 0 && units > capacity) break;
-        const float c = tiles_cost(units, (float)groups / (float)tiles[j], nkb);
-        if (j == 0 || c < least) {
-            least = c;
-            best = j;
-        }
-    }
-    return tile_height(best);
-}
-
 // ------------------------------------------------------------------ work list
 // An expert with c rows gets ceil(c/h) row tiles, h the launch's tile height, ordered (expert, feature tile, row tile).  Units
 // that share a weight tile are thus neighbours and, when they do the same amount of work, the blocks
@@ -127,8 +60,6 @@ __device__ inline int wave_scan(int v) {
     v += from_lanes<0x143, 0xc>(v);
     return v;
 }
-// One list for each projection: its feature tiles, K blocks and room.
-struct ListShape { int n_ft, nkb, capacity; bool one_height; };
 // Block (e, l) writes the units of expert e into list l (0: gate/up, 1: down); every block recomputes the tile counts of all
 // experts for its base index and the height.
 // choose: list 1 is left empty (n_work[1] = 0) unless the batch is concentrated, see DOWN_SKEW_UNITS.
@@ -152,7 +83,7 @@ __device__ inline void build_work(const int32_t* __restrict__ offsets, int E, in
     for (int j = 0; j < SUMS; ++j) sums[j] = s_sums[0][j] + s_sums[1][j] + s_sums[2][j] + s_sums[3][j];
 #pragma unroll
     for (int j = 0; j < HEIGHTS; ++j) tiles[j] = sums[j];
-    const int h = shape.one_height ? TOK_TILE : pick_height(tiles, sums[HEIGHTS], n_ft, shape.nkb, shape.capacity);
+    const int h = list_height(shape, tiles, sums[HEIGHTS]);
     int total = tiles[0];                                      // at the chosen height
 #pragma unroll
     for (int j = 1; j < HEIGHTS; ++j) total = h == tile_height(j) ? tiles[j] : total;
@@ -512,7 +443,7 @@ __global__ __launch_bounds__(NTHREADS, 1) void ffn_gemm(const uint8_t* __restric
     //      Staged weight row r: GATED: features f0 + (r/64)*32 + r%32, gate (Wa) if (r/32)%2 == 0 else up (Wb).
     //      NARROW tiles (at most 64 rows, see below): wave w's 32 staged rows are 32 consecutive features of the tile
     //      (down projection) or, GATED, [16 gate rows | 16 up rows] of features f0 + 16w .. 16w+15.
-    // (LINEAR: products of at most 64 rows stream, and a larger one has no tile as short)
+    // (LINEAR: a product of 129..160 rows can have a tile as short beside a taller one; k_loop<1> in both halves, their waves in step)
     const bool narrow = !LINEAR && wk.nrows <= NARROW_ROWS;    // block-uniform
     const bool once = !LINEAR && wk.tiles <= (GATED ? GATE_UP_ONCE_TILES : DOWN_ONCE_TILES);   // as is this
     // A wave whose features all lie beyond NOUT (down projection, NOUT an odd multiple of 128: feature tile half empty)
@@ -709,7 +640,7 @@ __global__ __launch_bounds__(NTHREADS, 1) void ffn_gemm(const uint8_t* __restric
         }
         return;
     }
-    // ---- full tile: 32-row token groups n = ceil(rows / 32) of 3..8; waves 0..3 (token half 0) take the first ceil(n/2)
+    // ---- full tile: 32-row token groups n = ceil(rows / 32) of 3..8 (LINEAR: 2..8); waves 0..3 (token half 0) take the first ceil(n/2)
     //      of them, waves 4..7 the others.  Wave w and wave w + 4 share a SIMD, so every SIMD multiplies n groups: the
     //      matrix time of a tile follows its height in steps of 32 rows.
     const int n_grp = (wk.nrows + 31) >> 5;
@@ -822,104 +753,6 @@ constexpr size_t SMEM_BYTES = NW_BUF * W_TILE + NX_BUF * X_TILE;   // 160 KiB
 
 }  // namespace
 
-// ------------------------------------------------------------------ which kernel takes which GEMM
-// The streaming kernels (ffn_stream.hip) where the weights are the bound, the big tiles where matrix work or the L2 reuse of
-// weights between row tiles counts.  The lines were measured with both sides on the same buffers (us, big tiles / streaming;
-// the big-tile side already reads the weights of narrow tiles past the caches):
-//   gate/up  rows per expert 2: 1026 / 1006 (256 experts), 3: 163 / 142, 6: 136 / 133, 12: 129.5 / 133, 16: 251..287 / 274..287
-//            and, where the tiles leave compute units idle: 96 units, 4 rows 35 / 23, 32 rows 33 / 28; 384 units, 8 rows 79 / 68
-//   down     even loads, rows per expert: 64 experts x 4096 x 1408 12: 72 / 67, 24: 77 / 72, 40: 82 / 80; 128 x 5120 x 1536 24: 199 /
-//            193, 40: 211 / 209, 64 level to 7 % slower; 128 x 2048 x 768 24: 51 / 48, 40: 55 / 52; 16 x 3072 x 2048 40: 24.8 / 25.4;
-//            256 x 7168 x 2048 12: 668 / 639, 24: 709 / 697, 30: 705 / 715, 40: 736 / 762.  The widest layers cross at 27 rows, but
-//            only with even loads: Zipf loads at a mean of 12..48 rows 638 / 624 to 931 / 887 there
-//   linear   by streaming units, big tiles of the chosen height / streaming (more than 64 rows; K = 1024 and 7168 cross at the same
-//            place): 128 units 512 x 4096 x 4096 27.4 / 17.4, 256 512 x 8192 35.0 / 31.5, 1000 x 4096 29.2 / 24.3, 2000 x 2048 29.2 / 24.7;
-//            320 320 x 16384 35.9 / 44.8, 352 1400 x 4096 30.7 / 36.2, 512 1000 x 8192 39.6 / 57.1, 704 700 x 16384 47.9 / 78.6
-constexpr int64_t GATE_UP_STREAM_ROWS = 8, GATE_UP_STREAM_ROWS_IDLE = 32, DOWN_STREAM_ROWS = 48;
-// Rows per expert are a mean.  A skewed load is no reason against streaming (down projection, Zipf loads at a mean of 6..48: 0.73..0.99
-// of the big tiles' time; nine tokens in ten on the same k experts: 0.70..0.97), but a concentrated one is: with every token on the same
-// k experts nothing but their weights is read, once for each tile of 64 rows, matrix work counts, and streaming takes 1.1..1.8 times as
-// long.  The host cannot see the load.  Where the streaming units of such a batch, k experts of T rows, are at most the figures
-// below it still costs a layer nothing to speak of (448 units: 145 us before there was a streaming kernel, 145 with it; 384: 98 and 86; 512: 74.3
-// and 74.0; above: 672 units 160 and 178, 3584 units 424 and 553).  Beyond them the gate/up projection takes the big tiles, which
-// are level there, and for the down projection the kernel that makes the lists counts: more than twice as many 64-row tiles as big ones
-// (an ordinary load has 1.0..1.55 times as many, a concentrated one of that size 2.5..4) fill the big tiles' list, otherwise it
-// stays empty; both kernels are launched and the one that has nothing to do returns.
-constexpr int64_t GATE_UP_SKEW_UNITS = 256, DOWN_SKEW_UNITS = 512;
-constexpr int CUS = 256, LINEAR_STREAM_UNITS = 256;
-
-static bool skew_is_harmless(const moe_dims* D, int feature_tiles, int64_t most_units) {
-    const int64_t tiles = (D->T + STREAM_ROWS - 1) / STREAM_ROWS;
-    return tiles <= 1 || D->k * tiles * feature_tiles <= most_units;    // one tile: no weight passes twice
-}
-enum class Down { BIG, STREAM, EITHER };
-static Down down_form(const moe_dims* D) {
-    if ((int64_t)D->T * D->k > DOWN_STREAM_ROWS * D->E) return Down::BIG;
-    return skew_is_harmless(D, (D->d + 255) / 256, DOWN_SKEW_UNITS) ? Down::STREAM : Down::EITHER;
-}
-static double experts_met(const moe_dims* D) {                 // with at least one row when the router favours none
-    return D->E * (1.0 - pow(1.0 - (double)D->k / D->E, (double)D->T));
-}
-// (only where the down projection streams for certain: then no lists are needed)
-static bool gate_up_streams(const moe_dims* D) {
-    const int64_t N = (int64_t)D->T * D->k;
-    if (N == 0 || down_form(D) != Down::STREAM || !skew_is_harmless(D, D->F / 128, GATE_UP_SKEW_UNITS)) return false;
-    if (N <= GATE_UP_STREAM_ROWS * D->E) return true;
-    return N <= GATE_UP_STREAM_ROWS_IDLE * D->E && experts_met(D) * (D->F / 128) < CUS;
-}
-// One token to a few: the kernels of ffn_few.hip while a tile of 16 rows holds every expert's rows and the streaming blocks leave the
-// chip half empty or in an uneven second round (streaming = 1).  Gate/up by units of 128 features, d = 4096: 66 units 0.81, 132 0.79,
-// 198 0.98, 308 0.91; d = 5120: 96 0.88, 192 0.90, 264 0.89, 336 level; shorter rows pay for the ends of a block (d = 2048: 48 units
-// 0.82, 132 0.94, 168 level, 234 1.17), longer ones keep a streaming block busy (d = 7168: 20 0.46, 64 0.73, 128 1.10, 256 1.10).
-// Down: F = 1408 0.91..1.00, 1536 0.84..0.95, 2048 0.95..1.04; F = 768: 1408 blocks 0.94, 1792 1.14.
-static bool gate_up_few(const moe_dims* D) {
-    if (D->T > FEW_ROWS || !gate_up_streams(D)) return false;
-    const double units = experts_met(D) * (D->F / 128);
-    return units < (D->d >= 6144 ? 112 : D->d >= 3072 ? 320 : 200);
-}
-static bool down_few(const moe_dims* D) {
-    return D->T <= FEW_ROWS && down_form(D) == Down::STREAM && (D->F >= 1280 || experts_met(D) * (D->d / 32) <= 1400);
-}
-static bool linear_streams(int32_t rows, int32_t NOUT) {
-    return rows <= STREAM_ROWS || ((int64_t)rows + STREAM_ROWS - 1) / STREAM_ROWS * ((NOUT + 255) / 256) <= LINEAR_STREAM_UNITS;
-}
-
-static int linear_tiles(int32_t rows, int nft, int nkb) {
-    int tiles[HEIGHTS];
-    for (int j = 0; j < HEIGHTS; ++j) tiles[j] = (int)(((int64_t)rows + tile_height(j) - 1) / tile_height(j));
-    const int h = pick_height(tiles, (int)(((int64_t)rows + 31) / 32), nft, nkb, (int64_t)1 << 30);
-    return (int)(((int64_t)rows + h - 1) / h);
-}
-
-// upper bound on row tiles: every full tile, and one more for each expert that has rows
-static int64_t max_row_tiles(const moe_dims* D, int rows) {
-    const int64_t N = (int64_t)D->T * D->k;
-    return N / rows + (N < D->E ? N : D->E);
-}
-// Room of a big-tile list, and blocks of its launch: the least height that can be the better one has to fit.  A first round that is
-// not full may gain from half the height; the more rounds, the less there is to gain, and blocks without a unit are not free either
-// (nor is the choice: 777 tokens x 5 of 60 experts 1.3 us, 256 x 6 of 64 0.8): experts with a mean of up to 96 rows are one tile each
-// whatever the height, but for a few of a skewed load.
-constexpr int64_t ONE_HEIGHT_ROWS = 96;
-static bool one_height(const moe_dims* D) { return (int64_t)D->T * D->k <= ONE_HEIGHT_ROWS * D->E; }
-static int64_t big_units(const moe_dims* D, int nft) {
-    const int64_t units = max_row_tiles(D, TOK_TILE) * nft, half = max_row_tiles(D, TOK_TILE / 2) * nft;
-    if (one_height(D)) return units;
-    if (half <= 2 * CUS) return half;
-    return units <= 8 * CUS ? max_row_tiles(D, 192) * nft : units <= 16 * CUS ? max_row_tiles(D, 224) * nft : units;
-}
-static int64_t gate_up_units(const moe_dims* D) {
-    if (!gate_up_streams(D)) return big_units(D, D->F / 128);
-    return max_row_tiles(D, gate_up_few(D) ? FEW_ROWS : STREAM_ROWS) * (D->F / 128);
-}
-static int64_t down_stream_units(const moe_dims* D) { return max_row_tiles(D, STREAM_ROWS) * ((D->d + 255) / 256); }
-// EITHER: S > 2B tiles of 64 / of 256 rows over m experts with rows (B >= m, S <= (N + 63m)/64) leave m <= N/65
-static int64_t down_big_units(const moe_dims* D) {
-    const int64_t N = (int64_t)D->T * D->k;
-    const int nft = (D->d + 255) / 256;
-    return down_form(D) == Down::EITHER ? (N / TOK_TILE + N / 65) * nft : big_units(D, nft);
-}
-
 // length of the gate/up projection's work list, behind which the down projection's lies; and room for both
 static int64_t gate_up_list(const moe_dims* D) { return gate_up_streams(D) ? 0 : gate_up_units(D); }
 size_t ffn_work_bytes(const moe_dims* D) {
@@ -983,8 +816,6 @@ hipError_t launch_expert_ffn(moe_ctx* c, const uint8_t* xq, const float* xs, con
     if (c->profiling && c->prof_calls < PROF_MAX_CALLS) ev = c->prof_events + 3 * c->prof_calls++;
 
     const int N = (int)((int64_t)D.T * D.k);
-    const int nft1 = D.F / 128;
-    const int nft2 = (D.d + 255) / 256;
     const bool stream1 = gate_up_streams(&D);
     const Down down = down_form(&D);
     const int units1 = (int)gate_up_units(&D);
@@ -994,8 +825,7 @@ hipError_t launch_expert_ffn(moe_ctx* c, const uint8_t* xq, const float* xs, con
         const int lists = down == Down::STREAM ? 1 : 2;
         const int64_t gather = perm ? (int64_t)((N + 255) / 256) * (D.d / QBLOCK) : 0;
         hipLaunchKernelGGL(prepare_big_tiles, dim3((unsigned)(D.E * lists + gather)), dim3(256), 0, c->stream, offsets, D.E, lists,
-                           ListShape{nft1, D.d / KB, units1, one_height(&D)},
-                           ListShape{nft2, D.F / KB, (int)down_big_units(&D), one_height(&D)}, down == Down::EITHER,
+                           gate_up_shape(&D), down_shape(&D), down == Down::EITHER,
                            work, work2, c->n_tiles, xs, D.T, perm, D.k, N, c->xs_sorted);
     }
     if (ev) (void)hipEventRecord(ev[0], c->stream);          // the timed interval is the GEMM kernel alone

@@ -22,6 +22,7 @@
 // 8192 21.4 / 17.3, 256 x 7168 x 1024 20.4 / 12.5; gate/up of one token x 6 of 4096 x 1408 21.7 / 17.5, x 2 of 3072 x 2048 15.6 /
 // 9.9; down 8.9 / 8.5 and 9.7 / 6.4.
 #include "ffn_rows.hpp"
+#include "ffn_rules.hpp"
 
 #include <type_traits>
 
@@ -284,18 +285,6 @@ hipError_t launch_few_down(moe_ctx* c, const int32_t* offsets, int max_tiles, co
     const StreamArgs a{c->hq, c->hs, m.T * m.k, nullptr, 1, 1, offsets, m.E, nullptr, nullptr, W2, nullptr, s2, nullptr, m.F, m.d,
                        true, nullptr, nullptr, nullptr, y_perm};
     return launch<1, DOWN_WK, DOWN_D, DOWN_EARLY, false, false, true>(c->stream, a, max_tiles);
-}
-
-// Up to how many blocks this is the better kernel, one to a CU (streaming kernel = 1): 256 blocks, 16-row tiles 16 x 4096 x 8192
-// 0.71, 32-row 32 x 4096 x 8192 0.76, 64-row 40 x 4096 x 8192 0.85, 64 x 4096 x 8192 0.97, 128 x 7168 x 4096 0.94, 256 x 4096 x 2048
-// 0.83; 384 blocks of 16-row tiles (75 KB, two to a CU) 0.91..1.02, of 32-row tiles 1.2, 512 of 64-row tiles 1.5.  Tiles of 32 rows
-// while they fit too (128 x 4096 x 2048 0.62 against 0.83 in tiles of 64).
-constexpr int FEW_BLOCKS = 256, FEW_BLOCKS_16 = 320;
-int few_linear_groups(int32_t rows, int32_t NOUT) {
-    const int64_t cols = NOUT / 32;
-    if (rows <= 16) return cols <= FEW_BLOCKS_16 ? 1 : 0;
-    if ((rows + 31) / 32 * cols <= FEW_BLOCKS) return 2;
-    return (rows + 63) / 64 * cols <= FEW_BLOCKS ? 4 : 0;
 }
 
 hipError_t launch_few_linear(moe_ctx* c, const uint8_t* xq, const float* xs, int32_t rows, int32_t K, const uint8_t* Wq,

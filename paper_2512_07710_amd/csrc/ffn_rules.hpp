@@ -1,0 +1,204 @@
+// Which kernel takes which GEMM, and how its rows are cut into tiles: arithmetic on sizes only, for the host and the device.
+#pragma once
+#include "moe_internal.hpp"
+
+#include <cmath>
+
+namespace moe355 {
+
+// Row tiles of an expert up to which its weights are read past the caches (us, through / past them; gate/up | down): 64 experts x 4096
+// x 1408 at 80 rows 141.6 / 133.8 | 102 / 89, 112 148 / 141 | 112 / 98, 224 200 / 197 | 153 / 140, 258 (two tiles) 234 / 236 | 164 /
+// 157, 420 337 / 340 | 232 / 235; 128 x 2048 x 768 at 112 88 / 83 | 76 / 69, 258 142 / 143 | 126 / 119; 16 x 3072 x 2048 at 80 42.1 /
+// 38.3 | 26.3 / 25.7.  With four tiles (1030 rows) the gate/up projection is 2 % slower past them, 4 % at 7168 x 2048.
+constexpr int GATE_UP_ONCE_TILES = 1, DOWN_ONCE_TILES = 2;
+constexpr int NARROW_ROWS = 64;                     // tiles of at most this many rows take the narrow path of ffn_gemm
+
+// one work unit: rows [row0, row0 + nrows) of an expert x feature tile ft (128 features gate/up, 256 down); tiles: row tiles of the
+// expert, as far as MANY_TILES
+struct Work { int32_t expert; int32_t row0; int32_t ft; int16_t nrows, tiles; };
+constexpr int MANY_TILES = 3;
+
+// Rows [row0, row0 + nrows) of tile i when `rows` rows make nt tiles.
+// The expert's G = ceil(cnt/32) groups of 32 rows are dealt out evenly: tile i covers groups [i*G/nt, (i+1)*G/nt).
+// The tiles that share a weight tile are then within one group of each other: they advance nearly in step and
+// fetch it once, only the expert's last group is partly filled, and a tile's matrix time follows its height.
+// With the groups of 64 of a layout whose short tiles left whole waves idle (so that every tile cost the time
+// of a full one) the gate/up projection took 1.98 ms at 1030 rows per expert and takes 1.82, at 258 rows
+// 0.81 -> 0.71 ms, at 896..1152 rows 1.94 -> 1.87 ms (d = 7168, F = 2048, 64 experts; 258: d = 5120, F = 1536,
+// 128 experts); at full tiles nothing changes.  The down projection is 6 % faster at 258 rows, 3 % at 960, and
+// 3..5 % slower at 1030..1152; cutting its remainder off as one short tile measures the same as dealing evenly.
+// A remainder of at most 64 rows as a narrow tile that reads past the caches does not pay in the gate/up projection: it runs ahead
+// of the tiles it shares the weight tile with, and the weight tile is fetched twice (8 % slower at 248..264 rows).
+// An expert of 129..160 rows in tiles of at most 128 has 64 rows in a narrow tile and the others in a full one.  Both read the
+// weights the same way (GATE_UP_ONCE_TILES): with the narrow one past the caches each of the two fetched them, and the gate/up
+// projection of such experts took (us, that / this / both on the full tile's loop / one tile of 160): 32 x 7168 x 512 113 / 80 / 85 /
+// 78, 16 x 7168 x 1024 91 / 69 / 76 / 77, 8 x 7168 x 2048 79 / 64 / 72 / 73, 8 x 5120 x 1536 53 / 48 / 51 / 57, 16 x 2048 x 768 24.3 /
+// 22.9 / 25.1 / 27.7.
+__host__ __device__ inline void split_rows(int rows, int nt, int i, Work& w) {
+    const int64_t G = (rows + 31) / 32;
+    const int lo = min(rows, 32 * (int)(i * G / nt)), hi = min(rows, 32 * (int)((i + 1) * G / nt));
+    w.row0 = lo;
+    w.nrows = (int16_t)(hi - lo);
+    w.tiles = (int16_t)min(nt, MANY_TILES);
+}
+
+// ------------------------------------------------------------------ tile heights
+// 256 rows are the most a tile can have, but not always the best: units come in rounds of one a CU, and a round that is a
+// quarter full takes nearly as long as a full one.  16 experts of 750 rows x 3072 x 2048 make 3.25 rounds of tiles of up to 256 rows,
+// 178 us, and 4 full ones of shorter tiles, 160.  The cost of `units` units in K steps of a tile of eight groups of 32 rows (a step costs 0.2 + 0.1 n at
+// n groups, what lies between two tiles 4 steps, a started round 0.7 of a full one) was fitted to 27 layers of 130 to 1100
+// rows per expert, both projections, heights 96 to 256: the height it picks is 0.2 % above the best of them on average, always
+// taking 256 5.7 %.
+constexpr int HEIGHTS = 5;                          // 256, 224, 192, 160, 128
+__host__ __device__ constexpr int tile_height(int j) { return TOK_TILE - 32 * j; }
+__host__ __device__ inline float tiles_cost(int64_t units, float groups_per_tile, int nkb) {
+    const int64_t full = units / 256, rest = units % 256;
+    const float rounds = (float)full + (rest ? 0.7f + 0.3f / 256.0f * (float)rest : 0.0f);
+    return rounds * (4.0f + (float)nkb * (0.2f + 0.1f * groups_per_tile));
+}
+// the best of the heights that need at most `capacity` units (256 needs no asking)
+__host__ __device__ inline int pick_height(const int (&tiles)[HEIGHTS], int groups, int n_ft, int nkb, int64_t capacity) {
+    int best = 0;
+    float least = 0.0f;
+    for (int j = 0; j < HEIGHTS && tiles[0] > 0; ++j) {
+        const int64_t units = (int64_t)tiles[j] * n_ft;
+        if (j > 0 && units > capacity) break;
+        const float c = tiles_cost(units, (float)groups / (float)tiles[j], nkb);
+        if (j == 0 || c < least) {
+            least = c;
+            best = j;
+        }
+    }
+    return tile_height(best);
+}
+
+// One list for each projection: its feature tiles, K blocks and room.
+struct ListShape { int n_ft, nkb, capacity; bool one_height; };
+__host__ __device__ inline int list_height(const ListShape& s, const int (&tiles)[HEIGHTS], int groups) {
+    return s.one_height ? TOK_TILE : pick_height(tiles, groups, s.n_ft, s.nkb, s.capacity);
+}
+
+// ------------------------------------------------------------------ which kernel takes which GEMM
+// The streaming kernels (ffn_stream.hip) where the weights are the bound, the big tiles where matrix work or the L2 reuse of
+// weights between row tiles counts.  The lines were measured with both sides on the same buffers (us, big tiles / streaming;
+// the big-tile side already reads the weights of narrow tiles past the caches):
+//   gate/up  rows per expert 2: 1026 / 1006 (256 experts), 3: 163 / 142, 6: 136 / 133, 12: 129.5 / 133, 16: 251..287 / 274..287
+//            and, where the tiles leave compute units idle: 96 units, 4 rows 35 / 23, 32 rows 33 / 28; 384 units, 8 rows 79 / 68
+//   down     even loads, rows per expert: 64 experts x 4096 x 1408 12: 72 / 67, 24: 77 / 72, 40: 82 / 80; 128 x 5120 x 1536 24: 199 /
+//            193, 40: 211 / 209, 64 level to 7 % slower; 128 x 2048 x 768 24: 51 / 48, 40: 55 / 52; 16 x 3072 x 2048 40: 24.8 / 25.4;
+//            256 x 7168 x 2048 12: 668 / 639, 24: 709 / 697, 30: 705 / 715, 40: 736 / 762.  The widest layers cross at 27 rows, but
+//            only with even loads: Zipf loads at a mean of 12..48 rows 638 / 624 to 931 / 887 there
+//   linear   by streaming units, big tiles of the chosen height / streaming (more than 64 rows; K = 1024 and 7168 cross at the same
+//            place): 128 units 512 x 4096 x 4096 27.4 / 17.4, 256 512 x 8192 35.0 / 31.5, 1000 x 4096 29.2 / 24.3, 2000 x 2048 29.2 / 24.7;
+//            320 320 x 16384 35.9 / 44.8, 352 1400 x 4096 30.7 / 36.2, 512 1000 x 8192 39.6 / 57.1, 704 700 x 16384 47.9 / 78.6
+constexpr int64_t GATE_UP_STREAM_ROWS = 8, GATE_UP_STREAM_ROWS_IDLE = 32, DOWN_STREAM_ROWS = 48;
+// Rows per expert are a mean.  A skewed load is no reason against streaming (down projection, Zipf loads at a mean of 6..48: 0.73..0.99
+// of the big tiles' time; nine tokens in ten on the same k experts: 0.70..0.97), but a concentrated one is: with every token on the same
+// k experts nothing but their weights is read, once for each tile of 64 rows, matrix work counts, and streaming takes 1.1..1.8 times as
+// long.  The host cannot see the load.  Where the streaming units of such a batch, k experts of T rows, are at most the figures
+// below it still costs a layer nothing to speak of (448 units: 145 us before there was a streaming kernel, 145 with it; 384: 98 and 86; 512: 74.3
+// and 74.0; above: 672 units 160 and 178, 3584 units 424 and 553).  Beyond them the gate/up projection takes the big tiles, which
+// are level there, and for the down projection the kernel that makes the lists counts: more than twice as many 64-row tiles as big ones
+// (an ordinary load has 1.0..1.55 times as many, a concentrated one of that size 2.5..4) fill the big tiles' list, otherwise it
+// stays empty; both kernels are launched and the one that has nothing to do returns.
+constexpr int64_t GATE_UP_SKEW_UNITS = 256, DOWN_SKEW_UNITS = 512;
+constexpr int CUS = 256, LINEAR_STREAM_UNITS = 256;
+
+inline bool skew_is_harmless(const moe_dims* D, int feature_tiles, int64_t most_units) {
+    const int64_t tiles = (D->T + STREAM_ROWS - 1) / STREAM_ROWS;
+    return tiles <= 1 || D->k * tiles * feature_tiles <= most_units;    // one tile: no weight passes twice
+}
+enum class Down { BIG, STREAM, EITHER };
+inline Down down_form(const moe_dims* D) {
+    if ((int64_t)D->T * D->k > DOWN_STREAM_ROWS * D->E) return Down::BIG;
+    return skew_is_harmless(D, (D->d + 255) / 256, DOWN_SKEW_UNITS) ? Down::STREAM : Down::EITHER;
+}
+inline double experts_met(const moe_dims* D) {                 // with at least one row when the router favours none
+    return D->E * (1.0 - pow(1.0 - (double)D->k / D->E, (double)D->T));
+}
+// (only where the down projection streams for certain: then no lists are needed)
+inline bool gate_up_streams(const moe_dims* D) {
+    const int64_t N = (int64_t)D->T * D->k;
+    if (N == 0 || down_form(D) != Down::STREAM || !skew_is_harmless(D, D->F / 128, GATE_UP_SKEW_UNITS)) return false;
+    if (N <= GATE_UP_STREAM_ROWS * D->E) return true;
+    return N <= GATE_UP_STREAM_ROWS_IDLE * D->E && experts_met(D) * (D->F / 128) < CUS;
+}
+// One token to a few, so that a tile of 16 rows holds every expert's rows: the kernels of ffn_few.hip (streaming = 1).
+// Gate/up while the streaming blocks leave the chip half empty or in an uneven second round.  By units of 128 features, d = 4096:
+// 66 units 0.81, 132 0.79, 198 0.98, 308 0.91; d = 5120: 96 0.88, 192 0.90, 264 0.89, 336 level; shorter rows pay for the ends of a
+// block (d = 2048: 48 units 0.82, 132 0.94, 168 level, 234 1.17), longer ones keep a streaming block busy (d = 7168: 20 0.46, 64 0.73,
+// 128 1.10, 256 1.10).
+// Down, six blocks of 25 KB to a CU: whatever their number where K = F is long enough for the ends of a block not
+// to count.  F = 1280, 6144 features, 1152..14054 blocks: 0.85..0.96; 1408, 768..6496: 0.94..1.00; 1536, 1280..13188: 0.86..1.00; 2048,
+// 4096 features, 1024..10550: 0.98..1.03, 2048 features, 512..6526: 0.81..1.04, 7168 features, 1792..22840: 0.96..1.03, level.
+// Shorter ones up to 1400 blocks: F = 768 0.93..1.00, beyond them 1464..6496 0.97..1.15; F = 1024, 2796..7913 1.02, 1.01, 0.95.
+inline bool gate_up_few(const moe_dims* D) {
+    if (D->T > FEW_ROWS || !gate_up_streams(D)) return false;
+    const double units = experts_met(D) * (D->F / 128);
+    return units < (D->d >= 6144 ? 112 : D->d >= 3072 ? 320 : 200);
+}
+inline bool down_few(const moe_dims* D) {
+    return D->T <= FEW_ROWS && down_form(D) == Down::STREAM && (D->F >= 1280 || experts_met(D) * (D->d / 32) <= 1400);
+}
+inline bool linear_streams(int32_t rows, int32_t NOUT) {
+    return rows <= STREAM_ROWS || ((int64_t)rows + STREAM_ROWS - 1) / STREAM_ROWS * ((NOUT + 255) / 256) <= LINEAR_STREAM_UNITS;
+}
+
+// 129..160 rows can make two tiles, one of them of 64 rows (us, as chosen / one tile: 130 x 1024 x 22016 12.1 / 13.4, 150 x 4096 x
+// 24576 39.0 / 41.3, 160 x 7168 x 32768 65.2 / 70.3)
+inline int linear_tiles(int32_t rows, int nft, int nkb) {
+    int tiles[HEIGHTS];
+    for (int j = 0; j < HEIGHTS; ++j) tiles[j] = (int)(((int64_t)rows + tile_height(j) - 1) / tile_height(j));
+    const int h = pick_height(tiles, (int)(((int64_t)rows + 31) / 32), nft, nkb, (int64_t)1 << 30);
+    return (int)(((int64_t)rows + h - 1) / h);
+}
+
+// upper bound on row tiles: every full tile, and one more for each expert that has rows
+inline int64_t max_row_tiles(const moe_dims* D, int rows) {
+    const int64_t N = (int64_t)D->T * D->k;
+    return N / rows + (N < D->E ? N : D->E);
+}
+// Room of a big-tile list, and blocks of its launch: the least height that can be the better one has to fit.  A first round that is
+// not full may gain from half the height; the more rounds, the less there is to gain.  us, this room / room for half the height
+// everywhere / for 256 alone, gate/up | down: 16 x 3072 x 2048 at 750 rows (992 | 744 units) 172 / 172 / 184 | 99 / 100 / 112, 32 x 3072 x
+// 2048 at 260 (1008 | 756) 150 / 150 / 150 | 82 / 82 / 99, 64 x 2048 x 768 at 400 109 / 109 / 108 | 100 / 89 / 94, 32 x 7168 x 2048 at
+// 520 (1552 | 2716) 501 / 513 / 507 | 308 / 311 / 310, 128 x 5120 x 1536 at 300 (3324 | 5540) 755 / 762 / 759 | 477 / 478 / 480: beyond a
+// few rounds level, and the longer list would be room and blocks for nothing.
+// The choice itself is not free (777 tokens x 5 of 60 experts 1.3 us, 256 x 6 of 64 0.8): experts with a mean of up to 96 rows are one
+// tile each whatever the height, but for a few of a skewed load.
+constexpr int64_t ONE_HEIGHT_ROWS = 96;
+inline bool one_height(const moe_dims* D) { return (int64_t)D->T * D->k <= ONE_HEIGHT_ROWS * D->E; }
+inline int64_t big_units(const moe_dims* D, int nft) {
+    const int64_t units = max_row_tiles(D, TOK_TILE) * nft, half = max_row_tiles(D, TOK_TILE / 2) * nft;
+    if (one_height(D)) return units;
+    if (half <= 2 * CUS) return half;
+    return units <= 8 * CUS ? max_row_tiles(D, 192) * nft : units <= 16 * CUS ? max_row_tiles(D, 224) * nft : units;
+}
+inline int64_t gate_up_units(const moe_dims* D) {
+    if (!gate_up_streams(D)) return big_units(D, D->F / 128);
+    return max_row_tiles(D, gate_up_few(D) ? FEW_ROWS : STREAM_ROWS) * (D->F / 128);
+}
+inline int64_t down_stream_units(const moe_dims* D) { return max_row_tiles(D, STREAM_ROWS) * ((D->d + 255) / 256); }
+// EITHER: S > 2B tiles of 64 / of 256 rows over m experts with rows (B >= m, S <= (N + 63m)/64) leave m <= N/65
+inline int64_t down_big_units(const moe_dims* D) {
+    const int64_t N = (int64_t)D->T * D->k;
+    const int nft = (D->d + 255) / 256;
+    return down_form(D) == Down::EITHER ? (N / TOK_TILE + N / 65) * nft : big_units(D, nft);
+}
+
+inline ListShape gate_up_shape(const moe_dims* D) { return {D->F / 128, D->d / QBLOCK, (int)gate_up_units(D), one_height(D)}; }
+inline ListShape down_shape(const moe_dims* D) { return {(D->d + 255) / 256, D->F / QBLOCK, (int)down_big_units(D), one_height(D)}; }
+
+// Dense linear, up to how many blocks of 32 features ffn_few.hip is the better kernel, one to a CU (streaming kernel = 1): 256 blocks, 16-row tiles 16 x 4096 x 8192
+// 0.71, 32-row 32 x 4096 x 8192 0.76, 64-row 40 x 4096 x 8192 0.85, 64 x 4096 x 8192 0.97, 128 x 7168 x 4096 0.94, 256 x 4096 x 2048
+// 0.83; 384 blocks of 16-row tiles (75 KB, two to a CU) 0.91..1.02, of 32-row tiles 1.2, 512 of 64-row tiles 1.5.  Tiles of 32 rows
+// while they fit too (128 x 4096 x 2048 0.62 against 0.83 in tiles of 64).
+constexpr int FEW_BLOCKS = 256, FEW_BLOCKS_16 = 320;
+inline int few_linear_groups(int32_t rows, int32_t NOUT) {           // 16-row groups per tile; 0: another kernel is the better one
+    const int64_t cols = NOUT / 32;
+    if (rows <= 16) return cols <= FEW_BLOCKS_16 ? 1 : 0;
+    if (((int64_t)rows + 31) / 32 * cols <= FEW_BLOCKS) return 2;
+    return ((int64_t)rows + 63) / 64 * cols <= FEW_BLOCKS ? 4 : 0;
+}
+
+}  // namespace moe355

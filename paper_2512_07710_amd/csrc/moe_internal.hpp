@@ -104,7 +104,6 @@ hipError_t set_few_lds_limits();
 hipError_t launch_few_gate_up(moe_ctx* c, const uint8_t* xq, const float* xs, const int32_t* perm, const int32_t* offsets,
                               int max_tiles, const uint8_t* W1, const uint8_t* W3, const float* s1, const float* s3);
 hipError_t launch_few_down(moe_ctx* c, const int32_t* offsets, int max_tiles, const uint8_t* W2, const float* s2, float* y_perm);
-int few_linear_groups(int32_t rows, int32_t NOUT);             // 16-row groups per tile; 0: another kernel is the better one
 hipError_t launch_few_linear(moe_ctx* c, const uint8_t* xq, const float* xs, int32_t rows, int32_t K, const uint8_t* Wq,
                              const float* ws, int32_t NOUT, float* y);
 size_t route_workspace_bytes(int E, int d);

@@ -16,14 +16,18 @@ def _codes(g, *shape):
     return (torch.randn(shape, generator=g, device="cuda") * 60).to(torch.float8_e4m3fn).view(torch.uint8)
 
 
-# all above 128 big tiles, so that none streams: one ragged row tile, two and four, many with a last one of five rows, and 3 to
-# 8 groups of 32 rows in a tile, odd and even
-@pytest.mark.parametrize("rows,K,NOUT", [(70, 384, 259 * 128), (129, 128, 257 * 128), (193, 256, 258 * 128), (257, 256, 131 * 128),
-                                         (300, 1280, 131 * 128), (777, 128, 67 * 128), (130 * 256 + 5, 256, 128), (9000, 640, 9 * 128)])
+# all above 256 streaming units, so that none streams (which tiles they get: tests/test_tile_rules_host.py): one ragged row tile, two and
+# four, many with a last one of five rows, and 2 to 8 groups of 32 rows in a tile, odd and even
+BIG_LINEARS = [(70, 384, 259 * 128), (129, 128, 257 * 128), (193, 256, 258 * 128), (257, 256, 131 * 128), (300, 1280, 131 * 128),
+               (777, 128, 67 * 128), (130 * 256 + 5, 256, 128), (9000, 640, 9 * 128),
+               (130, 640, 172 * 128), (150, 1024, 181 * 128), (160, 384, 176 * 128), (3000, 256, 42 * 128)]
+
+
+@pytest.mark.parametrize("rows,K,NOUT", BIG_LINEARS)
 def test_big_tile_linear_at_ragged_sizes(gpu_lib, rows, K, NOUT):
     """Every row of the product: against the same rows in calls of 64, which stream (the same instructions in the same order, so
     the same bits), and against a 64-bit evaluation (bar 1e-4: the matrix pipe's own rounding is 1.3e-5)."""
-    assert (rows + 255) // 256 * ((NOUT + 255) // 256) > 128
+    assert (rows + 63) // 64 * ((NOUT + 255) // 256) > 256
     g = torch.Generator(device="cuda").manual_seed(rows + K)
     xq, wq = _codes(g, rows, K), _codes(g, NOUT, K)
     xs = torch.rand((K // 128, rows), generator=g, device="cuda") + 0.5

@@ -182,16 +182,35 @@ def test_layer_under_hip_graph_capture(gpu_lib, mode):
             layer.close()
 
 
-@pytest.mark.parametrize("d,F", [(128, 128), (384, 256), (256, 640)])
-def test_tile_heights(gpu_lib, d, F):
-    """Replay logs (k = 1) that give the experts row counts around every tile height the grouped GEMMs distinguish: the
-    narrow tile's limit, each number of 32-row groups a wave can have (odd and even), one row over a full tile, and splits
-    of two and three tiles; one, two, three and five K blocks; output feature tiles that are half empty."""
-    counts = [0, 1, 31, 32, 33, 64, 65, 95, 97, 128, 129, 160, 161, 192, 193, 223, 225, 255, 256, 257, 289, 320, 511, 513, 600]
+# Row counts around every size that the big tiles of the grouped GEMMs distinguish: the narrow tile's limit, each number of 32-row
+# groups, one row over a full tile, splits of two and three tiles.  The launch's tile height depends on all counts and on the shape;
+# tests/test_tile_rules_host.py asks the rule which heights and tiles these layers get: in both projections every height, every number
+# of groups an expert's only tile or one of several can have, with one and with more K blocks, also in half-empty feature tiles.
+HEIGHT_COUNTS = [0, 1, 31, 32, 33, 64, 65, 95, 97, 128, 129, 160, 161, 192, 193, 223, 225, 255, 256, 257, 289, 320, 511, 513, 600]
+HEIGHT_SHAPES = [(128, 128), (384, 256), (256, 640)]
+_MIXED = [150, 185, 215, 250, 80, 40, 300, 420, 520, 700]
+HEIGHT_LAYERS = [([189, 189, 191, 20], 128, 128), ([226, 217, 194], 384, 128), ([247, 249, 247], 128, 384),
+                 (_MIXED * 5, 128, 128), (_MIXED * 7, 384, 256)]
+
+
+def _run_heights(gpu_lib, counts, d, F):
     cfg = MoEConfig("heights", T=sum(counts), d=d, E=len(counts), k=1, F=F, modes=("replay",), seed=d + F)
     rng = np.random.default_rng(cfg.seed)
     ids = rng.permutation(np.repeat(np.arange(cfg.E, dtype=np.int32), counts)).reshape(cfg.T, 1)
     _run_and_check_layer(gpu_lib, cfg, "replay", log=(np.ascontiguousarray(ids), np.ones((cfg.T, 1), dtype=np.float32)))
+
+
+@pytest.mark.parametrize("d,F", HEIGHT_SHAPES)
+def test_tile_heights(gpu_lib, d, F):
+    """Replay logs (k = 1) that give the experts all of HEIGHT_COUNTS; one, two, three and five K blocks; output feature tiles that are
+    half empty."""
+    _run_heights(gpu_lib, HEIGHT_COUNTS, d, F)
+
+
+@pytest.mark.parametrize("counts,d,F", HEIGHT_LAYERS, ids=lambda v: f"{len(v)}experts" if isinstance(v, list) else str(v))
+def test_chosen_tile_heights(gpu_lib, counts, d, F):
+    """Loads that make the launch take the other heights."""
+    _run_heights(gpu_lib, counts, d, F)
 
 
 @pytest.mark.parametrize("rows", [1, 15, 16, 17, 31, 32, 33, 48, 65])
@@ -272,17 +291,22 @@ def test_weight_streaming_tiles(gpu_lib, d, F):
     _run_and_check_layer(gpu_lib, cfg, "replay", log=(np.ascontiguousarray(ids), np.ones((cfg.T, 1), dtype=np.float32)))
 
 
-@pytest.mark.parametrize("rows,K,NOUT", [(1, 128, 128), (33, 256, 384), (64, 8320, 640), (65, 384, 256), (300, 1280, 1152)])
+# in small blocks, and streaming
+SMALL_LINEARS = [(1, 128, 128), (33, 256, 384), (64, 8320, 640), (65, 384, 256), (300, 1280, 1152),
+                 (33, 256, 65 * 128), (64, 8320, 65 * 128), (300, 1280, 13 * 128)]
+
+
+@pytest.mark.parametrize("rows,K,NOUT", SMALL_LINEARS)
 def test_small_linears_equal_the_big_tile_kernel(gpu_lib, rows, K, NOUT):
-    """Dense products small enough for the streaming kernel against the same rows inside a product that takes the big
-    tiles: the same instructions in the same order, so the same bits."""
-    big = 256 * 200                                                     # rows of the large product: over 128 big tiles
+    """Dense products small enough for the small-block or the streaming kernel against the same rows inside a product that takes the
+    big tiles: the same products in the same order, so the same bits."""
+    big = 256 * 200                                                     # rows of the large product: over 256 streaming units
     g = torch.Generator(device="cuda").manual_seed(rows + K)
     codes = lambda *s: (torch.randn(s, generator=g, device="cuda") * 60).to(torch.float8_e4m3fn).view(torch.uint8)
     xq, wq = codes(big, K), codes(NOUT, K)
     xs = torch.rand((K // 128, big), generator=g, device="cuda") + 0.5
     ws = torch.rand((NOUT // 128, K // 128), generator=g, device="cuda") + 0.5
-    ctx = gpu_lib.moe_create(big, K, 1, 1, 128 * 8)
+    ctx = gpu_lib.moe_create(big, K, 1, 1, max(NOUT, 128 * 8))
     try:
         y_big = torch.empty((big, NOUT), device="cuda")
         gpu_lib.moe_linear_fp8(ctx, xq, xs, big, K, wq, ws, NOUT, y_big)

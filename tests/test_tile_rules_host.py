@@ -1,0 +1,137 @@
+"""The rules that choose a GEMM's kernel and the heights of its row tiles (csrc/ffn_rules.hpp), compiled for the host: what the GPU
+tests' shapes reach, so that a change of a rule cannot empty those tests, and that tiles cover the rows and fit the lists."""
+import random
+import subprocess
+
+import pytest
+
+import test_gpu_dispatch as dispatch
+import test_gpu_edges as edges
+from paper_2512_07710_amd.build import CSRC, HIPCC, ROOT
+
+PROGRAM = r"""
+#include "ffn_rules.hpp"
+#include <cstdio>
+#include <vector>
+using namespace moe355;
+static int height(const ListShape& s, const std::vector<int>& c, long& units) {
+    int tiles[HEIGHTS] = {}, groups = 0;
+    for (int n : c) {
+        groups += (n + 31) / 32;
+        for (int j = 0; j < HEIGHTS; ++j) tiles[j] += (n + tile_height(j) - 1) / tile_height(j);
+    }
+    const int h = list_height(s, tiles, groups);
+    units = 0;
+    for (int j = 0; j < HEIGHTS; ++j) if (tile_height(j) == h) units = (long)tiles[j] * s.n_ft;
+    return h;
+}
+int main() {
+    char what;
+    while (scanf(" %c", &what) == 1) {
+        if (what == 'L') {                                     // rows K NOUT -> form, rows of the tiles
+            int rows, K, NOUT;
+            if (scanf("%d %d %d", &rows, &K, &NOUT) != 3) return 1;
+            if (few_linear_groups(rows, NOUT)) printf("few %d\n", few_linear_groups(rows, NOUT));
+            else if (linear_streams(rows, NOUT)) printf("stream\n");
+            else {
+                printf("big");
+                const int nt = linear_tiles(rows, (NOUT + 255) / 256, K / QBLOCK);
+                for (int i = 0; i < nt; ++i) { Work w; split_rows(rows, nt, i, w); printf(" %d", w.nrows); }
+                printf("\n");
+            }
+        } else {                                               // d F E k counts -> forms; height, units, room, then rows:tiles of each
+            moe_dims D{};
+            if (scanf("%d %d %d %d", &D.d, &D.F, &D.E, &D.k) != 4) return 1;
+            std::vector<int> c(D.E);
+            int N = 0;
+            for (int& n : c) { if (scanf("%d", &n) != 1) return 1; N += n; }
+            D.T = N / D.k;
+            printf("%s %s\n", gate_up_few(&D) ? "few" : gate_up_streams(&D) ? "stream" : "big",
+                   down_few(&D) ? "few" : down_form(&D) == Down::STREAM ? "stream" : down_form(&D) == Down::BIG ? "big" : "either");
+            for (int list = 0; list < 2; ++list) {
+                const ListShape s = list ? down_shape(&D) : gate_up_shape(&D);
+                long units;
+                const int h = height(s, c, units);
+                printf("%d %ld %d", h, units, s.capacity);
+                for (int n : c)
+                    for (int i = 0, nt = (n + h - 1) / h, at = 0; i < nt; ++i) {
+                        Work w;
+                        split_rows(n, nt, i, w);
+                        if (w.row0 != at) return 2;
+                        at += w.nrows;
+                        if (i == nt - 1 && at != n) return 3;
+                        printf(" %d:%d", w.nrows, w.tiles);
+                    }
+                printf("\n");
+            }
+        }
+    }
+    return 0;
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def rules(tmp_path_factory):
+    d = tmp_path_factory.mktemp("rules")
+    (d / "rules.hip").write_text(PROGRAM)
+    subprocess.run([HIPCC, "--cuda-host-only", "-O2", "-std=c++17", "-I", CSRC, "-I", ROOT + "/include", str(d / "rules.hip"), "-o",
+                    str(d / "rules")], check=True, capture_output=True)
+
+    def ask(text):
+        return subprocess.run([str(d / "rules")], input=text, check=True, capture_output=True, text=True).stdout.splitlines()
+    return ask
+
+
+def _layer(rules, counts, d, F, k=1):
+    """((form, height, units, room, [(rows, tiles of the expert)]) of the gate/up projection, of the down projection)"""
+    forms, *lists = rules(f"G {d} {F} {len(counts)} {k} " + " ".join(map(str, counts)))
+    out = []
+    for form, line in zip(forms.split(), lists):
+        h, units, room, *tiles = line.split()
+        out.append((form, int(h), int(units), int(room), [tuple(map(int, t.split(":"))) for t in tiles]))
+    return out
+
+
+def test_tile_height_layers_reach_every_height_and_group_count(rules):
+    heights, groups = [set(), set()], [set(), set()]
+    shapes = [(edges.HEIGHT_COUNTS, d, F) for d, F in edges.HEIGHT_SHAPES] + edges.HEIGHT_LAYERS
+    for counts, d, F in shapes:
+        for p, (form, h, _, _, tiles) in enumerate(_layer(rules, counts, d, F)):
+            assert form == "big"
+            heights[p].add(h)
+            groups[p] |= {((n + 31) // 32, nt > 1, "one K block" if (d, F)[p] == 128 else "more", p == 1 and d // 128 % 2 == 1)
+                          for n, nt in tiles}
+    for p in range(2):
+        assert heights[p] == {256, 224, 192, 160, 128}
+        for want in ("one K block", "more"):
+            met = {(g, shared) for g, shared, k_blocks, _ in groups[p] if k_blocks == want}
+            # narrow tiles alone, two groups beside a taller tile, full tiles alone and as one of several
+            assert met >= {(1, False), (2, False), (2, True)} | {(g, False) for g in range(3, 9)} | {(g, True) for g in range(3, 8)}
+    assert {g for g, _, _, half_empty in groups[1] if half_empty} == set(range(1, 9))
+
+
+def test_linear_shapes_reach_what_they_are_for(rules):
+    form = lambda r, K, n: rules(f"L {r} {K} {n}")[0].split()
+    met = set()
+    for shape in dispatch.BIG_LINEARS:
+        kind, *rows = form(*shape)
+        assert kind == "big" and sum(map(int, rows)) == shape[0]
+        met |= {(int(n) + 31) // 32 for n in rows}
+    assert met >= set(range(2, 9))
+    assert {form(*s)[0] for s in edges.SMALL_LINEARS} == {"few", "stream"}
+
+
+def test_lists_have_room_for_their_units(rules):
+    """Random loads, even to concentrated: whatever height is taken, its units fit the list (and the launch) made for it."""
+    rng = random.Random(1)
+    for _ in range(300):
+        E, k = rng.randint(1, 256), 1
+        mean = 2 ** rng.uniform(0, 10)
+        p = [rng.random() ** rng.choice([0, 1, 4, 30]) for _ in range(E)]
+        counts = [int(mean * E * v / sum(p)) for v in p]
+        if sum(counts) == 0 or max(counts) > 60000:
+            continue
+        for form, _, units, room, _ in _layer(rules, counts, 128 * rng.randint(1, 56), 128 * rng.randint(1, 16)):
+            if form == "big":
+                assert units <= room
