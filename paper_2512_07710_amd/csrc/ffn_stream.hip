@@ -271,7 +271,8 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
 // five stages (one block per CU) the same or worse.
 constexpr int NW = 4, D = 3;
 // A dense product of at most 64 units leaves half of the CUs idle in blocks of four waves: two waves and four stages
-// (40 rows x 4096 x 6144: 18.6 -> 17.4 us, 256 rows x 4096: 20.6 -> 18.9; 128 units: 22.3 -> 24.0).
+// (40 x 4096 x 10240, 40 units, 18.3 -> 14.0 us, 40 x 7168 x 12288 30.5 -> 22.3, 256 x 4096 x 4096, 64 units, 15.8 -> 13.5; 128 units:
+// 22.3 -> 24.0).
 constexpr int NW_FEW = 2, D_FEW = 4, FEW_UNITS = 64;
 // Weights that are read once go past the caches: a whole layer's experts never stay in the 256 MB last-level cache until the
 // next step of a model (one sequence, 104 MB of weights, after other data: 76 us for the layer through the caches, 67 past
@@ -279,8 +280,8 @@ constexpr int NW_FEW = 2, D_FEW = 4, FEW_UNITS = 64;
 // in turns on several sets of weights and inputs: 39.8, 51.4, 57.3 us through the caches, 37.4, 49.2, 53.0 past them); repeated on
 // the same weights with nothing between they pay for it (256 tokens x 2 of 2048 x 1024, 16 experts 35.2 / 36.1, 128 x 2 of 4096 x
 // 2048, 8 experts 48.2 / 57.2, the form before either 63.6), which no model does.
-// A dense matrix of up to this size may well stay (40 rows x 4096 x 6144: 25.4 and 24.4 us after other data, 16.6 and
-// 17.0 when it is still there), beyond it cannot.
+// A dense matrix of up to this size may well stay (40 rows x 4096 x 6144, in this kernel: 25.4 and 24.4 us after other data, 16.6
+// and 17.0 when it is still there), beyond it cannot.
 constexpr int64_t LINEAR_ONCE_BYTES = 256ll << 20;
 
 template <int WAVES, int STAGES, bool GATED, bool GATHER, bool GROUPED, bool CHOSEN = false>
