@@ -304,9 +304,11 @@ __device__ __forceinline__ void k_loop(const Tile& t, const Feed& f, v16f (&acc)
 
     int wslot = 0;                                             // ring slot of weight block kb
     int kb = 0;
-    // (the loop's place in the instruction cache's lines is worth 0.6 % to short tiles: 128 experts of 250..262 rows x 5120 x 1536 gate/up
-    // 645..648 us at multiples of 64 bytes, 651 and 652 at 24 of 64, as other code happened to push it)
-    asm volatile(".p2align 6");
+    // Gate/up loops start on a multiple of 64 bytes.  Where a loop lies, modulo 32 bytes, is worth up to 6 % either way, and what other code
+    // of the kernel happens to make of it changes with every edit: 128 experts of 250..262 rows x 5120 x 1536 645..648 us here, 651
+    // and 652 at 24 of 64.  The dense and the down projection's loops lie well as they are (linear 473 x 3712 x 9216 27.4 us,
+    // on a multiple of 64 28.1).
+    if (GATED) asm volatile(".p2align 6");
     do {                                                       // (K >= 128: at least one block)
         const int wnext = (wslot == NW_BUF - 1) ? 0 : wslot + 1;
         const int wprev = (wslot == 0) ? NW_BUF - 1 : wslot - 1;             // slot of block kb-1 = of block kb+2
