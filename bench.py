@@ -247,8 +247,8 @@ def main() -> int:
     roof = dict(res["roofline"])
     traffic, src = _recorded_traffic(args.config)
     roof.update({"traffic": traffic,
-                 "traffic_source": None if src is None else f"recorded in {src} (rocprofv3 --pmc FETCH_SIZE and WRITE_SIZE "
-                                                            "runs of this command), not measured in this run",
+                 "traffic_source": None if src is None else f"recorded in {src} (rocprofv3 counter passes over the same "
+                                                            "layer), not measured in this run",
                  "algorithmic_bytes": priv["gemm1_bytes"], "avg_launch_ms": res["gemm1_ms"],
                  "flop_per_launch": priv["gemm1_flop"]})
     kernels = {"gemm1_ms": res["gemm1_ms"], "gemm2_ms": res["gemm2_ms"],
