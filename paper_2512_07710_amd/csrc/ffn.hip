@@ -4,7 +4,7 @@
 // small kernel turns offsets[] into the list of work units (expert, first row, feature tile,
 // rows), so ragged experts need no host round trip, and orders it so that units sharing a
 // weight tile are adjacent; blocks map onto the list so that each XCD (blockIdx % 8) walks a
-// contiguous range and its L2 sees every weight tile once.
+// contiguous range, of equal cost, and its L2 sees every weight tile once (ffn_rules.hpp).
 //
 // Main loop, one iteration per 128-wide K block (= one scale block):
 //   * both operand tiles are copied global -> LDS by direct-to-LDS loads (no staging
@@ -61,12 +61,12 @@ __device__ inline int wave_scan(int v) {
     return v;
 }
 // Block (e, l) writes the units of expert e into list l (0: gate/up, 1: down); every block recomputes the tile counts of all
-// experts for its base index and the height.
-// choose: list 1 is left empty (n_work[1] = 0) unless the batch is concentrated, see DOWN_SKEW_UNITS.
+// experts for its base index and the height, and block (0, l) deals the list to the XCDs.
+// choose: list 1 is left empty (queue->total = 0) unless the batch is concentrated, see DOWN_SKEW_UNITS.
 __device__ inline void build_work(const int32_t* __restrict__ offsets, int E, int e, int list, const ListShape& shape, bool choose,
-                                  Work* __restrict__ work, int32_t* __restrict__ n_work) {
+                                  Work* __restrict__ work, Queue* __restrict__ queue, Rest* __restrict__ rest) {
     constexpr int SUMS = HEIGHTS + 2, WAVES = MAX_E / 64;      // tiles at each height, groups of 32 rows, tiles of 64
-    __shared__ int32_t s_sums[WAVES][SUMS], s_scan[WAVES], s_base;
+    __shared__ int32_t s_sums[WAVES][SUMS], s_scan[WAVES], s_cost[WAVES], s_begin[NXCD + 1], s_base;
     const int tid = threadIdx.x, wave = tid >> 6;
     const int n_ft = shape.n_ft;
     const int rows_t = tid < E ? offsets[tid + 1] - offsets[tid] : 0;
@@ -88,17 +88,40 @@ __device__ inline void build_work(const int32_t* __restrict__ offsets, int E, in
 #pragma unroll
     for (int j = 1; j < HEIGHTS; ++j) total = h == tile_height(j) ? tiles[j] : total;
     const bool empty = choose && list == 1 && sums[HEIGHTS + 1] <= 2 * tiles[0];
-    if (e == 0 && tid == 0) n_work[list] = empty ? 0 : total * n_ft;
-    if (empty) return;
-    const int before = wave_scan((rows_t + h - 1) / h);        // tiles up to expert tid, in its wave
-    if ((tid & 63) == 63) s_scan[wave] = before;
+    if (e == 0 && tid == 0) queue->total = empty ? 0 : total * n_ft;
+    if (empty) {
+        if (e == 0 && tid < NXCD) queue->fixed[tid] = 0;
+        if (e == 0 && tid == 0) queue->helpers = 0;
+        return;
+    }
+    const int nt_t = (rows_t + h - 1) / h, cost_t = tiles_share(nt_t, (rows_t + 31) / 32);
+    int tiles_to = wave_scan(nt_t), cost_to = wave_scan(cost_t);    // up to and with expert tid, first in its wave
+    if ((tid & 63) == 63) {
+        s_scan[wave] = tiles_to;
+        s_cost[wave] = cost_to;
+    }
+    if (tid <= NXCD) s_begin[tid] = tid == 0 ? 0 : total * n_ft;
     __syncthreads();
-    if (tid == e) {
-        int base = before - (rows_t + h - 1) / h;
-        for (int w = 0; w < wave; ++w) base += s_scan[w];
-        s_base = base;
+    int cost_all = 0;
+    for (int w = 0; w < WAVES; ++w) {
+        if (w < wave) tiles_to += s_scan[w];
+        if (w < wave) cost_to += s_cost[w];
+        cost_all += s_cost[w];
+    }
+    if (tid == e) s_base = tiles_to - nt_t;
+    if (e == 0 && nt_t > 0) {
+        // the XCD boundaries that fall into expert tid, on whole feature tiles (their row tiles share the weights)
+        const float per_cost = (float)n_ft / (float)cost_t;
+#pragma unroll
+        for (int x = 1; x < NXCD; ++x) {
+            const int in = (int)((int64_t)cost_all * x / NXCD) - (cost_to - cost_t);
+            if (in < 0 || in >= cost_t) continue;
+            s_begin[x] = (tiles_to - nt_t) * n_ft + min((int)((float)in * per_cost), n_ft - 1) * nt_t;
+        }
     }
     __syncthreads();
+    if (e == 0 && tid == 0) deal(s_begin, list_blocks(shape.capacity) / NXCD, *queue);
+    if (e == 0 && tid < NXCD) rest[tid].taken = 0;
     const int start = offsets[e], cnt = offsets[e + 1] - start;
     const int nt = (cnt + h - 1) / h;
     if (nt == 0) return;
@@ -112,6 +135,29 @@ __device__ inline void build_work(const int32_t* __restrict__ offsets, int E, in
         w.ft = f;
         work[base + idx] = w;
     }
+}
+
+// A unit of what the XCDs have left over, for a block with no unit of its own: of its own XCD while there are any, then of the one
+// with the most.  -1: none anywhere.  One thread of the block calls it.
+__device__ inline int take_rest(const Queue* __restrict__ q, Rest* __restrict__ rest, int x) {
+    for (int tries = 0; tries <= NXCD; ++tries) {              // (a try that fails has found one more XCD's rest used up, for good)
+        const int own = q->begin[x + 1] - q->begin[x] - q->fixed[x];
+        if (own > 0) {
+            const int t = __hip_atomic_fetch_add(&rest[x].taken, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (t < own) return q->begin[x] + q->fixed[x] + t;
+        }
+        int taken[NXCD], most = 0;
+#pragma unroll
+        for (int y = 0; y < NXCD; ++y) taken[y] = __hip_atomic_load(&rest[y].taken, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+        for (int y = 0; y < NXCD; ++y) {
+            const int left = q->begin[y + 1] - q->begin[y] - q->fixed[y] - taken[y];
+            x = left > most ? y : x;
+            most = max(most, left);
+        }
+        if (most == 0) return -1;
+    }
+    return -1;
 }
 
 // ------------------------------------------------------------------ helpers
@@ -400,7 +446,8 @@ __global__ __launch_bounds__(NTHREADS, 1) void ffn_gemm(const uint8_t* __restric
                                                         const float* __restrict__ act_s, int n_rows,
                                                         const int32_t* __restrict__ perm, int fan, int n_tok,
                                                         const Work* __restrict__ work,
-                                                        const int32_t* __restrict__ n_work,
+                                                        const Queue* __restrict__ queue,
+                                                        Rest* __restrict__ rest,
                                                         const uint8_t* __restrict__ Wa,
                                                         const uint8_t* __restrict__ Wb,
                                                         const float* __restrict__ sa,
@@ -413,20 +460,27 @@ __global__ __launch_bounds__(NTHREADS, 1) void ffn_gemm(const uint8_t* __restric
     // exchange of the epilogue reuses the first bytes once the main loop is over.
     float* const s_amax = reinterpret_cast<float*>(smem);
 
-    // ---- which work unit: XCD x (= blockIdx % 8) walks the contiguous range [x*chunk, (x+1)*chunk)
-    // (LINEAR: one "expert" owns all n_rows rows in `fan` row tiles, and the unit is worked out here instead of read from a list)
-    const int tiles = fan;
-    const int total = LINEAR ? tiles * ((NOUT + FT - 1) / FT) : *n_work;
-    const int chunk = (total + NXCD - 1) / NXCD;
-    const int slot = blockIdx.x / NXCD;
-    const int wi = (blockIdx.x % NXCD) * chunk + slot;
-    if (slot >= chunk || wi >= total) return;
+    // ---- which work unit: XCD x (= blockIdx % 8) walks the contiguous range of the list that it has been dealt, and then helps the others
+    const int xcd = blockIdx.x % NXCD, slot = blockIdx.x / NXCD;
     Work wk;
     if (LINEAR) {
+        // one "expert" owns all n_rows rows in `fan` row tiles, and the unit is worked out here instead of read from a list
+        const int tiles = fan, total = tiles * ((NOUT + FT - 1) / FT), chunk = (total + NXCD - 1) / NXCD;
+        const int wi = xcd * chunk + slot;
+        if (slot >= chunk || wi >= total) return;
         wk.expert = 0;
         wk.ft = wi / tiles;
         split_rows(n_rows, tiles, wi - wk.ft * tiles, wk);
     } else {
+        int wi = queue->begin[xcd] + slot;
+        if (slot >= queue->fixed[xcd]) {
+            if (slot >= queue->fixed[xcd] + queue->helpers) return;
+            int32_t& s_unit = *reinterpret_cast<int32_t*>(smem + X_RING - 16);
+            if (threadIdx.x == 0) s_unit = take_rest(queue, rest, xcd);
+            __syncthreads();                                   // (the last weight slot, first copied to behind another barrier)
+            wi = __builtin_amdgcn_readfirstlane(s_unit);
+            if (wi < 0) return;
+        }
         wk = work[wi];
     }
     const int e = wk.expert;
@@ -763,6 +817,7 @@ static int64_t gate_up_list(const moe_dims* D) { return gate_up_streams(D) ? 0 :
 size_t ffn_work_bytes(const moe_dims* D) {
     return sizeof(Work) * (size_t)(gate_up_list(D) + (down_form(D) == Down::STREAM ? 0 : down_big_units(D)) + 1);
 }
+size_t ffn_queue_bytes() { return 2 * (sizeof(Queue) + NXCD * sizeof(Rest)); }
 size_t ffn_ticket_bytes(const moe_dims* D) { return gate_up_streams(D) ? sizeof(int32_t) * (size_t)gate_up_units(D) : 0; }
 size_t ffn_h_rows_bytes(const moe_dims* D) {
     return gate_up_streams(D) ? sizeof(float) * (size_t)((int64_t)D->T * D->k) * (size_t)D->F : 0;
@@ -791,12 +846,12 @@ static hipError_t set_lds_limits() {
 // out[g][p] = in[g][perm[p] / fan].
 __global__ __launch_bounds__(256) void prepare_big_tiles(const int32_t* __restrict__ offsets, int E, int lists, ListShape shape0,
                                                          ListShape shape1, bool choose, Work* __restrict__ work0,
-                                                         Work* __restrict__ work1, int32_t* __restrict__ n_work,
+                                                         Work* __restrict__ work1, Queue* __restrict__ queues, Rest* __restrict__ rests,
                                                          const float* __restrict__ in, int T, const int32_t* __restrict__ perm,
                                                          int fan, int N, float* __restrict__ out) {
     if ((int)blockIdx.x < E * lists) {
         const int list = blockIdx.x / E;
-        build_work(offsets, E, blockIdx.x % E, list, list == 0 ? shape0 : shape1, choose, list == 0 ? work0 : work1, n_work);
+        build_work(offsets, E, blockIdx.x % E, list, list == 0 ? shape0 : shape1, choose, list == 0 ? work0 : work1, queues + list, rests + list * NXCD);
         return;
     }
     const uint32_t b = blockIdx.x - E * lists, row_blocks = (uint32_t)((N + 255) / 256);
@@ -825,16 +880,16 @@ hipError_t launch_expert_ffn(moe_ctx* c, const uint8_t* xq, const float* xs, con
     const Down down = down_form(&D);
     const int units1 = (int)gate_up_units(&D);
     Work* work2 = work + gate_up_list(&D);                     // the down projection's list
-    int32_t* n_work2 = c->n_tiles + 1;
+    Queue* const queues = reinterpret_cast<Queue*>(c->queues); // and how each of them is dealt to the XCDs
+    Rest* const rests = reinterpret_cast<Rest*>(queues + 2);
     if (!stream1) {                                            // (the streaming kernels need neither list nor sorted scales)
         const int lists = down == Down::STREAM ? 1 : 2;
         const int64_t gather = perm ? (int64_t)((N + 255) / 256) * (D.d / QBLOCK) : 0;
         hipLaunchKernelGGL(prepare_big_tiles, dim3((unsigned)(D.E * lists + gather)), dim3(256), 0, c->stream, offsets, D.E, lists,
                            gate_up_shape(&D), down_shape(&D), down == Down::EITHER,
-                           work, work2, c->n_tiles, xs, D.T, perm, D.k, N, c->xs_sorted);
+                           work, work2, queues, rests, xs, D.T, perm, D.k, N, c->xs_sorted);
     }
     if (ev) (void)hipEventRecord(ev[0], c->stream);          // the timed interval is the GEMM kernel alone
-    const int grid1 = (units1 + NXCD - 1) / NXCD * NXCD;
     if (gate_up_few(&D)) {
         hipError_t e = launch_few_gate_up(c, xq, xs, perm, offsets, (int)max_row_tiles(&D, FEW_ROWS), W1, W3, s1, s3);
         if (e != hipSuccess) return e;
@@ -843,8 +898,8 @@ hipError_t launch_expert_ffn(moe_ctx* c, const uint8_t* xq, const float* xs, con
         if (e != hipSuccess) return e;
     } else {
         auto launch = [&](auto kernel, const float* scales, int fan, int n_tok) {
-            hipLaunchKernelGGL(kernel, dim3(grid1), dim3(NTHREADS), SMEM_BYTES, c->stream, xq, scales, N, perm, fan, n_tok, work,
-                               c->n_tiles, W1, W3, s1, s3, D.d, D.F, c->hq, c->hs, (float*)nullptr);
+            hipLaunchKernelGGL(kernel, dim3(list_blocks(units1)), dim3(NTHREADS), SMEM_BYTES, c->stream, xq, scales, N, perm, fan, n_tok, work,
+                               queues, rests, W1, W3, s1, s3, D.d, D.F, c->hq, c->hs, (float*)nullptr);
         };
         if (perm) launch(ffn_gemm<true, true, false>, c->xs_sorted, D.k, D.T);
         else launch(ffn_gemm<true, false, false>, xs, 1, 1);
@@ -854,13 +909,12 @@ hipError_t launch_expert_ffn(moe_ctx* c, const uint8_t* xq, const float* xs, con
         hipError_t e = launch_few_down(c, offsets, (int)max_row_tiles(&D, FEW_ROWS), W2, s2, y_perm);
         if (e != hipSuccess) return e;
     } else if (down != Down::BIG) {
-        hipError_t e = launch_stream_down(c, offsets, (int)down_stream_units(&D), down == Down::EITHER ? n_work2 : nullptr, W2, s2, y_perm);
+        hipError_t e = launch_stream_down(c, offsets, (int)down_stream_units(&D), down == Down::EITHER ? &queues[1].total : nullptr, W2, s2, y_perm);
         if (e != hipSuccess) return e;
     }
     if (down != Down::STREAM) {
-        const int grid2 = ((int)down_big_units(&D) + NXCD - 1) / NXCD * NXCD;
-        hipLaunchKernelGGL((ffn_gemm<false, false, false>), dim3(grid2), dim3(NTHREADS), SMEM_BYTES, c->stream, c->hq, c->hs, N, (const int32_t*)nullptr, 1, 1,
-                           work2, n_work2, W2, (const uint8_t*)nullptr, s2, (const float*)nullptr, D.F, D.d, (uint8_t*)nullptr,
+        hipLaunchKernelGGL((ffn_gemm<false, false, false>), dim3(list_blocks((int)down_big_units(&D))), dim3(NTHREADS), SMEM_BYTES, c->stream, c->hq, c->hs, N, (const int32_t*)nullptr, 1, 1,
+                           work2, queues + 1, rests + NXCD, W2, (const uint8_t*)nullptr, s2, (const float*)nullptr, D.F, D.d, (uint8_t*)nullptr,
                            (float*)nullptr, y_perm);
     }
     if (ev) (void)hipEventRecord(ev[2], c->stream);
@@ -878,7 +932,7 @@ hipError_t launch_linear(moe_ctx* c, const uint8_t* xq, const float* xs, int32_t
     const int nft = (NOUT + 255) / 256, tiles = linear_tiles(rows, nft, K / KB);
     hipLaunchKernelGGL((ffn_gemm<false, false, true>), dim3((tiles * nft + NXCD - 1) / NXCD * NXCD), dim3(NTHREADS), SMEM_BYTES,
                        c->stream, xq, xs, rows, (const int32_t*)nullptr, tiles, 1, (const Work*)nullptr,
-                       (const int32_t*)nullptr, Wq, (const uint8_t*)nullptr, ws, (const float*)nullptr, K, NOUT,
+                       (const Queue*)nullptr, (Rest*)nullptr, Wq, (const uint8_t*)nullptr, ws, (const float*)nullptr, K, NOUT,
                        (uint8_t*)nullptr, (float*)nullptr, y);
     return hipGetLastError();
 }

@@ -9,7 +9,6 @@ typedef float v16f __attribute__((ext_vector_type(16)));
 typedef int v4i __attribute__((ext_vector_type(4)));
 
 constexpr int KB = QBLOCK;                        // K bytes per stage (= one scale block)
-constexpr int NXCD = 8;
 
 // Direct global -> LDS copies.  Lane i of the wave deposits its bytes at lds_addr + i*size;
 // the global address is sbase + voff (per lane).  Completion is tracked by vmcnt; the

@@ -1,6 +1,7 @@
 // What the two weight-streaming GEMMs share (ffn_stream.hip, ffn_few.hip): their arguments, and the row tiles worked out on the device.
 #pragma once
 #include "ffn_common.hpp"
+#include "ffn_rules.hpp"
 
 namespace moe355 {
 

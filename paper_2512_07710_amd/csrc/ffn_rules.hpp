@@ -49,6 +49,7 @@ __host__ __device__ inline void split_rows(int rows, int nt, int i, Work& w) {
 // n groups, what lies between two tiles 4 steps, a started round 0.7 of a full one) was fitted to 27 layers of 130 to 1100
 // rows per expert, both projections, heights 96 to 256: the height it picks is 0.2 % above the best of them on average, always
 // taking 256 5.7 %.
+constexpr int CUS = 256, NXCD = 8;
 constexpr int HEIGHTS = 5;                          // 256, 224, 192, 160, 128
 __host__ __device__ constexpr int tile_height(int j) { return TOK_TILE - 32 * j; }
 __host__ __device__ inline float tiles_cost(int64_t units, float groups_per_tile, int nkb) {
@@ -70,6 +71,49 @@ __host__ __device__ inline int pick_height(const int (&tiles)[HEIGHTS], int grou
         }
     }
     return tile_height(best);
+}
+
+// ------------------------------------------------------------------ dealing a list to the XCDs
+// Every XCD gets a contiguous part of its list, so that tiles which share weights stay behind one L2.  Parts of equal numbers are of
+// unequal cost where loads are skewed (4096 tokens x 8 of 128 Zipf experts, gate/up: XCDs done between 474 and 692 us), and XCDs are not
+// equally fast (256 experts of about 1024 rows: 6.66 to 7.10 ms with the same work).  Hence parts of equal cost, and the last sixteenth of
+// each is nobody's: a block that finds no unit of its own takes the next of its XCD, then of the XCD with the most left.  us, equal
+// numbers / this: the Zipf layer 1245 / 1175, the 256 experts 13505 / 13305, 128 experts of 257..261 rows 1100 / 1089.
+// What an expert's tiles cost, for each feature tile: a tile of 8 groups 1.6 times one of 2 (Zipf gate/up 68 and 46 us).
+__host__ __device__ inline int tiles_share(int tiles, int groups) { return 8 * tiles + groups; }
+struct alignas(128) Queue {
+    int32_t total;                                   // units of the list
+    int32_t helpers;                                 // blocks of each XCD that look for a unit of the rest
+    int32_t begin[NXCD + 1];                         // XCD x has [begin[x], begin[x+1])
+    int32_t fixed[NXCD];                             // of which the first so many go to its blocks in turn, and the rest to whoever is free
+};
+struct alignas(128) Rest { int32_t taken; };         // how many of an XCD's rest are gone
+__host__ __device__ inline int list_blocks(int units) { return (units + NXCD - 1) / NXCD * NXCD; }
+// A unit of the rest waits for an atomic, 1..2 us, and so does a block that finds none: with six rounds of units or more to an XCD it is
+// not felt, with four (64 experts of 150..200 rows x 4096 x 1408, down, 117 us) it took 7 us.  For the same reason only twice as many blocks
+// look for one as there are, or every block where those would be too few.
+constexpr int REST_UNITS = 192;
+// begin: boundaries of equal costs, given up for equal numbers where the two are close (whole rounds stay whole); slots: blocks that each
+// XCD will have.  Any unit of the rest finds a block: 8 * slots are at least as many as all units.
+__host__ __device__ inline void deal(const int32_t (&begin)[NXCD + 1], int slots, Queue& q) {
+    const int units = begin[NXCD], chunk = (units + NXCD - 1) / NXCD;
+    bool uneven = false;
+    for (int x = 1; x < NXCD; ++x) {
+        const int off = begin[x] - min(x * chunk, units);
+        uneven |= off > chunk / 8 || off < -chunk / 8;
+    }
+    int left = 0, room = 0, at[NXCD + 1], fixed[NXCD];
+    for (int x = 0; x <= NXCD; ++x) at[x] = uneven ? begin[x] : min(x * chunk, units);
+    for (int x = 0; x < NXCD; ++x) {
+        const int count = at[x + 1] - at[x];
+        fixed[x] = min(count >= REST_UNITS ? count - count / 16 : count, slots);
+        left += count - fixed[x];
+    }
+    const int helpers = (left + NXCD - 1) / NXCD * 2;
+    for (int x = 0; x < NXCD; ++x) room += min(helpers, slots - fixed[x]);
+    for (int x = 0; x <= NXCD; ++x) q.begin[x] = at[x];
+    for (int x = 0; x < NXCD; ++x) q.fixed[x] = fixed[x];
+    q.helpers = room >= left ? helpers : slots;
 }
 
 // One list for each projection: its feature tiles, K blocks and room.
@@ -102,7 +146,7 @@ constexpr int64_t GATE_UP_STREAM_ROWS = 8, GATE_UP_STREAM_ROWS_IDLE = 32, DOWN_S
 // (an ordinary load has 1.0..1.55 times as many, a concentrated one of that size 2.5..4) fill the big tiles' list, otherwise it
 // stays empty; both kernels are launched and the one that has nothing to do returns.
 constexpr int64_t GATE_UP_SKEW_UNITS = 256, DOWN_SKEW_UNITS = 512;
-constexpr int CUS = 256, LINEAR_STREAM_UNITS = 256;
+constexpr int LINEAR_STREAM_UNITS = 256;
 
 inline bool skew_is_harmless(const moe_dims* D, int feature_tiles, int64_t most_units) {
     const int64_t tiles = (D->T + STREAM_ROWS - 1) / STREAM_ROWS;

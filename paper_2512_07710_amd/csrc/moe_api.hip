@@ -90,7 +90,7 @@ int moe_create(moe_ctx** out, const moe_dims* dims, void* hip_stream) {
     ok = ok && hipMalloc((void**)&c->tiles, ffn_work_bytes(dims)) == hipSuccess;
     if (ffn_ticket_bytes(dims)) ok = ok && hipMalloc((void**)&c->tickets, ffn_ticket_bytes(dims)) == hipSuccess;
     if (ffn_h_rows_bytes(dims)) ok = ok && hipMalloc((void**)&c->h_rows, ffn_h_rows_bytes(dims)) == hipSuccess;
-    ok = ok && hipMalloc((void**)&c->n_tiles, 2 * sizeof(int32_t)) == hipSuccess;
+    ok = ok && hipMalloc((void**)&c->queues, ffn_queue_bytes()) == hipSuccess;
     ok = ok && hipMalloc((void**)&c->flags, 2 * sizeof(int32_t)) == hipSuccess;
     ok = ok && hipMalloc((void**)&c->router_planes, route_workspace_bytes(dims->E, dims->d)) == hipSuccess;
     if (route_partial_bytes(dims->T, dims->E))
@@ -99,7 +99,7 @@ int moe_create(moe_ctx** out, const moe_dims* dims, void* hip_stream) {
     ok = ok && hipMalloc((void**)&c->hq, nrow * (size_t)dims->F) == hipSuccess;
     ok = ok && hipMalloc((void**)&c->hs, nrow * (size_t)(dims->F / QBLOCK) * sizeof(float)) == hipSuccess;
     ok = ok && launch_fill_i32(c->stream, c->flags, 2, 0) == hipSuccess;
-    ok = ok && launch_fill_i32(c->stream, c->n_tiles, 2, 0) == hipSuccess;
+    ok = ok && launch_fill_i32(c->stream, (int32_t*)c->queues, (int)(ffn_queue_bytes() / sizeof(int32_t)), 0) == hipSuccess;
     if (c->tickets)
         ok = ok && launch_fill_i32(c->stream, c->tickets, (int)(ffn_ticket_bytes(dims) / sizeof(int32_t)), 0) == hipSuccess;
     if (!ok) {
@@ -116,7 +116,7 @@ int moe_destroy(moe_ctx* c) {
     (void)hipStreamSynchronize(c->stream);
     if (c->chunk_counts) (void)hipFree(c->chunk_counts);
     if (c->tiles) (void)hipFree(c->tiles);
-    if (c->n_tiles) (void)hipFree(c->n_tiles);
+    if (c->queues) (void)hipFree(c->queues);
     if (c->tickets) (void)hipFree(c->tickets);
     if (c->h_rows) (void)hipFree(c->h_rows);
     if (c->flags) (void)hipFree(c->flags);

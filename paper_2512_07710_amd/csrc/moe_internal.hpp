@@ -25,7 +25,7 @@ struct moe_ctx {
     int n_chunks;            // ceil(N / PERM_CHUNK)
     int32_t* chunk_counts;   // [n_chunks][E] per-chunk histograms, then their exclusive scans
     void* tiles;             // GEMM work lists (gate/up list, then down list)
-    int32_t* n_tiles;        // [2] their lengths
+    void* queues;            // [2] their lengths and how they are dealt to the XCDs
     int32_t* tickets;        // streaming gate/up projection only: one per unit, zero between launches
     int32_t* flags;          // [2] flags[0] != 0: an expert id outside [0,E) was met; flags[1] != 0: a logged id repeated
                              //     inside a token
@@ -88,6 +88,7 @@ hipError_t launch_linear(moe_ctx* c, const uint8_t* xq, const float* xs, int32_t
 hipError_t launch_quantize_weights(hipStream_t s, const uint16_t* w, int64_t rows, int32_t cols, uint8_t* q,
                                    float* scales);
 size_t ffn_work_bytes(const moe_dims* D);
+size_t ffn_queue_bytes();
 size_t ffn_ticket_bytes(const moe_dims* D);
 size_t ffn_h_rows_bytes(const moe_dims* D);
 // The weight-streaming GEMMs (ffn_stream.hip).  perm as in launch_expert_ffn

@@ -135,3 +135,50 @@ def test_lists_have_room_for_their_units(rules):
         for form, _, units, room, _ in _layer(rules, counts, 128 * rng.randint(1, 56), 128 * rng.randint(1, 16)):
             if form == "big":
                 assert units <= room
+
+
+DEAL = r"""
+#include "ffn_rules.hpp"
+#include <cstdio>
+using namespace moe355;
+int main() {                                                   // slots, nine boundaries -> helpers, begin and fixed of each XCD
+    int slots, begin[NXCD + 1];
+    while (scanf("%d", &slots) == 1) {
+        for (int& b : begin) if (scanf("%d", &b) != 1) return 1;
+        Queue q;
+        deal(begin, slots, q);
+        printf("%d", q.helpers);
+        for (int b : q.begin) printf(" %d", b);
+        for (int f : q.fixed) printf(" %d", f);
+        printf("\n");
+    }
+    return 0;
+}
+"""
+
+
+def test_every_unit_of_a_dealt_list_has_a_block(tmp_path):
+    """Random lists, even to all on one XCD, with barely enough blocks to twice as many: the parts cover the list in order, and the
+    blocks that look for a unit of the rest are at least as many as it has units."""
+    (tmp_path / "deal.hip").write_text(DEAL)
+    subprocess.run([HIPCC, "--cuda-host-only", "-O2", "-std=c++17", "-I", CSRC, "-I", ROOT + "/include", str(tmp_path / "deal.hip"), "-o",
+                    str(tmp_path / "deal")], check=True, capture_output=True)
+    rng, cases = random.Random(2), []
+    for _ in range(2000):
+        units = int(2 ** rng.uniform(0, 15)) - 1
+        even = [units * x // 8 for x in range(9)]
+        cuts = [0, *sorted(rng.randint(0, units) for _ in range(7)), units]
+        mix = rng.choice([0.0, 0.02, 0.3, 1.0])
+        slots = (units + 7) // 8 + rng.choice([0, 0, 1, units // 32, units // 8])
+        cases.append((slots, [0, *sorted(round(a + mix * (b - a)) for a, b in zip(even, cuts))[1:-1], units]))
+    cases.append((5, [0] * 8 + [40]))
+    out = subprocess.run([str(tmp_path / "deal")], input="\n".join(f"{s} " + " ".join(map(str, b)) for s, b in cases), check=True,
+                         capture_output=True, text=True).stdout.splitlines()
+    assert len(out) == len(cases)
+    for (slots, cuts), line in zip(cases, out):
+        helpers, *rest = map(int, line.split())
+        begin, fixed = rest[:9], rest[9:]
+        count = [b - a for a, b in zip(begin, begin[1:])]
+        assert begin[0] == 0 and begin[8] == cuts[8] and min(count) >= 0
+        assert all(0 <= f <= min(c, slots) for f, c in zip(fixed, count))
+        assert sum(min(helpers, slots - f) for f in fixed) >= sum(count) - sum(fixed)
