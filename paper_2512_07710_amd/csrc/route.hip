@@ -244,8 +244,14 @@ __global__ __launch_bounds__(256, 1) void route_mfma_kernel(const uint16_t* __re
             for (int p = 0; p < 3; ++p) a[slot][s][p] = wsrc[s][((size_t)kk * 3 + p) * 64];
     };
     issue_x(kc_begin);
+    // A wave whose experts are all padding only stages activations.  The planes come from the L2 for every token tile, and with 16
+    // experts padded to 128 three quarters of that were zeros (us for the whole pass, that / this: 6000 tokens x 3072, 16 experts, ids
+    // given 360.5 / 348.2, 9000 x 2048, 24 experts 298.0 / 280.8, 1000 x 4096, 40 experts 151.4 / 149.5, 100 x 4096, 60 experts
+    // 181.7 / 178.5; 128 and 256 experts level).
+    const bool idle = wave * NS * 32 >= E;
+    if (!idle)
 #pragma unroll
-    for (int i = 0; i < AH; ++i) load_a(i, kc_begin * KS + i);   // a block has at least one chunk = KS > AH steps
+        for (int i = 0; i < AH; ++i) load_a(i, kc_begin * KS + i);   // a block has at least one chunk = KS > AH steps
 
     // activation operands of one K step: TS reads of 16 bytes per lane from the staged chunk
     auto read_b = [&](v4i (&b)[TS], const uint8_t* stage, int ks) {
@@ -257,6 +263,13 @@ __global__ __launch_bounds__(256, 1) void route_mfma_kernel(const uint16_t* __re
         }
     };
     v4i b[2][TS];                                              // step ks multiplies out of b[ks & 1] while b[(ks+1) & 1] loads
+    if (idle) {
+        for (int kc = kc_begin; kc < nchunks; ++kc) {
+            WAIT_VM(0);
+            __syncthreads();
+            if (kc + 1 < nchunks) issue_x(kc + 1);
+        }
+    } else
     for (int kc = kc_begin; kc < nchunks; ++kc) {
         // chunk kc must have landed.  Vector-memory operations complete in issue order: after the copies
         // of chunk kc this wave has issued exactly KS K steps of weight loads (L each), except
@@ -305,6 +318,7 @@ __global__ __launch_bounds__(256, 1) void route_mfma_kernel(const uint16_t* __re
     __syncthreads();                                           // all reads of the activation stages are done
 
     if (SPLIT) {
+        if (idle) return;                                      // (nobody reads the padding's)
         // partial[y][t][e], t over the padded token tiles, e over the padded experts: a lane owns four consecutive experts
         const int T_pad = gridDim.x * RT, E_pad = 128 * NS;
 #pragma unroll
