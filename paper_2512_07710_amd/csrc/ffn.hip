@@ -9,18 +9,19 @@
 // Main loop, one iteration per 128-wide K block (= one scale block):
 //   * both operand tiles are copied global -> LDS by direct-to-LDS loads (no staging
 //     registers) into rings of three (weights) and two (activations) 32 KiB buffers, 16-byte
-//     chunks XOR-swizzled by row so that the 32-row operand reads spread over all 64 banks;
-//   * partial = W_tile * X_tile^T with two v_mfma_f32_32x32x64_f8f6f4 per 32x32 sub-tile;
+//     chunks XOR-swizzled by row so that the operand reads spread over all 64 banks;
+//   * partial = W_tile * X_tile^T with one v_mfma_f32_16x16x128_f8f6f4 per 16x16 sub-tile (narrow
+//     tiles: two v_mfma_f32_32x32x64_f8f6f4 per 32x32 sub-tile; same sums);
 //   * acc += (xs[kb][row] * ws[feature block,kb]) * partial in fp32.
-// The product is taken as (features x tokens): in the 32x32 accumulator layout a lane then
-// owns ONE token column and 16 feature rows, so the activation scale is one scalar per lane
-// and sub-tile, and the 128-wide amax of the epilogue is a lane-local reduction plus one
-// cross-half shuffle and one exchange between the four waves that share a token.
-// Activation scales are K-block major ([K/128][rows]): the 32 lanes of a half-wave read 32
+// The product is taken as (features x tokens): in the accumulator layout a lane then
+// owns ONE token column and 4 (16) feature rows, so the activation scale is one scalar per lane
+// and sub-tile, and the 128-wide amax of the epilogue is a lane-local reduction plus two
+// (one) shuffles and one exchange between the four waves that share a token.
+// Activation scales are K-block major ([K/128][rows]): the lanes of a wave read
 // consecutive floats of one plane.
 //
 // Eight waves per block: wave (wt, wf) owns 64 staged weight rows x half of the tile's groups of 32
-// tokens (2 x 4 sub-tiles in a full tile: 6 operand sub-tiles feed 8 MFMA pairs).  The two waves of
+// tokens (4 x 8 sub-tiles in a full tile: 12 operand sub-tiles feed 32 products).  The two waves of
 // a SIMD, w and w + 4, take the two halves, so a tile of n groups costs every SIMD n/8 of a full
 // tile's matrix work.  The K loop is instantiated for 1 to 4 groups per wave.
 //
@@ -30,6 +31,8 @@
 //        that every row is stored in contiguous 256-byte pieces.
 #include "ffn_common.hpp"
 #include "ffn_rules.hpp"
+
+#include <type_traits>
 
 namespace moe355 {
 namespace {
@@ -163,9 +166,9 @@ __device__ inline int take_rest(const Queue* __restrict__ q, Rest* __restrict__ 
 // ------------------------------------------------------------------ helpers
 // The matrix instructions are written as volatile asm so that they stay exactly where the
 // source puts them: the schedule below relies on it.  T = A*B (first K half) and T += A*B.
-__device__ inline void mfma_first(v16f& t, const v8i& a, const v8i& b) {
+__device__ inline void mfma_16(v4f& t, const v8i& a, const v8i& b) {
     // "+v", although t is only written: the product registers then stay where they are through the whole K loop
-    asm volatile("v_mfma_f32_32x32x64_f8f6f4 %0, %1, %2, 0" : "+v"(t) : "v"(a), "v"(b) : "memory");
+    asm volatile("v_mfma_f32_16x16x128_f8f6f4 %0, %1, %2, 0" : "+v"(t) : "v"(a), "v"(b) : "memory");
 }
 __device__ inline void mfma_new(v16f& t, const v8i& a, const v8i& b) {
     asm volatile("v_mfma_f32_32x32x64_f8f6f4 %0, %1, %2, 0" : "=&v"(t) : "v"(a), "v"(b) : "memory");
@@ -200,7 +203,7 @@ struct Feed {
 // stays a straight line, which the register allocation of the K loop depends on (with C++ conditions around the copies
 // the loop spills).
 #define COPY_IF(J, N, LDS, VOFF, SBASE, CACHE)                                                             \
-    asm volatile("s_cmp_gt_i32 %3, %4\n\ts_cbranch_scc0 .Lskip%=\n\ts_mov_b32 m0, %0\n\ts_nop 0\n\t"     \
+    asm volatile("s_mov_b32 m0, %0\n\ts_cmp_gt_i32 %3, %4\n\ts_cbranch_scc0 .Lskip%=\n\t"                  \
                  "global_load_lds_dwordx4 %1, %2" CACHE "\n.Lskip%=:"                                              \
                  :: "s"(LDS), "v"(VOFF), "s"(SBASE), "s"(N), "n"(J) : "memory", "scc")
 // a < b ? -1 : 0 for wave-uniform values, in a scalar register whatever the compiler makes of the comparison
@@ -240,44 +243,68 @@ struct Tile {
     uint32_t lds0;                                             // LDS address of ring slot 0
     int nkb;
     uint32_t a_row, b_row;                                     // LDS byte offset of the lane's row in weight / activation slot 0
-    int l32, half;
-    int row, n_rows;                                           // the lane's first token row; rows of a scale plane
+    int l16, quad;                                             // row of a 16-row operand tile; quarter of its K block
+    int row, n_rows;                                           // the wave's first token row, plus the lane; rows of a scale plane
     const uint8_t* act_s;
     const float *sa, *sb;                                      // weight scales of the wave's gate / up rows (or both the same)
 };
 
-// One wave: 64 staged weight rows (sub-tiles s = 0, 1) x NTS groups of 32 tokens, 2*NTS sub-tile products per K block.
+// The products of a K block, four tiles of 16 weight rows x two tiles of 16 tokens for each group of 32, in the order they are made: token
+// tile by token tile, the weights forwards and backwards in turn, so that each product shares an operand with the one before (energy,
+// see k_loop).  Forwards by the first token tile and by the last: the last one's weights are replaced in the order in which the next K
+// block wants them.
+struct Product { int weights, tokens; };
+constexpr Product product(int m) {
+    const int tokens = m >> 2, j = m & 3;
+    return {tokens > 0 && tokens % 2 == 0 ? 3 - j : j, tokens};
+}
+
+// One wave: 64 staged weight rows (four tiles of 16) x NTS groups of 32 tokens (two tiles each), 8*NTS products per K block, one
+// v_mfma_f32_16x16x128_f8f6f4 and four multiply-adds a lane each.
+//
+// With many rows this kernel runs at the power cap, so what counts is the energy of a product.  From registers alone, with the
+// multiply-adds, codes of quantised Gaussians, TFLOP/s: pairs of 32x32x64 3500 in any order, 16x16x128 3725 to 3790, in the order above
+// 3822.  Here, with the same sums bit for bit (inside an instruction the lane groups get their 16-byte chunks in the order in which
+// two 32x32x64 meet them, as in ffn_few.hip), against pairs of 32x32x64, us: linear 8192 x 7168 x 8192 475 / 464; 32768 tokens of
+// 7168 x 2048, 256 experts, gate/up 6940 / 6915, down 4370 / 4335; 4096 tokens of 5120 x 1536, 128 experts of 257..261 rows, 544 /
+// 546 and 350 / 343; 3000 x 6 of 2048 x 768 102.0 / 100.5 and 77.6 / 75.9.  The clock rises by what the energy falls, less 5 % more
+// cycles for twice the instructions and for handing out the scales.  Tried and level or worse: weight tile by weight tile, operands
+// requested eleven products ahead instead of seven, a raised wave priority around the matrix instructions (1..3 %).
 //
 // Pipeline.  K block kb of the weight tile lives in ring slot kb % 3, of the activation tile in slot kb % 2.  Each wave
-// passes ONE barrier per K block, placed after its last LDS read of block kb (before its last token group's two
-// products).  Behind that barrier block kb+1 is complete in LDS and the slots of block kb are free.  The copies that
+// passes ONE barrier per K block, after its last LDS read of block kb, behind the first product of its last token group: the pipe
+// has that one to work on while the waves meet (in front of it: 1.2 % more cycles).  Behind the barrier block kb+1 is complete in LDS
+// and the slots of block kb are free.  The copies that
 // refill them follow: activation block kb+2, then weight block kb+3 - always in that order, so that "all but the newest
-// four copies have landed" is exactly "everything but the weight block two steps ahead".  They go out one behind each
-// matrix instruction (activations over the last two products, weights over the first two of the next step; NTS = 1 has
+// four copies have landed" is exactly "everything but the weight block two steps ahead".  They go out one behind every
+// second product (activations over the last group, weights over the first group of the next step; NTS = 1 has
 // no products to spare and sends the weights at the end of the step), so that the wave does not sit at the issue of a
-// copy while the queue drains (in two bursts of four the gate/up projection ran 4 % slower).  The last two products
-// already fetch the first operands of block kb+1 into registers: the weight operands a[s] stay for a whole step, the
-// token operands go through two register sets in turn (three for NTS = 3, so that a step always starts with set 0).
+// copy while the queue drains (in two bursts of four the gate/up projection ran 4 % slower).  The last group's products
+// already fetch the first operands of block kb+1 into registers: the weight operands a[] stay for a whole step and are replaced one
+// by one behind their last product, the token operands go through two register sets in turn (three for NTS = 3, so that a step always
+// starts with set 0).
 template <int NTS, bool GATED, bool ONCE>
-__device__ __forceinline__ void k_loop(const Tile& t, const Feed& f, v16f (&acc)[2][4]) {
+__device__ __forceinline__ void k_loop(const Tile& t, const Feed& f, v4f (&acc)[4][8]) {
     const int nkb = t.nkb;
-    // LDS byte address of a lane's first operand chunk (ks = 0, j = 0) relative to a ring slot; chunk (ks, j) is that
-    // address with bits 6 and 4 flipped by ks and j (the swizzle is an exclusive or of the chunk number)
-    const uint32_t off00 = (uint32_t)((t.half * 2) ^ (t.l32 & 7) ^ ((t.l32 >> 3) & 1)) << 4;
-    const uint32_t a00 = t.lds0 + t.a_row + off00, b00 = t.lds0 + t.b_row + off00;
-    auto read_ops = [&](v8i (&o)[2], uint32_t at, int plus) {
-#pragma unroll
-        for (int ks = 0; ks < 2; ++ks) o[ks] = lds_operand((at ^ (ks * 64)), (at ^ (ks * 64 + 16)), plus);
+    // LDS byte address of a lane's first operand chunk relative to a ring slot; its second is four chunks on, that address with bit 6
+    // flipped (the swizzle is an exclusive or of the chunk number)
+    const int first = (t.quad & 1) * 2 + (t.quad >> 1);
+    const uint32_t off0 = (uint32_t)(first ^ (t.l16 & 7) ^ ((t.l16 >> 3) & 1)) << 4;
+    const uint32_t a00 = t.lds0 + t.a_row + off0, b00 = t.lds0 + t.b_row + off0;
+    auto read_op = [&](v8i& o, uint32_t at, int plus) { o = lds_operand(at, at ^ 64, plus); };
+    auto read_group = [&](v8i (&o)[2], uint32_t at, int plus) {
+        read_op(o[0], at, plus);
+        read_op(o[1], at, plus + 16 * KB);
     };
-    // activation scales of this lane's token columns (K-block major: one plane per K block), by buffer loads whose
+    // activation scales of this wave's token columns (K-block major: one plane per K block), by buffer loads whose
     // range check covers the token columns past the end of the plane (they read 0 and are never stored): one address
     // register for all groups.  Issued as asm; the data is only touched behind a vmcnt wait.
-    // The lanes of a pair (l, l+32) serve the same token: the lower one fetches the even groups' scales and the upper
-    // one the odd groups', and a half-wave swap hands them round (half the loads, half the registers in flight).
+    // A load fetches the scales of 64 tokens, four tiles; each tile's sixteen are then handed to all four lane groups by swaps of rows
+    // and of halves.
     constexpr int NXS = (NTS + 1) / 2;
-    const uint32_t xs_at = 4u * (uint32_t)(t.row + t.half * 32);
+    const uint32_t xs_at = 4u * (uint32_t)t.row;
     const size_t plane = (size_t)t.n_rows * 4;
-    float xs_n[NXS], xs[NXS * 2];
+    float xs_n[NXS], xs[NXS * 4];
 #pragma unroll
     for (int i = 0; i < NXS; ++i) xs_n[i] = 0.f;
     auto xs_load = [&](int kb, int go) {                       // scalar condition inside the asm, as in COPY_IF
@@ -295,8 +322,10 @@ __device__ __forceinline__ void k_loop(const Tile& t, const Feed& f, v16f (&acc)
     auto xs_take = [&]() {
 #pragma unroll
         for (int i = 0; i < NXS; ++i)
-            asm volatile("v_mov_b32 %0, %2\n\tv_mov_b32 %1, %2\n\ts_nop 1\n\tv_permlane32_swap_b32 %0, %1"
-                         : "=&v"(xs[2 * i]), "=&v"(xs[2 * i + 1]) : "v"(xs_n[i]));
+            asm volatile("v_mov_b32 %0, %4\n\tv_mov_b32 %1, %4\n\ts_nop 1\n\tv_permlane16_swap_b32 %0, %1\n\t"
+                         "s_nop 1\n\tv_mov_b32 %2, %0\n\tv_mov_b32 %3, %1\n\ts_nop 1\n\t"
+                         "v_permlane32_swap_b32 %0, %2\n\tv_permlane32_swap_b32 %1, %3"
+                         : "=&v"(xs[4 * i]), "=&v"(xs[4 * i + 1]), "=&v"(xs[4 * i + 2]), "=&v"(xs[4 * i + 3]) : "v"(xs_n[i]));
     };
     xs_load(0, 1);
     if (nkb > 1) {                                             // weight block 1 is not waited for
@@ -314,46 +343,51 @@ __device__ __forceinline__ void k_loop(const Tile& t, const Feed& f, v16f (&acc)
     }
     if (nkb > 2) copy_w<ONCE>(f, 2, 2);
     constexpr int NB = NTS == 3 ? 3 : 2;                      // register sets of token operands
-    v8i a[2][2], b[NB][2];
-    read_ops(a[0], a00, 0);
-    read_ops(b[0], b00, 0);
-    read_ops(a[1], a00, 32 * KB);
+    v8i a[4], b[NB][2];
+    read_group(b[0], b00, 0);
+#pragma unroll
+    for (int s = 0; s < 4; ++s) read_op(a[s], a00, s * 16 * KB);
     float wsc[2];                                              // weight scales of the block being folded, in scalar registers
     asm volatile("s_load_dword %0, %2, 0x0\n\ts_load_dword %1, %3, 0x0\n\ts_waitcnt lgkmcnt(0)"
                  : "=&s"(wsc[0]), "=&s"(wsc[1]) : "s"(t.sa), "s"(t.sb) : "memory");
+    auto load_wsc = [&](float (&w)[2], int kb) {               // issued by hand; complete at the barrier that follows
+        const float *const at_a = t.sa + kb, *const at_b = t.sb + kb;
+        asm volatile("s_load_dword %0, %2, 0x0\n\ts_load_dword %1, %3, 0x0" : "=&s"(w[0]), "=&s"(w[1]) : "s"(at_a), "s"(at_b) : "memory");
+    };
 #pragma unroll
-    for (int s = 0; s < 2; ++s)
+    for (int s = 0; s < 4; ++s)
 #pragma unroll
-        for (int ts = 0; ts < NTS; ++ts)
+        for (int tt = 0; tt < 2 * NTS; ++tt)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[s][ts][r] = 0.f;
-    v16f T[2];
+            for (int r = 0; r < 4; ++r) acc[s][tt][r] = 0.f;
+    // product m is held in T[m & 3] until it is folded behind product m + 2; the last two of a K block behind the first two of the next
+    // (at first: zeros, folded with scale 0)
+    v4f T[4];
 #pragma unroll
-    for (int r = 0; r < 16; ++r) T[1][r] = 0.f;                // folded once, with scale 0, before its first product
-    T[0] = T[1];
-    float sc_cur = 0.f, sc_pend = 0.f;                         // scale being folded with; of the product still held in T[1]
+    for (int s = 0; s < 4; ++s)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) T[s][r] = 0.f;
+    float sc = 0.f;                                            // scale being folded with
 
     auto scale = [&](float x, float w) {                       // w * x at this place (see PIN)
         float r;
         asm volatile("v_mul_f32 %0, %1, %2" : "=v"(r) : "s"(w), "v"(x));
         return r;
     };
-    // fold product (S, TS), held in T[S], into its accumulator
-#define FOLD(S, TS, SCV)                                                                        \
+    // fold the product of weight tile S and token tile TT, held in T[J], into its accumulator
+#define FOLD(J, S, TT, SCV)                                                                     \
     do {                                                                                        \
         const float scv_ = (SCV);                                                               \
-        PIN(T[S]);                                                                              \
-        _Pragma("unroll") for (int r = 0; r < 16; ++r)                                          \
-            acc[S][TS][r] = fmaf(scv_, T[S][r], acc[S][TS][r]);                                 \
-        PIN(acc[S][TS]);                                                                        \
+        PIN(T[J]);                                                                              \
+        _Pragma("unroll") for (int r = 0; r < 4; ++r)                                           \
+            acc[S][TT][r] = fmaf(scv_, T[J][r], acc[S][TT][r]);                                 \
+        PIN(acc[S][TT]);                                                                        \
     } while (0)
 
     int wslot = 0;                                             // ring slot of weight block kb
     int kb = 0;
     // Gate/up loops start on a multiple of 64 bytes.  Where a loop lies, modulo 32 bytes, is worth up to 6 % either way, and what other code
-    // of the kernel happens to make of it changes with every edit: 128 experts of 250..262 rows x 5120 x 1536 645..648 us here, 651
-    // and 652 at 24 of 64.  The dense and the down projection's loops lie well as they are (linear 473 x 3712 x 9216 27.4 us,
-    // on a multiple of 64 28.1).
+    // of the kernel happens to make of it changes with every edit.
     if (GATED) asm volatile(".p2align 6");
     do {                                                       // (K >= 128: at least one block)
         const int wnext = (wslot == NW_BUF - 1) ? 0 : wslot + 1;
@@ -366,15 +400,14 @@ __device__ __forceinline__ void k_loop(const Tile& t, const Feed& f, v16f (&acc)
         const int more = all_ones_if_less(kb + 2, nkb);        // is there a block kb+2?
         const int nx = f.x_copies & more;                      // copies of activation block kb+2
         const int nw = 4 & more & all_ones_if_less(0, kb);     // copies of weight block kb+2 (the prologue sent block 2)
-        // 2*NTS sub-tile products, two MFMAs each.  The 16 scale-FMAs of product i-1 sit behind the
-        // second MFMA of product i: by then its result has left the matrix pipe (two more MFMAs
-        // have been issued since), and the vector ALU works in the shadow of the MFMA just issued.
 #pragma unroll
-        for (int i = 0; i < 2 * NTS; ++i) {
-            const int ts = i >> 1, s = i & 1;
+        for (int m = 0; m < 8 * NTS; ++m) {
+            const int ts = m >> 3, q = m & 7;
             const int bi = ts % NB, bnext = ts + 1 < NTS ? (ts + 1) % NB : NTS == 1 ? 1 : 0;
-            const bool last2 = i == 2 * NTS - 2, last = i == 2 * NTS - 1;
-            if (last2) {
+            const bool last = ts == NTS - 1;
+            if (NTS == 1 && m == 0) load_wsc(wsc_n, kn);
+            mfma_16(T[m & 3], a[product(m).weights], b[bi][q >> 2]);
+            if (last && q == 0) {
                 // all of this wave's reads of block kb have been issued; wait for them and for the
                 // copies that must be complete (all of them in the last two steps), then meet the other waves
                 asm volatile("s_waitcnt vmcnt(4) lgkmcnt(0)\n\ts_cmp_lg_u32 %0, 0\n\ts_cbranch_scc1 .Lmore%=\n\t"
@@ -382,40 +415,36 @@ __device__ __forceinline__ void k_loop(const Tile& t, const Feed& f, v16f (&acc)
                 __builtin_amdgcn_s_barrier();
                 asm volatile("" ::: "memory");
             }
-            mfma_first(T[s], a[s][0], b[bi][0]);
-            // one copy behind every matrix instruction: weight block kb+2 over products 0 and 1
-            if (NTS > 1 && i == 0) copy_w1<ONCE, 0>(f, kb + 2, wprev, nw);
-            if (NTS > 1 && i == 1) copy_w1<ONCE, 2>(f, kb + 2, wprev, nw);
-            if (last) copy_x1<2>(f, kb + 2, kb & 1, nx);
-            if (s == 0 && !last2) read_ops(b[bnext], sX, (ts + 1) * 32 * KB);
-            if (last2) {
-                read_ops(b[bnext], sXn, 0);
-                copy_x1<0>(f, kb + 2, kb & 1, nx);
+            if (NTS > 1 && m == 0) copy_w1<ONCE, 0>(f, kb + 2, wprev, nw);
+            if (NTS > 1 && m == 2) copy_w1<ONCE, 1>(f, kb + 2, wprev, nw);
+            if (NTS > 1 && m == 4) copy_w1<ONCE, 2>(f, kb + 2, wprev, nw);
+            if (NTS > 1 && m == 6) copy_w1<ONCE, 3>(f, kb + 2, wprev, nw);
+            if (!last && q == 1) read_group(b[bnext], sX, (ts + 1) * 32 * KB);
+            if (last && q == 1) read_group(b[bnext], sXn, 0);
+            if (NTS > 1 && m == (NTS > 2 ? 9 : 1)) {
+                // behind operand reads that are not waited for until six products later (a scalar load in
+                // flight turns the next wait for an LDS read into a wait for everything)
+                load_wsc(wsc_n, kn);
             }
-            if (i == (NTS > 2 ? 2 : 0)) {
-                // issued by hand, behind operand reads that are not waited for until two products later (a scalar load in
-                // flight turns the next wait for an LDS read into a wait for everything); complete at the barrier
-                asm volatile("s_load_dword %0, %2, 0x0\n\ts_load_dword %1, %3, 0x0"
-                             : "=&s"(wsc_n[0]), "=&s"(wsc_n[1]) : "s"(t.sa + kn), "s"(t.sb + kn) : "memory");
+            if (last && q == 1) copy_x1<0>(f, kb + 2, kb & 1, nx);
+            if (last && q == 3) copy_x1<1>(f, kb + 2, kb & 1, nx);
+            if (last && q == 5) copy_x1<2>(f, kb + 2, kb & 1, nx);
+            if (last && q == 7) copy_x1<3>(f, kb + 2, kb & 1, nx);
+            if (last && q >= 4) read_op(a[q - 4], sWn, (q - 4) * 16 * KB);   // its last product is on its way
+            // The four multiply-adds of product m-2 sit behind product m: its result has left the matrix pipe (two more
+            // instructions have been issued since), and the vector ALU works in the shadow of the one just issued.
+            if (m < 2) {
+                FOLD(m + 2, m + 2, 2 * NTS - 1, sc);
+            } else {
+                const Product p = product(m - 2), before = product(m < 3 ? 0 : m - 3);
+                if (((m - 2) & 3) == 0 || (GATED && p.weights / 2 != before.weights / 2))
+                    sc = scale(xs[p.tokens], wsc[GATED ? p.weights / 2 : 0]);
+                FOLD((m - 2) & 3, p.weights, p.tokens, sc);
             }
-            mfma_acc(T[s], a[s][1], b[bi][1]);
-            if (NTS > 1 && i == 0) copy_w1<ONCE, 1>(f, kb + 2, wprev, nw);
-            if (NTS > 1 && i == 1) copy_w1<ONCE, 3>(f, kb + 2, wprev, nw);
-            if (last2) copy_x1<1>(f, kb + 2, kb & 1, nx);
-            if (last) copy_x1<3>(f, kb + 2, kb & 1, nx);
-            if (i == 0) FOLD(1, NTS - 1, sc_pend);
-            else {
-                const int ps = (i - 1) & 1, pts = (i - 1) >> 1;
-                if (GATED || ps == 0) sc_cur = scale(xs[pts], wsc[GATED ? ps : 0]);
-                FOLD(ps, pts, sc_cur);
-            }
-            if (last2) read_ops(a[0], sWn, 0);
-            if (last) {
-                sc_pend = GATED ? scale(xs[NTS - 1], wsc[1]) : sc_cur;
+            if (m == 8 * NTS - 1) {
+                if (GATED) sc = scale(xs[2 * NTS - 1], wsc[1]);
                 xs_take();                                     // block kb+1: landed before the barrier above
-                if (NTS == 1) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // (its barrier came before the load)
                 asm volatile("s_mov_b32 %0, %2\n\ts_mov_b32 %1, %3" : "=&s"(wsc[0]), "=&s"(wsc[1]) : "s"(wsc_n[0]), "s"(wsc_n[1]));
-                read_ops(a[1], sWn, 32 * KB);
                 xs_load(kb + 2, more);
                 if (NTS == 1) {
                     copy_w<ONCE>(f, kb + 3, wslot, 4 & all_ones_if_less(kb + 3, nkb));
@@ -426,9 +455,10 @@ __device__ __forceinline__ void k_loop(const Tile& t, const Feed& f, v16f (&acc)
         }
         wslot = wnext;
     } while (++kb < nkb);
-    // the last product: wait out the matrix pipe, then fold it
+    // the last two products: wait out the matrix pipe, then fold them
     asm volatile("s_nop 15\n\ts_nop 15\n\ts_nop 7" ::: "memory");
-    FOLD(1, NTS - 1, sc_pend);
+    FOLD(2, 2, 2 * NTS - 1, sc);
+    FOLD(3, 3, 2 * NTS - 1, sc);
 #undef FOLD
 }
 
@@ -498,12 +528,12 @@ __global__ __launch_bounds__(NTHREADS, 1) void ffn_gemm(const uint8_t* __restric
     // ---- copy plan: wave w brings staged weight rows [32w, 32w+32) and staged activation rows
     //      [32w, 32w+32) of every K block, 4 + 4 instructions of 8 rows each; lane i -> row i/8,
     //      LDS chunk slot i%8 which receives global chunk slot ^ (row & 7) ^ ((row >> 3) & 1): with that
-    //      swizzle the 32-row x 16-byte operand reads below touch all 64 LDS banks evenly.
+    //      swizzle the operand reads below touch all 64 LDS banks evenly.
     //      Staged weight row r: GATED: features f0 + (r/64)*32 + r%32, gate (Wa) if (r/32)%2 == 0 else up (Wb).
-    //      NARROW tiles (at most 64 rows, see below): wave w's 32 staged rows are 32 consecutive features of the tile
+    //      NARROW tiles (at most 64 rows, or 96, see below): wave w's 32 staged rows are 32 consecutive features of the tile
     //      (down projection) or, GATED, [16 gate rows | 16 up rows] of features f0 + 16w .. 16w+15.
     // (LINEAR: a product of 129..160 rows can have a tile as short beside a taller one; k_loop<1> in both halves, their waves in step)
-    const bool narrow = !LINEAR && wk.nrows <= NARROW_ROWS;    // block-uniform
+    const bool narrow = !LINEAR && wk.nrows <= (wk.tiles == 1 ? NARROW_ROWS : NARROW_SHARED_ROWS);   // block-uniform
     const bool once = !LINEAR && wk.tiles <= (GATED ? GATE_UP_ONCE_TILES : DOWN_ONCE_TILES);   // as is this
     // A wave whose features all lie beyond NOUT (down projection, NOUT an odd multiple of 128: feature tile half empty)
     // copies the last 32 features again; they are multiplied and not stored.
@@ -550,153 +580,177 @@ __global__ __launch_bounds__(NTHREADS, 1) void ffn_gemm(const uint8_t* __restric
 
     copy_x(feed, 0, 0);
     if (narrow) {
-        // ---- NARROW tile: at most 64 rows.  In the layout above a wave has at most two products per K block, with one token group
-        //      half of the waves none, behind a schedule made for eight.  Here
-        //      wave w multiplies the 32 staged weight rows it copies itself by the tile's 64 token columns (two
-        //      32x32 products, four matrix instructions per K block), so the matrix work is spread over every wave
+        // ---- NARROW tile: at most 64 rows, or 96 that are all of their expert's.  In the layout above a wave has one or two groups of tokens to multiply, the two waves of
+        //      a SIMD often not the same, behind a schedule made for eight groups.  Here
+        //      wave w multiplies the 32 staged weight rows it copies itself by the tile's two or three groups of 32 token
+        //      columns (two matrix instructions each per K block), so the matrix work is spread over every wave
         //      and the tile runs at the speed its weight tile streams in.  Same rings, same copy order, same
         //      barrier per K block as the full tiles; nothing is overlapped by hand - the copies are the bound.
-        //      Against k_loop<1> and weights through the caches, us: gate/up of 64 experts x 4096 x 1408 at 24 rows 117 / 137, at 58
-        //      125 / 145, 256 x 7168 x 2048 at 12 rows 1101 / 1260; down at 50 rows 83 / 88 and 754 / 799.
+        //      Two groups against k_loop<1> and weights through the caches, us: gate/up of 64 experts x 4096 x 1408 at 24 rows 117 / 137, at
+        //      58 125 / 145, 256 x 7168 x 2048 at 12 rows 1101 / 1260; down at 50 rows 83 / 88 and 754 / 799.  Three groups against
+        //      k_loop<2> beside k_loop<1>, gate/up | down: 60 experts x 2176 x 896 at 65 rows 52.5 / 54.2 | 39.8 / 40.9, 64 x 4096 x 1408
+        //      at 62 132.6 / 136.8 | 84.2 / 84.6, at 80 148.9 / 152.2 | 90.1 / 91.9, 256 x 7168 x 2048 at 94 1346 / 1361 | 809 / 826.  Four
+        //      are no better (at 106 rows 164.2 / 160.0 | 105.9 / 98).
         const uint32_t off00 = (uint32_t)((half * 2) ^ (l32 & 7) ^ ((l32 >> 3) & 1)) << 4;
         const uint32_t a00 = lds0 + (uint32_t)(wave * 32 + l32) * KB + off00;
         const uint32_t b00 = lds0 + (uint32_t)(X_RING + l32 * KB) + off00;
-        uint32_t xs_i[2];
+        auto run = [&](auto groups) __attribute__((always_inline)) {
+            constexpr int NG = decltype(groups)::value;
+            uint32_t xs_i[NG];
 #pragma unroll
-        for (int ts = 0; ts < 2; ++ts) xs_i[ts] = 4u * (uint32_t)min(wk.row0 + ts * 32 + l32, n_rows - 1);
-        const size_t plane = (size_t)n_rows * 4;
-        auto xs_load = [&](float& dst, int kb, int ts) {
-            asm volatile("global_load_dword %0, %1, %2" : "=v"(dst) : "v"(xs_i[ts]),
-                         "s"(reinterpret_cast<const uint8_t*>(act_s) + (size_t)kb * plane) : "memory");
-        };
-        float xs_n[2], xs_cur[2];
-        xs_load(xs_n[0], 0, 0);
-        xs_load(xs_n[1], 0, 1);
-        if (nkb > 1) {
-            weights(1, 1);
-            asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
-        } else {
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        }
-        __builtin_amdgcn_s_barrier();
-        asm volatile("" ::: "memory");
+            for (int ts = 0; ts < NG; ++ts) xs_i[ts] = 4u * (uint32_t)min(wk.row0 + ts * 32 + l32, n_rows - 1);
+            const size_t plane = (size_t)n_rows * 4;
+            auto xs_load = [&](float& dst, int kb, int ts) {
+                const uint8_t* const at = reinterpret_cast<const uint8_t*>(act_s) + (size_t)kb * plane;
+                const uint32_t off = xs_i[ts];
+                asm volatile("global_load_dword %0, %1, %2" : "=v"(dst) : "v"(off), "s"(at) : "memory");
+            };
+            float xs_n[NG], xs_cur[NG];
+            auto xs_loads = [&](int kb) {
 #pragma unroll
-        for (int ts = 0; ts < 2; ++ts) asm volatile("v_mov_b32 %0, %1" : "=v"(xs_cur[ts]) : "v"(xs_n[ts]));
-        if (nkb > 1) {
-            xs_load(xs_n[0], 1, 0);
-            xs_load(xs_n[1], 1, 1);
-            copy_x(feed, 1, 1);
-        }
-        if (nkb > 2) weights(2, 2);
-        v16f an[2];
-#pragma unroll
-        for (int ts = 0; ts < 2; ++ts)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) an[ts][r] = 0.f;
-        int wslot = 0;
-        for (int kb = 0; kb < nkb; ++kb) {
-            const uint32_t sW = a00 + wslot * W_TILE, sX = b00 + (kb & 1) * X_TILE;
-            v8i a[2], b[2][2];
-#pragma unroll
-            for (int ks = 0; ks < 2; ++ks) {
-                a[ks] = lds_operand(sW ^ (ks * 64), sW ^ (ks * 64 + 16), 0);
-                b[0][ks] = lds_operand(sX ^ (ks * 64), sX ^ (ks * 64 + 16), 0);
-                b[1][ks] = lds_operand(sX ^ (ks * 64), sX ^ (ks * 64 + 16), 32 * KB);
+                for (int ts = 0; ts < NG; ++ts) xs_load(xs_n[ts], kb, ts);
+            };
+            xs_loads(0);
+            if (nkb > 1) {
+                weights(1, 1);
+                asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
+            } else {
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             }
-            float wsa, wsb;                                    // complete at the barrier below
-            asm volatile("s_load_dword %0, %2, 0x0\n\ts_load_dword %1, %3, 0x0"
-                         : "=&s"(wsa), "=&s"(wsb) : "s"(sa_e + kb), "s"(sb_e + kb) : "memory");
-            v16f T0, T1;
-            mfma_new(T0, a[0], b[0][0]);
-            mfma_acc(T0, a[1], b[0][1]);
-            mfma_new(T1, a[0], b[1][0]);
-            mfma_acc(T1, a[1], b[1][1]);
-            // this wave's reads of block kb are done (the operands are in registers): wait for the copies that must be
-            // complete (all but the weight block two steps ahead), meet the other waves, refill the freed slots
-            if (kb + 2 < nkb) asm volatile("s_waitcnt vmcnt(4) lgkmcnt(0)" ::: "memory");
-            else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
             __builtin_amdgcn_s_barrier();
             asm volatile("" ::: "memory");
-            asm volatile("" : "+s"(wsa), "+s"(wsb));           // not used above this point
-            const float x0 = xs_cur[0], x1 = xs_cur[1];
 #pragma unroll
-            for (int ts = 0; ts < 2; ++ts) asm volatile("v_mov_b32 %0, %1" : "=v"(xs_cur[ts]) : "v"(xs_n[ts]));
-            if (kb + 2 < nkb) {
-                xs_load(xs_n[0], kb + 2, 0);
-                xs_load(xs_n[1], kb + 2, 1);
-                copy_x(feed, kb + 2, kb & 1);
+            for (int ts = 0; ts < NG; ++ts) asm volatile("v_mov_b32 %0, %1" : "=v"(xs_cur[ts]) : "v"(xs_n[ts]));
+            if (nkb > 1) {
+                xs_loads(1);
+                copy_x(feed, 1, 1);
             }
-            if (kb + 3 < nkb) weights(kb + 3, wslot);
-            // the four matrix instructions have left the pipe by now; a few wait states more cost nothing here
-            asm volatile("s_nop 15\n\ts_nop 15\n\ts_nop 7" ::: "memory");
-            PIN(T0);
-            PIN(T1);
-            // accumulator rows 0..15 of the product (registers 0..7) are gate rows, 16..31 (registers 8..15) up rows
+            if (nkb > 2) weights(2, 2);
+            v16f an[NG];
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const float w = (GATED && r >= 8) ? wsb : wsa;
-                an[0][r] = fmaf(x0 * w, T0[r], an[0][r]);
-                an[1][r] = fmaf(x1 * w, T1[r], an[1][r]);
-            }
-            PIN(an[0]);
-            PIN(an[1]);
-            wslot = (wslot == NW_BUF - 1) ? 0 : wslot + 1;
-        }
-        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
-        __builtin_amdgcn_s_barrier();                          // every wave is done with the operand rings
-        asm volatile("" ::: "memory");
-        // ---- narrow epilogue.  Register r of an[ts] belongs to token row0 + ts*32 + l32 and staged row
-        //      32w + (r/4)*8 + half*4 + r%4 of this wave.
-        if (GATED) {
-            // registers 0..7: gate of features f0 + 16w + (r/4)*8 + half*4 + r%4, registers 8..15: up of the same
-            float h[2][8];
-            float amax[2] = {0.f, 0.f};
+            for (int ts = 0; ts < NG; ++ts)
 #pragma unroll
-            for (int ts = 0; ts < 2; ++ts) {
+                for (int r = 0; r < 16; ++r) an[ts][r] = 0.f;
+            int wslot = 0;
+            for (int kb = 0; kb < nkb; ++kb) {
+                const uint32_t sW = a00 + wslot * W_TILE, sX = b00 + (kb & 1) * X_TILE;
+                v8i a[2], b[NG][2];
 #pragma unroll
-                for (int r = 0; r < 8; ++r) {
-                    const float v = swiglu(an[ts][r], an[ts][r + 8]);
-                    h[ts][r] = v;
-                    amax[ts] = fmaxf(amax[ts], fabsf(v));
+                for (int ks = 0; ks < 2; ++ks) {
+                    a[ks] = lds_operand(sW ^ (ks * 64), sW ^ (ks * 64 + 16), 0);
+#pragma unroll
+                    for (int ts = 0; ts < NG; ++ts) b[ts][ks] = lds_operand(sX ^ (ks * 64), sX ^ (ks * 64 + 16), ts * 32 * KB);
                 }
-                amax[ts] = fmaxf(amax[ts], __shfl_xor(amax[ts], 32));
-                if (half == 0) s_amax[wave * 64 + ts * 32 + l32] = amax[ts];
+                float wsa, wsb;                                    // complete at the barrier below
+                asm volatile("s_load_dword %0, %2, 0x0\n\ts_load_dword %1, %3, 0x0"
+                             : "=&s"(wsa), "=&s"(wsb) : "s"(sa_e + kb), "s"(sb_e + kb) : "memory");
+                v16f T[NG];
+#pragma unroll
+                for (int ts = 0; ts < NG; ++ts) {
+                    mfma_new(T[ts], a[0], b[ts][0]);
+                    mfma_acc(T[ts], a[1], b[ts][1]);
+                }
+                // this wave's reads of block kb are done (the operands are in registers): wait for the copies that must be
+                // complete (all but the weight block two steps ahead), meet the other waves, refill the freed slots
+                if (kb + 2 < nkb) asm volatile("s_waitcnt vmcnt(4) lgkmcnt(0)" ::: "memory");
+                else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+                __builtin_amdgcn_s_barrier();
+                asm volatile("" ::: "memory");
+                asm volatile("" : "+s"(wsa), "+s"(wsb));           // not used above this point
+                float x[NG];
+#pragma unroll
+                for (int ts = 0; ts < NG; ++ts) {
+                    x[ts] = xs_cur[ts];
+                    asm volatile("v_mov_b32 %0, %1" : "=v"(xs_cur[ts]) : "v"(xs_n[ts]));
+                }
+                if (kb + 2 < nkb) {
+                    xs_loads(kb + 2);
+                    copy_x(feed, kb + 2, kb & 1);
+                }
+                if (kb + 3 < nkb) weights(kb + 3, wslot);
+                // the matrix instructions have left the pipe by now; a few wait states more cost nothing here
+                asm volatile("s_nop 15\n\ts_nop 15\n\ts_nop 7" ::: "memory");
+#pragma unroll
+                for (int ts = 0; ts < NG; ++ts) PIN(T[ts]);
+                // accumulator rows 0..15 of the product (registers 0..7) are gate rows, 16..31 (registers 8..15) up rows
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const float w = (GATED && r >= 8) ? wsb : wsa;
+#pragma unroll
+                    for (int ts = 0; ts < NG; ++ts) an[ts][r] = fmaf(x[ts] * w, T[ts][r], an[ts][r]);
+                }
+#pragma unroll
+                for (int ts = 0; ts < NG; ++ts) PIN(an[ts]);
+                wslot = (wslot == NW_BUF - 1) ? 0 : wslot + 1;
             }
-            __syncthreads();                                   // the 128 features of a token's group live in all 8 waves
-            uint8_t* const s_codes = smem + 8 * NARROW_ROWS * 4;       // out through LDS, as from a full tile
+            asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+            __builtin_amdgcn_s_barrier();                          // every wave is done with the operand rings
+            asm volatile("" ::: "memory");
+            // ---- narrow epilogue.  Register r of an[ts] belongs to token row0 + ts*32 + l32 and staged row
+            //      32w + (r/4)*8 + half*4 + r%4 of this wave.
+            if (GATED) {
+                // registers 0..7: gate of features f0 + 16w + (r/4)*8 + half*4 + r%4, registers 8..15: up of the same
+                float h[NG][8];
+                float amax[NG];
 #pragma unroll
-            for (int ts = 0; ts < 2; ++ts) {
-                const int trow = ts * 32 + l32;
-                const int p = wk.row0 + trow;
-                float am = 0.f;
+                for (int ts = 0; ts < NG; ++ts) {
+                    amax[ts] = 0.f;
 #pragma unroll
-                for (int w = 0; w < 8; ++w) am = fmaxf(am, s_amax[w * 64 + trow]);
-                const float sc = (am == 0.f) ? 1.0f : am / 448.0f;
-                const Quotient q(sc);
-                uint8_t* const dst = s_codes + trow * CODES_LD + wave * 16 + half * 4;
+                    for (int r = 0; r < 8; ++r) {
+                        const float v = swiglu(an[ts][r], an[ts][r + 8]);
+                        h[ts][r] = v;
+                        amax[ts] = fmaxf(amax[ts], fabsf(v));
+                    }
+                    amax[ts] = fmaxf(amax[ts], __shfl_xor(amax[ts], 32));
+                    if (half == 0) s_amax[wave * NARROW_ROWS + ts * 32 + l32] = amax[ts];
+                }
+                __syncthreads();                                   // the 128 features of a token's group live in all 8 waves
+                uint8_t* const s_codes = smem + 8 * NARROW_ROWS * 4;       // out through LDS, as from a full tile
 #pragma unroll
-                for (int r4 = 0; r4 < 2; ++r4)
-                    *reinterpret_cast<uint32_t*>(dst + r4 * 8) =
-                        e4m3_codes4(q, h[ts][r4 * 4], h[ts][r4 * 4 + 1], h[ts][r4 * 4 + 2], h[ts][r4 * 4 + 3]);
-                if (half == 0 && wave == 0 && p < row_end) hs[(size_t)wk.ft * n_rows + p] = sc;
-            }
-            __syncthreads();
-            store_codes(hq, s_codes, wk, f0, NOUT, tid);
-        } else {
-            // 64 rows x 256 features: 16-byte pieces straight from the accumulator layout (a narrow tile's output is small)
+                for (int ts = 0; ts < NG; ++ts) {
+                    const int trow = ts * 32 + l32;
+                    const int p = wk.row0 + trow;
+                    float am = 0.f;
 #pragma unroll
-            for (int ts = 0; ts < 2; ++ts) {
-                const int p = wk.row0 + ts * 32 + l32;
-                if (p >= row_end) continue;
+                    for (int w = 0; w < 8; ++w) am = fmaxf(am, s_amax[w * NARROW_ROWS + trow]);
+                    const float sc = (am == 0.f) ? 1.0f : am / 448.0f;
+                    const Quotient q(sc);
+                    uint8_t* const dst = s_codes + trow * CODES_LD + wave * 16 + half * 4;
 #pragma unroll
-                for (int r4 = 0; r4 < 4; ++r4) {
-                    const int fcol = f0 + wave * 32 + r4 * 8 + half * 4;
-                    if (fcol < NOUT)
-                        *reinterpret_cast<float4*>(y_perm + (size_t)p * NOUT + fcol) =
-                            make_float4(an[ts][r4 * 4], an[ts][r4 * 4 + 1], an[ts][r4 * 4 + 2], an[ts][r4 * 4 + 3]);
+                    for (int r4 = 0; r4 < 2; ++r4)
+                        *reinterpret_cast<uint32_t*>(dst + r4 * 8) =
+                            e4m3_codes4(q, h[ts][r4 * 4], h[ts][r4 * 4 + 1], h[ts][r4 * 4 + 2], h[ts][r4 * 4 + 3]);
+                    if (half == 0 && wave == 0 && p < row_end) hs[(size_t)wk.ft * n_rows + p] = sc;
+                }
+                __syncthreads();
+                store_codes(hq, s_codes, wk, f0, NOUT, tid);
+            } else {
+                // a group's 32 features x 32 rows go through a region of the wave's own, so that eight lanes write 128 contiguous bytes of a
+                // row (straight from the accumulators 16 bytes for each of 64: the down projections above 42.8, 86.6, 93.4 and 829 us)
+                constexpr int LD = 36;
+                float* const stage = reinterpret_cast<float*>(smem) + wave * (32 * LD);
+                if (f0 + wave * 32 < NOUT) {
+#pragma unroll
+                    for (int ts = 0; ts < NG; ++ts) {
+#pragma unroll
+                        for (int r4 = 0; r4 < 4; ++r4)
+                            *reinterpret_cast<v4f*>(stage + l32 * LD + r4 * 8 + half * 4) =
+                                v4f{an[ts][r4 * 4], an[ts][r4 * 4 + 1], an[ts][r4 * 4 + 2], an[ts][r4 * 4 + 3]};
+                        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");      // as in the full tiles' epilogue
+                        v4f v[4];
+#pragma unroll
+                        for (int it = 0; it < 4; ++it) v[it] = *reinterpret_cast<const v4f*>(stage + (it * 8 + (lane >> 3)) * LD + (lane & 7) * 4);
+                        const int p = wk.row0 + ts * 32 + (lane >> 3);
+                        float* const dst = y_perm + (size_t)p * NOUT + f0 + wave * 32 + (lane & 7) * 4;
+#pragma unroll
+                        for (int it = 0; it < 4; ++it)
+                            if (p + it * 8 < row_end) *reinterpret_cast<v4f*>(dst + (size_t)(it * 8) * NOUT) = v[it];
+                    }
                 }
             }
-        }
+        };
+        if (wk.nrows <= 64) run(std::integral_constant<int, 2>{});
+        else run(std::integral_constant<int, 3>{});
         return;
     }
     // ---- full tile: 32-row token groups n = ceil(rows / 32) of 3..8 (LINEAR: 2..8); waves 0..3 (token half 0) take the first ceil(n/2)
@@ -705,15 +759,16 @@ __global__ __launch_bounds__(NTHREADS, 1) void ffn_gemm(const uint8_t* __restric
     const int n_grp = (wk.nrows + 31) >> 5;
     const int grp0 = wt == 0 ? 0 : (n_grp + 1) >> 1;           // this wave's first token group
     const int nts = wt == 0 ? (n_grp + 1) >> 1 : n_grp >> 1;   // and how many it has (1..4), wave-uniform
-    v16f acc[2][4];                                            // k_loop<nts> defines the first nts of each
+    const int l16 = lane & 15, quad = lane >> 4;
+    v4f acc[4][8];                                             // k_loop<nts> defines the first 2*nts of each
     Tile tile;
     tile.lds0 = lds0;
     tile.nkb = nkb;
-    tile.a_row = (uint32_t)(wf * 64 + l32) * KB;
-    tile.b_row = (uint32_t)(X_RING + (grp0 * 32 + l32) * KB);
-    tile.l32 = l32;
-    tile.half = half;
-    tile.row = wk.row0 + grp0 * 32 + l32;
+    tile.a_row = (uint32_t)(wf * 64 + l16) * KB;
+    tile.b_row = (uint32_t)(X_RING + (grp0 * 32 + l16) * KB);
+    tile.l16 = l16;
+    tile.quad = quad;
+    tile.row = wk.row0 + grp0 * 32 + lane;
     tile.n_rows = n_rows;
     tile.act_s = reinterpret_cast<const uint8_t*>(act_s);
     tile.sa = sa_e;
@@ -734,47 +789,48 @@ __global__ __launch_bounds__(NTHREADS, 1) void ffn_gemm(const uint8_t* __restric
     __builtin_amdgcn_s_barrier();                              // every wave is done with the operand rings
     asm volatile("" ::: "memory");
 
-    // ---- epilogue.  Accumulator (s, ts, r) of this lane belongs to token
-    //      row0 + (grp0 + ts)*32 + l32 and staged weight row wf*64 + s*32 + (r/4)*8 + half*4 + r%4.
+    // ---- epilogue.  Accumulator (s, tt, r) of this lane belongs to token
+    //      row0 + grp0*32 + tt*16 + l16 and staged weight row wf*64 + s*16 + quad*4 + r.
     if (GATED) {
-        // s = 0 gate, s = 1 up of features f0 + wf*32 + (r/4)*8 + half*4 + r%4
-        float h[4][16];
+        // s = 0, 1 gate, s = 2, 3 up of features f0 + wf*32 + (s%2)*16 + quad*4 + r
+        float h[8][8];
 #pragma unroll
-        for (int ts = 0; ts < 4; ++ts) {
-            if (ts >= nts) break;
+        for (int tt = 0; tt < 8; ++tt) {
+            if (tt >= 2 * nts) break;
             float am = 0.f;
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const float v = swiglu(acc[0][ts][r], acc[1][ts][r]);
-                h[ts][r] = v;
+            for (int i = 0; i < 8; ++i) {
+                const float v = swiglu(acc[i >> 2][tt][i & 3], acc[2 + (i >> 2)][tt][i & 3]);
+                h[tt][i] = v;
                 am = fmaxf(am, fabsf(v));
             }
-            am = fmaxf(am, __shfl_xor(am, 32));                // the lane pair covers 32 features
-            if (half == 0) s_amax[wf * X_ROWS + (grp0 + ts) * 32 + l32] = am;
+            am = fmaxf(am, __shfl_xor(am, 16));                // the four lane groups cover 32 features
+            am = fmaxf(am, __shfl_xor(am, 32));
+            if (quad == 0) s_amax[wf * X_ROWS + grp0 * 32 + tt * 16 + l16] = am;
         }
         __syncthreads();                                       // the other 96 features live in the other three waves of wt
         uint8_t* const s_codes = smem + 4 * X_ROWS * 4;        // [X_ROWS][CODES_LD], behind s_amax
 #pragma unroll
-        for (int ts = 0; ts < 4; ++ts) {
-            if (ts >= nts) break;
-            const int trow = (grp0 + ts) * 32 + l32;
+        for (int tt = 0; tt < 8; ++tt) {
+            if (tt >= 2 * nts) break;
+            const int trow = grp0 * 32 + tt * 16 + l16;
             const int p = wk.row0 + trow;
             const float am = fmaxf(fmaxf(s_amax[trow], s_amax[X_ROWS + trow]),
                                    fmaxf(s_amax[2 * X_ROWS + trow], s_amax[3 * X_ROWS + trow]));
             const float sc = (am == 0.f) ? 1.0f : am / 448.0f;
             const Quotient q(sc);
-            uint8_t* const dst = s_codes + trow * CODES_LD + wf * 32 + half * 4;
+            uint8_t* const dst = s_codes + trow * CODES_LD + wf * 32 + quad * 4;
 #pragma unroll
-            for (int r4 = 0; r4 < 4; ++r4)
-                *reinterpret_cast<uint32_t*>(dst + r4 * 8) =
-                    e4m3_codes4(q, h[ts][r4 * 4], h[ts][r4 * 4 + 1], h[ts][r4 * 4 + 2], h[ts][r4 * 4 + 3]);
-            if (half == 0 && wf == 0 && p < row_end) hs[(size_t)wk.ft * n_rows + p] = sc;
+            for (int s = 0; s < 2; ++s)
+                *reinterpret_cast<uint32_t*>(dst + s * 16) =
+                    e4m3_codes4(q, h[tt][s * 4], h[tt][s * 4 + 1], h[tt][s * 4 + 2], h[tt][s * 4 + 3]);
+            if (quad == 0 && wf == 0 && p < row_end) hs[(size_t)wk.ft * n_rows + p] = sc;
         }
         __syncthreads();
         store_codes(hq, s_codes, wk, f0, NOUT, tid);
     } else {
-        // The accumulators hold 16-byte pieces of 64 different rows per store instruction, which the memory
-        // pipeline would take as 64 separate requests.  Each wave therefore turns its 64 x 32-token blocks through a
+        // A store instruction straight from the accumulators would carry 64 bytes for each of 16 different rows in 16-byte pieces, which the
+        // memory pipeline takes as separate requests.  Each wave therefore turns its 64 x 32-token blocks through a
         // private LDS region (the operand rings are free now), two regions in turn, and writes 256 contiguous
         // bytes of a row with every 16 lanes.
         constexpr int TS_STRIDE = 68;                          // floats per staged token row: 64 + 4 of padding
@@ -785,24 +841,22 @@ __global__ __launch_bounds__(NTHREADS, 1) void ffn_gemm(const uint8_t* __restric
                 if (ts >= nts) break;
                 float* const stage = reinterpret_cast<float*>(smem) + (wave * 2 + (ts & 1)) * (32 * TS_STRIDE);
 #pragma unroll
-                for (int s = 0; s < 2; ++s)
+                for (int h = 0; h < 2; ++h)
 #pragma unroll
-                    for (int r4 = 0; r4 < 4; ++r4)
-                        *reinterpret_cast<float4*>(stage + l32 * TS_STRIDE + s * 32 + r4 * 8 + half * 4) =
-                            make_float4(acc[s][ts][r4 * 4], acc[s][ts][r4 * 4 + 1], acc[s][ts][r4 * 4 + 2],
-                                        acc[s][ts][r4 * 4 + 3]);
+                    for (int s = 0; s < 4; ++s)
+                        *reinterpret_cast<v4f*>(stage + (h * 16 + l16) * TS_STRIDE + s * 16 + quad * 4) = acc[s][2 * ts + h];
                 // the lanes of a wave run in step: once its own LDS writes have completed, every lane's have (and the
                 // reads of the region used two groups ago have been consumed by their stores)
                 asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-                float4 v[8];
+                v4f v[8];
 #pragma unroll
                 for (int it = 0; it < 8; ++it)
-                    v[it] = *reinterpret_cast<const float4*>(stage + (it * 4 + (lane >> 4)) * TS_STRIDE + (lane & 15) * 4);
+                    v[it] = *reinterpret_cast<const v4f*>(stage + (it * 4 + (lane >> 4)) * TS_STRIDE + (lane & 15) * 4);
                 const int p = wk.row0 + (grp0 + ts) * 32 + (lane >> 4);
                 float* const dst = y_perm + (size_t)p * NOUT + fcol + (lane & 15) * 4;
 #pragma unroll
                 for (int it = 0; it < 8; ++it)
-                    if (p + it * 4 < row_end) *reinterpret_cast<float4*>(dst + (size_t)(it * 4) * NOUT) = v[it];
+                    if (p + it * 4 < row_end) *reinterpret_cast<v4f*>(dst + (size_t)(it * 4) * NOUT) = v[it];
             }
         }
     }

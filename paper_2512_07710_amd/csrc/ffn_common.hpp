@@ -6,6 +6,7 @@ namespace moe355 {
 
 typedef int v8i __attribute__((ext_vector_type(8)));
 typedef float v16f __attribute__((ext_vector_type(16)));
+typedef float v4f __attribute__((ext_vector_type(4)));
 typedef int v4i __attribute__((ext_vector_type(4)));
 
 constexpr int KB = QBLOCK;                        // K bytes per stage (= one scale block)

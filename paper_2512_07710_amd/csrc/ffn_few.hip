@@ -29,8 +29,6 @@
 namespace moe355 {
 namespace {
 
-typedef float v4f __attribute__((ext_vector_type(4)));
-
 constexpr int PART_LD = 36;                           // floats per row of the LDS tile of partial sums: 32 + 4 of padding
 constexpr int few_stage(int nt) { return 32 * KB + nt * 16 * KB + 256; }
 constexpr int few_part(int nt) { return nt * 16 * PART_LD * 4; }

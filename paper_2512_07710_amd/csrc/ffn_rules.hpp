@@ -11,7 +11,10 @@ namespace moe355 {
 // 157, 420 337 / 340 | 232 / 235; 128 x 2048 x 768 at 112 88 / 83 | 76 / 69, 258 142 / 143 | 126 / 119; 16 x 3072 x 2048 at 80 42.1 /
 // 38.3 | 26.3 / 25.7.  With four tiles (1030 rows) the gate/up projection is 2 % slower past them, 4 % at 7168 x 2048.
 constexpr int GATE_UP_ONCE_TILES = 1, DOWN_ONCE_TILES = 2;
-constexpr int NARROW_ROWS = 64;                     // tiles of at most this many rows take the narrow path of ffn_gemm
+// Tiles that take the narrow path of ffn_gemm: up to so many rows if they are all of their expert's, up to so many if another tile shares
+// the weights.  (16 experts of 130 rows x 7168 x 512, tiles of 64 and 66, gate/up, us: both narrow 62.2, one 51.4: two and three groups
+// do not keep in step.)
+constexpr int NARROW_ROWS = 96, NARROW_SHARED_ROWS = 64;
 
 // one work unit: rows [row0, row0 + nrows) of an expert x feature tile ft (128 features gate/up, 256 down); tiles: row tiles of the
 // expert, as far as MANY_TILES

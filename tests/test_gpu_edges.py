@@ -213,6 +213,13 @@ def test_chosen_tile_heights(gpu_lib, counts, d, F):
     _run_heights(gpu_lib, counts, d, F)
 
 
+@pytest.mark.parametrize("d,F", [(128, 128), (384, 256), (640, 384)])
+def test_narrow_tiles_of_two_and_three_groups(gpu_lib, d, F):
+    """Experts on both sides of every row count at which a narrow tile changes: two or three groups of 32 rows, the copies of 8 rows
+    that are left out, and the first count that is no narrow tile any more; output feature tiles that are half empty."""
+    _run_heights(gpu_lib, [63, 64, 65, 72, 73, 80, 81, 88, 89, 95, 96, 97, 104, 90, 70], d, F)
+
+
 @pytest.mark.parametrize("rows", [1, 15, 16, 17, 31, 32, 33, 48, 65])
 def test_activation_codes_at_block_edges(gpu_lib, rows):
     """Row counts around the quantisation kernel's 32-row blocks, plain and fanned out, with the values its short quotient has
