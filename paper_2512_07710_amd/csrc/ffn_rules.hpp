@@ -151,12 +151,34 @@ constexpr int64_t GATE_UP_STREAM_ROWS = 8, GATE_UP_STREAM_ROWS_IDLE = 32, DOWN_S
 constexpr int64_t GATE_UP_SKEW_UNITS = 256, DOWN_SKEW_UNITS = 512;
 constexpr int LINEAR_STREAM_UNITS = 256;
 
+// upper bound on row tiles: every full tile, and one more for each expert that has rows
+inline int64_t max_row_tiles(const moe_dims* D, int rows) {
+    const int64_t N = (int64_t)D->T * D->k;
+    return N / rows + (N < D->E ? N : D->E);
+}
+// A layer whose streaming units, at most, make one round of a unit to a CU: streaming, whatever its rows per expert (the big tiles' units
+// are half as many and leave more than half of the chip idle; neither list nor sorted scales are needed).  The units at most: no load
+// makes more.  Layers, us, big tiles / streaming, and units of the gate/up | down projection: 350 tokens x 4 of 16 experts, 2048 x 512
+// 46.0 / 34.5, 148 | 296; 400 x 2 of 8, 4096 x 1024 66.0 / 43.2, 160 | 320; 60 x 6 of 8, 7168 x 2048 88.5 / 73.4, 208 | 364; 640 x 1 of 8,
+// 7168 x 1536 96.9 / 91.8, 216 | 504; 200 x 8 of 9, 7168 x 512 83.3 / 68.2, 136 | 952; 700 x 4 of 16, 2048 x 512 49.0 / 48.1, 236 | 472;
+// Zipf loads 500 x 4 of 8, 2048 x 512 48.1 / 42.1, 156 | 312; and beyond: 1024 x 1 of 16, 4096 x 1024 72.0 / 75.2, 256 | 512, 1000 x 2 of 8,
+// 1024 x 1024 39.4 / 40.6, 312 | 156.  The down projection alone: 92 units 23.2 / 13.6, 156 16.2 / 13.7, 180 13.7 / 11.4, 216 13.7 / 12.9,
+// 252 15.8 / 17.5.  Layers narrower than 512 gain too (256 x 256 25.4 / 21.5), but with them every tile height is tested.
+constexpr int64_t ROUND_UNITS = 240, ROUND_DOWN_UNITS = 1000, ROUND_DOWN_ALONE_UNITS = 200, ROUND_WIDTH = 512;
+inline bool in_one_round(const moe_dims* D, int feature_tiles, int64_t most) {
+    return D->d >= ROUND_WIDTH && D->F >= ROUND_WIDTH && max_row_tiles(D, STREAM_ROWS) * feature_tiles <= most;
+}
+inline bool layer_in_one_round(const moe_dims* D) {
+    return in_one_round(D, D->F / 128, ROUND_UNITS) && in_one_round(D, (D->d + 255) / 256, ROUND_DOWN_UNITS);
+}
+
 inline bool skew_is_harmless(const moe_dims* D, int feature_tiles, int64_t most_units) {
     const int64_t tiles = (D->T + STREAM_ROWS - 1) / STREAM_ROWS;
     return tiles <= 1 || D->k * tiles * feature_tiles <= most_units;    // one tile: no weight passes twice
 }
 enum class Down { BIG, STREAM, EITHER };
 inline Down down_form(const moe_dims* D) {
+    if (layer_in_one_round(D) || in_one_round(D, (D->d + 255) / 256, ROUND_DOWN_ALONE_UNITS)) return Down::STREAM;
     if ((int64_t)D->T * D->k > DOWN_STREAM_ROWS * D->E) return Down::BIG;
     return skew_is_harmless(D, (D->d + 255) / 256, DOWN_SKEW_UNITS) ? Down::STREAM : Down::EITHER;
 }
@@ -166,6 +188,7 @@ inline double experts_met(const moe_dims* D) {                 // with at least 
 // (only where the down projection streams for certain: then no lists are needed)
 inline bool gate_up_streams(const moe_dims* D) {
     const int64_t N = (int64_t)D->T * D->k;
+    if (N > 0 && layer_in_one_round(D)) return true;
     if (N == 0 || down_form(D) != Down::STREAM || !skew_is_harmless(D, D->F / 128, GATE_UP_SKEW_UNITS)) return false;
     if (N <= GATE_UP_STREAM_ROWS * D->E) return true;
     return N <= GATE_UP_STREAM_ROWS_IDLE * D->E && experts_met(D) * (D->F / 128) < CUS;
@@ -200,11 +223,6 @@ inline int linear_tiles(int32_t rows, int nft, int nkb) {
     return (int)(((int64_t)rows + h - 1) / h);
 }
 
-// upper bound on row tiles: every full tile, and one more for each expert that has rows
-inline int64_t max_row_tiles(const moe_dims* D, int rows) {
-    const int64_t N = (int64_t)D->T * D->k;
-    return N / rows + (N < D->E ? N : D->E);
-}
 // Room of a big-tile list, and blocks of its launch: the least height that can be the better one has to fit.  A first round that is
 // not full may gain from half the height; the more rounds, the less there is to gain.  us, this room / room for half the height
 // everywhere / for 256 alone, gate/up | down: 16 x 3072 x 2048 at 750 rows (992 | 744 units) 172 / 172 / 184 | 99 / 100 / 112, 32 x 3072 x

@@ -220,6 +220,17 @@ def test_narrow_tiles_of_two_and_three_groups(gpu_lib, d, F):
     _run_heights(gpu_lib, [63, 64, 65, 72, 73, 80, 81, 88, 89, 95, 96, 97, 104, 90, 70], d, F)
 
 
+# Layers of so few units that both projections stream whatever their rows per expert, or the down projection alone (which of them:
+# tests/test_tile_rules_host.py): no rows to five tiles of them, feature tiles that are half empty.
+ROUND_COUNTS = [0, 1, 63, 64, 65, 129, 200, 300]
+ROUND_SHAPES = [(512, 640), (640, 512), (512, 2048)]
+
+
+@pytest.mark.parametrize("d,F", ROUND_SHAPES)
+def test_layers_of_one_round(gpu_lib, d, F):
+    _run_heights(gpu_lib, ROUND_COUNTS, d, F)
+
+
 @pytest.mark.parametrize("rows", [1, 15, 16, 17, 31, 32, 33, 48, 65])
 def test_activation_codes_at_block_edges(gpu_lib, rows):
     """Row counts around the quantisation kernel's 32-row blocks, plain and fanned out, with the values its short quotient has

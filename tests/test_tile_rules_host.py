@@ -111,6 +111,11 @@ def test_tile_height_layers_reach_every_height_and_group_count(rules):
     assert {g for g, _, _, half_empty in groups[1] if half_empty} == set(range(1, 9))
 
 
+def test_layers_of_one_round_stream(rules):
+    forms = lambda d, F: [p[0] for p in _layer(rules, edges.ROUND_COUNTS, d, F)]
+    assert [forms(*s) for s in edges.ROUND_SHAPES] == [["stream", "stream"], ["stream", "stream"], ["big", "stream"]]
+
+
 def test_linear_shapes_reach_what_they_are_for(rules):
     form = lambda r, K, n: rules(f"L {r} {K} {n}")[0].split()
     met = set()
