@@ -63,13 +63,37 @@ __device__ inline int wave_scan(int v) {
     v += from_lanes<0x143, 0xc>(v);
     return v;
 }
+// How a list of `units` is dealt to the XCDs, by one wave: lane x <= NXCD brings the boundary of equal costs before XCD x, and the cost
+// up to that of equal numbers.  (By one thread, one XCD after another, 1.5 us of every list.)
+__device__ inline void deal(int begin, int cost_to, int units, int slots, int lane, Queue* __restrict__ q) {
+    const bool xcd = lane < NXCD;
+    const int chunk = (units + NXCD - 1) / NXCD, even = min(lane * chunk, units);
+    auto next = [](int v) { return from_lanes<0x101, 0xf>(v); };         // row_shl 1: the next lane's
+    auto sum = [](int v) { return __builtin_amdgcn_readlane(wave_scan(v), 63); };
+    auto slowest = [&](float t) {                              // row_shr 1, 2, 4: lane 7 has the largest of the eight (none is negative)
+        t = fmaxf(t, __int_as_float(from_lanes<0x111, 0xf>(__float_as_int(t))));
+        t = fmaxf(t, __int_as_float(from_lanes<0x112, 0xf>(__float_as_int(t))));
+        t = fmaxf(t, __int_as_float(from_lanes<0x114, 0xf>(__float_as_int(t))));
+        return __builtin_amdgcn_readlane(__float_as_int(t), NXCD - 1);   // (as bits: ordered as the numbers are)
+    };
+    const float all = (float)__builtin_amdgcn_readlane(cost_to, NXCD);
+    const int by_cost = slowest(rounds_time(next(begin) - begin, all / NXCD));
+    const int by_number = slowest(rounds_time(min((lane + 1) * chunk, units) - even, (float)(next(cost_to) - cost_to)));
+    const bool uneven = units > CUS && by_cost < by_number && __ballot(xcd && far_off(begin, even, chunk)) != 0;   // (XCD 0 begins at 0 both ways)
+    const int at = uneven ? begin : even;
+    const int count = next(at) - at, fixed = xcd ? fixed_units(count, slots) : 0;
+    const int left = sum(xcd ? count - fixed : 0), helpers = helpers_for(left), room = sum(xcd ? min(helpers, slots - fixed) : 0);
+    if (lane <= NXCD) q->begin[lane] = at;
+    if (xcd) q->fixed[lane] = fixed;
+    if (lane == 0) q->helpers = room >= left ? helpers : slots;
+}
 // Block (e, l) writes the units of expert e into list l (0: gate/up, 1: down); every block recomputes the tile counts of all
 // experts for its base index and the height, and block (0, l) deals the list to the XCDs.
 // choose: list 1 is left empty (queue->total = 0) unless the batch is concentrated, see DOWN_SKEW_UNITS.
 __device__ inline void build_work(const int32_t* __restrict__ offsets, int E, int e, int list, const ListShape& shape, bool choose,
                                   Work* __restrict__ work, Queue* __restrict__ queue, Rest* __restrict__ rest) {
     constexpr int SUMS = HEIGHTS + 2, WAVES = MAX_E / 64;      // tiles at each height, groups of 32 rows, tiles of 64
-    __shared__ int32_t s_sums[WAVES][SUMS], s_scan[WAVES], s_cost[WAVES], s_begin[NXCD + 1], s_base;
+    __shared__ int32_t s_sums[WAVES][SUMS], s_scan[WAVES], s_cost[WAVES], s_begin[NXCD + 1], s_cost_to[NXCD + 1], s_base;
     const int tid = threadIdx.x, wave = tid >> 6;
     const int n_ft = shape.n_ft;
     const int rows_t = tid < E ? offsets[tid + 1] - offsets[tid] : 0;
@@ -103,7 +127,10 @@ __device__ inline void build_work(const int32_t* __restrict__ offsets, int E, in
         s_scan[wave] = tiles_to;
         s_cost[wave] = cost_to;
     }
-    if (tid <= NXCD) s_begin[tid] = tid == 0 ? 0 : total * n_ft;
+    if (tid <= NXCD) {
+        s_begin[tid] = tid == 0 ? 0 : total * n_ft;
+        s_cost_to[tid] = 0;
+    }
     __syncthreads();
     int cost_all = 0;
     for (int w = 0; w < WAVES; ++w) {
@@ -112,18 +139,27 @@ __device__ inline void build_work(const int32_t* __restrict__ offsets, int E, in
         cost_all += s_cost[w];
     }
     if (tid == e) s_base = tiles_to - nt_t;
-    if (e == 0 && nt_t > 0) {
+    if (e == 0 && nt_t > 0 && total * n_ft > CUS) {            // (a round or less is dealt by numbers)
         // the XCD boundaries that fall into expert tid, on whole feature tiles (their row tiles share the weights)
-        const float per_cost = (float)n_ft / (float)cost_t;
+        const float per_cost = (float)n_ft / (float)cost_t, per_unit = (float)cost_t / (float)nt_t;
 #pragma unroll
         for (int x = 1; x < NXCD; ++x) {
-            const int in = (int)((int64_t)cost_all * x / NXCD) - (cost_to - cost_t);
+            const int in = cost_all * x / NXCD - (cost_to - cost_t);
             if (in < 0 || in >= cost_t) continue;
             s_begin[x] = (tiles_to - nt_t) * n_ft + min((int)((float)in * per_cost), n_ft - 1) * nt_t;
         }
+        // and what lies before the boundaries of equal numbers that fall into it
+        const int units = total * n_ft, chunk = (units + NXCD - 1) / NXCD, first = (tiles_to - nt_t) * n_ft;
+#pragma unroll
+        for (int x = 1; x <= NXCD; ++x) {
+            const int in = min(x * chunk, units) - first;
+            if (in <= 0 || in > nt_t * n_ft) continue;
+            s_cost_to[x] = (cost_to - cost_t) * n_ft + (int)((float)in * per_unit);
+        }
     }
     __syncthreads();
-    if (e == 0 && tid == 0) deal(s_begin, list_blocks(shape.capacity) / NXCD, *queue);
+    if (e == 0 && wave == 0)
+        deal(s_begin[min(tid, NXCD)], s_cost_to[min(tid, NXCD)], total * n_ft, list_blocks(shape.capacity) / NXCD, tid, queue);
     if (e == 0 && tid < NXCD) rest[tid].taken = 0;
     const int start = offsets[e], cnt = offsets[e + 1] - start;
     const int nt = (cnt + h - 1) / h;

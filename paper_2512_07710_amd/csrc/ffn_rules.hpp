@@ -84,6 +84,14 @@ __host__ __device__ inline int pick_height(const int (&tiles)[HEIGHTS], int grou
 // numbers / this: the Zipf layer 1245 / 1175, the 256 experts 13505 / 13305, 128 experts of 257..261 rows 1100 / 1089.
 // What an expert's tiles cost, for each feature tile: a tile of 8 groups 1.6 times one of 2 (Zipf gate/up 68 and 46 us).
 __host__ __device__ inline int tiles_share(int tiles, int groups) { return 8 * tiles + groups; }
+// Units run one to a CU in rounds, and with few rounds it is their number that counts: a list that makes one full round in parts of equal
+// numbers may make two where an XCD with cheap units gets more of them than it has CUs.  So parts of equal cost are taken only where the
+// slowest XCD, by its rounds and its mean unit, is the faster for it (us, equal numbers / equal cost always / this: 8 experts of 2372 x 5
+// tokens, 2816 x 640 148.8 / 181.1 / 148.7, 17 Zipf experts of 2920 x 2, 4096 x 1792 204.6 / 230.9 / 201.5, 43 of 1179 x 8, 3328 x 1152
+// 215.9 / 241.4 / 216.7, 60 of 777 x 5, 2176 x 896 130.4 / 117.1 / 122.7).
+__host__ __device__ inline float rounds_time(int units, float cost) {
+    return units > 0 ? (float)((units + CUS / NXCD - 1) / (CUS / NXCD)) * cost / (float)units : 0.0f;
+}
 struct alignas(128) Queue {
     int32_t total;                                   // units of the list
     int32_t helpers;                                 // blocks of each XCD that look for a unit of the rest
@@ -96,28 +104,11 @@ __host__ __device__ inline int list_blocks(int units) { return (units + NXCD - 1
 // not felt, with four (64 experts of 150..200 rows x 4096 x 1408, down, 117 us) it took 7 us.  For the same reason only twice as many blocks
 // look for one as there are, or every block where those would be too few.
 constexpr int REST_UNITS = 192;
-// begin: boundaries of equal costs, given up for equal numbers where the two are close (whole rounds stay whole); slots: blocks that each
-// XCD will have.  Any unit of the rest finds a block: 8 * slots are at least as many as all units.
-__host__ __device__ inline void deal(const int32_t (&begin)[NXCD + 1], int slots, Queue& q) {
-    const int units = begin[NXCD], chunk = (units + NXCD - 1) / NXCD;
-    bool uneven = false;
-    for (int x = 1; x < NXCD; ++x) {
-        const int off = begin[x] - min(x * chunk, units);
-        uneven |= off > chunk / 8 || off < -chunk / 8;
-    }
-    int left = 0, room = 0, at[NXCD + 1], fixed[NXCD];
-    for (int x = 0; x <= NXCD; ++x) at[x] = uneven ? begin[x] : min(x * chunk, units);
-    for (int x = 0; x < NXCD; ++x) {
-        const int count = at[x + 1] - at[x];
-        fixed[x] = min(count >= REST_UNITS ? count - count / 16 : count, slots);
-        left += count - fixed[x];
-    }
-    const int helpers = (left + NXCD - 1) / NXCD * 2;
-    for (int x = 0; x < NXCD; ++x) room += min(helpers, slots - fixed[x]);
-    for (int x = 0; x <= NXCD; ++x) q.begin[x] = at[x];
-    for (int x = 0; x < NXCD; ++x) q.fixed[x] = fixed[x];
-    q.helpers = room >= left ? helpers : slots;
-}
+// Parts of equal cost are not taken either where no XCD would be off by more than an eighth of its part (whole rounds stay whole).
+__host__ __device__ inline bool far_off(int begin, int even, int chunk) { return begin - even > chunk / 8 || even - begin > chunk / 8; }
+// slots: blocks that each XCD will have.  Any unit of the rest finds a block: 8 * slots are at least as many as all units.
+__host__ __device__ inline int fixed_units(int count, int slots) { return min(count >= REST_UNITS ? count - count / 16 : count, slots); }
+__host__ __device__ inline int helpers_for(int left) { return (left + NXCD - 1) / NXCD * 2; }
 
 // One list for each projection: its feature tiles, K blocks and room.
 struct ListShape { int n_ft, nkb, capacity; bool one_height; };

@@ -150,11 +150,17 @@ int main() {                                                   // slots, nine bo
     int slots, begin[NXCD + 1];
     while (scanf("%d", &slots) == 1) {
         for (int& b : begin) if (scanf("%d", &b) != 1) return 1;
-        Queue q;
-        deal(begin, slots, q);
-        printf("%d", q.helpers);
-        for (int b : q.begin) printf(" %d", b);
-        for (int f : q.fixed) printf(" %d", f);
+        const int units = begin[NXCD], chunk = (units + NXCD - 1) / NXCD;
+        bool uneven = false;                                   // as the wave of the kernel that makes the lists does, lane by lane
+        int at[NXCD + 1], fixed[NXCD], left = 0, room = 0;
+        for (int x = 0; x < NXCD; ++x) uneven |= far_off(begin[x], min(x * chunk, units), chunk);
+        for (int x = 0; x <= NXCD; ++x) at[x] = uneven ? begin[x] : min(x * chunk, units);
+        for (int x = 0; x < NXCD; ++x) left += at[x + 1] - at[x] - (fixed[x] = fixed_units(at[x + 1] - at[x], slots));
+        const int helpers = helpers_for(left);
+        for (int x = 0; x < NXCD; ++x) room += min(helpers, slots - fixed[x]);
+        printf("%d", room >= left ? helpers : slots);
+        for (int b : at) printf(" %d", b);
+        for (int f : fixed) printf(" %d", f);
         printf("\n");
     }
     return 0;
