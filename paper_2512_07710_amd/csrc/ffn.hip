@@ -63,37 +63,33 @@ __device__ inline int wave_scan(int v) {
     v += from_lanes<0x143, 0xc>(v);
     return v;
 }
-// How a list of `units` is dealt to the XCDs, by one wave: lane x <= NXCD brings the boundary of equal costs before XCD x, and the cost
-// up to that of equal numbers.  (By one thread, one XCD after another, 1.5 us of every list.)
-__device__ inline void deal(int begin, int cost_to, int units, int slots, int lane, Queue* __restrict__ q) {
-    const bool xcd = lane < NXCD;
-    const int chunk = (units + NXCD - 1) / NXCD, even = min(lane * chunk, units);
-    auto next = [](int v) { return from_lanes<0x101, 0xf>(v); };         // row_shl 1: the next lane's
-    auto sum = [](int v) { return __builtin_amdgcn_readlane(wave_scan(v), 63); };
-    auto slowest = [&](float t) {                              // row_shr 1, 2, 4: lane 7 has the largest of the eight (none is negative)
+// The lanes of a wave as deal() wants them: lane x has XCD x's number, lane NXCD the one after the last.
+struct WaveLanes {
+    int lane;
+    template <class F, class... A>
+    __device__ auto each(F f, A... a) const { return f(min(lane, NXCD), a...); }
+    __device__ int next(int v) const { return from_lanes<0x101, 0xf>(v); }       // row_shl 1
+    __device__ int last(int v) const { return __builtin_amdgcn_readlane(v, NXCD); }
+    __device__ float most(float t) const {                     // row_shr 1, 2, 4: lane 7 has the largest of the eight (none is negative)
         t = fmaxf(t, __int_as_float(from_lanes<0x111, 0xf>(__float_as_int(t))));
         t = fmaxf(t, __int_as_float(from_lanes<0x112, 0xf>(__float_as_int(t))));
         t = fmaxf(t, __int_as_float(from_lanes<0x114, 0xf>(__float_as_int(t))));
-        return __builtin_amdgcn_readlane(__float_as_int(t), NXCD - 1);   // (as bits: ordered as the numbers are)
-    };
-    const float all = (float)__builtin_amdgcn_readlane(cost_to, NXCD);
-    const int by_cost = slowest(rounds_time(next(begin) - begin, all / NXCD));
-    const int by_number = slowest(rounds_time(min((lane + 1) * chunk, units) - even, (float)(next(cost_to) - cost_to)));
-    const bool uneven = units > CUS && by_cost < by_number && __ballot(xcd && far_off(begin, even, chunk)) != 0;   // (XCD 0 begins at 0 both ways)
-    const int at = uneven ? begin : even;
-    const int count = next(at) - at, fixed = xcd ? fixed_units(count, slots) : 0;
-    const int left = sum(xcd ? count - fixed : 0), helpers = helpers_for(left), room = sum(xcd ? min(helpers, slots - fixed) : 0);
-    if (lane <= NXCD) q->begin[lane] = at;
-    if (xcd) q->fixed[lane] = fixed;
-    if (lane == 0) q->helpers = room >= left ? helpers : slots;
-}
+        return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(t), NXCD - 1));
+    }
+    __device__ int sum(int v) const { return __builtin_amdgcn_readlane(wave_scan(v), NXCD - 1); }
+    __device__ bool any(bool b) const { return (__ballot(b) & ((1ull << NXCD) - 1)) != 0; }
+    __device__ void put(int32_t* to, int v, int n) const {
+        if (lane < n) to[lane] = v;
+    }
+};
 // Block (e, l) writes the units of expert e into list l (0: gate/up, 1: down); every block recomputes the tile counts of all
 // experts for its base index and the height, and block (0, l) deals the list to the XCDs.
 // choose: list 1 is left empty (queue->total = 0) unless the batch is concentrated, see DOWN_SKEW_UNITS.
 __device__ inline void build_work(const int32_t* __restrict__ offsets, int E, int e, int list, const ListShape& shape, bool choose,
                                   Work* __restrict__ work, Queue* __restrict__ queue, Rest* __restrict__ rest) {
     constexpr int SUMS = HEIGHTS + 2, WAVES = MAX_E / 64;      // tiles at each height, groups of 32 rows, tiles of 64
-    __shared__ int32_t s_sums[WAVES][SUMS], s_scan[WAVES], s_cost[WAVES], s_begin[NXCD + 1], s_cost_to[NXCD + 1], s_base;
+    __shared__ int32_t s_sums[WAVES][SUMS], s_scan[WAVES], s_cost[WAVES], s_base;
+    __shared__ Cuts s_cuts;
     const int tid = threadIdx.x, wave = tid >> 6;
     const int n_ft = shape.n_ft;
     const int rows_t = tid < E ? offsets[tid + 1] - offsets[tid] : 0;
@@ -115,10 +111,10 @@ __device__ inline void build_work(const int32_t* __restrict__ offsets, int E, in
 #pragma unroll
     for (int j = 1; j < HEIGHTS; ++j) total = h == tile_height(j) ? tiles[j] : total;
     const bool empty = choose && list == 1 && sums[HEIGHTS + 1] <= 2 * tiles[0];
-    if (e == 0 && tid == 0) queue->total = empty ? 0 : total * n_ft;
+    const int units = total * n_ft;
     if (empty) {
         if (e == 0 && tid < NXCD) queue->fixed[tid] = 0;
-        if (e == 0 && tid == 0) queue->helpers = 0;
+        if (e == 0 && tid == 0) queue->total = queue->helpers = 0;
         return;
     }
     const int nt_t = (rows_t + h - 1) / h, cost_t = tiles_share(nt_t, (rows_t + 31) / 32);
@@ -127,10 +123,7 @@ __device__ inline void build_work(const int32_t* __restrict__ offsets, int E, in
         s_scan[wave] = tiles_to;
         s_cost[wave] = cost_to;
     }
-    if (tid <= NXCD) {
-        s_begin[tid] = tid == 0 ? 0 : total * n_ft;
-        s_cost_to[tid] = 0;
-    }
+    if (tid <= NXCD) no_cut(s_cuts, tid, units);
     __syncthreads();
     int cost_all = 0;
     for (int w = 0; w < WAVES; ++w) {
@@ -139,27 +132,9 @@ __device__ inline void build_work(const int32_t* __restrict__ offsets, int E, in
         cost_all += s_cost[w];
     }
     if (tid == e) s_base = tiles_to - nt_t;
-    if (e == 0 && nt_t > 0 && total * n_ft > CUS) {            // (a round or less is dealt by numbers)
-        // the XCD boundaries that fall into expert tid, on whole feature tiles (their row tiles share the weights)
-        const float per_cost = (float)n_ft / (float)cost_t, per_unit = (float)cost_t / (float)nt_t;
-#pragma unroll
-        for (int x = 1; x < NXCD; ++x) {
-            const int in = cost_all * x / NXCD - (cost_to - cost_t);
-            if (in < 0 || in >= cost_t) continue;
-            s_begin[x] = (tiles_to - nt_t) * n_ft + min((int)((float)in * per_cost), n_ft - 1) * nt_t;
-        }
-        // and what lies before the boundaries of equal numbers that fall into it
-        const int units = total * n_ft, chunk = (units + NXCD - 1) / NXCD, first = (tiles_to - nt_t) * n_ft;
-#pragma unroll
-        for (int x = 1; x <= NXCD; ++x) {
-            const int in = min(x * chunk, units) - first;
-            if (in <= 0 || in > nt_t * n_ft) continue;
-            s_cost_to[x] = (cost_to - cost_t) * n_ft + (int)((float)in * per_unit);
-        }
-    }
+    if (e == 0 && nt_t > 0 && units > CUS) cut_expert(s_cuts, nt_t, tiles_to, cost_t, cost_to, cost_all, n_ft, units);
     __syncthreads();
-    if (e == 0 && wave == 0)
-        deal(s_begin[min(tid, NXCD)], s_cost_to[min(tid, NXCD)], total * n_ft, list_blocks(shape.capacity) / NXCD, tid, queue);
+    if (e == 0 && wave == 0) deal(WaveLanes{tid}, s_cuts, units, list_blocks(shape.capacity) / NXCD, *queue);
     if (e == 0 && tid < NXCD) rest[tid].taken = 0;
     const int start = offsets[e], cnt = offsets[e + 1] - start;
     const int nt = (cnt + h - 1) / h;
@@ -176,28 +151,11 @@ __device__ inline void build_work(const int32_t* __restrict__ offsets, int E, in
     }
 }
 
-// A unit of what the XCDs have left over, for a block with no unit of its own: of its own XCD while there are any, then of the one
-// with the most.  -1: none anywhere.  One thread of the block calls it.
-__device__ inline int take_rest(const Queue* __restrict__ q, Rest* __restrict__ rest, int x) {
-    for (int tries = 0; tries <= NXCD; ++tries) {              // (a try that fails has found one more XCD's rest used up, for good)
-        const int own = q->begin[x + 1] - q->begin[x] - q->fixed[x];
-        if (own > 0) {
-            const int t = __hip_atomic_fetch_add(&rest[x].taken, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if (t < own) return q->begin[x] + q->fixed[x] + t;
-        }
-        int taken[NXCD], most = 0;
-#pragma unroll
-        for (int y = 0; y < NXCD; ++y) taken[y] = __hip_atomic_load(&rest[y].taken, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-#pragma unroll
-        for (int y = 0; y < NXCD; ++y) {
-            const int left = q->begin[y + 1] - q->begin[y] - q->fixed[y] - taken[y];
-            x = left > most ? y : x;
-            most = max(most, left);
-        }
-        if (most == 0) return -1;
-    }
-    return -1;
-}
+struct RestCounts {
+    Rest* rest;
+    __device__ int take(int x) const { return __hip_atomic_fetch_add(&rest[x].taken, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+    __device__ int taken(int y) const { return __hip_atomic_load(&rest[y].taken, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+};
 
 // ------------------------------------------------------------------ helpers
 // The matrix instructions are written as volatile asm so that they stay exactly where the
@@ -538,11 +496,11 @@ __global__ __launch_bounds__(NTHREADS, 1) void ffn_gemm(const uint8_t* __restric
         wk.ft = wi / tiles;
         split_rows(n_rows, tiles, wi - wk.ft * tiles, wk);
     } else {
-        int wi = queue->begin[xcd] + slot;
-        if (slot >= queue->fixed[xcd]) {
-            if (slot >= queue->fixed[xcd] + queue->helpers) return;
+        int wi = own_unit(*queue, xcd, slot);
+        if (wi == NO_UNIT) return;
+        if (wi == LOOK) {
             int32_t& s_unit = *reinterpret_cast<int32_t*>(smem + X_RING - 16);
-            if (threadIdx.x == 0) s_unit = take_rest(queue, rest, xcd);
+            if (threadIdx.x == 0) s_unit = take_rest(*queue, RestCounts{rest}, xcd);
             __syncthreads();                                   // (the last weight slot, first copied to behind another barrier)
             wi = __builtin_amdgcn_readfirstlane(s_unit);
             if (wi < 0) return;

@@ -110,6 +110,83 @@ __host__ __device__ inline bool far_off(int begin, int even, int chunk) { return
 __host__ __device__ inline int fixed_units(int count, int slots) { return min(count >= REST_UNITS ? count - count / 16 : count, slots); }
 __host__ __device__ inline int helpers_for(int left) { return (left + NXCD - 1) / NXCD * 2; }
 
+// Where a list of `units` would be cut, at equal costs (begin) and at equal numbers (what lies before those cuts costs cost_to).
+struct Cuts { int32_t begin[NXCD + 1], cost_to[NXCD + 1]; };
+__host__ __device__ inline void no_cut(Cuts& c, int x, int units) {
+    c.begin[x] = x == 0 ? 0 : units;
+    c.cost_to[x] = 0;
+}
+// The cuts that fall into one expert of nt > 0 tiles and cost `cost`; the list up to and with it has tiles_to tiles that cost cost_to.
+__host__ __device__ inline void cut_expert(Cuts& c, int nt, int tiles_to, int cost, int cost_to, int cost_all, int n_ft, int units) {
+    const float per_cost = (float)n_ft / (float)cost, per_unit = (float)cost / (float)nt;
+    const int first = (tiles_to - nt) * n_ft, chunk = (units + NXCD - 1) / NXCD;
+#pragma unroll
+    for (int x = 1; x < NXCD; ++x) {                           // on whole feature tiles: their row tiles share the weights
+        const int in = cost_all * x / NXCD - (cost_to - cost);
+        if (in >= 0 && in < cost) c.begin[x] = first + min((int)((float)in * per_cost), n_ft - 1) * nt;
+    }
+#pragma unroll
+    for (int x = 1; x <= NXCD; ++x) {
+        const int in = min(x * chunk, units) - first;
+        if (in > 0 && in <= nt * n_ft) c.cost_to[x] = (cost_to - cost) * n_ft + (int)((float)in * per_unit);
+    }
+}
+// Which of the two cuts a list gets, and what of it is left to whoever is free.  V holds a number for every XCD and one more: a lane
+// each in a wave of the kernel (by one thread, one XCD after another, 1.5 us), an array on the host.
+template <class V>
+__host__ __device__ inline void deal(const V& v, const Cuts& cuts, int units, int slots, Queue& q) {
+    const int chunk = (units + NXCD - 1) / NXCD;
+    const auto even = v.each([&](int x) { return min(x * chunk, units); });
+    auto at = even;
+    if (units > CUS) {                                         // (a round or less: by numbers)
+        const auto begin = v.each([&](int x) { return cuts.begin[x]; });
+        const auto cost_to = v.each([&](int x) { return cuts.cost_to[x]; });
+        const float part = (float)v.last(cost_to) / NXCD;
+        const float by_cost = v.most(v.each([&](int, int b, int next) { return rounds_time(next - b, part); }, begin, v.next(begin)));
+        const float by_number = v.most(v.each([&](int, int e, int next, int c, int c_next) { return rounds_time(next - e, (float)(c_next - c)); },
+                                              even, v.next(even), cost_to, v.next(cost_to)));
+        if (by_cost < by_number && v.any(v.each([&](int, int b, int e) { return far_off(b, e, chunk); }, begin, even))) at = begin;
+    }
+    const auto count = v.each([&](int, int b, int next) { return next - b; }, at, v.next(at));
+    const auto fixed = v.each([&](int, int n) { return fixed_units(n, slots); }, count);
+    const int left = v.sum(v.each([&](int, int n, int f) { return n - f; }, count, fixed)), helpers = helpers_for(left);
+    const int room = v.sum(v.each([&](int, int f) { return min(helpers, slots - f); }, fixed));
+    v.put(q.begin, at, NXCD + 1);
+    v.put(q.fixed, fixed, NXCD);
+    q.total = units;
+    q.helpers = room >= left ? helpers : slots;
+}
+
+// The unit of block `slot` of XCD x, or whether it looks for one of the rest.
+constexpr int LOOK = -1, NO_UNIT = -2;
+__host__ __device__ inline int own_unit(const Queue& q, int x, int slot) {
+    const int fixed = q.fixed[x];
+    return slot < fixed ? q.begin[x] + slot : slot < fixed + q.helpers ? LOOK : NO_UNIT;
+}
+// A unit of what the XCDs have left over, for a block of XCD x with no unit of its own: of its own XCD while there are any, then of the
+// one with the most.  NO_UNIT: none anywhere.  R counts what is gone of each XCD's rest: take(y) one more, of how many before; taken(y).
+template <class R>
+__host__ __device__ inline int take_rest(const Queue& q, R rest, int x) {
+    for (int tries = 0; tries <= NXCD; ++tries) {              // (a try that fails has found one more XCD's rest used up, for good)
+        const int own = q.begin[x + 1] - q.begin[x] - q.fixed[x];
+        if (own > 0) {
+            const int t = rest.take(x);
+            if (t < own) return q.begin[x] + q.fixed[x] + t;
+        }
+        int taken[NXCD], most = 0;
+#pragma unroll
+        for (int y = 0; y < NXCD; ++y) taken[y] = rest.taken(y);
+#pragma unroll
+        for (int y = 0; y < NXCD; ++y) {
+            const int left = q.begin[y + 1] - q.begin[y] - q.fixed[y] - taken[y];
+            x = left > most ? y : x;
+            most = max(most, left);
+        }
+        if (most == 0) return NO_UNIT;
+    }
+    return NO_UNIT;
+}
+
 // One list for each projection: its feature tiles, K blocks and room.
 struct ListShape { int n_ft, nkb, capacity; bool one_height; };
 __host__ __device__ inline int list_height(const ListShape& s, const int (&tiles)[HEIGHTS], int groups) {

@@ -193,11 +193,16 @@ HEIGHT_LAYERS = [([189, 189, 191, 20], 128, 128), ([226, 217, 194], 384, 128), (
                  (_MIXED * 5, 128, 128), (_MIXED * 7, 384, 256)]
 
 
-def _run_heights(gpu_lib, counts, d, F):
+def _heights_log(counts, d, F):
     cfg = MoEConfig("heights", T=sum(counts), d=d, E=len(counts), k=1, F=F, modes=("replay",), seed=d + F)
     rng = np.random.default_rng(cfg.seed)
     ids = rng.permutation(np.repeat(np.arange(cfg.E, dtype=np.int32), counts)).reshape(cfg.T, 1)
-    _run_and_check_layer(gpu_lib, cfg, "replay", log=(np.ascontiguousarray(ids), np.ones((cfg.T, 1), dtype=np.float32)))
+    return cfg, (np.ascontiguousarray(ids), np.ones((cfg.T, 1), dtype=np.float32))
+
+
+def _run_heights(gpu_lib, counts, d, F):
+    cfg, log = _heights_log(counts, d, F)
+    _run_and_check_layer(gpu_lib, cfg, "replay", log=log)
 
 
 @pytest.mark.parametrize("d,F", HEIGHT_SHAPES)
@@ -218,6 +223,34 @@ def test_narrow_tiles_of_two_and_three_groups(gpu_lib, d, F):
     """Experts on both sides of every row count at which a narrow tile changes: two or three groups of 32 rows, the copies of 8 rows
     that are left out, and the first count that is no narrow tile any more; output feature tiles that are half empty."""
     _run_heights(gpu_lib, [63, 64, 65, 72, 73, 80, 81, 88, 89, 95, 96, 97, 104, 90, 70], d, F)
+
+
+# Lists that are dealt to the XCDs in parts of equal numbers and of equal cost, with and without units left to whoever is free, and with
+# so uneven parts that every block has to look (which of them: tests/test_tile_rules_host.py).
+DEALT_LAYERS = [([8 + i % 33 for i in range(64)], 128, 4096), ([270, 22, 18, 16, 16, 8, 7, 2], 128, 4096),
+                ([150, 137, 59, 50, 45, 45] + [41] * 3 + [39, 37, 37, 26, 25, 24, 23, 20] + [19] * 3 + [17, 16, 16, 13, 10, 10, 10, 9, 8, 7]
+                 + [6] * 4 + [5] * 3 + [3, 2], 128, 1024),
+                ([18, 17, 552, 133, 70, 15, 36, 7, 26, 39, 2, 28, 11, 77, 17, 45, 3, 8, 12, 23, 14, 30, 88, 31], 6144, 128)]
+
+
+@pytest.mark.parametrize("counts,d,F", DEALT_LAYERS, ids=lambda v: f"{len(v)}experts" if isinstance(v, list) else str(v))
+def test_dealt_lists(gpu_lib, counts, d, F):
+    """Against the oracle, and further passes over the same context, which find the counts of the last one's shared units."""
+    from workloads import make_inputs
+    _run_heights(gpu_lib, counts, d, F)
+    cfg, (ids, w) = _heights_log(counts, d, F)
+    inp = {n: (v.cuda() if isinstance(v, torch.Tensor) else v) for n, v in make_inputs(cfg).items()}
+    layer = gpu_lib.MoELayer(cfg.T, cfg.d, cfg.E, cfg.k, cfg.F)
+    try:
+        want = None
+        for _ in range(3):
+            layer.y_perm.fill_(float("nan"))
+            layer.forward_replay(inp["x"], torch.from_numpy(ids).cuda(), torch.from_numpy(w).cuda(), inp)
+            torch.cuda.synchronize()
+            want = layer.y_perm.clone() if want is None else want
+            assert not torch.isnan(layer.y_perm).any() and torch.equal(layer.y_perm, want)
+    finally:
+        layer.close()
 
 
 # Layers of so few units that both projections stream whatever their rows per expert, or the down projection alone (which of them:

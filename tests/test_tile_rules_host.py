@@ -144,52 +144,170 @@ def test_lists_have_room_for_their_units(rules):
 
 DEAL = r"""
 #include "ffn_rules.hpp"
+#include <algorithm>
+#include <array>
 #include <cstdio>
+#include <random>
+#include <vector>
 using namespace moe355;
-int main() {                                                   // slots, nine boundaries -> helpers, begin and fixed of each XCD
-    int slots, begin[NXCD + 1];
-    while (scanf("%d", &slots) == 1) {
-        for (int& b : begin) if (scanf("%d", &b) != 1) return 1;
-        const int units = begin[NXCD], chunk = (units + NXCD - 1) / NXCD;
-        bool uneven = false;                                   // as the wave of the kernel that makes the lists does, lane by lane
-        int at[NXCD + 1], fixed[NXCD], left = 0, room = 0;
-        for (int x = 0; x < NXCD; ++x) uneven |= far_off(begin[x], min(x * chunk, units), chunk);
-        for (int x = 0; x <= NXCD; ++x) at[x] = uneven ? begin[x] : min(x * chunk, units);
-        for (int x = 0; x < NXCD; ++x) left += at[x + 1] - at[x] - (fixed[x] = fixed_units(at[x + 1] - at[x], slots));
-        const int helpers = helpers_for(left);
-        for (int x = 0; x < NXCD; ++x) room += min(helpers, slots - fixed[x]);
-        printf("%d", room >= left ? helpers : slots);
-        for (int b : at) printf(" %d", b);
-        for (int f : fixed) printf(" %d", f);
-        printf("\n");
+struct Xcds {                                                  // what the lanes of a wave are to deal() on the device
+    template <class T> using Each = std::array<T, NXCD + 1>;
+    template <class F, class... A>
+    auto each(F f, const A&... a) const {
+        Each<decltype(f(0, a[0]...))> r;
+        for (int x = 0; x <= NXCD; ++x) r[x] = f(x, a[x]...);
+        return r;
+    }
+    Each<int> next(const Each<int>& v) const { return each([&](int x) { return v[std::min(x + 1, NXCD)]; }); }
+    int last(const Each<int>& v) const { return v[NXCD]; }
+    float most(const Each<float>& v) const { return *std::max_element(v.begin(), v.end() - 1); }
+    int sum(const Each<int>& v) const { int s = 0; for (int x = 0; x < NXCD; ++x) s += v[x]; return s; }
+    bool any(const Each<bool>& v) const { return std::any_of(v.begin(), v.end() - 1, [](bool b) { return b; }); }
+    void put(int32_t* to, const Each<int>& v, int n) const { std::copy_n(v.begin(), n, to); }
+};
+struct Launch {                                                // its blocks, in an order as mixed as can be: one that looks may be overtaken
+    const Queue& q;
+    std::mt19937& rng;
+    std::vector<int> blocks, times;
+    size_t started = 0;
+    int lost = 0;
+    Rest rest[NXCD] = {};
+    struct Counts {
+        Launch& l;
+        int take(int x) const { return l.rest[x].taken++; }
+        int taken(int y) const {
+            const int t = l.rest[y].taken;
+            while (y == NXCD - 1 && l.rng() % 4 != 0 && l.block()) {}
+            return t;
+        }
+    };
+    bool block() {
+        if (started == blocks.size()) return false;
+        const int b = blocks[started++];
+        int u = own_unit(q, b % NXCD, b / NXCD);
+        if (u == LOOK) u = take_rest(q, Counts{*this}, b % NXCD);
+        if (u >= (int)times.size()) ++lost;
+        else if (u >= 0) ++times[u];
+        return true;
+    }
+};
+int main() {                       // height, feature tiles, slots, experts, their rows -> the queue, the cuts; how often each unit is taken
+    int h, n_ft, slots, E;
+    std::mt19937 rng(1);
+    while (scanf("%d %d %d %d", &h, &n_ft, &slots, &E) == 4) {
+        std::vector<int> rows(E);
+        int tiles = 0, cost_all = 0, tiles_to = 0, cost_to = 0;
+        for (int& r : rows) {
+            if (scanf("%d", &r) != 1) return 1;
+            tiles += (r + h - 1) / h;
+            cost_all += tiles_share((r + h - 1) / h, (r + 31) / 32);
+        }
+        const int units = tiles * n_ft;
+        Cuts cuts;
+        for (int x = 0; x <= NXCD; ++x) no_cut(cuts, x, units);
+        for (int r : rows) {
+            const int nt = (r + h - 1) / h, cost = tiles_share(nt, (r + 31) / 32);
+            tiles_to += nt;
+            cost_to += cost;
+            if (nt > 0) cut_expert(cuts, nt, tiles_to, cost, cost_to, cost_all, n_ft, units);
+        }
+        Queue q;
+        deal(Xcds{}, cuts, units, slots, q);
+        printf("%d %d", q.total, q.helpers);
+        for (int b : q.begin) printf(" %d", b);
+        for (int f : q.fixed) printf(" %d", f);
+        for (int b : cuts.begin) printf(" %d", b);
+        for (int c : cuts.cost_to) printf(" %d", c);
+        Launch l{q, rng, std::vector<int>(NXCD * slots), std::vector<int>(units)};
+        for (int i = 0; i < NXCD * slots; ++i) l.blocks[i] = i;
+        std::shuffle(l.blocks.begin(), l.blocks.end(), rng);
+        while (l.block()) {}
+        for (int t : l.times) l.lost += t != 1;
+        printf(" %d\n", l.lost);
     }
     return 0;
 }
 """
 
 
-def test_every_unit_of_a_dealt_list_has_a_block(tmp_path):
-    """Random lists, even to all on one XCD, with barely enough blocks to twice as many: the parts cover the list in order, and the
-    blocks that look for a unit of the rest are at least as many as it has units."""
-    (tmp_path / "deal.hip").write_text(DEAL)
-    subprocess.run([HIPCC, "--cuda-host-only", "-O2", "-std=c++17", "-I", CSRC, "-I", ROOT + "/include", str(tmp_path / "deal.hip"), "-o",
-                    str(tmp_path / "deal")], check=True, capture_output=True)
-    rng, cases = random.Random(2), []
-    for _ in range(2000):
-        units = int(2 ** rng.uniform(0, 15)) - 1
-        even = [units * x // 8 for x in range(9)]
-        cuts = [0, *sorted(rng.randint(0, units) for _ in range(7)), units]
-        mix = rng.choice([0.0, 0.02, 0.3, 1.0])
-        slots = (units + 7) // 8 + rng.choice([0, 0, 1, units // 32, units // 8])
-        cases.append((slots, [0, *sorted(round(a + mix * (b - a)) for a, b in zip(even, cuts))[1:-1], units]))
-    cases.append((5, [0] * 8 + [40]))
-    out = subprocess.run([str(tmp_path / "deal")], input="\n".join(f"{s} " + " ".join(map(str, b)) for s, b in cases), check=True,
-                         capture_output=True, text=True).stdout.splitlines()
-    assert len(out) == len(cases)
-    for (slots, cuts), line in zip(cases, out):
-        helpers, *rest = map(int, line.split())
-        begin, fixed = rest[:9], rest[9:]
-        count = [b - a for a, b in zip(begin, begin[1:])]
-        assert begin[0] == 0 and begin[8] == cuts[8] and min(count) >= 0
-        assert all(0 <= f <= min(c, slots) for f, c in zip(fixed, count))
-        assert sum(min(helpers, slots - f) for f in fixed) >= sum(count) - sum(fixed)
+@pytest.fixture(scope="module")
+def deal(tmp_path_factory):
+    """(list height, feature tiles, blocks of an XCD, rows of the experts), ... -> (helpers, begin, fixed, cuts, cost up to the even cuts) of each,
+    after every block of the launch has taken its unit."""
+    d = tmp_path_factory.mktemp("deal")
+    (d / "deal.hip").write_text(DEAL)
+    subprocess.run([HIPCC, "--cuda-host-only", "-O2", "-std=c++17", "-I", CSRC, "-I", ROOT + "/include", str(d / "deal.hip"), "-o",
+                    str(d / "deal")], check=True, capture_output=True)
+
+    def ask(lists):
+        text = "\n".join(" ".join(map(str, [h, n_ft, slots, len(rows), *rows])) for h, n_ft, slots, rows in lists)
+        out = subprocess.run([str(d / "deal")], input=text, check=True, capture_output=True, text=True).stdout.splitlines()
+        assert len(out) == len(lists)
+        answers = []
+        for (h, n_ft, slots, rows), line in zip(lists, out):
+            total, helpers, *v, lost = map(int, line.split())
+            begin, fixed, cuts, cost_to = v[:9], v[9:17], v[17:26], v[26:]
+            assert total == n_ft * sum(-(-r // h) for r in rows) and lost == 0
+            assert begin[0] == 0 and begin[8] == total and begin == sorted(begin)
+            assert all(0 <= f <= min(b - a, slots) for f, a, b in zip(fixed, begin, begin[1:]))
+            answers.append((helpers, begin, fixed, cuts, cost_to))
+        return answers
+    return ask
+
+
+def _random_list(rng):
+    h, n_ft, E = rng.choice([256, 224, 192, 160, 128]), rng.choice([1, 2, 3, 9, 16, 28, 56]), rng.randint(1, 256)
+    mean, skew = 2 ** rng.uniform(0, 10), rng.choice([0.0, 0.5, 2.0])
+    rows = [int(mean * rng.lognormvariate(0, skew)) if rng.random() > 0.1 else 0 for _ in range(E)]
+    units = n_ft * sum(-(-r // h) for r in rows)
+    if units > 60000:
+        return _random_list(rng)
+    return h, n_ft, (units + 7) // 8 + rng.choice([0, 0, 1, units // 32, units // 8]), rows
+
+
+def test_every_unit_of_a_dealt_list_has_a_block(deal):
+    """Random lists, even to all on one XCD, with barely enough blocks to many more: every unit is taken once, whoever comes first; the cuts of
+    equal cost lie on the feature tile in which that cost is reached, and are taken where the slowest XCD gains by them and only there."""
+    rng = random.Random(2)
+    lists = [_random_list(rng) for _ in range(1500)] + [(256, 8, 6, [1300]), (128, 1, 0, [0, 0])]
+    branches = set()
+    for (h, n_ft, slots, rows), (helpers, begin, fixed, cuts, cost_to) in zip(lists, deal(lists)):
+        tiles = [-(-r // h) for r in rows]
+        cost = [8 * t + -(-r // 32) for t, r in zip(tiles, rows)]
+        units, chunk = begin[8], -(-begin[8] // 8)
+        even = [min(x * chunk, units) for x in range(9)]
+        for x in range(1, 8):                                  # feature tile by feature tile, an expert's cost is spread evenly
+            before = base = 0
+            for t, c in zip(tiles, cost):
+                if t and before + c > sum(cost) * x // 8:
+                    reached = (sum(cost) * x // 8 - before) * n_ft / c
+                    assert (cuts[x] - base) % t == 0 and abs((cuts[x] - base) // t - reached) < 1 + 1e-3
+                    break
+                before, base = before + c, base + t * n_ft
+        for x in range(9):
+            left, want = even[x], 0.0
+            for t, c in zip(tiles, cost):
+                if t:
+                    want += c / t * min(left, t * n_ft)
+                    left -= min(left, t * n_ft)
+            assert abs(cost_to[x] - want) <= 1 + 1e-6 * want
+        slowest = lambda cut, part: max([-(-(b - a) // 32) * c / (b - a) for a, b, c in zip(cut, cut[1:], part) if b > a], default=0)
+        by_cost, by_number = slowest(cuts, [cost_to[8] / 8] * 8), slowest(even, [b - a for a, b in zip(cost_to, cost_to[1:])])
+        gains = units > 256 and by_cost < by_number and any(abs(c - e) > chunk // 8 for c, e in zip(cuts[:8], even))
+        if abs(by_cost - by_number) > 1e-5 * by_number:
+            assert begin == (cuts if gains else even)
+        shared = sum(b - a - f for a, b, f in zip(begin, begin[1:], fixed))
+        branches.add(("cost" if begin != even else "numbers", shared > 0, helpers == slots and shared > 0))
+    assert branches == {("numbers", False, False), ("numbers", True, False), ("cost", False, False), ("cost", True, False), ("cost", True, True)}
+
+
+def test_dealt_layers_reach_what_they_are_for(rules, deal):
+    def branch(counts, d, F, projection):
+        form, h, units, room, _ = _layer(rules, counts, d, F)[projection]
+        assert form == "big"
+        slots = -(-room // 8)
+        (helpers, begin, fixed, *_), = deal([(h, (F // 128, (d + 255) // 256)[projection], slots, counts)])
+        shared = sum(begin[1:]) - sum(begin[:8]) - sum(fixed)
+        return "numbers" if begin == [min(x * -(-units // 8), units) for x in range(9)] else "cost", shared > 0, helpers == slots
+    assert [branch(*layer, p) for layer, p in zip(edges.DEALT_LAYERS, (0, 0, 0, 1))] == [
+        ("numbers", True, False), ("cost", True, True), ("cost", False, False), ("cost", True, False)]
