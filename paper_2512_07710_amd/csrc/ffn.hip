@@ -82,23 +82,19 @@ struct WaveLanes {
         if (lane < n) to[lane] = v;
     }
 };
-// Block (e, l) writes the units of expert e into list l (0: gate/up, 1: down); every block recomputes the tile counts of all
-// experts for its base index and the height, and block (0, l) deals the list to the XCDs.
-// choose: list 1 is left empty (queue->total = 0) unless the batch is concentrated, see DOWN_SKEW_UNITS.
-__device__ inline void build_work(const int32_t* __restrict__ offsets, int E, int e, int list, const ListShape& shape, bool choose,
-                                  Work* __restrict__ work, Queue* __restrict__ queue, Rest* __restrict__ rest) {
+// What every block of a list works out for itself from the rows of all experts (thread tid has those of expert tid): the height of the
+// tiles, and how many there are.  empty: list 1 stays so unless the batch is concentrated, see DOWN_SKEW_UNITS.
+struct ListPlan { int h, tiles; bool empty; };
+__device__ inline ListPlan plan_list(int rows_t, int list, const ListShape& shape, bool choose) {
     constexpr int SUMS = HEIGHTS + 2, WAVES = MAX_E / 64;      // tiles at each height, groups of 32 rows, tiles of 64
-    __shared__ int32_t s_sums[WAVES][SUMS], s_scan[WAVES], s_cost[WAVES], s_base;
-    __shared__ Cuts s_cuts;
-    const int tid = threadIdx.x, wave = tid >> 6;
-    const int n_ft = shape.n_ft;
-    const int rows_t = tid < E ? offsets[tid + 1] - offsets[tid] : 0;
+    __shared__ int32_t s_sums[WAVES][SUMS];
+    const int tid = threadIdx.x;
 #pragma unroll
     for (int j = 0; j < SUMS; ++j) {
         if (shape.one_height && j > 0 && j <= HEIGHTS) continue;
         const int h = j < HEIGHTS ? tile_height(j) : j == HEIGHTS ? 32 : STREAM_ROWS;
         const int sum = wave_scan((rows_t + h - 1) / h);
-        if ((tid & 63) == 63) s_sums[wave][j] = sum;
+        if ((tid & 63) == 63) s_sums[tid >> 6][j] = sum;
     }
     __syncthreads();
     int sums[SUMS], tiles[HEIGHTS];
@@ -110,32 +106,65 @@ __device__ inline void build_work(const int32_t* __restrict__ offsets, int E, in
     int total = tiles[0];                                      // at the chosen height
 #pragma unroll
     for (int j = 1; j < HEIGHTS; ++j) total = h == tile_height(j) ? tiles[j] : total;
-    const bool empty = choose && list == 1 && sums[HEIGHTS + 1] <= 2 * tiles[0];
-    const int units = total * n_ft;
-    if (empty) {
-        if (e == 0 && tid < NXCD) queue->fixed[tid] = 0;
-        if (e == 0 && tid == 0) queue->total = queue->helpers = 0;
+    return {h, total, choose && list == 1 && sums[HEIGHTS + 1] <= 2 * tiles[0]};
+}
+// One block for each list l (0: gate/up, 1: down) deals it to the XCDs, beside the blocks that write its units (the first expert's block
+// dealing before it wrote its own: passes of 656 x 4 tokens of 32 experts, 1024 x 512, 40.6 us / 40.0 with a block for it, 600 x 4 39.5 /
+// 39.0, 2000 x 4 of 16, 1536 x 1024 93.3 / 92.9; without any dealing 39.5, 38.8 and 92.7).
+__device__ inline void deal_list(const int32_t* __restrict__ offsets, int E, int list, const ListShape& shape, bool choose,
+                                 Queue* __restrict__ queue, Rest* __restrict__ rest) {
+    constexpr int WAVES = MAX_E / 64;
+    __shared__ int32_t s_scan[WAVES], s_cost[WAVES];
+    __shared__ Cuts s_cuts;
+    const int tid = threadIdx.x, wave = tid >> 6, n_ft = shape.n_ft;
+    const int rows_t = tid < E ? offsets[tid + 1] - offsets[tid] : 0;
+    const ListPlan plan = plan_list(rows_t, list, shape, choose);
+    if (plan.empty) {
+        if (tid < NXCD) queue->fixed[tid] = 0;
+        if (tid == 0) queue->total = queue->helpers = 0;
         return;
     }
-    const int nt_t = (rows_t + h - 1) / h, cost_t = tiles_share(nt_t, (rows_t + 31) / 32);
-    int tiles_to = wave_scan(nt_t), cost_to = wave_scan(cost_t);    // up to and with expert tid, first in its wave
-    if ((tid & 63) == 63) {
-        s_scan[wave] = tiles_to;
-        s_cost[wave] = cost_to;
+    const int units = plan.tiles * n_ft;
+    if (units > CUS) {                                         // (a round or less is dealt by numbers: no cuts)
+        const int nt_t = (rows_t + plan.h - 1) / plan.h, cost_t = tiles_share(nt_t, (rows_t + 31) / 32);
+        int tiles_to = wave_scan(nt_t), cost_to = wave_scan(cost_t), cost_all = 0;    // up to and with expert tid, first in its wave
+        if ((tid & 63) == 63) {
+            s_scan[wave] = tiles_to;
+            s_cost[wave] = cost_to;
+        }
+        if (tid <= NXCD) no_cut(s_cuts, tid, units);
+        __syncthreads();
+        for (int w = 0; w < WAVES; ++w) {
+            if (w < wave) tiles_to += s_scan[w];
+            if (w < wave) cost_to += s_cost[w];
+            cost_all += s_cost[w];
+        }
+        if (nt_t > 0) cut_expert(s_cuts, nt_t, tiles_to, cost_t, cost_to, cost_all, n_ft, units);
+        __syncthreads();
     }
-    if (tid <= NXCD) no_cut(s_cuts, tid, units);
+    if (wave == 0) deal(WaveLanes{tid}, s_cuts, units, list_blocks(shape.capacity) / NXCD, *queue);
+    if (tid < NXCD) rest[tid].taken = 0;
+}
+// Block (e, l) writes the units of expert e into list l; every block recomputes the tile counts of all experts for its base index and
+// the height.
+__device__ inline void build_work(const int32_t* __restrict__ offsets, int E, int e, int list, const ListShape& shape, bool choose,
+                                  Work* __restrict__ work) {
+    constexpr int WAVES = MAX_E / 64;
+    __shared__ int32_t s_scan[WAVES], s_base;
+    const int tid = threadIdx.x, wave = tid >> 6;
+    const int n_ft = shape.n_ft;
+    const int rows_t = tid < E ? offsets[tid + 1] - offsets[tid] : 0;
+    const ListPlan plan = plan_list(rows_t, list, shape, choose);
+    if (plan.empty) return;
+    const int h = plan.h, before = wave_scan((rows_t + h - 1) / h);    // tiles up to expert tid, in its wave
+    if ((tid & 63) == 63) s_scan[wave] = before;
     __syncthreads();
-    int cost_all = 0;
-    for (int w = 0; w < WAVES; ++w) {
-        if (w < wave) tiles_to += s_scan[w];
-        if (w < wave) cost_to += s_cost[w];
-        cost_all += s_cost[w];
+    if (tid == e) {
+        int base = before - (rows_t + h - 1) / h;
+        for (int w = 0; w < wave; ++w) base += s_scan[w];
+        s_base = base;
     }
-    if (tid == e) s_base = tiles_to - nt_t;
-    if (e == 0 && nt_t > 0 && units > CUS) cut_expert(s_cuts, nt_t, tiles_to, cost_t, cost_to, cost_all, n_ft, units);
     __syncthreads();
-    if (e == 0 && wave == 0) deal(WaveLanes{tid}, s_cuts, units, list_blocks(shape.capacity) / NXCD, *queue);
-    if (e == 0 && tid < NXCD) rest[tid].taken = 0;
     const int start = offsets[e], cnt = offsets[e + 1] - start;
     const int nt = (cnt + h - 1) / h;
     if (nt == 0) return;
@@ -889,20 +918,26 @@ static hipError_t set_lds_limits() {
     return hipSuccess;
 }
 
-// What the big tiles need before they start, in one launch (two took 2..3 us more of every layer): the work lists (blocks
-// 0 .. E*lists-1) and, with perm, the scales of the expert-sorted rows from the per-token scales:
+// What the big tiles need before they start, in one launch (two took 2..3 us more of every layer): how the lists are dealt (one block
+// each), the work lists (the next E*lists blocks) and, with perm, the scales of the expert-sorted rows from the per-token scales:
 // out[g][p] = in[g][perm[p] / fan].
 __global__ __launch_bounds__(256) void prepare_big_tiles(const int32_t* __restrict__ offsets, int E, int lists, ListShape shape0,
                                                          ListShape shape1, bool choose, Work* __restrict__ work0,
                                                          Work* __restrict__ work1, Queue* __restrict__ queues, Rest* __restrict__ rests,
                                                          const float* __restrict__ in, int T, const int32_t* __restrict__ perm,
                                                          int fan, int N, float* __restrict__ out) {
-    if ((int)blockIdx.x < E * lists) {
-        const int list = blockIdx.x / E;
-        build_work(offsets, E, blockIdx.x % E, list, list == 0 ? shape0 : shape1, choose, list == 0 ? work0 : work1, queues + list, rests + list * NXCD);
+    if ((int)blockIdx.x < lists) {
+        const int list = blockIdx.x;
+        deal_list(offsets, E, list, list == 0 ? shape0 : shape1, choose, queues + list, rests + list * NXCD);
         return;
     }
-    const uint32_t b = blockIdx.x - E * lists, row_blocks = (uint32_t)((N + 255) / 256);
+    const int block = blockIdx.x - lists;
+    if (block < E * lists) {
+        const int list = block / E;
+        build_work(offsets, E, block % E, list, list == 0 ? shape0 : shape1, choose, list == 0 ? work0 : work1);
+        return;
+    }
+    const uint32_t b = block - E * lists, row_blocks = (uint32_t)((N + 255) / 256);
     const size_t g = b / row_blocks;
     const int p = (int)(b % row_blocks) * 256 + (int)threadIdx.x;
     if (p >= N) return;
@@ -933,7 +968,7 @@ hipError_t launch_expert_ffn(moe_ctx* c, const uint8_t* xq, const float* xs, con
     if (!stream1) {                                            // (the streaming kernels need neither list nor sorted scales)
         const int lists = down == Down::STREAM ? 1 : 2;
         const int64_t gather = perm ? (int64_t)((N + 255) / 256) * (D.d / QBLOCK) : 0;
-        hipLaunchKernelGGL(prepare_big_tiles, dim3((unsigned)(D.E * lists + gather)), dim3(256), 0, c->stream, offsets, D.E, lists,
+        hipLaunchKernelGGL(prepare_big_tiles, dim3((unsigned)((D.E + 1) * lists + gather)), dim3(256), 0, c->stream, offsets, D.E, lists,
                            gate_up_shape(&D), down_shape(&D), down == Down::EITHER,
                            work, work2, queues, rests, xs, D.T, perm, D.k, N, c->xs_sorted);
     }

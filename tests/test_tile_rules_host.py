@@ -204,8 +204,9 @@ int main() {                       // height, feature tiles, slots, experts, the
         }
         const int units = tiles * n_ft;
         Cuts cuts;
-        for (int x = 0; x <= NXCD; ++x) no_cut(cuts, x, units);
-        for (int r : rows) {
+        for (int x = 0; x <= NXCD; ++x) cuts.begin[x] = 1000 * x, cuts.cost_to[x] = 1000 * x * x;   // not read in one round
+        if (units > CUS) for (int x = 0; x <= NXCD; ++x) no_cut(cuts, x, units);
+        if (units > CUS) for (int r : rows) {
             const int nt = (r + h - 1) / h, cost = tiles_share(nt, (r + 31) / 32);
             tiles_to += nt;
             cost_to += cost;
@@ -276,6 +277,10 @@ def test_every_unit_of_a_dealt_list_has_a_block(deal):
         cost = [8 * t + -(-r // 32) for t, r in zip(tiles, rows)]
         units, chunk = begin[8], -(-begin[8] // 8)
         even = [min(x * chunk, units) for x in range(9)]
+        if units <= 256:
+            assert begin == even and cuts == [1000 * x for x in range(9)]
+            branches.add("one round")
+            continue
         for x in range(1, 8):                                  # feature tile by feature tile, an expert's cost is spread evenly
             before = base = 0
             for t, c in zip(tiles, cost):
@@ -293,12 +298,12 @@ def test_every_unit_of_a_dealt_list_has_a_block(deal):
             assert abs(cost_to[x] - want) <= 1 + 1e-6 * want
         slowest = lambda cut, part: max([-(-(b - a) // 32) * c / (b - a) for a, b, c in zip(cut, cut[1:], part) if b > a], default=0)
         by_cost, by_number = slowest(cuts, [cost_to[8] / 8] * 8), slowest(even, [b - a for a, b in zip(cost_to, cost_to[1:])])
-        gains = units > 256 and by_cost < by_number and any(abs(c - e) > chunk // 8 for c, e in zip(cuts[:8], even))
+        gains = by_cost < by_number and any(abs(c - e) > chunk // 8 for c, e in zip(cuts[:8], even))
         if abs(by_cost - by_number) > 1e-5 * by_number:
             assert begin == (cuts if gains else even)
         shared = sum(b - a - f for a, b, f in zip(begin, begin[1:], fixed))
         branches.add(("cost" if begin != even else "numbers", shared > 0, helpers == slots and shared > 0))
-    assert branches == {("numbers", False, False), ("numbers", True, False), ("cost", False, False), ("cost", True, False), ("cost", True, True)}
+    assert branches == {"one round", ("numbers", False, False), ("numbers", True, False), ("cost", False, False), ("cost", True, False), ("cost", True, True)}
 
 
 def test_dealt_layers_reach_what_they_are_for(rules, deal):
