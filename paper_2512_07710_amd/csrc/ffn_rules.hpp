@@ -224,20 +224,25 @@ inline int64_t max_row_tiles(const moe_dims* D, int rows) {
     const int64_t N = (int64_t)D->T * D->k;
     return N / rows + (N < D->E ? N : D->E);
 }
-// A layer whose streaming units, at most, make one round of a unit to a CU: streaming, whatever its rows per expert (the big tiles' units
-// are half as many and leave more than half of the chip idle; neither list nor sorted scales are needed).  The units at most: no load
+// A small layer streams whatever its rows per expert: at most one gate/up unit to a CU, and at most four of the shorter down units (the big
+// tiles' units are half as many and leave more than half of the chip idle; neither list nor sorted scales are needed).  The down projection
+// alone, beside big gate/up tiles that need their list anyway: one unit to a CU.  The units at most: no load
 // makes more.  Layers, us, big tiles / streaming, and units of the gate/up | down projection: 350 tokens x 4 of 16 experts, 2048 x 512
 // 46.0 / 34.5, 148 | 296; 400 x 2 of 8, 4096 x 1024 66.0 / 43.2, 160 | 320; 60 x 6 of 8, 7168 x 2048 88.5 / 73.4, 208 | 364; 640 x 1 of 8,
 // 7168 x 1536 96.9 / 91.8, 216 | 504; 200 x 8 of 9, 7168 x 512 83.3 / 68.2, 136 | 952; 700 x 4 of 16, 2048 x 512 49.0 / 48.1, 236 | 472;
 // Zipf loads 500 x 4 of 8, 2048 x 512 48.1 / 42.1, 156 | 312; and beyond: 1024 x 1 of 16, 4096 x 1024 72.0 / 75.2, 256 | 512, 1000 x 2 of 8,
 // 1024 x 1024 39.4 / 40.6, 312 | 156.  The down projection alone: 92 units 23.2 / 13.6, 156 16.2 / 13.7, 180 13.7 / 11.4, 216 13.7 / 12.9,
-// 252 15.8 / 17.5.  Layers narrower than 512 gain too (256 x 256 25.4 / 21.5), but with them every tile height is tested.
-constexpr int64_t ROUND_UNITS = 240, ROUND_DOWN_UNITS = 1000, ROUND_DOWN_ALONE_UNITS = 200, ROUND_WIDTH = 512;
-inline bool in_one_round(const moe_dims* D, int feature_tiles, int64_t most) {
-    return D->d >= ROUND_WIDTH && D->F >= ROUND_WIDTH && max_row_tiles(D, STREAM_ROWS) * feature_tiles <= most;
+// 252 15.8 / 17.5.
+// Layers narrower than 512 do not cross at these units: with one to three K blocks a unit, many units are mostly ends (7000 x 1 of 4,
+// 2048 x 256 65.0 / 69.7, 226 | 904; 700 x 5 of 64, 2048 x 256 58.6 / 63.2, 236 | 944; 500 x 5 of 40, 3072 x 384 70.2 / 73.5, 237 | 948;
+// 2500 x 4 of 16, 1024 x 128 51.4 / 52.9, 172 | 688), while few units or narrow inputs gain (400 x 2 of 8, 7168 x 384 86.4 / 54.4, 60 | 560;
+// 300 x 4 of 8, 256 x 1536 34.7 / 30.0, 312 | 26).
+constexpr int64_t SMALL_GATE_UP_UNITS = 240, SMALL_DOWN_UNITS = 1000, SMALL_DOWN_ALONE_UNITS = 200, SMALL_WIDTH = 512;
+inline bool few_units(const moe_dims* D, int feature_tiles, int64_t most) {
+    return D->d >= SMALL_WIDTH && D->F >= SMALL_WIDTH && max_row_tiles(D, STREAM_ROWS) * feature_tiles <= most;
 }
-inline bool layer_in_one_round(const moe_dims* D) {
-    return in_one_round(D, D->F / 128, ROUND_UNITS) && in_one_round(D, (D->d + 255) / 256, ROUND_DOWN_UNITS);
+inline bool small_layer(const moe_dims* D) {
+    return few_units(D, D->F / 128, SMALL_GATE_UP_UNITS) && few_units(D, (D->d + 255) / 256, SMALL_DOWN_UNITS);
 }
 
 inline bool skew_is_harmless(const moe_dims* D, int feature_tiles, int64_t most_units) {
@@ -246,7 +251,7 @@ inline bool skew_is_harmless(const moe_dims* D, int feature_tiles, int64_t most_
 }
 enum class Down { BIG, STREAM, EITHER };
 inline Down down_form(const moe_dims* D) {
-    if (layer_in_one_round(D) || in_one_round(D, (D->d + 255) / 256, ROUND_DOWN_ALONE_UNITS)) return Down::STREAM;
+    if (small_layer(D) || few_units(D, (D->d + 255) / 256, SMALL_DOWN_ALONE_UNITS)) return Down::STREAM;
     if ((int64_t)D->T * D->k > DOWN_STREAM_ROWS * D->E) return Down::BIG;
     return skew_is_harmless(D, (D->d + 255) / 256, DOWN_SKEW_UNITS) ? Down::STREAM : Down::EITHER;
 }
@@ -256,7 +261,7 @@ inline double experts_met(const moe_dims* D) {                 // with at least 
 // (only where the down projection streams for certain: then no lists are needed)
 inline bool gate_up_streams(const moe_dims* D) {
     const int64_t N = (int64_t)D->T * D->k;
-    if (N > 0 && layer_in_one_round(D)) return true;
+    if (N > 0 && small_layer(D)) return true;
     if (N == 0 || down_form(D) != Down::STREAM || !skew_is_harmless(D, D->F / 128, GATE_UP_SKEW_UNITS)) return false;
     if (N <= GATE_UP_STREAM_ROWS * D->E) return true;
     return N <= GATE_UP_STREAM_ROWS_IDLE * D->E && experts_met(D) * (D->F / 128) < CUS;
