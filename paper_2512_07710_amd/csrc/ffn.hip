@@ -556,7 +556,7 @@ __global__ __launch_bounds__(NTHREADS, 1) void ffn_gemm(const uint8_t* __restric
     //      NARROW tiles (at most 64 rows, or 96, see below): wave w's 32 staged rows are 32 consecutive features of the tile
     //      (down projection) or, GATED, [16 gate rows | 16 up rows] of features f0 + 16w .. 16w+15.
     // (LINEAR: a product of 129..160 rows can have a tile as short beside a taller one; k_loop<1> in both halves, their waves in step)
-    const bool narrow = !LINEAR && wk.nrows <= (wk.tiles == 1 ? NARROW_ROWS : NARROW_SHARED_ROWS);   // block-uniform
+    const bool narrow = !LINEAR && narrow_tile(wk);            // block-uniform
     const bool once = !LINEAR && wk.tiles <= (GATED ? GATE_UP_ONCE_TILES : DOWN_ONCE_TILES);   // as is this
     // A wave whose features all lie beyond NOUT (down projection, NOUT an odd multiple of 128: feature tile half empty)
     // copies the last 32 features again; they are multiplied and not stored.

@@ -20,6 +20,7 @@ constexpr int NARROW_ROWS = 96, NARROW_SHARED_ROWS = 64;
 // expert, as far as MANY_TILES
 struct Work { int32_t expert; int32_t row0; int32_t ft; int16_t nrows, tiles; };
 constexpr int MANY_TILES = 3;
+__host__ __device__ inline bool narrow_tile(const Work& w) { return w.nrows <= (w.tiles == 1 ? NARROW_ROWS : NARROW_SHARED_ROWS); }
 
 // Rows [row0, row0 + nrows) of tile i when `rows` rows make nt tiles.
 // The expert's G = ceil(cnt/32) groups of 32 rows are dealt out evenly: tile i covers groups [i*G/nt, (i+1)*G/nt).

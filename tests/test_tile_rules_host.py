@@ -39,7 +39,7 @@ int main() {
                 for (int i = 0; i < nt; ++i) { Work w; split_rows(rows, nt, i, w); printf(" %d", w.nrows); }
                 printf("\n");
             }
-        } else {                                               // d F E k counts -> forms; height, units, room, then rows:tiles of each
+        } else {                                               // d F E k counts -> forms; height, units, room, then rows:tiles:narrow of each
             moe_dims D{};
             if (scanf("%d %d %d %d", &D.d, &D.F, &D.E, &D.k) != 4) return 1;
             std::vector<int> c(D.E);
@@ -60,7 +60,7 @@ int main() {
                         if (w.row0 != at) return 2;
                         at += w.nrows;
                         if (i == nt - 1 && at != n) return 3;
-                        printf(" %d:%d", w.nrows, w.tiles);
+                        printf(" %d:%d:%d", w.nrows, w.tiles, narrow_tile(w));
                     }
                 printf("\n");
             }
@@ -84,7 +84,7 @@ def rules(tmp_path_factory):
 
 
 def _layer(rules, counts, d, F, k=1):
-    """((form, height, units, room, [(rows, tiles of the expert)]) of the gate/up projection, of the down projection)"""
+    """((form, height, units, room, [(rows, tiles of the expert, narrow)]) of the gate/up projection, of the down projection)"""
     forms, *lists = rules(f"G {d} {F} {len(counts)} {k} " + " ".join(map(str, counts)))
     out = []
     for form, line in zip(forms.split(), lists):
@@ -100,15 +100,17 @@ def test_tile_height_layers_reach_every_height_and_group_count(rules):
         for p, (form, h, _, _, tiles) in enumerate(_layer(rules, counts, d, F)):
             assert form == "big"
             heights[p].add(h)
-            groups[p] |= {((n + 31) // 32, nt > 1, "one K block" if (d, F)[p] == 128 else "more", p == 1 and d // 128 % 2 == 1)
-                          for n, nt in tiles}
+            groups[p] |= {((n + 31) // 32, nt > 1, narrow, "one K block" if (d, F)[p] == 128 else "more", p == 1 and d // 128 % 2 == 1)
+                          for n, nt, narrow in tiles}
     for p in range(2):
         assert heights[p] == {256, 224, 192, 160, 128}
         for want in ("one K block", "more"):
-            met = {(g, shared) for g, shared, k_blocks, _ in groups[p] if k_blocks == want}
+            met = {(g, shared, narrow) for g, shared, narrow, k_blocks, _ in groups[p] if k_blocks == want}
             # narrow tiles alone, two groups beside a taller tile, full tiles alone and as one of several
-            assert met >= {(1, False), (2, False), (2, True)} | {(g, False) for g in range(3, 9)} | {(g, True) for g in range(3, 8)}
-    assert {g for g, _, _, half_empty in groups[1] if half_empty} == set(range(1, 9))
+            assert met >= {(g, False, 1) for g in (1, 2, 3)} | {(2, True, 1)} | {(g, False, 0) for g in range(4, 9)} | {(g, True, 0) for g in range(3, 8)}
+            assert {(g, shared) for g, shared, narrow in met if narrow} == {(1, False), (2, False), (3, False), (2, True)}
+    half_empty = {(g, narrow) for g, _, narrow, _, empty in groups[1] if empty}
+    assert half_empty >= {(1, 1), (2, 1), (3, 1)} | {(g, 0) for g in range(3, 9)}
 
 
 def test_layers_of_one_round_stream(rules):
