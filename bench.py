@@ -83,15 +83,15 @@ def _ceilings(torch, moe, ctx, dev):
     del src, dst
     sink = torch.zeros(4, dtype=torch.float32, device=dev)
     blocks, steps = 256 * 4, 2048
-    flop = blocks * 8 * steps * 16 * 2.0 * 32 * 32 * 64
+    flop = blocks * 8 * steps * 32 * 2.0 * 16 * 16 * 128
     t_bare = _stage_ms(torch, lambda: moe.moe_probe_fp8_mfma(ctx, blocks, steps, False, sink), reps=3)
     t_scaled = _stage_ms(torch, lambda: moe.moe_probe_fp8_mfma(ctx, blocks, steps, True, sink), reps=3)
     return {"copy_GBs": 2.0 * nbytes / (t_copy * 1e-3) / 1e9,
             "fp8_mfma_loop_tflops": flop / (t_bare * 1e-3) / 1e12,
             "fp8_mfma_loop_with_block_scaling_tflops": flop / (t_scaled * 1e-3) / 1e12,
             "note": "measured in this run: 1 GiB streaming copy (read + write bytes); register-only loop of "
-                    "v_mfma_f32_32x32x64_f8f6f4 on random operand bits, bare and with the 16 fp32 multiply-adds per "
-                    "product that per-128-block scaling needs (no LDS, no memory).  Reported beside the published "
+                    "v_mfma_f32_16x16x128_f8f6f4 in the GEMMs' order on random operand bits, bare and with the fp32 "
+                    "multiply-adds that per-128-block scaling needs (no LDS, no memory).  Reported beside the published "
                     "peaks, which stay the denominators of every `frac`."}
 
 

@@ -234,9 +234,9 @@ int moe_debug_copy_hidden(moe_ctx* ctx, uint8_t* hq_out, float* hs_out);
  *   device pointers owned by the caller: 2*bytes / its duration is what HBM delivers to a kernel that
  *   does nothing else.
  * moe_probe_fp8_mfma: `blocks` workgroups of 8 waves run `steps` times the matrix work one wave of the grouped
- *   GEMM does per 128-wide K block (8 sub-tile products of two 32x32x64 FP8 matrix instructions, random operand
- *   bits held in registers: no LDS, no memory), scaled != 0: each product folded into its accumulator with 16
- *   fp32 multiply-adds as per-block scaling requires.  FLOP = blocks * 8 waves * steps * 16 * 2*32*32*64.
+ *   GEMM does per 128-wide K block (32 products of one 16x16x128 FP8 matrix instruction each, random operand
+ *   bits held in registers: no LDS, no memory), scaled != 0: each product folded into its accumulator with four
+ *   fp32 multiply-adds a lane as per-block scaling requires.  FLOP = blocks * 8 waves * steps * 32 * 2*16*16*128.
  *   sink: one float of device memory (practically never written). */
 int moe_probe_copy(moe_ctx* ctx, const void* src, void* dst, int64_t bytes);
 int moe_probe_fp8_mfma(moe_ctx* ctx, int32_t blocks, int32_t steps, int32_t scaled, float* sink);

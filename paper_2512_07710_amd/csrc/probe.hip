@@ -1,8 +1,7 @@
 // Measured ceilings of the machine the benchmark runs on, reported beside the published peaks:
 //   * a plain streaming copy (what HBM delivers to a kernel that does nothing else), and
-//   * a register-only loop of the FP8 matrix instruction the narrow and streaming GEMM tiles are built from (the big tiles' 16x16x128
-//     reaches 9 % more in such a loop), with random operand
-//     bits, once bare and once with the fp32 multiply-adds that per-128-block scaling adds to every product
+//   * a register-only loop of the FP8 matrix instruction that the big tiles of the GEMMs are built from, in their order, with random
+//     operand bits, once bare and once with the fp32 multiply-adds that per-128-block scaling adds to every product
 //     (no LDS, no memory: what the matrix cores sustain for this arithmetic at the clock the power limit allows).
 // Neither kernel is part of the layer.
 #include "moe_internal.hpp"
@@ -11,7 +10,7 @@ namespace moe355 {
 namespace {
 
 typedef int v8i __attribute__((ext_vector_type(8)));
-typedef float v16f __attribute__((ext_vector_type(16)));
+typedef float v4f __attribute__((ext_vector_type(4)));
 
 __global__ __launch_bounds__(256) void copy_kernel(const uint4* __restrict__ src, uint4* __restrict__ dst, size_t n16) {
     size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
@@ -28,10 +27,10 @@ __device__ inline uint32_t mix(uint32_t x) {
     return x;
 }
 
-// One "step" is what a wave of the grouped GEMM does per 128-wide K block: eight 32x32 sub-tile products of
-// two matrix instructions each (K = 64 + 64), SCALED: each product folded into its accumulator by 16 fp32
-// multiply-adds; bare: the matrix instructions accumulate in place.  Operand registers hold random e4m3
-// bytes (exponent field kept below the NaN pattern), four sets of each, used in rotation.
+// One "step" is what a wave of a full tile does per 128-wide K block: 32 products of four weight tiles and eight token tiles, 16x16x128
+// each, in the GEMM's order: token tile by token tile, the weights forwards and backwards in turn.  SCALED: every product is folded into its accumulator by four fp32 multiply-adds a lane; bare: the matrix
+// instructions accumulate in place.  Operand registers hold random e4m3 bytes (never the NaN pattern); two token tiles share a set.
+__device__ constexpr int weights_of(int m) { return m >> 2 > 0 && (m >> 2) % 2 == 0 ? 3 - (m & 3) : m & 3; }
 template <bool SCALED>
 __global__ __launch_bounds__(512, 1) void mfma_loop(int steps, float scale, float* __restrict__ sink) {
     v8i a[4], b[4];
@@ -43,47 +42,41 @@ __global__ __launch_bounds__(512, 1) void mfma_loop(int steps, float scale, floa
             a[s][j] = (int)(mix(seed + s * 8 + j) & 0xF7F7F7F7u);
             b[s][j] = (int)(mix(seed + 32 + s * 8 + j) & 0xF7F7F7F7u);
         }
-    v16f acc[8];
+    v4f acc[4][8], t[4];
 #pragma unroll
-    for (int i = 0; i < 8; ++i)
+    for (int w = 0; w < 4; ++w)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) acc[i][r] = 0.f;
-    // As in the GEMM, the multiply-adds of product i-1 follow the second matrix instruction of product i: by then
-    // its result has left the matrix pipe (no wait states needed) and the vector ALU works in the pipe's shadow.
-    v16f t0, t1;
+        for (int r = 0; r < 4; ++r) {
+            t[w][r] = 0.f;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) { t0[r] = 0.f; t1[r] = 0.f; }
+            for (int i = 0; i < 8; ++i) acc[w][i][r] = 0.f;
+        }
+    // As in the GEMM, the multiply-adds of product m-2 follow product m: by then its result has left the matrix pipe (no wait
+    // states needed) and the vector ALU works in the pipe's shadow.
     for (int it = 0; it < steps; ++it) {
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
+        for (int m = 0; m < 32; ++m) {
+            const int i = m >> 2, w = weights_of(m);
             if (SCALED) {
-                if (i & 1) {
-                    asm volatile("v_mfma_f32_32x32x64_f8f6f4 %0, %1, %2, 0" : "=&v"(t1) : "v"(a[i & 3]), "v"(b[i >> 1]));
-                    asm volatile("v_mfma_f32_32x32x64_f8f6f4 %0, %1, %2, %0" : "+v"(t1) : "v"(a[(i + 1) & 3]), "v"(b[(i >> 1) ^ 1]));
-                    asm volatile("" : "+v"(t0));
+                asm volatile("v_mfma_f32_16x16x128_f8f6f4 %0, %1, %2, 0" : "+v"(t[m & 3]) : "v"(a[w]), "v"(b[i & 3]));
+                const int p = (m + 30) & 31, pi = p >> 2, pw = weights_of(p);
+                asm volatile("" : "+v"(t[p & 3]));
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) acc[i - 1][r] = fmaf(scale, t0[r], acc[i - 1][r]);
-                    asm volatile("" : "+v"(acc[i - 1]));
-                } else {
-                    asm volatile("v_mfma_f32_32x32x64_f8f6f4 %0, %1, %2, 0" : "=&v"(t0) : "v"(a[i & 3]), "v"(b[i >> 1]));
-                    asm volatile("v_mfma_f32_32x32x64_f8f6f4 %0, %1, %2, %0" : "+v"(t0) : "v"(a[(i + 1) & 3]), "v"(b[(i >> 1) ^ 1]));
-                    asm volatile("" : "+v"(t1));
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) acc[(i + 7) & 7][r] = fmaf(scale, t1[r], acc[(i + 7) & 7][r]);
-                    asm volatile("" : "+v"(acc[(i + 7) & 7]));
-                }
+                for (int r = 0; r < 4; ++r) acc[pw][pi][r] = fmaf(scale, t[p & 3][r], acc[pw][pi][r]);
+                asm volatile("" : "+v"(acc[pw][pi]));
             } else {
-                asm volatile("v_mfma_f32_32x32x64_f8f6f4 %0, %1, %2, %0" : "+v"(acc[i]) : "v"(a[i & 3]), "v"(b[i >> 1]));
-                asm volatile("v_mfma_f32_32x32x64_f8f6f4 %0, %1, %2, %0" : "+v"(acc[i]) : "v"(a[(i + 1) & 3]), "v"(b[(i >> 1) ^ 1]));
+                asm volatile("v_mfma_f32_16x16x128_f8f6f4 %0, %1, %2, %0" : "+v"(acc[w][i]) : "v"(a[w]), "v"(b[i & 3]));
             }
         }
     }
     asm volatile("s_nop 15\n\ts_nop 15\n\ts_nop 7" ::: "memory");   // the last matrix results must have left the pipe
     float s = 0.f;
 #pragma unroll
-    for (int i = 0; i < 8; ++i)
+    for (int w = 0; w < 4; ++w)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) s += acc[i][r];
+        for (int i = 0; i < 8; ++i)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) s += acc[w][i][r];
     if (s == 12345.678f) sink[0] = s;                          // keeps the loop alive; practically never taken
 }
 
