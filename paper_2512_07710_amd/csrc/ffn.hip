@@ -525,7 +525,11 @@ __global__ __launch_bounds__(NTHREADS, 1) void ffn_gemm(const uint8_t* __restric
         wk.ft = wi / tiles;
         split_rows(n_rows, tiles, wi - wk.ft * tiles, wk);
     } else {
-        int wi = own_unit(*queue, xcd, slot);
+        // read together, not each where the compiler finds it needed: a round trip less at the start of every unit (passes, us, one after
+        // another / this: 656 x 4 tokens of 32 experts, 1024 x 512 40.3 / 39.9, 777 x 5 of 60, 2176 x 896 107.2 / 106.5)
+        int begin = queue->begin[xcd], fixed = queue->fixed[xcd], helpers = queue->helpers;
+        asm volatile("" : "+s"(begin), "+s"(fixed), "+s"(helpers));
+        int wi = own_unit(begin, fixed, helpers, slot);
         if (wi == NO_UNIT) return;
         if (wi == LOOK) {
             int32_t& s_unit = *reinterpret_cast<int32_t*>(smem + X_RING - 16);

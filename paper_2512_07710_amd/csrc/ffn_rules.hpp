@@ -158,11 +158,10 @@ __host__ __device__ inline void deal(const V& v, const Cuts& cuts, int units, in
     q.helpers = room >= left ? helpers : slots;
 }
 
-// The unit of block `slot` of XCD x, or whether it looks for one of the rest.
+// The unit of block `slot` of an XCD, or whether it looks for one of the rest.
 constexpr int LOOK = -1, NO_UNIT = -2;
-__host__ __device__ inline int own_unit(const Queue& q, int x, int slot) {
-    const int fixed = q.fixed[x];
-    return slot < fixed ? q.begin[x] + slot : slot < fixed + q.helpers ? LOOK : NO_UNIT;
+__host__ __device__ inline int own_unit(int begin, int fixed, int helpers, int slot) {
+    return slot < fixed ? begin + slot : slot < fixed + helpers ? LOOK : NO_UNIT;
 }
 // A unit of what the XCDs have left over, for a block of XCD x with no unit of its own: of its own XCD while there are any, then of the
 // one with the most.  NO_UNIT: none anywhere.  R counts what is gone of each XCD's rest: take(y) one more, of how many before; taken(y).

@@ -186,7 +186,7 @@ struct Launch {                                                // its blocks, in
     bool block() {
         if (started == blocks.size()) return false;
         const int b = blocks[started++];
-        int u = own_unit(q, b % NXCD, b / NXCD);
+        int u = own_unit(q.begin[b % NXCD], q.fixed[b % NXCD], q.helpers, b / NXCD);
         if (u == LOOK) u = take_rest(q, Counts{*this}, b % NXCD);
         if (u >= (int)times.size()) ++lost;
         else if (u >= 0) ++times[u];
