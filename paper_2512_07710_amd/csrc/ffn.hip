@@ -409,9 +409,14 @@ __device__ __forceinline__ void k_loop(const Tile& t, const Feed& f, v4f (&acc)[
 
     int wslot = 0;                                             // ring slot of weight block kb
     int kb = 0;
-    // Gate/up loops start on a multiple of 64 bytes.  Where a loop lies, modulo 32 bytes, is worth up to 6 % either way, and what other code
-    // of the kernel happens to make of it changes with every edit.
+    // Where a loop lies is worth up to 6 % either way, and what other code of the kernel happens to make of it changes with every edit.  So
+    // gate/up loops start on a multiple of 64 bytes, the others 28 bytes past one, with four groups 36.  us at 0 / 20 / 24 / 28 past: down
+    // projection of 16 experts, 2048 x 2048, of 150 rows 30.0 / 30.1 / 30.0 / 29.2 (where an edit elsewhere left it 30.0), of 165 rows 30.1 /
+    // 30.3 / 30.0 / 29.5; linear 473 x 3712 x 9216 31.0 / 31.7 / 31.8 / 30.8, 700 x 4096 x 8192 34.7 / 35.3 / 35.5 / 34.5.  Where they lay
+    // before / at 28 / with four groups at 36: linear 170 x 7168 x 32768 62.9 / 60.6 / 60.5, 12727 x 4864 x 14208 832 / 838 / 833; layers
+    // of 250 rows an expert and more level.
     if (GATED) asm volatile(".p2align 6");
+    else asm volatile(".p2align 6\n\t.rept %0\n\ts_nop 0\n\t.endr" :: "n"(NTS < 4 ? 7 : 9));
     do {                                                       // (K >= 128: at least one block)
         const int wnext = (wslot == NW_BUF - 1) ? 0 : wslot + 1;
         const int wprev = (wslot == 0) ? NW_BUF - 1 : wslot - 1;             // slot of block kb-1 = of block kb+2
