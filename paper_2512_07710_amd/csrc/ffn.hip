@@ -4,7 +4,8 @@
 // small kernel turns offsets[] into the list of work units (expert, first row, feature tile,
 // rows), so ragged experts need no host round trip, and orders it so that units sharing a
 // weight tile are adjacent; blocks map onto the list so that each XCD (blockIdx % 8) walks a
-// contiguous range, of equal cost, and its L2 sees every weight tile once (ffn_rules.hpp).
+// contiguous range, of equal numbers of units or, where the slowest XCD gains by it, of equal cost, and its L2 sees
+// every weight tile once (ffn_rules.hpp).
 //
 // Main loop, one iteration per 128-wide K block (= one scale block):
 //   * both operand tiles are copied global -> LDS by direct-to-LDS loads (no staging
@@ -188,7 +189,8 @@ struct RestCounts {
 
 // ------------------------------------------------------------------ helpers
 // The matrix instructions are written as volatile asm so that they stay exactly where the
-// source puts them: the schedule below relies on it.  T = A*B (first K half) and T += A*B.
+// source puts them: the schedule below relies on it.  A product over a whole K block at once, or over its first half (new) and
+// its second (acc).
 __device__ inline void mfma_16(v4f& t, const v8i& a, const v8i& b) {
     // "+v", although t is only written: the product registers then stay where they are through the whole K loop
     asm volatile("v_mfma_f32_16x16x128_f8f6f4 %0, %1, %2, 0" : "+v"(t) : "v"(a), "v"(b) : "memory");
@@ -287,8 +289,9 @@ constexpr Product product(int m) {
 //
 // With many rows this kernel runs at the power cap, so what counts is the energy of a product.  From registers alone, with the
 // multiply-adds, codes of quantised Gaussians, TFLOP/s: pairs of 32x32x64 3500 in any order, 16x16x128 3725 to 3790, in the order above
-// 3822.  Here, with the same sums bit for bit (inside an instruction the lane groups get their 16-byte chunks in the order in which
-// two 32x32x64 meet them, as in ffn_few.hip), against pairs of 32x32x64, us: linear 8192 x 7168 x 8192 475 / 464; 32768 tokens of
+// 3822 (3680 to 3730 on random bits: mfma_loop in probe.hip, where pairs of 32x32x64 reached 3460).  Here, with the same
+// sums bit for bit (inside an instruction the lane groups get their 16-byte chunks in the order in which two 32x32x64 meet them, as in
+// ffn_few.hip), against pairs of 32x32x64, us: linear 8192 x 7168 x 8192 486 / 475; 32768 tokens of
 // 7168 x 2048, 256 experts, gate/up 6940 / 6915, down 4370 / 4335; 4096 tokens of 5120 x 1536, 128 experts of 257..261 rows, 544 /
 // 546 and 350 / 343; 3000 x 6 of 2048 x 768 102.0 / 100.5 and 77.6 / 75.9.  The clock rises by what the energy falls, less 5 % more
 // cycles for twice the instructions and for handing out the scales.  Tried and level or worse: weight tile by weight tile, operands

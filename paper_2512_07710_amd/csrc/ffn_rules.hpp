@@ -80,9 +80,10 @@ __host__ __device__ inline int pick_height(const int (&tiles)[HEIGHTS], int grou
 // ------------------------------------------------------------------ dealing a list to the XCDs
 // Every XCD gets a contiguous part of its list, so that tiles which share weights stay behind one L2.  Parts of equal numbers are of
 // unequal cost where loads are skewed (4096 tokens x 8 of 128 Zipf experts, gate/up: XCDs done between 474 and 692 us), and XCDs are not
-// equally fast (256 experts of about 1024 rows: 6.66 to 7.10 ms with the same work).  Hence parts of equal cost, and the last sixteenth of
-// each is nobody's: a block that finds no unit of its own takes the next of its XCD, then of the XCD with the most left.  us, equal
-// numbers / this: the Zipf layer 1245 / 1175, the 256 experts 13505 / 13305, 128 experts of 257..261 rows 1100 / 1089.
+// equally fast (256 experts of about 1024 rows: 6.66 to 7.10 ms with the same work).  Hence parts of equal cost where the slowest XCD
+// gains by them, and of a part of six rounds and more the last sixteenth is nobody's: a block that finds no unit of its own takes the next of
+// its XCD, then of the XCD with the most left.  us, equal numbers / this: the Zipf layer 1245 / 1175, the 256 experts 13505 / 13305, 128
+// experts of 257..261 rows 1116 / 1100.
 // What an expert's tiles cost, for each feature tile: a tile of 8 groups 1.6 times one of 2 (Zipf gate/up 68 and 46 us).
 __host__ __device__ inline int tiles_share(int tiles, int groups) { return 8 * tiles + groups; }
 // Units run one to a CU in rounds, and with few rounds it is their number that counts: a list that makes one full round in parts of equal
