@@ -17,13 +17,15 @@ __device__ inline E4m3Coder group_coder(const u32x4& raw) {
     return E4m3Coder((amax == 0.f) ? 1.0f : amax / 448.0f);
 }
 
-// Group g of row r in token order.  All sixteen lanes of a live row call it.
+// Group g of row r in token order.  All sixteen lanes of a live row call it.  Codes and scales go past the caches: they are read next
+// by the CUs of other XCDs, from which lines that are still dirty in this one's L2 come slowly (gate/up projection of 3584 tokens x 1 of
+// 64 experts, 7168 x 512, behind this: 92 us / 79 past the caches, 777 x 5 of 60, 2176 x 896 49.5 / 48.9; larger batches level).
 __device__ inline void quantize_row_group(const token_quant& t, int64_t r, int g, int sub) {
     const size_t at = (size_t)r * t.cols + (size_t)g * QBLOCK + sub * 8;
     const u32x4 raw = *reinterpret_cast<const u32x4*>(t.x + at);
     const E4m3Coder coder = group_coder(raw);
-    *reinterpret_cast<u32x2*>(t.q + at) = coder.pack8(raw);
-    if (sub == 0) t.scales[(size_t)g * t.rows + r] = coder.s;
+    __builtin_nontemporal_store(coder.pack8(raw), reinterpret_cast<u32x2*>(t.q + at));
+    if (sub == 0) __builtin_nontemporal_store(coder.s, t.scales + (size_t)g * t.rows + r);
 }
 
 // block `unit` of THREADS threads: TOKEN_QUANT_ROWS rows of THREADS/(16*TOKEN_QUANT_ROWS) groups at a time (scales leave in runs of
