@@ -52,18 +52,6 @@ constexpr int CODES_LD = 128 + 16;                  // bytes from row to row of 
 // that run them side by side on one XCD advance in step and hit each other's lines in that XCD's L2
 // (a few K steps of skew already exceed what the L2 retains, and the shared tile is then fetched
 // again from HBM).
-// inclusive prefix sum over the wave, by lane shifts
-template <int CTRL, int ROWS>
-__device__ inline int from_lanes(int v) { return __builtin_amdgcn_update_dpp(0, v, CTRL, ROWS, 0xf, false); }
-__device__ inline int wave_scan(int v) {
-    v += from_lanes<0x111, 0xf>(v);                            // row_shr 1, 2, 4, 8: rows of 16 lanes
-    v += from_lanes<0x112, 0xf>(v);
-    v += from_lanes<0x114, 0xf>(v);
-    v += from_lanes<0x118, 0xf>(v);
-    v += from_lanes<0x142, 0xa>(v);                            // row_bcast 15, 31: over the rows
-    v += from_lanes<0x143, 0xc>(v);
-    return v;
-}
 // The lanes of a wave as deal() wants them: lane x has XCD x's number, lane NXCD the one after the last.
 struct WaveLanes {
     int lane;
@@ -231,12 +219,6 @@ struct Feed {
     asm volatile("s_mov_b32 m0, %0\n\ts_cmp_gt_i32 %3, %4\n\ts_cbranch_scc0 .Lskip%=\n\t"                  \
                  "global_load_lds_dwordx4 %1, %2" CACHE "\n.Lskip%=:"                                              \
                  :: "s"(LDS), "v"(VOFF), "s"(SBASE), "s"(N), "n"(J) : "memory", "scc")
-// a < b ? -1 : 0 for wave-uniform values, in a scalar register whatever the compiler makes of the comparison
-__device__ __forceinline__ int all_ones_if_less(int a, int b) {
-    int r;
-    asm("s_cmp_lt_i32 %1, %2\n\ts_cselect_b32 %0, -1, 0" : "=s"(r) : "s"(a), "s"(b) : "scc");
-    return r;
-}
 // ONCE: weights that few other tiles read go past the caches (non-temporal: a block stream of 128-byte row pieces into LDS reaches
 // 6.0..6.6 TB/s that way and 5.3..5.9 through them)
 template <bool ONCE, int J>
@@ -904,12 +886,13 @@ constexpr size_t SMEM_BYTES = NW_BUF * W_TILE + NX_BUF * X_TILE;   // 160 KiB
 // length of the gate/up projection's work list, behind which the down projection's lies; and room for both
 static int64_t gate_up_list(const moe_dims* D) { return gate_up_streams(D) ? 0 : gate_up_units(D); }
 size_t ffn_work_bytes(const moe_dims* D) {
+    if (gate_up_flows(D)) return sizeof(Work);                 // (then neither projection needs a list)
     return sizeof(Work) * (size_t)(gate_up_list(D) + (down_form(D) == Down::STREAM ? 0 : down_big_units(D)) + 1);
 }
 size_t ffn_queue_bytes() { return 2 * (sizeof(Queue) + NXCD * sizeof(Rest)); }
-size_t ffn_ticket_bytes(const moe_dims* D) { return gate_up_streams(D) ? sizeof(int32_t) * (size_t)gate_up_units(D) : 0; }
+size_t ffn_ticket_bytes(const moe_dims* D) { return gate_up_streams(D) && !gate_up_flows(D) ? sizeof(int32_t) * (size_t)gate_up_units(D) : 0; }
 size_t ffn_h_rows_bytes(const moe_dims* D) {
-    return gate_up_streams(D) ? sizeof(float) * (size_t)((int64_t)D->T * D->k) * (size_t)D->F : 0;
+    return gate_up_streams(D) && !gate_up_flows(D) ? sizeof(float) * (size_t)((int64_t)D->T * D->k) * (size_t)D->F : 0;
 }
 
 static hipError_t set_lds_limits() {
@@ -925,6 +908,7 @@ static hipError_t set_lds_limits() {
     }
     hipError_t e = set_stream_lds_limits();
     if (e == hipSuccess) e = set_few_lds_limits();
+    if (e == hipSuccess) e = set_flow_lds_limits();
     if (e != hipSuccess) return e;
     attr_set = true;
     return hipSuccess;
@@ -971,13 +955,13 @@ hipError_t launch_expert_ffn(moe_ctx* c, const uint8_t* xq, const float* xs, con
     if (c->profiling && c->prof_calls < PROF_MAX_CALLS) ev = c->prof_events + 3 * c->prof_calls++;
 
     const int N = (int)((int64_t)D.T * D.k);
-    const bool stream1 = gate_up_streams(&D);
+    const bool flow1 = gate_up_flows(&D), flow2 = down_flows(&D), stream1 = !flow1 && gate_up_streams(&D);
     const Down down = down_form(&D);
     const int units1 = (int)gate_up_units(&D);
     Work* work2 = work + gate_up_list(&D);                     // the down projection's list
     Queue* const queues = reinterpret_cast<Queue*>(c->queues); // and how each of them is dealt to the XCDs
     Rest* const rests = reinterpret_cast<Rest*>(queues + 2);
-    if (!stream1) {                                            // (the streaming kernels need neither list nor sorted scales)
+    if (!stream1 && !flow1) {                                  // (the streaming kernels need neither list nor sorted scales)
         const int lists = down == Down::STREAM ? 1 : 2;
         const int64_t gather = perm ? (int64_t)((N + 255) / 256) * (D.d / QBLOCK) : 0;
         hipLaunchKernelGGL(prepare_big_tiles, dim3((unsigned)((D.E + 1) * lists + gather)), dim3(256), 0, c->stream, offsets, D.E, lists,
@@ -985,7 +969,10 @@ hipError_t launch_expert_ffn(moe_ctx* c, const uint8_t* xq, const float* xs, con
                            work, work2, queues, rests, xs, D.T, perm, D.k, N, c->xs_sorted);
     }
     if (ev) (void)hipEventRecord(ev[0], c->stream);          // the timed interval is the GEMM kernel alone
-    if (gate_up_few(&D)) {
+    if (flow1) {
+        hipError_t e = launch_flow_gate_up(c, xq, xs, perm, offsets, W1, W3, s1, s3);
+        if (e != hipSuccess) return e;
+    } else if (gate_up_few(&D)) {
         hipError_t e = launch_few_gate_up(c, xq, xs, perm, offsets, (int)max_row_tiles(&D, FEW_ROWS), W1, W3, s1, s3);
         if (e != hipSuccess) return e;
     } else if (stream1) {
@@ -1000,14 +987,17 @@ hipError_t launch_expert_ffn(moe_ctx* c, const uint8_t* xq, const float* xs, con
         else launch(ffn_gemm<true, false, false>, xs, 1, 1);
     }
     if (ev) (void)hipEventRecord(ev[1], c->stream);
-    if (down_few(&D)) {
+    if (flow2) {
+        hipError_t e = launch_flow_down(c, offsets, W2, s2, y_perm);
+        if (e != hipSuccess) return e;
+    } else if (down_few(&D)) {
         hipError_t e = launch_few_down(c, offsets, (int)max_row_tiles(&D, FEW_ROWS), W2, s2, y_perm);
         if (e != hipSuccess) return e;
     } else if (down != Down::BIG) {
         hipError_t e = launch_stream_down(c, offsets, (int)down_stream_units(&D), down == Down::EITHER ? &queues[1].total : nullptr, W2, s2, y_perm);
         if (e != hipSuccess) return e;
     }
-    if (down != Down::STREAM) {
+    if (down != Down::STREAM && !flow2) {
         hipLaunchKernelGGL((ffn_gemm<false, false, false>), dim3(list_blocks((int)down_big_units(&D))), dim3(NTHREADS), SMEM_BYTES, c->stream, c->hq, c->hs, N, (const int32_t*)nullptr, 1, 1,
                            work2, queues + 1, rests + NXCD, W2, (const uint8_t*)nullptr, s2, (const float*)nullptr, D.F, D.d, (uint8_t*)nullptr,
                            (float*)nullptr, y_perm);

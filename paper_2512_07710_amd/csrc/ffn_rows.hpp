@@ -1,4 +1,4 @@
-// What the two weight-streaming GEMMs share (ffn_stream.hip, ffn_few.hip): their arguments, and the row tiles worked out on the device.
+// What the weight-streaming GEMMs share (ffn_stream.hip, ffn_flow.hip, ffn_few.hip): their arguments, and the row tiles worked out on the device.
 #pragma once
 #include "ffn_common.hpp"
 #include "ffn_rules.hpp"
@@ -84,12 +84,7 @@ struct RowTiles {
         int mine = 0;
 #pragma unroll
         for (int i = 0; i < 4; ++i) mine += count(i);
-        int incl = mine;
-#pragma unroll
-        for (int d = 1; d < 64; d <<= 1) {
-            const int v = __shfl_up(incl, d);
-            incl += lane >= d ? v : 0;
-        }
+        const int incl = wave_scan(mine);
         before = incl - mine;
         total = __builtin_amdgcn_readlane(incl, 63);
     }

@@ -107,6 +107,11 @@ hipError_t launch_few_gate_up(moe_ctx* c, const uint8_t* xq, const float* xs, co
 hipError_t launch_few_down(moe_ctx* c, const int32_t* offsets, int max_tiles, const uint8_t* W2, const float* s2, float* y_perm);
 hipError_t launch_few_linear(moe_ctx* c, const uint8_t* xq, const float* xs, int32_t rows, int32_t K, const uint8_t* Wq,
                              const float* ws, int32_t NOUT, float* y);
+// The GEMMs in persistent blocks (ffn_flow.hip)
+hipError_t set_flow_lds_limits();
+hipError_t launch_flow_gate_up(moe_ctx* c, const uint8_t* xq, const float* xs, const int32_t* perm, const int32_t* offsets,
+                               const uint8_t* W1, const uint8_t* W3, const float* s1, const float* s3);
+hipError_t launch_flow_down(moe_ctx* c, const int32_t* offsets, const uint8_t* W2, const float* s2, float* y_perm);
 size_t route_workspace_bytes(int E, int d);
 size_t route_partial_bytes(int T, int E);
 hipError_t launch_combine(moe_ctx* c, const float* y_perm, const int32_t* inv_perm,
