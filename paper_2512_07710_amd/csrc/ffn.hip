@@ -202,6 +202,13 @@ __device__ inline void store_codes(uint8_t* __restrict__ hq, const uint8_t* s_co
             *reinterpret_cast<const uint4*>(s_codes + (i >> 3) * CODES_LD + (i & 7) * 16);
 }
 
+// sixteen bytes of an output row, past the caches or through them
+template <bool PAST>
+__device__ inline void put_row(float* dst, const v4f& v) {
+    if (PAST) __builtin_nontemporal_store(v, reinterpret_cast<v4f*>(dst));
+    else *reinterpret_cast<v4f*>(dst) = v;
+}
+
 // ------------------------------------------------------------------ operand copies
 // What one wave brings of every K block: staged weight rows [32w, 32w+32) and staged activation rows [32w, 32w+32).
 struct Feed {
@@ -484,7 +491,8 @@ __device__ __forceinline__ void k_loop(const Tile& t, const Feed& f, v4f (&acc)[
 // expert-ordered copy of the codes is never materialised.  The scales act_s
 // [K/128][n_rows] are in sorted order in both cases (they are 1/128 of the data; a lane-scattered
 // scale read per K step would cost more than it saves).
-template <bool GATED, bool GATHER, bool LINEAR>
+// PAST: y_perm goes past the caches (down_goes_past, linear_goes_past).  An instance of its own: with both forms in one, the layers of the other took 0.3 % longer.
+template <bool GATED, bool GATHER, bool LINEAR, bool PAST = false>
 __global__ __launch_bounds__(NTHREADS, 1) void ffn_gemm(const uint8_t* __restrict__ act,
                                                         const float* __restrict__ act_s, int n_rows,
                                                         const int32_t* __restrict__ perm, int fan, int n_tok,
@@ -761,7 +769,7 @@ __global__ __launch_bounds__(NTHREADS, 1) void ffn_gemm(const uint8_t* __restric
                         float* const dst = y_perm + (size_t)p * NOUT + f0 + wave * 32 + (lane & 7) * 4;
 #pragma unroll
                         for (int it = 0; it < 4; ++it)
-                            if (p + it * 8 < row_end) *reinterpret_cast<v4f*>(dst + (size_t)(it * 8) * NOUT) = v[it];
+                            if (p + it * 8 < row_end) put_row<PAST>(dst + (size_t)(it * 8) * NOUT, v[it]);
                     }
                 }
             }
@@ -873,7 +881,7 @@ __global__ __launch_bounds__(NTHREADS, 1) void ffn_gemm(const uint8_t* __restric
                 float* const dst = y_perm + (size_t)p * NOUT + fcol + (lane & 15) * 4;
 #pragma unroll
                 for (int it = 0; it < 8; ++it)
-                    if (p + it * 4 < row_end) *reinterpret_cast<v4f*>(dst + (size_t)(it * 4) * NOUT) = v[it];
+                    if (p + it * 4 < row_end) put_row<PAST>(dst + (size_t)(it * 4) * NOUT, v[it]);
             }
         }
     }
@@ -898,10 +906,12 @@ size_t ffn_h_rows_bytes(const moe_dims* D) {
 static hipError_t set_lds_limits() {
     static bool attr_set = false;
     if (attr_set) return hipSuccess;
-    const void* kernels[4] = {reinterpret_cast<const void*>(&ffn_gemm<true, false, false>),
+    const void* kernels[6] = {reinterpret_cast<const void*>(&ffn_gemm<true, false, false>),
                               reinterpret_cast<const void*>(&ffn_gemm<true, true, false>),
                               reinterpret_cast<const void*>(&ffn_gemm<false, false, false>),
-                              reinterpret_cast<const void*>(&ffn_gemm<false, false, true>)};
+                              reinterpret_cast<const void*>(&ffn_gemm<false, false, false, true>),
+                              reinterpret_cast<const void*>(&ffn_gemm<false, false, true>),
+                              reinterpret_cast<const void*>(&ffn_gemm<false, false, true, true>)};
     for (const void* k : kernels) {
         hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)SMEM_BYTES);
         if (e != hipSuccess) return e;
@@ -998,9 +1008,13 @@ hipError_t launch_expert_ffn(moe_ctx* c, const uint8_t* xq, const float* xs, con
         if (e != hipSuccess) return e;
     }
     if (down != Down::STREAM && !flow2) {
-        hipLaunchKernelGGL((ffn_gemm<false, false, false>), dim3(list_blocks((int)down_big_units(&D))), dim3(NTHREADS), SMEM_BYTES, c->stream, c->hq, c->hs, N, (const int32_t*)nullptr, 1, 1,
-                           work2, queues + 1, rests + NXCD, W2, (const uint8_t*)nullptr, s2, (const float*)nullptr, D.F, D.d, (uint8_t*)nullptr,
-                           (float*)nullptr, y_perm);
+        auto launch = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, dim3(list_blocks((int)down_big_units(&D))), dim3(NTHREADS), SMEM_BYTES, c->stream, c->hq, c->hs, N, (const int32_t*)nullptr, 1, 1,
+                               work2, queues + 1, rests + NXCD, W2, (const uint8_t*)nullptr, s2, (const float*)nullptr, D.F, D.d, (uint8_t*)nullptr,
+                               (float*)nullptr, y_perm);
+        };
+        if (down_goes_past(&D)) launch(ffn_gemm<false, false, false, true>);
+        else launch(ffn_gemm<false, false, false>);
     }
     if (ev) (void)hipEventRecord(ev[2], c->stream);
     return hipGetLastError();
@@ -1015,10 +1029,14 @@ hipError_t launch_linear(moe_ctx* c, const uint8_t* xq, const float* xs, int32_t
     if (few_linear_groups(rows, NOUT)) return launch_few_linear(c, xq, xs, rows, K, Wq, ws, NOUT, y);
     if (linear_streams(rows, NOUT)) return launch_stream_linear(c, xq, xs, rows, K, Wq, ws, NOUT, y);
     const int nft = (NOUT + 255) / 256, tiles = linear_tiles(rows, nft, K / KB);
-    hipLaunchKernelGGL((ffn_gemm<false, false, true>), dim3((tiles * nft + NXCD - 1) / NXCD * NXCD), dim3(NTHREADS), SMEM_BYTES,
-                       c->stream, xq, xs, rows, (const int32_t*)nullptr, tiles, 1, (const Work*)nullptr,
-                       (const Queue*)nullptr, (Rest*)nullptr, Wq, (const uint8_t*)nullptr, ws, (const float*)nullptr, K, NOUT,
-                       (uint8_t*)nullptr, (float*)nullptr, y);
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3((tiles * nft + NXCD - 1) / NXCD * NXCD), dim3(NTHREADS), SMEM_BYTES,
+                           c->stream, xq, xs, rows, (const int32_t*)nullptr, tiles, 1, (const Work*)nullptr,
+                           (const Queue*)nullptr, (Rest*)nullptr, Wq, (const uint8_t*)nullptr, ws, (const float*)nullptr, K, NOUT,
+                           (uint8_t*)nullptr, (float*)nullptr, y);
+    };
+    if (linear_goes_past(rows, K, NOUT)) launch(ffn_gemm<false, false, true, true>);
+    else launch(ffn_gemm<false, false, true>);
     return hipGetLastError();
 }
 
