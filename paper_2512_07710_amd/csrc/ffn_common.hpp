@@ -1,5 +1,6 @@
 // What the two grouped FP8 GEMMs share: the big-tile kernel (ffn.hip) and the weight-streaming one (ffn_stream.hip).
 #pragma once
+#include "lanes.hpp"
 #include "moe_internal.hpp"
 
 namespace moe355 {
@@ -34,18 +35,6 @@ __device__ __forceinline__ int all_ones_if_less(int a, int b) {
     int r;
     asm("s_cmp_lt_i32 %1, %2\n\ts_cselect_b32 %0, -1, 0" : "=s"(r) : "s"(a), "s"(b) : "scc");
     return r;
-}
-// inclusive prefix sum over the wave, by lane shifts
-template <int CTRL, int ROWS>
-__device__ inline int from_lanes(int v) { return __builtin_amdgcn_update_dpp(0, v, CTRL, ROWS, 0xf, false); }
-__device__ inline int wave_scan(int v) {
-    v += from_lanes<0x111, 0xf>(v);                            // row_shr 1, 2, 4, 8: rows of 16 lanes
-    v += from_lanes<0x112, 0xf>(v);
-    v += from_lanes<0x114, 0xf>(v);
-    v += from_lanes<0x118, 0xf>(v);
-    v += from_lanes<0x142, 0xa>(v);                            // row_bcast 15, 31: over the rows
-    v += from_lanes<0x143, 0xc>(v);
-    return v;
 }
 
 // the 32 K-bytes a lane feeds to one 32x32x64 MFMA, from its row's two swizzled 16-byte chunks at LDS addresses c0, c1

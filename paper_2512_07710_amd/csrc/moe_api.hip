@@ -91,14 +91,14 @@ int moe_create(moe_ctx** out, const moe_dims* dims, void* hip_stream) {
     if (ffn_ticket_bytes(dims)) ok = ok && hipMalloc((void**)&c->tickets, ffn_ticket_bytes(dims)) == hipSuccess;
     if (ffn_h_rows_bytes(dims)) ok = ok && hipMalloc((void**)&c->h_rows, ffn_h_rows_bytes(dims)) == hipSuccess;
     ok = ok && hipMalloc((void**)&c->queues, ffn_queue_bytes()) == hipSuccess;
-    ok = ok && hipMalloc((void**)&c->flags, 2 * sizeof(int32_t)) == hipSuccess;
+    ok = ok && hipMalloc((void**)&c->flags, FLAG_INTS * sizeof(int32_t)) == hipSuccess;
     ok = ok && hipMalloc((void**)&c->router_planes, route_workspace_bytes(dims->E, dims->d)) == hipSuccess;
     if (route_partial_bytes(dims->T, dims->E))
         ok = ok && hipMalloc((void**)&c->route_partial, route_partial_bytes(dims->T, dims->E)) == hipSuccess;
     ok = ok && hipMalloc((void**)&c->xs_sorted, nrow * (size_t)(dims->d / QBLOCK) * sizeof(float)) == hipSuccess;
     ok = ok && hipMalloc((void**)&c->hq, nrow * (size_t)dims->F) == hipSuccess;
     ok = ok && hipMalloc((void**)&c->hs, nrow * (size_t)(dims->F / QBLOCK) * sizeof(float)) == hipSuccess;
-    ok = ok && launch_fill_i32(c->stream, c->flags, 2, 0) == hipSuccess;
+    ok = ok && launch_fill_i32(c->stream, c->flags, FLAG_INTS, 0) == hipSuccess;
     ok = ok && launch_fill_i32(c->stream, (int32_t*)c->queues, (int)(ffn_queue_bytes() / sizeof(int32_t)), 0) == hipSuccess;
     if (c->tickets)
         ok = ok && launch_fill_i32(c->stream, c->tickets, (int)(ffn_ticket_bytes(dims) / sizeof(int32_t)), 0) == hipSuccess;

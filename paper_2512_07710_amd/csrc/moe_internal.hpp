@@ -14,6 +14,7 @@ constexpr int FEW_ROWS = 16;       // expert-sorted rows per tile of the small-b
 constexpr int MAX_E = 256;
 constexpr int MAX_K = 16;
 constexpr int PROF_MAX_CALLS = 512;
+constexpr int ROUTE_TICKET = 32, FLAG_INTS = 33;   // (the ticket has a cache line of its own)
 
 
 }  // namespace moe355
@@ -27,8 +28,8 @@ struct moe_ctx {
     void* tiles;             // GEMM work lists (gate/up list, then down list)
     void* queues;            // [2] their lengths and how they are dealt to the XCDs
     int32_t* tickets;        // streaming gate/up projection only: one per unit, zero between launches
-    int32_t* flags;          // [2] flags[0] != 0: an expert id outside [0,E) was met; flags[1] != 0: a logged id repeated
-                             //     inside a token
+    int32_t* flags;          // [0] != 0: an expert id outside [0,E) was met; [1] != 0: a logged id repeated inside a token;
+                             //     [ROUTE_TICKET] the router's ticket, zero between launches
     float* h_rows;           // streaming gate/up projection only: [N][F] hidden activations before their codes
     float* xs_sorted;        // [d/128][N] activation scales in sorted order (gathered FFN only)
     uint16_t* router_planes; // router weights split into three bf16 planes, matrix-core order

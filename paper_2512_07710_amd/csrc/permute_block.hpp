@@ -1,5 +1,6 @@
 // The whole permutation of a small batch in one block: shared by the permutation's own launch and the router's last one.
 #pragma once
+#include "lanes.hpp"
 #include "moe_internal.hpp"
 
 namespace moe355 {
@@ -104,6 +105,59 @@ __device__ inline void permute_block(IdAt id_at, int N, int E, int32_t* __restri
         inv_perm[i] = pos;
         perm[pos] = i;
     }
+}
+
+// The same for up to 64 assignments by one wave: lane i ranks assignment i among the wave's, nothing is left to count.
+template <class IdAt>
+__device__ inline void permute_wave(IdAt id_at, int N, int E, int32_t* __restrict__ offsets, int32_t* __restrict__ perm,
+                                    int32_t* __restrict__ inv_perm, int k, bool check_dups, int32_t* __restrict__ flags) {
+    __shared__ int32_t s_of[MAX_E];                   // rows of each expert, then where they start
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int i = 0; i < MAX_E / 64; ++i) s_of[i * 64 + lane] = 0;
+    const int e = lane < N ? id_at(lane) : -1;
+    const bool valid = e >= 0 && e < E;
+    const int key = e & (MAX_E - 1);
+    uint64_t same = __ballot(valid);
+    if (!valid) same = ~same;
+#pragma unroll
+    for (int bit = 0; bit < 8; ++bit) {
+        const uint64_t bal = __ballot((key >> bit) & 1);
+        same &= ((key >> bit) & 1) ? bal : ~bal;
+    }
+    const uint64_t before = same & ((1ull << lane) - 1ull);
+    // LDS operations of a wave execute in order
+    if (valid && before == 0ull) s_of[key] = __popcll(same);
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    int n[MAX_E / 64], mine = 0;                      // lane l has experts 4l .. 4l+3
+#pragma unroll
+    for (int i = 0; i < MAX_E / 64; ++i) {
+        n[i] = s_of[lane * (MAX_E / 64) + i];
+        mine += n[i];
+    }
+    int at = wave_scan(mine) - mine;
+#pragma unroll
+    for (int i = 0; i < MAX_E / 64; ++i) {
+        const int expert = lane * (MAX_E / 64) + i;
+        s_of[expert] = at;
+        at += n[i];
+        if (expert < E) offsets[expert + 1] = at;
+    }
+    if (lane == 0) offsets[0] = 0;
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    if (lane >= N) return;
+    if (!valid) {
+        flags[0] = 1;
+        inv_perm[lane] = -1;
+        return;
+    }
+    if (check_dups) {
+        // earlier slots of the same token with the same id
+        if (before >> (lane - lane % k)) flags[1] = 1;
+    }
+    const int pos = s_of[key] + __popcll(before);
+    inv_perm[lane] = pos;
+    perm[pos] = lane;
 }
 
 }  // namespace moe355

@@ -515,12 +515,11 @@ __device__ inline float wave_sum_63(float v) {                 // (left in lane 
 // (3.1e-7 -> 2.3e-7 and 1.0e-6 -> 3.9e-7 at those sizes): sixteen products per chain instead of all of them in one.
 constexpr int ROWS_COLS = 1024, ROWS_GROUP = 8;
 
-__global__ __launch_bounds__(256) void route_rows_kernel(const uint16_t* __restrict__ x, const float* __restrict__ W, int T,
-                                                         int T_pad, int d, int E, int E_pad, float* __restrict__ partial) {
-    const int lane = threadIdx.x & 63;
-    const int e = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    if (e >= E) return;                                        // wave-uniform
-    const int c0 = blockIdx.y * ROWS_COLS + lane * 4;          // columns c0 + 256*j + 0..3 (d is a multiple of 128)
+// Expert e, slice `slice`; put(at, sum) is called by one lane.
+template <class Put>
+__device__ inline void score_rows(const uint16_t* __restrict__ x, const float* __restrict__ W, int T, int T_pad, int d, int E_pad, int e,
+                                  int slice, int lane, Put put) {
+    const int c0 = slice * ROWS_COLS + lane * 4;               // columns c0 + 256*j + 0..3 (d is a multiple of 128)
     float4 w[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
@@ -549,9 +548,15 @@ __global__ __launch_bounds__(256) void route_rows_kernel(const uint16_t* __restr
                 s = fmaf(__uint_as_float(v[t][j].y & 0xFFFF0000u), w[j].w, s);
             }
             s = wave_sum_63(s);
-            if (lane == 63) partial[((size_t)blockIdx.y * T_pad + t0 + t) * E_pad + e] = s;
+            if (lane == 63) put(((size_t)slice * T_pad + t0 + t) * E_pad + e, s);
         }
     }
+}
+__global__ __launch_bounds__(256) void route_rows_kernel(const uint16_t* __restrict__ x, const float* __restrict__ W, int T,
+                                                         int T_pad, int d, int E, int E_pad, float* __restrict__ partial) {
+    const int e = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    if (e >= E) return;                                        // wave-uniform
+    score_rows(x, W, T, T_pad, d, E_pad, e, blockIdx.y, threadIdx.x & 63, [&](size_t at, float s) { partial[at] = s; });
 }
 
 // Second half of the split router: one wave per token adds the partial logits up in split order, then
@@ -562,7 +567,12 @@ __global__ __launch_bounds__(256) void route_rows_kernel(const uint16_t* __restr
 // vector and scalar units.  (Twelve LDS-routed shuffles a round, and two more per slot in the softmax, made this chain 9.3 us
 // for one token of k = 6 and 12.7 for sixteen of k = 8 over 256 experts; it takes 5.6 and 8.8.)
 struct Choice { int id; float w; };                            // lane j < k: slot j of the token
-template <bool IDS>
+template <bool SHARED>
+__device__ inline float get_partial(const float* p) {
+    return SHARED ? __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : *p;
+}
+// SHARED: the partial logits were put by other blocks of this launch.
+template <bool IDS, bool SHARED = false>
 __device__ inline Choice finish_token(const float* __restrict__ partial, int splits, int T_pad, int E_pad,
                                       const float* __restrict__ bias, const int32_t* __restrict__ logged_idx, int t, int lane, int E,
                                       int k) {
@@ -577,7 +587,7 @@ __device__ inline Choice finish_token(const float* __restrict__ partial, int spl
         float part[ROUTE_MAX_SPLITS];
 #pragma unroll
         for (int sp = 0; sp < ROUTE_MAX_SPLITS; ++sp)
-            part[sp] = (e < E_pad && sp < splits) ? partial[((size_t)sp * T_pad + t) * E_pad + e] : 0.f;
+            part[sp] = (e < E_pad && sp < splits) ? get_partial<SHARED>(partial + ((size_t)sp * T_pad + t) * E_pad + e) : 0.f;
         float v = 0.f;
 #pragma unroll
         for (int sp = 0; sp < ROUTE_MAX_SPLITS; ++sp) v += part[sp];
@@ -663,6 +673,50 @@ __global__ __launch_bounds__(ONE_BLOCK_WAVES * 64) void route_finish_permute(
     permute_block<1>([&](int i) { return s_ids[i]; }, T * k, E, nullptr, nullptr, nullptr, offsets, perm, inv_perm, k, IDS, flags);
 }
 
+// All of it in one launch for at most a token to each wave of a block: the scores, as in route_rows_kernel, each put where all XCDs see
+// it; the last of the scoring blocks to arrive (an atomic ticket, returned to zero) selects and permutes, and nobody waits.  The tokens'
+// quantisation may come along in further blocks.  Bound by its chain of memory round trips.  One token x 64 experts x 4096, us: the two launches
+// before 3.1 + 7.1, this 8.8; one token x 8 experts x 1024 2.7 + 6.0 and 7.2.  Beyond TINY_BLOCKS scoring blocks their tickets come one behind another
+// (layers, us, two launches / this: 2 blocks 25.8 / 21.8, 48 37.8 / 37.3, 64 36.1 / 35.0, 128 63.5 / 63.5, 448 35.7 / 38.8 and 101.3 / 104.9).
+constexpr int TINY_WAVES = 4, TINY_BLOCKS = 64;
+template <bool IDS>
+__global__ __launch_bounds__(TINY_WAVES * 64) void route_tiny(
+    const uint16_t* __restrict__ x, const float* __restrict__ W, int T, int T_pad, int d, int E, int E_pad, int slices,
+    float* __restrict__ partial, const float* __restrict__ bias, const int32_t* __restrict__ logged_idx, int k,
+    int32_t* __restrict__ topk_idx, float* __restrict__ topk_w, int32_t* __restrict__ offsets, int32_t* __restrict__ perm,
+    int32_t* __restrict__ inv_perm, int32_t* __restrict__ flags, int32_t* __restrict__ ticket, token_quant tokens) {
+    const int groups = (E + TINY_WAVES - 1) / TINY_WAVES, scoring = groups * slices;
+    if ((int)blockIdx.x >= scoring) {
+        quantize_block<TINY_WAVES * 64, 2>(tokens, blockIdx.x - scoring);
+        return;
+    }
+    __shared__ int32_t s_ticket, s_ids[TINY_WAVES * MAX_K];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int e = (int)(blockIdx.x % groups) * TINY_WAVES + wave;
+    if (e < E)
+        score_rows(x, W, T, T_pad, d, E_pad, e, blockIdx.x / groups, lane, [&](size_t at, float s) {
+            __hip_atomic_store(partial + at, s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        });
+    // every wave's scores have reached the common point before the block takes its ticket
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (tid == 0) s_ticket = __hip_atomic_fetch_add(ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    if (s_ticket != scoring - 1) return;
+    if (tid == 0) __hip_atomic_store(ticket, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // for the next launch
+    if (wave < T) {
+        const Choice c = finish_token<IDS, true>(partial, slices, T_pad, E_pad, bias, logged_idx, wave, lane, E, k);
+        if (lane < k) {
+            s_ids[wave * k + lane] = c.id;
+            topk_idx[(size_t)wave * k + lane] = c.id;
+            topk_w[(size_t)wave * k + lane] = c.w;
+        }
+    }
+    __syncthreads();
+    if (wave == 0) permute_wave([&](int i) { return s_ids[i]; }, T * k, E, offsets, perm, inv_perm, k, IDS, flags);
+}
+
 }  // namespace
 
 size_t route_workspace_bytes(int E, int d) {
@@ -720,6 +774,17 @@ hipError_t launch_route(moe_ctx* c, const uint16_t* x, const float* W_r, const f
     const int rows_max = D.d == 128 && E_pad == 128 ? ROUTE_ROWS_ONE_CHUNK_MAX_T : ROUTE_ROWS_MAX_T;
     if (D.T <= rows_max && c->route_partial && slices <= ROUTE_MAX_SPLITS) {
         const int T_pad = (D.T + 31) / 32 * 32;
+        const int scoring = (D.E + TINY_WAVES - 1) / TINY_WAVES * slices;
+        if (D.T <= TINY_WAVES && scoring <= TINY_BLOCKS) {
+            const unsigned grid = (unsigned)(scoring + quantize_blocks<TINY_WAVES * 64, 2>(tokens));
+            auto launch = [&](auto kernel) {
+                hipLaunchKernelGGL(kernel, dim3(grid), dim3(TINY_WAVES * 64), 0, c->stream, x, W_r, D.T, T_pad, D.d, D.E, E_pad, slices,
+                                   c->route_partial, logged_idx ? nullptr : bias, logged_idx, D.k, topk_idx, topk_w, offsets, perm, inv_perm,
+                                   c->flags, c->flags + ROUTE_TICKET, tokens);
+                return hipGetLastError();
+            };
+            return logged_idx ? launch(route_tiny<true>) : launch(route_tiny<false>);
+        }
         hipLaunchKernelGGL(route_rows_kernel, dim3((D.E + 3) / 4, slices), dim3(256), 0, c->stream, x, W_r, D.T, T_pad, D.d, D.E,
                            E_pad, c->route_partial);
         return finish(slices, T_pad);
