@@ -35,6 +35,12 @@ constexpr int NO_CAND = 0x7FFFFFFF;
 // split over up to ROUTE_MAX_SPLITS blocks per token tile: as many as bring the grid to about 256 blocks.
 constexpr int ROUTE_SPLIT_MAX_T = 4096;
 constexpr int ROUTE_MAX_SPLITS = 16;
+// With at most so many chunks of 128 columns to a block the waves split the fp32 weights themselves instead of reading planes that a launch
+// of its own has made.  Splitting weights and bits are the same; a load takes 64 bytes of 32 rows where the planes lie as they are wanted, so long K loops are
+// slower (us, router launches with planes / this: 2 chunks, 256 tokens x 64 experts x 4096 11.0 / 6.3, 4 chunks, 1000 x 64 x 4096 13.1 / 10.0 and 128
+// x 256 x 7168 23.1 / 20.4; 7 chunks, 1000 x 256 x 7168 32.1 / 34.8, 20 chunks, 4096 x 128 x 5120 40.8 / 57.6, also with the splitting put between the
+// dependent products).
+constexpr int ROUTE_RAW_CHUNKS = 4;
 // Batches of at most ROUTE_ROWS_MAX_T tokens score on the vector ALU instead (us for the whole layer, that / matrix cores: one
 // token 44 / 52, 8 x 256 experts 138 / 157, 16 717 / 738 on the widest layer, 32 level, 64 120 / 114, 128 141 / 119).
 constexpr int ROUTE_ROWS_MAX_T = 32;
@@ -83,6 +89,27 @@ __global__ __launch_bounds__(256) void split_router_weights(const float* __restr
         v.z = p[pl][4] | (p[pl][5] << 16); v.w = p[pl][6] | (p[pl][7] << 16);
         const size_t off = ((((size_t)st * nk + kk) * 3 + pl) * 64 + half * 32 + row) * 8;
         *reinterpret_cast<uint4*>(planes + off) = v;
+    }
+}
+
+// Eight fp32 weights -> the same three planes, as matrix-core operands.
+typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
+__device__ inline uint32_t bf16_pair(float a, float b) {       // both rounded to nearest even
+    uint32_t r;
+    asm("v_cvt_pk_bf16_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+__device__ inline void split_weights(const v4i (&raw)[2], v4i (&w)[3]) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        float a = __int_as_float(raw[i >> 1][(i & 1) * 2]), b = __int_as_float(raw[i >> 1][(i & 1) * 2 + 1]);
+#pragma unroll
+        for (int p = 0; p < 3; ++p) {
+            const uint32_t h = bf16_pair(a, b);
+            w[p][i] = (int)h;
+            a -= bf16_bits_to_f32(h & 0xFFFFu);                // exact
+            b -= __uint_as_float(h & 0xFFFF0000u);
+        }
     }
 }
 
@@ -168,9 +195,10 @@ __device__ inline void wait_vm(int n) {
 // SPLIT = true (small batches, where one block per token tile would leave most compute units idle): block
 // (x, y) runs only chunks [y*cps, (y+1)*cps) of the K loop and writes its partial logits to
 // partial[y][token][expert]; route_finish_kernel adds the partials up and does the selection.
-template <int NS, int TS, int KS, bool IDS, bool SPLIT = false>
+// RAW: the weights come as fp32 rows and every wave splits them into the planes itself (ROUTE_RAW_CHUNKS).
+template <int NS, int TS, int KS, bool IDS, bool SPLIT = false, bool RAW = false>
 __global__ __launch_bounds__(256, 1) void route_mfma_kernel(const uint16_t* __restrict__ x,
-                                                            const uint16_t* __restrict__ planes,
+                                                            const void* __restrict__ weights,
                                                             const float* __restrict__ bias,
                                                             const int32_t* __restrict__ logged_idx, int T, int d,
                                                             int E, int k, int32_t* __restrict__ topk_idx,
@@ -180,7 +208,9 @@ __global__ __launch_bounds__(256, 1) void route_mfma_kernel(const uint16_t* __re
     constexpr int PANELS = KS / 4;                             // a chunk is staged as panels of RT rows x 128 bytes (64 columns)
     constexpr int STAGE = PANELS * RT * 128;                   // bytes of one staged chunk
     constexpr int AH = KS - 1;                                 // K steps the weight loads run ahead
-    constexpr int L = 3 * NS;                                  // weight loads per K step and wave
+    constexpr int PARTS = RAW ? 2 : 3;                         // 16-byte loads of a lane per K step and sub-tile
+    constexpr int L = PARTS * NS;                              // weight loads per K step and wave
+    static_assert(!RAW || TS == 1, "the split is ordered between the products of one token tile");
     constexpr int C = PANELS * TS;                             // activation copies per chunk and wave
     static_assert(KS == 4 || KS == 8, "a ring slot is a step's position inside its chunk");
     // two activation stages; the candidate lists [token][wave][MAX_K] of {logit, expert id} reuse the
@@ -220,8 +250,12 @@ __global__ __launch_bounds__(256, 1) void route_mfma_kernel(const uint16_t* __re
     };
     const v4i* wsrc[NS];
 #pragma unroll
-    for (int s = 0; s < NS; ++s)
-        wsrc[s] = reinterpret_cast<const v4i*>(planes) + ((size_t)(wave * NS + s) * (d / 16) * 3) * 64 + lane;
+    for (int s = 0; s < NS; ++s) {
+        if (RAW)                                               // lane (l32, half): expert l32's columns half*8 .. half*8 + 7 of a K step
+            wsrc[s] = reinterpret_cast<const v4i*>(reinterpret_cast<const float*>(weights) +
+                                                   (size_t)min((wave * NS + s) * 32 + l32, E - 1) * d + half * 8);
+        else wsrc[s] = reinterpret_cast<const v4i*>(weights) + ((size_t)(wave * NS + s) * (d / 16) * 3) * 64 + lane;
+    }
 
     // accumulators live in the accumulation registers for the whole K loop; the matrix instructions are
     // volatile asm with a memory clobber, so they and the loads around them stay in source order
@@ -236,12 +270,12 @@ __global__ __launch_bounds__(256, 1) void route_mfma_kernel(const uint16_t* __re
     // Weight operands run KS - 1 K steps ahead of the matrix cores in a ring of KS register sets
     // (a K step is 16 columns; a staged activation chunk holds KS of them, so the ring slot of a
     // step is its position inside the chunk).
-    v4i a[KS][NS][3];
+    v4i a[KS][NS][PARTS];
     auto load_a = [&](int slot, int kk) {
 #pragma unroll
         for (int s = 0; s < NS; ++s)
 #pragma unroll
-            for (int p = 0; p < 3; ++p) a[slot][s][p] = wsrc[s][((size_t)kk * 3 + p) * 64];
+            for (int p = 0; p < PARTS; ++p) a[slot][s][p] = RAW ? wsrc[s][(size_t)kk * 4 + p] : wsrc[s][((size_t)kk * 3 + p) * 64];
     };
     issue_x(kc_begin);
     // A wave whose experts are all padding only stages activations.  The planes come from the L2 for every token tile, and with 16
@@ -303,14 +337,26 @@ __global__ __launch_bounds__(256, 1) void route_mfma_kernel(const uint16_t* __re
             // must have returned (the compiler cannot see this through the asm below, so it is written out)
             if (ks + 1 < KS) asm volatile("s_waitcnt lgkmcnt(%0)" :: "n"(TS) : "memory");
             else asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            if constexpr (RAW) {
+                v4i w[NS][3];
 #pragma unroll
-            for (int s = 0; s < NS; ++s)
+                for (int s = 0; s < NS; ++s) split_weights(a[ks][s], w[s]);
 #pragma unroll
                 for (int p = 0; p < 3; ++p)
 #pragma unroll
-                    for (int ts = 0; ts < TS; ++ts)
+                    for (int s = 0; s < NS; ++s)
                         asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0"
-                                     : "+a"(acc[s][ts]) : "v"(a[ks][s][p]), "v"(b[ks & 1][ts]) : "memory");
+                                     : "+a"(acc[s][0]) : "v"(w[s][p]), "v"(b[ks & 1][0]) : "memory");
+            } else {
+#pragma unroll
+                for (int s = 0; s < NS; ++s)
+#pragma unroll
+                    for (int p = 0; p < 3; ++p)
+#pragma unroll
+                        for (int ts = 0; ts < TS; ++ts)
+                            asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0"
+                                         : "+a"(acc[s][ts]) : "v"(a[ks][s][p]), "v"(b[ks & 1][ts]) : "memory");
+            }
         }
     }
     // the last matrix instructions must have left the pipe before the accumulators are read
@@ -789,9 +835,11 @@ hipError_t launch_route(moe_ctx* c, const uint16_t* x, const float* W_r, const f
                            E_pad, c->route_partial);
         return finish(slices, T_pad);
     }
-    const int64_t nthreads = (int64_t)E_pad * (D.d / 8);
-    hipLaunchKernelGGL(split_router_weights, dim3((unsigned)((nthreads + 255) / 256)), dim3(256), 0, c->stream,
-                       W_r, D.E, E_pad, D.d, c->router_planes);
+    auto split_weights_first = [&]() {
+        const int64_t nthreads = (int64_t)E_pad * (D.d / 8);
+        hipLaunchKernelGGL(split_router_weights, dim3((unsigned)((nthreads + 255) / 256)), dim3(256), 0, c->stream,
+                           W_r, D.E, E_pad, D.d, c->router_planes);
+    };
     const int nchunks = D.d / 128;
     if (D.T <= ROUTE_SPLIT_MAX_T && c->route_partial && nchunks >= 2) {
         // small batch: 32-token tiles, the K loop of each split over enough blocks to occupy the chip
@@ -801,14 +849,23 @@ hipError_t launch_route(moe_ctx* c, const uint16_t* x, const float* W_r, const f
         splits = (nchunks + cps - 1) / cps;                    // no empty block
         if (splits >= 2) {
             const dim3 grid(tiles, splits);
-#define MOE_ROUTE_SPLIT(NS_)                                                                                       \
-    hipLaunchKernelGGL((route_mfma_kernel<NS_, 1, 8, false, true>), grid, dim3(256), 0, c->stream, x, c->router_planes, \
-                       bias, logged_idx, D.T, D.d, D.E, D.k, topk_idx, topk_w, c->route_partial, cps)
-            if (E_pad == 128) MOE_ROUTE_SPLIT(1); else MOE_ROUTE_SPLIT(2);
-#undef MOE_ROUTE_SPLIT
+            const bool raw = cps <= ROUTE_RAW_CHUNKS;
+            if (!raw) split_weights_first();
+            auto launch = [&](auto kernel) {
+                hipLaunchKernelGGL(kernel, grid, dim3(256), 0, c->stream, x, raw ? (const void*)W_r : (const void*)c->router_planes,
+                                   bias, logged_idx, D.T, D.d, D.E, D.k, topk_idx, topk_w, c->route_partial, cps);
+            };
+            if (E_pad == 128) {
+                if (raw) launch(route_mfma_kernel<1, 1, 8, false, true, true>);
+                else launch(route_mfma_kernel<1, 1, 8, false, true>);
+            } else {
+                if (raw) launch(route_mfma_kernel<2, 1, 8, false, true, true>);
+                else launch(route_mfma_kernel<2, 1, 8, false, true>);
+            }
             return finish(splits, tiles * 32);
         }
     }
+    split_weights_first();
     // token tile: the largest of 128 / 64 / 32 rows that still gives every compute unit a block
     const int TS = D.T >= 256 * 128 ? 4 : D.T >= 256 * 64 ? 2 : 1;
     const int grid = (D.T + 32 * TS - 1) / (32 * TS);
