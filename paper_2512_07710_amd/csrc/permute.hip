@@ -180,7 +180,7 @@ __global__ __launch_bounds__(256) void scatter(const int32_t* __restrict__ ids, 
 }
 
 constexpr int ONE_BLOCK_MAX_N = ONE_BLOCK_WAVES * ONE_BLOCK_MAX_STEPS * 64;
-constexpr int ONE_BLOCK_CHECKED_MAX_N = 4096;
+constexpr int ONE_BLOCK_CHECKED_MAX_N = 5120;
 static_assert(ONE_BLOCK_CHECKED_MAX_N <= ONE_BLOCK_MAX_N, "the block holds that many");
 inline int one_block_max_n(bool check_dups, int k) { return check_dups && k > 1 ? ONE_BLOCK_CHECKED_MAX_N : ONE_BLOCK_MAX_N; }
 

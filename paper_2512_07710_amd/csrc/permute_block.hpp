@@ -8,13 +8,11 @@ namespace moe355 {
 // Up to one_block_max_n assignments: the three steps of permute.hip in one block and one launch, where the launches themselves are most of the
 // time.  Sixteen waves rank STEPS times 64 entries each in the manner of chunk_hist_rank, then scan over the experts and scatter
 // from registers; bound by its chain of barriers and memory round trips.
-// Whole calls in a row, us, this form / the three launches: replay of 2100 assignments k = 6 7.6 / 10.6, 4000 k = 2 6.9 / 10.3,
-// k = 6 8.7 / 10.7, k = 8 9.5 / 10.9, k = 16 12.0 / 11.5 (on cleared caches 16.3 / 18.0).  Beyond that the search for repeated ids, up to
-// k - 1 reads of earlier slots one after another in each of a thread's STEPS entries, weighs more in one block than launches
-// that overlap: 4500 k = 6 13.3 / 10.6, 8100 15.4 / 11.4, 8096 k = 16 22.3 / 11.9; layers of 4500 k = 6 57.7 / 55.0, 4800 k = 16
-// 94.2 / 86.8, 8000 k = 8 177 / 173, but 3360 k = 16 54.4 / 55.4.  Without that search (ids from the router
-// itself, one slot a token) the one block stays ahead: with the router 23.4 / 25.7 at 4500, 25.5 / 27.0 at 8100 and level at 8096 with
-// k = 8; replay of 8100 k = 1 11.6 / 11.2, a replayed layer of 4500 k = 1 55.2 / 56.3.
+// Whole calls in a row, us, this form / the three launches: replay of 2100 assignments k = 6 6.0 / 10.6, 4000 k = 2 7.2 / 10.3, k = 8 7.5 / 10.9,
+// 4096 k = 16 7.5 / 11.5, 4500 k = 6 10.8 / 11.2, 6000 11.9 / 11.2, 7800 14.1 / 11.5, 8000 k = 8 12.9 / 11.5, k = 16 13.3 / 12.0; layers of 750 x 6 of 32,
+// 1024 x 512 48.3 / 49.6, 1000 x 6 of 64, 4096 x 512 level, 1300 x 6 of 32, 3072 x 512 107.5 / 106.0.  Ids from the router itself, one slot a token: with the
+// router 23.4 / 25.7 at 4500, 25.5 / 27.0 at 8100 and level at 8096 with k = 8; replay of 8100 k = 1 11.6 / 11.2, a replayed layer of 4500 k = 1 55.2 /
+// 56.3.  (With repeats searched for by reading all earlier slots of a token, 350 x 6 7.6, 500 x 8 9.4, 256 x 16 11.9.)
 constexpr int ONE_BLOCK_WAVES = 16;
 constexpr int ONE_BLOCK_MAX_STEPS = 8;
 
@@ -58,6 +56,14 @@ __device__ inline void permute_block(IdAt id_at, int N, int E, int32_t* __restri
         const int before = s_cnt[wave][key];
         my_rank[st] = before + __popcll(same & lower);
         if (valid && (same & lower) == 0ull) s_cnt[wave][key] = before + __popcll(same);
+        // A repeat of an earlier slot of the same token: among the 64 that are looked at together the ballots have found it; slots before them are
+        // read, by the few lanes whose token begins there.
+        if (check_dups && valid) {
+            const int slot = i % k, here = lane < slot ? lane : slot;
+            bool dup = ((same & lower) >> (lane - here)) != 0ull;
+            for (int q = i - slot; q < i - here; ++q) dup |= id_at(q) == v;
+            if (dup) flags[1] = 1;
+        }
     }
     __syncthreads();
     int total = 0, incl = 0;
@@ -94,12 +100,6 @@ __device__ inline void permute_block(IdAt id_at, int N, int E, int32_t* __restri
             flags[0] = 1;
             inv_perm[i] = -1;
             continue;
-        }
-        if (check_dups) {
-            const int first = i - i % k;
-            bool dup = false;
-            for (int q = first; q < i; ++q) dup |= id_at(q) == e;
-            if (dup) flags[1] = 1;
         }
         const int pos = s_off[e] + s_cnt[wave][e] + my_rank[st];
         inv_perm[i] = pos;
