@@ -320,7 +320,7 @@ inline bool linear_streams(int32_t rows, int32_t NOUT) {
 
 // Output rows of the big tiles go past the caches where nobody will find them there: stored through them, each XCD's L2 is full of dirty
 // lines that wait to be written while the next kernel loads (us, through / past).  Linear with its quantisation, by bytes of y: 268 MB
-// 8192 x 7168 x 8192 476 / 445, 8192 x 2048 x 8192 191 / 181, with K = 1024 130.5 / 129.1 and 16384 x 1024 x 4096 113.9 / 115.6, 724 MB 12727
+// 8192 x 7168 x 8192 476 / 445 (other inputs in each pass 489 / 483), 8192 x 2048 x 8192 191 / 181, with K = 1024 130.5 / 129.1 and 16384 x 1024 x 4096 113.9 / 115.6, 724 MB 12727
 // x 4864 x 14208 841 / 828; less than the last-level cache's 256 MB 197 MB 3000 x 2048 x 16384 113.4 / 113.8, 65 MB 2000 x 4096 x 8192 69.8 /
 // 70.8, others level.  Layers, whose combine comes at once and finds the last part: 805 MB 8192 x 6 of 64, 4096 x 1408 1102 / 1093, 1.3 GB
 // 8192 x 8 of 128, 5120 x 1536 1980 / 1956, 1.6 GB 16000 x 6 of 64, 4096 x 1024 1656 / 1617, 7.5 GB 32768 x 8 of 256, 7168 x 2048 13224 /
