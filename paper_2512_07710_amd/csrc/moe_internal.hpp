@@ -29,7 +29,7 @@ struct moe_ctx {
     void* queues;            // [2] their lengths and how they are dealt to the XCDs
     int32_t* tickets;        // streaming gate/up projection only: one per unit, zero between launches
     int32_t* flags;          // [0] != 0: an expert id outside [0,E) was met; [1] != 0: a logged id repeated inside a token;
-                             //     [ROUTE_TICKET] the router's ticket, zero between launches
+                             //     [ROUTE_TICKET] ticket of the router and the permutation, zero between launches
     float* h_rows;           // streaming gate/up projection only: [N][F] hidden activations before their codes
     float* xs_sorted;        // [d/128][N] activation scales in sorted order (gathered FFN only)
     uint16_t* router_planes; // router weights split into three bf16 planes, matrix-core order
@@ -65,12 +65,13 @@ struct permute_args {
     int T, E, k;
     int32_t* chunk_counts;
     int32_t* flags;
+    int32_t* ticket;             // zero between launches
     bool check_dups;
 };
 hipError_t launch_permute(const permute_args& a, const int32_t* ids_in, int32_t* ids_copy, const float* w_in,
                           float* w_copy, int32_t* offsets, int32_t* perm, int32_t* inv_perm, const token_quant& tokens);
 inline permute_args permute_args_of(moe_ctx* c, bool check_dups) {
-    return permute_args{c->stream, c->dims.T, c->dims.E, c->dims.k, c->chunk_counts, c->flags, check_dups};
+    return permute_args{c->stream, c->dims.T, c->dims.E, c->dims.k, c->chunk_counts, c->flags, c->flags + ROUTE_TICKET, check_dups};
 }
 // Router Replay with every byte of workspace in a static device array (permute.hip)
 int route_replay_noalloc(hipStream_t stream, int32_t T, int32_t E, int32_t k, const int32_t* logged_idx,

@@ -1,12 +1,12 @@
 // Stable counting sort of the T*k (token, slot) assignments by expert id.
 //
-// Three atomics-free kernels:
+// Two kernels:
 //   1. chunk_hist_rank: each block ranks PERM_CHUNK ids with wave ballots and per-wave
 //      running counts in LDS, which yields the chunk's histogram and every entry's rank
 //      among earlier equal ids of the chunk.
-//   2. scan_chunks: one block turns the per-chunk histograms into exclusive prefix
-//      sums over chunks (per expert) and the expert totals into offsets[0..E].
-//   3. scatter: position = offsets[e] + prefix[chunk][e] + rank; writes perm/inv_perm.  Ids that come
+//      Its last block turns the per-chunk histograms into exclusive prefix
+//      sums over chunks (per expert) and the expert totals into offsets[0..E] (scan_chunks).
+//   2. scatter: position = offsets[e] + prefix[chunk][e] + rank; writes perm/inv_perm.  Ids that come
 //      from a log are also checked here: an id outside [0,E) raises flags[0], an id that repeats an
 //      earlier slot of the same token raises flags[1] (the permutation is still the stable sort of
 //      what was given).
@@ -20,8 +20,8 @@
 namespace moe355 {
 namespace {
 
-// Scratch of moe_route_replay_noalloc: the per-chunk histograms of the three-kernel permutation, then two flag
-// words.  A file-scope device array (every GPU the library runs on holds its own copy until the process ends)
+// Scratch of moe_route_replay_noalloc: the per-chunk histograms of the two-kernel permutation, then two flag
+// words and a ticket.  A file-scope device array (every GPU the library runs on holds its own copy until the process ends)
 // instead of a hipMalloc'ed workspace, so that the call allocates nothing.
 constexpr int NOALLOC_MAX_N = 1 << 20;                                  // assignments (T*k) per call
 constexpr int NOALLOC_COUNT_INTS = (NOALLOC_MAX_N / PERM_CHUNK) * MAX_E; // 512 chunks x 256 experts
@@ -51,16 +51,57 @@ hipError_t scratch_on_current_device(int32_t** out) {
     return hipSuccess;
 }
 
+// Per-chunk histograms -> their exclusive prefix sums over chunks (per expert), and the experts' totals -> offsets[0..E].  One block, whose
+// launch's other blocks have put the histograms.
+__device__ inline void scan_chunks(int32_t* __restrict__ chunk_counts, int n_chunks, int E, int32_t* __restrict__ offsets) {
+    __shared__ int32_t s_part[MAX_E / 64];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    auto count = [&](int c) {
+        return __hip_atomic_load(chunk_counts + (size_t)c * E + tid, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
+    int run = 0;
+    if (tid < E) {
+        int c = 0;
+        for (; c + 16 <= n_chunks; c += 16) {
+            int v[16];
+#pragma unroll
+            for (int u = 0; u < 16; ++u) v[u] = count(c + u);
+#pragma unroll
+            for (int u = 0; u < 16; ++u) {
+                chunk_counts[(size_t)(c + u) * E + tid] = run;
+                run += v[u];
+            }
+        }
+        for (; c < n_chunks; ++c) {
+            const int v = count(c);
+            chunk_counts[(size_t)c * E + tid] = run;
+            run += v;
+        }
+    }
+    int incl = wave_scan(run);
+    if (lane == 63) s_part[wave] = incl;
+    __syncthreads();
+    for (int w = 0; w < wave; ++w) incl += s_part[w];
+    if (tid < E) offsets[tid + 1] = incl;
+    if (tid == 0) offsets[0] = 0;
+}
+
 // Each of the four waves ranks a quarter of the chunk, 64 entries at a time: eight ballots (one per
 // bit of the expert id) give every lane the set of lanes that hold the same id, its rank among them is
 // a population count of the lower lanes, and the lowest lane of each set advances that expert's running
 // count, kept per wave in LDS (read by the whole set, then written by one lane: LDS operations of a wave
 // execute in order).  A second pass turns the per-wave counts into the chunk histogram and the per-wave
 // bases.  Ids outside [0,E) are ranked among themselves; that rank is never used.
+// The last block to arrive (an atomic ticket, returned to zero) scans the histograms; nobody waits.  In a launch of its own the scan came behind the
+// tokens' quantisation that rides in this one (us, two launches / this: 8000 assignments of 64 experts 7.4 + 2.7 / 9.0, 12000 of 16 6.6 + 4.6 /
+// 8.8, 262144 of 256 11.6 + 20.2 / 28.4; layers of 1000 x 8 of 64, 1024 x 512 61.4 / 60.2, 6000 x 2 of 16, 3072 x 2048 337.0 / 334.8, 4096 x 8 of 128, 5120 x
+// 1536 1093 / 1091).
 __global__ __launch_bounds__(256) void chunk_hist_rank(const int32_t* __restrict__ ids, int N, int E,
                                                        int32_t* __restrict__ chunk_counts,
                                                        int32_t* __restrict__ rank_out,
-                                                       int32_t* __restrict__ ids_copy, int n_chunks, token_quant tokens) {
+                                                       int32_t* __restrict__ ids_copy, int n_chunks,
+                                                       int32_t* __restrict__ offsets, int32_t* __restrict__ ticket,
+                                                       token_quant tokens) {
     if ((int)blockIdx.x >= n_chunks) {                // (as in permute_one_block)
         quantize_block<256, 2>(tokens, blockIdx.x - n_chunks);
         return;
@@ -105,7 +146,8 @@ __global__ __launch_bounds__(256) void chunk_hist_rank(const int32_t* __restrict
             s_cnt[w][tid] = run;
             run += c;
         }
-        if (tid < E) chunk_counts[(size_t)blockIdx.x * E + tid] = run;
+        if (tid < E)
+            __hip_atomic_store(chunk_counts + (size_t)blockIdx.x * E + tid, run, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     __syncthreads();
 #pragma unroll
@@ -113,43 +155,15 @@ __global__ __launch_bounds__(256) void chunk_hist_rank(const int32_t* __restrict
         const int i = base + wave * PER_WAVE + st * 64 + lane;
         if (i < N) rank_out[i] = my_rank[st] + s_cnt[wave][my_id[st] & (MAX_E - 1)];
     }
-}
-
-__global__ __launch_bounds__(256) void scan_chunks(int32_t* __restrict__ chunk_counts, int n_chunks,
-                                                   int E, int N, int32_t* __restrict__ offsets) {
-    __shared__ int32_t s_tot[MAX_E];
-    const int tid = threadIdx.x;
-    int run = 0;
-    if (tid < E) {
-        int c = 0;
-        for (; c + 8 <= n_chunks; c += 8) {
-            int v[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) v[u] = chunk_counts[(size_t)(c + u) * E + tid];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                chunk_counts[(size_t)(c + u) * E + tid] = run;
-                run += v[u];
-            }
-        }
-        for (; c < n_chunks; ++c) {
-            const int v = chunk_counts[(size_t)c * E + tid];
-            chunk_counts[(size_t)c * E + tid] = run;
-            run += v;
-        }
-    }
-    s_tot[tid] = (tid < E) ? run : 0;
+    // the histogram has reached the point where all XCDs see it before the block takes its ticket
+    __shared__ int32_t s_ticket;
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
     __syncthreads();
-    // inclusive scan over experts (Hillis-Steele, 256 entries)
-    for (int off = 1; off < MAX_E; off <<= 1) {
-        int add = (tid >= off) ? s_tot[tid - off] : 0;
-        __syncthreads();
-        s_tot[tid] += add;
-        __syncthreads();
-    }
-    if (tid < E) offsets[tid + 1] = s_tot[tid];
-    if (tid == 0) offsets[0] = 0;
-    (void)N;
+    if (tid == 0) s_ticket = __hip_atomic_fetch_add(ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    if (s_ticket != n_chunks - 1) return;
+    if (tid == 0) __hip_atomic_store(ticket, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // for the next launch
+    scan_chunks(chunk_counts, n_chunks, E, offsets);
 }
 
 __global__ __launch_bounds__(256) void scatter(const int32_t* __restrict__ ids, int N, int E,
@@ -203,6 +217,11 @@ __global__ void fill_i32(int32_t* __restrict__ p, int n, int32_t v) {
     if (i < n) p[i] = v;
 }
 
+__global__ void clear_flags(int32_t* __restrict__ flags, int32_t* __restrict__ ticket) {
+    if (threadIdx.x < 2) flags[threadIdx.x] = 0;
+    if (threadIdx.x == 2) *ticket = 0;
+}
+
 }  // namespace
 
 // a fill kernel, not hipMemsetAsync: it stays correct when a caller records the call into a HIP graph
@@ -228,11 +247,9 @@ hipError_t launch_permute(const permute_args& a, const int32_t* ids_in, int32_t*
 #undef MOE_ONE_BLOCK
         return hipGetLastError();
     }
-    if (n_chunks > 0)
+    if (N > 0)
         hipLaunchKernelGGL(chunk_hist_rank, dim3((unsigned)(n_chunks + quantize_blocks<256, 2>(tokens))), dim3(256), 0, a.stream, ids_in,
-                           N, a.E, a.chunk_counts, inv_perm, ids_copy, n_chunks, tokens);
-    hipLaunchKernelGGL(scan_chunks, dim3(1), dim3(256), 0, a.stream, a.chunk_counts, n_chunks, a.E, N,
-                       offsets);
+                           N, a.E, a.chunk_counts, inv_perm, ids_copy, n_chunks, offsets, a.ticket, tokens);
     if (N > 0)
         hipLaunchKernelGGL(scatter, dim3((N + 255) / 256), dim3(256), 0, a.stream, ids_in, N, a.E,
                            a.chunk_counts, offsets, w_in, w_copy, perm, inv_perm, a.k, a.check_dups, a.flags);
@@ -251,10 +268,13 @@ int route_replay_noalloc(hipStream_t stream, int32_t T, int32_t E, int32_t k, co
     int32_t* base = nullptr;
     if (scratch_on_current_device(&base) != hipSuccess) return MOE_EHIP;
     int32_t* flags = id_flags ? id_flags : base + NOALLOC_COUNT_INTS;
-    // the flags must start at zero (the histograms need no clearing: every chunk in use is rewritten in full)
-    if (launch_fill_i32(stream, flags, 2, 0) != hipSuccess) return MOE_EHIP;
+    int32_t* const ticket = base + NOALLOC_COUNT_INTS + 2;
+    // the flags must start at zero, and so must the ticket, whatever calls that overlapped have left in it (the histograms need no
+    // clearing: every chunk in use is rewritten in full)
+    hipLaunchKernelGGL(clear_flags, dim3(1), dim3(64), 0, stream, flags, ticket);
+    if (hipGetLastError() != hipSuccess) return MOE_EHIP;
     if (T == 0) return launch_fill_i32(stream, offsets, E + 1, 0) == hipSuccess ? MOE_OK : MOE_EHIP;
-    const permute_args a{stream, T, E, k, base, flags, true};
+    const permute_args a{stream, T, E, k, base, flags, ticket, true};
     int32_t* idx_copy = (topk_idx == logged_idx) ? nullptr : topk_idx;
     float* w_copy = (topk_w == logged_w) ? nullptr : topk_w;
     return launch_permute(a, logged_idx, idx_copy, logged_w, w_copy, offsets, perm, inv_perm, token_quant{}) == hipSuccess ? MOE_OK
