@@ -289,7 +289,8 @@ inline bool down_few(const moe_dims* D) {
 // expert) 42.2 / 39.4, 180 79.0 / 72.5, 204 102.5 / 94.4, 245 123.6 / 115.0, 315 130 / 124, 376 143 / 137, 533 272 / 263, 704 (256 x 6 of 64,
 // 4096 x 1408) 247 / 237, 1120 (112 experts of 13 rows, 1152 x 1280) 113 / 97, 1632 (16 x 8 of 256, 7168 x 2048) 687 / 682.  Up to eight rows per
 // expert the streaming kernel is the other one, whose blocks are half a unit, two to a CU: this one has to fill its rounds of units (as even
-// loads make them; skewed ones make fewer).  A single round, 190 units 49.4 / 45.1, but of a Zipf load 207 expected 50.7 / 53.6; more, by the share of
+// loads make them; skewed ones make fewer), and more than one: a single round gains with even loads, 190 units 49.4 / 45.1, and loses as much where
+// a log meets fewer experts than that, 207 expected of a Zipf load (63 x 1 of 69, 4480 x 640) 52.3 / 57.7.  By the share of
 // the last round's blocks that have a unit and those before it: 0.52 137 / 150, 0.66 165 / 179 and 63.4 / 65.8, 0.70 81.1 / 84.2, 0.74 94.8 / 98.9, 0.81
 // (Zipf) 245 / 258, 0.82 496 / 503; 0.91 687 / 682, 0.97 189 / 178, 0.98 105 / 97; in between either way, 0.78 104 / 100, 0.79 166 / 158.
 // Tiles are of up to 96 rows, so a concentrated log's weights pass more often than in tiles of 256 (GATE_UP_SKEW_UNITS).  Where its
@@ -299,7 +300,7 @@ inline bool down_few(const moe_dims* D) {
 // Down: level with the streaming kernel (0.97 to 1.1), so taken where that one is not: with more rows, or where a list would be needed to choose
 // (48..96 rows and more, us, big tiles / this, behind gate/up in persistent blocks: 62.3 / 58.2, 56.2 / 50.5, 56.6 / 52.4).
 constexpr int FLOW_ROWS = 96, FLOW_MAX_KB = 128;  // expert-sorted rows per tile; K blocks
-constexpr int64_t FLOW_UNITS = 140, FLOW_UNITS_FEW_ROWS = 170, FLOW_SKEW_UNITS = 256;
+constexpr int64_t FLOW_UNITS = 140, FLOW_SKEW_UNITS = 256;
 constexpr double FLOW_FILL_FEW_ROWS = 0.85;
 inline bool gate_up_flows(const moe_dims* D) {
     const int64_t N = (int64_t)D->T * D->k;
@@ -309,7 +310,7 @@ inline bool gate_up_flows(const moe_dims* D) {
     if ((D->T + FLOW_ROWS - 1) / FLOW_ROWS * D->k * (D->F / 128) > FLOW_SKEW_UNITS) return false;
     const double units = experts_met(D) * (D->F / 128);
     if (N > GATE_UP_STREAM_ROWS * D->E) return units >= FLOW_UNITS;
-    return units <= CUS ? units >= FLOW_UNITS_FEW_ROWS : units >= FLOW_FILL_FEW_ROWS * CUS * ceil(units / CUS);
+    return units > CUS && units >= FLOW_FILL_FEW_ROWS * CUS * ceil(units / CUS);
 }
 inline bool down_flows(const moe_dims* D) {
     return gate_up_flows(D) && ((int64_t)D->T * D->k > DOWN_STREAM_ROWS * D->E || down_form(D) != Down::STREAM);

@@ -59,3 +59,8 @@ def test_what_the_persistent_kernel_cannot_take_is_not_given_to_it(flows):
                   (96 * E + 1, 512, E, k, 512), (0, 512, E, k, 512))
     assert [a[0] for a in asked] == ["1", "0", "0", "1", "0", "0", "0"]
     assert all(a[0] == "1" or a[1] == "0" for a in asked)
+
+
+def test_few_rows_of_a_single_round_stay_with_the_streaming_kernel(flows):
+    """About one row per expert: a skewed log meets far fewer experts than an even one, which would leave a single round half empty."""
+    assert flows((63, 4480, 69, 1, 640), (256, 4096, 64, 6, 1408)) == ["00", "10"]
