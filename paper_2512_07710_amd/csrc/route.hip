@@ -266,6 +266,12 @@ __global__ __launch_bounds__(256, 1) void route_mfma_kernel(const uint16_t* __re
         for (int ts = 0; ts < TS; ++ts)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[s][ts][r] = 0.f;
+    // Two wait states have to lie between a vector-ALU write of a register and a matrix instruction that reads it.  The compiler, which pads its
+    // own so, cannot see into asm: the zeros are in their registers here, and RAW's products, whose weights the vector ALU makes, bring their own.
+#pragma unroll
+    for (int s = 0; s < NS; ++s)
+#pragma unroll
+        for (int ts = 0; ts < TS; ++ts) asm volatile("s_nop 1" : "+a"(acc[s][ts]) :: "memory");
 
     // Weight operands run KS - 1 K steps ahead of the matrix cores in a ring of KS register sets
     // (a K step is 16 columns; a staged activation chunk holds KS of them, so the ring slot of a
@@ -345,7 +351,7 @@ __global__ __launch_bounds__(256, 1) void route_mfma_kernel(const uint16_t* __re
                 for (int p = 0; p < 3; ++p)
 #pragma unroll
                     for (int s = 0; s < NS; ++s)
-                        asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0"
+                        asm volatile("s_nop 1\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %2, %0"
                                      : "+a"(acc[s][0]) : "v"(w[s][p]), "v"(b[ks & 1][0]) : "memory");
             } else {
 #pragma unroll

@@ -35,3 +35,35 @@ def test_either_side_of_the_line(gpu_lib, T, d, E, k, chunks):
             assert torch.equal(layer.topk_w.view(torch.int32), routed.view(torch.int32))
     finally:
         layer.close()
+
+
+@pytest.mark.parametrize("E,k", [(33, 16), (200, 16)])
+@pytest.mark.parametrize("chunks", [1, 2, 3, 4])
+def test_weights_split_by_the_waves_give_the_bits_of_the_planes(gpu_lib, chunks, E, k):
+    """1000 tokens take eight blocks a token tile.  With up to four chunks of 128 columns to a block the waves split the weights; five are
+    multiplied from planes.  The same columns of every block, in the second batch with zeros of x behind them, have to give the same partial
+    logits: the same ids and the same bits of their weights.  Every 7th column is of weights whose last planes are subnormal."""
+    T, blocks = 1000, 8
+    assert min(16, 256 // ((T + 31) // 32)) == blocks
+    g = torch.Generator(device="cuda").manual_seed(chunks + E)
+    W = torch.randn((E, blocks, chunks * 128), generator=g, device="cuda") * (blocks * chunks * 128) ** -0.5
+    x = torch.randn((T, blocks, chunks * 128), generator=g, device="cuda").to(torch.bfloat16)
+    W[:, :, ::5] *= 2.0 ** -9
+    W[:, :, 3::7] *= 2.0 ** -112
+    x[:, :, 3::7] *= 2.0 ** 112
+    pad = (5 - chunks) * 128
+    W_5 = torch.cat([W, torch.randn((E, blocks, pad), generator=g, device="cuda")], dim=2).reshape(E, -1).contiguous()
+    x_5 = torch.cat([x, torch.zeros((T, blocks, pad), dtype=torch.bfloat16, device="cuda")], dim=2).reshape(T, -1).contiguous()
+    raw, planes = gpu_lib.MoELayer(T, blocks * chunks * 128, E, k, 128), gpu_lib.MoELayer(T, blocks * 640, E, k, 128)
+    try:
+        for bias in (None, torch.randn((E,), generator=g, device="cuda")):
+            raw.route(x.reshape(T, -1), W.reshape(E, -1), bias)
+            planes.route(x_5, W_5, bias)
+            assert torch.equal(raw.topk_idx, planes.topk_idx)
+            assert torch.equal(raw.topk_w.view(torch.int32), planes.topk_w.view(torch.int32))
+        logits = x.reshape(T, -1).double() @ W.reshape(E, -1).double().T.contiguous()
+        w = torch.softmax(logits.gather(1, raw.topk_idx.long()), dim=1)
+        assert ((raw.topk_w.double() - w).abs() <= 1e-6 + 1e-5 * w).all()
+    finally:
+        raw.close()
+        planes.close()
