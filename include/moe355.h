@@ -15,7 +15,9 @@
  *   - Every data pointer is a DEVICE pointer owned by the caller.  The library
  *     neither frees nor keeps it after the call returns.
  *   - All work is enqueued on the HIP stream given to moe_create(); calls return
- *     without synchronising.  A context must not be used from two threads at once.
+ *     without synchronising.  A context must not be used from two threads at once, nor may its calls run
+ *     at the same time (a captured graph of them beside others): they share its workspace, and what such calls
+ *     leave, offsets and perm among it, is undefined.  Calls behind them are not affected.
  *   - Notation: T tokens, d hidden size, E experts, k experts per token, F expert
  *     FFN width, N = T*k assignments.  d and F must be multiples of 128.
  *   - bf16 values are passed as uint16_t bit patterns, e4m3 codes as uint8_t

@@ -11,7 +11,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB_PATH = os.path.join(HERE, "libmoe355.so")
 SOURCES = ("moe_api.hip", "route.hip", "permute.hip", "quantize.hip", "wquant.hip", "ffn.hip", "ffn_stream.hip", "ffn_few.hip", "ffn_flow.hip", "combine.hip", "balance.hip", "probe.hip")
-HEADERS = ("moe_internal.hpp", "lanes.hpp", "e4m3.hpp", "ffn_common.hpp", "ffn_rows.hpp", "ffn_rules.hpp", "permute_block.hpp", "quantize_rows.hpp")
+HEADERS = ("moe_internal.hpp", "lanes.hpp", "e4m3.hpp", "ffn_common.hpp", "ffn_rows.hpp", "ffn_rules.hpp", "permute_block.hpp", "quantize_rows.hpp", "ticket.hpp")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 # packed-fp32 code generation is switched off for every device compile
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Xclang", "-target-feature", "-Xclang",

@@ -223,7 +223,7 @@ __global__ __launch_bounds__(WK * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
         put2(dst, swiglu(gt[0], up[0]), swiglu(gt[1], up[1]));
         put2(dst + 2, swiglu(gt[2], up[2]), swiglu(gt[3], up[3]));
     }
-    if (!last_of_unit<S>(g.tickets, unit, s_ticket, tid)) return;
+    if (!last_block(g.tickets + unit, S, s_ticket)) return;
     for (int r = tid >> 4; r < wk.nrows; r += NTHR / 16) {     // (the 16 lanes of a row share r)
         float h[8];
 #pragma unroll

@@ -2,6 +2,7 @@
 #pragma once
 #include "ffn_common.hpp"
 #include "ffn_rules.hpp"
+#include "ticket.hpp"
 
 namespace moe355 {
 
@@ -36,18 +37,7 @@ struct StreamArgs {
 };
 
 // ---- hidden rows of a unit whose 128 features are spread over S blocks
-// Every wave's part of h has been put; is this the last of the unit's blocks to arrive?  (Then all of h can be read with get2.)
-template <int S>
-__device__ inline bool last_of_unit(int32_t* tickets, int unit, int32_t& s_ticket, int tid) {
-    // every wave's stores have reached the common point before the block takes its ticket
-    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
-    __syncthreads();
-    if (tid == 0) s_ticket = __hip_atomic_fetch_add(tickets + unit, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __syncthreads();
-    if (s_ticket != S - 1) return false;
-    if (tid == 0) __hip_atomic_store(tickets + unit, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // for the next launch
-    return true;
-}
+// Every wave's part of h has been put; the last of the unit's blocks (last_block) can read all of it with get2.
 // Sixteen lanes own row p of feature tile ft, lane `sub` features 8*sub .. 8*sub+7 in h: their scale and codes.
 __device__ inline void put_hidden_row(const StreamArgs& g, int p, int ft, int sub, const float (&h)[8]) {
     float am = 0.f;

@@ -245,7 +245,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
             const int r = i / (HW / 2), c = i % (HW / 2) * 2;
             put2(rows + (size_t)r * g.NOUT + sub_f + c, s_h[r * HP + c], s_h[r * HP + c + 1]);
         }
-        if (!last_of_unit<S>(g.tickets, unit, *s_ticket, tid)) return;
+        if (!last_block(g.tickets + unit, S, *s_ticket)) return;
     }
     // the unit's last block: 16 lanes per row, 8 features each
     for (int r = tid >> 4; r < wk.nrows; r += NW * 4) {        // (the 16 lanes of a row share r)

@@ -13,6 +13,7 @@
 // The result is unique (stable), so it can be compared bit for bit.  Batches of at most one_block_max_n
 // assignments take one fused launch instead (permute_one_block).
 #include "permute_block.hpp"
+#include "ticket.hpp"
 #include "quantize_rows.hpp"
 
 #include <mutex>
@@ -92,7 +93,7 @@ __device__ inline void scan_chunks(int32_t* __restrict__ chunk_counts, int n_chu
 // count, kept per wave in LDS (read by the whole set, then written by one lane: LDS operations of a wave
 // execute in order).  A second pass turns the per-wave counts into the chunk histogram and the per-wave
 // bases.  Ids outside [0,E) are ranked among themselves; that rank is never used.
-// The last block to arrive (an atomic ticket, returned to zero) scans the histograms; nobody waits.  In a launch of its own the scan came behind the
+// The last block to arrive (ticket.hpp) scans the histograms; nobody waits.  In a launch of its own the scan came behind the
 // tokens' quantisation that rides in this one (us, two launches / this: 8000 assignments of 64 experts 7.4 + 2.7 / 9.0, 12000 of 16 6.6 + 4.6 /
 // 8.8, 262144 of 256 11.6 + 20.2 / 28.4; layers of 1000 x 8 of 64, 1024 x 512 61.4 / 60.2, 6000 x 2 of 16, 3072 x 2048 337.0 / 334.8, 4096 x 8 of 128, 5120 x
 // 1536 1093 / 1091).
@@ -155,14 +156,8 @@ __global__ __launch_bounds__(256) void chunk_hist_rank(const int32_t* __restrict
         const int i = base + wave * PER_WAVE + st * 64 + lane;
         if (i < N) rank_out[i] = my_rank[st] + s_cnt[wave][my_id[st] & (MAX_E - 1)];
     }
-    // the histogram has reached the point where all XCDs see it before the block takes its ticket
     __shared__ int32_t s_ticket;
-    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
-    __syncthreads();
-    if (tid == 0) s_ticket = __hip_atomic_fetch_add(ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __syncthreads();
-    if (s_ticket != n_chunks - 1) return;
-    if (tid == 0) __hip_atomic_store(ticket, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // for the next launch
+    if (!last_block(ticket, n_chunks, s_ticket)) return;
     scan_chunks(chunk_counts, n_chunks, E, offsets);
 }
 
@@ -189,8 +184,10 @@ __global__ __launch_bounds__(256) void scatter(const int32_t* __restrict__ ids, 
     }
     const int chunk = i / PERM_CHUNK;
     const int pos = offsets[e] + chunk_prefix[(size_t)chunk * E + e] + inv_perm[i];   // inv_perm holds the rank
-    inv_perm[i] = pos;
-    perm[pos] = i;
+    // (within the rows unless calls overlapped that must not: then at least nothing outside is written, or read by the combine)
+    const bool inside = (uint32_t)pos < (uint32_t)N;
+    inv_perm[i] = inside ? pos : -1;
+    if (inside) perm[pos] = i;
 }
 
 constexpr int ONE_BLOCK_MAX_N = ONE_BLOCK_WAVES * ONE_BLOCK_MAX_STEPS * 64;
@@ -217,7 +214,8 @@ __global__ void fill_i32(int32_t* __restrict__ p, int n, int32_t v) {
     if (i < n) p[i] = v;
 }
 
-__global__ void clear_flags(int32_t* __restrict__ flags, int32_t* __restrict__ ticket) {
+__global__ void clear_flags(int32_t* __restrict__ flags, int32_t* __restrict__ ticket, int32_t* __restrict__ offsets, int E) {
+    if ((int)threadIdx.x <= E) offsets[threadIdx.x] = 0;
     if (threadIdx.x < 2) flags[threadIdx.x] = 0;
     if (threadIdx.x == 2) *ticket = 0;
 }
@@ -269,11 +267,12 @@ int route_replay_noalloc(hipStream_t stream, int32_t T, int32_t E, int32_t k, co
     if (scratch_on_current_device(&base) != hipSuccess) return MOE_EHIP;
     int32_t* flags = id_flags ? id_flags : base + NOALLOC_COUNT_INTS;
     int32_t* const ticket = base + NOALLOC_COUNT_INTS + 2;
-    // the flags must start at zero, and so must the ticket, whatever calls that overlapped have left in it (the histograms need no
+    // the flags must start at zero, and so must the ticket, whatever calls that overlapped have left in it (their counts differ from
+    // batch to batch); offsets, so that such a call leaves experts without rows and not what was there before (the histograms need no
     // clearing: every chunk in use is rewritten in full)
-    hipLaunchKernelGGL(clear_flags, dim3(1), dim3(64), 0, stream, flags, ticket);
+    hipLaunchKernelGGL(clear_flags, dim3(1), dim3((MAX_E + 64) / 64 * 64), 0, stream, flags, ticket, offsets, E);
     if (hipGetLastError() != hipSuccess) return MOE_EHIP;
-    if (T == 0) return launch_fill_i32(stream, offsets, E + 1, 0) == hipSuccess ? MOE_OK : MOE_EHIP;
+    if (T == 0) return MOE_OK;
     const permute_args a{stream, T, E, k, base, flags, ticket, true};
     int32_t* idx_copy = (topk_idx == logged_idx) ? nullptr : topk_idx;
     float* w_copy = (topk_w == logged_w) ? nullptr : topk_w;

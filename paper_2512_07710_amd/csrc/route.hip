@@ -20,6 +20,7 @@
 // the same selection with wave-wide reductions.  Up to 32 tokens the partial logits come from the vector ALU (route_rows_kernel).
 #include "permute_block.hpp"
 #include "quantize_rows.hpp"
+#include "ticket.hpp"
 
 #include <type_traits>
 
@@ -726,7 +727,7 @@ __global__ __launch_bounds__(ONE_BLOCK_WAVES * 64) void route_finish_permute(
 }
 
 // All of it in one launch for at most a token to each wave of a block: the scores, as in route_rows_kernel, each put where all XCDs see
-// it; the last of the scoring blocks to arrive (an atomic ticket, returned to zero) selects and permutes, and nobody waits.  The tokens'
+// it; the last of the scoring blocks to arrive (ticket.hpp) selects and permutes, and nobody waits.  The tokens'
 // quantisation may come along in further blocks.  Bound by its chain of memory round trips.  One token x 64 experts x 4096, us: the two launches
 // before 3.1 + 7.1, this 8.8; one token x 8 experts x 1024 2.7 + 6.0 and 7.2.  Beyond TINY_BLOCKS scoring blocks their tickets come one behind another
 // (layers, us, two launches / this: 2 blocks 25.8 / 21.8, 48 37.8 / 37.3, 64 36.1 / 35.0, 128 63.5 / 63.5, 448 35.7 / 38.8 and 101.3 / 104.9).
@@ -750,13 +751,7 @@ __global__ __launch_bounds__(TINY_WAVES * 64) void route_tiny(
         score_rows(x, W, T, T_pad, d, E_pad, e, blockIdx.x / groups, lane, [&](size_t at, float s) {
             __hip_atomic_store(partial + at, s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         });
-    // every wave's scores have reached the common point before the block takes its ticket
-    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
-    __syncthreads();
-    if (tid == 0) s_ticket = __hip_atomic_fetch_add(ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __syncthreads();
-    if (s_ticket != scoring - 1) return;
-    if (tid == 0) __hip_atomic_store(ticket, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // for the next launch
+    if (!last_block(ticket, scoring, s_ticket)) return;
     if (wave < T) {
         const Choice c = finish_token<IDS, true>(partial, slices, T_pad, E_pad, bias, logged_idx, wave, lane, E, k);
         if (lane < k) {
