@@ -42,6 +42,16 @@ constexpr int ROUTE_MAX_SPLITS = 16;
 // x 256 x 7168 23.1 / 20.4; 7 chunks, 1000 x 256 x 7168 32.1 / 34.8, 20 chunks, 4096 x 128 x 5120 40.8 / 57.6, also with the splitting put between the
 // dependent products).
 constexpr int ROUTE_RAW_CHUNKS = 4;
+// Every token tile splits all weights again.  With more than 128 experts, two sub-tiles a wave, that is the slower form once chunks x tiles x experts
+// exceed ROUTE_RAW_WORK (whole router calls, us, planes / this, weights in the caches and cleared caches, by chunks x tiles; 256 experts: 4 x 17, 7168 columns
+// 41.6 / 36.8 and 48.4 / 43.9, 2 x 32, 2048 34.0 / 33.1 and 37.9 / 38.1, 3 x 25, 3584 36.0 / 35.1 and 41.3 / 41.5; 3 x 32, 2560 35.3 / 36.6 and 39.7 / 42.6,
+// 4 x 47, 2048 39.8 / 42.4 and 44.8 / 48.6, 4 x 94, 1024 40.7 / 44.5 and 45.5 / 50.2; 192: 4 x 32, 4096 35.9 / 35.6 and 42.2 / 41.8, 4 x 64, 2048 37.6 / 39.3
+// and 42.7 / 45.4).  Up to 128 experts it stays ahead or level: 4 x 44, 2048 31.5 / 29.9 and 35.8 / 35.2, 4 x 94, 1024 32.7 / 33.0 and
+// 37.7 / 38.5, 4 x 128, 1024 35.2 / 33.2 and 40.0 / 39.4.
+constexpr int ROUTE_RAW_WORK = 20480;
+inline bool route_splits_weights(int E, int tiles, int chunks) {
+    return chunks <= ROUTE_RAW_CHUNKS && (E <= 128 || chunks * tiles * E <= ROUTE_RAW_WORK);
+}
 // Batches of at most ROUTE_ROWS_MAX_T tokens score on the vector ALU instead (us for the whole layer, that / matrix cores: one
 // token 44 / 52, 8 x 256 experts 138 / 157, 16 717 / 738 on the widest layer, 32 level, 64 120 / 114, 128 141 / 119).
 constexpr int ROUTE_ROWS_MAX_T = 32;
@@ -196,7 +206,7 @@ __device__ inline void wait_vm(int n) {
 // SPLIT = true (small batches, where one block per token tile would leave most compute units idle): block
 // (x, y) runs only chunks [y*cps, (y+1)*cps) of the K loop and writes its partial logits to
 // partial[y][token][expert]; route_finish_kernel adds the partials up and does the selection.
-// RAW: the weights come as fp32 rows and every wave splits them into the planes itself (ROUTE_RAW_CHUNKS).
+// RAW: the weights come as fp32 rows and every wave splits them into the planes itself (route_splits_weights).
 template <int NS, int TS, int KS, bool IDS, bool SPLIT = false, bool RAW = false>
 __global__ __launch_bounds__(256, 1) void route_mfma_kernel(const uint16_t* __restrict__ x,
                                                             const void* __restrict__ weights,
@@ -850,7 +860,7 @@ hipError_t launch_route(moe_ctx* c, const uint16_t* x, const float* W_r, const f
         splits = (nchunks + cps - 1) / cps;                    // no empty block
         if (splits >= 2) {
             const dim3 grid(tiles, splits);
-            const bool raw = cps <= ROUTE_RAW_CHUNKS;
+            const bool raw = route_splits_weights(D.E, tiles, cps);
             if (!raw) split_weights_first();
             auto launch = [&](auto kernel) {
                 hipLaunchKernelGGL(kernel, grid, dim3(256), 0, c->stream, x, raw ? (const void*)W_r : (const void*)c->router_planes,
