@@ -5,6 +5,7 @@ import subprocess
 import numpy as np
 import pytest
 
+import test_gpu_dispatch as dispatch
 from paper_2512_07710_amd.build import CSRC, HIPCC, ROOT
 
 EDGE_ROWS = np.array([1, 16, 17, 32, 33, 48, 49, 64, 65, 80, 81, 96, 97, 0, 5, 200, 15, 2, 31, 47, 63, 79, 95, 100, 8, 129])
@@ -50,6 +51,11 @@ def test_the_layers_of_the_gpu_test_flow_and_their_references_do_not(flows):
         assert here[0] == "1" and big == "00", (d, E, k, F)
         met.add(here)
     assert met == {"10", "11"}
+
+
+def test_the_graph_tests_layers_are_what_their_names_say(flows):
+    assert dict(zip(dispatch.GRAPH_LAYERS, flows(*dispatch.GRAPH_LAYERS.values()))) == {
+        "streaming": "00", "chosen-on-device": "00", "persistent-blocks": "10", "persistent-blocks-down": "11"}
 
 
 def test_what_the_persistent_kernel_cannot_take_is_not_given_to_it(flows):

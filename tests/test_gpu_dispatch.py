@@ -158,7 +158,11 @@ def test_router_of_one_chunk_either_side_of_its_rule(gpu_lib, T, E, k):
 
 
 # --------------------------------------------------------------------------- graph replay
-@pytest.mark.parametrize("T,d,E,k,F", [(24, 640, 16, 2, 384), (520, 2048, 90, 8, 128)], ids=["streaming", "chosen-on-device"])
+GRAPH_LAYERS = {"streaming": (24, 640, 16, 2, 384), "chosen-on-device": (520, 2048, 90, 8, 128), "persistent-blocks": (400, 512, 60, 2, 512),
+                "persistent-blocks-down": (1000, 512, 36, 2, 640)}
+
+
+@pytest.mark.parametrize("T,d,E,k,F", GRAPH_LAYERS.values(), ids=GRAPH_LAYERS)
 def test_graph_replay_with_other_logs_and_activations(gpu_lib, T, d, E, k, F):
     """A replayed layer recorded into a graph; between replays its inputs change in place, from an even log to one that sends
     every token to the same experts and back, with eager work in between.  Every replay equals the eager result."""

@@ -429,10 +429,11 @@ def test_permutation_at_block_edges(gpu_lib, T, k):
         layer.close()
 
 
-@pytest.mark.parametrize("T,k", [(1366, 3), (4097, 1), (1024, 8), (8193, 1), (512, 8), (513, 8), (256, 16), (257, 16)])
+@pytest.mark.parametrize("T,k", [(1366, 3), (4097, 1), (1024, 8), (8193, 1), (512, 8), (513, 8), (256, 16), (257, 16),
+                                 (640, 8), (641, 8), (320, 16), (321, 16)])
 def test_permutation_either_side_of_the_one_block_form(gpu_lib, T, k):
     """Assignment counts around the sizes up to which one block permutes a batch: the router's own ids (no search for repeats:
-    up to 8192) and logged ids (up to 4096, with one slot a token up to 8192), the latter also with an id repeated in the
+    up to 8192) and logged ids (up to 5120, with one slot a token up to 8192), the latter also with an id repeated in the
     last token."""
     from workloads import make_inputs
     from test_gpu_parity import _check_permutation

@@ -57,3 +57,48 @@ def test_persistent_blocks_have_the_bits_of_the_big_tiles(gpu_lib, name):
     finally:
         big.close()
         layer.close()
+
+
+def test_values_and_ids_that_are_not_valid(gpu_lib):
+    """Slots of ids outside [0, E) have no row; activations that are not finite, weight codes of NaN and scales of infinity reach the rows
+    that multiply them and no others: hidden codes, scales and outputs are those of the big tiles, a NaN for a NaN."""
+    d, E, k, F, scale = LAYERS["two-a-token"]
+    g = np.random.default_rng(5)
+    extra = 97 * (E + k)
+    ids, T = _log(np.resize(EDGE_ROWS, E) * scale // 4, k, extra, g)
+    assert T > 40
+    for n, bad in enumerate((-1, E + k, 1 << 20, -(1 << 31))):
+        ids[7 * n + 3, n % 2] = bad
+    ids[30] = -1                                               # a token without any row
+    gen = torch.Generator(device="cuda").manual_seed(d)
+    code = lambda *s: (torch.randn(s, generator=gen, device="cuda") * 60).to(torch.float8_e4m3fn).view(torch.uint8)
+    scales = lambda *s: torch.rand(s, generator=gen, device="cuda") * 2e-4 + 1e-4
+    w = {"W1q": code(E + k, F, d), "W3q": code(E + k, F, d), "W2q": code(E + k, d, F), "s1": scales(E + k, F // 128, d // 128),
+         "s3": scales(E + k, F // 128, d // 128), "s2": scales(E + k, d // 128, F // 128)}
+    w["W1q"][3, 5, 7], w["W3q"][20, 130, 0], w["W2q"][6, 200, 300] = 0x7F, 0xFF, 0x7F
+    w["s1"][9, 1, 2], w["s2"][12, 0, 3] = float("inf"), float("nan")
+    x = torch.randn((T + extra, d), generator=gen, device="cuda").to(torch.bfloat16)
+    x[11, 130], x[12, 0], x[13, 700], x[14] = float("nan"), float("inf"), -float("inf"), float("nan")
+    gates = torch.rand((T + extra, k), generator=gen, device="cuda")
+    ids = torch.from_numpy(ids).cuda()
+    big, layer = gpu_lib.MoELayer(T + extra, d, E + k, k, F), gpu_lib.MoELayer(T, d, E, k, F)
+    same = lambda a, b: torch.equal(a.isnan(), b.isnan()) and torch.equal(a.nan_to_num(0.0), b.nan_to_num(0.0))
+    try:
+        big.y_perm.zero_()
+        y_w = big.forward_replay(x, ids, gates, w)[:T].clone()
+        hq_w, hs_w = big.hidden()
+        N = int(big.offsets[E])
+        assert N == T * k - 6 and gpu_lib.moe_check_ids(big.ctx) != 0
+        for fused in (True, False):
+            layer.y_perm.zero_()
+            y = layer.forward_replay(x[:T].contiguous(), ids[:T].contiguous(), gates[:T].contiguous(), {n: v[:E].contiguous() for n, v in w.items()}, fused=fused)
+            assert gpu_lib.moe_check_ids(layer.ctx) != 0
+            hq, hs = layer.hidden()
+            assert torch.equal(layer.offsets, big.offsets[:E + 1])
+            assert same(hs[:, :N], hs_w[:, :N]) and torch.equal(hq[:N], hq_w[:N]), fused
+            assert same(layer.y_perm[:N], big.y_perm[:N]) and not layer.y_perm[N:].any(), fused
+            assert same(y, y_w), fused
+        assert y_w[30].eq(0).all() and 0 < int(y_w.isnan().any(dim=1).sum()) < T // 2
+    finally:
+        big.close()
+        layer.close()

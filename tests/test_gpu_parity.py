@@ -298,7 +298,7 @@ def test_replay_rejects_nothing_but_flags_bad_ids(gpu_lib):
 
 @pytest.mark.parametrize("T,E,k", [(5000, 64, 6), (300, 200, 16)])
 def test_replay_duplicate_check_at_several_chunks(gpu_lib, T, E, k):
-    """The duplicate check in the three-kernel permutation (more than 2048 assignments) and in the single-block
+    """The duplicate check in the two-kernel permutation (more than 5120 assignments) and in the single-block
     one: a clean log passes, one repeated id anywhere in it is found."""
     rng = np.random.default_rng(T)
     good = np.stack([rng.permutation(E)[:k] for _ in range(T)]).astype(np.int32)

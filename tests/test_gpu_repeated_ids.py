@@ -1,5 +1,5 @@
 """GPU: repeated ids inside a token are found wherever the token lies among the 64 assignments that a wave of the one-block permutation looks at
-together, in the three launches as well, and nothing else is reported."""
+together, in the two launches as well, and nothing else is reported."""
 import pytest
 import torch
 
@@ -25,7 +25,10 @@ def test_repeats(gpu_lib, T, E, k):
                 layer.route_replay(x, bad, w)
                 assert gpu_lib.moe_check_ids(layer.ctx) != 0, (t, first, again)
                 flat = bad.flatten().long()
-                assert torch.equal(layer.perm.long(), torch.sort(flat, stable=True).indices)
+                order = torch.sort(flat, stable=True).indices
+                assert torch.equal(layer.perm.long(), order)
+                assert torch.equal(layer.inv_perm.long()[order], torch.arange(T * k, device="cuda"))
+                assert torch.equal(layer.topk_idx, bad) and torch.equal(layer.topk_w, w)
         layer.route_replay(x, ids, w)
         assert gpu_lib.moe_check_ids(layer.ctx) == 0 and torch.equal(layer.offsets, offsets)
     finally:

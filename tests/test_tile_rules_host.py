@@ -46,8 +46,8 @@ int main() {
             int N = 0;
             for (int& n : c) { if (scanf("%d", &n) != 1) return 1; N += n; }
             D.T = N / D.k;
-            printf("%s %s\n", gate_up_few(&D) ? "few" : gate_up_streams(&D) ? "stream" : "big",
-                   down_few(&D) ? "few" : down_form(&D) == Down::STREAM ? "stream" : down_form(&D) == Down::BIG ? "big" : "either");
+            printf("%s %s\n", gate_up_flows(&D) ? "flow" : gate_up_few(&D) ? "few" : gate_up_streams(&D) ? "stream" : "big",
+                   down_flows(&D) ? "flow" : down_few(&D) ? "few" : down_form(&D) == Down::STREAM ? "stream" : down_form(&D) == Down::BIG ? "big" : "either");
             for (int list = 0; list < 2; ++list) {
                 const ListShape s = list ? down_shape(&D) : gate_up_shape(&D);
                 long units;
