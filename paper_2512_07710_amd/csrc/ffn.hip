@@ -491,7 +491,8 @@ __device__ __forceinline__ void k_loop(const Tile& t, const Feed& f, v4f (&acc)[
 // expert-ordered copy of the codes is never materialised.  The scales act_s
 // [K/128][n_rows] are in sorted order in both cases (they are 1/128 of the data; a lane-scattered
 // scale read per K step would cost more than it saves).
-// PAST: y_perm goes past the caches (down_goes_past, linear_goes_past).  An instance of its own: with both forms in one, the layers of the other took 0.3 % longer.
+// PAST: y_perm goes past the caches (down_goes_past, linear_goes_past).  An instance of its own: with both forms in one, the layers of the other took
+// 0.3 % longer.
 template <bool GATED, bool GATHER, bool LINEAR, bool PAST = false>
 __global__ __launch_bounds__(NTHREADS, 1) void ffn_gemm(const uint8_t* __restrict__ act,
                                                         const float* __restrict__ act_s, int n_rows,
@@ -605,8 +606,8 @@ __global__ __launch_bounds__(NTHREADS, 1) void ffn_gemm(const uint8_t* __restric
 
     copy_x(feed, 0, 0);
     if (narrow) {
-        // ---- NARROW tile: at most 64 rows, or 96 that are all of their expert's.  In the layout above a wave has one or two groups of tokens to multiply, the two waves of
-        //      a SIMD often not the same, behind a schedule made for eight groups.  Here
+        // ---- NARROW tile: at most 64 rows, or 96 that are all of their expert's.  In the layout above a wave has one or two groups of tokens
+        //      to multiply, the two waves of a SIMD often not the same, behind a schedule made for eight groups.  Here
         //      wave w multiplies the 32 staged weight rows it copies itself by the tile's two or three groups of 32 token
         //      columns (two matrix instructions each per K block), so the matrix work is spread over every wave
         //      and the tile runs at the speed its weight tile streams in.  Same rings, same copy order, same
@@ -1009,9 +1010,9 @@ hipError_t launch_expert_ffn(moe_ctx* c, const uint8_t* xq, const float* xs, con
     }
     if (down != Down::STREAM && !flow2) {
         auto launch = [&](auto kernel) {
-            hipLaunchKernelGGL(kernel, dim3(list_blocks((int)down_big_units(&D))), dim3(NTHREADS), SMEM_BYTES, c->stream, c->hq, c->hs, N, (const int32_t*)nullptr, 1, 1,
-                               work2, queues + 1, rests + NXCD, W2, (const uint8_t*)nullptr, s2, (const float*)nullptr, D.F, D.d, (uint8_t*)nullptr,
-                               (float*)nullptr, y_perm);
+            hipLaunchKernelGGL(kernel, dim3(list_blocks((int)down_big_units(&D))), dim3(NTHREADS), SMEM_BYTES, c->stream, c->hq, c->hs, N,
+                               (const int32_t*)nullptr, 1, 1, work2, queues + 1, rests + NXCD, W2, (const uint8_t*)nullptr, s2,
+                               (const float*)nullptr, D.F, D.d, (uint8_t*)nullptr, (float*)nullptr, y_perm);
         };
         if (down_goes_past(&D)) launch(ffn_gemm<false, false, false, true>);
         else launch(ffn_gemm<false, false, false>);

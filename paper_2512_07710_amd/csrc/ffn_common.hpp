@@ -1,4 +1,4 @@
-// What the two grouped FP8 GEMMs share: the big-tile kernel (ffn.hip) and the weight-streaming one (ffn_stream.hip).
+// What the block-scaled FP8 GEMMs share: the big tiles (ffn.hip) and the weight-streaming kernels (ffn_stream.hip, ffn_flow.hip, ffn_few.hip).
 #pragma once
 #include "lanes.hpp"
 #include "moe_internal.hpp"

@@ -17,10 +17,10 @@
 // The K loop has to be a straight line.  With C++ conditions around the copies (which weights go past the caches, which waves bring
 // rows and which scales) the same schedule took 600 instead of 440 us for 16 tokens x 8 of 256 experts, 7168 x 2048: at 1.2 us for
 // a stage of 32 KB whatever stands between a barrier and the copies behind it is time without requests.
-// Bound by the weights: 16 x 8 of 256, 7168 x 2048 6.8 TB/s, 256 x 6 of 64, 4096 x 1408 6.5 TB/s.  Gate/up, us, big tiles or
-// streaming kernel (with the launch that makes lists) / here: 256 tokens x 6 of 64, 4096 x 1408 124 / 114, 300 x 5 of 112, 1152 x 1280
-// 71 / 55, 335 x 2 of 40, 3072 x 512 32.2 / 27.4, 16 x 8 of 256, 7168 x 2048 445 / 442; whole layers of random shapes in ffn_rules.hpp.  Four stages with tiles of 64 or 32 rows, row lookups behind the first weights, and waits that leave a
-// unit's stores outstanding: level.
+// Bound by the weights: 16 x 8 of 256, 7168 x 2048 6.8 TB/s, 256 x 6 of 64, 4096 x 1408 6.5 TB/s.  Gate/up, us, big tiles or streaming kernel (with
+// the launch that makes lists) / here: 256 tokens x 6 of 64, 4096 x 1408 124 / 114, 300 x 5 of 112, 1152 x 1280 71 / 55, 335 x 2 of 40, 3072 x 512
+// 32.2 / 27.4, 16 x 8 of 256, 7168 x 2048 445 / 442; whole layers of random shapes in ffn_rules.hpp.  Four stages with tiles of 64 or 32 rows, row
+// lookups behind the first weights, and waits that leave a unit's stores outstanding: level.
 #include "ffn_rows.hpp"
 #include "ffn_rules.hpp"
 

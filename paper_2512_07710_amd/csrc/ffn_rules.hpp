@@ -49,8 +49,8 @@ __host__ __device__ inline void split_rows(int rows, int nt, int i, Work& w) {
 // ------------------------------------------------------------------ tile heights
 // 256 rows are the most a tile can have, but not always the best: units come in rounds of one a CU, and a round that is a
 // quarter full takes nearly as long as a full one.  16 experts of 750 rows x 3072 x 2048 make 3.25 rounds of tiles of up to 256 rows,
-// 178 us, and 4 full ones of shorter tiles, 160.  The cost of `units` units in K steps of a tile of eight groups of 32 rows (a step costs 0.2 + 0.1 n at
-// n groups, what lies between two tiles 4 steps, a started round 0.7 of a full one) was fitted to 27 layers of 130 to 1100
+// 178 us, and 4 full ones of shorter tiles, 160.  The cost of `units` units in K steps of a tile of eight groups of 32 rows (a step costs
+// 0.2 + 0.1 n at n groups, what lies between two tiles 4 steps, a started round 0.7 of a full one) was fitted to 27 layers of 130 to 1100
 // rows per expert, both projections, heights 96 to 256: the height it picks is 0.2 % above the best of them on average, always
 // taking 256 5.7 %.
 constexpr int CUS = 256, NXCD = 8;
@@ -284,15 +284,15 @@ inline bool gate_up_few(const moe_dims* D) {
 inline bool down_few(const moe_dims* D) {
     return D->T <= FEW_ROWS && down_form(D) == Down::STREAM && (D->F >= 1280 || experts_met(D) * (D->d / 32) <= 1400);
 }
-// Persistent blocks (ffn_flow.hip), one to a CU: gate/up projections bound by their weights, with enough units to keep most CUs busy.
-// Whole layers, us, big tiles or streaming / this, by units of 128 features: 108..120 units 55 / 68, 41 / 46, 39 / 43; 155 (34 rows per
-// expert) 42.2 / 39.4, 180 79.0 / 72.5, 204 102.5 / 94.4, 245 123.6 / 115.0, 315 130 / 124, 376 143 / 137, 533 272 / 263, 704 (256 x 6 of 64,
-// 4096 x 1408) 247 / 237, 1120 (112 experts of 13 rows, 1152 x 1280) 113 / 97, 1632 (16 x 8 of 256, 7168 x 2048) 687 / 682.  Up to eight rows per
-// expert the streaming kernel is the other one, whose blocks are half a unit, two to a CU: this one has to fill its rounds of units (as even
-// loads make them; skewed ones make fewer), and more than one: a single round gains with even loads, 190 units 49.4 / 45.1, and loses as much where
-// a log meets fewer experts than that, 207 expected of a Zipf load (63 x 1 of 69, 4480 x 640) 52.3 / 57.7.  By the share of
-// the last round's blocks that have a unit and those before it: 0.52 137 / 150, 0.66 165 / 179 and 63.4 / 65.8, 0.70 81.1 / 84.2, 0.74 94.8 / 98.9, 0.81
-// (Zipf) 245 / 258, 0.82 496 / 503; 0.91 687 / 682, 0.97 189 / 178, 0.98 105 / 97; in between either way, 0.78 104 / 100, 0.79 166 / 158.
+// Persistent blocks (ffn_flow.hip), one to a CU: gate/up projections bound by their weights, with enough units to keep most CUs busy.  Whole layers,
+// us, big tiles or streaming / this, by units of 128 features: 108..120 units 55 / 68, 41 / 46, 39 / 43; 155 (34 rows per expert) 42.2 / 39.4, 180
+// 79.0 / 72.5, 204 102.5 / 94.4, 245 123.6 / 115.0, 315 130 / 124, 376 143 / 137, 533 272 / 263, 704 (256 x 6 of 64, 4096 x 1408) 247 / 237, 1120
+// (112 experts of 13 rows, 1152 x 1280) 113 / 97, 1632 (16 x 8 of 256, 7168 x 2048) 687 / 682.  Up to eight rows per expert the streaming kernel is
+// the other one, whose blocks are half a unit, two to a CU: this one has to fill its rounds of units (as even loads make them; skewed ones make
+// fewer), and more than one: a single round gains with even loads, 190 units 49.4 / 45.1, and loses as much where a log meets fewer experts than
+// that, 207 expected of a Zipf load (63 x 1 of 69, 4480 x 640) 52.3 / 57.7.  By the share of the last round's blocks that have a unit and those
+// before it: 0.52 137 / 150, 0.66 165 / 179 and 63.4 / 65.8, 0.70 81.1 / 84.2, 0.74 94.8 / 98.9, 0.81 (Zipf) 245 / 258, 0.82 496 / 503; 0.91 687 /
+// 682, 0.97 189 / 178, 0.98 105 / 97; in between either way, 0.78 104 / 100, 0.79 166 / 158.
 // Tiles are of up to 96 rows, so a concentrated log's weights pass more often than in tiles of 256 (GATE_UP_SKEW_UNITS).  Where its
 // units make one round of blocks at most this is still the faster form, 210 units 86.6 / 70.9, 200 109.6 / 97.9, 208 75.4 / 62.4 and 45.0 /
 // 35.8; beyond one round not: 294 117.5 / 142.5, 315 64.9 / 73.9, 396 102.8 / 110.5, 672 127.6 / 155.9, and neither is it with Zipf loads of
@@ -320,12 +320,19 @@ inline bool linear_streams(int32_t rows, int32_t NOUT) {
 }
 
 // Output rows of the big tiles go past the caches where nobody will find them there: stored through them, each XCD's L2 is full of dirty
-// lines that wait to be written while the next kernel loads (us, through / past).  Linear with its quantisation, by bytes of y: 268 MB
-// 8192 x 7168 x 8192 476 / 445 (other inputs in each pass 489 / 483), 8192 x 2048 x 8192 191 / 181, with K = 1024 130.5 / 129.1 and 16384 x 1024 x 4096 113.9 / 115.6, 724 MB 12727
-// x 4864 x 14208 841 / 828; less than the last-level cache's 256 MB 197 MB 3000 x 2048 x 16384 113.4 / 113.8, 65 MB 2000 x 4096 x 8192 69.8 /
-// 70.8, others level.  Layers, whose combine comes at once and finds the last part: 805 MB 8192 x 6 of 64, 4096 x 1408 1102 / 1093, 1.3 GB
-// 8192 x 8 of 128, 5120 x 1536 1980 / 1956, 1.6 GB 16000 x 6 of 64, 4096 x 1024 1656 / 1617, 7.5 GB 32768 x 8 of 256, 7168 x 2048 13224 /
-// 13097; 671 MB 4096 x 8 of 128, 5120 x 1536 1095 / 1100, below level.
+// lines that wait to be written while the next kernel loads, and the last-level cache keeps outputs instead of inputs (us, through / past).
+// Linear with its quantisation, calls one behind another, nine states in turn (nothing is found in a cache): 268 MB of y 8192 x 7168 x 8192
+// 486 / 476, K = 4096 309 / 305, K = 2048 191 / 193, 302 MB 9216 x 7168 x 8192 562 / 552, 537 MB 16384 x 7168 x 8192 939 / 928, K = 2048
+// 366 / 367, 724 MB 12727 x 4864 x 14208 858 / 847; the same weights again 476 / 450, 305 / 285, 189 / 179, 557 / 528, 942 / 928, 354 /
+// 344, 851 / 842; everything again 481 / 445 and, K = 2048, 190 / 179.  One call alone on new inputs and buffers ends later, 470 / 481 and
+// 483 / 489, K = 2048 177 / 201, 9216 rows 552 / 552, 12727 rows 814 / 810: what the caches would have written behind its end has been
+// written in it.  256 MB is the last-level cache's size.  Below it the same buffers gain as well, 210 MB 3200 x 2048 x 16384 126 / 123,
+// K = 7168 356 / 347, 235 MB 7168 x 7168 x 8192 419 / 391, but 197 MB 3000 x 2048 x 16384 114.5 / 116.1; so do some with K = 1024, 393 MB 6000
+// x 1024 x 16384 153 / 147, 268 MB 16384 x 1024 x 4096 120 / 121.
+// Layers, whose combine comes at once and finds the last part, three states in turn: 805 MB 8192 x 6 of 64, 4096 x 1408 1133 / 1116, 1.3 GB
+// 8192 x 8 of 128, 5120 x 1536 2037 / 2007, 1.6 GB 16000 x 6 of 64, 4096 x 1024 1692 / 1659, 7.5 GB 32768 x 8 of 256, 7168 x 2048 13040 /
+// 12943, a call alone on new inputs and buffers 1 to 2 % shorter as well; 720 MB 5500 x 8 of 64, 4096 x 1024 817 / 812 (alone 843 / 847), 671 MB 4096 x 8 of 128, 5120 x 1536
+// 1150 / 1157, 402 MB 4096 x 6 of 64, 4096 x 1408 633 / 643.
 constexpr int64_t LINEAR_Y_PAST_BYTES = 256ll << 20, LAYER_Y_PAST_BYTES = 768ll << 20;
 constexpr int LINEAR_Y_PAST_MIN_K = 2048;
 inline bool y_bytes_at_least(int64_t rows, int32_t cols, int64_t bytes) { return rows * cols * (int64_t)sizeof(float) >= bytes; }
@@ -374,10 +381,10 @@ inline int64_t down_big_units(const moe_dims* D) {
 inline ListShape gate_up_shape(const moe_dims* D) { return {D->F / 128, D->d / QBLOCK, (int)gate_up_units(D), one_height(D)}; }
 inline ListShape down_shape(const moe_dims* D) { return {(D->d + 255) / 256, D->F / QBLOCK, (int)down_big_units(D), one_height(D)}; }
 
-// Dense linear, up to how many blocks of 32 features ffn_few.hip is the better kernel, one to a CU (streaming kernel = 1): 256 blocks, 16-row tiles 16 x 4096 x 8192
-// 0.71, 32-row 32 x 4096 x 8192 0.76, 64-row 40 x 4096 x 8192 0.85, 64 x 4096 x 8192 0.97, 128 x 7168 x 4096 0.94, 256 x 4096 x 2048
-// 0.83; 384 blocks of 16-row tiles (75 KB, two to a CU) 0.91..1.02, of 32-row tiles 1.2, 512 of 64-row tiles 1.5.  Tiles of 32 rows
-// while they fit too (128 x 4096 x 2048 0.62 against 0.83 in tiles of 64).
+// Dense linear, up to how many blocks of 32 features ffn_few.hip is the better kernel, one to a CU (streaming kernel = 1): 256 blocks,
+// 16-row tiles 16 x 4096 x 8192 0.71, 32-row 32 x 4096 x 8192 0.76, 64-row 40 x 4096 x 8192 0.85, 64 x 4096 x 8192 0.97, 128 x 7168 x 4096
+// 0.94, 256 x 4096 x 2048 0.83; 384 blocks of 16-row tiles (75 KB, two to a CU) 0.91..1.02, of 32-row tiles 1.2, 512 of 64-row tiles 1.5.
+// Tiles of 32 rows while they fit too (128 x 4096 x 2048 0.62 against 0.83 in tiles of 64).
 constexpr int FEW_BLOCKS = 256, FEW_BLOCKS_16 = 320;
 inline int few_linear_groups(int32_t rows, int32_t NOUT) {           // 16-row groups per tile; 0: another kernel is the better one
     const int64_t cols = NOUT / 32;

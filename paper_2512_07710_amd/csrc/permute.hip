@@ -93,10 +93,10 @@ __device__ inline void scan_chunks(int32_t* __restrict__ chunk_counts, int n_chu
 // count, kept per wave in LDS (read by the whole set, then written by one lane: LDS operations of a wave
 // execute in order).  A second pass turns the per-wave counts into the chunk histogram and the per-wave
 // bases.  Ids outside [0,E) are ranked among themselves; that rank is never used.
-// The last block to arrive (ticket.hpp) scans the histograms; nobody waits.  In a launch of its own the scan came behind the
-// tokens' quantisation that rides in this one (us, two launches / this: 8000 assignments of 64 experts 7.4 + 2.7 / 9.0, 12000 of 16 6.6 + 4.6 /
-// 8.8, 262144 of 256 11.6 + 20.2 / 28.4; layers of 1000 x 8 of 64, 1024 x 512 61.4 / 60.2, 6000 x 2 of 16, 3072 x 2048 337.0 / 334.8, 4096 x 8 of 128, 5120 x
-// 1536 1093 / 1091).
+// The last block to arrive (ticket.hpp) scans the histograms; nobody waits.  In a launch of its own the scan came behind the tokens' quantisation
+// that rides in this one (us, two launches / this: 8000 assignments of 64 experts 7.4 + 2.7 / 9.0, 12000 of 16 6.6 + 4.6 / 8.8, 262144 of 256 11.6 +
+// 20.2 / 28.4; layers of 1000 x 8 of 64, 1024 x 512 61.4 / 60.2, 6000 x 2 of 16, 3072 x 2048 337.0 / 334.8, 4096 x 8 of 128, 5120 x 1536 1093 /
+// 1091).
 __global__ __launch_bounds__(256) void chunk_hist_rank(const int32_t* __restrict__ ids, int N, int E,
                                                        int32_t* __restrict__ chunk_counts,
                                                        int32_t* __restrict__ rank_out,

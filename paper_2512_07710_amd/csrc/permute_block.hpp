@@ -8,11 +8,12 @@ namespace moe355 {
 // Up to one_block_max_n assignments: the three steps of permute.hip in one block and one launch, where the launches themselves are most of the
 // time.  Sixteen waves rank STEPS times 64 entries each in the manner of chunk_hist_rank, then scan over the experts and scatter
 // from registers; bound by its chain of barriers and memory round trips.
-// Whole calls in a row, us, this form / three launches (the scan in one of its own): replay of 2100 assignments k = 6 6.0 / 10.6, 4000 k = 2 7.2 / 10.3, k = 8 7.5 / 10.9,
-// 4096 k = 16 7.5 / 11.5, 4500 k = 6 10.8 / 11.2, 6000 11.9 / 11.2, 7800 14.1 / 11.5, 8000 k = 8 12.9 / 11.5, k = 16 13.3 / 12.0; layers of 750 x 6 of 32,
-// 1024 x 512 48.3 / 49.6, 1000 x 6 of 64, 4096 x 512 level, 1300 x 6 of 32, 3072 x 512 107.5 / 106.0.  Ids from the router itself, one slot a token: with the
-// router 23.4 / 25.7 at 4500, 25.5 / 27.0 at 8100 and level at 8096 with k = 8; replay of 8100 k = 1 11.6 / 11.2, a replayed layer of 4500 k = 1 55.2 /
-// 56.3.  (With repeats searched for by reading all earlier slots of a token, 350 x 6 7.6, 500 x 8 9.4, 256 x 16 11.9.)
+// Whole calls in a row, us, this form / the two launches: replay of 2100 assignments k = 6 6.3 / 9.9, 4000 k = 2 7.3 / 10.0, 4096 k = 8 7.6 / 10.1,
+// k = 16 7.7 / 10.9, 4500 k = 6 10.6 / 10.2, 4800 11.4 / 10.4, 5000 k = 2 10.0 / 10.0, 5120 k = 8 10.9 / 10.5, k = 16 10.6 / 11.1, 8100 k = 1 11.9 /
+// 10.1 (beyond the line, before the other form lost a launch: 6000 k = 6 11.9 / 11.2, 8000 k = 16 13.3 / 12.0); replayed layers of 512 x 8 of 64,
+// 2048 x 512 65.0 / 68.6, 750 x 6 of 32, 1024 x 512 48.5 / 48.2, 800 x 6 of 64, 4096 x 512 132.7 / 131.9, 640 x 8 of 128, 2048 x 768 145.4 / 145.8,
+// 320 x 16 of 64, 2048 x 512 74.1 / 74.7, 8100 x 1 of 16 85.4 / 85.3.  Ids from the router itself: layers of 750 x 6 55.0 / 56.7, 640 x 8 156.8 /
+// 158.1, 4500 x 1 of 32, 2048 x 512 89.3 / 92.4, 8100 x 1 105.7 / 107.4.
 constexpr int ONE_BLOCK_WAVES = 16;
 constexpr int ONE_BLOCK_MAX_STEPS = 8;
 

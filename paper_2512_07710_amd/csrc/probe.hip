@@ -28,8 +28,9 @@ __device__ inline uint32_t mix(uint32_t x) {
 }
 
 // One "step" is what a wave of a full tile does per 128-wide K block: 32 products of four weight tiles and eight token tiles, 16x16x128
-// each, in the GEMM's order: token tile by token tile, the weights forwards and backwards in turn.  SCALED: every product is folded into its accumulator by four fp32 multiply-adds a lane; bare: the matrix
-// instructions accumulate in place.  Operand registers hold random e4m3 bytes (never the NaN pattern); two token tiles share a set.
+// each, in the GEMM's order: token tile by token tile, the weights forwards and backwards in turn.  SCALED: every product is folded into
+// its accumulator by four fp32 multiply-adds a lane; bare: the matrix instructions accumulate in place.  Operand registers hold random e4m3
+// bytes (never the NaN pattern); two token tiles share a set.
 __device__ constexpr int weights_of(int m) { return m >> 2 > 0 && (m >> 2) % 2 == 0 ? 3 - (m & 3) : m & 3; }
 template <bool SCALED>
 __global__ __launch_bounds__(512, 1) void mfma_loop(int steps, float scale, float* __restrict__ sink) {

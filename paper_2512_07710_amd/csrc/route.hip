@@ -36,18 +36,18 @@ constexpr int NO_CAND = 0x7FFFFFFF;
 // split over up to ROUTE_MAX_SPLITS blocks per token tile: as many as bring the grid to about 256 blocks.
 constexpr int ROUTE_SPLIT_MAX_T = 4096;
 constexpr int ROUTE_MAX_SPLITS = 16;
-// With at most so many chunks of 128 columns to a block the waves split the fp32 weights themselves instead of reading planes that a launch
-// of its own has made.  Splitting weights and bits are the same; a load takes 64 bytes of 32 rows where the planes lie as they are wanted, so long K loops are
-// slower (us, router launches with planes / this: 2 chunks, 256 tokens x 64 experts x 4096 11.0 / 6.3, 4 chunks, 1000 x 64 x 4096 13.1 / 10.0 and 128
-// x 256 x 7168 23.1 / 20.4; 7 chunks, 1000 x 256 x 7168 32.1 / 34.8, 20 chunks, 4096 x 128 x 5120 40.8 / 57.6, also with the splitting put between the
-// dependent products).
+// With at most so many chunks of 128 columns to a block the waves split the fp32 weights themselves instead of reading planes that a launch of its
+// own has made.  Splitting weights and bits are the same; a load takes 64 bytes of 32 rows where the planes lie as they are wanted, so long K loops
+// are slower (us, router launches with planes / this: 2 chunks, 256 tokens x 64 experts x 4096 11.0 / 6.3, 4 chunks, 1000 x 64 x 4096 13.1 / 10.0 and
+// 128 x 256 x 7168 23.1 / 20.4; 7 chunks, 1000 x 256 x 7168 32.1 / 34.8, 20 chunks, 4096 x 128 x 5120 40.8 / 57.6, also with the splitting put
+// between the dependent products).
 constexpr int ROUTE_RAW_CHUNKS = 4;
 // Every token tile splits all weights again.  With more than 128 experts, two sub-tiles a wave, that is the slower form once chunks x tiles x experts
-// exceed ROUTE_RAW_WORK (whole router calls, us, planes / this, weights in the caches and cleared caches, by chunks x tiles; 256 experts: 4 x 17, 7168 columns
-// 41.6 / 36.8 and 48.4 / 43.9, 2 x 32, 2048 34.0 / 33.1 and 37.9 / 38.1, 3 x 25, 3584 36.0 / 35.1 and 41.3 / 41.5; 3 x 32, 2560 35.3 / 36.6 and 39.7 / 42.6,
-// 4 x 47, 2048 39.8 / 42.4 and 44.8 / 48.6, 4 x 94, 1024 40.7 / 44.5 and 45.5 / 50.2; 192: 4 x 32, 4096 35.9 / 35.6 and 42.2 / 41.8, 4 x 64, 2048 37.6 / 39.3
-// and 42.7 / 45.4).  Up to 128 experts it stays ahead or level: 4 x 44, 2048 31.5 / 29.9 and 35.8 / 35.2, 4 x 94, 1024 32.7 / 33.0 and
-// 37.7 / 38.5, 4 x 128, 1024 35.2 / 33.2 and 40.0 / 39.4.
+// exceed ROUTE_RAW_WORK (whole router calls, us, planes / this, weights in the caches and cleared caches, by chunks x tiles; 256 experts: 4 x 17,
+// 7168 columns 41.6 / 36.8 and 48.4 / 43.9, 2 x 32, 2048 34.0 / 33.1 and 37.9 / 38.1, 3 x 25, 3584 36.0 / 35.1 and 41.3 / 41.5; 3 x 32, 2560 35.3 /
+// 36.6 and 39.7 / 42.6, 4 x 47, 2048 39.8 / 42.4 and 44.8 / 48.6, 4 x 94, 1024 40.7 / 44.5 and 45.5 / 50.2; 192: 4 x 32, 4096 35.9 / 35.6 and 42.2 /
+// 41.8, 4 x 64, 2048 37.6 / 39.3 and 42.7 / 45.4).  Up to 128 experts it stays ahead or level: 4 x 44, 2048 31.5 / 29.9 and 35.8 / 35.2, 4 x 94, 1024
+// 32.7 / 33.0 and 37.7 / 38.5, 4 x 128, 1024 35.2 / 33.2 and 40.0 / 39.4.
 constexpr int ROUTE_RAW_WORK = 20480;
 inline bool route_splits_weights(int E, int tiles, int chunks) {
     return chunks <= ROUTE_RAW_CHUNKS && (E <= 128 || chunks * tiles * E <= ROUTE_RAW_WORK);
@@ -736,11 +736,11 @@ __global__ __launch_bounds__(ONE_BLOCK_WAVES * 64) void route_finish_permute(
     permute_block<1>([&](int i) { return s_ids[i]; }, T * k, E, nullptr, nullptr, nullptr, offsets, perm, inv_perm, k, IDS, flags);
 }
 
-// All of it in one launch for at most a token to each wave of a block: the scores, as in route_rows_kernel, each put where all XCDs see
-// it; the last of the scoring blocks to arrive (ticket.hpp) selects and permutes, and nobody waits.  The tokens'
-// quantisation may come along in further blocks.  Bound by its chain of memory round trips.  One token x 64 experts x 4096, us: the two launches
-// before 3.1 + 7.1, this 8.8; one token x 8 experts x 1024 2.7 + 6.0 and 7.2.  Beyond TINY_BLOCKS scoring blocks their tickets come one behind another
-// (layers, us, two launches / this: 2 blocks 25.8 / 21.8, 48 37.8 / 37.3, 64 36.1 / 35.0, 128 63.5 / 63.5, 448 35.7 / 38.8 and 101.3 / 104.9).
+// All of it in one launch for at most a token to each wave of a block: the scores, as in route_rows_kernel, each put where all XCDs see it; the last
+// of the scoring blocks to arrive (ticket.hpp) selects and permutes, and nobody waits.  The tokens' quantisation may come along in further blocks.
+// Bound by its chain of memory round trips.  One token x 64 experts x 4096, us: the two launches before 3.1 + 7.1, this 8.8; one token x 8 experts x
+// 1024 2.7 + 6.0 and 7.2.  Beyond TINY_BLOCKS scoring blocks their tickets come one behind another (layers, us, two launches / this: 2 blocks 25.8 /
+// 21.8, 48 37.8 / 37.3, 64 36.1 / 35.0, 128 63.5 / 63.5, 448 35.7 / 38.8 and 101.3 / 104.9).
 constexpr int TINY_WAVES = 4, TINY_BLOCKS = 64;
 template <bool IDS>
 __global__ __launch_bounds__(TINY_WAVES * 64) void route_tiny(

@@ -5,9 +5,9 @@
 
 namespace moe355 {
 
-// A ticket is one wrapping increment and always of the same n, so any number of whole launches leaves it at zero.  That holds for launches that overlapped
-// as well, which a context does not allow: what they computed is undefined, but the calls behind them find their last block again.  (An add, with
-// the last block's store of zero behind it, lost the arrivals between the two, and no later launch on the ticket had a last block.)
+// A ticket is one wrapping increment and always of the same n, so any number of whole launches leaves it at zero.  That holds for launches that
+// overlapped as well, which a context does not allow: what they computed is undefined, but the calls behind them find their last block again.  (An
+// add, with the last block's store of zero behind it, lost the arrivals between the two, and no later launch on the ticket had a last block.)
 template <class Count>             // increment(limit): the value before; from `limit` the count goes to zero
 __host__ __device__ inline bool last_to_arrive(const Count& count, int n) { return count.increment(n - 1) == n - 1; }
 

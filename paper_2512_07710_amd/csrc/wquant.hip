@@ -7,10 +7,10 @@
 // and scales are reproducible bit for bit.  Each element is read once and written once: 3 bytes of HBM traffic per weight,
 // which bound the kernel.  Neither the weights nor the codes are touched again soon: both go past the caches.
 //
-// 196608 x 5120 weights: 690 us (4.4 TB/s) with 64 contiguous elements per thread and true divisions; 571 with 256 threads
-// in this arrangement and the shorter quotient, 532 with non-temporal loads and stores, 521 (5.8 TB/s) with 512 threads, 501 (6.0) in pairs.  Pairs on
-// 512 threads 504, on 256 510, four blocks on 1024 565; loads through the caches 519, stores 527; an eighth of the matrix to each XCD 504; fewer
-// workgroups to a CU 505 to 630.
+// 196608 x 5120 weights: 690 us (4.4 TB/s) with 64 contiguous elements per thread and true divisions; 571 with 256 threads in this arrangement and
+// the shorter quotient, 532 with non-temporal loads and stores, 521 (5.8 TB/s) with 512 threads, 501 (6.0) in pairs.  Pairs on 512 threads 504, on
+// 256 510, four blocks on 1024 565; loads through the caches 519, stores 527; an eighth of the matrix to each XCD 504; fewer workgroups to a CU 505
+// to 630.
 #include "e4m3.hpp"
 #include "moe_internal.hpp"
 
@@ -52,9 +52,9 @@ __global__ __launch_bounds__(512 * B) void quantize_blocks_kernel(const uint16_t
 
 }  // namespace
 
-// Pairs, where a row is a whole number of them and the matrix is more than the last-level cache holds (us, single blocks / pairs): 262144 x 7168
-// 975 / 922, 262144 x 1536 203 / 194, 131072 x 3072 201 / 195, 32768 x 4096 (256 MB of weights) 65.8 / 64.5; 16384 x 4096 33.4 / 33.6, 8192 x 4096 18.0 / 18.2;
-// rows that end in half a pair, whose pieces are then not aligned to their size, 32768 x 7040 104.7 / 110.9, 131072 x 2944 177.7 / 186.5.
+// Pairs, where a row is a whole number of them and the matrix is more than the last-level cache holds (us, single blocks / pairs): 262144 x 7168 975
+// / 922, 262144 x 1536 203 / 194, 131072 x 3072 201 / 195, 32768 x 4096 (256 MB of weights) 65.8 / 64.5; 16384 x 4096 33.4 / 33.6, 8192 x 4096 18.0 /
+// 18.2; rows that end in half a pair, whose pieces are then not aligned to their size, 32768 x 7040 104.7 / 110.9, 131072 x 2944 177.7 / 186.5.
 static constexpr int64_t PAIRS_FROM_BYTES = 256ll << 20;
 
 hipError_t launch_quantize_weights(hipStream_t s, const uint16_t* w, int64_t rows, int32_t cols, uint8_t* q,

@@ -91,7 +91,8 @@ def test_values_and_ids_that_are_not_valid(gpu_lib):
         assert N == T * k - 6 and gpu_lib.moe_check_ids(big.ctx) != 0
         for fused in (True, False):
             layer.y_perm.zero_()
-            y = layer.forward_replay(x[:T].contiguous(), ids[:T].contiguous(), gates[:T].contiguous(), {n: v[:E].contiguous() for n, v in w.items()}, fused=fused)
+            y = layer.forward_replay(x[:T].contiguous(), ids[:T].contiguous(), gates[:T].contiguous(),
+                                     {n: v[:E].contiguous() for n, v in w.items()}, fused=fused)
             assert gpu_lib.moe_check_ids(layer.ctx) != 0
             hq, hs = layer.hidden()
             assert torch.equal(layer.offsets, big.offsets[:E + 1])

@@ -44,9 +44,11 @@ def test_the_search_finds_what_it_is_for():
     mfma = "\tv_mfma_f32_32x32x16_bf16 a[0:15], v[96:99], v[4:7], a[0:15]\n"
     write = "\tv_cvt_pk_bf16_f32 v99, v1, v2\n"
     waits = [short_waits("k:\n" + write + between + mfma)[0] != [] for between in
-             ("", "\ts_cmp_ge_i32 s0, s1\n", "\ts_nop 0\n", "\ts_nop 1\n", "\tv_mov_b32_e32 v1, v2\n\ts_cmp_ge_i32 s0, s1\n", "\tds_read_b128 v[8:11], v3\n\ts_nop 0\n")]
+             ("", "\ts_cmp_ge_i32 s0, s1\n", "\ts_nop 0\n", "\ts_nop 1\n", "\tv_mov_b32_e32 v1, v2\n\ts_cmp_ge_i32 s0, s1\n",
+              "\tds_read_b128 v[8:11], v3\n\ts_nop 0\n")]
     assert waits == [True, True, True, False, False, False]
-    assert short_waits("k:\n\tv_accvgpr_write_b32 a3, 0\n" + mfma)[0] and not short_waits("k:\n\tglobal_load_dwordx4 v[96:99], v[0:1], off\n" + mfma)[0]
+    assert short_waits("k:\n\tv_accvgpr_write_b32 a3, 0\n" + mfma)[0]
+    assert not short_waits("k:\n\tglobal_load_dwordx4 v[96:99], v[0:1], off\n" + mfma)[0]
 
 
 @pytest.mark.parametrize("source", ["route.hip", "ffn.hip", "probe.hip"])
