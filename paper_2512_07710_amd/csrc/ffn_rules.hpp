@@ -331,8 +331,8 @@ inline bool linear_streams(int32_t rows, int32_t NOUT) {
 // x 1024 x 16384 153 / 147, 268 MB 16384 x 1024 x 4096 120 / 121.
 // Layers, whose combine comes at once and finds the last part, three states in turn: 805 MB 8192 x 6 of 64, 4096 x 1408 1133 / 1116, 1.3 GB
 // 8192 x 8 of 128, 5120 x 1536 2037 / 2007, 1.6 GB 16000 x 6 of 64, 4096 x 1024 1692 / 1659, 7.5 GB 32768 x 8 of 256, 7168 x 2048 13040 /
-// 12943, a call alone on new inputs and buffers 1 to 2 % shorter as well; 720 MB 5500 x 8 of 64, 4096 x 1024 817 / 812 (alone 843 / 847), 671 MB 4096 x 8 of 128, 5120 x 1536
-// 1150 / 1157, 402 MB 4096 x 6 of 64, 4096 x 1408 633 / 643.
+// 12943, a call alone on new inputs and buffers 1 to 2 % shorter as well; 720 MB 5500 x 8 of 64, 4096 x 1024 817 / 812 (alone 843 / 847),
+// 671 MB 4096 x 8 of 128, 5120 x 1536 1150 / 1157, 402 MB 4096 x 6 of 64, 4096 x 1408 633 / 643.
 constexpr int64_t LINEAR_Y_PAST_BYTES = 256ll << 20, LAYER_Y_PAST_BYTES = 768ll << 20;
 constexpr int LINEAR_Y_PAST_MIN_K = 2048;
 inline bool y_bytes_at_least(int64_t rows, int32_t cols, int64_t bytes) { return rows * cols * (int64_t)sizeof(float) >= bytes; }
